@@ -221,6 +221,7 @@ int fftconv_plan_destroy(fftconv_plan *p)
     staged_destroy(p);
     long_fft_destroy(p);
     if (p->keep_dev) (void)hipFree(p->keep_dev);
+    if (p->row_tw) (void)hipFree(p->row_tw);
     delete p;
     return FFTCONV_OK;
 }
@@ -305,7 +306,7 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         if (rc) return rc;
         switch (p->path) {
         case PATH_MULTIPASS: rc = multipass_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
-        case PATH_SMALL: rc = small_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
+        case PATH_SMALL: rc = row_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
         default: rc = staged_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
         }
         if (rc) return rc;
@@ -440,7 +441,7 @@ int fftconv_forward(const fftconv_plan *p, const void *u, const void *k_f, void 
     case PATH_MULTIPASS:
         return multipass_forward(p, u, k_f, y, B, workspace, s);
     case PATH_SMALL:
-        return small_forward(p, u, k_f, y, B, s);
+        return row_forward(p, u, k_f, y, B, s);
     default:
         return staged_forward(p, u, k_f, y, B, workspace, s);
     }

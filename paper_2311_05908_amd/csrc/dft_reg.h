@@ -24,8 +24,11 @@ constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
 // In-register DFT of length R (power of two <= 32), natural order in and out, unnormalised;
 // INV conjugates the kernel.  Radix-2 decimation in time, fully unrolled so every index and
-// twiddle is a compile-time constant.
-template <int R, bool INV> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
+// twiddle is a compile-time constant.  A butterfly with a twiddle is six fused operations: the sum a + w b
+// as two chained multiply-adds per part, the difference as 2 a - (a + w b); those with w = 1 or -+i are
+// four additions.  HALFIN: the inputs x[R/2 ..] are zero (the padding of a causal convolution) and are not
+// read; the first level of butterflies then only copies.
+template <int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
 {
     constexpr int LG = ilog2(R);
 #pragma unroll
@@ -37,26 +40,30 @@ template <int R, bool INV> __device__ __forceinline__ void dft_reg(float2 (&x)[R
             x[j] = t;
         }
     }
+    if constexpr (HALFIN && R >= 2) {
 #pragma unroll
-    for (int len = 2; len <= R; len *= 2) {
+        for (int blk = 0; blk < R; blk += 2) x[blk + 1] = x[blk];
+    }
+#pragma unroll
+    for (int len = HALFIN ? 4 : 2; len <= R; len *= 2) {
 #pragma unroll
         for (int blk = 0; blk < R; blk += len) {
 #pragma unroll
             for (int j = 0; j < len / 2; ++j) {
                 const int q = j * (32 / len);                  // twiddle W_32^q, 0 <= q < 16
                 const float2 a = x[blk + j], b = x[blk + j + len / 2];
-                float2 t;
-                if (q == 0) {
-                    t = b;
-                } else if (q == 8) {                           // -i forward, +i inverse
-                    t = INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x);
+                if (q == 0 || q == 8) {                        // 1; -i forward, +i inverse
+                    const float2 t = q == 0 ? b : INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x);
+                    x[blk + j] = make_float2(a.x + t.x, a.y + t.y);
+                    x[blk + j + len / 2] = make_float2(a.x - t.x, a.y - t.y);
                 } else {
                     const float wr = C32[q];
                     const float wi = INV ? S32[q] : -S32[q];
-                    t = make_float2(b.x * wr - b.y * wi, b.x * wi + b.y * wr);
+                    const float sx = __builtin_fmaf(-b.y, wi, __builtin_fmaf(b.x, wr, a.x));
+                    const float sy = __builtin_fmaf(b.y, wr, __builtin_fmaf(b.x, wi, a.y));
+                    x[blk + j] = make_float2(sx, sy);
+                    x[blk + j + len / 2] = make_float2(__builtin_fmaf(2.f, a.x, -sx), __builtin_fmaf(2.f, a.y, -sy));
                 }
-                x[blk + j] = make_float2(a.x + t.x, a.y + t.y);
-                x[blk + j + len / 2] = make_float2(a.x - t.x, a.y - t.y);
             }
         }
     }

@@ -126,6 +126,7 @@ struct fftconv_plan {
     int64_t filt_chunk = 0;           // channels per pass through the scratch
     uint8_t *keep_dev = nullptr;      // device copy of a frequency-block mask (sparse filter transform)
     float2 *long_tw = nullptr;        // twiddle tables of the two-kernel long transforms (long_fft.hip)
+    float2 *row_tw = nullptr;         // twiddle table of the fp32 row kernels (row_fft.h)
 };
 
 namespace fftconv {
@@ -262,14 +263,16 @@ int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *d
 int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, void *tmp, float *dk, int64_t Nk, hipStream_t s);
 }  // namespace f3
 
-// ---- short transforms, fft_size 256 .. 4096, any dtype (small.hip); radices reported in f3.N1..N3
+// ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle table, k_f layout, the convolution
+int row_tables_init(fftconv_plan *p, int64_t M);
+int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
+                void *kf, hipStream_t s);
+int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
+// short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);
 FacList small_factor_list(int64_t M);      // its radices, outermost first
 int small_init(fftconv_plan *p);
 size_t small_kf_bytes(const fftconv_plan *p);
-int small_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev,
-                  int64_t n_blocks, void *kf, hipStream_t s);
-int small_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
 
 // ---- the per-GPU static workspace of fftconv_forward_static (multipass.hip)
 int static_workspace_init(int device);     // once per device, with that device current (plan creation)

@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
                 if (a < RAIN)                                        // (row b, row b+1) = (re, im)
                     x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
             }
-            dft_reg<RA, false>(x);
+            dft_reg<RA, false, !FULLN>(x);
 #pragma unroll
             for (int ka = 0; ka < RA; ++ka) o[ka][v] = cmulf(x[ka], wno[ka * b2]);
         }
@@ -516,7 +516,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
                 x[a] = unpack2<F16>(wd[a]);        // (column c, column c+1) = (re, im)
             }
         }
-        dft_reg<RA, false>(x);
+        dft_reg<RA, false, !FULLN>(x);
 #pragma unroll
         for (int ka = 0; ka < RA; ++ka) T[(ka * RB + b2) * CG + cg] = cmulf(x[ka], wno[ka * b2]);
     }
@@ -722,7 +722,7 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restr
             if (n >= Nk) x[a].x = 0.f;
             if (n + 1 >= Nk) x[a].y = 0.f;
         }
-        dft_reg<RA, false>(x);
+        dft_reg<RA, false, !FULLN>(x);
 #pragma unroll
         for (int ka = 0; ka < RA; ++ka) T[(ka * RB + b2) * CG + cg] = cmulf(x[ka], wno[ka * b2]);
     }

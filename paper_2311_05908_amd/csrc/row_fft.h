@@ -1,0 +1,272 @@
+// fp32 transforms of whole rows of M = 256 .. 16384 complex points, two or three passes of in-register
+// butterflies (dft_reg.h) with one exchange through LDS between passes: the engine of the kernels that compute
+// in fp32 (short and fp32 convolutions, filter transforms, filter gradients).
+//
+// M = R0 R1 R2 (R2 = 1: two passes).  T = M / R0 threads hold a row, R0 points each; time n = j + (M / R0) m:
+//   pass 0: thread j < T transforms m (radix R0, stride T) straight from where its caller loaded the samples,
+//           times W_M^{j k0};
+//   pass 1: in every block k0 of L1 = T positions, radix R1 at stride S1 = L1 / R1, times W_L1^{j1 k1}, j1 < S1;
+//   pass 2: radix R2 over adjacent positions, no twiddles.
+// The last pass leaves frequency f = k0 + R0 k1 + R0 R1 k2 in registers (freq() below names it), where the caller
+// multiplies, stores or accumulates; the inverse runs the mirrored passes (conjugate twiddles before the
+// butterflies) and returns sample j + T m in x[m].  A complete convolution therefore makes four trips through LDS
+// (two with two passes) and touches every sample and every bin once in registers.  Every position is written by
+// the thread that read it last, so one barrier per exchange suffices; rows of up to 64 threads live inside one wave
+// and need none (LDS operations of a wave complete in order).
+//
+// What bounds these kernels is the vector ALU (about 110 operations per point and convolution at M = 8192), so
+//  * radices 32 and 16 (fewest twiddle products and exchanges that 64 data registers allow);
+//  * the R - 1 twiddles of a butterfly are products of those for 1, 2, 3 and the multiples of 4, which come from
+//    tables in thread order, [factor][thread] (a full table would save 4 of 8 operations on half of the points
+//    and cost an 8-byte load each; gathers from a table of W_M^t, one cache line per lane, bounded the kernels
+//    that this file replaces).  Each is exact to its own rounding, a product adds one more.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <vector>
+
+#include "dft_reg.h"
+#include "fused3_common.h"
+
+namespace fftconv {
+namespace rf {
+
+template <int M> struct Radix;
+template <> struct Radix<256> { static constexpr int R0 = 16, R1 = 16, R2 = 1; };
+template <> struct Radix<512> { static constexpr int R0 = 32, R1 = 16, R2 = 1; };
+template <> struct Radix<1024> { static constexpr int R0 = 32, R1 = 32, R2 = 1; };
+template <> struct Radix<2048> { static constexpr int R0 = 16, R1 = 16, R2 = 8; };
+template <> struct Radix<4096> { static constexpr int R0 = 16, R1 = 16, R2 = 16; };
+template <> struct Radix<8192> { static constexpr int R0 = 32, R1 = 16, R2 = 16; };
+template <> struct Radix<16384> { static constexpr int R0 = 32, R1 = 32, R2 = 16; };
+
+// number of twiddles of a radix-R pass that come from the table: 1, 2, 3, 4, 8, 12, ..
+constexpr int tw_count(int R) { return R / 4 + 2; }
+constexpr int tw_power(int i) { return i < 3 ? i + 1 : 4 * (i - 2); }
+
+template <int M_> struct Row {
+    static constexpr int M = M_;
+    static constexpr int R0 = Radix<M>::R0, R1 = Radix<M>::R1, R2 = Radix<M>::R2;
+    static constexpr int P = R0;                           // points per thread
+    static constexpr int T = M / R0;                       // threads per row
+    static constexpr bool THREE = R2 > 1;
+    static constexpr int RL = THREE ? R2 : R1;             // radix of the last pass
+    static constexpr int S1 = R2;                          // stride of pass 1 (three passes)
+    static constexpr int NB1 = P / R1, NBL = P / RL;       // butterflies per thread of pass 1, of the last pass
+    static constexpr int TW0 = tw_count(R0), TW1 = THREE ? tw_count(R1) : 0;
+    static constexpr int TABLE = TW0 * T + (THREE ? TW1 * S1 : 0);         // entries of the twiddle table
+    // LDS slot of position blk * T + sub * RL + r (r < RL, sub < T / RL): one word pair of padding per RL positions
+    // spreads the last pass (lanes RL positions apart) over the banks; where blocks of T positions would still start
+    // at the same bank, 16 more per block.
+    static constexpr int PAD = RL + 1;                     // distance of two runs of RL positions
+    static constexpr int PITCH = T / RL * PAD + ((THREE && (T / RL * PAD * 2) % 64 == 0) ? 16 : 0);   // ... of two blocks
+    // rows of up to 64 threads: real and imaginary parts go through LDS one after the other, in half the space
+    static constexpr bool SPLIT = !THREE && T <= 64;
+    static constexpr int SLOTS = R0 * PITCH + (SPLIT && R0 * PITCH % 64 == 32 && T == 16 ? 16 : 0);
+    static constexpr int LDS_BYTES = SLOTS * (SPLIT ? 4 : 8);
+    static_assert(T % RL == 0, "blocks hold whole runs");
+    static __device__ __forceinline__ int slot0(int j) { return j / RL * PAD + j % RL; }              // position j < T
+    // first slot of butterfly bi of pass 1 (its points are PAD slots apart) and of the last pass (adjacent slots)
+    static __device__ __forceinline__ int slot1(int bi) { return bi / S1 * PITCH + bi % S1; }
+    static __device__ __forceinline__ int slotl(int bi) { return bi / (T / RL) * PITCH + bi % (T / RL) * PAD; }
+    // frequency held in register p = i * RL + r after forward() (butterfly i of the last pass, digit r)
+    static __host__ __device__ __forceinline__ int freq(int tid, int p)
+    {
+        const int bi = tid + T * (p / RL), r = p % RL;
+        if constexpr (THREE) return bi / R1 + R0 * (bi % R1) + R0 * R1 * r;
+        else return bi + R0 * r;
+    }
+};
+
+__device__ __forceinline__ float2 mul(float2 a, float2 b)
+{
+    return make_float2(__builtin_fmaf(-a.y, b.y, a.x * b.x), __builtin_fmaf(a.y, b.x, a.x * b.y));
+}
+__device__ __forceinline__ float2 mul_conj(float2 a, float2 b)     // a * conj(b)
+{
+    return make_float2(__builtin_fmaf(a.y, b.y, a.x * b.x), __builtin_fmaf(a.y, b.x, -(a.x * b.y)));
+}
+
+// x[k] *= W^k (CONJ: its conjugate), k < R, from the tw_count(R) table entries t
+template <int R, bool CONJ> __device__ __forceinline__ void twiddle(float2 (&x)[R], const float2 (&t)[tw_count(R)])
+{
+#pragma unroll
+    for (int k = 1; k < R; ++k) {
+        const int a = k / 4, b = k % 4;
+        const float2 w = a == 0 ? t[b - 1] : b == 0 ? t[a + 2] : mul(t[a + 2], t[b - 1]);
+        x[k] = CONJ ? mul_conj(x[k], w) : mul(x[k], w);
+    }
+}
+
+// The exchanges of a row whose threads span several waves meet at a workgroup barrier; a row inside one wave
+// only has to keep the compiler from moving LDS accesses across.
+template <int T> __device__ __forceinline__ void row_barrier()
+{
+    if constexpr (T > 64) f3::lds_barrier();
+    else asm volatile("" ::: "memory");
+}
+
+// The twiddles of pass 1, the same for every butterfly of a thread (its position inside a block does not change).
+template <typename G> struct Tw1 {
+    float2 t[G::THREE ? G::TW1 : 1];
+    __device__ __forceinline__ void load(const float2 *__restrict__ tab, int tid)
+    {
+        if constexpr (G::THREE) {
+#pragma unroll
+            for (int i = 0; i < G::TW1; ++i) t[i] = tab[G::TW0 * G::T + i * G::S1 + tid % G::S1];
+        }
+    }
+};
+template <typename G> __device__ __forceinline__ void load_tw0(float2 (&t)[G::TW0], const float2 *__restrict__ tab, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < G::TW0; ++i) t[i] = tab[i * G::T + tid];
+}
+
+// The exchange of a two-pass row inside one wave: x[k] of column tid <-> x[i * RL + r] of the butterflies of the last pass
+// (FWD: first to last pass), one part at a time.
+template <typename G, bool FWD> __device__ __forceinline__ void exchange(float2 (&x)[G::P], float *Z, int tid)
+{
+    float *const z0 = Z + G::slot0(tid);
+    auto at = [&](int p) { return Z + G::slotl(tid + G::T * (p / G::RL)) + p % G::RL; };
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) *(FWD ? z0 + p * G::PITCH : at(p)) = part ? x[p].y : x[p].x;
+        row_barrier<G::T>();
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) (part ? x[p].y : x[p].x) = *(FWD ? at(p) : z0 + p * G::PITCH);
+        row_barrier<G::T>();
+    }
+}
+
+// Forward transform of the row whose samples j + T m the thread j = tid holds in x[m]; Z: the row's Row<M>::SLOTS
+// slots of LDS, free (the caller's barrier lies before).  HALF: x[m] = 0 for m >= R0 / 2.  On return x[p] holds
+// frequency freq(tid, p).  before_last() runs ahead of the last pass (loads that whoever uses the result needs).
+template <typename G, bool HALF, typename F>
+__device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const float2 *__restrict__ tab, const Tw1<G> &tw1, int tid,
+                                        F before_last)
+{
+    {
+        float2 t[G::TW0];
+        load_tw0<G>(t, tab, tid);
+        dft_reg<G::R0, false, HALF>(x);
+        twiddle<G::R0, false>(x, t);
+    }
+    if constexpr (G::SPLIT) {
+        before_last();
+        exchange<G, true>(x, (float *)Z, tid);
+#pragma unroll
+        for (int i = 0; i < G::NBL; ++i) {
+            float2 v[G::RL];
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
+            dft_reg<G::RL, false>(v);
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
+        }
+        return;
+    }
+    float2 *const z0 = Z + G::slot0(tid);
+#pragma unroll
+    for (int k = 0; k < G::R0; ++k) z0[k * G::PITCH] = x[k];
+    row_barrier<G::T>();
+    if constexpr (G::THREE) {
+#pragma unroll
+        for (int i = 0; i < G::NB1; ++i) {
+            float2 *const z = Z + G::slot1(tid + G::T * i);
+            float2 v[G::R1];
+#pragma unroll
+            for (int m = 0; m < G::R1; ++m) v[m] = z[m * G::PAD];
+            dft_reg<G::R1, false>(v);
+            twiddle<G::R1, false>(v, tw1.t);
+#pragma unroll
+            for (int k = 0; k < G::R1; ++k) z[k * G::PAD] = v[k];
+        }
+        before_last();
+        row_barrier<G::T>();
+    } else {
+        before_last();
+    }
+#pragma unroll
+    for (int i = 0; i < G::NBL; ++i) {
+        float2 *const z = Z + G::slotl(tid + G::T * i);
+        float2 v[G::RL];
+#pragma unroll
+        for (int r = 0; r < G::RL; ++r) v[r] = z[r];
+        dft_reg<G::RL, false>(v);
+#pragma unroll
+        for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
+    }
+}
+
+// Unnormalised inverse of forward(), in the slots that forward() left (no barrier needed between the two).
+template <typename G>
+__device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const float2 *__restrict__ tab, const Tw1<G> &tw1, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < G::NBL; ++i) {
+        float2 v[G::RL];
+#pragma unroll
+        for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
+        dft_reg<G::RL, true>(v);
+        if constexpr (G::SPLIT) {
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
+        } else {
+            float2 *const z = Z + G::slotl(tid + G::T * i);
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) z[r] = v[r];
+        }
+    }
+    if constexpr (G::SPLIT) {
+        exchange<G, false>(x, (float *)Z, tid);
+        float2 t[G::TW0];
+        load_tw0<G>(t, tab, tid);
+        twiddle<G::R0, true>(x, t);
+        dft_reg<G::R0, true>(x);
+        return;
+    }
+    row_barrier<G::T>();
+    if constexpr (G::THREE) {
+#pragma unroll
+        for (int i = 0; i < G::NB1; ++i) {
+            float2 *const z = Z + G::slot1(tid + G::T * i);
+            float2 v[G::R1];
+#pragma unroll
+            for (int k = 0; k < G::R1; ++k) v[k] = z[k * G::PAD];
+            twiddle<G::R1, true>(v, tw1.t);
+            dft_reg<G::R1, true>(v);
+#pragma unroll
+            for (int m = 0; m < G::R1; ++m) z[m * G::PAD] = v[m];
+        }
+        row_barrier<G::T>();
+    }
+    float2 t[G::TW0];
+    load_tw0<G>(t, tab, tid);
+    const float2 *const z0 = Z + G::slot0(tid);
+#pragma unroll
+    for (int k = 0; k < G::R0; ++k) x[k] = z0[k * G::PITCH];
+    twiddle<G::R0, true>(x, t);
+    dft_reg<G::R0, true>(x);
+}
+
+// Host side: the twiddle table of Row<M>, in fp64 and rounded once.
+template <typename G> inline void fill_table(float2 *tab)
+{
+    const double two_pi = 6.283185307179586476925286766559;
+    auto wpow = [&](double num, double den) {
+        const double a = two_pi * num / den;
+        return make_float2((float)std::cos(a), (float)-std::sin(a));
+    };
+    for (int i = 0; i < G::TW0; ++i)
+        for (int j = 0; j < G::T; ++j) tab[i * G::T + j] = wpow((double)tw_power(i) * j, (double)G::M);
+    if (G::THREE)
+        for (int i = 0; i < G::TW1; ++i)
+            for (int j = 0; j < G::S1; ++j) tab[G::TW0 * G::T + i * G::S1 + j] = wpow((double)tw_power(i) * j, (double)G::T);
+}
+
+}  // namespace rf
+}  // namespace fftconv
