@@ -359,43 +359,11 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_dk(const float2 *__restric
     }
 }
 
-// ---- The convolution itself in fp32 (plans with fp32 I/O from fft_size 8192 up): y = iFFT(FFT(pad(u)) . k_f)[0:N]
-// with k_f as fp32 pairs in position order, already scaled by 1 / fft_size.  Two batch rows share a complex
-// transform (re = row b, im = row b + 1; k is real, so the two convolutions come back as re and im).
+// ---- The convolution itself in fp32 (plans with fp32 I/O from fft_size 32768 up; shorter rows: row_conv.hip):
+// y = iFFT(FFT(pad(u)) . k_f)[0:N] with k_f as fp32 pairs in position order, already scaled by 1 / fft_size.  Two batch
+// rows share a complex transform (re = row b, im = row b + 1; k is real, so the two convolutions come back as re and im).
 //
-// Rows that fit in LDS (fft_size <= 16384): one workgroup per (pair, channel) does everything.
-template <typename IO>
-__global__ void __launch_bounds__(LT) k_rows_conv_lds(const IO *__restrict__ u, const float2 *__restrict__ kf,
-                                                     IO *__restrict__ y, const float2 *__restrict__ w, FacList fl, int M,
-                                                     int64_t N, int B, int H)
-{
-    extern __shared__ float2 XL[];
-    const int h = blockIdx.x, b0 = 2 * blockIdx.y;
-    const bool two = b0 + 1 < B;
-    const int64_t r0 = ((int64_t)b0 * H + h) * N, r1 = r0 + (int64_t)H * N;
-    // (a sample beyond N, or of a missing second row, reads a valid one and is discarded: unconditional loads,
-    //  several in flight per thread)
-    const int64_t r1e = two ? r1 : r0;
-#pragma unroll 8
-    for (int n = threadIdx.x; n < M; n += LT) {
-        const int64_t at = n < N ? n : 0;
-        const float a = ld_real(u, r0 + at), b = ld_real(u, r1e + at);
-        XL[lds_slot(n)] = n < N ? make_float2(a, two ? b : 0.f) : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    lds_forward(XL, w, fl, M, 1);
-#pragma unroll 8
-    for (int i = threadIdx.x; i < M; i += LT) XL[lds_slot(i)] = cmul(XL[lds_slot(i)], kf[(int64_t)h * M + i]);
-    __syncthreads();
-    lds_inverse(XL, w, fl, M, 1);
-    for (int n = threadIdx.x; n < N; n += LT) {
-        const float2 v = XL[lds_slot(n)];
-        st_real(y, r0 + n, v.x);
-        if (two) st_real(y, r1 + n, v.y);
-    }
-}
-
-// Longer rows, middle kernel: a block of 8192 positions forward, times its piece of k_f, and back, in place in tmp.
+// Middle kernel: a block of 8192 positions forward, times its piece of k_f, and back, in place in tmp.
 // natural: tmp holds the rows ko <= A/2 of real sequences in the order of ko (A/2 + 1 blocks per channel, the output
 // of k_filter_outer_real); the k_f of digit ko sits at that digit's position among the A blocks of the channel.
 __global__ void __launch_bounds__(LT) k_long_conv_blocks(float2 *__restrict__ tmp, const float2 *__restrict__ kf, LongTw w,
@@ -567,19 +535,7 @@ int64_t conv_chunk(const fftconv_plan *p)
 template <typename IO>
 int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, int64_t B, void *workspace, hipStream_t s)
 {
-    const int64_t M = p->M, N = p->N, H = p->H, npairs = (B + 1) / 2;
-    if (M <= 2 * LB) {                                   // the whole row in LDS
-        if (H > 2147483647 || npairs > 65535) {
-            set_error("fftconv_forward: H = %lld or ceil(B/2) = %lld exceeds the grid limits of this plan", (long long)H,
-                      (long long)npairs);
-            return FFTCONV_EUNSUPPORTED;
-        }
-            FC_TRY(raise_dynamic_lds((const void *)k_rows_conv_lds<IO>, (int)lds_row_bytes(2 * LB, sizeof(float2))));
-        hipLaunchKernelGGL(k_rows_conv_lds<IO>, dim3((unsigned)H, (unsigned)npairs), dim3(LT), lds_row_bytes(M, sizeof(float2)),
-                           s, u, kf, y, (const float2 *)p->st.w32, staged_fac_list(p), (int)M, N, (int)B, (int)H);
-        FC_HIP(hipGetLastError());
-        return FFTCONV_OK;
-    }
+    const int64_t M = p->M, N = p->N, H = p->H;
     const LongGeo g = long_geo(M);
     const LongTw tw = long_tw(p);
     float2 *tmp = (float2 *)workspace;
@@ -715,17 +671,10 @@ size_t long_forward_workspace_bytes(const fftconv_plan *p)
     return p->M <= 2 * LB ? 0 : (size_t)(conv_chunk(p) * p->M) * sizeof(float2);
 }
 
-// fp32 forward pass of the plans without a 16-bit kernel (fft_size >= 8192); kf: (H, fft_size) fp32 pairs in position order
+// forward pass of the fp32 plans from fft_size 32768 up; kf: (H, fft_size) fp32 pairs in position order
 int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, hipStream_t s)
 {
-    switch (p->dtype) {
-    case FFTCONV_F32: return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace, s);
-    case FFTCONV_F16:
-        return long_forward_t<__half>(p, (const __half *)u, (const float2 *)kf, (__half *)y, B, workspace, s);
-    default:
-        return long_forward_t<__hip_bfloat16>(p, (const __hip_bfloat16 *)u, (const float2 *)kf, (__hip_bfloat16 *)y, B,
-                                              workspace, s);
-    }
+    return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace, s);
 }
 
 size_t long_backward_filter_bytes(const fftconv_plan *p) { return (size_t)(3 * p->H * p->M) * sizeof(float2); }

@@ -317,10 +317,11 @@ size_t staged_kf_bytes(const fftconv_plan *p) { return (size_t)(p->H * p->M) * s
 
 size_t staged_workspace_bytes(const fftconv_plan *p, int64_t) { return long_forward_workspace_bytes(p); }
 
-// fp32 I/O from fft_size 8192 up: the whole row in LDS up to 16384, three kernels above (long_fft.hip)
+// fp32 I/O from fft_size 8192 up: one kernel up to 16384 (row_conv.hip), three above (long_fft.hip)
 int staged_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace,
                    hipStream_t s)
 {
+    if (p->M <= 16384) return row_forward(p, u, kf, y, B, s);
     return long_forward(p, u, kf, y, B, workspace, s);
 }
 
@@ -375,6 +376,7 @@ FacList staged_factors_for(int64_t M)
 int staged_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev,
                    int64_t n_blocks, void *kf, hipStream_t s)
 {
+    if (p->M <= 16384) return row_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, kf, s);
     const int bs = 256;
     hipLaunchKernelGGL(k_pack_staged, dim3(grid_for(nh * p->M, bs)), dim3(bs), 0, s, spec, (float2 *)kf, fac_list(p),
                        p->M, h0, nh, keep_dev, n_blocks);

@@ -20,3 +20,13 @@ def test_row_convolution_edges(M, dtype):
         err, plan = check_all_sequences(w, path="small")
         print("rows %s M=%d N=%d err=%.3e" % (dtype, M, N, err), flush=True)
         assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("M", [8192, 16384])
+def test_row_convolution_edges_long(M):
+    for N in (1, 3, M // 2 - 1, M // 2, M // 2 + 1, M):
+        w = synth.scaled(W["cfg2"], B=3, H=2, N=N, fft_size=M, dtype="f32", alpha=(1e-2, 1e-1))
+        err, plan = check_all_sequences(w)
+        print("rows f32 M=%d N=%d err=%.3e" % (M, N, err), flush=True)
+        assert plan.path == "staged"
+        assert err <= TOL["f32"]
