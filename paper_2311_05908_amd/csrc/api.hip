@@ -205,7 +205,6 @@ int fftconv_plan_create_path(fftconv_plan **out, int64_t N, int64_t fft_size, in
         if (p->path == PATH_FUSED3) rc = fused3_init(p);
         else if (p->path == PATH_SMALL) rc = small_init(p);
         else if (p->path == PATH_MULTIPASS) rc = multipass_init(p);
-        else if (p->M <= 16384) rc = row_tables_init(p, p->M);
     }
     if (rc != FFTCONV_OK) {
         fftconv_plan_destroy(p);
@@ -222,7 +221,6 @@ int fftconv_plan_destroy(fftconv_plan *p)
     staged_destroy(p);
     long_fft_destroy(p);
     if (p->keep_dev) (void)hipFree(p->keep_dev);
-    if (p->row_tw) (void)hipFree(p->row_tw);
     delete p;
     return FFTCONV_OK;
 }
@@ -489,6 +487,7 @@ size_t fftconv_workspace_bytes_backward_filter(const fftconv_plan *p, int64_t B)
         return (size_t)(p->H * 8192) * sizeof(float2);
     if (f3::fused3_big_dk_supported(p))
         return (size_t)(2 * p->H * p->M) * sizeof(float2);
+    if (row_backward_filter_ok(p)) return row_backward_filter_bytes(p, B);
     if (long_fft_supported(p)) return long_backward_filter_bytes(p);
     return staged_backward_filter_bytes(p);
 }
@@ -523,6 +522,7 @@ int fftconv_backward_filter(const fftconv_plan *p, const void *u, const void *dy
         if (!rc) rc = f3::fused3_big_dk_finish(p, dkf, dkf + p->H * p->M, dk, Nk, s);
         return rc;
     }
+    if (B > 0 && row_backward_filter_ok(p)) return row_backward_filter(p, u, dy, dk, Nk, B, workspace, s);
     if (long_fft_supported(p)) return long_backward_filter(p, u, dy, dk, Nk, B, workspace, s);
     return staged_backward_filter(p, u, dy, dk, Nk, B, workspace, s);
 }

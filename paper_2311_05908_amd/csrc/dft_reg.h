@@ -24,11 +24,12 @@ constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
 // In-register DFT of length R (power of two <= 32), natural order in and out, unnormalised;
 // INV conjugates the kernel.  Radix-2 decimation in time, fully unrolled so every index and
-// twiddle is a compile-time constant.  A butterfly with a twiddle is six fused operations: the sum a + w b
-// as two chained multiply-adds per part, the difference as 2 a - (a + w b); those with w = 1 or -+i are
-// four additions.  HALFIN: the inputs x[R/2 ..] are zero (the padding of a causal convolution) and are not
-// read; the first level of butterflies then only copies.
-template <int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
+// twiddle is a compile-time constant.  A butterfly with a twiddle is eight fused operations, a + w b and
+// a - w b as two chained multiply-adds per part each; SIX: six, the difference as 2 a - (a + w b), which carries the
+// rounding of the sum (4 % more error of a transform).  Those with w = 1 or -+i are four additions.  HALFIN: the
+// inputs x[R/2 ..] are zero (the padding of a causal convolution) and are not read; the first level of butterflies then
+// only copies.
+template <int R, bool INV, bool HALFIN = false, bool SIX = false> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
 {
     constexpr int LG = ilog2(R);
 #pragma unroll
@@ -61,8 +62,10 @@ template <int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void 
                     const float wi = INV ? S32[q] : -S32[q];
                     const float sx = __builtin_fmaf(-b.y, wi, __builtin_fmaf(b.x, wr, a.x));
                     const float sy = __builtin_fmaf(b.y, wr, __builtin_fmaf(b.x, wi, a.y));
+                    const float dx = SIX ? __builtin_fmaf(2.f, a.x, -sx) : __builtin_fmaf(b.y, wi, __builtin_fmaf(-b.x, wr, a.x));
+                    const float dy = SIX ? __builtin_fmaf(2.f, a.y, -sy) : __builtin_fmaf(-b.y, wr, __builtin_fmaf(-b.x, wi, a.y));
                     x[blk + j] = make_float2(sx, sy);
-                    x[blk + j + len / 2] = make_float2(__builtin_fmaf(2.f, a.x, -sx), __builtin_fmaf(2.f, a.y, -sy));
+                    x[blk + j + len / 2] = make_float2(dx, dy);
                 }
             }
         }

@@ -126,7 +126,7 @@ struct fftconv_plan {
     int64_t filt_chunk = 0;           // channels per pass through the scratch
     uint8_t *keep_dev = nullptr;      // device copy of a frequency-block mask (sparse filter transform)
     float2 *long_tw = nullptr;        // twiddle tables of the two-kernel long transforms (long_fft.hip)
-    float2 *row_tw = nullptr;         // twiddle table of the fp32 row kernels (row_fft.h)
+    const float2 *row_tw = nullptr;   // twiddle tables of the row kernels (row_io.h), behind st.w32
 };
 
 namespace fftconv {
@@ -244,14 +244,11 @@ int fused3_forward_gated(const fftconv_plan *p, const void *u, const void *w, co
 int gate_multiply(int dtype, const void *a, const void *b, void *out, int64_t n, hipStream_t s);
 
 // filter gradient dk[h,t] = sum_b sum_i dy[b,h,i] upad[b,h,(i-t) mod M], t < Nk, through the generic
-// one-kernel-per-stage transforms in fp32 (staged.hip); any plan
+// one-kernel-per-stage transforms in fp32 (staged.hip); any plan above fft_size 16384
 size_t staged_backward_filter_bytes(const fftconv_plan *p);
 int staged_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B,
                            void *workspace, hipStream_t s);
 
-int staged_inverse_to_dk(const fftconv_plan *p, float2 *spec, float2 *other, int64_t nrows, float *dk, int64_t Nk,
-                         hipStream_t s);
-int64_t staged_backward_chunk(const fftconv_plan *p);
 // fused filter gradient of the 8192-point plans (fused3_dk.hip)
 namespace f3 {
 bool fused3_dk_supported(const fftconv_plan *p);
@@ -263,11 +260,16 @@ int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *d
 int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, void *tmp, float *dk, int64_t Nk, hipStream_t s);
 }  // namespace f3
 
-// ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle table, k_f layout, the convolution
-int row_tables_init(fftconv_plan *p, int64_t M);
+// ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle tables, k_f layout, the convolution
+std::vector<float2> row_tables(int64_t M, const double2 *w);
 int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
                 void *kf, hipStream_t s);
 int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
+// the filter gradient on the same rows (row_grad.hip): plans up to fft_size 16384 without a matrix-core gradient kernel
+bool row_backward_filter_ok(const fftconv_plan *p);
+size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B);
+int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace,
+                        hipStream_t s);
 // short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);
 FacList small_factor_list(int64_t M);      // its radices, outermost first

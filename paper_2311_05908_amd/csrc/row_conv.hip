@@ -17,13 +17,8 @@
 // the copy of its bytes.  201 MB of rows (a copy takes 41 us): bf16 circular 50 / 54 / 57 / 67 / 70 us at fft 256 / 512 /
 // 1024 / 2048 / 4096 (57 / 100 / 121 / 99 / 123 us with the samples staged through LDS, an exchange for every pass and
 // the twiddles gathered from a table in LDS), fp32 causal 41 / 47 / 51 / 60 / 61 us (91 / 114 / 130 / 100 / 122).
-#include <hip/hip_bf16.h>
-#include <hip/hip_fp16.h>
-
-#include <type_traits>
-
 #include "fftconv_internal.h"
-#include "row_fft.h"
+#include "row_io.h"
 
 namespace fftconv {
 
@@ -31,52 +26,20 @@ namespace {
 
 using rf::Row;
 
-template <typename IO> __device__ __forceinline__ float ld(const IO *p, int64_t i)
-{
-    if constexpr (std::is_same<IO, float>::value) return p[i];
-    else if constexpr (std::is_same<IO, __half>::value) return __half2float(p[i]);
-    else return __bfloat162float(p[i]);
-}
-template <typename IO> __device__ __forceinline__ void st(IO *p, int64_t i, float v)
-{
-    if constexpr (std::is_same<IO, float>::value) p[i] = v;
-    else if constexpr (std::is_same<IO, __half>::value) p[i] = __float2half_rn(v);
-    else p[i] = __float2bfloat16(v);
-}
-// a packed pair of 16-bit values <-> fp32
-template <typename IO> __device__ __forceinline__ float2 unpack(uint32_t w)
-{
-    if constexpr (std::is_same<IO, __half>::value) {
-        const f3::f16x2 h = __builtin_bit_cast(f3::f16x2, w);
-        return make_float2((float)h[0], (float)h[1]);
-    } else {
-        return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
-    }
-}
-template <typename IO> __device__ __forceinline__ uint32_t pack(float lo, float hi)
-{
-    if constexpr (std::is_same<IO, __half>::value) return f3::F16::pack(lo, hi);
-    else return f3::BF16::pack(lo, hi);
-}
-// the word of the neighbouring lane (lane ^ 1)
-__device__ __forceinline__ uint32_t neighbour(uint32_t w)
-{
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xf, 0xf, true);
-}
-
-constexpr int threads_of(int M) { return M <= 8192 ? 256 : 512; }
 // waves per SIMD the register budget is held to: what LDS allows (8.5 KB a wave, 17 KB where 32 points of a thread go
 // through it as pairs) and the registers can be had for without spills
 constexpr int waves_of(int M) { return M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2; }
 
+template <int M, typename IO> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096>;
+
 // kf: see the head of this file, scaled by 1/M.  HALF: N <= M / 2.  total: pairs of rows, t = h * npairs + pair.
 template <int M, typename IO, bool HALF>
-__global__ void __launch_bounds__(threads_of(M), waves_of(M))
+__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     k_row_conv(const IO *__restrict__ u, IO *__restrict__ y, const float4 *__restrict__ kf, const float2 *__restrict__ tab, int B,
                int H, int N, int npairs, int total, int per_die)
 {
-    using G = Row<M>;
-    constexpr int RW = threads_of(M) / G::T;                      // rows (pairs) per workgroup
+    using G = ConvRow<M, IO>;
+    constexpr int RW = rf::threads_of(M) / G::T;                  // rows (pairs) per workgroup
     constexpr int MIN = HALF ? G::R0 / 2 : G::R0;                 // registers that can hold samples
     extern __shared__ float2 smem_rows[];
     const int group = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
@@ -89,52 +52,12 @@ __global__ void __launch_bounds__(threads_of(M), waves_of(M))
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     const bool exact = N == MIN * G::T;                           // every sample of the registers exists
-    // 16-bit rows whose words are aligned: lane pair (2i, 2i+1) fetches / stores the words of samples (2i, 2i+1)
-    const bool words = sizeof(IO) == 2 && N % 2 == 0 && ((((uintptr_t)u | (uintptr_t)y) & 3) == 0);
+    const bool words = rf::word_rows<IO>(u, y, N);
     const int odd = tid & 1;
     const int64_t wrow = (odd ? r1 : r0) - odd;                   // its row, so that element wrow + n starts its word
 
     float2 x[G::P];
-    if (words) {
-        const uint32_t sel = odd ? 0x03020706u : 0x05040100u;     // even: own.lo, other.lo; odd: other.hi, own.hi
-        uint32_t wd[MIN];
-        if (exact) {
-#pragma unroll
-            for (int m = 0; m < MIN; ++m) wd[m] = *(const uint32_t *)(u + wrow + tid + G::T * m);
-        } else {
-#pragma unroll
-            for (int m = 0; m < MIN; ++m) {
-                const int n = tid + G::T * m;
-                wd[m] = *(const uint32_t *)(u + wrow + (n < N ? n : odd));
-            }
-#pragma unroll
-            for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(wd[m]));      // the loads stay unconditional
-#pragma unroll
-            for (int m = 0; m < MIN; ++m)
-                if (tid + G::T * m >= N) wd[m] = 0;
-        }
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            uint32_t z = __builtin_amdgcn_perm(neighbour(wd[m]), wd[m], sel);
-            if (!two) z &= 0xffffu;
-            x[m] = unpack<IO>(z);
-        }
-    } else {
-        float a[MIN], b[MIN];
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            const int n = tid + G::T * m, at = n < N ? n : 0;
-            a[m] = ld(u, r0 + at);
-            b[m] = ld(u, r1 + at);
-        }
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(a[m]), "v"(b[m]));
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            const bool in = exact || tid + G::T * m < N;
-            x[m] = make_float2(in ? a[m] : 0.f, in && two ? b[m] : 0.f);
-        }
-    }
+    rf::load_pair<G, IO, HALF>(x, u + r0, u + r1, N, tid, exact, words, true, two);
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
     // k_f of this thread's bins: requested ahead of the last pass as far as the registers go
@@ -160,8 +83,8 @@ __global__ void __launch_bounds__(threads_of(M), waves_of(M))
         const bool put = two || !odd;
 #pragma unroll
         for (int m = 0; m < MIN; ++m) {
-            const uint32_t z = pack<IO>(x[m].x, x[m].y);
-            const uint32_t o = __builtin_amdgcn_perm(neighbour(z), z, sel);
+            const uint32_t z = rf::pack<IO>(x[m].x, x[m].y);
+            const uint32_t o = __builtin_amdgcn_perm(rf::neighbour(z), z, sel);
             if (put && (exact || tid + G::T * m < N)) *(uint32_t *)(y + wrow + tid + G::T * m) = o;
         }
     } else {
@@ -169,8 +92,8 @@ __global__ void __launch_bounds__(threads_of(M), waves_of(M))
         for (int m = 0; m < MIN; ++m) {
             const int n = tid + G::T * m;
             if (exact || n < N) {
-                st(y, r0 + n, x[m].x);
-                if (two) st(y, r1 + n, x[m].y);
+                rf::st(y, r0 + n, x[m].x);
+                if (two) rf::st(y, r1 + n, x[m].y);
             }
         }
     }
@@ -195,8 +118,8 @@ __global__ void k_pack_rows(const double2 *spec, float2 *kf, FacList fl, int64_t
 template <int M, typename IO, bool HALF>
 int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
 {
-    using G = Row<M>;
-    constexpr int NTHR = threads_of(M), RW = NTHR / G::T;
+    using G = ConvRow<M, IO>;
+    constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T;
     constexpr int lds = RW * G::LDS_BYTES;
     const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
     if (total >= ((int64_t)1 << 31) - 8 * RW) {
@@ -206,7 +129,7 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
     const int64_t groups = (total + RW - 1) / RW, per_die = (groups + 7) / 8;
     FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF>, lds));
     hipLaunchKernelGGL((k_row_conv<M, IO, HALF>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
-                       (const float4 *)kf, p->row_tw, (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
+                       (const float4 *)kf, rf::row_table<G>(p), (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -215,23 +138,6 @@ template <int M, typename IO>
 int launch_half(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
 {
     return p->N <= M / 2 ? launch<M, IO, true>(p, u, kf, y, B, s) : launch<M, IO, false>(p, u, kf, y, B, s);
-}
-
-// calls f(Row<M>()) for the row length of the plan
-template <typename F> int with_row(int64_t M, F f)
-{
-    switch (M) {
-    case 256: return f(Row<256>());
-    case 512: return f(Row<512>());
-    case 1024: return f(Row<1024>());
-    case 2048: return f(Row<2048>());
-    case 4096: return f(Row<4096>());
-    case 8192: return f(Row<8192>());
-    case 16384: return f(Row<16384>());
-    default:
-        set_error("row kernels: no instance for rows of %lld points", (long long)M);
-        return FFTCONV_EUNSUPPORTED;
-    }
 }
 
 struct SmallRadices { int r0, r1, r2; };
@@ -248,23 +154,32 @@ SmallRadices small_radices(int64_t M)
 
 }  // namespace
 
-// The twiddle table of the rows of the plan
-int row_tables_init(fftconv_plan *p, int64_t M)
+// The twiddle tables of the row kernels for a plan of M points (see row_table()), from w[t] = W_M^t
+std::vector<float2> row_tables(int64_t M, const double2 *w)
 {
-    return with_row(M, [&](auto g) -> int {
+    std::vector<float2> t;
+    auto add = [&](auto g) {
         using G = decltype(g);
-        std::vector<float2> t((size_t)G::TABLE);
-        rf::fill_table<G>(t.data());
-        FC_HIP(hipMalloc((void **)&p->row_tw, t.size() * sizeof(float2)));
-        FC_HIP(hipMemcpy(p->row_tw, t.data(), t.size() * sizeof(float2), hipMemcpyHostToDevice));
-        return FFTCONV_OK;
-    });
+        t.resize(t.size() + G::TABLE);
+        rf::fill_table<G>(t.data() + t.size() - G::TABLE, [&](int num, int den) { return w[num * (M / den)]; });
+    };
+    auto add_length = [&](int64_t L) {
+        (void)rf::with_row(L, [&](auto g) -> int {
+            using G = decltype(g);
+            add(Row<G::M, false>());
+            add(Row<G::M, true>());
+            return FFTCONV_OK;
+        });
+    };
+    add_length(M < 8192 ? M : 8192);
+    if (M == 16384) add_length(M);
+    return t;
 }
 
 int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
                 void *kf, hipStream_t s)
 {
-    return with_row(p->M, [&](auto g) -> int {
+    return rf::with_row(p->M, [&](auto g) -> int {
         using G = decltype(g);
         const int bs = 256;
         hipLaunchKernelGGL(k_pack_rows<G::M>, dim3((unsigned)((nh * G::M + bs - 1) / bs)), dim3(bs), 0, s, spec, (float2 *)kf,
@@ -276,7 +191,7 @@ int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t 
 
 int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
 {
-    return with_row(p->M, [&](auto g) -> int {
+    return rf::with_row(p->M, [&](auto g) -> int {
         using G = decltype(g);
         if (p->dtype == FFTCONV_F32) return launch_half<G::M, float>(p, u, kf, y, B, s);
         if constexpr (G::M <= 4096) {                             // longer 16-bit rows run on the matrix cores
@@ -312,7 +227,7 @@ int small_init(fftconv_plan *p)
     p->f3.N1 = r.r0;
     p->f3.N2 = r.r1;
     p->f3.N3 = r.r2;
-    return row_tables_init(p, p->M);
+    return FFTCONV_OK;
 }
 
 size_t small_kf_bytes(const fftconv_plan *p) { return (size_t)(p->H * p->M) * sizeof(float2); }

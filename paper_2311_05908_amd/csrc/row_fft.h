@@ -16,16 +16,18 @@
 //
 // What bounds these kernels is the vector ALU (about 110 operations per point and convolution at M = 8192), so
 //  * radices 32 and 16 (fewest twiddle products and exchanges that 64 data registers allow);
-//  * the R - 1 twiddles of a butterfly are products of those for 1, 2, 3 and the multiples of 4, which come from
-//    tables in thread order, [factor][thread] (a full table would save 4 of 8 operations on half of the points
-//    and cost an 8-byte load each; gathers from a table of W_M^t, one cache line per lane, bounded the kernels
-//    that this file replaces).  Each is exact to its own rounding, a product adds one more.
+//  * twiddles come from tables in thread order, [factor][thread] (gathers from a table of W_M^t, one cache line per lane,
+//    bounded the kernels that this file replaces).
+// Two kinds of row.  EXACT: all R - 1 twiddles of a butterfly come from the table, each correct to its own rounding, and the
+// in-register butterflies take eight operations.  Otherwise the table holds those for 1, 2, 3 and the multiples of 4, the
+// others are products of them, and butterflies take six: a tenth more error of a transform, and at fft 1024 68 us
+// instead of 79 for 201 MB of rows.  Convolutions with fp32 I/O up to fft 4096 and all filter gradients are exact, so that
+// they are no less accurate than kernels with a gather for every twiddle; 16-bit results do not show the
+// difference; and fp32 convolutions of 8192 and 16384 points have an error 8 - 12 % below that of the four and more
+// passes they replace with either kind.
 #pragma once
 
 #include <hip/hip_runtime.h>
-
-#include <cmath>
-#include <vector>
 
 #include "dft_reg.h"
 #include "fused3_common.h"
@@ -42,12 +44,13 @@ template <> struct Radix<4096> { static constexpr int R0 = 16, R1 = 16, R2 = 16;
 template <> struct Radix<8192> { static constexpr int R0 = 32, R1 = 16, R2 = 16; };
 template <> struct Radix<16384> { static constexpr int R0 = 32, R1 = 32, R2 = 16; };
 
-// number of twiddles of a radix-R pass that come from the table: 1, 2, 3, 4, 8, 12, ..
-constexpr int tw_count(int R) { return R / 4 + 2; }
-constexpr int tw_power(int i) { return i < 3 ? i + 1 : 4 * (i - 2); }
+// number of twiddles of a radix-R pass that come from the table, all or 1, 2, 3, 4, 8, 12, .., and their powers
+constexpr int tw_count(int R, bool exact) { return exact ? R - 1 : R / 4 + 2; }
+constexpr int tw_power(int i, bool exact) { return exact || i < 3 ? i + 1 : 4 * (i - 2); }
 
-template <int M_> struct Row {
+template <int M_, bool EXACT_ = false> struct Row {
     static constexpr int M = M_;
+    static constexpr bool EXACT = EXACT_;
     static constexpr int R0 = Radix<M>::R0, R1 = Radix<M>::R1, R2 = Radix<M>::R2;
     static constexpr int P = R0;                           // points per thread
     static constexpr int T = M / R0;                       // threads per row
@@ -55,7 +58,7 @@ template <int M_> struct Row {
     static constexpr int RL = THREE ? R2 : R1;             // radix of the last pass
     static constexpr int S1 = R2;                          // stride of pass 1 (three passes)
     static constexpr int NB1 = P / R1, NBL = P / RL;       // butterflies per thread of pass 1, of the last pass
-    static constexpr int TW0 = tw_count(R0), TW1 = THREE ? tw_count(R1) : 0;
+    static constexpr int TW0 = tw_count(R0, EXACT), TW1 = THREE ? tw_count(R1, EXACT) : 0;
     static constexpr int TABLE = TW0 * T + (THREE ? TW1 * S1 : 0);         // entries of the twiddle table
     // LDS slot of position blk * T + sub * RL + r (r < RL, sub < T / RL): one word pair of padding per RL positions
     // spreads the last pass (lanes RL positions apart) over the banks; where blocks of T positions would still start
@@ -89,14 +92,29 @@ __device__ __forceinline__ float2 mul_conj(float2 a, float2 b)     // a * conj(b
     return make_float2(__builtin_fmaf(a.y, b.y, a.x * b.x), __builtin_fmaf(a.y, b.x, -(a.x * b.y)));
 }
 
-// x[k] *= W^k (CONJ: its conjugate), k < R, from the tw_count(R) table entries t
-template <int R, bool CONJ> __device__ __forceinline__ void twiddle(float2 (&x)[R], const float2 (&t)[tw_count(R)])
+// x[k] *= W^k (CONJ: its conjugate), k < R, from the products of the tw_count(R) table entries t
+template <int R, bool CONJ> __device__ __forceinline__ void twiddle(float2 (&x)[R], const float2 (&t)[tw_count(R, false)])
 {
 #pragma unroll
     for (int k = 1; k < R; ++k) {
         const int a = k / 4, b = k % 4;
         const float2 w = a == 0 ? t[b - 1] : b == 0 ? t[a + 2] : mul(t[a + 2], t[b - 1]);
         x[k] = CONJ ? mul_conj(x[k], w) : mul(x[k], w);
+    }
+}
+// the same, W^k = tab[(k - 1) * stride], at most 16 of them in registers at a time
+template <int R, bool CONJ> __device__ __forceinline__ void twiddle_exact(float2 (&x)[R], const float2 *tab, int stride)
+{
+#pragma unroll
+    for (int k0 = 0; k0 < R; k0 += 16) {
+        if (k0 > 0) asm volatile("" : "+v"(tab) : "v"(x[k0 - 1].x), "v"(x[k0 - 1].y));
+        float2 t[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (k0 + k > 0 && k0 + k < R) t[k] = tab[(k0 + k - 1) * stride];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (k0 + k > 0 && k0 + k < R) x[k0 + k] = CONJ ? mul_conj(x[k0 + k], t[k]) : mul(x[k0 + k], t[k]);
     }
 }
 
@@ -108,22 +126,43 @@ template <int T> __device__ __forceinline__ void row_barrier()
     else asm volatile("" ::: "memory");
 }
 
-// The twiddles of pass 1, the same for every butterfly of a thread (its position inside a block does not change).
+// The twiddles of pass 1, the same for every butterfly of a thread (its position inside a block does not change):
+// in registers, or where to read them.
 template <typename G> struct Tw1 {
-    float2 t[G::THREE ? G::TW1 : 1];
+    float2 t[G::THREE && !G::EXACT ? G::TW1 : 1];
+    const float2 *p;
     __device__ __forceinline__ void load(const float2 *__restrict__ tab, int tid)
     {
-        if constexpr (G::THREE) {
+        p = tab + G::TW0 * G::T + tid % G::S1;
+        if constexpr (G::THREE && !G::EXACT) {
 #pragma unroll
-            for (int i = 0; i < G::TW1; ++i) t[i] = tab[G::TW0 * G::T + i * G::S1 + tid % G::S1];
+            for (int i = 0; i < G::TW1; ++i) t[i] = p[i * G::S1];
         }
     }
+    template <bool CONJ> __device__ __forceinline__ void apply(float2 (&v)[G::R1]) const
+    {
+        if constexpr (G::EXACT) twiddle_exact<G::R1, CONJ>(v, p, G::S1);
+        else twiddle<G::R1, CONJ>(v, t);
+    }
 };
-template <typename G> __device__ __forceinline__ void load_tw0(float2 (&t)[G::TW0], const float2 *__restrict__ tab, int tid)
-{
+// The twiddles of pass 0, ready to use: requested by load(), or read by apply() where they are too many to hold
+template <typename G> struct Tw0 {
+    float2 t[G::EXACT ? 1 : G::TW0];
+    const float2 *p;
+    __device__ __forceinline__ void load(const float2 *__restrict__ tab, int tid)
+    {
+        p = tab + tid;
+        if constexpr (!G::EXACT) {
 #pragma unroll
-    for (int i = 0; i < G::TW0; ++i) t[i] = tab[i * G::T + tid];
-}
+            for (int i = 0; i < G::TW0; ++i) t[i] = p[i * G::T];
+        }
+    }
+    template <bool CONJ> __device__ __forceinline__ void apply(float2 (&x)[G::R0]) const
+    {
+        if constexpr (G::EXACT) twiddle_exact<G::R0, CONJ>(x, p, G::T);
+        else twiddle<G::R0, CONJ>(x, t);
+    }
+};
 
 // The exchange of a two-pass row inside one wave: x[k] of column tid <-> x[i * RL + r] of the butterflies of the last pass
 // (FWD: first to last pass), one part at a time.
@@ -150,10 +189,10 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
                                         F before_last)
 {
     {
-        float2 t[G::TW0];
-        load_tw0<G>(t, tab, tid);
-        dft_reg<G::R0, false, HALF>(x);
-        twiddle<G::R0, false>(x, t);
+        Tw0<G> t;
+        t.load(tab, tid);
+        dft_reg<G::R0, false, HALF, !G::EXACT>(x);
+        t.template apply<false>(x);
     }
     if constexpr (G::SPLIT) {
         before_last();
@@ -163,7 +202,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
             float2 v[G::RL];
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
-            dft_reg<G::RL, false>(v);
+            dft_reg<G::RL, false, false, !G::EXACT>(v);
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
         }
@@ -180,8 +219,8 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
             float2 v[G::R1];
 #pragma unroll
             for (int m = 0; m < G::R1; ++m) v[m] = z[m * G::PAD];
-            dft_reg<G::R1, false>(v);
-            twiddle<G::R1, false>(v, tw1.t);
+            dft_reg<G::R1, false, false, !G::EXACT>(v);
+            tw1.template apply<false>(v);
 #pragma unroll
             for (int k = 0; k < G::R1; ++k) z[k * G::PAD] = v[k];
         }
@@ -196,7 +235,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
         float2 v[G::RL];
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) v[r] = z[r];
-        dft_reg<G::RL, false>(v);
+        dft_reg<G::RL, false, false, !G::EXACT>(v);
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
     }
@@ -211,7 +250,7 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
         float2 v[G::RL];
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
-        dft_reg<G::RL, true>(v);
+        dft_reg<G::RL, true, false, !G::EXACT>(v);
         if constexpr (G::SPLIT) {
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
@@ -223,10 +262,10 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
     }
     if constexpr (G::SPLIT) {
         exchange<G, false>(x, (float *)Z, tid);
-        float2 t[G::TW0];
-        load_tw0<G>(t, tab, tid);
-        twiddle<G::R0, true>(x, t);
-        dft_reg<G::R0, true>(x);
+        Tw0<G> t;
+        t.load(tab, tid);
+        t.template apply<true>(x);
+        dft_reg<G::R0, true, false, !G::EXACT>(x);
         return;
     }
     row_barrier<G::T>();
@@ -237,35 +276,34 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
             float2 v[G::R1];
 #pragma unroll
             for (int k = 0; k < G::R1; ++k) v[k] = z[k * G::PAD];
-            twiddle<G::R1, true>(v, tw1.t);
-            dft_reg<G::R1, true>(v);
+            tw1.template apply<true>(v);
+            dft_reg<G::R1, true, false, !G::EXACT>(v);
 #pragma unroll
             for (int m = 0; m < G::R1; ++m) z[m * G::PAD] = v[m];
         }
         row_barrier<G::T>();
     }
-    float2 t[G::TW0];
-    load_tw0<G>(t, tab, tid);
+    Tw0<G> t;
+    t.load(tab, tid);
     const float2 *const z0 = Z + G::slot0(tid);
 #pragma unroll
     for (int k = 0; k < G::R0; ++k) x[k] = z0[k * G::PITCH];
-    twiddle<G::R0, true>(x, t);
-    dft_reg<G::R0, true>(x);
+    t.template apply<true>(x);
+    dft_reg<G::R0, true, false, !G::EXACT>(x);
 }
 
-// Host side: the twiddle table of Row<M>, in fp64 and rounded once.
-template <typename G> inline void fill_table(float2 *tab)
+// Host side: the twiddle table of Row<M>, rounded once; w(num, den) = exp(-2 pi i num / den) in fp64, num < den.
+template <typename G, typename W> inline void fill_table(float2 *tab, W w)
 {
-    const double two_pi = 6.283185307179586476925286766559;
-    auto wpow = [&](double num, double den) {
-        const double a = two_pi * num / den;
-        return make_float2((float)std::cos(a), (float)-std::sin(a));
+    auto put = [&](float2 *at, int num, int den) {
+        const double2 v = w(num % den, den);
+        *at = make_float2((float)v.x, (float)v.y);
     };
     for (int i = 0; i < G::TW0; ++i)
-        for (int j = 0; j < G::T; ++j) tab[i * G::T + j] = wpow((double)tw_power(i) * j, (double)G::M);
+        for (int j = 0; j < G::T; ++j) put(tab + i * G::T + j, tw_power(i, G::EXACT) * j, G::M);
     if (G::THREE)
         for (int i = 0; i < G::TW1; ++i)
-            for (int j = 0; j < G::S1; ++j) tab[G::TW0 * G::T + i * G::S1 + j] = wpow((double)tw_power(i) * j, (double)G::T);
+            for (int j = 0; j < G::S1; ++j) put(tab + G::TW0 * G::T + i * G::S1 + j, tw_power(i, G::EXACT) * j, G::T);
 }
 
 }  // namespace rf

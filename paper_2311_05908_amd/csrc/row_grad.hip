@@ -1,0 +1,217 @@
+// Filter gradient with fp32 arithmetic of rows that fit on chip, fft_size M in {256 .. 16384}, any I/O dtype, any
+// N <= M (paper Section 3.1 "Kernel Fusion and Recomputation"):
+//     dk_f[h] = sum_b conj(FFT(pad(u[b,h]))) . FFT(pad(dy[b,h])),      dk[h] = Re(iFFT(dk_f[h]))[0:Nk].
+// Serves the plans without a matrix-core gradient kernel (fp32 I/O, circular and ragged shapes).
+//
+//  * The transforms are those of row_fft.h with exact twiddles, one of every row of u and of dy with zeros for an imaginary
+//    part.  (Two rows in one complex transform, as in the convolution, would halve them; but dk is a real result of real
+//    sequences, and half of the rounding errors of a real row's spectrum go with the imaginary part in the end: sharing
+//    transforms costs a fifth in accuracy.)
+//  * A row of threads owns a run of a channel's batch rows and adds their products up in registers.  A channel is cut into S
+//    runs where channels alone would leave compute units idle (grad_splits); their sums meet in a second kernel, in a fixed
+//    order, which also transforms back.  With S = 1 the first kernel does that itself and no sum leaves the registers.
+//  * The sums go through memory in register order, [run][h][register pair][thread][2], as 16-byte accesses.
+// Bound by the vector ALU and, at two waves per SIMD (the accumulator, a spectrum of u and the transform under way take
+// 192 registers), by the latency of the exchanges between passes.  It replaces one
+// kernel for every factor of either transform, batch row by batch row, with the row in memory between them.  A training step
+// (filter transforms, forward pass, both gradients), us: fp32 8 x 128 x 3000 fft 8192 750 -> 124; bf16 circular
+// 16 x 256 x 1024 699 -> 86, 8 x 256 x 8192 1005 -> 229; bf16 8 x 256 x 777 fft 2048 490 -> 78.
+#include "fftconv_internal.h"
+#include "row_io.h"
+
+namespace fftconv {
+
+namespace {
+
+using rf::Row;
+
+// waves per SIMD that the registers allow without spills: 192 data registers with 32 points a thread, half of that with 16
+template <int M> constexpr int GRAD_WAVES = Row<M, true>::P == 32 ? 2 : 3;
+
+template <typename G>
+__device__ __forceinline__ void store_dk(const float2 (&x)[G::P], float *__restrict__ dk, int64_t Nk, float scale, int tid)
+{
+#pragma unroll
+    for (int m = 0; m < G::P; ++m) {
+        const int n = tid + G::T * m;
+        if (n < Nk) dk[n] = x[m].x * scale;
+    }
+}
+
+// HALF: N <= M / 2.  Row t = h * S + s of threads: batch rows [s * per, (s + 1) * per) of channel h.
+template <int M, typename IO, bool HALF>
+__global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
+    k_row_corr(const IO *__restrict__ u, const IO *__restrict__ dy, float4 *__restrict__ part, float *__restrict__ dk,
+               const float2 *__restrict__ tab, int B, int H, int N, int64_t Nk, int S, int per)
+{
+    using G = Row<M, true>;
+    constexpr int RW = rf::threads_of(M) / G::T;
+    extern __shared__ float2 smem_rows[];
+    const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T, rows = H * S;
+    const int t = min((int)blockIdx.x * RW + row, rows - 1);      // rows beyond the last one repeat it, unstored
+    const bool live = (int)blockIdx.x * RW + row < rows;
+    const int h = t / S, s = t - h * S;
+    float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
+    const bool exact = N == (HALF ? G::R0 / 2 : G::R0) * G::T;
+    const bool words = rf::word_rows<IO>(u, dy, N);
+
+    float2 acc[G::P], zu[G::P];
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) acc[p] = make_float2(0.f, 0.f);
+    // one transform a step: a u row, then the dy row; the same count in every row of threads (shared barriers)
+    float next[G::P];                                             // the dy row, fetched with the u row
+#pragma unroll 1
+    for (int i = 0; i < 2 * per; ++i) {
+        const int b = s * per + i / 2;
+        int j = tid;
+        asm volatile("" : "+v"(j));                               // addresses, masks and twiddles of a step are not kept for the next
+        float2 x[G::P];
+        if (i & 1) {
+#pragma unroll
+            for (int m = 0; m < G::P; ++m) x[m] = make_float2(next[m], 0.f);
+        } else {
+            const int64_t at = ((int64_t)min(b, B - 1) * H + h) * N;          // past the channel's end: the last row, as zeros
+            rf::load_pair<G, IO, HALF>(x, u + at, dy + at, N, j, exact, words, b < B, b < B);
+#pragma unroll
+            for (int m = 0; m < (HALF ? G::P / 2 : G::P); ++m) {
+                next[m] = x[m].y;
+                x[m].y = 0.f;
+            }
+        }
+        rf::Tw1<G> tw1;
+        tw1.load(tab, j);
+        rf::row_barrier<G::T>();                                  // the slots are free
+        rf::forward<G, HALF>(x, Z, tab, tw1, j, [] {});
+        if (i & 1) {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) {                      // acc += conj(Z_u) Z_dy
+                acc[p].x = __builtin_fmaf(zu[p].y, x[p].y, __builtin_fmaf(zu[p].x, x[p].x, acc[p].x));
+                acc[p].y = __builtin_fmaf(-zu[p].y, x[p].x, __builtin_fmaf(zu[p].x, x[p].y, acc[p].y));
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) zu[p] = x[p];
+        }
+    }
+    if (S == 1) {
+        rf::Tw1<G> tw1;
+        tw1.load(tab, tid);
+        rf::inverse<G>(acc, Z, tab, tw1, tid);
+        if (live) store_dk<G>(acc, dk + (int64_t)h * Nk, Nk, 1.f / M, tid);
+        return;
+    }
+    if (!live) return;
+    float4 *const o = part + ((int64_t)s * H + h) * (M / 2) + tid;
+#pragma unroll
+    for (int q = 0; q < G::P / 2; ++q) o[q * G::T] = make_float4(acc[2 * q].x, acc[2 * q].y, acc[2 * q + 1].x, acc[2 * q + 1].y);
+}
+
+// dk[h] from the S sums of channel h
+template <int M>
+__global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
+    k_row_dk(const float4 *__restrict__ part, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk, int S)
+{
+    using G = Row<M, true>;
+    constexpr int RW = rf::threads_of(M) / G::T;
+    extern __shared__ float2 smem_rows[];
+    const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
+    const int h = min((int)blockIdx.x * RW + row, H - 1);
+    const bool live = (int)blockIdx.x * RW + row < H;
+    float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    float2 x[G::P];
+    const float4 *in = part + (int64_t)h * (M / 2) + tid;
+#pragma unroll
+    for (int q = 0; q < G::P / 2; ++q) {
+        const float4 v = in[q * G::T];
+        x[2 * q] = make_float2(v.x, v.y);
+        x[2 * q + 1] = make_float2(v.z, v.w);
+    }
+    for (int s = 1; s < S; ++s) {
+        in += (int64_t)H * (M / 2);
+        float4 v[G::P / 2];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) v[q] = in[q * G::T];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) {
+            x[2 * q].x += v[q].x;
+            x[2 * q].y += v[q].y;
+            x[2 * q + 1].x += v[q].z;
+            x[2 * q + 1].y += v[q].w;
+        }
+    }
+    rf::inverse<G>(x, Z, tab, tw1, tid);
+    if (live) store_dk<G>(x, dk + (int64_t)h * Nk, Nk, 1.f / M, tid);
+}
+
+// Runs per channel: as many as give every SIMD of 256 compute units two waves (16 points a thread: four), no more than
+// the batch has rows, of equal length.
+struct Splits { int64_t S, per; };
+Splits grad_splits(int64_t M, int64_t H, int64_t B)
+{
+    int64_t want = 1;
+    (void)rf::with_row(M, [&](auto g) -> int {
+        using G = Row<decltype(g)::M, true>;
+        want = 256 * 4 * GRAD_WAVES<G::M> * 64 / G::T / H;
+        return FFTCONV_OK;
+    });
+    if (want > B) want = B;
+    if (want < 1) want = 1;
+    const int64_t per = (B + want - 1) / want;
+    return Splits{(B + per - 1) / per, per};
+}
+
+template <int M, typename IO, bool HALF>
+int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
+{
+    using G = Row<M, true>;
+    constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
+    const Splits sp = grad_splits(M, p->H, B);
+    if (B >= ((int64_t)1 << 31) || p->H * sp.S >= ((int64_t)1 << 31) - RW) {
+        set_error("fftconv_backward_filter: too many sequences for the row kernel");
+        return FFTCONV_EUNSUPPORTED;
+    }
+    FC_TRY(raise_dynamic_lds((const void *)k_row_corr<M, IO, HALF>, lds));
+    hipLaunchKernelGGL((k_row_corr<M, IO, HALF>), dim3((unsigned)((p->H * sp.S + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u,
+                       (const IO *)dy, (float4 *)workspace, dk, rf::row_table<G>(p), (int)B, (int)p->H, (int)p->N, Nk, (int)sp.S, (int)sp.per);
+    FC_HIP(hipGetLastError());
+    if (sp.S == 1) return FFTCONV_OK;
+    FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M>, lds));
+    hipLaunchKernelGGL(k_row_dk<M>, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float4 *)workspace, dk,
+                       rf::row_table<G>(p), (int)p->H, Nk, (int)sp.S);
+    FC_HIP(hipGetLastError());
+    return FFTCONV_OK;
+}
+
+template <int M, typename IO>
+int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
+{
+    return p->N <= M / 2 ? launch<M, IO, true>(p, u, dy, dk, Nk, B, workspace, s)
+                         : launch<M, IO, false>(p, u, dy, dk, Nk, B, workspace, s);
+}
+
+}  // namespace
+
+bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSED3 && p->M <= 16384; }
+
+// the sums of the runs; never 0 (the entry point refuses a missing workspace)
+size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B)
+{
+    const Splits sp = grad_splits(p->M, p->H, B);
+    return sp.S == 1 ? 256 : (size_t)(sp.S * p->H * p->M) * sizeof(float2);
+}
+
+// B >= 1
+int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace,
+                        hipStream_t s)
+{
+    return rf::with_row(p->M, [&](auto g) -> int {
+        using G = decltype(g);
+        if (p->dtype == FFTCONV_F32) return launch_half<G::M, float>(p, u, dy, dk, Nk, B, workspace, s);
+        if (p->dtype == FFTCONV_F16) return launch_half<G::M, __half>(p, u, dy, dk, Nk, B, workspace, s);
+        return launch_half<G::M, __hip_bfloat16>(p, u, dy, dk, Nk, B, workspace, s);
+    });
+}
+
+}  // namespace fftconv

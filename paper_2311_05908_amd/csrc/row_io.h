@@ -1,0 +1,132 @@
+// Samples of the row kernels (row_fft.h): pairs of batch rows of any I/O dtype into the registers of the first pass.
+#pragma once
+
+#include <hip/hip_bf16.h>
+#include <hip/hip_fp16.h>
+
+#include <type_traits>
+
+#include "fftconv_internal.h"
+#include "row_fft.h"
+
+namespace fftconv {
+namespace rf {
+
+template <typename IO> __device__ __forceinline__ float ld(const IO *p, int64_t i)
+{
+    if constexpr (std::is_same<IO, float>::value) return p[i];
+    else if constexpr (std::is_same<IO, __half>::value) return __half2float(p[i]);
+    else return __bfloat162float(p[i]);
+}
+template <typename IO> __device__ __forceinline__ void st(IO *p, int64_t i, float v)
+{
+    if constexpr (std::is_same<IO, float>::value) p[i] = v;
+    else if constexpr (std::is_same<IO, __half>::value) p[i] = __float2half_rn(v);
+    else p[i] = __float2bfloat16(v);
+}
+// a packed pair of 16-bit values <-> fp32
+template <typename IO> __device__ __forceinline__ float2 unpack(uint32_t w)
+{
+    if constexpr (std::is_same<IO, __half>::value) {
+        const f3::f16x2 h = __builtin_bit_cast(f3::f16x2, w);
+        return make_float2((float)h[0], (float)h[1]);
+    } else {
+        return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+    }
+}
+template <typename IO> __device__ __forceinline__ uint32_t pack(float lo, float hi)
+{
+    if constexpr (std::is_same<IO, __half>::value) return f3::F16::pack(lo, hi);
+    else return f3::BF16::pack(lo, hi);
+}
+// the word of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ uint32_t neighbour(uint32_t w)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xf, 0xf, true);
+}
+
+constexpr int threads_of(int M) { return M <= 8192 ? 256 : 512; }
+
+// 16-bit rows of N samples at a and b whose words are aligned: lane pair (2i, 2i+1) can move the words of samples (2i, 2i+1)
+template <typename IO> __device__ __forceinline__ bool word_rows(const void *a, const void *b, int N)
+{
+    return sizeof(IO) == 2 && N % 2 == 0 && ((((uintptr_t)a | (uintptr_t)b) & 3) == 0);
+}
+
+// x[m] = sample tid + T m of the rows r0 (real part) and r1 (imaginary part), zero from N on; a row that is not there
+// (has0, has1 false; its pointer still leads to N samples) is zero.  HALF: only m < R0 / 2.  exact: N fills them all.
+// Every load is issued before the first is used.
+template <typename G, typename IO, bool HALF>
+__device__ __forceinline__ void load_pair(float2 (&x)[G::P], const IO *__restrict__ r0, const IO *__restrict__ r1, int N, int tid,
+                                          bool exact, bool words, bool has0, bool has1)
+{
+    constexpr int MIN = HALF ? G::R0 / 2 : G::R0;                 // registers that can hold samples
+    if (words) {
+        const int odd = tid & 1;
+        const IO *const wrow = (odd ? r1 : r0) - odd;             // the lane's row, so that element wrow + n starts its word
+        const uint32_t sel = odd ? 0x03020706u : 0x05040100u;     // even: own.lo, other.lo; odd: other.hi, own.hi
+        const uint32_t keep = (has0 ? 0xffffu : 0u) | (has1 ? 0xffff0000u : 0u);
+        uint32_t wd[MIN];
+        if (exact) {
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) wd[m] = *(const uint32_t *)(wrow + tid + G::T * m);
+        } else {
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) {
+                const int n = tid + G::T * m;
+                wd[m] = *(const uint32_t *)(wrow + (n < N ? n : odd));
+            }
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(wd[m]));      // the loads stay unconditional
+#pragma unroll
+            for (int m = 0; m < MIN; ++m)
+                if (tid + G::T * m >= N) wd[m] = 0;
+        }
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) x[m] = unpack<IO>(__builtin_amdgcn_perm(neighbour(wd[m]), wd[m], sel) & keep);
+    } else {
+        float a[MIN], b[MIN];
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const int n = tid + G::T * m, at = n < N ? n : 0;
+            a[m] = ld(r0, at);
+            b[m] = ld(r1, at);
+        }
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(a[m]), "v"(b[m]));
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const bool in = exact || tid + G::T * m < N;
+            x[m] = make_float2(in && has0 ? a[m] : 0.f, in && has1 ? b[m] : 0.f);
+        }
+    }
+}
+
+// calls f(Row<M>()) for the row length of the plan
+template <typename F> int with_row(int64_t M, F f)
+{
+    switch (M) {
+    case 256: return f(Row<256>());
+    case 512: return f(Row<512>());
+    case 1024: return f(Row<1024>());
+    case 2048: return f(Row<2048>());
+    case 4096: return f(Row<4096>());
+    case 8192: return f(Row<8192>());
+    case 16384: return f(Row<16384>());
+    default:
+        set_error("row kernels: no instance for rows of %lld points", (long long)M);
+        return FFTCONV_EUNSUPPORTED;
+    }
+}
+
+
+// The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
+// that.
+template <typename G> inline const float2 *row_table(const fftconv_plan *p)
+{
+    const size_t at = G::M == 16384 ? Row<8192, false>::TABLE + Row<8192, true>::TABLE : 0;
+    return p->row_tw + at + (G::EXACT ? Row<G::M, false>::TABLE : 0);
+}
+
+}  // namespace rf
+}  // namespace fftconv

@@ -184,21 +184,6 @@ __global__ void __launch_bounds__(LDS_ROW_THREADS) k_rows_fwd_lds(const float *_
     for (int n = threadIdx.x; n < M; n += LDS_ROW_THREADS) spec[row * M + n] = XD[lds_slot(n)];
 }
 
-// Unnormalised inverse transform of position-ordered spectra, real part of the first Nk samples times scale
-// (the tail of the filter gradient).
-__global__ void __launch_bounds__(LDS_ROW_THREADS) k_rows_inv_dk_lds(const float2 *__restrict__ spec, float *__restrict__ dk,
-                                                                    const float2 *__restrict__ w, FacList fl, int M,
-                                                                    int64_t Nk, float scale)
-{
-    extern __shared__ float2 XF[];
-    const int64_t row = blockIdx.x;
-#pragma unroll 8
-    for (int n = threadIdx.x; n < M; n += LDS_ROW_THREADS) XF[lds_slot(n)] = spec[row * M + n];
-    __syncthreads();
-    lds_inverse(XF, w, fl, M, 1);
-    for (int n = threadIdx.x; n < Nk; n += LDS_ROW_THREADS) dk[row * Nk + n] = XF[lds_slot(n)].x * scale;
-}
-
 inline unsigned grid_of(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 // one stage, in registers when the factor allows; returns false if it does not
@@ -286,9 +271,12 @@ int staged_init(fftconv_plan *p)
         w32[t] = make_float2((float)w64[t].x, (float)w64[t].y);
     }
     FC_HIP(hipMalloc((void **)&p->st.w64, sizeof(double2) * M));
-    FC_HIP(hipMalloc((void **)&p->st.w32, sizeof(float2) * M));
+    const std::vector<float2> rows = row_tables(M, w64.data());       // one buffer and one copy with w32
+    w32.insert(w32.end(), rows.begin(), rows.end());
+    FC_HIP(hipMalloc((void **)&p->st.w32, sizeof(float2) * w32.size()));
+    p->row_tw = p->st.w32 + M;
     FC_HIP(hipMemcpy(p->st.w64, w64.data(), sizeof(double2) * M, hipMemcpyHostToDevice));
-    FC_HIP(hipMemcpy(p->st.w32, w32.data(), sizeof(float2) * M, hipMemcpyHostToDevice));
+    FC_HIP(hipMemcpy(p->st.w32, w32.data(), sizeof(float2) * w32.size(), hipMemcpyHostToDevice));
 
     // filter-transform scratch: two ping-pong buffers of at most 64 MiB, or 8 channels, each
     const int64_t cap = (int64_t)64 << 20;
@@ -435,20 +423,11 @@ static int64_t bwd_chunk(const fftconv_plan *p)
 
 // dk rows from position-ordered spectra: unnormalised inverse stages (ping-pong between spec and other,
 // both nrows * M), real part of the first Nk samples, times 1/M.  spec is overwritten.
-int staged_inverse_to_dk(const fftconv_plan *p, float2 *spec, float2 *other, int64_t nrows, float *dk, int64_t Nk,
-                         hipStream_t s)
+static int staged_inverse_to_dk(const fftconv_plan *p, float2 *spec, float2 *other, int64_t nrows, float *dk, int64_t Nk,
+                                hipStream_t s)
 {
     const int bs = 256;
     const int64_t M = p->M;
-    const size_t lds_bytes = lds_row_bytes(M, sizeof(float2));
-    if (lds_bytes <= LDS_ROW_MAX && lds_factors_ok(fac_list(p))) {
-        const int rc = raise_lds_limit((const void *)k_rows_inv_dk_lds);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_rows_inv_dk_lds, dim3((unsigned)nrows), dim3(LDS_ROW_THREADS), lds_bytes, s, spec, dk,
-                           p->st.w32, fac_list(p), (int)M, Nk, 1.0f / (float)M);
-        FC_HIP(hipGetLastError());
-        return FFTCONV_OK;
-    }
     float2 *src = spec, *dst = other;
     int64_t S = 1, R = M;
     for (int i = p->st.nf - 1; i >= 0; --i) {
@@ -468,8 +447,6 @@ int staged_inverse_to_dk(const fftconv_plan *p, float2 *spec, float2 *other, int
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
-
-int64_t staged_backward_chunk(const fftconv_plan *p) { return bwd_chunk(p); }
 
 size_t staged_backward_filter_bytes(const fftconv_plan *p)
 {

@@ -1,11 +1,14 @@
 """The fp32 row kernels (one kernel per convolution, row_fft.h) at the edges of what they are dispatched for:
 every row length, the shortest and longest rows, odd and even sample counts around fft/2 (16-bit rows of even length
 move as words, the others element by element; the padded half is skipped up to fft/2), odd batches (a pair without
-partner) and row counts that leave a workgroup partly empty."""
+partner) and row counts that leave a workgroup partly empty.  For the filter gradient on the same rows also the ways a
+channel's pairs are cut into runs."""
 import pytest
+import torch
 
-from paper_2311_05908_amd import synth
-from parity_util import TOL, check_all_sequences
+import oracle
+from paper_2311_05908_amd import fftconv, synth
+from parity_util import TOL, check_all_sequences, parity_error
 
 pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS
@@ -30,3 +33,34 @@ def test_row_convolution_edges_long(M):
         print("rows f32 M=%d N=%d err=%.3e" % (M, N, err), flush=True)
         assert plan.path == "staged"
         assert err <= TOL["f32"]
+
+
+def check_row_gradient(dtype, B, H, N, M, Nk, path):
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
+    u, dy = synth.gen_u(w), synth.gen_gate(w, "dy")
+    plan = fftconv.Plan(N, M, H, dtype, path=path)
+    dk = plan.backward_filter(u.cuda(), dy.cuda(), Nk)
+    torch.cuda.synchronize()
+    assert torch.isfinite(dk).all()
+    err = parity_error(dk.cpu().double().numpy(), oracle.backward_k(u.double().numpy(), dy.double().numpy(), M, Nk), TOL["f32"])
+    print("row gradient %s B=%d H=%d N=%d M=%d Nk=%d err=%.3e" % (dtype, B, H, N, M, Nk, err), flush=True)
+    assert err <= TOL["f32"]                    # fp32 sums whatever the I/O type
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_row_gradient_edges(M, dtype):
+    path = "small" if M <= 4096 else "staged" if dtype == "f32" else "multipass"
+    for N, Nk in ((1, M), (7, 5), (M // 2, 300), (M // 2 + 1, 33), (M - 2, 77), (M, 200)):
+        check_row_gradient(dtype, 3, 3, N, M, min(Nk, M), path)
+
+
+@pytest.mark.parametrize("B,H,M", [
+    (1, 3, 1024),        # one run: transformed back in the same kernel
+    (13, 6000, 256),     # two runs of four pairs, the last one short of a pair; partly empty workgroups
+    (9, 256, 8192),      # two runs of three pairs
+    (5, 513, 8192),      # more channels than rows of threads wanted: one run of three pairs
+    (40, 3, 512),        # a run for every pair
+])
+def test_row_gradient_runs(B, H, M):
+    check_row_gradient("f32", B, H, 40, M, 50, None)
