@@ -5,7 +5,7 @@
 //             of the (A, 8192) view of a row into LDS (8192 points), runs those stages there with the twiddles
 //             W_M^{k R r} of the full length and writes the tile back in place;
 //             "blocks"  - the remaining factors act inside contiguous blocks of 8192 positions: one workgroup
-//             per block, the length-8192 forward transform of lds_fft.h (its own table of W_8192).
+//             per block, a transform of the row engine (row_fft.h) in registers and LDS.
 //   inverse:  the same two kernels mirrored (blocks first, then columns).
 // Users: the filter transform of the multi-pass plans (taps -> spectrum -> k_f, fp32 is ample for constants
 // that are rounded to 16 bits) and the filter gradient of every plan from fft_size 16384 up that has no
@@ -23,6 +23,7 @@
 
 #include "fftconv_internal.h"
 #include "lds_fft.h"
+#include "row_io.h"
 
 namespace fftconv {
 
@@ -67,7 +68,6 @@ __device__ __forceinline__ void st_real(__hip_bfloat16 *p, int64_t i, float v) {
 // W_M^e of the full length as a product of two small tables, e = 2048 e_hi + e_lo: the exponents of the outer
 // stages are spread over the whole range, and gathers from a table of M entries (16 MB at 2^21) miss every cache
 struct LongTw {
-    const float2 *w8k;                         // W_8192^t, t < 8192: the table of the block transforms
     const float2 *lo, *hi;                     // W_M^t, t < 2048; W_M^{2048 t}, t < M / 2048
     __device__ __forceinline__ float2 operator()(int64_t e) const { return cmul(hi[e >> 11], lo[e & 2047]); }
 };
@@ -76,20 +76,6 @@ struct LongTw {
 // first value is used (a loop of load -> LDS write waits for every load in turn, and the round trip to HBM was most
 // of these kernels' time); the launches use LT threads.
 constexpr int LPT = LB / LT;
-// contiguous block: src[i] -> slot i
-__device__ __forceinline__ void load_block(float2 *XL, const float2 *__restrict__ src)
-{
-    float2 v[LPT];
-#pragma unroll
-    for (int j = 0; j < LPT; ++j) v[j] = src[threadIdx.x + j * LT];
-#pragma unroll
-    for (int j = 0; j < LPT; ++j) XL[lds_slot(threadIdx.x + j * LT)] = v[j];
-}
-__device__ __forceinline__ void store_block(const float2 *XL, float2 *__restrict__ dst)
-{
-#pragma unroll
-    for (int j = 0; j < LPT; ++j) dst[threadIdx.x + j * LT] = XL[lds_slot(threadIdx.x + j * LT)];
-}
 // column tile: slot i = a * C + c <- row[a * 8192 + col0 + c] (C a power of two)
 __device__ __forceinline__ void load_cols(float2 *XL, const float2 *__restrict__ row, int C, int col0)
 {
@@ -144,7 +130,7 @@ __device__ inline void cols_stage_any(float2 *X, const LongTw &w, int A, int C, 
 // Forward, columns: rows of real input (re from src_re, im from src_im or zero; `len` valid samples, zeros
 // beyond; reversed: position n holds sample (M - n) mod M) -> tmp (rows, M) after the factors of A.
 // half_rows (real input only, src_im == nullptr): only the blocks of the outer frequency digits ko <= A/2 are
-// written; the others hold mirror images (see k_long_fwd_blocks_kf) and nobody reads them.
+// written; the others hold mirror images (see k_long_blocks_kf) and nobody reads them.
 template <typename In>
 __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src_re, const In *__restrict__ src_im,
                                                      float2 *__restrict__ tmp, LongTw w, FacList flA, int A, int C, int64_t len,
@@ -193,145 +179,133 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
     }
 }
 
-// Forward, blocks: tmp -> spectrum in position order.  MODE 0: store to out.  MODE 1: acc (+)= conj(other) * X
-// (other: the spectrum of the u rows, X: that of the dy rows; first: assign instead of add).
-template <int MODE>
-__global__ void __launch_bounds__(LT) k_long_fwd_blocks(const float2 *__restrict__ tmp, float2 *__restrict__ out,
-                                                       const float2 *__restrict__ other, LongTw w, FacList flB, int A,
-                                                       bool first)
+// ---- blocks of 8192 positions: whole rows of the row engine (row_fft.h), one to a workgroup of 256 threads, samples and
+// results straight between HBM and registers.
+using RB = rf::Row<LB>;                        // convolutions, filters whose spectrum is kept in 16 bits
+using RX = rf::Row<LB, true>;                  // exact twiddles: everything whose result is fp32
+static_assert(RB::SLOTS == RX::SLOTS && RB::T == RX::T, "rows differ in their tables only");
+
+template <typename G> __device__ __forceinline__ void load_row(float2 (&x)[G::P], const float2 *src, int tid)
 {
-    extern __shared__ float2 XL[];
-    const int64_t base = ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
-    load_block(XL, tmp + base);
-    __syncthreads();
-    lds_forward(XL, w.w8k, flB, LB, 1);
-    if (MODE == 0) {
-        store_block(XL, out + base);
-    } else {
-        float2 a[LPT], o[LPT];
 #pragma unroll
-        for (int j = 0; j < LPT; ++j) a[j] = other[base + threadIdx.x + j * LT];
-        if (!first) {
+    for (int m = 0; m < G::P; ++m) x[m] = src[tid + G::T * m];
+}
+template <typename G> __device__ __forceinline__ void store_row(const float2 (&x)[G::P], float2 *dst, int tid)
+{
 #pragma unroll
-            for (int j = 0; j < LPT; ++j) o[j] = out[base + threadIdx.x + j * LT];
-        }
-#pragma unroll
-        for (int j = 0; j < LPT; ++j) {
-            const int i = threadIdx.x + j * LT;
-            const float2 x = XL[lds_slot(i)];
-            float2 v = make_float2(a[j].x * x.x + a[j].y * x.y, a[j].x * x.y - a[j].y * x.x);
-            if (!first) {
-                v.x += o[j].x;
-                v.y += o[j].y;
-            }
-            out[base + i] = v;
-        }
-    }
+    for (int m = 0; m < G::P; ++m) dst[tid + G::T * m] = x[m];
 }
 
-// Forward, blocks, for the filter transform of the multi-pass plans: the block at position a' of a row holds the
-// bins f = ko + A f' of one outer frequency digit ko (the digit reversal of a'), f' < 8192 in position order; they
-// go straight to that digit's row of k_f, [h][ko][slot of f' in the 8192-point kernel's per-lane order] as 16-bit
-// (re, im) pairs, scaled by 1/M (times the fp16 range boost, multipass_kf_boost) and by the frequency mask.
+// Filter transform: the block at position a' of a row holds the bins f = ko + A f' of one outer frequency digit ko (the
+// digit reversal of a'), f' < 8192; they go straight to that digit's row of k_f, scaled by 1/M and by the frequency mask:
+//   KF 0 / 1: bf16 / fp16 pairs [h][ko][slot of f' in the 8192-point kernel's per-lane order] (multi-pass plans; fp16
+//             times the range boost, multipass_kf_boost);
+//   KF 2:     fp32 pairs [h][position of ko][register order of the row engine] (fp32 I/O from fft_size 32768 up).
 // The taps are real, so K[M - f] = conj K[f]: with f = ko + A f', M - f = (A - ko) + A (8191 - f') for ko >= 1.  Only the
-// blocks of the digits ko <= A/2 are transformed (the column kernel wrote no others); a block with 0 < ko < A/2 also
+// blocks of the digits ko <= A/2 are transformed (the kernel before wrote no others); a block with 0 < ko < A/2 also
 // writes the row of the digit A - ko, bin g of which is the conjugate of this row's bin 8191 - g.  The rows ko = 0 and
 // ko = A/2 are their own mirror images.
 // natural: tmp holds the rows ko <= A/2 only, in the order of ko (A/2 + 1 blocks per channel: the output of
 // k_filter_outer_real, multipass.hip) instead of all A blocks in position order.  conj_out: the conjugate spectrum
 // (that of the circularly time-reversed taps, which are real).
-template <bool F16>
-__global__ void __launch_bounds__(LT) k_long_fwd_blocks_kf(const float2 *__restrict__ tmp, uint32_t *__restrict__ kf, LongTw w,
-                                                          FacList flA, FacList flB, int A, int64_t h0,
-                                                          const uint8_t *__restrict__ keep, int64_t n_blocks, bool natural,
-                                                          bool conj_out)
+// Bound by the writes of k_f: the digits (k1, k2, k3) of f' are those of the row engine's registers (k1 = k0, k2 = digit 1,
+// k3 = digit 2), so a wave stores runs of 16 slots without another exchange.
+template <int KF>
+__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__restrict__ tmp, void *__restrict__ kf,
+                                                             const float2 *__restrict__ tab, FacList flA, int A, int64_t h0,
+                                                             const uint8_t *__restrict__ keep, int64_t n_blocks, bool natural,
+                                                             bool conj_out)
 {
+    using G = std::conditional_t<KF == 2, RX, RB>;
     extern __shared__ float2 XL[];
     const int ko = natural ? (int)blockIdx.x : lds_freq(blockIdx.x, flA, A);
     if (2 * ko > A) return;                                   // written by the block of A - ko
     const int64_t base = natural ? ((int64_t)blockIdx.y * (A / 2 + 1) + ko) * LB : ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
-    load_block(XL, tmp + base);
-    __syncthreads();
-    lds_forward(XL, w.w8k, flB, LB, 1);
+    const int tid = threadIdx.x;
+    float2 x[G::P];
+    load_row<G>(x, tmp + base, tid);
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::forward<G, false>(x, XL, tab, tw1, tid, [] {});
     const int M = A * LB;
-    const float boost = (float)multipass_kf_boost(F16, A) / (float)M;
-    typedef __attribute__((ext_vector_type(2))) float f32x2;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-    auto pair16 = [](float re, float im) {                    // round to nearest even, one conversion instruction
-        const f32x2 v = {re, im};
-        if constexpr (F16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-        else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    const float scale = (KF == 1 ? (float)multipass_kf_boost(true, A) : 1.f) / (float)M, sgn = conj_out ? -1.f : 1.f;
+    const bool mirror = ko > 0 && 2 * ko < A;
+    const int km = mirror ? A - ko : ko;
+    const int64_t row = ((h0 + blockIdx.y) * A + (KF == 2 ? lds_pos(ko, flA, A) : ko)) * (int64_t)LB;
+    const int64_t row_m = ((h0 + blockIdx.y) * A + (KF == 2 ? lds_pos(km, flA, A) : km)) * (int64_t)LB;
+    auto put = [&](int64_t r, int f, float re, float im) {
+        if constexpr (KF == 2) ((float2 *)kf)[r + G::index(f)] = make_float2(re, im);
+        else ((uint32_t *)kf)[r + fused3_kf_slot_8192(f)] = KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
     };
-    // position of inner frequency f after the block transform, for the factors 16, 16, 16, 2 of 8192 (lds_pos()
-    // with the loop over the factor list folded; the launch checks the list)
-    auto pos8k = [](int f) { return ((f & 15) << 9) | (((f >> 4) & 15) << 5) | (((f >> 8) & 15) << 1) | (f >> 12); };
-    uint32_t *dst = kf + ((h0 + blockIdx.y) * A + ko) * (int64_t)LB;
-    const bool mirror = ko > 0 && 2 * ko < A;
-    uint32_t *dst_m = kf + ((h0 + blockIdx.y) * A + (mirror ? A - ko : ko)) * (int64_t)LB;
-#pragma unroll 4
-    for (int d = threadIdx.x; d < LB; d += LT) {
-        const int lane = d % 64, r = (d / 64) % 4, k1 = d / 256;
-        const int k2 = lane % 16, k3 = k3_at_index(4 * (lane / 16) + r, 16);
-        const int fi = k1 + 32 * (k2 + 16 * k3);              // the inner frequency of slot d
-        const float2 v = XL[lds_slot(pos8k(fi))];
-        const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * boost : boost;
-        dst[d] = pair16(v.x * sc, conj_out ? -v.y * sc : v.y * sc);
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) {
+        const int fi = G::freq(tid, p);
+        const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * scale : scale;
+        put(row, fi, x[p].x * sc, sgn * x[p].y * sc);
         if (mirror) {
-            const float2 vm = XL[lds_slot(pos8k(LB - 1 - fi))];
-            const float scm = keep ? lds_mask_weight(keep, n_blocks, (A - ko) + A * fi, M) * boost : boost;
-            dst_m[d] = pair16(vm.x * scm, conj_out ? vm.y * scm : -vm.y * scm);
+            const int fm = LB - 1 - fi;
+            const float scm = keep ? lds_mask_weight(keep, n_blocks, km + A * fm, M) * scale : scale;
+            put(row_m, fm, x[p].x * scm, -sgn * x[p].y * scm);
         }
     }
 }
 
-// The same for the plans that keep k_f as fp32 pairs in position order (fp32 I/O from fft_size 32768 up): tmp
-// holds the rows ko <= A/2 in the order of ko (k_filter_outer_real); row ko goes to the block at the position of
-// digit ko, bins in the block transform's own order, scaled by 1/M and by the frequency mask; the mirror row
-// A - ko likewise, bin g = conj of this row's bin 8191 - g.
-__global__ void __launch_bounds__(LT) k_long_fwd_blocks_kf32(const float2 *__restrict__ tmp, float2 *__restrict__ kf, LongTw w,
-                                                            FacList flA, FacList flB, int A, int64_t h0,
-                                                            const uint8_t *__restrict__ keep, int64_t n_blocks, bool conj_out)
+// Filter gradient: sum over nb batch rows of conj(FFT(block of u)) . FFT(block of dy) for the blocks of a launch (grid:
+// blocks of a channel, channels; batch row b at a distance of b * stride), then back: acc holds the sum of earlier rows
+// unless first, and takes it unless last, when the inverse transform goes to out (which may be a block of tu).
+// The spectra and their sum stay in registers (one transform at a time: 192 data registers), where three kernels
+// wrote and read them.
+__global__ void __launch_bounds__(RX::T, 2) k_long_blocks_corr(const float2 *tu, const float2 *td, int64_t stride, int nb,
+                                                               float4 *acc, float2 *out, const float2 *__restrict__ tab, bool first,
+                                                               bool last)
 {
+    using G = RX;
     extern __shared__ float2 XL[];
-    const int ko = blockIdx.x;                                // <= A/2
-    const int64_t base = ((int64_t)blockIdx.y * (A / 2 + 1) + ko) * LB;
-    load_block(XL, tmp + base);
-    __syncthreads();
-    lds_forward(XL, w.w8k, flB, LB, 1);
-    const int M = A * LB;
-    const float inv = 1.0f / (float)M;
-    // the factors 16, 16, 16, 2 of 8192 folded (the launch checks the list): position of a frequency and back
-    auto pos8k = [](int f) { return ((f & 15) << 9) | (((f >> 4) & 15) << 5) | (((f >> 8) & 15) << 1) | (f >> 12); };
-    auto freq8k = [](int i) { return (i >> 9) | (((i >> 5) & 15) << 4) | (((i >> 1) & 15) << 8) | ((i & 1) << 12); };
-    const bool mirror = ko > 0 && 2 * ko < A;
-    float2 *dst = kf + ((h0 + blockIdx.y) * A + lds_pos(ko, flA, A)) * (int64_t)LB;
-    float2 *dst_m = kf + ((h0 + blockIdx.y) * A + lds_pos(mirror ? A - ko : ko, flA, A)) * (int64_t)LB;
-    const float sgn = conj_out ? -1.f : 1.f;
-#pragma unroll 4
-    for (int i = threadIdx.x; i < LB; i += LT) {
-        const int fi = freq8k(i);
-        const float2 v = XL[lds_slot(i)];
-        const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * inv : inv;
-        dst[i] = make_float2(v.x * sc, sgn * v.y * sc);
-        if (mirror) {
-            const float2 vm = XL[lds_slot(pos8k(LB - 1 - fi))];
-            const float scm = keep ? lds_mask_weight(keep, n_blocks, (A - ko) + A * fi, M) * inv : inv;
-            dst_m[i] = make_float2(vm.x * scm, -sgn * vm.y * scm);
+    const int64_t base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * LB;
+    const int tid = threadIdx.x;
+    float2 sum[G::P], zu[G::P];
+    if (first) {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) sum[p] = make_float2(0.f, 0.f);
+    } else {
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) {
+            const float4 v = acc[base / 2 + tid + q * G::T];
+            sum[2 * q] = make_float2(v.x, v.y);
+            sum[2 * q + 1] = make_float2(v.z, v.w);
         }
     }
-}
-
-// Inverse, blocks: spectrum in position order -> tmp after the factors of 8192 (unnormalised).
-__global__ void __launch_bounds__(LT) k_long_inv_blocks(const float2 *__restrict__ spec, float2 *__restrict__ tmp, LongTw w,
-                                                       FacList flB, int A)
-{
-    extern __shared__ float2 XL[];
-    const int64_t base = ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
-    load_block(XL, spec + base);
-    __syncthreads();
-    lds_inverse(XL, w.w8k, flB, LB, 1);
-    store_block(XL, tmp + base);
+#pragma unroll 1
+    for (int i = 0; i < 2 * nb; ++i) {
+        int j = tid;
+        asm volatile("" : "+v"(j));                           // nothing of a step's addresses and twiddles is kept for the next
+        float2 x[G::P];
+        load_row<G>(x, (i & 1 ? td : tu) + (i / 2) * stride + base, j);
+        rf::Tw1<G> tw1;
+        tw1.load(tab, j);
+        rf::row_barrier<G::T>();                              // the slots are free
+        rf::forward<G, false>(x, XL, tab, tw1, j, [] {});
+        if (i & 1) {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) {                  // sum += conj(Z_u) Z_dy
+                sum[p].x = __builtin_fmaf(zu[p].y, x[p].y, __builtin_fmaf(zu[p].x, x[p].x, sum[p].x));
+                sum[p].y = __builtin_fmaf(-zu[p].y, x[p].x, __builtin_fmaf(zu[p].x, x[p].y, sum[p].y));
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) zu[p] = x[p];
+        }
+    }
+    if (!last) {
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q)
+            acc[base / 2 + tid + q * G::T] = make_float4(sum[2 * q].x, sum[2 * q].y, sum[2 * q + 1].x, sum[2 * q + 1].y);
+        return;
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::inverse<G>(sum, XL, tab, tw1, tid);
+    store_row<G>(sum, out + base, tid);
 }
 
 // Inverse, columns: the factors of A, then real part times scale of the samples n < Nk -> dk (rows, Nk).
@@ -366,27 +340,32 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_dk(const float2 *__restric
 // Middle kernel: a block of 8192 positions forward, times its piece of k_f, and back, in place in tmp.
 // natural: tmp holds the rows ko <= A/2 of real sequences in the order of ko (A/2 + 1 blocks per channel, the output
 // of k_filter_outer_real); the k_f of digit ko sits at that digit's position among the A blocks of the channel.
-__global__ void __launch_bounds__(LT) k_long_conv_blocks(float2 *__restrict__ tmp, const float2 *__restrict__ kf, LongTw w,
-                                                        FacList flA, FacList flB, int A, bool natural)
+__global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restrict__ tmp, const float4 *__restrict__ kf,
+                                                               const float2 *__restrict__ tab, FacList flA, int A, bool natural)
 {
+    using G = RB;
     extern __shared__ float2 XL[];
     const int64_t base = natural ? ((int64_t)blockIdx.y * (A / 2 + 1) + blockIdx.x) * LB
                                  : ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
     const int64_t kbase = natural ? ((int64_t)blockIdx.y * A + lds_pos(blockIdx.x, flA, A)) * LB : base;
-    load_block(XL, tmp + base);
-    float2 kv[LPT];                                          // in flight during the forward transform
+    const int tid = threadIdx.x;
+    float2 x[G::P];
+    load_row<G>(x, tmp + base, tid);
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    float4 kv[G::P / 2];
+    const float4 *const kr = kf + kbase / 2 + tid;
+    rf::forward<G, false>(x, XL, tab, tw1, tid, [&] {
 #pragma unroll
-    for (int j = 0; j < LPT; ++j) kv[j] = kf[kbase + threadIdx.x + j * LT];
-    __syncthreads();
-    lds_forward(XL, w.w8k, flB, LB, 1);
+        for (int q = 0; q < G::P / 2; ++q) kv[q] = kr[q * G::T];
+    });
 #pragma unroll
-    for (int j = 0; j < LPT; ++j) {
-        const int i = threadIdx.x + j * LT;
-        XL[lds_slot(i)] = cmul(XL[lds_slot(i)], kv[j]);
+    for (int q = 0; q < G::P / 2; ++q) {
+        x[2 * q] = rf::mul(x[2 * q], make_float2(kv[q].x, kv[q].y));
+        x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
     }
-    __syncthreads();
-    lds_inverse(XL, w.w8k, flB, LB, 1);
-    store_block(XL, tmp + base);
+    rf::inverse<G>(x, XL, tab, tw1, tid);
+    store_row<G>(x, tmp + base, tid);
 }
 
 // Longer rows, last kernel: the outer factors back, real part -> row of y_re, imaginary part -> row of y_im
@@ -429,8 +408,7 @@ __global__ void k_zero_dk(float *x, int64_t n)
 LongTw long_tw(const fftconv_plan *p)
 {
     LongTw t;
-    t.w8k = p->long_tw;
-    t.lo = p->long_tw + LB;
+    t.lo = p->long_tw;
     t.hi = t.lo + 2048;
     return t;
 }
@@ -449,14 +427,15 @@ int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, c
     return FFTCONV_OK;
 }
 
-template <int MODE>
-int launch_fwd_blocks(const LongGeo &g, const float2 *tmp, float2 *out, const float2 *other, const LongTw &w, int64_t rows,
-                      bool first, hipStream_t s)
+// rows of the block kernels' launches: their LDS and the plan's table
+constexpr int B_LDS = RB::LDS_BYTES;
+
+int launch_corr(const fftconv_plan *p, int blocks, const float2 *tu, const float2 *td, int64_t stride, int64_t nb, float2 *acc,
+                float2 *out, bool first, bool last, hipStream_t s)
 {
-    const int rc = raise_lds((const void *)k_long_fwd_blocks<MODE>);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_long_fwd_blocks<MODE>, dim3((unsigned)g.A, (unsigned)rows), dim3(LT), L_LDS, s, tmp, out, other, w,
-                       g.flB, g.A, first);
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_corr, B_LDS));
+    hipLaunchKernelGGL(k_long_blocks_corr, dim3((unsigned)blocks, (unsigned)p->H), dim3(RB::T), B_LDS, s, tu, td, stride, (int)nb,
+                       (float4 *)acc, out, rf::row_table<RX>(p), first, last);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -468,7 +447,6 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
     const LongGeo g = long_geo(p->M);
     const LongTw tw = long_tw(p);
     const int64_t M = p->M, N = p->N, H = p->H;
-    float2 *acc = (float2 *)workspace, *spec_u = acc + H * M, *tmp = spec_u + H * M;
     if (B == 0) {
         const int bs = 256;
         hipLaunchKernelGGL(k_zero_dk, dim3((unsigned)((H * Nk + bs - 1) / bs)), dim3(bs), 0, s, dk, H * Nk);
@@ -481,45 +459,45 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         // acc (+)= conj(U) DY on them -- and the sum, the spectrum of a real sequence again, goes back through the
         // inverse block transforms and the real inverse outer pass: half the intermediate traffic of the complex
         // pipeline below, and a row without a partner costs no more than half a pair.
+        // The workspace holds the transformed rows of u and dy of as many batch rows as fit, and the sum if they do not all.
         const int NR = g.A / 2 + 1;
-        const int64_t RW = (int64_t)NR * LB;
-        float2 *acc2 = (float2 *)workspace, *spec2 = acc2 + H * RW, *tmp2 = spec2 + H * RW;
-        const dim3 grid((unsigned)NR, (unsigned)H);
-        int rc = raise_lds((const void *)k_long_fwd_blocks<0>);
-        if (!rc) rc = raise_lds((const void *)k_long_fwd_blocks<1>);
-        if (!rc) rc = raise_lds((const void *)k_long_inv_blocks);
-        if (rc) return rc;
-        for (int64_t b = 0; b < B; ++b) {
-            rc = multipass_filter_outer(p, u + b * H * N, p->dtype, N, H, tmp2, s);
-            if (rc) return rc;
-            hipLaunchKernelGGL(k_long_fwd_blocks<0>, grid, dim3(LT), L_LDS, s, tmp2, spec2, nullptr, tw, g.flB, NR, false);
-            FC_HIP(hipGetLastError());
-            rc = multipass_filter_outer(p, dy + b * H * N, p->dtype, N, H, tmp2, s);
-            if (rc) return rc;
-            hipLaunchKernelGGL(k_long_fwd_blocks<1>, grid, dim3(LT), L_LDS, s, tmp2, acc2, spec2, tw, g.flB, NR, b == 0);
-            FC_HIP(hipGetLastError());
+        const int64_t RW = H * NR * (int64_t)LB, fit = 3 * H * M / RW;
+        const bool once = 2 * B <= fit;
+        const int64_t nb = once ? B : (fit - 1) / 2;
+        float2 *acc = (float2 *)workspace, *tu = once ? acc : acc + RW, *td = tu + nb * RW;
+        for (int64_t b = 0; b < B; b += nb) {
+            const int64_t n = B - b < nb ? B - b : nb;
+            for (int64_t i = 0; i < n; ++i) {
+                FC_TRY(multipass_filter_outer(p, u + (b + i) * H * N, p->dtype, N, H, tu + i * RW, s));
+                FC_TRY(multipass_filter_outer(p, dy + (b + i) * H * N, p->dtype, N, H, td + i * RW, s));
+            }
+            FC_TRY(launch_corr(p, NR, tu, td, RW, n, acc, tu, b == 0, b + n == B, s));
         }
-        hipLaunchKernelGGL(k_long_inv_blocks, grid, dim3(LT), L_LDS, s, acc2, tmp2, tw, g.flB, NR);
-        FC_HIP(hipGetLastError());
-        return multipass_dk_outer_inv(p, tmp2, dk, Nk, H, 1.0f / (float)M, s);
+        return multipass_dk_outer_inv(p, tu, dk, Nk, H, 1.0f / (float)M, s);
     }
+    float2 *acc = (float2 *)workspace, *tu = acc + H * M, *td = tu + H * M;
     for (int64_t b = 0; b < B; b += 2) {                      // rows b and b + 1 share a transform
         const IO *u0 = u + b * H * N, *u1 = b + 1 < B ? u0 + H * N : nullptr;
         const IO *d0 = dy + b * H * N, *d1 = b + 1 < B ? d0 + H * N : nullptr;
-        int rc = launch_fwd_cols<IO>(g, u0, u1, tmp, tw, H, N, false, s);
-        if (!rc) rc = launch_fwd_blocks<0>(g, tmp, spec_u, nullptr, tw, H, false, s);
-        if (!rc) rc = launch_fwd_cols<IO>(g, d0, d1, tmp, tw, H, N, false, s);
-        if (!rc) rc = launch_fwd_blocks<1>(g, tmp, acc, spec_u, tw, H, b == 0, s);
-        if (rc) return rc;
+        FC_TRY(launch_fwd_cols<IO>(g, u0, u1, tu, tw, H, N, false, s));
+        FC_TRY(launch_fwd_cols<IO>(g, d0, d1, td, tw, H, N, false, s));
+        FC_TRY(launch_corr(p, g.A, tu, td, 0, 1, acc, tu, b == 0, b + 2 >= B, s));
     }
-    int rc = raise_lds((const void *)k_long_inv_blocks);
-    if (!rc) rc = raise_lds((const void *)k_long_inv_cols_dk);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_long_inv_blocks, dim3((unsigned)g.A, (unsigned)H), dim3(LT), L_LDS, s, acc, tmp, tw, g.flB,
-                       g.A);
-    FC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_long_inv_cols_dk, dim3((unsigned)g.A, (unsigned)H), dim3(LT), L_LDS, s, tmp, dk, tw, g.flA,
+    FC_TRY(raise_lds((const void *)k_long_inv_cols_dk));
+    hipLaunchKernelGGL(k_long_inv_cols_dk, dim3((unsigned)g.A, (unsigned)H), dim3(LT), L_LDS, s, tu, dk, tw, g.flA,
                        g.A, g.C, Nk, 1.0f / (float)M);
+    FC_HIP(hipGetLastError());
+    return FFTCONV_OK;
+}
+
+template <int KF>
+int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 *tmp, void *kf, int64_t h0, const uint8_t *keep_dev,
+              int64_t n_blocks, bool natural, bool conj_out, hipStream_t s)
+{
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF>, B_LDS));
+    const float2 *tab = KF == 2 ? rf::row_table<RX>(p) : rf::row_table<RB>(p);
+    hipLaunchKernelGGL(k_long_blocks_kf<KF>, dim3((unsigned)(natural ? g.A / 2 + 1 : g.A), (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
+                       kf, tab, g.flA, g.A, h0, keep_dev, n_blocks, natural, conj_out);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -540,7 +518,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
     const LongTw tw = long_tw(p);
     float2 *tmp = (float2 *)workspace;
     const int64_t chunk = conv_chunk(p);
-    int rc = raise_lds((const void *)k_long_conv_blocks);
+    int rc = raise_dynamic_lds((const void *)k_long_conv_blocks, B_LDS);
     if (!rc) rc = raise_lds((const void *)k_long_inv_cols_y<IO>);
     if (rc) return rc;
     // fp32 rows at outer lengths with register kernels for real rows (multipass.hip) can go one row at a time as
@@ -561,8 +539,8 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
             if (as_real) {
                 rc = multipass_filter_outer(p, u + o0, FFTCONV_F32, N, nh, tmp, s);
                 if (rc) return rc;
-                hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)NR, (unsigned)nh), dim3(LT), L_LDS, s, tmp, kf + h0 * M,
-                                   tw, g.flA, g.flB, g.A, true);
+                hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)NR, (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
+                                   (const float4 *)(kf + h0 * M), rf::row_table<RB>(p), g.flA, g.A, true);
                 FC_HIP(hipGetLastError());
                 rc = multipass_dk_outer_inv(p, tmp, (float *)(y + o0), N, nh, 1.0f, s);
                 if (rc) return rc;
@@ -570,8 +548,8 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
             }
             rc = launch_fwd_cols<IO>(g, u + o0, two ? u + o0 + H * N : nullptr, tmp, tw, nh, N, false, s);
             if (rc) return rc;
-            hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)g.A, (unsigned)nh), dim3(LT), L_LDS, s, tmp, kf + h0 * M, tw,
-                               g.flA, g.flB, g.A, false);
+            hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)g.A, (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
+                               (const float4 *)(kf + h0 * M), rf::row_table<RB>(p), g.flA, g.A, false);
             FC_HIP(hipGetLastError());
             hipLaunchKernelGGL(k_long_inv_cols_y<IO>, dim3((unsigned)g.A, (unsigned)nh), dim3(LT), L_LDS, s,
                                (const float2 *)tmp, y + o0, two ? y + o0 + H * N : nullptr, tw, g.flA, g.A, g.C, N);
@@ -590,15 +568,14 @@ bool long_fft_supported(const fftconv_plan *p) { return p->M >= 2 * LB && p->M <
 int long_fft_init(fftconv_plan *p)
 {
     const int64_t M = p->M, nhi = M / 2048;
-    std::vector<float2> t((size_t)(LB + 2048 + nhi));
+    std::vector<float2> t((size_t)(2048 + nhi));
     const double two_pi = 6.283185307179586476925286766559;
     auto wpow = [&](double num, double den) {
         const double a = two_pi * num / den;
         return make_float2((float)std::cos(a), (float)-std::sin(a));
     };
-    for (int64_t i = 0; i < LB; ++i) t[(size_t)i] = wpow((double)i, (double)LB);
-    for (int64_t i = 0; i < 2048; ++i) t[(size_t)(LB + i)] = wpow((double)i, (double)M);
-    for (int64_t i = 0; i < nhi; ++i) t[(size_t)(LB + 2048 + i)] = wpow((double)i, (double)nhi);
+    for (int64_t i = 0; i < 2048; ++i) t[(size_t)i] = wpow((double)i, (double)M);
+    for (int64_t i = 0; i < nhi; ++i) t[(size_t)(2048 + i)] = wpow((double)i, (double)nhi);
     FC_HIP(hipMalloc((void **)&p->long_tw, t.size() * sizeof(float2)));
     FC_HIP(hipMemcpy(p->long_tw, t.data(), t.size() * sizeof(float2), hipMemcpyHostToDevice));
     return FFTCONV_OK;
@@ -617,50 +594,25 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
 {
     const LongGeo g = long_geo(p->M);
     const LongTw tw = long_tw(p);
-    if (g.flB.nf != 4 || g.flB.fac[0] != 16 || g.flB.fac[1] != 16 || g.flB.fac[2] != 16 || g.flB.fac[3] != 2) {
-        set_error("multi-pass filter transform: the block transform's factors are not 16, 16, 16, 2");
-        return FFTCONV_EUNSUPPORTED;
-    }
     // outer factor: the register kernel of the multi-pass route where it exists for this outer length (rows ko <= A/2
     // in natural order; the adjoint spectrum is then the conjugate, taken on the way out), else the generic column kernel
     const bool natural = multipass_filter_outer_ok(p);
     int rc = natural ? multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s)
                      : launch_fwd_cols<float>(g, k, nullptr, tmp, tw, nh, Nk, adjoint, s, true);
     if (rc) return rc;
-    rc = raise_lds((const void *)k_long_fwd_blocks_kf<true>);
-    if (!rc) rc = raise_lds((const void *)k_long_fwd_blocks_kf<false>);
     if (rc) return rc;
-    const dim3 grid((unsigned)(natural ? g.A / 2 + 1 : g.A), (unsigned)nh);
-    if (p->dtype == FFTCONV_F16)
-        hipLaunchKernelGGL(k_long_fwd_blocks_kf<true>, grid, dim3(LT), L_LDS, s, tmp, (uint32_t *)kf, tw, g.flA, g.flB, g.A, h0,
-                           keep_dev, n_blocks, natural, natural && adjoint);
-    else
-        hipLaunchKernelGGL(k_long_fwd_blocks_kf<false>, grid, dim3(LT), L_LDS, s, tmp, (uint32_t *)kf, tw, g.flA, g.flB, g.A, h0,
-                           keep_dev, n_blocks, natural, natural && adjoint);
-    FC_HIP(hipGetLastError());
-    return FFTCONV_OK;
+    return p->dtype == FFTCONV_F16 ? launch_kf<1>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s)
+                                   : launch_kf<0>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s);
 }
 
-// The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs in the position order of
-// long_fft_factor_list() (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block transforms of the
+// The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block transforms of the
 // rows ko <= A/2, as above.  tmp holds nh * (A/2 + 1) * 8192 float2.  Needs multipass_filter_outer_ok(p).
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                               const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
 {
     const LongGeo g = long_geo(p->M);
-    const LongTw tw = long_tw(p);
-    if (g.flB.nf != 4 || g.flB.fac[0] != 16 || g.flB.fac[1] != 16 || g.flB.fac[2] != 16 || g.flB.fac[3] != 2) {
-        set_error("long filter transform: the block transform's factors are not 16, 16, 16, 2");
-        return FFTCONV_EUNSUPPORTED;
-    }
-    int rc = multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s);
-    if (rc) return rc;
-    rc = raise_lds((const void *)k_long_fwd_blocks_kf32);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_long_fwd_blocks_kf32, dim3((unsigned)(g.A / 2 + 1), (unsigned)nh), dim3(LT), L_LDS, s, tmp,
-                       (float2 *)kf, tw, g.flA, g.flB, g.A, h0, keep_dev, n_blocks, adjoint);
-    FC_HIP(hipGetLastError());
-    return FFTCONV_OK;
+    FC_TRY(multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s));
+    return launch_kf<2>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, true, adjoint, s);
 }
 
 // The position order of the spectra of these transforms (k_f of the fp32 plans from fft_size 32768 up is stored in it)

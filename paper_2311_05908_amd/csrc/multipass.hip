@@ -667,7 +667,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
 // ---- the outer pass of the FILTER transform of a multi-pass plan (fftconv_filter_fft: taps -> k_f): pass A of a
 // lone real row (k_outer_fwd_real above) with fp32 taps in and fp32 rows out.  k_f holds 16-bit constants, so
 // its transform runs in fp32 throughout: this kernel, then the 8192-point transform of every row in LDS
-// (k_long_fwd_blocks_kf, long_fft.hip).  Rows ko <= No/2 only, T2[h][ko][r] (No/2 + 1 rows of 8192 fp32 pairs per
+// (k_long_blocks_kf, long_fft.hip).  Rows ko <= No/2 only, T2[h][ko][r] (No/2 + 1 rows of 8192 fp32 pairs per
 // channel): the taps are real, the other rows are mirror images that the second kernel writes from these.
 // Taps at and beyond Nk are zeros (their loads read tap 0 and are discarded: no load sits behind a branch).
 // The filter gradient of these plans (long_fft.hip) transforms its rows of u and dy the same way: IN = 0: fp32

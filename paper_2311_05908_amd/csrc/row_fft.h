@@ -81,6 +81,12 @@ template <int M_, bool EXACT_ = false> struct Row {
         if constexpr (THREE) return bi / R1 + R0 * (bi % R1) + R0 * R1 * r;
         else return bi + R0 * r;
     }
+    // place of frequency f in register order, [register pair][thread][2]
+    static __host__ __device__ __forceinline__ int index(int f)
+    {
+        const int bi = THREE ? f % R0 * R1 + f / R0 % R1 : f % R0, r = THREE ? f / (R0 * R1) : f / R0, p = bi / T * RL + r;
+        return (p / 2 * T + bi % T) * 2 + p % 2;
+    }
 };
 
 __device__ __forceinline__ float2 mul(float2 a, float2 b)

@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "lds_fft.h"
+#include "row_fft.h"
 #include "fftconv_internal.h"
 
 namespace fftconv {
@@ -211,8 +212,9 @@ bool launch_stage_reg(bool inverse, const V *src, V *dst, const V *w, int64_t M,
 #undef STAGE_REG
 }
 
-// spectra in position order (fp64) -> staged k_f (fp32 pairs, same position order), scaled 1/M,
-// with dropped frequency blocks zeroed.
+// spectra in position order (fp64) -> staged k_f of the long rows (fp32 pairs; long_fft.hip: the blocks of 8192 bins
+// f = ko + A f' at the position of ko, inside a block the register order of the row engine), scaled 1/M, with dropped
+// frequency blocks zeroed.
 __global__ void k_pack_staged(const double2 *spec, float2 *kf, FacList fl, int64_t M, int64_t h0, int64_t nh,
                               const uint8_t *keep, int64_t n_blocks)
 {
@@ -222,7 +224,8 @@ __global__ void k_pack_staged(const double2 *spec, float2 *kf, FacList fl, int64
     int64_t p = freq_to_pos(f, fl, M);
     double2 v = spec[h * M + p];
     double sc = mask_weight(keep, n_blocks, f, M) / (double)M;
-    kf[(h0 + h) * M + p] = make_float2((float)(v.x * sc), (float)(v.y * sc));
+    kf[(h0 + h) * M + (p & ~(int64_t)8191) + rf::Row<8192>::index((int)(f / (M / 8192)))] =
+        make_float2((float)(v.x * sc), (float)(v.y * sc));
 }
 
 FacList fac_list(const fftconv_plan *p) { return staged_fac_list(p); }
