@@ -281,12 +281,17 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
     const bool long_rows = p->path == PATH_MULTIPASS && long_fft_supported(p);
     // fp32 k_f in the position order of the long transforms (staged plans from fft 32768 up) with a real outer pass
     const bool long_rows_f32 = p->path == PATH_STAGED && p->M >= 32768 && long_fft_supported(p) && multipass_filter_outer_ok(p);
-    // fp32 in two kernels per chunk; the scratch buffer is sized for fp64 spectra, so it takes twice the rows, and
-    // where only the outer rows ko <= No/2 pass through it (multipass_filter_outer) nearly twice as many again
-    int64_t long_chunk = 2 * p->filt_chunk;
+    // fp32 in two kernels per chunk; the scratch buffers, one behind the other, are sized for fp64 spectra, so they take four
+    // times the rows, and where only the outer rows ko <= No/2 pass through them (multipass_filter_outer) nearly twice as
+    // many again
+    int64_t long_chunk = 4 * p->filt_chunk;
     if ((long_rows || long_rows_f32) && multipass_filter_outer_ok(p)) {
         const int64_t No = p->M / 8192;
         long_chunk = long_chunk * No / (No / 2 + 1);
+    }
+    if (long_rows || long_rows_f32) {                         // as few passes as fit, of about equal size
+        const int64_t n = (p->H + long_chunk - 1) / long_chunk;
+        long_chunk = (p->H + n - 1) / n;
     }
     for (int64_t h0 = 0; long_rows && h0 < p->H; h0 += long_chunk) {
         const int64_t nh = p->H - h0 < long_chunk ? p->H - h0 : long_chunk;

@@ -181,8 +181,8 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
 
 // ---- blocks of 8192 positions: whole rows of the row engine (row_fft.h), one to a workgroup of 256 threads, samples and
 // results straight between HBM and registers.
-using RB = rf::Row<LB>;                        // convolutions, filters whose spectrum is kept in 16 bits
-using RX = rf::Row<LB, true>;                  // exact twiddles: everything whose result is fp32
+using RB = rf::Row<LB>;
+using RX = rf::Row<LB, true>;                  // exact twiddles: spectra that are kept in fp32
 static_assert(RB::SLOTS == RX::SLOTS && RB::T == RX::T, "rows differ in their tables only");
 
 template <typename G> __device__ __forceinline__ void load_row(float2 (&x)[G::P], const float2 *src, int tid)
@@ -210,42 +210,56 @@ template <typename G> __device__ __forceinline__ void store_row(const float2 (&x
 // (that of the circularly time-reversed taps, which are real).
 // Bound by the writes of k_f: the digits (k1, k2, k3) of f' are those of the row engine's registers (k1 = k0, k2 = digit 1,
 // k3 = digit 2), so a wave stores runs of 16 slots without another exchange.
+// Workgroups are persistent, two to a compute unit, and fetch the next block ahead of the present one's transform: loads,
+// transforms and stores of workgroups that all start together otherwise take turns on the whole chip.
 template <int KF>
 __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__restrict__ tmp, void *__restrict__ kf,
-                                                             const float2 *__restrict__ tab, FacList flA, int A, int64_t h0,
+                                                             const float2 *__restrict__ tab, FacList flA, int A, int64_t h0, int blocks,
                                                              const uint8_t *__restrict__ keep, int64_t n_blocks, bool natural,
                                                              bool conj_out)
 {
     using G = std::conditional_t<KF == 2, RX, RB>;
     extern __shared__ float2 XL[];
-    const int ko = natural ? (int)blockIdx.x : lds_freq(blockIdx.x, flA, A);
-    if (2 * ko > A) return;                                   // written by the block of A - ko
-    const int64_t base = natural ? ((int64_t)blockIdx.y * (A / 2 + 1) + ko) * LB : ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
-    const int tid = threadIdx.x;
-    float2 x[G::P];
-    load_row<G>(x, tmp + base, tid);
-    rf::Tw1<G> tw1;
-    tw1.load(tab, tid);
-    rf::forward<G, false>(x, XL, tab, tw1, tid, [] {});
-    const int M = A * LB;
+    const int M = A * LB, NR = A / 2 + 1;
     const float scale = (KF == 1 ? (float)multipass_kf_boost(true, A) : 1.f) / (float)M, sgn = conj_out ? -1.f : 1.f;
-    const bool mirror = ko > 0 && 2 * ko < A;
-    const int km = mirror ? A - ko : ko;
-    const int64_t row = ((h0 + blockIdx.y) * A + (KF == 2 ? lds_pos(ko, flA, A) : ko)) * (int64_t)LB;
-    const int64_t row_m = ((h0 + blockIdx.y) * A + (KF == 2 ? lds_pos(km, flA, A) : km)) * (int64_t)LB;
+    auto source = [&](int blk) {                              // block blk = channel * (A / 2 + 1) + ko
+        const int h = blk / NR, ko = blk % NR;
+        return tmp + (natural ? (int64_t)blk : (int64_t)h * A + lds_pos(ko, flA, A)) * LB;
+    };
     auto put = [&](int64_t r, int f, float re, float im) {
         if constexpr (KF == 2) ((float2 *)kf)[r + G::index(f)] = make_float2(re, im);
         else ((uint32_t *)kf)[r + fused3_kf_slot_8192(f)] = KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
     };
+    float2 next[G::P];
+    load_row<G>(next, source(blockIdx.x), threadIdx.x);
+#pragma unroll 1
+    for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                         // nothing of a step's addresses and twiddles is kept for the next
+        float2 x[G::P];
 #pragma unroll
-    for (int p = 0; p < G::P; ++p) {
-        const int fi = G::freq(tid, p);
-        const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * scale : scale;
-        put(row, fi, x[p].x * sc, sgn * x[p].y * sc);
-        if (mirror) {
-            const int fm = LB - 1 - fi;
-            const float scm = keep ? lds_mask_weight(keep, n_blocks, km + A * fm, M) * scale : scale;
-            put(row_m, fm, x[p].x * scm, -sgn * x[p].y * scm);
+        for (int p = 0; p < G::P; ++p) x[p] = next[p];
+        load_row<G>(next, source(blk + (int)gridDim.x < blocks ? blk + (int)gridDim.x : blk), tid);
+        rf::Tw1<G> tw1;
+        tw1.load(tab, tid);
+        rf::row_barrier<G::T>();                              // the slots are free
+        rf::forward<G, false>(x, XL, tab, tw1, tid, [] {});
+        const int ko = blk % NR;
+        const int64_t h = h0 + blk / NR;
+        const bool mirror = ko > 0 && 2 * ko < A;
+        const int km = mirror ? A - ko : ko;
+        const int64_t row = (h * A + (KF == 2 ? lds_pos(ko, flA, A) : ko)) * LB;
+        const int64_t row_m = (h * A + (KF == 2 ? lds_pos(km, flA, A) : km)) * LB;
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) {
+            const int fi = G::freq(tid, p);
+            const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * scale : scale;
+            put(row, fi, x[p].x * sc, sgn * x[p].y * sc);
+            if (mirror) {
+                const int fm = LB - 1 - fi;
+                const float scm = keep ? lds_mask_weight(keep, n_blocks, km + A * fm, M) * scale : scale;
+                put(row_m, fm, x[p].x * scm, -sgn * x[p].y * scm);
+            }
         }
     }
 }
@@ -255,11 +269,11 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
 // unless first, and takes it unless last, when the inverse transform goes to out (which may be a block of tu).
 // The spectra and their sum stay in registers (one transform at a time: 192 data registers), where three kernels
 // wrote and read them.
-__global__ void __launch_bounds__(RX::T, 2) k_long_blocks_corr(const float2 *tu, const float2 *td, int64_t stride, int nb,
+__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(const float2 *tu, const float2 *td, int64_t stride, int nb,
                                                                float4 *acc, float2 *out, const float2 *__restrict__ tab, bool first,
                                                                bool last)
 {
-    using G = RX;
+    using G = RB;
     extern __shared__ float2 XL[];
     const int64_t base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * LB;
     const int tid = threadIdx.x;
@@ -435,7 +449,7 @@ int launch_corr(const fftconv_plan *p, int blocks, const float2 *tu, const float
 {
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_corr, B_LDS));
     hipLaunchKernelGGL(k_long_blocks_corr, dim3((unsigned)blocks, (unsigned)p->H), dim3(RB::T), B_LDS, s, tu, td, stride, (int)nb,
-                       (float4 *)acc, out, rf::row_table<RX>(p), first, last);
+                       (float4 *)acc, out, rf::row_table<RB>(p), first, last);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -496,8 +510,9 @@ int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 
 {
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF>, B_LDS));
     const float2 *tab = KF == 2 ? rf::row_table<RX>(p) : rf::row_table<RB>(p);
-    hipLaunchKernelGGL(k_long_blocks_kf<KF>, dim3((unsigned)(natural ? g.A / 2 + 1 : g.A), (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
-                       kf, tab, g.flA, g.A, h0, keep_dev, n_blocks, natural, conj_out);
+    const int64_t blocks = nh * (g.A / 2 + 1);                // at most 2^16 channels of 257
+    hipLaunchKernelGGL(k_long_blocks_kf<KF>, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(RB::T), B_LDS, s, tmp, kf, tab, g.flA,
+                       g.A, h0, (int)blocks, keep_dev, n_blocks, natural, conj_out);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

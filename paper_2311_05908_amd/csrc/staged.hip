@@ -288,8 +288,8 @@ int staged_init(fftconv_plan *p)
     if (chunk < 8) chunk = 8;
     if (chunk > p->H) chunk = p->H;
     p->filt_chunk = chunk;
-    FC_HIP(hipMalloc((void **)&p->filt_a, (size_t)(chunk * per_ch)));
-    FC_HIP(hipMalloc((void **)&p->filt_b, (size_t)(chunk * per_ch)));
+    FC_HIP(hipMalloc((void **)&p->filt_a, (size_t)(2 * chunk * per_ch)));
+    p->filt_b = p->filt_a + chunk * M;
     return FFTCONV_OK;
 }
 
@@ -298,7 +298,6 @@ void staged_destroy(fftconv_plan *p)
     if (p->st.w64) (void)hipFree(p->st.w64);
     if (p->st.w32) (void)hipFree(p->st.w32);
     if (p->filt_a) (void)hipFree(p->filt_a);
-    if (p->filt_b) (void)hipFree(p->filt_b);
     p->st.w64 = nullptr;
     p->st.w32 = nullptr;
     p->filt_a = p->filt_b = nullptr;
