@@ -518,7 +518,7 @@ int fftconv_backward_filter(const fftconv_plan *p, const void *u, const void *dy
     hipStream_t s = (hipStream_t)stream;
     if (B > 0 && f3::fused3_dk_supported(p)) {
         rc = f3::fused3_dk_accumulate(p, u, dy, workspace, B, s);       // 8192 accumulator slots per channel
-        if (!rc) rc = f3::fused3_dk_finish(p, workspace, dk, Nk, s);
+        if (!rc) rc = row_dk_finish(p, workspace, dk, Nk, s);
         return rc;
     }
     if (B > 0 && f3::fused3_big_dk_supported(p)) {

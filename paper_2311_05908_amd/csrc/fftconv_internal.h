@@ -253,7 +253,6 @@ int staged_backward_filter(const fftconv_plan *p, const void *u, const void *dy,
 namespace f3 {
 bool fused3_dk_supported(const fftconv_plan *p);
 int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s);
-int fused3_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s);
 // the same for fft 16384 plans (fused3_big.hip); dkf = H * 16384 float2
 bool fused3_big_dk_supported(const fftconv_plan *p);
 int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s);
@@ -270,6 +269,10 @@ bool row_backward_filter_ok(const fftconv_plan *p);
 size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B);
 int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace,
                         hipStream_t s);
+// the fp32 ends of the 8192-point matrix-core plans (row_filter.hip): taps -> k_f, accumulated spectra -> dk
+int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
+               int64_t n_blocks, uint2 *kf, hipStream_t s);
+int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s);
 // short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);
 FacList small_factor_list(int64_t M);      // its radices, outermost first

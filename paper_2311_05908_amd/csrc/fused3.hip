@@ -54,72 +54,12 @@
 #include <type_traits>
 
 #include "fused3_common.h"
-#include "lds_fft.h"
 
 namespace fftconv {
 
 namespace {
 
 using namespace f3;
-
-// Filter transform of the plans that run on the 8192-point kernel, one workgroup per channel and no
-// intermediate in HBM: taps -> LDS (zero padded, fp32), forward transform of length Ms = 8192 / groups in
-// LDS (the stages of the generic path, lds_fft.h; fp32 is ample for constants that are rounded to 16 bits),
-// then k_f[h] in the kernel's per-lane order, scaled by 1/Ms:
-//   slot d = (k1 * 4 + r) * 64 + lane holds k2 = lane % 16, k3 = k3_at_index(4 (lane / 16) + r), as 16-bit
-//   constant pairs for TT::ctw (fmt 1: bf16 dot-product form, fmt 2: fp16 packed form).
-// groups > 1: slot (k1, k2, k3) takes bin k1 % N1s + N1s (k2 + 16 k3) of the short spectrum, N1s = 32 / groups
-// (the same spectrum for every group), see build_tables().  reversed: see the adjoint filter transform.
-constexpr int FILT_THREADS = 512;
-__global__ void __launch_bounds__(FILT_THREADS) k_filter_fused3(const float *__restrict__ k, uint2 *__restrict__ kf,
-                                                               const float2 *__restrict__ w, FacList fl, int64_t Nk,
-                                                               int tws, bool reversed, const uint8_t *__restrict__ keep,
-                                                               int64_t n_blocks, int fmt, int groups)
-{
-    extern __shared__ float2 XF[];
-    constexpr int M = 8192;
-    const int Ms = M / groups, N1s = N1 / groups;
-    const int64_t h = blockIdx.x;
-    // all taps of the thread are requested before the first is used (a tap beyond Nk reads tap 0 and is discarded:
-    // behind a branch every load would be waited for in turn)
-    constexpr int TPT = M / FILT_THREADS;
-    float tap[TPT];
-#pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int n = threadIdx.x + j * FILT_THREADS;
-        const int t = (reversed && n != 0) ? Ms - n : n;
-        tap[j] = k[h * Nk + ((n < Ms && t < Nk) ? t : 0)];
-    }
-#pragma unroll
-    for (int j = 0; j < TPT; ++j) asm volatile("" ::"v"(tap[j]));
-#pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int n = threadIdx.x + j * FILT_THREADS;
-        const int t = (reversed && n != 0) ? Ms - n : n;
-        if (n < Ms) XF[lds_slot(n)] = make_float2(t < Nk ? tap[j] : 0.f, 0.f);
-    }
-    __syncthreads();
-    lds_forward(XF, w, fl, Ms, tws);
-    for (int d = threadIdx.x; d < M; d += FILT_THREADS) {
-        const int lane = d % 64, r = (d / 64) % 4, k1 = d / 256;
-        const int k2 = lane % 16, k3 = k3_at_index(4 * (lane / 16) + r, 16);
-        const int fs = (k1 % N1s) + N1s * (k2 + 16 * k3);                      // bin of the (sub-)transform
-        const float2 v = XF[lds_slot(lds_pos(fs, fl, Ms))];
-        const double sc = (double)lds_mask_weight(keep, n_blocks, fs, Ms) / (double)Ms;
-        uint2 c;
-        if (fmt == 1)
-            c = ctw_const(v.x * sc, v.y * sc, 1, [](double x) {
-                __hip_bfloat16 b = __float2bfloat16((float)x);
-                return *(uint16_t *)&b;
-            });
-        else
-            c = ctw_const(v.x * sc, v.y * sc, 2, [](double x) {
-                __half hv = __float2half_rn((float)x);
-                return *(uint16_t *)&hv;
-            });
-        kf[h * M + d] = c;
-    }
-}
 
 // ---------------------------------------------------------------- host side
 
@@ -486,24 +426,11 @@ bool fused3_short_ok(const fftconv_plan *p, int64_t Nk)
     return p->f3.consts_short != nullptr && Nk >= 1 && history_of(Nk) <= SHORT_MAX_P;
 }
 
-static int launch_filter_fused3(const float *k, int64_t Nk, int64_t H, uint2 *kf, const float2 *w, const FacList &fl,
-                                int64_t Ms, int64_t tws, bool reversed, const uint8_t *keep_dev, int64_t n_blocks, int fmt,
-                                hipStream_t s)
-{
-    const size_t bytes = lds_row_bytes(Ms, sizeof(float2));
-    FC_TRY(raise_dynamic_lds((const void *)k_filter_fused3, (int)lds_row_bytes(8192, sizeof(float2))));
-    hipLaunchKernelGGL(k_filter_fused3, dim3((unsigned)H), dim3(FILT_THREADS), bytes, s, k, kf, w, fl, Nk, (int)tws, reversed,
-                       keep_dev, n_blocks, fmt, (int)(8192 / Ms));
-    FC_HIP(hipGetLastError());
-    return FFTCONV_OK;
-}
-
 // the 8192-point spectrum of a short filter, behind the dense one (see fused3_forward_short)
 int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, hipStream_t s)
 {
     uint2 *dst = (uint2 *)((char *)kf + dense_kf_bytes(p));
-    return launch_filter_fused3(k, Nk, p->H, dst, p->st.w32, staged_factors_for(SHORT_M), SHORT_M, p->M / SHORT_M, false,
-                                nullptr, 1, p->dtype == FFTCONV_F16 ? 2 : 1, s);
+    return row_filter(p, k, Nk, SHORT_M, false, nullptr, 1, dst, s);
 }
 
 // Partial convolution (Section 3.3) of a plan for fft >= 16384: the filter covers Nk <= 2049 taps, so
@@ -532,8 +459,7 @@ int fused3_filter(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoin
     if (p->M > 8192) return fused3_big_filter(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s);
     // the 8192-point kernel takes k_f as 16-bit constant pairs; shorter transforms fill its 8192 slots with
     // 8192 / fft_size copies of their spectrum (see build_tables())
-    return launch_filter_fused3(k, Nk, p->H, (uint2 *)kf, p->st.w32, staged_fac_list(p), p->M, 1, adjoint, keep_dev,
-                                n_blocks, p->dtype == FFTCONV_F16 ? 2 : 1, s);
+    return row_filter(p, k, Nk, p->M, adjoint, keep_dev, n_blocks, (uint2 *)kf, s);
 }
 
 bool fused3_gates_fused(const fftconv_plan *p) { return p->path == PATH_FUSED3; }

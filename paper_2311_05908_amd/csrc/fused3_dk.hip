@@ -16,9 +16,8 @@
 //                        dy input that follows multiplies it in and adds to the channel's accumulator.
 // A workgroup owns whole channels, so the accumulator (fp32, 64 registers per lane) never leaves the
 // registers until the channel's last pair, when it is written out in the kernel's k_f order.  The
-// inverse transform of the H accumulated spectra runs afterwards, one workgroup per channel in LDS (k_dk_finish).
+// inverse transform of the H accumulated spectra runs afterwards (row_dk_finish, row_filter.hip).
 #include "fused3_common.h"
-#include "lds_fft.h"
 
 namespace fftconv {
 namespace f3 {
@@ -231,42 +230,6 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
     }
 }
 
-// dk_f in the kernel's order (slot (k1 * 4 + r) * 64 + lane as in the fused k_f layout) -> dk, one workgroup
-// per channel: the 8192 slots are read in order and scattered to their positions in LDS, the unnormalised
-// inverse transform of length Ms = 8192 / groups runs there (lds_fft.h), real part times 1/Ms of the first Nk
-// samples goes out.  groups > 1: bin k1' + N1s (k2 + 16 k3) of the short transform is the sum over the groups g
-// of the slots k1 = g N1s + k1'; the groups are added one after the other (a fixed order).
-constexpr int DK_FIN_THREADS = 512;
-__global__ void __launch_bounds__(DK_FIN_THREADS) k_dk_finish(const float2 *__restrict__ dkf, float *__restrict__ dk,
-                                                             const float2 *__restrict__ w, FacList fl, int64_t Nk, int groups)
-{
-    extern __shared__ float2 XD[];
-    const int Ms = G::M / groups, N1s = N1 / groups;
-    const int64_t h = blockIdx.x;
-    const int per_group = G::M / groups;                     // slots of one group: k1 in [g N1s, (g + 1) N1s)
-    for (int g = 0; g < groups; ++g) {
-#pragma unroll 4
-        for (int i = threadIdx.x; i < per_group; i += DK_FIN_THREADS) {
-            const int d = g * per_group + i;
-            const int lane = d % 64, r = (d / 64) % 4, k1 = d / 256;
-            const int k2 = lane % 16, k3 = k3_at_index(4 * (lane / 16) + r, 16);
-            const int fs = (k1 % N1s) + N1s * (k2 + 16 * k3);
-            const int slot = lds_slot(lds_pos(fs, fl, Ms));
-            float2 v = dkf[h * G::M + d];
-            if (g > 0) {
-                const float2 o = XD[slot];
-                v.x += o.x;
-                v.y += o.y;
-            }
-            XD[slot] = v;
-        }
-        __syncthreads();
-    }
-    lds_inverse(XD, w, fl, Ms, 1);
-    const float scale = 1.0f / (float)Ms;
-    for (int n = threadIdx.x; n < Nk; n += DK_FIN_THREADS) dk[h * Nk + n] = XD[lds_slot(n)].x * scale;
-}
-
 }  // namespace
 
 bool fused3_dk_supported(const fftconv_plan *p) { return p->path == PATH_FUSED3 && p->M <= G::M; }
@@ -296,15 +259,6 @@ int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, v
     const int grid = (int)(p->H < p->f3.num_cu ? p->H : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), DK_LDS_BYTES, s, (const uint16_t *)u, (const uint16_t *)dy,
                        (float2 *)dkf, consts_at<16, 16>(p->f3.consts), (int)B, (int)p->H, (int)p->N, groups, lg_half);
-    FC_HIP(hipGetLastError());
-    return FFTCONV_OK;
-}
-
-int fused3_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s)
-{
-    FC_TRY(raise_dynamic_lds((const void *)k_dk_finish, (int)lds_row_bytes(G::M, sizeof(float2))));
-    hipLaunchKernelGGL(k_dk_finish, dim3((unsigned)p->H), dim3(DK_FIN_THREADS), lds_row_bytes(p->M, sizeof(float2)), s,
-                       (const float2 *)dkf, dk, (const float2 *)p->st.w32, staged_fac_list(p), Nk, (int)(G::M / p->M));
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

@@ -1,0 +1,191 @@
+// The two ends of the 8192-point matrix-core plans (fft_size 256 .. 8192) that are computed in fp32, on the row engine
+// (row_fft.h): the filter transform, taps -> k_f, and the tail of the filter gradient, accumulated spectra -> dk.  One row
+// of threads per channel, nothing in memory in between.
+//
+// The frequency digits of the kernels' slots are those of the engine's registers or multiples of them (8192: k1, k2, k3 are
+// its digits 0, 1, 2), so both ends move 8-byte slots in runs of 8 or 16 lanes straight between memory and registers.
+// Plans below 8192 keep G = 8192 / fft_size copies of the spectrum (of the sum, in the gradient: one per group, see
+// build_tables() in fused3.hip): slot k1 of group g is g (32 / G) + k1'.
+// Up to 1024 points a row is part of one wave and most of the work is the copies: there a workgroup takes one channel, and all
+// of it moves the 64 KB, through an image of one group in LDS.
+// Bound by the 64 KB a channel that k_f and the accumulated spectra take.  768 channels of 4096 taps, fft 8192: filter
+// transform 40 -> 27 us, tail of the gradient 46 -> 24 (with every factor a trip through LDS and gathered twiddles before).
+#include "fftconv_internal.h"
+#include "lds_fft.h"
+#include "row_io.h"
+
+namespace fftconv {
+
+namespace {
+
+using rf::Row;
+
+constexpr int SLOTS = 8192;                                       // of a channel, whatever the transform's length
+
+template <int M> constexpr bool IMAGE = M <= 1024;                // one channel per workgroup, one group's slots in LDS
+template <int M> constexpr int ROWS = IMAGE<M> ? 1 : rf::threads_of(M) / Row<M>::T;      // channels per workgroup
+template <int M> constexpr int LDS_BYTES = ROWS<M> * Row<M>::LDS_BYTES + (IMAGE<M> ? 8 * M : 0);
+
+// slot of bin f of a transform of M points, group 0; the groups follow M slots apart
+template <int M> __device__ __forceinline__ int slot_of(int f)
+{
+    constexpr int N1 = M / 256;
+    const int k1 = f % N1, k2 = f / N1 % 16, idx = k3_index(f / N1 / 16, 16);
+    return (k1 * 4 + idx % 4) * 64 + idx / 4 * 16 + k2;
+}
+
+// HALF: Nk <= M / 2.  conj_out: the conjugate spectrum, that of the circularly time-reversed taps, which are real.  k_f
+// scaled by 1/M and by the frequency mask, as the constants of TT::ctw (bf16 dot-product form, fp16 packed form).
+template <int M, bool F16, bool HALF>
+__global__ void __launch_bounds__(rf::threads_of(M), 2)
+    k_row_filter(const float *__restrict__ k, uint2 *__restrict__ kf, const float2 *__restrict__ tab, int H, int64_t Nk, bool conj_out,
+                 const uint8_t *__restrict__ keep, int64_t n_blocks)
+{
+    using G = Row<M>;
+    constexpr int RW = ROWS<M>, MIN = HALF ? G::P / 2 : G::P, NTHR = rf::threads_of(M);
+    extern __shared__ float2 smem_rows[];
+    const int row = IMAGE<M> ? 0 : threadIdx.x / G::T, tid = IMAGE<M> ? threadIdx.x : threadIdx.x % G::T;
+    const int h = min((int)blockIdx.x * RW + row, H - 1);         // rows beyond the last one repeat it, unstored
+    float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
+    uint2 *const image = (uint2 *)((char *)smem_rows + G::LDS_BYTES);
+    uint2 *const o = kf + (int64_t)h * SLOTS;
+    if (!IMAGE<M> || tid < G::T) {
+        float tap[MIN];
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const int n = tid + G::T * m;
+            tap[m] = k[h * Nk + (n < Nk ? n : 0)];
+        }
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(tap[m]));   // the loads stay unconditional
+        float2 x[G::P];
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) x[m] = make_float2(tid + G::T * m < Nk ? tap[m] : 0.f, 0.f);
+        rf::Tw1<G> tw1;
+        tw1.load(tab, tid);
+        rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
+        if ((int)blockIdx.x * RW + row >= H) return;
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) {
+            const int f = G::freq(tid, p), d = slot_of<M>(f);
+            const float sc = keep ? lds_mask_weight(keep, n_blocks, f, M) / M : 1.f / M;
+            const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
+            uint2 c;
+            if constexpr (F16) c = make_uint2(f3::F16::pack(re, re), f3::F16::pack(-im, im));
+            else c = make_uint2(f3::BF16::pack(re, -im), f3::BF16::pack(im, re));
+            if constexpr (IMAGE<M>) {
+                image[d] = c;
+            } else {
+#pragma unroll
+                for (int g = 0; g < SLOTS / M; ++g) o[g * M + d] = c;
+            }
+        }
+    }
+    if constexpr (IMAGE<M>) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < SLOTS; i += NTHR) o[i] = image[i % M];
+    }
+}
+
+// dk[h][n] = Re(inverse transform)[n] / M, n < Nk, of the sum of the groups' spectra (added one after the other).
+template <int M>
+__global__ void __launch_bounds__(rf::threads_of(M), 2)
+    k_row_dk_finish(const float2 *__restrict__ dkf, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk)
+{
+    using G = Row<M>;
+    constexpr int RW = ROWS<M>, NTHR = rf::threads_of(M);
+    extern __shared__ float2 smem_rows[];
+    const int row = IMAGE<M> ? 0 : threadIdx.x / G::T, tid = IMAGE<M> ? threadIdx.x : threadIdx.x % G::T;
+    const int h = min((int)blockIdx.x * RW + row, H - 1);
+    float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
+    float2 x[G::P];
+    const float2 *in = dkf + (int64_t)h * SLOTS;
+    if constexpr (IMAGE<M>) {
+        float2 *const image = (float2 *)((char *)smem_rows + G::LDS_BYTES);
+#pragma unroll
+        for (int d = threadIdx.x; d < M; d += NTHR) {
+            float2 v[SLOTS / M];
+#pragma unroll
+            for (int g = 0; g < SLOTS / M; ++g) v[g] = in[g * M + d];
+#pragma unroll
+            for (int g = 1; g < SLOTS / M; ++g) {
+                v[0].x += v[g].x;
+                v[0].y += v[g].y;
+            }
+            image[d] = v[0];
+        }
+        __syncthreads();
+        if (tid >= G::T) return;
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) x[p] = image[slot_of<M>(G::freq(tid, p))];
+    } else {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) x[p] = in[slot_of<M>(G::freq(tid, p))];
+#pragma unroll
+        for (int g = 1; g < SLOTS / M; ++g) {
+            float2 v[G::P];
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) v[p] = in[g * M + slot_of<M>(G::freq(tid, p))];
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) {
+                x[p].x += v[p].x;
+                x[p].y += v[p].y;
+            }
+        }
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::inverse<G>(x, Z, tab, tw1, tid);
+    if ((int)blockIdx.x * RW + row >= H) return;
+    float *const o = dk + (int64_t)h * Nk;
+#pragma unroll
+    for (int m = 0; m < G::P; ++m) {
+        const int n = tid + G::T * m;
+        if (n < Nk) o[n] = x[m].x * (1.f / M);
+    }
+}
+
+}  // namespace
+
+// k_f (H, 8192 slots) of the 8192-point kernels for a transform of Ms = 256 .. 8192 points (min(fft_size, 8192): plans above
+// keep the spectrum of a short filter this way)
+int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
+               int64_t n_blocks, uint2 *kf, hipStream_t s)
+{
+    return rf::with_row(Ms, [&](auto g) -> int {
+        using G = decltype(g);
+        if constexpr (G::M > SLOTS) {
+            return FFTCONV_EUNSUPPORTED;
+        } else {
+            constexpr int M = G::M, NTHR = rf::threads_of(M), RW = ROWS<M>, lds = LDS_BYTES<M>;
+            const bool f16 = p->dtype == FFTCONV_F16, half = 2 * Nk <= M;
+            auto kern = f16 ? (half ? k_row_filter<M, true, true> : k_row_filter<M, true, false>)
+                            : (half ? k_row_filter<M, false, true> : k_row_filter<M, false, false>);
+            FC_TRY(raise_dynamic_lds((const void *)kern, lds));
+            hipLaunchKernelGGL(kern, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, k, kf, rf::row_table<G>(p), (int)p->H,
+                               Nk, conj_out, keep_dev, n_blocks);
+            FC_HIP(hipGetLastError());
+            return FFTCONV_OK;
+        }
+    });
+}
+
+// dkf: H * 8192 float2 in the kernels' slot order
+int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s)
+{
+    return rf::with_row(p->M, [&](auto g) -> int {
+        using G = decltype(g);
+        if constexpr (G::M > SLOTS) {
+            return FFTCONV_EUNSUPPORTED;
+        } else {
+            constexpr int NTHR = rf::threads_of(G::M), RW = ROWS<G::M>, lds = LDS_BYTES<G::M>;
+            FC_TRY(raise_dynamic_lds((const void *)k_row_dk_finish<G::M>, lds));
+            hipLaunchKernelGGL(k_row_dk_finish<G::M>, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float2 *)dkf,
+                               dk, rf::row_table<G>(p), (int)p->H, Nk);
+            FC_HIP(hipGetLastError());
+            return FFTCONV_OK;
+        }
+    });
+}
+
+}  // namespace fftconv

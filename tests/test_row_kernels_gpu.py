@@ -64,3 +64,31 @@ def test_row_gradient_edges(M, dtype):
 ])
 def test_row_gradient_runs(B, H, M):
     check_row_gradient("f32", B, H, 40, M, 50, None)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
+def test_row_filter_edges(M, dtype):
+    """The filter transform and the tail of the filter gradient of the matrix-core plans: filters of up to fft/2 taps skip
+    the padded half, longer ones do not; H = 9 leaves workgroups of several channels partly empty."""
+    w = synth.scaled(W["cfg1"], B=3, H=9, N=M // 2, fft_size=M, dtype=dtype, alpha=(1e-2, 1e-1))
+    u, dy = synth.gen_u(w), synth.gen_gate(w, "dy")
+    plan = fftconv.Plan(M // 2, M, 9, dtype)
+    assert plan.path == "fused3"
+    for Nk in (1, M // 2 - 1, M // 2, M // 2 + 1, M):
+        k = torch.randn(9, Nk, generator=torch.Generator().manual_seed(Nk))
+        y = plan.forward(u.cuda(), plan.filter_fft(k.cuda()))
+        du = plan.backward_input(dy.cuda(), plan.filter_fft_adjoint(k.cuda()))
+        # all M samples of dk against the reference (an error relative to a few of them is one draw of the rounding errors, not
+        # their size), a shorter dk against those
+        dk = plan.backward_filter(u.cuda(), dy.cuda(), M)
+        assert torch.equal(plan.backward_filter(u.cuda(), dy.cuda(), Nk), dk[:, :Nk])
+        kd = torch.zeros(9, M, dtype=torch.float64)
+        kd[:, :Nk] = k
+        K, U, D = torch.fft.rfft(kd), torch.fft.rfft(u.double(), M), torch.fft.rfft(dy.double(), M)
+        for name, got, ref in (("y", y, torch.fft.irfft(U * K, M)[..., :M // 2]),
+                               ("du", du, torch.fft.irfft(D * K.conj(), M)[..., :M // 2]),
+                               ("dk", dk, torch.fft.irfft((U.conj() * D).sum(0), M))):
+            err = parity_error(got.cpu().double().numpy(), ref.numpy(), TOL[dtype], name)
+            print("row filter %s M=%d Nk=%d %s err=%.3e" % (dtype, M, Nk, name, err), flush=True)
+            assert err <= TOL[dtype]
