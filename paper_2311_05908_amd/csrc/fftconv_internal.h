@@ -227,6 +227,15 @@ __host__ __device__ inline int multipass_row_slot(int r, bool quarter)
     return quarter ? ((r & 12) << 9) | ((r >> 8) << 6) | (((r >> 4) & 15) << 2) | (r & 3) : r;
 }
 
+// slot of bin f of a transform of M = 256 .. 8192 points in the k_f of the 8192-point kernels (shorter transforms: of group 0,
+// the groups' copies follow M slots apart)
+template <int M> __host__ __device__ inline int kernel_slot(int f)
+{
+    constexpr int N1 = M / 256;
+    const int k1 = f % N1, k2 = f / N1 % 16, idx = k3_index(f / N1 / 16, 16);
+    return (k1 * 4 + idx % 4) * 64 + idx / 4 * 16 + k2;
+}
+
 // slot of inner frequency fi (< 8192) in the 8192-point kernel's per-lane k_f order
 __host__ __device__ inline int fused3_kf_slot_8192(int64_t fi)
 {
@@ -264,6 +273,10 @@ std::vector<float2> row_tables(int64_t M, const double2 *w);
 int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
                 void *kf, hipStream_t s);
 int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
+// the convolution of a matrix-core plan up to fft_size 4096 on them, and whether a call has few enough rows for it
+bool row_few(const fftconv_plan *p, int64_t B);
+int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
+                    hipStream_t s);
 // the filter gradient on the same rows (row_grad.hip): plans up to fft_size 16384 without a matrix-core gradient kernel
 bool row_backward_filter_ok(const fftconv_plan *p);
 size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B);

@@ -40,7 +40,6 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
 {
     using G = ConvRow<M, IO>;
     constexpr int RW = rf::threads_of(M) / G::T;                  // rows (pairs) per workgroup
-    constexpr int MIN = HALF ? G::R0 / 2 : G::R0;                 // registers that can hold samples
     extern __shared__ float2 smem_rows[];
     const int group = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
     if ((int64_t)group * RW >= total) return;
@@ -51,10 +50,8 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     const bool two = 2 * pair + 1 < B;
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
-    const bool exact = N == MIN * G::T;                           // every sample of the registers exists
+    const bool exact = N == (HALF ? G::R0 / 2 : G::R0) * G::T;    // every sample of the registers exists
     const bool words = rf::word_rows<IO>(u, y, N);
-    const int odd = tid & 1;
-    const int64_t wrow = (odd ? r1 : r0) - odd;                   // its row, so that element wrow + n starts its word
 
     float2 x[G::P];
     rf::load_pair<G, IO, HALF>(x, u + r0, u + r1, N, tid, exact, words, true, two);
@@ -76,27 +73,8 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
         x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
     }
     rf::inverse<G>(x, Z, tab, tw1, tid);
-    if (!live) return;
     // real part -> row b, imaginary part -> row b + 1
-    if (words) {
-        const uint32_t sel = odd ? 0x03020706u : 0x05040100u;     // even: own.re, other.re; odd: other.im, own.im
-        const bool put = two || !odd;
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            const uint32_t z = rf::pack<IO>(x[m].x, x[m].y);
-            const uint32_t o = __builtin_amdgcn_perm(rf::neighbour(z), z, sel);
-            if (put && (exact || tid + G::T * m < N)) *(uint32_t *)(y + wrow + tid + G::T * m) = o;
-        }
-    } else {
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            const int n = tid + G::T * m;
-            if (exact || n < N) {
-                rf::st(y, r0 + n, x[m].x);
-                if (two) rf::st(y, r1 + n, x[m].y);
-            }
-        }
-    }
+    if (live) rf::store_pair<G, IO, HALF>(x, y + r0, y + r1, N, tid, exact, words, two);
 }
 
 // the fp64 spectra of the filters in the order of the kernel above
@@ -113,6 +91,57 @@ __global__ void k_pack_rows(const double2 *spec, float2 *kf, FacList fl, int64_t
     const double2 v = spec[h * M + freq_to_pos(f, fl, M)];
     const double sc = mask_weight(keep, n_blocks, f, M) / (double)M;
     kf[(h0 + h) * M + d] = make_float2((float)(v.x * sc), (float)(v.y * sc));
+}
+
+// The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
+// with their k_f: 16-bit constant pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
+// wg multiplies u, bit 1: vg multiplies y), in fp32.  For calls of few rows: see row_forward_few().
+template <int M, typename IO, int GATE>
+__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
+    k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint2 *__restrict__ kf, const float2 *__restrict__ tab,
+                   const IO *__restrict__ wg, const IO *__restrict__ vg, int B, int H, int N, int npairs, int total)
+{
+    using G = Row<M>;
+    constexpr int RW = rf::threads_of(M) / G::T;
+    extern __shared__ float2 smem_rows[];
+    const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
+    const int t = min((int)blockIdx.x * RW + row, total - 1);
+    const bool live = (int)blockIdx.x * RW + row < total;
+    const int h = t / npairs, pair = t - h * npairs;
+    const bool two = 2 * pair + 1 < B;
+    const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
+    float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
+    const bool exact = N == M / 2;
+    float2 x[G::P];
+    rf::load_pair<G, IO, true>(x, u + r0, u + r1, N, tid, exact, true, true, two);
+    if constexpr (GATE & 1) {
+        float2 g[G::P];
+        rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
+#pragma unroll
+        for (int m = 0; m < G::P / 2; ++m) x[m] = make_float2(x[m].x * g[m].x, x[m].y * g[m].y);
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    uint2 kv[G::P];
+    const uint2 *kr = kf + (int64_t)h * 8192;
+    rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) kv[p] = kr[kernel_slot<M>(G::freq(tid, p))];
+    });
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) {                              // bf16: (re, -im), (im, re); fp16: (re, re), (-im, im)
+        const float re = rf::unpack<IO>(kv[p].x).x;
+        const float2 c = rf::unpack<IO>(kv[p].y);
+        x[p] = rf::mul(x[p], make_float2(re, std::is_same<IO, __half>::value ? c.y : c.x));
+    }
+    rf::inverse<G>(x, Z, tab, tw1, tid);
+    if constexpr (GATE & 2) {
+        float2 g[G::P];
+        rf::load_pair<G, IO, true>(g, vg + r0, vg + r1, N, tid, exact, true, true, two);
+#pragma unroll
+        for (int m = 0; m < G::P / 2; ++m) x[m] = make_float2(x[m].x * g[m].x, x[m].y * g[m].y);
+    }
+    if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }
 
 template <int M, typename IO, bool HALF>
@@ -200,6 +229,50 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
         }
         set_error("row kernels: no 16-bit instance for rows of %lld points", (long long)p->M);
         return FFTCONV_EUNSUPPORTED;
+    });
+}
+
+// Few rows: the wave-specialised kernel needs 8 us for a call whatever its size (tables, a pipeline of four steps) and
+// 2.8 us for every 256 work items (a channel's 2 * 8192 / fft rows each, however few there are); the row kernel starts at
+// 4.5 - 9 us and spends about 2.9 ps on a point, twice as much as a full work item.  So it takes the calls with
+//     points of all transforms  <  800 * 1024 + 4096 * work items
+// (shortest rows: more waves, cheaper points; 1024 points a row: the longest chain in one wave, from 8.7 us of the other
+// kernel on it is the faster only if there is more than one item for every second compute unit).  Measured, us, bf16, one kernel
+// against the other, 768 channels: fft 4096, B = 1 / 2 / 4: 18 -> 14, 19 -> 15, (19, 25); 2048, B = 4 / 8: 19 -> 15, (20, 25);
+// 1024, B = 8 / 16: 19 -> 15, (20, 23); 512, B = 1 / 16: 18 -> 8, 19 -> 12; 256, B = 1 / 32: 17 -> 5, 19 -> 8; 16 channels,
+// fft 4096, B = 1 / 32: 9 -> 7, 9 -> 8.  At 8192 points it never was (16 channels: 8.8 against 12.8).
+bool row_few(const fftconv_plan *p, int64_t B)
+{
+    const int64_t M = p->M;
+    if (M > 4096) return false;
+    const int64_t npairs = (B + 1) / 2, groups = 8192 / M, items = p->H * ((npairs + groups - 1) / groups);
+    const int64_t points = p->H * npairs * (M == 256 ? 128 : M == 512 ? 384 : M);
+    return points < 800 * 1024 + 4096 * items && (M != 1024 || items > 128);
+}
+
+int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
+                    hipStream_t s)
+{
+    return rf::with_row(p->M, [&](auto g) -> int {
+        constexpr int M = decltype(g)::M;
+        if constexpr (M > 4096) {
+            return FFTCONV_EUNSUPPORTED;
+        } else {
+            auto go = [&](auto io) -> int {
+                using IO = decltype(io);
+                constexpr int NTHR = rf::threads_of(M), RW = NTHR / Row<M>::T, lds = RW * Row<M>::LDS_BYTES;
+                auto kern = wg ? (vg ? k_row_conv_few<M, IO, 3> : k_row_conv_few<M, IO, 1>)
+                               : (vg ? k_row_conv_few<M, IO, 2> : k_row_conv_few<M, IO, 0>);
+                const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
+                FC_TRY(raise_dynamic_lds((const void *)kern, lds));
+                hipLaunchKernelGGL(kern, dim3((unsigned)((total + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
+                                   (const uint2 *)kf, rf::row_table<Row<M>>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,
+                                   (int)p->N, (int)npairs, (int)total);
+                FC_HIP(hipGetLastError());
+                return FFTCONV_OK;
+            };
+            return p->dtype == FFTCONV_F16 ? go(__half()) : go(__hip_bfloat16());
+        }
     });
 }
 

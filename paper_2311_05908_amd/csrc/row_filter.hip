@@ -26,14 +26,6 @@ template <int M> constexpr bool IMAGE = M <= 1024;                // one channel
 template <int M> constexpr int ROWS = IMAGE<M> ? 1 : rf::threads_of(M) / Row<M>::T;      // channels per workgroup
 template <int M> constexpr int LDS_BYTES = ROWS<M> * Row<M>::LDS_BYTES + (IMAGE<M> ? 8 * M : 0);
 
-// slot of bin f of a transform of M points, group 0; the groups follow M slots apart
-template <int M> __device__ __forceinline__ int slot_of(int f)
-{
-    constexpr int N1 = M / 256;
-    const int k1 = f % N1, k2 = f / N1 % 16, idx = k3_index(f / N1 / 16, 16);
-    return (k1 * 4 + idx % 4) * 64 + idx / 4 * 16 + k2;
-}
-
 // HALF: Nk <= M / 2.  conj_out: the conjugate spectrum, that of the circularly time-reversed taps, which are real.  k_f
 // scaled by 1/M and by the frequency mask, as the constants of TT::ctw (bf16 dot-product form, fp16 packed form).
 template <int M, bool F16, bool HALF>
@@ -67,7 +59,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
         if ((int)blockIdx.x * RW + row >= H) return;
 #pragma unroll
         for (int p = 0; p < G::P; ++p) {
-            const int f = G::freq(tid, p), d = slot_of<M>(f);
+            const int f = G::freq(tid, p), d = kernel_slot<M>(f);
             const float sc = keep ? lds_mask_weight(keep, n_blocks, f, M) / M : 1.f / M;
             const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
             uint2 c;
@@ -117,15 +109,15 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
         __syncthreads();
         if (tid >= G::T) return;
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = image[slot_of<M>(G::freq(tid, p))];
+        for (int p = 0; p < G::P; ++p) x[p] = image[kernel_slot<M>(G::freq(tid, p))];
     } else {
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = in[slot_of<M>(G::freq(tid, p))];
+        for (int p = 0; p < G::P; ++p) x[p] = in[kernel_slot<M>(G::freq(tid, p))];
 #pragma unroll
         for (int g = 1; g < SLOTS / M; ++g) {
             float2 v[G::P];
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) v[p] = in[g * M + slot_of<M>(G::freq(tid, p))];
+            for (int p = 0; p < G::P; ++p) v[p] = in[g * M + kernel_slot<M>(G::freq(tid, p))];
 #pragma unroll
             for (int p = 0; p < G::P; ++p) {
                 x[p].x += v[p].x;

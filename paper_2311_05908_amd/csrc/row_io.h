@@ -102,6 +102,35 @@ __device__ __forceinline__ void load_pair(float2 (&x)[G::P], const IO *__restric
     }
 }
 
+// The way back: x[m].x -> sample tid + T m of row r0, x[m].y -> r1 (two), below N.
+template <typename G, typename IO, bool HALF>
+__device__ __forceinline__ void store_pair(const float2 (&x)[G::P], IO *__restrict__ r0, IO *__restrict__ r1, int N, int tid,
+                                           bool exact, bool words, bool two)
+{
+    constexpr int MIN = HALF ? G::R0 / 2 : G::R0;
+    if (words) {
+        const int odd = tid & 1;
+        IO *const wrow = (odd ? r1 : r0) - odd;
+        const uint32_t sel = odd ? 0x03020706u : 0x05040100u;     // even: own.re, other.re; odd: other.im, own.im
+        const bool put = two || !odd;
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const uint32_t z = pack<IO>(x[m].x, x[m].y);
+            const uint32_t o = __builtin_amdgcn_perm(neighbour(z), z, sel);
+            if (put && (exact || tid + G::T * m < N)) *(uint32_t *)(wrow + tid + G::T * m) = o;
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const int n = tid + G::T * m;
+            if (exact || n < N) {
+                st(r0, n, x[m].x);
+                if (two) st(r1, n, x[m].y);
+            }
+        }
+    }
+}
+
 // calls f(Row<M>()) for the row length of the plan
 template <typename F> int with_row(int64_t M, F f)
 {

@@ -92,3 +92,39 @@ def test_row_filter_edges(M, dtype):
             err = parity_error(got.cpu().double().numpy(), ref.numpy(), TOL[dtype], name)
             print("row filter %s M=%d Nk=%d %s err=%.3e" % (dtype, M, Nk, name, err), flush=True)
             assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,N,M", [
+    (1, 5, 128, 256), (3, 17, 120, 256),        # rows of a part of a wave, partly empty workgroups, a lone row
+    (2, 3, 256, 512), (5, 9, 8, 512),
+    (1, 150, 512, 1024),                        # only with more than 128 work items
+    (3, 3, 1024, 2048), (1, 2, 1000, 2048),
+    (1, 3, 2048, 4096), (2, 1, 2040, 4096), (9, 2, 16, 4096),
+])
+def test_few_rows(dtype, B, H, N, M):
+    """Calls of few rows on matrix-core plans up to fft 4096: with the plan's 16-bit k_f, with none, one or both gates, against
+    the oracle; the same rows in a batch that is large enough for the matrix-core kernel agree within both kernels' errors."""
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype, alpha=(1e-2, 1e-1))
+    u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
+    k = synth.gen_k(w)
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.path == "fused3"
+    kf = plan.filter_fft(torch.from_numpy(k).cuda())
+    for wg, vg in ((None, None), (g, None), (None, v), (g, v)):
+        cu = [None if t is None else t.cuda() for t in (wg, vg)]
+        y = plan.forward_gated(u.cuda(), cu[0], cu[1], kf)
+        torch.cuda.synchronize()
+        ud = u.double().numpy() * (1.0 if wg is None else wg.double().numpy())
+        ref = oracle.fftconv(ud, k, M)
+        weight = None
+        if vg is not None:
+            ref, weight = ref * vg.double().numpy(), abs(vg.double().numpy())
+        err = parity_error(y.cpu().double().numpy(), ref, TOL[dtype], "y", weight=weight)
+        print("few rows %s B=%d H=%d N=%d M=%d gates=%d%d err=%.3e" % (dtype, B, H, N, M, wg is not None, vg is not None, err),
+              flush=True)
+        assert err <= TOL[dtype]
+    reps = 2 * 8192 // M * 40                                     # batches of work items for the matrix-core kernel
+    many = plan.forward(u.cuda().repeat(reps, 1, 1), kf)[:B]
+    one = plan.forward(u.cuda(), kf)
+    assert parity_error(many.cpu().double().numpy(), one.cpu().double().numpy(), 2 * TOL[dtype]) <= 2 * TOL[dtype]
