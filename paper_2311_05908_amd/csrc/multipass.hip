@@ -119,6 +119,9 @@ template <bool F16> __device__ __forceinline__ uint32_t mul_pair16(uint32_t a, u
 
 struct OuterGeo {
     int No, Ra, Rb, CT;          // outer length, its two factors, columns per block
+    // of the passes over real rows: column pairs per block (the same tile), and the tile's bytes
+    int pairs() const { return Rb == 1 ? CT / 2 : CT; }
+    size_t lds() const { return Rb == 1 ? 0 : sizeof(float2) * ((size_t)No + (size_t)No * CT); }
 };
 
 // ---- pass A: zero-padded pair of real rows -> outer forward DFT (No = RA * RB) -> twiddle -> S.
@@ -127,6 +130,11 @@ struct OuterGeo {
 // Step 1: for every b2 < RB the length-RA transform over a (unless FULLN, inputs a >= RA/2 are the
 // implicit zeros), times W_No^{ka b2}, into the fp32 LDS tile T[ka*RB + b2][c].  Step 2: for every ka the
 // length-RB transform over b2, times W_M^{r ko} (ko = ka + RA kb, by recurrence over kb), to S.
+// RB == 1 (No <= 16; all six outer kernels): a thread reads every outer row of its two columns, transforms them in registers
+// and writes every row; no tile, no barrier, 8 or 16 loads of a thread in flight instead of one per trip of a loop.  Bound by
+// the copy of the bytes.  Same operations on the same values as through the tile.  us, before and after: fft 131072, 2 x 256 x 65536
+// bf16: pass A 54 -> 40 (201 MB), pass C 67 -> 52, gradient: rows of u and dy 39 -> 36 each, last pass 56 -> 37; fft 32768,
+// 5 x 256 x 10007: A 29 -> 21, C 30 -> 17, lone row 13 -> 9 and 13 -> 8.
 // EXACT (all four outer kernels): N is even and equals the input length the instantiation is for (M/2, or M
 // with FULLN), so every load of u and store of y is in range, 4-byte aligned and unconditional: the compiler
 // can then issue a thread's loads back to back instead of one guarded load at a time.
@@ -155,8 +163,12 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
     const bool wide = CV == 2 && (EXACT || N % 2 == 0);       // rows start 4-byte aligned
     const int CG = CT / CV;                        // column groups, a power of two
     const int lgCG = 31 - __builtin_clz(CG);
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
+    const float ihm = 2.0f / (float)M;
+    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     for (int e = tid; e < RB * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, b2 = e >> lgCG;
         uint32_t in0[RAIN], in1[RAIN];             // CV 16-bit values of row b / row b+1
@@ -214,6 +226,33 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
                 in1[a] = mul_pair16<F16>(in1[a], gt1[a]);
             }
         }
+        if constexpr (RB == 1) {
+            uint32_t o[RA][CV];
+#pragma unroll
+            for (int v = 0; v < CV; ++v) {
+                float2 x[RA];
+#pragma unroll
+                for (int a = 0; a < RA; ++a) {
+                    x[a] = make_float2(0.f, 0.f);
+                    if (a < RAIN) x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
+                }
+                dft_reg<RA, false, !FULLN>(x);
+                const int r = r0 + c + v;
+#pragma unroll
+                for (int ka = 0; ka < RA; ++ka) {
+                    const float2 t = cmulf(x[ka], wm((r * ka) & Mmask, ihm));
+                    o[ka][v] = (uint32_t)cv16<F16>(t.x) | ((uint32_t)cv16<F16>(t.y) << 16);
+                }
+            }
+            uint32_t *dst = &S[(size_t)ph * No * MI + multipass_row_slot(r0 + c, multipass_quarter_rows(No))];
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka)
+                if (ko_lo >= ko_hi || ka < ko_lo || ka >= ko_hi) {        // (a zeroed part of the spectrum is never used)
+                    if constexpr (CV == 2) *(uint2 *)(dst + (size_t)ka * MI) = make_uint2(o[ka][0], o[ka][1]);
+                    else dst[(size_t)ka * MI] = o[ka][0];
+                }
+            continue;
+        }
         float2 o[RA][CV];
 #pragma unroll
         for (int v = 0; v < CV; ++v) {
@@ -237,9 +276,8 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
                 *dst = o[ka][0];
         }
     }
+    if constexpr (RB == 1) return;
     __syncthreads();
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     for (int e = tid; e < RA * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, ka = e >> lgCG;
         uint32_t o[RB][CV];
@@ -301,8 +339,10 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     const bool wide = CV == 2 && (EXACT || N % 2 == 0);
     const int CG = CT / CV;
     const int lgCG = 31 - __builtin_clz(CG);
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
     const float ihm = 2.0f / (float)M;
     const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     // step 1: T[ka*RB + b2] = conj(W_No^{ka b2}) * sum_{kb} conj(W_RB^{b2 kb}) conj(W_M^{r ko}) S[ko], ko = ka + RA kb
@@ -312,7 +352,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     // so the value that enters the inverse is conj(S[ko']) conj(conj(W_Mi^{r}) W_M^{r ko}): the mirror row is
     // read and conjugated (a sign flip on the packed word), and from the first mirrored row on the twiddle of the
     // recurrence carries the extra factor conj(W_Mi^{r}).
-    for (int e = tid; e < RA * CG; e += TB) {
+    for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, ka = e >> lgCG;
         uint32_t in[RB][CV];
 #pragma unroll
@@ -385,7 +425,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
                 *dst = o[b2][0];
         }
     }
-    __syncthreads();
+    if constexpr (RB > 1) __syncthreads();
     // step 2: z[a*RB + b2] = sum_{ka} conj(W_RA^{a ka}) T[ka*RB + b2], kept for a < RAIN (n < M/2 unless FULLN)
     uint16_t *row0 = y + ((size_t)b0 * H + h) * N;
     uint16_t *row1 = y + ((size_t)(b0 + (two ? 1 : 0)) * H + h) * N;
@@ -394,6 +434,35 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     const uint16_t *g1 = GATED ? vg + ((size_t)(b0 + (two ? 1 : 0)) * H + h) * N : nullptr;
     for (int e = tid; e < RB * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, b2 = e >> lgCG;
+        // RB == 1: a thread reads all rows of its columns and no tile lies in between
+        uint32_t in[RB == 1 ? RA : 1][CV];
+        if constexpr (RB == 1) {
+            auto mirrored = [](int ka) { return MIRROR && ka > RA / 2; };
+            auto dead = [&](int ka) { return ka >= ko_lo && ka < ko_hi; };
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka) {
+                const uint32_t *src = &S[((size_t)ph * No + (dead(ka) ? 0 : (mirrored(ka) ? No - ka : ka))) * MI +
+                                         multipass_row_slot(r0 + c, multipass_quarter_rows(No))];
+                if constexpr (CV == 2) {
+                    const uint2 t = *(const uint2 *)src;
+                    in[ka][0] = t.x;
+                    in[ka][1] = t.y;
+                } else {
+                    in[ka][0] = *src;
+                }
+            }
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka)
+#pragma unroll
+                for (int v = 0; v < CV; ++v) asm volatile("" ::"v"(in[ka][v]));
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka)
+#pragma unroll
+                for (int v = 0; v < CV; ++v) {
+                    if (dead(ka)) in[ka][v] = 0;
+                    if (mirrored(ka)) in[ka][v] ^= 0x80000000u;
+                }
+        }
         uint32_t o0[RAIN], o1[RAIN];
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) o0[a] = o1[a] = 0;
@@ -401,7 +470,19 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
         for (int v = 0; v < CV; ++v) {
             float2 x[RA];
 #pragma unroll
-            for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CT + c + v];
+            for (int ka = 0; ka < RA; ++ka) {
+                if constexpr (RB == 1) {
+                    constexpr float unboost = 1.0f / (float)multipass_kf_boost(F16, No);     // exact: a power of two
+                    const int r = r0 + c + v;
+                    float2 w = wm((r * ka) & Mmask, ihm);
+                    w.x *= unboost;
+                    w.y *= unboost;
+                    if (MIRROR && ka > RA / 2) w = cmulcf(w, wm((r * No) & Mmask, ihm));
+                    x[ka] = cmulcf(unpack2<F16>(in[ka][v]), w);
+                } else {
+                    x[ka] = T[(ka * RB + b2) * CT + c + v];
+                }
+            }
             dft_reg<RA, true>(x);
 #pragma unroll
             for (int a = 0; a < RAIN; ++a) {
@@ -466,8 +547,12 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
     const uint16_t *row0 = u + (size_t)h * N;
     const uint16_t *g0 = GATED ? wg + (size_t)h * N : nullptr;
     const bool wide = EXACT || N % 2 == 0;         // rows start 4-byte aligned
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
+    const float ihm = 2.0f / (float)M;
+    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     // step 1: length-RA transforms over a, times W_No^{ka b2}
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
@@ -517,9 +602,25 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
             }
         }
         dft_reg<RA, false, !FULLN>(x);
+        if constexpr (RB == 1) {                   // Z[ko] and its mirror row are both at hand
+            const int r = r0 + 2 * cg;
+#pragma unroll
+            for (int ko = 0; ko <= No / 2; ++ko) {
+                const float2 z = x[ko], zm = x[(No - ko) % No];
+                const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
+                const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
+                const float2 ta = cmulf(xa, wm((r * ko) & Mmask, ihm)), tb = cmulf(xb, wm(((r + 1) * ko) & Mmask, ihm));
+                if (ko < ko_lo)
+                    *(uint2 *)&S[((size_t)h * No + ko) * MI + multipass_row_slot(r, multipass_quarter_rows(No))] =
+                        make_uint2((uint32_t)cv16<F16>(ta.x) | ((uint32_t)cv16<F16>(ta.y) << 16),
+                                   (uint32_t)cv16<F16>(tb.x) | ((uint32_t)cv16<F16>(tb.y) << 16));
+            }
+            continue;
+        }
 #pragma unroll
         for (int ka = 0; ka < RA; ++ka) T[(ka * RB + b2) * CG + cg] = cmulf(x[ka], wno[ka * b2]);
     }
+    if constexpr (RB == 1) return;
     __syncthreads();
     // step 2: length-RB transforms over b2, in place: slot ka*RB + kb then holds Z[ko], ko = ka + RA kb
     for (int e = tid; e < RA * CG; e += TB) {
@@ -533,8 +634,6 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
     }
     __syncthreads();
     // step 3: split the two columns, twiddle (by recurrence over kb), store the rows ko <= No/2
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
@@ -575,14 +674,16 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int h = blockIdx.y;
     const bool wide = EXACT || N % 2 == 0;
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
     const float ihm = 2.0f / (float)M;
     const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     constexpr float unboost = 1.0f / (float)multipass_kf_boost(F16, No);     // exact: a power of two
     // step 1: untwiddle both columns, complete the rows ko > No/2 from their mirror rows, combine the columns
     // into one complex sequence, length-RB inverse over kb, times conj(W_No^{ka b2})
-    for (int e = tid; e < RA * CG; e += TB) {
+    for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
         uint2 in[RB];
@@ -632,15 +733,44 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
 #pragma unroll
         for (int b2 = 0; b2 < RB; ++b2) T[(ka * RB + b2) * CG + cg] = cmulcf(x[b2], wno[ka * b2]);
     }
-    __syncthreads();
+    if constexpr (RB > 1) __syncthreads();
     // step 2: length-RA inverse over ka; real part -> column c, imaginary part -> column c+1
     uint16_t *row0 = y + (size_t)h * N;
     const uint16_t *g0 = GATED ? vg + (size_t)h * N : nullptr;
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
+        if constexpr (RB == 1) {                   // every row <= No/2 is read once and serves its mirror row too
+            const int r = r0 + 2 * cg;
+            uint2 in[No / 2 + 1];
 #pragma unroll
-        for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CG + cg];
+            for (int ko = 0; ko <= No / 2; ++ko)
+                in[ko] = *(const uint2 *)&S[((size_t)h * No + (ko < ko_lo ? ko : 0)) * MI + multipass_row_slot(r, multipass_quarter_rows(No))];
+#pragma unroll
+            for (int ko = 0; ko <= No / 2; ++ko) asm volatile("" ::"v"(in[ko].x), "v"(in[ko].y));
+            const float2 m0 = wm((r * No) & Mmask, ihm), m1 = wm(((r + 1) * No) & Mmask, ihm);
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka) {
+                const bool mir = ka > RA / 2;
+                const int kr = mir ? No - ka : ka;
+                uint2 v = kr < ko_lo ? in[kr] : make_uint2(0, 0);
+                if (mir) {
+                    v.x ^= 0x80000000u;
+                    v.y ^= 0x80000000u;
+                }
+                float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
+                w0.x *= unboost, w0.y *= unboost, w1.x *= unboost, w1.y *= unboost;
+                if (mir) {
+                    w0 = cmulcf(w0, m0);
+                    w1 = cmulcf(w1, m1);
+                }
+                const float2 ua = cmulcf(unpack2<F16>(v.x), w0), ub = cmulcf(unpack2<F16>(v.y), w1);
+                x[ka] = make_float2(ua.x - ub.y, ua.y + ub.x);           // U_c + i U_{c+1}
+            }
+        } else {
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CG + cg];
+        }
         dft_reg<RA, true>(x);
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
@@ -687,8 +817,12 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restr
     const int64_t h = blockIdx.y;
     const float *row0 = (const float *)src + h * Nk;               // IN == 0
     const uint16_t *row16 = (const uint16_t *)src + h * Nk;        // IN != 0
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
+    const float ihm = 2.0f / (float)M;
+    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     // step 1: length-RA transforms over a, times W_No^{ka b2}; (column c, column c+1) = (re, im)
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
@@ -723,9 +857,22 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restr
             if (n + 1 >= Nk) x[a].y = 0.f;
         }
         dft_reg<RA, false, !FULLN>(x);
+        if constexpr (RB == 1) {                   // Z[ko] and its mirror row are both at hand
+            const int r = r0 + 2 * cg;
+#pragma unroll
+            for (int ko = 0; ko <= No / 2; ++ko) {
+                const float2 z = x[ko], zm = x[(No - ko) % No];
+                const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
+                const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
+                const float2 ta = cmulf(xa, wm((r * ko) & Mmask, ihm)), tb = cmulf(xb, wm(((r + 1) * ko) & Mmask, ihm));
+                *(float4 *)&T2[((size_t)h * NR + ko) * MI + r] = make_float4(ta.x, ta.y, tb.x, tb.y);
+            }
+            continue;
+        }
 #pragma unroll
         for (int ka = 0; ka < RA; ++ka) T[(ka * RB + b2) * CG + cg] = cmulf(x[ka], wno[ka * b2]);
     }
+    if constexpr (RB == 1) return;
     __syncthreads();
     // step 2: length-RB transforms over b2, in place: slot ka*RB + kb then holds Z[ko], ko = ka + RA kb
     for (int e = tid; e < RA * CG; e += TB) {
@@ -739,8 +886,6 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restr
     }
     __syncthreads();
     // step 3: split the two columns, twiddle (by recurrence over kb), store the rows ko <= No/2
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
@@ -782,13 +927,15 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int64_t h = blockIdx.y;
-    for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
-    __syncthreads();
+    if constexpr (RB > 1) {
+        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        __syncthreads();
+    }
     const float ihm = 2.0f / (float)M;
     const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
     // step 1: untwiddle both columns, complete the rows ko > No/2 from their mirror rows, combine the columns
     // into one complex sequence, length-RB inverse over kb, times conj(W_No^{ka b2})
-    for (int e = tid; e < RA * CG; e += TB) {
+    for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
         float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
@@ -828,15 +975,36 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
 #pragma unroll
         for (int b2 = 0; b2 < RB; ++b2) T[(ka * RB + b2) * CG + cg] = cmulcf(x[b2], wno[ka * b2]);
     }
-    __syncthreads();
+    if constexpr (RB > 1) __syncthreads();
     // step 2: length-RA inverse over ka; real part -> column c, imaginary part -> column c+1
     float *row0 = dk + h * Nk;
     const bool wide = Nk % 2 == 0 && ((uintptr_t)dk & 7) == 0;
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
+        if constexpr (RB == 1) {                   // every row is read once and serves its mirror row too
+            const int r = r0 + 2 * cg;
+            float4 in[NR];
 #pragma unroll
-        for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CG + cg];
+            for (int ko = 0; ko < NR; ++ko) in[ko] = *(const float4 *)&T2[((size_t)h * NR + ko) * MI + r];
+            const float2 m0 = wm((r * No) & Mmask, ihm), m1 = wm(((r + 1) * No) & Mmask, ihm);
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka) {
+                const bool mir = ka > RA / 2;
+                const float4 v = in[mir ? No - ka : ka];
+                float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
+                w0.x *= scale, w0.y *= scale, w1.x *= scale, w1.y *= scale;
+                if (mir) {
+                    w0 = cmulcf(w0, m0);
+                    w1 = cmulcf(w1, m1);
+                }
+                const float2 ua = cmulcf(make_float2(v.x, mir ? -v.y : v.y), w0), ub = cmulcf(make_float2(v.z, mir ? -v.w : v.w), w1);
+                x[ka] = make_float2(ua.x - ub.y, ua.y + ub.x);           // U_c + i U_{c+1}
+            }
+        } else {
+#pragma unroll
+            for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CG + cg];
+        }
         dft_reg<RA, true>(x);
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
@@ -855,14 +1023,14 @@ template <int RA, int RB>
 int launch_dk_outer_inv(const OuterGeo &g, const float2 *T2, float *dk, int64_t Nk, int64_t M, int64_t nh, float scale,
                         hipStream_t s)
 {
-    const size_t lds = sizeof(float2) * ((size_t)g.No + (size_t)g.No * g.CT);
-    const dim3 grid((unsigned)(MI / (2 * g.CT)), (unsigned)nh);
+    const size_t lds = g.lds();
+    const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
     if (Nk > M / 2) {
         FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, true>), grid, dim3(TB), lds, s, T2, dk, g.CT, Nk, M, scale);
+        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, true>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, M, scale);
     } else {
         FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, false>), grid, dim3(TB), lds, s, T2, dk, g.CT, Nk, M, scale);
+        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, false>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, M, scale);
     }
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
@@ -871,15 +1039,15 @@ int launch_dk_outer_inv(const OuterGeo &g, const float2 *T2, float *dk, int64_t 
 template <int IN, int RA, int RB>
 int launch_filter_outer_in(const OuterGeo &g, const void *k, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
 {
-    const size_t lds = sizeof(float2) * ((size_t)g.No + (size_t)g.No * g.CT);
-    const dim3 grid((unsigned)(MI / (2 * g.CT)), (unsigned)nh);
+    const size_t lds = g.lds();
+    const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
     const bool wide = Nk % 2 == 0 && ((uintptr_t)k & (IN == 0 ? 7 : 3)) == 0;
     if (Nk > M / 2) {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, k, T2, g.CT, Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, k, T2, g.pairs(), Nk, M, wide);
     } else {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, k, T2, g.CT, Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, k, T2, g.pairs(), Nk, M, wide);
     }
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
@@ -916,8 +1084,9 @@ OuterGeo outer_geo(int64_t M)
     g.No = (int)(M / MI);
     g.Ra = g.No < 16 ? g.No : 16;
     g.Rb = g.No / g.Ra;
-    // fp32 tile T[No][CT] of 64 KiB (two blocks per compute unit), at least 32 columns
-    g.CT = MI / g.No < 32 ? 32 : MI / g.No;
+    // No > 16: an fp32 tile T[No][CT] of 64 KiB (two blocks per compute unit), at least 32 columns.  Up to 16 a thread
+    // transforms a pair of columns in registers and there is no tile: two columns for every thread of a block.
+    g.CT = g.Rb == 1 ? 2 * TB : MI / g.No < 32 ? 32 : MI / g.No;
     return g;
 }
 
@@ -929,7 +1098,7 @@ int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, 
     // (at No = 256 a block has 32 columns: 16 x 32 / 2 entries would keep half of its 512 threads idle)
     constexpr int CTC = MI / (RA * RB) < 32 ? 32 : MI / (RA * RB);
     constexpr int CV = (RB <= 16 && RA * CTC / 2 >= TB) ? 2 : 1;
-    const size_t lds = sizeof(float2) * ((size_t)g.No + (size_t)g.No * g.CT);
+    const size_t lds = g.lds();
     FC_TRY(raise_dynamic_lds((const void *)k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>, 160 * 1024));
@@ -990,20 +1159,19 @@ template <bool F16, int RA, int RB>
 int launch_outer_real(bool inverse, const OuterGeo &g, const void *src, void *dst, int H, int N, int64_t M, hipStream_t s,
                       int ko_lo, const void *gate)
 {
-    // a block takes 2 g.CT columns as g.CT pairs: the same tile T[No][g.CT] as the paired passes
-    const size_t lds = sizeof(float2) * ((size_t)g.No + (size_t)g.No * g.CT);
-    const dim3 grid((unsigned)(MI / (2 * g.CT)), (unsigned)H);
+    const size_t lds = g.lds();
+    const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)H);
     const bool fulln = (int64_t)N > M / 2;
 #define FFTCONV_REAL_LAUNCH(FULLN, GATED, EXACT)                                                                                  \
     do {                                                                                                                    \
         if (!inverse) {                                                                                                     \
             FC_TRY(raise_dynamic_lds((const void *)k_outer_fwd_real<F16, RA, RB, FULLN, GATED, EXACT>, 160 * 1024));               \
             hipLaunchKernelGGL((k_outer_fwd_real<F16, RA, RB, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint16_t *)src, \
-                               (uint32_t *)dst, g.CT, H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
+                               (uint32_t *)dst, g.pairs(), H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
         } else {                                                                                                            \
             FC_TRY(raise_dynamic_lds((const void *)k_outer_inv_real<F16, RA, RB, FULLN, GATED, EXACT>, 160 * 1024));               \
             hipLaunchKernelGGL((k_outer_inv_real<F16, RA, RB, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint32_t *)src, \
-                               (uint16_t *)dst, g.CT, H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
+                               (uint16_t *)dst, g.pairs(), H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
         }                                                                                                                   \
     } while (0)
     // exact: N is even and fills its half (or the whole transform): no range checks (ungated calls only)
