@@ -208,8 +208,9 @@ template <typename G> __device__ __forceinline__ void store_row(const float2 (&x
 // natural: tmp holds the rows ko <= A/2 only, in the order of ko (A/2 + 1 blocks per channel: the output of
 // k_filter_outer_real, multipass.hip) instead of all A blocks in position order.  conj_out: the conjugate spectrum
 // (that of the circularly time-reversed taps, which are real).
-// Bound by the writes of k_f: the digits (k1, k2, k3) of f' are those of the row engine's registers (k1 = k0, k2 = digit 1,
-// k3 = digit 2), so a wave stores runs of 16 slots without another exchange.
+// Bound by the memory traffic: the digits (k1, k2, k3) of f' are those of the row engine's registers (k1 = k0, k2 = digit 1,
+// k3 = digit 2), so k_f needs no exchange through LDS.  128 channels of fft 131072 (142 MB): 54 us with stores of 16
+// slots in a row, 41 with four lane groups transposed and runs of 64.
 // Workgroups are persistent, two to a compute unit, and fetch the next block ahead of the present one's transform: loads,
 // transforms and stores of workgroups that all start together otherwise take turns on the whole chip.
 template <int KF>
@@ -225,10 +226,6 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
     auto source = [&](int blk) {                              // block blk = channel * (A / 2 + 1) + ko
         const int h = blk / NR, ko = blk % NR;
         return tmp + (natural ? (int64_t)blk : (int64_t)h * A + lds_pos(ko, flA, A)) * LB;
-    };
-    auto put = [&](int64_t r, int f, float re, float im) {
-        if constexpr (KF == 2) ((float2 *)kf)[r + G::index(f)] = make_float2(re, im);
-        else ((uint32_t *)kf)[r + fused3_kf_slot_8192(f)] = KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
     };
     float2 next[G::P];
     load_row<G>(next, source(blockIdx.x), threadIdx.x);
@@ -250,15 +247,53 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
         const int km = mirror ? A - ko : ko;
         const int64_t row = (h * A + (KF == 2 ? lds_pos(ko, flA, A) : ko)) * LB;
         const int64_t row_m = (h * A + (KF == 2 ? lds_pos(km, flA, A) : km)) * LB;
+        // weights of the bins of register p in this row and in the mirror row
+        auto weight = [&](int p) { return keep ? lds_mask_weight(keep, n_blocks, ko + A * G::freq(tid, p), M) * scale : scale; };
+        auto weight_m = [&](int p) {
+            return keep ? lds_mask_weight(keep, n_blocks, km + A * (LB - 1 - G::freq(tid, p)), M) * scale : scale;
+        };
+        if constexpr (KF == 2) {
+            float2 *const o = (float2 *)kf;
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) {
-            const int fi = G::freq(tid, p);
-            const float sc = keep ? lds_mask_weight(keep, n_blocks, ko + A * fi, M) * scale : scale;
-            put(row, fi, x[p].x * sc, sgn * x[p].y * sc);
-            if (mirror) {
-                const int fm = LB - 1 - fi;
-                const float scm = keep ? lds_mask_weight(keep, n_blocks, km + A * fm, M) * scale : scale;
-                put(row_m, fm, x[p].x * scm, -sgn * x[p].y * scm);
+            for (int p = 0; p < G::P; ++p) {
+                const int fi = G::freq(tid, p);
+                const float sc = weight(p);
+                o[row + G::index(fi)] = make_float2(x[p].x * sc, sgn * x[p].y * sc);
+                if (mirror) {
+                    const float scm = weight_m(p);
+                    o[row_m + G::index(LB - 1 - fi)] = make_float2(x[p].x * scm, -sgn * x[p].y * scm);
+                }
+            }
+        } else {
+            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
+            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
+            auto pack = [](float re, float im) { return KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im); };
+            const int lane = tid & 63, k1w = tid / 64 * 4;
+            uint32_t *const o = (uint32_t *)kf + row + lane, *const om = (uint32_t *)kf + row_m + (lane & 48) + 15 - (lane & 15);
+#pragma unroll
+            for (int ir = 0; ir < 8; ++ir) {
+                const int i = ir / 4, r = ir % 4;
+                uint32_t v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int p = 16 * i + k3_at_index(4 * c + r, 16);
+                    const float sc = weight(p);
+                    v[c] = pack(x[p].x * sc, sgn * x[p].y * sc);
+                }
+                rf::transpose_groups(v);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64] = v[j];
+                if (mirror) {                                     // bin 8191 - f': every digit is complemented
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int p = 16 * i + 15 - k3_at_index(4 * c + r, 16);
+                        const float scm = weight_m(p);
+                        v[c] = pack(x[p].x * scm, -sgn * x[p].y * scm);
+                    }
+                    rf::transpose_groups(v);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) om[((31 - (k1w + j + 16 * i)) * 4 + r) * 64] = v[j];
+                }
             }
         }
     }

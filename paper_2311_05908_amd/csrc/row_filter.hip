@@ -9,7 +9,7 @@
 // Up to 1024 points a row is part of one wave and most of the work is the copies: there a workgroup takes one channel, and all
 // of it moves the 64 KB, through an image of one group in LDS.
 // Bound by the 64 KB a channel that k_f and the accumulated spectra take.  768 channels of 4096 taps, fft 8192: filter
-// transform 40 -> 27 us, tail of the gradient 46 -> 24 (with every factor a trip through LDS and gathered twiddles before).
+// transform 40 -> 20 us (27 with stores of 16 slots in a row), tail of the gradient 46 -> 22 (with every factor a trip through LDS and gathered twiddles before).
 #include "fftconv_internal.h"
 #include "lds_fft.h"
 #include "row_io.h"
@@ -57,19 +57,42 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
         tw1.load(tab, tid);
         rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
         if ((int)blockIdx.x * RW + row >= H) return;
-#pragma unroll
-        for (int p = 0; p < G::P; ++p) {
-            const int f = G::freq(tid, p), d = kernel_slot<M>(f);
-            const float sc = keep ? lds_mask_weight(keep, n_blocks, f, M) / M : 1.f / M;
+        auto constant = [&](int p) {
+            const float sc = keep ? lds_mask_weight(keep, n_blocks, G::freq(tid, p), M) / M : 1.f / M;
             const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
-            uint2 c;
-            if constexpr (F16) c = make_uint2(f3::F16::pack(re, re), f3::F16::pack(-im, im));
-            else c = make_uint2(f3::BF16::pack(re, -im), f3::BF16::pack(im, re));
-            if constexpr (IMAGE<M>) {
-                image[d] = c;
-            } else {
+            if constexpr (F16) return make_uint2(f3::F16::pack(re, re), f3::F16::pack(-im, im));
+            else return make_uint2(f3::BF16::pack(re, -im), f3::BF16::pack(im, re));
+        };
+        if constexpr (M == SLOTS) {
+            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
+            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
+            const int k1w = tid / 64 * 4;
 #pragma unroll
-                for (int g = 0; g < SLOTS / M; ++g) o[g * M + d] = c;
+            for (int ir = 0; ir < 8; ++ir) {
+                const int i = ir / 4, r = ir % 4;
+                uint32_t a[4], b[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint2 v = constant(16 * i + k3_at_index(4 * c + r, 16));
+                    a[c] = v.x;
+                    b[c] = v.y;
+                }
+                rf::transpose_groups(a);
+                rf::transpose_groups(b);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = make_uint2(a[j], b[j]);
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) {
+                const int d = kernel_slot<M>(G::freq(tid, p));
+                const uint2 c = constant(p);
+                if constexpr (IMAGE<M>) {
+                    image[d] = c;
+                } else {
+#pragma unroll
+                    for (int g = 0; g < SLOTS / M; ++g) o[g * M + d] = c;
+                }
             }
         }
     }

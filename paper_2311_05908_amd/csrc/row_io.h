@@ -149,6 +149,24 @@ template <typename F> int with_row(int64_t M, F f)
 }
 
 
+// 4 x 4 transpose between the registers v[0 .. 3] and the four groups of 16 lanes of a wave: lane group g of v[j] gets what
+// lane group j of v[g] held.
+__device__ __forceinline__ void transpose_groups(uint32_t (&v)[4])
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {                                 // upper 32 lanes of v[c] <-> lower 32 of v[c + 2]
+        const auto t = __builtin_amdgcn_permlane32_swap(v[c], v[c + 2], false, false);
+        v[c] = t[0];
+        v[c + 2] = t[1];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c += 2) {                              // odd groups of v[c] <-> even groups of v[c + 1]
+        const auto t = __builtin_amdgcn_permlane16_swap(v[c], v[c + 1], false, false);
+        v[c] = t[0];
+        v[c + 1] = t[1];
+    }
+}
+
 // The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
 // that.
 template <typename G> inline const float2 *row_table(const fftconv_plan *p)
