@@ -278,6 +278,12 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         rc = fused3_filter(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, s);
         if (rc) return rc;
     }
+    // fp32 k_f in the row engine's order, in fp64 arithmetic
+    const bool rows64 = p->path == PATH_SMALL || (p->path == PATH_STAGED && p->M <= 16384);
+    if (rows64) {
+        rc = row_filter64(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, s);
+        if (rc) return rc;
+    }
     const bool long_rows = p->path == PATH_MULTIPASS && long_fft_supported(p);
     // fp32 k_f in the position order of the long transforms (staged plans from fft 32768 up) with a real outer pass
     const bool long_rows_f32 = p->path == PATH_STAGED && p->M >= 32768 && long_fft_supported(p) && multipass_filter_outer_ok(p);
@@ -303,16 +309,13 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         rc = long_filter_transform_f32(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, s);
         if (rc) return rc;
     }
-    for (int64_t h0 = 0; p->path != PATH_FUSED3 && !long_rows && !long_rows_f32 && h0 < p->H; h0 += p->filt_chunk) {
+    for (int64_t h0 = 0; p->path != PATH_FUSED3 && !rows64 && !long_rows && !long_rows_f32 && h0 < p->H; h0 += p->filt_chunk) {
         int64_t nh = p->H - h0 < p->filt_chunk ? p->H - h0 : p->filt_chunk;
         double2 *spec = nullptr;
         rc = staged_filter_transform(p, k, Nk, h0, nh, s, &spec, adjoint);
         if (rc) return rc;
-        switch (p->path) {
-        case PATH_MULTIPASS: rc = multipass_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
-        case PATH_SMALL: rc = row_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
-        default: rc = staged_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s); break;
-        }
+        rc = p->path == PATH_MULTIPASS ? multipass_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s)
+                                       : staged_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s);
         if (rc) return rc;
     }
     // a short filter of a plan that can run partial convolutions as short segments: add the

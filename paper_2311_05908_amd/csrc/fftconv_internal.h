@@ -270,8 +270,6 @@ int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, void *tmp, floa
 
 // ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle tables, k_f layout, the convolution
 std::vector<float2> row_tables(int64_t M, const double2 *w);
-int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
-                void *kf, hipStream_t s);
 int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
 // the convolution of a matrix-core plan up to fft_size 4096 on them, and whether a call has few enough rows for it
 bool row_few(const fftconv_plan *p, int64_t B);
@@ -285,6 +283,9 @@ int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, fl
 // the fp32 ends of the 8192-point matrix-core plans (row_filter.hip): taps -> k_f, accumulated spectra -> dk
 int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
                int64_t n_blocks, uint2 *kf, hipStream_t s);
+// fp64 filter transform of the plans that convolve on the row engine with k_f in fp32
+int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
+                 void *kf, hipStream_t s);
 int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s);
 // short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);

@@ -77,22 +77,6 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     if (live) rf::store_pair<G, IO, HALF>(x, y + r0, y + r1, N, tid, exact, words, two);
 }
 
-// the fp64 spectra of the filters in the order of the kernel above
-template <int M>
-__global__ void k_pack_rows(const double2 *spec, float2 *kf, FacList fl, int64_t h0, int64_t nh, const uint8_t *keep,
-                            int64_t n_blocks)
-{
-    using G = Row<M>;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nh * M) return;
-    const int64_t h = idx / M;
-    const int d = (int)(idx % M), p = d / (2 * G::T) * 2 + d % 2, tid = d / 2 % G::T;
-    const int f = G::freq(tid, p);
-    const double2 v = spec[h * M + freq_to_pos(f, fl, M)];
-    const double sc = mask_weight(keep, n_blocks, f, M) / (double)M;
-    kf[(h0 + h) * M + d] = make_float2((float)(v.x * sc), (float)(v.y * sc));
-}
-
 // The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
 // with their k_f: 16-bit constant pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
 // wg multiplies u, bit 1: vg multiplies y), in fp32.  For calls of few rows: see row_forward_few().
@@ -203,19 +187,6 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     add_length(M < 8192 ? M : 8192);
     if (M == 16384) add_length(M);
     return t;
-}
-
-int row_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev, int64_t n_blocks,
-                void *kf, hipStream_t s)
-{
-    return rf::with_row(p->M, [&](auto g) -> int {
-        using G = decltype(g);
-        const int bs = 256;
-        hipLaunchKernelGGL(k_pack_rows<G::M>, dim3((unsigned)((nh * G::M + bs - 1) / bs)), dim3(bs), 0, s, spec, (float2 *)kf,
-                           staged_fac_list(p), h0, nh, keep_dev, n_blocks);
-        FC_HIP(hipGetLastError());
-        return FFTCONV_OK;
-    });
 }
 
 int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)

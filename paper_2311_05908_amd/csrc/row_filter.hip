@@ -160,7 +160,69 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     }
 }
 
+// ---- the filter transform of the plans that convolve on the row engine with k_f in fp32 (fft_size 256 .. 16384), in fp64:
+// k_f[h] in the order of the engine's registers, [register pair][thread][2], scaled by 1/M and by the frequency mask.
+// The taps are real, so a row is half as long: z[n] = k[2n] + i k[2n+1] is transformed in LDS (lds_fft.h, M/2 points: 139 KB at
+// M = 16384), and with its even and odd parts E, O every bin is K[f] = E[f] + W_M^f O[f] on the way out.
+// Bound by the LDS passes of its one or two workgroups on a compute unit.  128 channels of fft 8192: 25 us with a transform of M
+// points, its spectrum in memory and a kernel that permuted it; 19 us now, and fft 16384, which went through memory for every factor: fp32 8 x 64 x 8192 training step 217 -> 169.
+template <int M> constexpr int FILTER64_THREADS = M >= 8192 ? 512 : M <= 1024 ? 64 : M / 16;
+template <int M>
+__global__ void __launch_bounds__(FILTER64_THREADS<M>)
+    k_row_filter64(const float *__restrict__ k, float2 *__restrict__ kf, const double2 *__restrict__ w, FacList fl, int64_t Nk,
+                   bool conj_out, const uint8_t *__restrict__ keep, int64_t n_blocks)
+{
+    using G = Row<M>;
+    constexpr int MH = M / 2, NTHR = FILTER64_THREADS<M>, PER = MH / NTHR < 8 ? MH / NTHR : 8;
+    extern __shared__ double2 XD[];
+    const float *row = k + blockIdx.x * Nk;
+    for (int n0 = threadIdx.x; n0 < MH; n0 += PER * NTHR) {
+        float a[PER], b[PER];                                     // (a tap beyond Nk reads tap 0 and is discarded)
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int n = 2 * (n0 + j * NTHR);
+            a[j] = row[n < Nk ? n : 0];
+            b[j] = row[n + 1 < Nk ? n + 1 : 0];
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) asm volatile("" ::"v"(a[j]), "v"(b[j]));
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int n = 2 * (n0 + j * NTHR);
+            XD[lds_slot(n / 2)] = make_double2(n < Nk ? (double)a[j] : 0.0, n + 1 < Nk ? (double)b[j] : 0.0);
+        }
+    }
+    __syncthreads();
+    lds_forward(XD, w, fl, MH, 2);
+    float2 *const o = kf + (int64_t)blockIdx.x * M;
+#pragma unroll 4
+    for (int d = threadIdx.x; d < M; d += NTHR) {
+        const int f = G::freq(d / 2 % G::T, d / (2 * G::T) * 2 + d % 2), fh = f & (MH - 1);
+        const double2 z = XD[lds_slot(lds_pos(fh, fl, MH))], m = XD[lds_slot(lds_pos((MH - fh) & (MH - 1), fl, MH))];
+        const double2 e = make_double2(0.5 * (z.x + m.x), 0.5 * (z.y - m.y));          // (Z + conj Zm) / 2
+        const double2 q = make_double2(0.5 * (z.y + m.y), -0.5 * (z.x - m.x));         // (Z - conj Zm) / (2i)
+        const double2 v = cmul(q, w[f]);
+        const double sc = (double)lds_mask_weight(keep, n_blocks, f, M) / (double)M;
+        const double im = (e.y + v.y) * sc;
+        o[d] = make_float2((float)((e.x + v.x) * sc), (float)(conj_out ? -im : im));
+    }
+}
+
 }  // namespace
+
+int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
+                 void *kf, hipStream_t s)
+{
+    return rf::with_row(p->M, [&](auto g) -> int {
+        constexpr int M = decltype(g)::M;
+        constexpr size_t lds = (size_t)(M / 2 + M / 32) * sizeof(double2);
+        FC_TRY(raise_dynamic_lds((const void *)k_row_filter64<M>, (int)lds));
+        hipLaunchKernelGGL(k_row_filter64<M>, dim3((unsigned)p->H), dim3(FILTER64_THREADS<M>), lds, s, k, (float2 *)kf, p->st.w64,
+                           staged_factors_for(M / 2), Nk, conj_out, keep_dev, n_blocks);
+        FC_HIP(hipGetLastError());
+        return FFTCONV_OK;
+    });
+}
 
 // k_f (H, 8192 slots) of the 8192-point kernels for a transform of Ms = 256 .. 8192 points (min(fft_size, 8192): plans above
 // keep the spectrum of a short filter this way)

@@ -366,7 +366,6 @@ FacList staged_factors_for(int64_t M)
 int staged_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev,
                    int64_t n_blocks, void *kf, hipStream_t s)
 {
-    if (p->M <= 16384) return row_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, kf, s);
     const int bs = 256;
     hipLaunchKernelGGL(k_pack_staged, dim3(grid_for(nh * p->M, bs)), dim3(bs), 0, s, spec, (float2 *)kf, fac_list(p),
                        p->M, h0, nh, keep_dev, n_blocks);
