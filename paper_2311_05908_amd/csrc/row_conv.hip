@@ -16,7 +16,8 @@
 // What bounds it: the vector ALU (about 80 operations per point and convolution at fft 1024, 100 at 4096), close to
 // the copy of its bytes.  201 MB of rows (a copy takes 41 us): bf16 circular 50 / 54 / 57 / 67 / 70 us at fft 256 / 512 /
 // 1024 / 2048 / 4096 (57 / 100 / 121 / 99 / 123 us with the samples staged through LDS, an exchange for every pass and
-// the twiddles gathered from a table in LDS), fp32 causal 41 / 47 / 51 / 60 / 61 us (91 / 114 / 130 / 100 / 122).
+// the twiddles gathered from a table in LDS), fp32 causal 47 / 55 / 57 / 70 / 76 us with
+// exact twiddles (91 / 114 / 130 / 100 / 122 before; 41 / 47 / 51 / 60 / 61 with products of them, see row_fft.h).
 #include "fftconv_internal.h"
 #include "row_io.h"
 
