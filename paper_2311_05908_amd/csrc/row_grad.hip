@@ -147,7 +147,8 @@ __global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
 
 // Runs per channel: as many as give every SIMD of 256 compute units two waves (16 points a thread: four), no more than
 // the batch has rows, of equal length.
-struct Splits { int64_t S, per; };
+// most: the runs that no smaller batch exceeds (4 rows in runs of 1 are more than 5 in runs of 2): what the workspace holds.
+struct Splits { int64_t S, per, most; };
 Splits grad_splits(int64_t M, int64_t H, int64_t B)
 {
     int64_t want = 1;
@@ -159,7 +160,7 @@ Splits grad_splits(int64_t M, int64_t H, int64_t B)
     if (want > B) want = B;
     if (want < 1) want = 1;
     const int64_t per = (B + want - 1) / want;
-    return Splits{(B + per - 1) / per, per};
+    return Splits{(B + per - 1) / per, per, want};
 }
 
 template <int M, typename IO, bool HALF>
@@ -195,11 +196,11 @@ int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk,
 
 bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSED3 && p->M <= 16384; }
 
-// the sums of the runs; never 0 (the entry point refuses a missing workspace)
+// the sums of the runs; never 0 (the entry point refuses a missing workspace), and enough for every smaller batch
 size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B)
 {
     const Splits sp = grad_splits(p->M, p->H, B);
-    return sp.S == 1 ? 256 : (size_t)(sp.S * p->H * p->M) * sizeof(float2);
+    return sp.most == 1 ? 256 : (size_t)(sp.most * p->H * p->M) * sizeof(float2);
 }
 
 // B >= 1

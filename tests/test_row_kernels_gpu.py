@@ -66,6 +66,15 @@ def test_row_gradient_runs(B, H, M):
     check_row_gradient("f32", B, H, 40, M, 50, None)
 
 
+@pytest.mark.parametrize("H,M", [(128, 8192), (3, 512), (6000, 256), (70, 16384)])
+def test_row_gradient_workspace_of_a_larger_batch(H, M):
+    """A workspace asked for once, for the largest batch, holds every smaller one (a last, partial batch)."""
+    plan = fftconv.Plan(40, M, H, "f32")
+    sizes = [int(plan._lib.fftconv_workspace_bytes_backward_filter(plan._h, B)) for B in range(1, 40)]
+    assert sizes[0] > 0
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
 def test_row_filter_edges(M, dtype):
