@@ -80,7 +80,9 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
 
 // The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
 // with their k_f: 16-bit constant pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
-// wg multiplies u, bit 1: vg multiplies y), in fp32.  For calls of few rows: see row_forward_few().
+// wg multiplies u, bit 1: vg multiplies y).  The transforms and the product with k_f are fp32; u . w is rounded to the I/O type,
+// as is the convolution before it meets the output gate: the same values as without a fused gate, whichever kernel a call
+// takes.  For calls of few rows: see row_forward_few().
 template <int M, typename IO, int GATE>
 __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint2 *__restrict__ kf, const float2 *__restrict__ tab,
@@ -103,7 +105,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
         float2 g[G::P];
         rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
 #pragma unroll
-        for (int m = 0; m < G::P / 2; ++m) x[m] = make_float2(x[m].x * g[m].x, x[m].y * g[m].y);
+        for (int m = 0; m < G::P / 2; ++m) x[m] = rf::rounded<IO>(x[m].x * g[m].x, x[m].y * g[m].y);
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
@@ -124,7 +126,10 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
         float2 g[G::P];
         rf::load_pair<G, IO, true>(g, vg + r0, vg + r1, N, tid, exact, true, true, two);
 #pragma unroll
-        for (int m = 0; m < G::P / 2; ++m) x[m] = make_float2(x[m].x * g[m].x, x[m].y * g[m].y);
+        for (int m = 0; m < G::P / 2; ++m) {
+            const float2 c = rf::rounded<IO>(x[m].x, x[m].y);
+            x[m] = make_float2(c.x * g[m].x, c.y * g[m].y);
+        }
     }
     if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }

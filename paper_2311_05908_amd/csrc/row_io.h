@@ -39,6 +39,8 @@ template <typename IO> __device__ __forceinline__ uint32_t pack(float lo, float 
     if constexpr (std::is_same<IO, __half>::value) return f3::F16::pack(lo, hi);
     else return f3::BF16::pack(lo, hi);
 }
+// the nearest values of the 16-bit type
+template <typename IO> __device__ __forceinline__ float2 rounded(float lo, float hi) { return unpack<IO>(pack<IO>(lo, hi)); }
 // the word of the neighbouring lane (lane ^ 1)
 __device__ __forceinline__ uint32_t neighbour(uint32_t w)
 {

@@ -137,3 +137,29 @@ def test_few_rows(dtype, B, H, N, M):
     many = plan.forward(u.cuda().repeat(reps, 1, 1), kf)[:B]
     one = plan.forward(u.cuda(), kf)
     assert parity_error(many.cpu().double().numpy(), one.cpu().double().numpy(), 2 * TOL[dtype]) <= 2 * TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096])
+def test_few_rows_round_at_the_gates(M, dtype):
+    """u . w and the convolution are each rounded to the I/O type (fftconv_forward_gated).  The filter, taps of 1 and 91/128 a
+    quarter of the transform apart, has a spectrum of 16-bit numbers, so the convolution is p[n] + 91/128 p[n - M/4] up to a few
+    1e-7 and every rounding can be followed.  Sums lie on a grid 128 times finer than the type's: one in 128 is a tie, which
+    the fp32 errors may send either way (0.4 % of the elements; a rounding left out changes 10 % and more)."""
+    B, H, N = 2, (150 if M == 1024 else 3), M // 2
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
+    u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.path == "fused3"
+    taps = torch.zeros(H, N, device="cuda")
+    taps[:, 0], taps[:, M // 4] = 1.0, 91 / 128
+    kf = plan.filter_fft(taps)
+    for wg, vg in ((None, None), (g, None), (None, v), (g, v)):
+        y = plan.forward_gated(u.cuda(), None if wg is None else wg.cuda(), None if vg is None else vg.cuda(), kf).cpu()
+        p = u if wg is None else u * wg                           # (products of 16-bit tensors round once)
+        c = p.double()
+        c[..., M // 4:] += 91 / 128 * p[..., : N - M // 4].double()
+        ref = c.to(u.dtype) if vg is None else c.to(u.dtype) * vg
+        differ = (y != ref).float().mean().item()
+        print("gates %s M=%d w=%d v=%d differ=%.4f" % (dtype, M, wg is not None, vg is not None, differ), flush=True)
+        assert differ <= 0.02
