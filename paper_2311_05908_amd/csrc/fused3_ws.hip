@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(NT) k_fused3_ws(const uint16_t *__restrict__ u
 int fused3_ws_launch(const fftconv_plan *p, const void *consts, const void *u, const void *kf, void *y, int64_t B,
                      int nseg, int P, hipStream_t s, const void *wg, const void *vg, uint32_t live_k1)
 {
-    if (consts == p->f3.consts && nseg == 1 && row_few(p, B)) return row_forward_few(p, u, kf, y, B, wg, vg, s);
+    if (consts == p->f3.consts && nseg == 1 && row_few(p->M, p->H, B)) return row_forward_few(p, u, kf, y, B, wg, vg, s);
     // plans for fft 512 .. 4096 put 8192 / fft transforms into one work item (their tables say so)
     const int groups = p->M < G::M && consts == p->f3.consts ? (int)(G::M / p->M) : 1;
     int lg_half = 0;

@@ -218,15 +218,17 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 // against the other, 768 channels: fft 4096, B = 1 / 2 / 4: 18 -> 14, 19 -> 15, (19, 25); 2048, B = 4 / 8: 19 -> 15, (20, 25);
 // 1024, B = 8 / 16: 19 -> 15, (20, 23); 512, B = 1 / 16: 18 -> 8, 19 -> 12; 256, B = 1 / 32: 17 -> 5, 19 -> 8; 16 channels,
 // fft 4096, B = 1 / 32: 9 -> 7, 9 -> 8.  At 8192 points it never was (16 channels: 8.8 against 12.8).
-bool row_few(const fftconv_plan *p, int64_t B)
+// The kernel counts rows and threads (at most M / 16 to a pair of rows) in 32 bits: calls beyond that are not few rows.
+bool row_few(int64_t M, int64_t H, int64_t B)
 {
-    const int64_t M = p->M;
-    if (M > 4096) return false;
-    const int64_t npairs = (B + 1) / 2, groups = 8192 / M, items = p->H * ((npairs + groups - 1) / groups);
-    const int64_t points = p->H * npairs * (M == 256 ? 128 : M == 512 ? 384 : M);
+    const int64_t npairs = (B + 1) / 2;
+    if (M > 4096 || npairs > INT32_MAX / (H * (M / 16))) return false;
+    const int64_t groups = 8192 / M, items = H * ((npairs + groups - 1) / groups);
+    const int64_t points = H * npairs * (M == 256 ? 128 : M == 512 ? 384 : M);
     return points < 800 * 1024 + 4096 * items && (M != 1024 || items > 128);
 }
 
+// for calls that row_few() takes
 int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
                     hipStream_t s)
 {

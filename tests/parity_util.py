@@ -1,5 +1,7 @@
 """Shared helpers of the GPU parity tests: run the HIP path through the C ABI
 and compare it with the CPU oracle on the same seeded inputs."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -8,6 +10,14 @@ from paper_2311_05908_amd import fftconv, synth
 
 TOL = {"f32": 1e-5, "f16": 1e-2, "bf16": 1e-2}     # max per-sequence relative L2 error
 ELEM_FACTOR = 8.0                                  # element-wise bound: |y_i - ref_i| <= ELEM_FACTOR * tol * rms(ref)
+
+
+def row_few(M, H, B):
+    """Whether a forward call of B x H rows on a matrix-core plan of fft_size M runs on the row kernel (the library's own
+    rule, csrc/row_conv.hip; no device involved)."""
+    rule = fftconv.load()["_ZN7fftconv7row_fewElll"]
+    rule.argtypes, rule.restype = [ctypes.c_int64] * 3, ctypes.c_bool
+    return rule(M, H, B)
 
 
 def parity_error(y, ref, tol, what="", weight=None, floor_rms=None):

@@ -4,6 +4,7 @@ import math
 import pytest
 
 from paper_2311_05908_amd import fftconv
+from parity_util import row_few
 
 
 def a100():
@@ -128,3 +129,14 @@ def test_measured_machine_constants_are_plausible_and_near_the_preset():
     for name in ("sigma_H", "tau_M", "tau_G"):
         assert abs(getattr(m, name) / getattr(g, name) - 1.0) < 0.4, (name, getattr(m, name), getattr(g, name))
     assert 0.5 < m.sigma_S / g.sigma_S < 2.0, (m.sigma_S, g.sigma_S)
+
+
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096])
+def test_row_kernel_calls_stay_within_its_32_bit_counts(M):
+    """Rows and threads of the row kernel are 32-bit numbers: whatever else the rule says, it takes no call beyond them."""
+    for lgh in range(0, 25, 2):
+        for lgb in range(0, 40):
+            H, B = 1 << lgh, (1 << lgb) + 1
+            if row_few(M, H, B):
+                assert (B + 1) // 2 * H * (M // 16) < 2 ** 31, (M, H, B)
+    assert not row_few(M, 1 << 20, 1 << 12) and not row_few(M, 1, 1 << 32) and not row_few(M, 1 << 24, 1 << 40)
