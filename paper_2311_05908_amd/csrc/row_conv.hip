@@ -209,23 +209,35 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
     });
 }
 
-// Few rows: the wave-specialised kernel needs 8 us for a call whatever its size (tables, a pipeline of four steps) and
-// 2.8 us for every 256 work items (a channel's 2 * 8192 / fft rows each, however few there are); the row kernel starts at
-// 4.5 - 9 us and spends about 2.9 ps on a point, twice as much as a full work item.  So it takes the calls with
-//     points of all transforms  <  800 * 1024 + 4096 * work items
-// (shortest rows: more waves, cheaper points; 1024 points a row: the longest chain in one wave, from 8.7 us of the other
-// kernel on it is the faster only if there is more than one item for every second compute unit).  Measured, us, bf16, one kernel
-// against the other, 768 channels: fft 4096, B = 1 / 2 / 4: 18 -> 14, 19 -> 15, (19, 25); 2048, B = 4 / 8: 19 -> 15, (20, 25);
-// 1024, B = 8 / 16: 19 -> 15, (20, 23); 512, B = 1 / 16: 18 -> 8, 19 -> 12; 256, B = 1 / 32: 17 -> 5, 19 -> 8; 16 channels,
-// fft 4096, B = 1 / 32: 9 -> 7, 9 -> 8.  At 8192 points it never was (16 channels: 8.8 against 12.8).
+// Few rows: which calls of a matrix-core plan up to fft 4096 the row kernel takes.  Both kernels' times are staircases.  The
+// matrix-core kernel runs its work items (8192 / fft pairs of rows of one channel, however few there are) in rounds of one per
+// compute unit: 9 - 10 us for the first, 15, 19, 23 us for 2, 3, 4, each round also fetching the k_f of its channels (64 KB).
+// The row kernel runs workgroups of `rows` pairs: 8, 12, 15, 19 us for 1, 2, 3, 4 of them per compute unit (fft 2048 and
+// 4096; fft 512: 9, 14, 19, 26; fft 1024, a chain in half a wave: 11, 17, 23, 31).  So
+//   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer;
+//   fft 1024: half as many, and not in the first round (9.2 against 9.7 us);
+//   fft 512: half as many, and only if items are not full (full ones: 9.0 against 9.3 us, gated fp16);
+//   fft 256: it reads 2 KB of k_f a channel, the matrix cores 64 KB, so the line rises with H: 40 Ki pairs + 56 a channel.
+//     B x 768 channels, bf16, matrix cores -> rows: B = 64 20 -> 14 us, 128 29 -> 25, 212 46 -> 37, (512 78, 85), (1365
+//     191, 258); 256 channels: B = 256 22 -> 19, (1024 53, 57).
+// Measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates: what the rule
+// takes is at most 4 % slower than on the matrix cores (one fp16 shape at fft 1024) and 0.59 / 0.76 / 0.66 / 0.83 / 0.85
+// of its time in the mean.  (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
+// calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
+// At 8192 points the row kernel never was the faster one (16 channels: 8.8 against 12.8).
 // The kernel counts rows and threads (at most M / 16 to a pair of rows) in 32 bits: calls beyond that are not few rows.
 bool row_few(int64_t M, int64_t H, int64_t B)
 {
     const int64_t npairs = (B + 1) / 2;
     if (M > 4096 || npairs > INT32_MAX / (H * (M / 16))) return false;
-    const int64_t groups = 8192 / M, items = H * ((npairs + groups - 1) / groups);
-    const int64_t points = H * npairs * (M == 256 ? 128 : M == 512 ? 384 : M);
-    return points < 800 * 1024 + 4096 * items && (M != 1024 || items > 128);
+    const int64_t pairs = H * npairs;
+    if (M == 256) return pairs < 40 * 1024 + 56 * H;
+    constexpr int CUS = 256;
+    const int64_t full = 8192 / M, items = H * ((npairs + full - 1) / full), rounds = (items + CUS - 1) / CUS;
+    const int64_t rows = M == 512 ? 16 : M == 1024 ? 8 : M == 2048 ? 2 : 1, groups = (pairs + rows - 1) / rows;
+    if (M >= 2048) return groups <= CUS * rounds;
+    if (M == 1024) return rounds > 1 && groups <= CUS * ((rounds + 1) / 2);
+    return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
 }
 
 // for calls that row_few() takes

@@ -20,6 +20,18 @@ def row_few(M, H, B):
     return rule(M, H, B)
 
 
+def batches(plan, B):
+    """The batches in which a test runs its B rows, as row numbers: once, and, where so few rows of a matrix-core plan run on the
+    row kernel, also repeated up to a batch (odd if B is) that runs on the matrix cores."""
+    out = [np.arange(B)]
+    if plan.path == "fused3" and B > 0 and row_few(plan.fft_size, plan.H, B):
+        b = B
+        while row_few(plan.fft_size, plan.H, b):
+            b = 2 * b + B % 2
+        out.append(np.arange(b) % B)
+    return out
+
+
 def parity_error(y, ref, tol, what="", weight=None, floor_rms=None):
     """Compare along the last axis (one sequence per row).  Returns the largest per-sequence relative L2 error
     (the caller asserts it against tol) and itself asserts the element-wise bound

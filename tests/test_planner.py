@@ -140,3 +140,16 @@ def test_row_kernel_calls_stay_within_its_32_bit_counts(M):
             if row_few(M, H, B):
                 assert (B + 1) // 2 * H * (M // 16) < 2 ** 31, (M, H, B)
     assert not row_few(M, 1 << 20, 1 << 12) and not row_few(M, 1, 1 << 32) and not row_few(M, 1 << 24, 1 << 40)
+
+
+@pytest.mark.parametrize("M,H,few,many", [
+    # batches measured on either side of the line, the larger ones up to 2^27 samples
+    (256, 768, (1, 64, 212), (512, 1365)), (256, 16, (1, 2048), (16384,)), (256, 8192, (1, 64), (128,)),
+    (512, 768, (1, 16), (64, 682)), (512, 16, (1, 33), (32, 2048)),
+    (1024, 768, (1, 4), (16, 341)), (1024, 16, (), (1, 64, 1024)),
+    (2048, 768, (1, 4), (8, 170)), (2048, 64, (1, 16), (24, 512)),
+    (4096, 768, (1, 2), (4, 64)), (4096, 16, (1, 32), (33, 1024)),
+])
+def test_rule_of_the_row_kernel_draws_a_line_at_every_length(M, H, few, many):
+    assert [row_few(M, H, B) for B in few] == [True] * len(few)
+    assert [row_few(M, H, B) for B in many] == [False] * len(many)

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 from paper_2311_05908_amd import fftconv, synth
-from parity_util import TOL, check_all_sequences, parity_error
+from parity_util import TOL, batches, check_all_sequences, parity_error, row_few
 
 pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS
@@ -107,13 +107,15 @@ def test_row_filter_edges(M, dtype):
 @pytest.mark.parametrize("B,H,N,M", [
     (1, 5, 128, 256), (3, 17, 120, 256),        # rows of a part of a wave, partly empty workgroups, a lone row
     (2, 3, 256, 512), (5, 9, 8, 512),
-    (1, 150, 512, 1024),                        # only with more than 128 work items
+    (1, 300, 512, 1024),                        # only with more work items than compute units
     (3, 3, 1024, 2048), (1, 2, 1000, 2048),
     (1, 3, 2048, 4096), (2, 1, 2040, 4096), (9, 2, 16, 4096),
+    (1, 768, 2048, 4096),                       # several rounds of the matrix-core kernel
 ])
 def test_few_rows(dtype, B, H, N, M):
     """Calls of few rows on matrix-core plans up to fft 4096: with the plan's 16-bit k_f, with none, one or both gates, against
     the oracle; the same rows in a batch that is large enough for the matrix-core kernel agree within both kernels' errors."""
+    assert row_few(M, H, B)
     w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype, alpha=(1e-2, 1e-1))
     u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
     k = synth.gen_k(w)
@@ -133,10 +135,13 @@ def test_few_rows(dtype, B, H, N, M):
         print("few rows %s B=%d H=%d N=%d M=%d gates=%d%d err=%.3e" % (dtype, B, H, N, M, wg is not None, vg is not None, err),
               flush=True)
         assert err <= TOL[dtype]
-    reps = 2 * 8192 // M * 40                                     # batches of work items for the matrix-core kernel
-    many = plan.forward(u.cuda().repeat(reps, 1, 1), kf)[:B]
-    one = plan.forward(u.cuda(), kf)
-    assert parity_error(many.cpu().double().numpy(), one.cpu().double().numpy(), 2 * TOL[dtype]) <= 2 * TOL[dtype]
+        # and in a batch for the matrix-core kernel; an error of either kernel's convolution is multiplied by the output gate
+        rows = batches(plan, B)[-1]
+        assert not row_few(M, H, len(rows))
+        many = plan.forward_gated(*[None if t is None else t[rows].cuda() for t in (u, wg, vg)], kf)[-B:]
+        one = y.cpu().double().numpy()[rows[-B:]]
+        err = parity_error(many.cpu().double().numpy(), one, 2 * TOL[dtype], "both", weight=None if vg is None else weight[rows[-B:]])
+        assert err <= 2 * TOL[dtype]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -146,7 +151,8 @@ def test_few_rows_round_at_the_gates(M, dtype):
     quarter of the transform apart, has a spectrum of 16-bit numbers, so the convolution is p[n] + 91/128 p[n - M/4] up to a few
     1e-7 and every rounding can be followed.  Sums lie on a grid 128 times finer than the type's: one in 128 is a tie, which
     the fp32 errors may send either way (0.4 % of the elements; a rounding left out changes 10 % and more)."""
-    B, H, N = 2, (150 if M == 1024 else 3), M // 2
+    B, H, N = 2, (300 if M == 1024 else 3), M // 2
+    assert row_few(M, H, B)
     w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
     u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
     plan = fftconv.Plan(N, M, H, dtype)
