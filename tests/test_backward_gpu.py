@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2311_05908_amd import fftconv, synth
-from parity_util import TOL, parity_error
+from parity_util import TOL, batches, parity_error
 
 pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS
@@ -50,24 +50,26 @@ def test_backward_input_and_filter(dtype, B, H, N, M, Nk):
     plan = fftconv.Plan(N, M, H, dtype)
     kd = torch.from_numpy(k).cuda()
     kfa = plan.filter_fft_adjoint(kd)
-    du = plan.backward_input(dy.cuda(), kfa)
     dk = plan.backward_filter(u.cuda(), dy.cuda(), Nk)
     torch.cuda.synchronize()
-    assert torch.isfinite(du.float()).all() and torch.isfinite(dk).all()
+    assert torch.isfinite(dk).all()
     du_ref = oracle.backward_u(dy.double().numpy(), k, M)
     dk_ref = oracle.backward_k(u.double().numpy(), dy.double().numpy(), M, Nk)
     # single-kernel plans transform u and dy on the matrix cores (16-bit operands); the others in fp32
     tol_k = TOL[dtype] if plan.path == "fused3" else TOL["f32"]
-    e_u = parity_error(du.cpu().double().numpy(), du_ref, TOL[dtype], "du")
+    e_u = max(parity_error(plan.backward_input(dy[rows].cuda(), kfa).cpu().double().numpy(), du_ref[rows], TOL[dtype], "du")
+              for rows in batches(plan, B))
     e_k = parity_error(dk.cpu().double().numpy(), dk_ref, tol_k, "dk")
     print("backward %s B=%d H=%d N=%d M=%d Nk=%d path=%s du err=%.3e dk err=%.3e" % (dtype, B, H, N, M, Nk, plan.path, e_u, e_k),
           flush=True)
     assert e_u <= TOL[dtype]
     assert e_k <= tol_k
     # the forward pass on the same plan still sees the ordinary spectrum
-    y = plan.forward(u.cuda(), plan.filter_fft(kd))
+    kf = plan.filter_fft(kd)
     y_ref = oracle.fftconv(u.double().numpy(), k, M)
-    assert parity_error(y.cpu().double().numpy(), y_ref, TOL[dtype], "y") <= TOL[dtype]
+    for rows in batches(plan, B):
+        y = plan.forward(u[rows].cuda(), kf)
+        assert parity_error(y.cpu().double().numpy(), y_ref[rows], TOL[dtype], "y") <= TOL[dtype]
 
 
 @pytest.mark.parametrize("dtype,B,H,N,M,Nk", [

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 from paper_2311_05908_amd import fftconv, synth
-from parity_util import TOL, parity_error
+from parity_util import TOL, batches, parity_error
 
 pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS
@@ -24,14 +24,18 @@ def run_gated(w, use_w=True, use_v=True):
     y = plan.forward_gated(u.cuda(), None if gw is None else gw.cuda(), None if gv is None else gv.cuda(), kf)
     torch.cuda.synchronize()
     assert torch.isfinite(y.float()).all()
-    return u, gw, gv, k, y.cpu(), plan
+    return u, gw, gv, k, y.cpu(), plan, kf
 
 
 def check_all(w, use_w=True, use_v=True):
-    u, gw, gv, k, y, plan = run_gated(w, use_w, use_v)
-    ref = oracle.fftconv_gated(u.double().numpy(), None if gw is None else gw.double().numpy(),
-                               None if gv is None else gv.double().numpy(), k, w.fft_size)
-    return parity_error(y.double().numpy(), ref, TOL[w.dtype], "gated", None if gv is None else gv.double().numpy()), plan
+    u, gw, gv, k, y, plan, kf = run_gated(w, use_w, use_v)
+    v = None if gv is None else gv.double().numpy()
+    ref = oracle.fftconv_gated(u.double().numpy(), None if gw is None else gw.double().numpy(), v, k, w.fft_size)
+    err = parity_error(y.double().numpy(), ref, TOL[w.dtype], "gated", v)
+    for rows in batches(plan, w.B)[1:]:
+        y = plan.forward_gated(*[None if t is None else t[rows].cuda() for t in (u, gw, gv)], kf).cpu()
+        err = max(err, parity_error(y.double().numpy(), ref[rows], TOL[w.dtype], "gated B=%d" % len(rows), None if v is None else v[rows]))
+    return err, plan
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -106,7 +110,7 @@ def test_gated_without_gates_is_forward_and_errors():
 
 def test_gated_cfg2_full_size_sampled_sequences():
     w = W["cfg2"]
-    u, gw, gv, k, y, plan = run_gated(w)
+    u, gw, gv, k, y, plan, _ = run_gated(w)
     assert plan.path == "fused3"
     kext = oracle.extend_filter(k, w.fft_size)
     worst = 0.0

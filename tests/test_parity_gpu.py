@@ -66,7 +66,8 @@ def test_small_transform_kernel_group_shapes(dtype, B, H, N, M):
 ])
 def test_short_transforms_grouped_on_the_8192_kernel(dtype, B, H, N, M):
     """fft 256 .. 4096, 16-bit I/O: 8192 / fft transforms share one work item of the wave-specialised kernel
-    (block-diagonal outermost stage)."""
+    (block-diagonal outermost stage).  Shapes of few rows run on the row kernel as they are and, repeated to a batch for the
+    matrix cores (batches() in parity_util), on this one."""
     w = synth.scaled(W["cfg2"], B=B, H=H, N=N, fft_size=M, dtype=dtype, alpha=(1e-2, 1e-1))
     err, plan = check_all_sequences(w)
     print("grouped %s B=%d H=%d N=%d M=%d path=%s factors=%s err=%.3e" % (dtype, B, H, N, M, plan.path, plan.factors, err),

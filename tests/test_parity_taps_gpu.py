@@ -13,7 +13,7 @@ import torch
 
 import oracle
 from paper_2311_05908_amd import fftconv, synth
-from parity_util import TOL, parity_error
+from parity_util import TOL, batches, parity_error
 
 pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS
@@ -27,8 +27,6 @@ def run_taps(dtype, B, H, N, M, seed=77):
     u = synth.gen_u(w)
     plan = fftconv.Plan(N, M, H, dtype)
     kf = plan.filter_fft(torch.from_numpy(k).cuda())
-    y = plan.forward(u.cuda(), kf)
-    torch.cuda.synchronize()
     ref = oracle.fftconv_taps(u.double().numpy(), pos, val, M)
     # all fft_size outputs of the circular convolution (the input zero-padded to the transform length): a unit
     # tap at N-1 leaves one non-zero sample among the N kept ones, so the error is measured against the rms of
@@ -37,8 +35,9 @@ def run_taps(dtype, B, H, N, M, seed=77):
     upad[..., :N] = u.double().numpy()
     full_rms = np.sqrt((oracle.fftconv_taps(upad, pos, val, M) ** 2).mean(axis=-1))
     del upad
-    err = parity_error(y.cpu().double().numpy(), ref, TOL[dtype], "taps %s B=%d H=%d N=%d M=%d" % (dtype, B, H, N, M),
-                       floor_rms=full_rms)
+    err = max(parity_error(plan.forward(u[rows].cuda(), kf).cpu().double().numpy(), ref[rows], TOL[dtype],
+                           "taps %s B=%d H=%d N=%d M=%d" % (dtype, len(rows), H, N, M), floor_rms=full_rms[rows])
+              for rows in batches(plan, B))
     print("taps %s B=%d H=%d N=%d M=%d path=%s factors=%s max rel L2 = %.3e" % (dtype, B, H, N, M, plan.path, plan.factors, err),
           flush=True)
     assert err <= TOL[dtype]

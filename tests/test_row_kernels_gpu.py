@@ -2,7 +2,7 @@
 every row length, the shortest and longest rows, odd and even sample counts around fft/2 (16-bit rows of even length
 move as words, the others element by element; the padded half is skipped up to fft/2), odd batches (a pair without
 partner) and row counts that leave a workgroup partly empty.  For the filter gradient on the same rows also the ways a
-channel's pairs are cut into runs."""
+channel's rows are cut into runs."""
 import pytest
 import torch
 
@@ -57,10 +57,10 @@ def test_row_gradient_edges(M, dtype):
 
 @pytest.mark.parametrize("B,H,M", [
     (1, 3, 1024),        # one run: transformed back in the same kernel
-    (13, 6000, 256),     # two runs of four pairs, the last one short of a pair; partly empty workgroups
-    (9, 256, 8192),      # two runs of three pairs
-    (5, 513, 8192),      # more channels than rows of threads wanted: one run of three pairs
-    (40, 3, 512),        # a run for every pair
+    (13, 6000, 256),     # two runs of seven rows, the last one a row short; partly empty workgroups
+    (9, 256, 8192),      # runs of five and of four rows
+    (5, 513, 8192),      # more channels than rows of threads wanted: one run of five rows
+    (40, 3, 512),        # a run for every row
 ])
 def test_row_gradient_runs(B, H, M):
     check_row_gradient("f32", B, H, 40, M, 50, None)
