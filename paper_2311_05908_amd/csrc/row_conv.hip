@@ -140,16 +140,22 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
     using G = ConvRow<M, IO>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T;
     constexpr int lds = RW * G::LDS_BYTES;
-    const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
-    if (total >= ((int64_t)1 << 31) - 8 * RW) {
-        set_error("fftconv_forward: too many sequences for the row kernel");
-        return FFTCONV_EUNSUPPORTED;
-    }
-    const int64_t groups = (total + RW - 1) / RW, per_die = (groups + 7) / 8;
     FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF>, lds));
-    hipLaunchKernelGGL((k_row_conv<M, IO, HALF>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
-                       (const float4 *)kf, rf::row_table<G>(p), (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
-    FC_HIP(hipGetLastError());
+    // A launch holds less than 2^32 threads, and the kernel counts rows in 32 bits: longer calls go out in pieces of MOST
+    // pairs, whole channels where the batch allows it.
+    constexpr int64_t MOST = ((int64_t)1 << 31) / G::T;
+    const int64_t H = p->H, N = p->N, npairs = (B + 1) / 2;
+    for (int64_t p0 = 0; p0 < npairs; p0 += MOST) {
+        const int64_t np = npairs - p0 < MOST ? npairs - p0 : MOST, nb = B - 2 * p0 < 2 * np ? B - 2 * p0 : 2 * np, nh = MOST / np;
+        for (int64_t h0 = 0; h0 < H; h0 += nh) {
+            const int64_t total = (H - h0 < nh ? H - h0 : nh) * np, groups = (total + RW - 1) / RW, per_die = (groups + 7) / 8;
+            const int64_t at = (2 * p0 * H + h0) * N;
+            hipLaunchKernelGGL((k_row_conv<M, IO, HALF>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u + at,
+                               (IO *)y + at, (const float4 *)kf + h0 * (M / 2), rf::row_table<G>(p), (int)nb, (int)H, (int)N, (int)np,
+                               (int)total, (int)per_die);
+            FC_HIP(hipGetLastError());
+        }
+    }
     return FFTCONV_OK;
 }
 

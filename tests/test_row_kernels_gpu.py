@@ -35,6 +35,22 @@ def test_row_convolution_edges_long(M):
         assert err <= TOL["f32"]
 
 
+@pytest.mark.parametrize("B,H,M", [
+    (2 ** 24 + 3, 2, 4096),          # a channel's pairs do not fit into a launch: cut along the batch
+    (2 ** 13 - 1, 2 ** 16 + 3, 256), # they do, but not those of all channels
+])
+def test_more_rows_than_threads_of_a_launch(B, H, M):
+    """Rows of one sample, which a filter of one tap scales: every output is a product, up to the fp32 errors of the transforms."""
+    g = torch.Generator(device="cuda").manual_seed(B)
+    u = torch.randn(B, H, 1, generator=g, device="cuda")
+    k = 1.0 + torch.rand(H, 1, generator=g, device="cuda")
+    plan = fftconv.Plan(1, M, H, "f32", path="small")
+    y = plan.forward(u, plan.filter_fft(k), out=torch.full_like(u, float("nan")))
+    err = ((y - u * k).abs().max() / u.abs().max()).item()
+    print("rows B=%d H=%d M=%d err=%.3e" % (B, H, M, err), flush=True)
+    assert err <= TOL["f32"]
+
+
 def check_row_gradient(dtype, B, H, N, M, Nk, path):
     w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
     u, dy = synth.gen_u(w), synth.gen_gate(w, "dy")
