@@ -169,14 +169,22 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
     using G = Row<M, true>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
     const Splits sp = grad_splits(M, p->H, B);
-    if (B >= ((int64_t)1 << 31) || p->H * sp.S >= ((int64_t)1 << 31) - RW) {
+    // rows of threads, and the threads of a launch (cut short without an error beyond 2^32), are 32-bit numbers
+    if ((p->H * sp.S + RW) * G::T > UINT32_MAX || (sp.S == 1 && B >= ((int64_t)1 << 31))) {
         set_error("fftconv_backward_filter: too many sequences for the row kernel");
         return FFTCONV_EUNSUPPORTED;
     }
     FC_TRY(raise_dynamic_lds((const void *)k_row_corr<M, IO, HALF>, lds));
-    hipLaunchKernelGGL((k_row_corr<M, IO, HALF>), dim3((unsigned)((p->H * sp.S + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u,
-                       (const IO *)dy, (float4 *)workspace, dk, rf::row_table<G>(p), (int)B, (int)p->H, (int)p->N, Nk, (int)sp.S, (int)sp.per);
-    FC_HIP(hipGetLastError());
+    // so are batch rows: a longer batch goes out in pieces of whole runs, two or more in each
+    const int64_t pieces = (sp.S * sp.per + (1 << 30) - 1) >> 30;
+    for (int64_t i = 0; i < pieces; ++i) {
+        const int64_t s0 = sp.S * i / pieces, ns = sp.S * (i + 1) / pieces - s0, b0 = s0 * sp.per, at = b0 * p->H * p->N;
+        const int64_t nb = B - b0 < ns * sp.per ? B - b0 : ns * sp.per;
+        hipLaunchKernelGGL((k_row_corr<M, IO, HALF>), dim3((unsigned)((p->H * ns + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u + at,
+                           (const IO *)dy + at, (float4 *)workspace + s0 * p->H * (M / 2), dk, rf::row_table<G>(p), (int)nb, (int)p->H,
+                           (int)p->N, Nk, (int)ns, (int)sp.per);
+        FC_HIP(hipGetLastError());
+    }
     if (sp.S == 1) return FFTCONV_OK;
     FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M>, lds));
     hipLaunchKernelGGL(k_row_dk<M>, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float4 *)workspace, dk,

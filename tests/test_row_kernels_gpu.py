@@ -82,6 +82,28 @@ def test_row_gradient_runs(B, H, M):
     check_row_gradient("f32", B, H, 40, M, 50, None)
 
 
+def test_row_gradient_of_more_rows_than_32_bits_count():
+    """2^31 + 5 rows of one sample: dk[0] is the sum of all products, a run at a time (exact here) and the 12288 runs one after the
+    other, each addition rounded to half a unit of the sum's last place (2^-24)."""
+    B = 2 ** 31 + 5
+    plan = fftconv.Plan(1, 256, 1, "bf16", path="small")
+    u = torch.ones(B, 1, 1, dtype=torch.bfloat16, device="cuda")
+    dy = torch.ones(B, 1, 1, dtype=torch.bfloat16, device="cuda")
+    u[-5:] = 2.0 ** 20                                            # the rows beyond 2^31 count too
+    dk = plan.backward_filter(u, dy, 2).cpu().double()
+    want = 2.0 ** 31 + 5 * 2.0 ** 20
+    print("row gradient B=%d dk=%s want=%.9e" % (B, dk.tolist(), want), flush=True)
+    assert abs(dk[0, 0].item() - want) <= 12288 * 2.0 ** -24 * want
+
+
+def test_row_gradient_refuses_more_threads_than_a_launch_holds():
+    plan = fftconv.Plan(1, 4096, 2 ** 24, "f32")
+    u = torch.zeros(1, 2 ** 24, 1, device="cuda")
+    with pytest.raises(fftconv.FFTConvError) as e:
+        plan.backward_filter(u, u, 1)
+    assert e.value.code == -2
+
+
 @pytest.mark.parametrize("H,M", [(128, 8192), (3, 512), (6000, 256), (70, 16384)])
 def test_row_gradient_workspace_of_a_larger_batch(H, M):
     """A workspace asked for once, for the largest batch, holds every smaller one (a last, partial batch)."""
