@@ -18,6 +18,7 @@
 //  * radices 32 and 16 (fewest twiddle products and exchanges that 64 data registers allow);
 //  * twiddles come from tables in thread order, [factor][thread] (gathers from a table of W_M^t, one cache line per lane,
 //    bounded the kernels that this file replaces).
+// FINE: radix-32 butterflies as 4 x 8 (dft32_4x8()), see row_grad.hip.
 // Two kinds of row.  EXACT: all R - 1 twiddles of a butterfly come from the table, each correct to its own rounding, and the
 // in-register butterflies take eight operations.  Otherwise the table holds those for 1, 2, 3 and the multiples of 4, the
 // others are products of them, and butterflies take six: a tenth more error of a transform, and at fft 1024 68 us
@@ -48,9 +49,9 @@ template <> struct Radix<16384> { static constexpr int R0 = 32, R1 = 32, R2 = 16
 constexpr int tw_count(int R, bool exact) { return exact ? R - 1 : R / 4 + 2; }
 constexpr int tw_power(int i, bool exact) { return exact || i < 3 ? i + 1 : 4 * (i - 2); }
 
-template <int M_, bool EXACT_ = false> struct Row {
+template <int M_, bool EXACT_ = false, bool FINE_ = false> struct Row {
     static constexpr int M = M_;
-    static constexpr bool EXACT = EXACT_;
+    static constexpr bool EXACT = EXACT_, FINE = FINE_;
     static constexpr int R0 = Radix<M>::R0, R1 = Radix<M>::R1, R2 = Radix<M>::R2;
     static constexpr int P = R0;                           // points per thread
     static constexpr int T = M / R0;                       // threads per row
@@ -187,6 +188,13 @@ template <typename G, bool FWD> __device__ __forceinline__ void exchange(float2 
     }
 }
 
+// a butterfly of the row's passes
+template <typename G, int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void butterfly(float2 (&x)[R])
+{
+    if constexpr (G::FINE && R == 32) dft32_4x8<INV, HALFIN>(x);
+    else dft_reg<R, INV, HALFIN, !G::EXACT>(x);
+}
+
 // Forward transform of the row whose samples j + T m the thread j = tid holds in x[m]; Z: the row's Row<M>::SLOTS
 // slots of LDS, free (the caller's barrier lies before).  HALF: x[m] = 0 for m >= R0 / 2.  On return x[p] holds
 // frequency freq(tid, p).  before_last() runs ahead of the last pass (loads that whoever uses the result needs).
@@ -197,7 +205,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
     {
         Tw0<G> t;
         t.load(tab, tid);
-        dft_reg<G::R0, false, HALF, !G::EXACT>(x);
+        butterfly<G, G::R0, false, HALF>(x);
         t.template apply<false>(x);
     }
     if constexpr (G::SPLIT) {
@@ -208,7 +216,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
             float2 v[G::RL];
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
-            dft_reg<G::RL, false, false, !G::EXACT>(v);
+            butterfly<G, G::RL, false>(v);
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
         }
@@ -225,7 +233,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
             float2 v[G::R1];
 #pragma unroll
             for (int m = 0; m < G::R1; ++m) v[m] = z[m * G::PAD];
-            dft_reg<G::R1, false, false, !G::EXACT>(v);
+            butterfly<G, G::R1, false>(v);
             tw1.template apply<false>(v);
 #pragma unroll
             for (int k = 0; k < G::R1; ++k) z[k * G::PAD] = v[k];
@@ -241,7 +249,7 @@ __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const floa
         float2 v[G::RL];
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) v[r] = z[r];
-        dft_reg<G::RL, false, false, !G::EXACT>(v);
+        butterfly<G, G::RL, false>(v);
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
     }
@@ -256,7 +264,7 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
         float2 v[G::RL];
 #pragma unroll
         for (int r = 0; r < G::RL; ++r) v[r] = x[i * G::RL + r];
-        dft_reg<G::RL, true, false, !G::EXACT>(v);
+        butterfly<G, G::RL, true>(v);
         if constexpr (G::SPLIT) {
 #pragma unroll
             for (int r = 0; r < G::RL; ++r) x[i * G::RL + r] = v[r];
@@ -271,7 +279,7 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
         Tw0<G> t;
         t.load(tab, tid);
         t.template apply<true>(x);
-        dft_reg<G::R0, true, false, !G::EXACT>(x);
+        butterfly<G, G::R0, true>(x);
         return;
     }
     row_barrier<G::T>();
@@ -283,7 +291,7 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
 #pragma unroll
             for (int k = 0; k < G::R1; ++k) v[k] = z[k * G::PAD];
             tw1.template apply<true>(v);
-            dft_reg<G::R1, true, false, !G::EXACT>(v);
+            butterfly<G, G::R1, true>(v);
 #pragma unroll
             for (int m = 0; m < G::R1; ++m) z[m * G::PAD] = v[m];
         }
@@ -295,7 +303,7 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
 #pragma unroll
     for (int k = 0; k < G::R0; ++k) x[k] = z0[k * G::PITCH];
     t.template apply<true>(x);
-    dft_reg<G::R0, true, false, !G::EXACT>(x);
+    butterfly<G, G::R0, true>(x);
 }
 
 // Host side: the twiddle table of Row<M>, rounded once; w(num, den) = exp(-2 pi i num / den) in fp64, num < den.

@@ -23,10 +23,14 @@ namespace fftconv {
 
 namespace {
 
-using rf::Row;
+// Rows of the gradient.  Of 1024 points: radix-32 butterflies as 4 x 8 (FINE), as both passes are of radix 32 there and dk came out
+// at 2.05e-7 of error (fp32, 4 x 64 rows of 512 samples), where a kernel for every factor had 1.97e-7; now 1.78e-7.
+// Same time: 64 x 768 rows of 512, 125 -> 117 us, of 1024, 158 - 161 -> 171, 16 x 256 37 -> 37.  Dividing 16 x 16 x 4 instead, 1.80e-7, costs
+// a trip through LDS: 154, 177, 30.
+template <int M> using GradRow = rf::Row<M, true, M == 1024>;
 
 // waves per SIMD that the registers allow without spills: 192 data registers with 32 points a thread, half of that with 16
-template <int M> constexpr int GRAD_WAVES = Row<M, true>::P == 32 ? 2 : 3;
+template <int M> constexpr int GRAD_WAVES = GradRow<M>::P == 32 ? 2 : 3;
 
 template <typename G>
 __device__ __forceinline__ void store_dk(const float2 (&x)[G::P], float *__restrict__ dk, int64_t Nk, float scale, int tid)
@@ -44,7 +48,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
     k_row_corr(const IO *__restrict__ u, const IO *__restrict__ dy, float4 *__restrict__ part, float *__restrict__ dk,
                const float2 *__restrict__ tab, int B, int H, int N, int64_t Nk, int S, int per)
 {
-    using G = Row<M, true>;
+    using G = GradRow<M>;
     constexpr int RW = rf::threads_of(M) / G::T;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T, rows = H * S;
@@ -111,7 +115,7 @@ template <int M>
 __global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
     k_row_dk(const float4 *__restrict__ part, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk, int S)
 {
-    using G = Row<M, true>;
+    using G = GradRow<M>;
     constexpr int RW = rf::threads_of(M) / G::T;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
@@ -153,7 +157,7 @@ Splits grad_splits(int64_t M, int64_t H, int64_t B)
 {
     int64_t want = 1;
     (void)rf::with_row(M, [&](auto g) -> int {
-        using G = Row<decltype(g)::M, true>;
+        using G = GradRow<decltype(g)::M>;
         want = 256 * 4 * GRAD_WAVES<G::M> * 64 / G::T / H;
         return FFTCONV_OK;
     });
@@ -166,7 +170,7 @@ Splits grad_splits(int64_t M, int64_t H, int64_t B)
 template <int M, typename IO, bool HALF>
 int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
 {
-    using G = Row<M, true>;
+    using G = GradRow<M>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
     const Splits sp = grad_splits(M, p->H, B);
     // rows of threads, and the threads of a launch (cut short without an error beyond 2^32), are 32-bit numbers
