@@ -196,7 +196,7 @@ int fftconv_plan_create_path(fftconv_plan **out, int64_t N, int64_t fft_size, in
     p->path = chosen;
     if (rc == FFTCONV_OK) rc = static_workspace_init(p->device);       // address of this device's static workspace
     if (rc == FFTCONV_OK) rc = staged_init(p);      // twiddle tables, scratch of the filter transform
-    if (rc == FFTCONV_OK && long_fft_supported(p)) rc = long_fft_init(p);
+    if (rc == FFTCONV_OK && fft_size >= 16384) rc = long_fft_init(p);      // (long_forward needs its tables whatever H)
     if (rc == FFTCONV_OK && hipMalloc((void **)&p->keep_dev, (size_t)(fft_size > MAX_BLOCKS ? fft_size : MAX_BLOCKS)) != hipSuccess) {
         set_error("fftconv_plan_create: hipMalloc of the block mask failed");
         rc = FFTCONV_ENOMEM;

@@ -612,7 +612,8 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
 
 }  // namespace
 
-// rows of fft_size = A * 8192, A = 2 .. 512; a row index must fit the grid's second dimension
+// The filter transform and the filter gradient: rows of fft_size = A * 8192, A = 2 .. 512; a channel must fit the grid's second
+// dimension (the forward pass goes in chunks of channels and takes any number)
 bool long_fft_supported(const fftconv_plan *p) { return p->M >= 2 * LB && p->M <= 512 * (int64_t)LB && p->H <= 65535; }
 
 int long_fft_init(fftconv_plan *p)

@@ -105,6 +105,22 @@ def test_fp32_long_rows_sampled_positions(lg, circular):
     assert err <= TOL["f32"]
 
 
+def test_fp32_long_rows_of_more_channels_than_a_grid_dimension():
+    """The generic filter transform, and the three-kernel forward pass with pairs of rows and a row without a partner."""
+    B, H, N, M = 3, 65537, 5, 32768
+    g = torch.Generator(device="cuda").manual_seed(1)
+    u, k = (torch.randn(*s, generator=g, device="cuda") for s in ((B, H, N), (H, N)))
+    plan = fftconv.Plan(N, M, H, "f32")
+    assert plan.path == "staged"
+    y = plan.forward(u, plan.filter_fft(k)).double()
+    ref = torch.zeros_like(y)
+    for j in range(N):
+        ref[..., j:] += k[:, j, None].double() * u[..., : N - j].double()
+    err = (y - ref).norm(dim=-1).div(ref.norm(dim=-1)).max().item()
+    print("fp32 long H=%d err=%.3e" % (H, err), flush=True)
+    assert err <= TOL["f32"]
+
+
 @pytest.mark.parametrize("dtype,B,H,N,M,paths", [
     ("bf16", 4, 3, 1024, 2048, ("fused3", "small")),          # matrix cores against vector ALUs
     ("f16", 5, 2, 128, 256, ("fused3", "small")),
