@@ -164,16 +164,20 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
 // k_f[h] in the order of the engine's registers, [register pair][thread][2], scaled by 1/M and by the frequency mask.
 // The taps are real, so a row is half as long: z[n] = k[2n] + i k[2n+1] is transformed in LDS (lds_fft.h, M/2 points: 139 KB at
 // M = 16384), and with its even and odd parts E, O every bin is K[f] = E[f] + W_M^f O[f] on the way out.
-// Bound by the LDS passes of its one or two workgroups on a compute unit.  128 channels of fft 8192: 25 us with a transform of M
-// points, its spectrum in memory and a kernel that permuted it; 19 us now, and fft 16384, which went through memory for every factor: fp32 8 x 64 x 8192 training step 217 -> 169.
-template <int M> constexpr int FILTER64_THREADS = M >= 8192 ? 512 : M <= 1024 ? 64 : M / 16;
-template <int M>
-__global__ void __launch_bounds__(FILTER64_THREADS<M>)
+// Bound by the latency of its passes.  Where a compute unit has one workgroup, which LDS makes it at 16384 points and up to 256
+// channels at any length, M / 4 threads (at most 1024) shorten them most; with more channels than that, workgroups
+// that fit beside one another do.  us, 4 / 256 / 3000 channels, one kernel for every row and one that permuted its spectrum (fft 16384: a
+// kernel for every factor) -> half-length rows with few threads -> now: fft 1024 8.3, 14, 70 -> 12.3, 12.6, 21 -> 7.0, 7.6, 21;
+// 4096 10.6, 46, 416 -> 13.2, 14.8, 60 -> 8.4, 10.2, 60; 8192 15, 53, 554 -> 15, 18, 112 -> 12, 15, 112; 16384 (4, 256, 1500) 26, 158, 966 ->
+// 32, 37, 206 -> 25, 29, 150.
+template <int M, bool FEW> constexpr int FILTER64_THREADS = FEW ? (M >= 4096 ? 1024 : M / 4) : M >= 8192 ? 512 : M <= 1024 ? 64 : M / 16;
+template <int M, bool FEW>
+__global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
     k_row_filter64(const float *__restrict__ k, float2 *__restrict__ kf, const double2 *__restrict__ w, FacList fl, int64_t Nk,
                    bool conj_out, const uint8_t *__restrict__ keep, int64_t n_blocks)
 {
     using G = Row<M>;
-    constexpr int MH = M / 2, NTHR = FILTER64_THREADS<M>, PER = MH / NTHR < 8 ? MH / NTHR : 8;
+    constexpr int MH = M / 2, NTHR = FILTER64_THREADS<M, FEW>, PER = MH / NTHR < 8 ? MH / NTHR : 8;
     extern __shared__ double2 XD[];
     const float *row = k + blockIdx.x * Nk;
     for (int n0 = threadIdx.x; n0 < MH; n0 += PER * NTHR) {
@@ -216,11 +220,16 @@ int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_ou
     return rf::with_row(p->M, [&](auto g) -> int {
         constexpr int M = decltype(g)::M;
         constexpr size_t lds = (size_t)(M / 2 + M / 32) * sizeof(double2);
-        FC_TRY(raise_dynamic_lds((const void *)k_row_filter64<M>, (int)lds));
-        hipLaunchKernelGGL(k_row_filter64<M>, dim3((unsigned)p->H), dim3(FILTER64_THREADS<M>), lds, s, k, (float2 *)kf, p->st.w64,
-                           staged_factors_for(M / 2), Nk, conj_out, keep_dev, n_blocks);
-        FC_HIP(hipGetLastError());
-        return FFTCONV_OK;
+        auto go = [&](auto few) -> int {
+            constexpr bool FEW = decltype(few)::value;
+            FC_TRY(raise_dynamic_lds((const void *)k_row_filter64<M, FEW>, (int)lds));
+            hipLaunchKernelGGL((k_row_filter64<M, FEW>), dim3((unsigned)p->H), dim3(FILTER64_THREADS<M, FEW>), lds, s, k, (float2 *)kf,
+                               p->st.w64, staged_factors_for(M / 2), Nk, conj_out, keep_dev, n_blocks);
+            FC_HIP(hipGetLastError());
+            return FFTCONV_OK;
+        };
+        if constexpr (M == 16384) return go(std::true_type());
+        else return p->H <= 256 ? go(std::true_type()) : go(std::false_type());
     });
 }
 

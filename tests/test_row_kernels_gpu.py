@@ -133,6 +133,17 @@ def test_row_gradient_workspace_of_a_larger_batch(H, M):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_fp64_filter_transform_of_few_and_many_channels(M):
+    """Up to 256 channels a workgroup has more threads; every channel's k_f is the same (to the bit) on either side."""
+    path = "small" if M <= 4096 else "staged"
+    for Nk in (1, M // 2 - 1, M):
+        k = torch.randn(257, Nk, generator=torch.Generator().manual_seed(Nk)).cuda()
+        many = fftconv.Plan(Nk, M, 257, "f32", path=path).filter_fft(k).view(257, -1)
+        few = fftconv.Plan(Nk, M, 256, "f32", path=path).filter_fft(k[1:]).view(256, -1)
+        assert torch.equal(many[1:], few)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
 def test_row_filter_edges(M, dtype):
