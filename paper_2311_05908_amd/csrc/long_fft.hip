@@ -211,6 +211,8 @@ template <typename G> __device__ __forceinline__ void store_row(const float2 (&x
 // Bound by the memory traffic: the digits (k1, k2, k3) of f' are those of the row engine's registers (k1 = k0, k2 = digit 1,
 // k3 = digit 2), so k_f needs no exchange through LDS.  128 channels of fft 131072 (142 MB): 54 us with stores of 16
 // slots in a row, 41 with four lane groups transposed and runs of 64.
+// fp32 pairs, 4 channels: fft 2^18 20.7 us with an LDS kernel, 22.5 with 8-byte stores and the last block fetched once more, 18.7
+// now; 2^21 46.6, 50.8, 42.5; 768 channels of fft 32768 151, 134, 110; bf16, 768 channels of fft 65536 230, 163, 157.
 // Workgroups are persistent, two to a compute unit, and fetch the next block ahead of the present one's transform: loads,
 // transforms and stores of workgroups that all start together otherwise take turns on the whole chip.
 template <int KF>
@@ -236,7 +238,7 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
         float2 x[G::P];
 #pragma unroll
         for (int p = 0; p < G::P; ++p) x[p] = next[p];
-        load_row<G>(next, source(blk + (int)gridDim.x < blocks ? blk + (int)gridDim.x : blk), tid);
+        if (blk + (int)gridDim.x < blocks) load_row<G>(next, source(blk + (int)gridDim.x), tid);
         rf::Tw1<G> tw1;
         tw1.load(tab, tid);
         rf::row_barrier<G::T>();                              // the slots are free
@@ -253,15 +255,20 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
             return keep ? lds_mask_weight(keep, n_blocks, km + A * (LB - 1 - G::freq(tid, p)), M) * scale : scale;
         };
         if constexpr (KF == 2) {
-            float2 *const o = (float2 *)kf;
+            // pairs of registers, as they lie in memory; bin 8191 - f' belongs to the thread and the register with all digits
+            // complemented, T - 1 - tid and P - 1 - p
+            float4 *const o = (float4 *)kf + row / 2 + tid, *const om = (float4 *)kf + row_m / 2 + (G::T - 1 - tid);
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) {
-                const int fi = G::freq(tid, p);
-                const float sc = weight(p);
-                o[row + G::index(fi)] = make_float2(x[p].x * sc, sgn * x[p].y * sc);
-                if (mirror) {
-                    const float scm = weight_m(p);
-                    o[row_m + G::index(LB - 1 - fi)] = make_float2(x[p].x * scm, -sgn * x[p].y * scm);
+            for (int q = 0; q < G::P / 2; ++q) {
+                const float s0 = weight(2 * q), s1 = weight(2 * q + 1);
+                o[q * G::T] = make_float4(x[2 * q].x * s0, sgn * x[2 * q].y * s0, x[2 * q + 1].x * s1, sgn * x[2 * q + 1].y * s1);
+            }
+            if (mirror) {
+#pragma unroll
+                for (int q = 0; q < G::P / 2; ++q) {
+                    const int a = G::P - 1 - 2 * q, b = a - 1;
+                    const float s0 = weight_m(a), s1 = weight_m(b);
+                    om[q * G::T] = make_float4(x[a].x * s0, -sgn * x[a].y * s0, x[b].x * s1, -sgn * x[b].y * s1);
                 }
             }
         } else {

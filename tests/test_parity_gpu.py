@@ -423,6 +423,7 @@ def test_frequency_sparse_masks_fft16384(keep_blocks):
     ("bf16", 16384, 32768, 64, tuple(range(8)) + tuple(range(56, 64)), "fused3"),   # half-length real transform
     ("bf16", 20000, 65536, 32, (0, 1, 30, 31), "multipass"),              # two-kernel fp32 transform, k_f by the block kernel
     ("f16", 8192, 8192, 8, (0, 7), "multipass"),                          # circular 8192: fp64 rows in LDS
+    ("f32", 16384, 32768, 32, (0, 1, 2, 31), "staged"),                   # fp32 k_f by the block kernel, mirror rows weighted by their own bins
 ])
 def test_block_masks_through_every_filter_transform(dtype, N, M, n_blocks, keep_blocks, path):
     """Frequency-block masks (weights 1 / 1/2 / 0 per bin) are applied inside each plan family's own filter transform."""
