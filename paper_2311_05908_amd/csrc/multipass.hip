@@ -1078,15 +1078,21 @@ __global__ void k_pack_multipass(const double2 *spec, uint32_t *kf, FacList fl, 
         (uint32_t)cv16<F16>((float)(v.x * sc)) | ((uint32_t)cv16<F16>((float)(v.y * sc)) << 16);
 }
 
-OuterGeo outer_geo(int64_t M)
+// rows: pairs of rows of a launch of the paired passes
+OuterGeo outer_geo(int64_t M, int64_t rows = 0)
 {
     OuterGeo g;
     g.No = (int)(M / MI);
     g.Ra = g.No < 16 ? g.No : 16;
     g.Rb = g.No / g.Ra;
     // No > 16: an fp32 tile T[No][CT] of 64 KiB (two blocks per compute unit), at least 32 columns.  Up to 16 a thread
-    // transforms a pair of columns in registers and there is no tile: two columns for every thread of a block.
+    // transforms a pair of columns in registers and there is no tile: two columns for every thread of a block, and up to No = 4
+    // several times that (of 8192 points, as above) where 1024 blocks or more remain: a block's start and its one trip to
+    // memory are most of its time there.  us, 8 x 1268 x 1321 bf16, fft 8192, plain / gated: 220 / 258 in blocks of 8192 columns with a
+    // tile, 225 / 361 with 1024, 150 / 196 with 8192; 2 x 16 x 8192 gated: 22, 14, 19 (1024 columns: 14); fft 16384, 8 x 512 x 1321: 158 / 169,
+    // 136 / 153, 111 / 116; fft 32768, 8 x 512 x 1321: 343 / 408, 251 / 300, 239 / 280.
     g.CT = g.Rb == 1 ? 2 * TB : MI / g.No < 32 ? 32 : MI / g.No;
+    while (g.Rb == 1 && g.CT * g.No < MI && rows * (MI / (2 * g.CT)) >= 1024) g.CT *= 2;
     return g;
 }
 
@@ -1316,9 +1322,10 @@ int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int
 static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, uint32_t *S,
                             hipStream_t s, int ko_lo, int ko_hi, const void *wg, const void *vg, bool lone)
 {
-    const OuterGeo g = outer_geo(p->M);
     const int64_t npairs = (B + 1) / 2;
     const int64_t rows = npairs * p->H;
+    const bool packed = lone && outer_real_ok((int)(p->M / MI));
+    const OuterGeo g = outer_geo(p->M, packed ? 0 : rows);
     if (rows > 65535) {
         set_error("fftconv_forward: ceil(B/2) * H = %lld exceeds the multi-pass grid limit 65535", (long long)rows);
         return FFTCONV_EUNSUPPORTED;
@@ -1328,7 +1335,6 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
     if (ko_lo >= ko_hi) ko_lo = ko_hi = g.No;            // nothing skipped
     // rows that passes A and B leave out, rows that pass C takes as zero, rows that pass C mirrors
     int ab_lo = ko_lo, ab_hi = ko_hi, c_lo = ko_lo, c_hi = ko_hi, mirror_from = g.No;
-    const bool packed = lone && outer_real_ok(g.No);
     if (packed) {
         // a sparse filter keeps ko < ko_lo and ko >= ko_hi = No - (ko_lo - 1), mirror images of each other: of the rows
         // ko <= No/2 those below ko_lo are live

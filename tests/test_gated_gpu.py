@@ -146,6 +146,9 @@ def test_gated_fused_16384_32768(dtype, B, H, N, M):
     ("f16", 3, 2, 20000, 65536),    # odd batch, ragged N (2-byte accesses)
     ("bf16", 2, 2, 8192, 8192),     # circular, no outer transform
     ("f16", 1, 1, 12002, 16384),    # N > fft/2, N not a multiple of 4
+    ("bf16", 9, 256, 1321, 8192),   # many rows: blocks of the outer passes make 8, 4 and 2 trips
+    ("f16", 8, 128, 3001, 16384),
+    ("bf16", 7, 86, 9999, 32768),
 ])
 def test_gated_multipass(dtype, B, H, N, M):
     w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype, alpha=(1e-3, 1e-2))

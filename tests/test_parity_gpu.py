@@ -301,6 +301,9 @@ def test_multipass_all_outputs(dtype, B, H, N, M):
     ("bf16", 2, 1, 32768, 32768),    # circular, outer length 4
     ("f16", 1, 1, 65536, 65536),     # circular, outer length 8
     ("bf16", 1, 1, 50000, 65536),    # N > fft/2, wrap-around taps
+    ("bf16", 9, 256, 1321, 8192),    # many rows: blocks of the outer passes make 8, 4 and 2 trips
+    ("f16", 8, 128, 3001, 16384),
+    ("bf16", 7, 86, 9999, 32768),
 ])
 def test_multipass_circular_and_ragged(dtype, B, H, N, M):
     """16-bit shapes with the input filling more than half of the transform (Section 2.1: circular convolution)
