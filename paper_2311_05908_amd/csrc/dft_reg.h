@@ -26,10 +26,12 @@ constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 // INV conjugates the kernel.  Radix-2 decimation in time, fully unrolled so every index and
 // twiddle is a compile-time constant.  A butterfly with a twiddle is eight fused operations, a + w b and
 // a - w b as two chained multiply-adds per part each; SIX: six, the difference as 2 a - (a + w b), which carries the
-// rounding of the sum (4 % more error of a transform).  Those with w = 1 or -+i are four additions.  HALFIN: the
+// rounding of the sum (4 % more error of a transform); PRODUCT: eight, w b first, then sum and difference in the place of its
+// operands (for kernels that are out of registers).  Those with w = 1 or -+i are four additions.  HALFIN: the
 // inputs x[R/2 ..] are zero (the padding of a causal convolution) and are not read; the first level of butterflies then
 // only copies.
-template <int R, bool INV, bool HALFIN = false, bool SIX = false> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
+enum Butterfly { EIGHT, SIX, PRODUCT };
+template <int R, bool INV, bool HALFIN = false, Butterfly FORM = EIGHT> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
 {
     constexpr int LG = ilog2(R);
 #pragma unroll
@@ -53,8 +55,11 @@ template <int R, bool INV, bool HALFIN = false, bool SIX = false> __device__ __f
             for (int j = 0; j < len / 2; ++j) {
                 const int q = j * (32 / len);                  // twiddle W_32^q, 0 <= q < 16
                 const float2 a = x[blk + j], b = x[blk + j + len / 2];
-                if (q == 0 || q == 8) {                        // 1; -i forward, +i inverse
-                    const float2 t = q == 0 ? b : INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x);
+                if (q == 0 || q == 8 || FORM == PRODUCT) {     // 1; -i forward, +i inverse
+                    const float wr = C32[q], wi = INV ? S32[q] : -S32[q];
+                    const float2 t = q == 0   ? b
+                                     : q == 8 ? (INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x))
+                                              : make_float2(__builtin_fmaf(-b.y, wi, b.x * wr), __builtin_fmaf(b.y, wr, b.x * wi));
                     x[blk + j] = make_float2(a.x + t.x, a.y + t.y);
                     x[blk + j + len / 2] = make_float2(a.x - t.x, a.y - t.y);
                 } else {
@@ -62,8 +67,8 @@ template <int R, bool INV, bool HALFIN = false, bool SIX = false> __device__ __f
                     const float wi = INV ? S32[q] : -S32[q];
                     const float sx = __builtin_fmaf(-b.y, wi, __builtin_fmaf(b.x, wr, a.x));
                     const float sy = __builtin_fmaf(b.y, wr, __builtin_fmaf(b.x, wi, a.y));
-                    const float dx = SIX ? __builtin_fmaf(2.f, a.x, -sx) : __builtin_fmaf(b.y, wi, __builtin_fmaf(-b.x, wr, a.x));
-                    const float dy = SIX ? __builtin_fmaf(2.f, a.y, -sy) : __builtin_fmaf(-b.y, wr, __builtin_fmaf(-b.x, wi, a.y));
+                    const float dx = FORM == SIX ? __builtin_fmaf(2.f, a.x, -sx) : __builtin_fmaf(b.y, wi, __builtin_fmaf(-b.x, wr, a.x));
+                    const float dy = FORM == SIX ? __builtin_fmaf(2.f, a.y, -sy) : __builtin_fmaf(-b.y, wr, __builtin_fmaf(-b.x, wi, a.y));
                     x[blk + j] = make_float2(sx, sy);
                     x[blk + j + len / 2] = make_float2(dx, dy);
                 }

@@ -138,6 +138,8 @@ struct OuterGeo {
 // EXACT (all four outer kernels): N is even and equals the input length the instantiation is for (M/2, or M
 // with FULLN), so every load of u and store of y is in range, 4-byte aligned and unconditional: the compiler
 // can then issue a thread's loads back to back instead of one guarded load at a time.
+// RB > 1: butterflies with the product first.  As chained multiply-adds they cost the passes of full-length rows their last
+// registers (28 - 40 bytes of scratch; 2 x 192 x 2^18 circular bf16 333 -> 352 us, 334 so; 2 x 48 x 2^20 334 - 342 -> 362, 342).
 template <bool F16, int RA, int RB, int CV, bool FULLN, bool GATED, bool EXACT>
 __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict__ u, uint32_t *__restrict__ S, int CT,
                                                  int B, int H, int N, int64_t M, int ko_lo, int ko_hi,
@@ -146,6 +148,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
     extern __shared__ float2 sm[];
     if (gate_closed(gate)) return;
     constexpr int No = RA * RB;
+    constexpr Butterfly FORM = RB > 1 ? PRODUCT : EIGHT;
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that can hold input
     float2 *wno = sm;                              // W_No^j, j < No
     float2 *T = sm + No;                           // [No][CT]
@@ -236,7 +239,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
                     x[a] = make_float2(0.f, 0.f);
                     if (a < RAIN) x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
                 }
-                dft_reg<RA, false, !FULLN>(x);
+                dft_reg<RA, false, !FULLN, FORM>(x);
                 const int r = r0 + c + v;
 #pragma unroll
                 for (int ka = 0; ka < RA; ++ka) {
@@ -263,7 +266,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
                 if (a < RAIN)                                        // (row b, row b+1) = (re, im)
                     x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
             }
-            dft_reg<RA, false, !FULLN>(x);
+            dft_reg<RA, false, !FULLN, FORM>(x);
 #pragma unroll
             for (int ka = 0; ka < RA; ++ka) o[ka][v] = cmulf(x[ka], wno[ka * b2]);
         }
@@ -286,7 +289,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
             float2 x[RB];
 #pragma unroll
             for (int b2 = 0; b2 < RB; ++b2) x[b2] = T[(ka * RB + b2) * CT + c + v];
-            dft_reg<RB, false>(x);
+            dft_reg<RB, false, false, FORM>(x);
             const int r = r0 + c + v;
             float2 w = wm((r * ka) & Mmask, ihm);                 // W_M^{r ka}
             const float2 step = wm((r * RA) & Mmask, ihm);        // W_M^{r RA}
@@ -327,6 +330,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     extern __shared__ float2 sm[];
     if (gate_closed(gate)) return;
     constexpr int No = RA * RB;
+    constexpr Butterfly FORM = RB > 1 ? PRODUCT : EIGHT;
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that are kept
     float2 *wno = sm;
     float2 *T = sm + No;                           // [No][CT]
@@ -412,7 +416,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
                 x[kb] = cmulcf(unpack2<F16>(in[kb][v]), w);
                 w = cmulf(w, step);
             }
-            dft_reg<RB, true>(x);
+            dft_reg<RB, true, false, FORM>(x);
 #pragma unroll
             for (int b2 = 0; b2 < RB; ++b2) o[b2][v] = cmulcf(x[b2], wno[ka * b2]);
         }
@@ -483,7 +487,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
                     x[ka] = T[(ka * RB + b2) * CT + c + v];
                 }
             }
-            dft_reg<RA, true>(x);
+            dft_reg<RA, true, false, FORM>(x);
 #pragma unroll
             for (int a = 0; a < RAIN; ++a) {
                 o0[a] |= (uint32_t)cv16<F16>(x[a].x) << (16 * v);

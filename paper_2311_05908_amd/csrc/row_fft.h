@@ -192,7 +192,7 @@ template <typename G, bool FWD> __device__ __forceinline__ void exchange(float2 
 template <typename G, int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void butterfly(float2 (&x)[R])
 {
     if constexpr (G::FINE && R == 32) dft32_4x8<INV, HALFIN>(x);
-    else dft_reg<R, INV, HALFIN, !G::EXACT>(x);
+    else dft_reg<R, INV, HALFIN, G::EXACT ? EIGHT : SIX>(x);
 }
 
 // Forward transform of the row whose samples j + T m the thread j = tid holds in x[m]; Z: the row's Row<M>::SLOTS
