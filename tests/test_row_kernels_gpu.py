@@ -51,6 +51,21 @@ def test_more_rows_than_threads_of_a_launch(B, H, M):
     assert err <= TOL["f32"]
 
 
+@pytest.mark.parametrize("N,H", [(256, 400), (250, 410), (128, 799)])
+def test_short_rows_beyond_the_memory_side_cache(N, H):
+    """fft 256, more than 256 MB of rows: channels instead of pairs are neighbours there, with the same bits as in two halves
+    (of an even number of rows, so that the pairs are the same)."""
+    B = 2 ** 26 // (H * N) + 3
+    B += 1 - B % 2
+    g = torch.Generator(device="cuda").manual_seed(N)
+    u = torch.randn(B, H, N, generator=g, device="cuda", dtype=torch.bfloat16)
+    plan = fftconv.Plan(N, 256, H, "bf16", path="small")
+    kf = plan.filter_fft(torch.randn(H, N, generator=g, device="cuda"))
+    y = plan.forward(u, kf, out=torch.full_like(u, float("nan")))
+    half = B // 4 * 2
+    assert torch.equal(y[:half], plan.forward(u[:half], kf)) and torch.equal(y[half:], plan.forward(u[half:], kf))
+
+
 def check_row_gradient(dtype, B, H, N, M, Nk, path):
     w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
     u, dy = synth.gen_u(w), synth.gen_gate(w, "dy")
