@@ -59,7 +59,7 @@ template <int R, bool INV, bool HALFIN = false, Butterfly FORM = EIGHT> __device
                     const float wr = C32[q], wi = INV ? S32[q] : -S32[q];
                     const float2 t = q == 0   ? b
                                      : q == 8 ? (INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x))
-                                              : make_float2(__builtin_fmaf(-b.y, wi, b.x * wr), __builtin_fmaf(b.y, wr, b.x * wi));
+                                              : make_float2(b.x * wr - b.y * wi, b.x * wi + b.y * wr);
                     x[blk + j] = make_float2(a.x + t.x, a.y + t.y);
                     x[blk + j + len / 2] = make_float2(a.x - t.x, a.y - t.y);
                 } else {

@@ -964,7 +964,7 @@ __global__ void k_big_dk_last(const float2 *__restrict__ tmp, float *__restrict_
     float2 x[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) x[k] = cmul_conj(tmp[h * BM + k * BLK + r], w[k * r]);
-    dft_reg<16, true>(x);
+    dft_reg<16, true, false, PRODUCT>(x);
 #pragma unroll
     for (int n = 0; n < 16; ++n)
         if (n * BLK + r < Nk) dk[h * Nk + n * BLK + r] = x[n].x * (1.0f / (float)BM);

@@ -63,6 +63,10 @@ template <typename V> struct TwTable {         // W^x = w[x]
     __device__ __forceinline__ V operator()(int64_t x) const { return w[x]; }
 };
 
+// the product first: filter transform of fft 16384, 768 channels of 5120 taps, 72.9 us with chained multiply-adds, 69.4 so
+template <int R, bool INV> __device__ __forceinline__ void lds_butterfly(float2 (&x)[R]) { dft_reg<R, INV, false, PRODUCT>(x); }
+template <int R, bool INV> __device__ __forceinline__ void lds_butterfly(double2 (&x)[R]) { dft_reg<R, INV>(x); }
+
 template <int R, bool INV, typename V>
 __device__ inline void lds_stage(V *X, const V *__restrict__ w, int M, int Sj, int Rj, int tws)
 {
@@ -77,7 +81,7 @@ __device__ inline void lds_stage(V *X, const V *__restrict__ w, int M, int Sj, i
             V x[R];
 #pragma unroll
             for (int n = 0; n < R; ++n) x[n] = X[lds_slot(base + n)];
-            dft_reg<R, INV>(x);
+            lds_butterfly<R, INV>(x);
 #pragma unroll
             for (int k = 0; k < R; ++k) X[lds_slot(base + k)] = x[k];
         }
@@ -93,7 +97,7 @@ __device__ inline void lds_stage(V *X, const V *__restrict__ w, int M, int Sj, i
             x[n] = X[lds_slot(base + n * Sj)];
             if (INV) x[n] = cmul_conj(x[n], c[n]);
         }
-        dft_reg<R, INV>(x);
+        lds_butterfly<R, INV>(x);
 #pragma unroll
         for (int k = 0; k < R; ++k) X[lds_slot(base + k * Sj)] = INV ? x[k] : cmul(x[k], c[k]);
     }
