@@ -420,14 +420,15 @@ def main():
                    "speedup_vs_dense": None if dense_ms is None else dense_ms / ms_per_step},
         # bound: the roof the kernel is nearer to (fraction of the HBM peak on algorithmic bytes against
         # fraction of the matrix-core peak on the decomposition's operations); neither is reached: the
-        # profiles show the step paced by vector-instruction issue ("limiter")
+        # board's power cap sets the clock, and in clocks the step is paced by vector-instruction issue ("limiter")
         "roofline": {"bound": "hbm" if hbm_frac >= mfma_frac else "mfma", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": hbm_frac, "traffic": None if args.gated else measured_traffic(w.name),
                      "mfma_frac": mfma_frac, "mfma_achieved": mfma_tflops, "mfma_peak": MFMA_PEAK_TFLOPS,
                      "mfma_unit": "TFLOP/s", "mfma_flops": flops,
                      "limiter": ("HBM traffic of the workspace (three passes, measured traffic about 2 x the algorithmic bytes, "
                                  "moved at 3.4-4.7 TB/s; profiles/multipass_cfg4.md)" if plan.path == "multipass" else
-                                 "vector-instruction issue (SQ_INSTS_VALU against SQ_BUSY_CYCLES in profiles/)"),
+                                 "board power cap (profiles/power.md); in clocks, vector-instruction issue (SQ_INSTS_VALU against "
+                                 "SQ_BUSY_CYCLES in profiles/)"),
                      "kernel": ("k_fused3_ws" if w.fft_size == 8192 else "k_fused3_big") if plan.path == "fused3" else plan.path,
                      "algorithmic_bytes": abytes},
     }

@@ -43,7 +43,10 @@
  *    kernel has been launched by that call.  fftconv_last_error() returns a
  *    thread-local description of the most recent failure on this thread.
  *  - Arithmetic: 16-bit I/O plans multiply bf16/fp16 operands on the matrix
- *    cores with fp32 accumulation; fp32 I/O plans compute in fp32.  All
+ *    cores with fp32 accumulation; fp32 I/O plans compute in fp32.  Plans of
+ *    the "small" family, and calls of few rows on "fused3" plans up to
+ *    fft_size 4096, run their transforms in fp32 whatever the I/O type: the
+ *    last bits of a row may depend on how many rows the call has.  All
  *    16-bit roundings are round-to-nearest-even.
  */
 #ifndef FFTCONV_H
@@ -103,8 +106,8 @@ size_t fftconv_workspace_bytes(const fftconv_plan *plan, int64_t B);
  * filter transform is computed once and reused over the batch).
  *   k: device, (H, Nk) fp32, 1 <= Nk <= fft_size; taps t >= Nk are zero.
  * The transform runs on the device: in fp32 for plans whose k_f is stored as 16-bit constants (16-bit I/O
- * from fft_size 256 up with N <= fft_size / 2 and N a multiple of 8, and every 16-bit plan from 16384 up), in
- * fp64 otherwise.  Asynchronous on `stream`; uses scratch memory owned by the plan, so calls on one plan must
+ * from fft_size 256 up with N <= fft_size / 2 and N a multiple of 8, and every 16-bit plan from 16384 up) and
+ * for fp32 plans of fft_size 32768 .. 2^21 with at most 65535 channels, in fp64 otherwise.  Asynchronous on `stream`; uses scratch memory owned by the plan, so calls on one plan must
  * not overlap. */
 int fftconv_filter_fft(const fftconv_plan *plan, const float *k, int64_t Nk, void *k_f, void *stream);
 
@@ -217,8 +220,8 @@ int fftconv_forward_gated(const fftconv_plan *plan, const void *u, const void *w
  * fftconv_backward_input: du from dy and the adjoint spectrum; arguments, layouts, workspace and
  * kernels are those of fftconv_forward (du must not alias dy).
  * fftconv_backward_filter: dk (device, (H, Nk) fp32, 1 <= Nk <= fft_size) from u and dy (device,
- * (B, H, N), plan dtype); the reduction over the batch runs in frequency space in fp32, in the
- * order of b (results are reproducible).  workspace: fftconv_workspace_bytes_backward_filter bytes. */
+ * (B, H, N), plan dtype); the reduction over the batch runs in frequency space in fp32, in an order
+ * that the sizes alone decide (results are reproducible).  workspace: fftconv_workspace_bytes_backward_filter bytes. */
 int fftconv_filter_fft_adjoint(const fftconv_plan *plan, const float *k, int64_t Nk, void *k_f, void *stream);
 int fftconv_backward_input(const fftconv_plan *plan, const void *dy, const void *k_f_adjoint, void *du,
                            int64_t B, int64_t H, int64_t N, void *workspace, void *stream);

@@ -646,7 +646,7 @@ void long_fft_destroy(fftconv_plan *p)
 }
 
 // The filter transform of channels [h0, h0 + nh) of a multi-pass plan: taps (nh, Nk) -> their rows of k_f; tmp holds
-// nh * M float2.  adjoint: the spectrum of the circularly time-reversed filter (the conjugate spectrum).
+// nh * (A/2 + 1) * 8192 float2 with multipass_filter_outer_ok(p) (the chunks of the caller count on it), else nh * M.  adjoint: the spectrum of the circularly time-reversed filter (the conjugate spectrum).
 int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
 {
@@ -657,7 +657,6 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
     const bool natural = multipass_filter_outer_ok(p);
     int rc = natural ? multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s)
                      : launch_fwd_cols<float>(g, k, nullptr, tmp, tw, nh, Nk, adjoint, s, true);
-    if (rc) return rc;
     if (rc) return rc;
     return p->dtype == FFTCONV_F16 ? launch_kf<1>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s)
                                    : launch_kf<0>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s);

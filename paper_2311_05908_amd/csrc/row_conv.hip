@@ -28,7 +28,7 @@ namespace {
 using rf::Row;
 
 // waves per SIMD the register budget is held to: what LDS allows (8.5 KB a wave, 17 KB where 32 points of a thread go
-// through it as pairs) and the registers can be had for without spills
+// through it as pairs) and the registers can be had for (spilled: 16 - 28 bytes of k_row_conv_few<2048> with an output gate)
 constexpr int waves_of(int M) { return M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2; }
 
 template <int M, typename IO> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096>;
@@ -175,18 +175,6 @@ int launch_half(const fftconv_plan *p, const void *u, const void *kf, void *y, i
     return p->N <= M / 2 ? launch<M, IO, true>(p, u, kf, y, B, s) : launch<M, IO, false>(p, u, kf, y, B, s);
 }
 
-struct SmallRadices { int r0, r1, r2; };
-SmallRadices small_radices(int64_t M)
-{
-    switch (M) {
-    case 256: return {16, 16, 1};
-    case 512: return {32, 16, 1};
-    case 1024: return {32, 32, 1};
-    case 2048: return {16, 16, 8};
-    default: return {16, 16, 16};
-    }
-}
-
 }  // namespace
 
 // The twiddle tables of the row kernels for a plan of M points (see row_table()), from w[t] = W_M^t
@@ -285,13 +273,12 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
 
 FacList small_factor_list(int64_t M)
 {
-    const SmallRadices r = small_radices(M);
-    FacList fl;
-    for (int i = 0; i < MAX_FACTORS; ++i) fl.fac[i] = 0;
-    fl.fac[0] = r.r0;
-    fl.fac[1] = r.r1;
-    fl.fac[2] = r.r2;
-    fl.nf = r.r2 > 1 ? 3 : 2;
+    FacList fl{};
+    (void)rf::with_row(M, [&](auto g) -> int {
+        using G = decltype(g);
+        fl = FacList{G::THREE ? 3 : 2, {G::R0, G::R1, G::R2}};
+        return FFTCONV_OK;
+    });
     return fl;
 }
 
@@ -303,10 +290,10 @@ bool small_supported(int64_t N, int64_t M, int dtype)
 
 int small_init(fftconv_plan *p)
 {
-    const SmallRadices r = small_radices(p->M);
-    p->f3.N1 = r.r0;
-    p->f3.N2 = r.r1;
-    p->f3.N3 = r.r2;
+    const FacList fl = small_factor_list(p->M);
+    p->f3.N1 = fl.fac[0];
+    p->f3.N2 = fl.fac[1];
+    p->f3.N3 = fl.fac[2];
     return FFTCONV_OK;
 }
 

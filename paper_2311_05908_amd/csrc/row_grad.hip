@@ -29,7 +29,8 @@ namespace {
 // a trip through LDS: 154, 177, 30.
 template <int M> using GradRow = rf::Row<M, true, M == 1024>;
 
-// waves per SIMD that the registers allow without spills: 192 data registers with 32 points a thread, half of that with 16
+// waves per SIMD that the registers allow: 192 data registers with 32 points a thread (12 - 60 bytes spilled where N > M / 2, and at
+// 1024 points), half of that with 16
 template <int M> constexpr int GRAD_WAVES = GradRow<M>::P == 32 ? 2 : 3;
 
 template <typename G>

@@ -134,9 +134,15 @@ def _check(rc: int, lib=None):
         raise FFTConvError(rc, detail)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr():
-    """The current stream of the current device as a plain integer (no Stream object: 1 us less on a call of 9)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The current stream of the current device as a plain integer (no Stream object, where this torch can do without: 1 us less
+    on a call of 9)."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def sparsity_fraction(dims, cuts) -> float:
