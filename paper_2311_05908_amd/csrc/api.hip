@@ -496,7 +496,7 @@ size_t fftconv_workspace_bytes_backward_filter(const fftconv_plan *p, int64_t B)
     if (f3::fused3_big_dk_supported(p))
         return (size_t)(2 * p->H * p->M) * sizeof(float2);
     if (row_backward_filter_ok(p)) return row_backward_filter_bytes(p, B);
-    if (long_fft_supported(p)) return long_backward_filter_bytes(p);
+    if (long_fft_supported(p)) return long_backward_filter_bytes(p, B);
     return staged_backward_filter_bytes(p);
 }
 

@@ -160,7 +160,7 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
 FacList long_fft_factor_list(int64_t M);
 size_t long_forward_workspace_bytes(const fftconv_plan *p);
 int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, hipStream_t s);
-size_t long_backward_filter_bytes(const fftconv_plan *p);
+size_t long_backward_filter_bytes(const fftconv_plan *p, int64_t B);
 int long_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B,
                          void *workspace, hipStream_t s);
 
@@ -304,7 +304,14 @@ size_t multipass_kf_bytes(const fftconv_plan *p);
 size_t multipass_workspace_bytes(const fftconv_plan *p, int64_t B);
 // outer pass of the filter transform of a multi-pass plan (multipass.hip), where a kernel for the plan's outer length exists
 bool multipass_filter_outer_ok(const fftconv_plan *p);
-int multipass_filter_outer(const fftconv_plan *p, const void *rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s);
+// The rows of a launch of it: row i < split is row (i / nh) * H + i % nh of src (channels [0, nh) of batch row after batch
+// row), row i >= split the same of src2 with i - split
+struct OuterRows {
+    const void *src, *src2;
+    int split, nh, H;
+};
+inline OuterRows outer_rows(const void *src) { return OuterRows{src, nullptr, INT32_MAX, INT32_MAX, 0}; }       // one after another
+int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s);
 int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int64_t Nk, int64_t nh, float scale, hipStream_t s);
 int multipass_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh,
                       const uint8_t *keep_dev, int64_t n_blocks, void *kf, hipStream_t s);

@@ -307,20 +307,25 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
 }
 
 // Filter gradient: sum over nb batch rows of conj(FFT(block of u)) . FFT(block of dy) for the blocks of a launch (grid:
-// blocks of a channel, channels; batch row b at a distance of b * stride), then back: acc holds the sum of earlier rows
-// unless first, and takes it unless last, when the inverse transform goes to out (which may be a block of tu).
+// blocks of a channel, channels, runs of `per` batch rows; batch row b at a distance of b * stride), then back: acc holds the sum
+// of earlier rows unless first, and takes it unless last, when the inverse transform goes to out (which may be a block of tu).
 // The spectra and their sum stay in registers (one transform at a time: 192 data registers), where three kernels
-// wrote and read them.
-__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(const float2 *tu, const float2 *td, int64_t stride, int nb,
+// wrote and read them; the row of dy is fetched with that of u, in the registers that then take the spectrum of u.
+// Several runs: a run's sum goes, in register order, where its first row of u was (nobody else reads that block), and
+// k_long_blocks_sum adds them up.  Few channels leave the chip idle otherwise, and two launches per batch row and tensor ahead of
+// this one: whole gradient, us, bf16 16 x 1 x 65536 307 -> 63, f16 73 x 1 x 20000 fft 65536 1317 -> 101, 16 x 1 x 2^20 467 -> 192, fp32
+// 8 x 16 x 10000 fft 32768 170 -> 52; 16 x 64 x 16384 464 -> 231; where the chip was full, bf16 2 x 256 x 65536, 414 -> 402.
+__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(float2 *tu, const float2 *td, int64_t stride, int nb, int per,
                                                                float4 *acc, float2 *out, const float2 *__restrict__ tab, bool first,
                                                                bool last)
 {
     using G = RB;
     extern __shared__ float2 XL[];
     const int64_t base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * LB;
-    const int tid = threadIdx.x;
-    float2 sum[G::P], zu[G::P];
-    if (first) {
+    const int tid = threadIdx.x, b0 = blockIdx.z * per, b1 = min(b0 + per, nb);
+    const bool runs = gridDim.z > 1;
+    float2 sum[G::P];
+    if (first || runs) {
 #pragma unroll
         for (int p = 0; p < G::P; ++p) sum[p] = make_float2(0.f, 0.f);
     } else {
@@ -332,36 +337,73 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(const float2 *tu,
         }
     }
 #pragma unroll 1
-    for (int i = 0; i < 2 * nb; ++i) {
+    for (int b = b0; b < b1; ++b) {
+        float2 x[G::P], z[G::P];
+        auto transform = [&](float2 (&v)[G::P], int j) {
+            rf::Tw1<G> tw1;
+            tw1.load(tab, j);
+            rf::row_barrier<G::T>();                          // the slots are free
+            rf::forward<G, false>(v, XL, tab, tw1, j, [] {});
+        };
         int j = tid;
         asm volatile("" : "+v"(j));                           // nothing of a step's addresses and twiddles is kept for the next
-        float2 x[G::P];
-        load_row<G>(x, (i & 1 ? td : tu) + (i / 2) * stride + base, j);
-        rf::Tw1<G> tw1;
-        tw1.load(tab, j);
-        rf::row_barrier<G::T>();                              // the slots are free
-        rf::forward<G, false>(x, XL, tab, tw1, j, [] {});
-        if (i & 1) {
+        load_row<G>(z, tu + b * stride + base, j);
+        load_row<G>(x, td + b * stride + base, j);
+        transform(z, j);
+        asm volatile("" : "+v"(j));
+        transform(x, j);
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) {                  // sum += conj(Z_u) Z_dy
-                sum[p].x = __builtin_fmaf(zu[p].y, x[p].y, __builtin_fmaf(zu[p].x, x[p].x, sum[p].x));
-                sum[p].y = __builtin_fmaf(-zu[p].y, x[p].x, __builtin_fmaf(zu[p].x, x[p].y, sum[p].y));
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < G::P; ++p) zu[p] = x[p];
+        for (int p = 0; p < G::P; ++p) {                      // sum += conj(Z_u) Z_dy
+            sum[p].x = __builtin_fmaf(z[p].y, x[p].y, __builtin_fmaf(z[p].x, x[p].x, sum[p].x));
+            sum[p].y = __builtin_fmaf(-z[p].y, x[p].x, __builtin_fmaf(z[p].x, x[p].y, sum[p].y));
         }
     }
-    if (!last) {
+    if (runs || !last) {
+        float4 *const o = (runs ? (float4 *)(tu + b0 * stride) : acc) + base / 2 + tid;
 #pragma unroll
-        for (int q = 0; q < G::P / 2; ++q)
-            acc[base / 2 + tid + q * G::T] = make_float4(sum[2 * q].x, sum[2 * q].y, sum[2 * q + 1].x, sum[2 * q + 1].y);
+        for (int q = 0; q < G::P / 2; ++q) o[q * G::T] = make_float4(sum[2 * q].x, sum[2 * q].y, sum[2 * q + 1].x, sum[2 * q + 1].y);
         return;
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
     rf::inverse<G>(sum, XL, tab, tw1, tid);
     store_row<G>(sum, out + base, tid);
+}
+
+// The sums of the runs above, `apart` pairs from one to the next, added up in order; acc, first, last, out as there.
+__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_sum(const float2 *part, int64_t apart, int runs, float4 *acc, float2 *out,
+                                                              const float2 *__restrict__ tab, bool first, bool last)
+{
+    using G = RB;
+    extern __shared__ float2 XL[];
+    const int64_t base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * LB;
+    const int tid = threadIdx.x;
+    float2 x[G::P];
+    auto add = [&](const float4 *in, bool set) {
+        float4 v[G::P / 2];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) v[q] = in[q * G::T];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) {
+            x[2 * q].x = set ? v[q].x : x[2 * q].x + v[q].x;
+            x[2 * q].y = set ? v[q].y : x[2 * q].y + v[q].y;
+            x[2 * q + 1].x = set ? v[q].z : x[2 * q + 1].x + v[q].z;
+            x[2 * q + 1].y = set ? v[q].w : x[2 * q + 1].y + v[q].w;
+        }
+    };
+    const float4 *const in = (const float4 *)(part + base) + tid;
+    add(first ? in : acc + base / 2 + tid, true);
+    for (int r = first ? 1 : 0; r < runs; ++r) add(in + r * (apart / 2), false);
+    if (!last) {
+        float4 *const o = acc + base / 2 + tid;
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) o[q * G::T] = make_float4(x[2 * q].x, x[2 * q].y, x[2 * q + 1].x, x[2 * q + 1].y);
+        return;
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::inverse<G>(x, XL, tab, tw1, tid);
+    store_row<G>(x, out + base, tid);
 }
 
 // Inverse, columns: the factors of A, then real part times scale of the samples n < Nk -> dk (rows, Nk).
@@ -486,14 +528,42 @@ int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, c
 // rows of the block kernels' launches: their LDS and the plan's table
 constexpr int B_LDS = RB::LDS_BYTES;
 
-int launch_corr(const fftconv_plan *p, int blocks, const float2 *tu, const float2 *td, int64_t stride, int64_t nb, float2 *acc,
+// Filter gradient of real rows: pairs of transformed rows of u and dy that a trip through the workspace aims at, 256 MiB.  us
+// with trips of 64, 128, 256 MiB, all at once: bf16 2 x 256 x 65536 545, 408, 402, 404; fp32 16 x 64 x 16384 fft 32768 510, 310, 231, 244;
+// bf16 64 rows of 2^20, one batch row 1196, 983, 911, 936; below, launches too short for the chip cost more than the memory-side
+// cache returns.
+constexpr int64_t GRAD_TRIP = (int64_t)1 << 25;
+
+// nh channels of `blocks` blocks each; runs of batch rows where channels alone leave compute units idle: as many as fill the
+// chip (two workgroups to a unit), and no more than pay for adding them up (a run's sum takes about a sixteenth of the time of
+// a batch row's two transforms, one after another)
+int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const float2 *td, int64_t stride, int64_t nb, float2 *acc,
                 float2 *out, bool first, bool last, hipStream_t s)
 {
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_corr, B_LDS));
-    hipLaunchKernelGGL(k_long_blocks_corr, dim3((unsigned)blocks, (unsigned)p->H), dim3(RB::T), B_LDS, s, tu, td, stride, (int)nb,
-                       (float4 *)acc, out, rf::row_table<RB>(p), first, last);
+    int64_t runs = 512 / (blocks * nh);
+    if (runs > nb) runs = nb;
+    while (runs > 1 && runs * runs > 16 * nb) --runs;
+    if (runs < 1) runs = 1;
+    const int64_t per = (nb + runs - 1) / runs;
+    runs = (nb + per - 1) / per;
+    const float2 *tab = rf::row_table<RB>(p);
+    hipLaunchKernelGGL(k_long_blocks_corr, dim3((unsigned)blocks, (unsigned)nh, (unsigned)runs), dim3(RB::T), B_LDS, s, tu, td, stride,
+                       (int)nb, (int)per, (float4 *)acc, out, tab, first, last);
+    FC_HIP(hipGetLastError());
+    if (runs == 1) return FFTCONV_OK;
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_sum, B_LDS));
+    hipLaunchKernelGGL(k_long_blocks_sum, dim3((unsigned)blocks, (unsigned)nh), dim3(RB::T), B_LDS, s, tu, per * stride, (int)runs,
+                       (float4 *)acc, out, tab, first, last);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
+}
+
+// Rows of a batch row's channel (A/2 + 1 blocks of 8192 pairs) that the workspace of the real pipeline below holds at most
+int64_t grad_rows(const fftconv_plan *p)
+{
+    const int64_t row = (p->M / LB / 2 + 1) * LB, all = 3 * p->H * p->M;
+    return (all > GRAD_TRIP ? all : GRAD_TRIP) / row;
 }
 
 template <typename IO>
@@ -515,21 +585,31 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         // acc (+)= conj(U) DY on them -- and the sum, the spectrum of a real sequence again, goes back through the
         // inverse block transforms and the real inverse outer pass: half the intermediate traffic of the complex
         // pipeline below, and a row without a partner costs no more than half a pair.
-        // The workspace holds the transformed rows of u and dy of as many batch rows as fit, and the sum if they do not all.
+        // The channels go in trips of about GRAD_TRIP pairs of transformed rows of u and dy, with all batch rows where they fit,
+        // else in pieces with the sum so far behind them.
         const int NR = g.A / 2 + 1;
-        const int64_t RW = H * NR * (int64_t)LB, fit = 3 * H * M / RW;
-        const bool once = 2 * B <= fit;
-        const int64_t nb = once ? B : (fit - 1) / 2;
-        float2 *acc = (float2 *)workspace, *tu = once ? acc : acc + RW, *td = tu + nb * RW;
-        for (int64_t b = 0; b < B; b += nb) {
-            const int64_t n = B - b < nb ? B - b : nb;
-            for (int64_t i = 0; i < n; ++i) {
-                FC_TRY(multipass_filter_outer(p, u + (b + i) * H * N, p->dtype, N, H, tu + i * RW, s));
-                FC_TRY(multipass_filter_outer(p, dy + (b + i) * H * N, p->dtype, N, H, td + i * RW, s));
+        const int64_t row = NR * (int64_t)LB, fit = grad_rows(p);
+        int64_t nh = H;
+        if (2 * B * H > GRAD_TRIP / row) nh = GRAD_TRIP / row / (2 * B);
+        if (nh > 16384 / B) nh = 16384 / B;                       // rows of a launch
+        if (nh < 1) nh = 1;
+        const int64_t trips = (H + nh - 1) / nh;
+        nh = (H + trips - 1) / trips;
+        const bool once = 2 * B * nh <= fit && 2 * B * nh <= 65535;
+        int64_t nb = once ? B : (fit - 1) / 2;                    // (nh is 1 then)
+        if (nb > 32767) nb = 32767;
+        for (int64_t h0 = 0; h0 < H; h0 += nh) {
+            const int64_t n_h = H - h0 < nh ? H - h0 : nh, stride = n_h * row;
+            for (int64_t b = 0; b < B; b += nb) {
+                const int64_t n = B - b < nb ? B - b : nb;
+                float2 *const tu = (float2 *)workspace, *const td = tu + n * stride, *const acc = tu + (fit - 1) * row;
+                const int64_t o = (b * H + h0) * N;
+                FC_TRY(multipass_filter_outer(p, OuterRows{u + o, dy + o, (int)(n * n_h), (int)n_h, (int)H}, p->dtype, N, 2 * n * n_h, tu, s));
+                FC_TRY(launch_corr(p, NR, n_h, tu, td, stride, n, acc, tu, b == 0, b + n == B, s));
             }
-            FC_TRY(launch_corr(p, NR, tu, td, RW, n, acc, tu, b == 0, b + n == B, s));
+            FC_TRY(multipass_dk_outer_inv(p, workspace, dk + h0 * Nk, Nk, n_h, 1.0f / (float)M, s));
         }
-        return multipass_dk_outer_inv(p, tu, dk, Nk, H, 1.0f / (float)M, s);
+        return FFTCONV_OK;
     }
     float2 *acc = (float2 *)workspace, *tu = acc + H * M, *td = tu + H * M;
     for (int64_t b = 0; b < B; b += 2) {                      // rows b and b + 1 share a transform
@@ -537,7 +617,7 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         const IO *d0 = dy + b * H * N, *d1 = b + 1 < B ? d0 + H * N : nullptr;
         FC_TRY(launch_fwd_cols<IO>(g, u0, u1, tu, tw, H, N, false, s));
         FC_TRY(launch_fwd_cols<IO>(g, d0, d1, td, tw, H, N, false, s));
-        FC_TRY(launch_corr(p, g.A, tu, td, 0, 1, acc, tu, b == 0, b + 2 >= B, s));
+        FC_TRY(launch_corr(p, g.A, H, tu, td, 0, 1, acc, tu, b == 0, b + 2 >= B, s));
     }
     FC_TRY(raise_lds((const void *)k_long_inv_cols_dk));
     hipLaunchKernelGGL(k_long_inv_cols_dk, dim3((unsigned)g.A, (unsigned)H), dim3(LT), L_LDS, s, tu, dk, tw, g.flA,
@@ -594,7 +674,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
             const int64_t nh = H - h0 < chunk ? H - h0 : chunk;
             const int64_t o0 = (b * H + h0) * N;
             if (as_real) {
-                rc = multipass_filter_outer(p, u + o0, FFTCONV_F32, N, nh, tmp, s);
+                rc = multipass_filter_outer(p, outer_rows(u + o0), FFTCONV_F32, N, nh, tmp, s);
                 if (rc) return rc;
                 hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)NR, (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
                                    (const float4 *)(kf + h0 * M), rf::row_table<RB>(p), g.flA, g.A, true);
@@ -655,7 +735,7 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
     // outer factor: the register kernel of the multi-pass route where it exists for this outer length (rows ko <= A/2
     // in natural order; the adjoint spectrum is then the conjugate, taken on the way out), else the generic column kernel
     const bool natural = multipass_filter_outer_ok(p);
-    int rc = natural ? multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s)
+    int rc = natural ? multipass_filter_outer(p, outer_rows(k), FFTCONV_F32, Nk, nh, tmp, s)
                      : launch_fwd_cols<float>(g, k, nullptr, tmp, tw, nh, Nk, adjoint, s, true);
     if (rc) return rc;
     return p->dtype == FFTCONV_F16 ? launch_kf<1>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s)
@@ -668,7 +748,7 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
                               const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
 {
     const LongGeo g = long_geo(p->M);
-    FC_TRY(multipass_filter_outer(p, k, FFTCONV_F32, Nk, nh, tmp, s));
+    FC_TRY(multipass_filter_outer(p, outer_rows(k), FFTCONV_F32, Nk, nh, tmp, s));
     return launch_kf<2>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, true, adjoint, s);
 }
 
@@ -686,7 +766,13 @@ int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, 
     return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace, s);
 }
 
-size_t long_backward_filter_bytes(const fftconv_plan *p) { return (size_t)(3 * p->H * p->M) * sizeof(float2); }
+// enough for every smaller batch
+size_t long_backward_filter_bytes(const fftconv_plan *p, int64_t B)
+{
+    if (!multipass_filter_outer_ok(p)) return (size_t)(3 * p->H * p->M) * sizeof(float2);
+    const int64_t row = (p->M / LB / 2 + 1) * LB, fit = grad_rows(p);
+    return (size_t)(2 * B < fit / p->H ? 2 * B * p->H * row : fit * row) * sizeof(float2);
+}
 
 int long_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B,
                          void *workspace, hipStream_t s)

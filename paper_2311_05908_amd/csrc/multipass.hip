@@ -805,9 +805,9 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
 // channel): the taps are real, the other rows are mirror images that the second kernel writes from these.
 // Taps at and beyond Nk are zeros (their loads read tap 0 and are discarded: no load sits behind a branch).
 // The filter gradient of these plans (long_fft.hip) transforms its rows of u and dy the same way: IN = 0: fp32
-// rows, 1: fp16, 2: bf16; row h starts at element h * Nk.
+// rows, 1: fp16, 2: bf16; row i of the launch is row rows.at(i) of its source, Nk elements each.
 template <int IN, int RA, int RB, bool FULLN>
-__global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restrict__ src, float2 *__restrict__ T2, int CG,
+__global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, float2 *__restrict__ T2, int CG,
                                                          int64_t Nk, int64_t M, bool wide)
 {
     extern __shared__ float2 sm[];
@@ -819,8 +819,12 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(const void *__restr
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int64_t h = blockIdx.y;
-    const float *row0 = (const float *)src + h * Nk;               // IN == 0
-    const uint16_t *row16 = (const uint16_t *)src + h * Nk;        // IN != 0
+    const bool second = (int)blockIdx.y >= rows.split;
+    const int at = (int)blockIdx.y - (second ? rows.split : 0);
+    const void *const src = second ? rows.src2 : rows.src;
+    const int64_t first = ((int64_t)(at / rows.nh) * rows.H + at % rows.nh) * Nk;
+    const float *row0 = (const float *)src + first;                // IN == 0
+    const uint16_t *row16 = (const uint16_t *)src + first;         // IN != 0
     if constexpr (RB > 1) {
         for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
         __syncthreads();
@@ -1041,28 +1045,28 @@ int launch_dk_outer_inv(const OuterGeo &g, const float2 *T2, float *dk, int64_t 
 }
 
 template <int IN, int RA, int RB>
-int launch_filter_outer_in(const OuterGeo &g, const void *k, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
+int launch_filter_outer_in(const OuterGeo &g, const OuterRows &rows, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
 {
     const size_t lds = g.lds();
     const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
-    const bool wide = Nk % 2 == 0 && ((uintptr_t)k & (IN == 0 ? 7 : 3)) == 0;
+    const bool wide = Nk % 2 == 0 && (((uintptr_t)rows.src | (uintptr_t)rows.src2) & (IN == 0 ? 7 : 3)) == 0;
     if (Nk > M / 2) {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, k, T2, g.pairs(), Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, M, wide);
     } else {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, k, T2, g.pairs(), Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, M, wide);
     }
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
 // dtype: FFTCONV_F32 / F16 / BF16 of the rows
 template <int RA, int RB>
-int launch_filter_outer(const OuterGeo &g, const void *k, int dtype, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
+int launch_filter_outer(const OuterGeo &g, const OuterRows &rows, int dtype, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
 {
-    if (dtype == FFTCONV_F32) return launch_filter_outer_in<0, RA, RB>(g, k, T2, Nk, M, nh, s);
-    if (dtype == FFTCONV_F16) return launch_filter_outer_in<1, RA, RB>(g, k, T2, Nk, M, nh, s);
-    return launch_filter_outer_in<2, RA, RB>(g, k, T2, Nk, M, nh, s);
+    if (dtype == FFTCONV_F32) return launch_filter_outer_in<0, RA, RB>(g, rows, T2, Nk, M, nh, s);
+    if (dtype == FFTCONV_F16) return launch_filter_outer_in<1, RA, RB>(g, rows, T2, Nk, M, nh, s);
+    return launch_filter_outer_in<2, RA, RB>(g, rows, T2, Nk, M, nh, s);
 }
 
 // k_f for the multi-pass path: [h][ko][inner order of f'] 16-bit (re, im) pairs, f = ko + No*f', scaled 1/M
@@ -1263,12 +1267,12 @@ int multipass_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, in
     return FFTCONV_OK;
 }
 
-// Outer pass of the transform of nh real rows of Nk samples each (see k_filter_outer_real; dtype: FFTCONV_F32 / F16 /
+// Outer pass of the transform of nh real rows of Nk samples each (see k_filter_outer_real, OuterRows; dtype: FFTCONV_F32 / F16 /
 // BF16 of the rows); T2 takes nh * (No/2 + 1) * 8192 fp32 pairs.  multipass_filter_outer_ok(): false = no such kernel
 // for this outer length (the caller takes the generic column kernel instead).
 bool multipass_filter_outer_ok(const fftconv_plan *p) { return outer_real_ok((int)(p->M / MI)); }
 
-int multipass_filter_outer(const fftconv_plan *p, const void *rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s)
+int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s)
 {
     const OuterGeo g = outer_geo(p->M);
     if (nh > 65535) {
