@@ -491,10 +491,11 @@ int fftconv_backward_input(const fftconv_plan *p, const void *dy, const void *k_
 size_t fftconv_workspace_bytes_backward_filter(const fftconv_plan *p, int64_t B)
 {
     if (!p || B <= 0) return 0;
+    // (the runs of a channel do not get fewer with a larger batch: a workspace holds every smaller one)
     if (f3::fused3_dk_supported(p))        // accumulated spectra of every channel (8192 slots each, whatever the plan's fft_size)
-        return (size_t)(p->H * 8192) * sizeof(float2);
+        return (size_t)(f3::fused3_dk_runs(p, B) * p->H * 8192) * sizeof(float2);
     if (f3::fused3_big_dk_supported(p))
-        return (size_t)(2 * p->H * p->M) * sizeof(float2);
+        return (size_t)((f3::fused3_big_dk_runs(p, B) + 1) * p->H * p->M) * sizeof(float2);
     if (row_backward_filter_ok(p)) return row_backward_filter_bytes(p, B);
     if (long_fft_supported(p)) return long_backward_filter_bytes(p, B);
     return staged_backward_filter_bytes(p);
@@ -521,13 +522,14 @@ int fftconv_backward_filter(const fftconv_plan *p, const void *u, const void *dy
     hipStream_t s = (hipStream_t)stream;
     if (B > 0 && f3::fused3_dk_supported(p)) {
         rc = f3::fused3_dk_accumulate(p, u, dy, workspace, B, s);       // 8192 accumulator slots per channel
-        if (!rc) rc = row_dk_finish(p, workspace, dk, Nk, s);
+        if (!rc) rc = row_dk_finish(p, workspace, f3::fused3_dk_runs(p, B), dk, Nk, s);
         return rc;
     }
     if (B > 0 && f3::fused3_big_dk_supported(p)) {
         float2 *dkf = (float2 *)workspace;                          // accumulated spectra, then a scratch row each
+        const int64_t runs = f3::fused3_big_dk_runs(p, B);
         rc = f3::fused3_big_dk_accumulate(p, u, dy, dkf, B, s);
-        if (!rc) rc = f3::fused3_big_dk_finish(p, dkf, dkf + p->H * p->M, dk, Nk, s);
+        if (!rc) rc = f3::fused3_big_dk_finish(p, dkf, runs, dkf + runs * p->H * p->M, dk, Nk, s);
         return rc;
     }
     if (B > 0 && row_backward_filter_ok(p)) return row_backward_filter(p, u, dy, dk, Nk, B, workspace, s);

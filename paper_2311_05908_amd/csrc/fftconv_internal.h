@@ -261,11 +261,13 @@ int staged_backward_filter(const fftconv_plan *p, const void *u, const void *dy,
 // fused filter gradient of the 8192-point plans (fused3_dk.hip)
 namespace f3 {
 bool fused3_dk_supported(const fftconv_plan *p);
+int64_t fused3_dk_runs(const fftconv_plan *p, int64_t B);          // accumulated spectra of a channel, to be added up
 int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s);
-// the same for fft 16384 plans (fused3_big.hip); dkf = H * 16384 float2
+// the same for fft 16384 and 32768 plans (fused3_big.hip); dkf = runs * H * fft_size float2
 bool fused3_big_dk_supported(const fftconv_plan *p);
+int64_t fused3_big_dk_runs(const fftconv_plan *p, int64_t B);
 int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s);
-int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, void *tmp, float *dk, int64_t Nk, hipStream_t s);
+int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, void *tmp, float *dk, int64_t Nk, hipStream_t s);
 }  // namespace f3
 
 // ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle tables, k_f layout, the convolution
@@ -286,7 +288,7 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
 // fp64 filter transform of the plans that convolve on the row engine with k_f in fp32
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s);
-int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s);
+int row_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, float *dk, int64_t Nk, hipStream_t s);
 // short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);
 FacList small_factor_list(int64_t M);      // its radices, outermost first

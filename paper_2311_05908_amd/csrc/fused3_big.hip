@@ -649,10 +649,12 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
 // at N2 = 16 and would be 2 x 128 at N2 = 32, where the kernel therefore walks through a channel's pairs twice,
 // each time keeping one k3 tile of the bins (phase A is repeated, stage 3 is not) with the spectrum of u held as
 // 16-bit pairs (32 registers; the accumulator stays fp32).  One workgroup per compute unit.
+// runs > 1 (fewer channels than compute units; gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's
+// pairs, dkf[run][h], and k_big_dk_blocks adds the runs up.
 template <typename TT, bool FULL, int N2>
 __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restrict__ u, const uint16_t *__restrict__ dy,
                                                          float2 *__restrict__ dkf, const void *__restrict__ consts, int B,
-                                                         int H, int N)
+                                                         int H, int N, int runs)
 {
     using CW = typename TT::CW;
     using BG = BigGeo<N2>;
@@ -664,8 +666,10 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
     extern __shared__ uint32_t XB[];
     const int tid = threadIdx.x, l = tid & 63, q = l >> 4, c16 = l & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int npairs = (B + 1) / 2;
-    const int nch = (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;      // channels h = blockIdx.x + j gridDim.x
+    const int run = runs > 1 ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
+    const int all_pairs = (B + 1) / 2, pair0 = (int)((int64_t)all_pairs * run / runs);
+    const int npairs = (int)((int64_t)all_pairs * (run + 1) / runs) - pair0;
+    const int nch = runs > 1 ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;      // channels h = blockIdx.x + j gridDim.x
     const int S = nch * NPASS * npairs * 2;                // inputs: ((j * NPASS + pass) * npairs + pair) * 2 + (0 = u, 1 = dy)
     if (S <= 0) return;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -731,8 +735,8 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
     uint2 x1r[2][R2][4];
     auto issue_pre = [&](int s, int c0, int c1) {         // chunks c0 .. c1 - 1
         const int item = s >> 1, which = s & 1;
-        const int jp = item / npairs, pair = item - jp * npairs;
-        const int h = (int)blockIdx.x + (jp / NPASS) * (int)gridDim.x;
+        const int jp = item / npairs, pair = pair0 + item - jp * npairs;
+        const int h = h_first + (jp / NPASS) * (int)gridDim.x;
         const uint16_t *src = which ? dy : u;
 #pragma unroll
         for (int c = c0; c < c1; ++c) {
@@ -904,8 +908,7 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
             }
         }
         if (which == 1 && pair == npairs - 1) {           // the pass's last pair: write its accumulator, start anew
-            const int h = (int)blockIdx.x + j * (int)gridDim.x;
-            float2 *dst = dkf + (size_t)h * BG::M;
+            float2 *dst = dkf + ((size_t)run * H + h_first + j * (int)gridDim.x) * BG::M;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -932,7 +935,7 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
 constexpr int DK_BLK_THREADS = 256;
 template <int N2>
 __global__ void __launch_bounds__(DK_BLK_THREADS) k_big_dk_blocks(const float2 *__restrict__ dkf, float2 *__restrict__ tmp,
-                                                                 const float2 *__restrict__ w, FacList fl, FacList fl_tail)
+                                                                 const float2 *__restrict__ w, FacList fl, FacList fl_tail, int runs)
 {
     constexpr int BM = BigGeo<N2>::M, BLK = BM / 16, RUN = BLK / 2, R2 = BigGeo<N2>::R2;
     __shared__ float2 XS[BLK + BLK / 16];
@@ -944,7 +947,13 @@ __global__ void __launch_bounds__(DK_BLK_THREADS) k_big_dk_blocks(const float2 *
         const int lane = j % 64, r = (j / 64) % 4, t3 = (j / 256) % 2, t2 = (j / 512) % R2;
         const int k2 = big_tau<N2>(16 * t2 + lane % 16), k3 = big_sigma(16 * t3 + 4 * (lane / 16) + r);
         const int f = k1 + 32 * k2 + 32 * N2 * k3;
-        XS[lds_slot(lds_pos(f, fl, BM) - d0 * BLK)] = dkf[h * BM + k1 * RUN + j];
+        float2 v = dkf[h * BM + k1 * RUN + j];
+        for (int i2 = 1; i2 < runs; ++i2) {
+            const float2 t = dkf[((int64_t)i2 * gridDim.y + h) * BM + k1 * RUN + j];
+            v.x += t.x;
+            v.y += t.y;
+        }
+        XS[lds_slot(lds_pos(f, fl, BM) - d0 * BLK)] = v;
     }
     __syncthreads();
     lds_inverse(XS, w, fl_tail, BLK, 16);
@@ -1300,18 +1309,31 @@ static int big_dk_accumulate_t(const fftconv_plan *p, const void *u, const void 
     using BG = BigGeo<N2>;
     const bool full = (B % 2 == 0) && p->N == BG::M / 2;
     const bool f16 = p->dtype == FFTCONV_F16;
-    void (*kern)(const uint16_t *, const uint16_t *, float2 *, const void *, int, int, int) =
+    void (*kern)(const uint16_t *, const uint16_t *, float2 *, const void *, int, int, int, int) =
         f16 ? (full ? k_fused3_big_dk<H16, true, N2> : k_fused3_big_dk<H16, false, N2>)
             : (full ? k_fused3_big_dk<B16, true, N2> : k_fused3_big_dk<B16, false, N2>);
     FC_TRY(raise_dynamic_lds((const void *)kern, (int)BG::LDS_BYTES));
-    const int grid = (int)(p->H < p->f3.num_cu ? p->H : p->f3.num_cu);
+    const int64_t runs = fused3_big_dk_runs(p, B);
+    const int grid = (int)(p->H < p->f3.num_cu ? p->H * runs : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), BG::LDS_BYTES, s, (const uint16_t *)u, (const uint16_t *)dy,
-                       (float2 *)dkf, (const void *)p->f3.consts, (int)B, (int)p->H, (int)p->N);
+                       (float2 *)dkf, (const void *)p->f3.consts, (int)B, (int)p->H, (int)p->N, (int)runs);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
 
-// dkf: H * fft_size float2 in the kernel's order
+// Runs of a channel's pairs: a workgroup for every compute unit, no more than there are pairs, and no more than pay for their sum
+// (20 us and more for a pair; a run's spectrum is added up by 16 workgroups a channel, 0.3 us).  Whole gradient, us, one run ->
+// these: f16 fft 16384, 64 x 4 rows 205 -> 60; bf16 fft 32768, 73 x 1 1006 -> 114, 16 x 1 (f16) 202 -> 57.
+int64_t fused3_big_dk_runs(const fftconv_plan *p, int64_t B)
+{
+    const int64_t npairs = (B + 1) / 2;
+    int64_t runs = p->f3.num_cu / p->H;
+    if (runs > npairs) runs = npairs;
+    while (runs > 1 && runs * runs > 64 * npairs) --runs;
+    return runs < 1 ? 1 : runs;
+}
+
+// dkf: runs * H * fft_size float2 in the kernel's order
 int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s)
 {
     if (((uintptr_t)u | (uintptr_t)dy) & 15) {
@@ -1328,7 +1350,7 @@ int fused3_big_dk_accumulate(const fftconv_plan *p, const void *u, const void *d
 }
 
 template <int N2>
-static int big_dk_finish_t(const fftconv_plan *p, const void *dkf, void *tmp, float *dk, int64_t Nk, hipStream_t s)
+static int big_dk_finish_t(const fftconv_plan *p, const void *dkf, int64_t runs, void *tmp, float *dk, int64_t Nk, hipStream_t s)
 {
     constexpr int BLK = BigGeo<N2>::M / 16;
     const FacList fl = staged_fac_list(p);
@@ -1340,7 +1362,7 @@ static int big_dk_finish_t(const fftconv_plan *p, const void *dkf, void *tmp, fl
     tail.nf = fl.nf - 1;
     for (int i = 0; i < MAX_FACTORS; ++i) tail.fac[i] = i + 1 < fl.nf ? fl.fac[i + 1] : 0;
     hipLaunchKernelGGL(k_big_dk_blocks<N2>, dim3(16, (unsigned)p->H), dim3(DK_BLK_THREADS), 0, s, (const float2 *)dkf,
-                       (float2 *)tmp, (const float2 *)p->st.w32, fl, tail);
+                       (float2 *)tmp, (const float2 *)p->st.w32, fl, tail, (int)runs);
     FC_HIP(hipGetLastError());
     const int bs = 256;
     hipLaunchKernelGGL(k_big_dk_last<N2>, dim3((unsigned)((p->H * BLK + bs - 1) / bs)), dim3(bs), 0, s, (const float2 *)tmp,
@@ -1350,9 +1372,9 @@ static int big_dk_finish_t(const fftconv_plan *p, const void *dkf, void *tmp, fl
 }
 
 // dkf: the accumulated spectra of fused3_big_dk_accumulate; tmp: H * fft_size float2 of scratch
-int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, void *tmp, float *dk, int64_t Nk, hipStream_t s)
+int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, void *tmp, float *dk, int64_t Nk, hipStream_t s)
 {
-    return p->M == 32768 ? big_dk_finish_t<32>(p, dkf, tmp, dk, Nk, s) : big_dk_finish_t<16>(p, dkf, tmp, dk, Nk, s);
+    return p->M == 32768 ? big_dk_finish_t<32>(p, dkf, runs, tmp, dk, Nk, s) : big_dk_finish_t<16>(p, dkf, runs, tmp, dk, Nk, s);
 }
 
 }  // namespace f3

@@ -15,8 +15,9 @@
 //   waves 4-7 ("inner"): stage 3 of input s; a u input leaves its spectrum in registers (fp32), the
 //                        dy input that follows multiplies it in and adds to the channel's accumulator.
 // A workgroup owns whole channels, so the accumulator (fp32, 64 registers per lane) never leaves the
-// registers until the channel's last pair, when it is written out in the kernel's k_f order.  The
-// inverse transform of the H accumulated spectra runs afterwards (row_dk_finish, row_filter.hip).
+// registers until the channel's last pair, when it is written out in the kernel's k_f order.  Where there are fewer
+// channels than compute units a channel's pairs are cut into runs, a workgroup each.  The
+// inverse transform of the H accumulated spectra, summed over the runs, follows (row_dk_finish, row_filter.hip).
 #include "fused3_common.h"
 
 namespace fftconv {
@@ -36,10 +37,11 @@ constexpr int PCH = G::M / 8 / PT;            // 16-byte input chunks per outer-
 // input (fused3.hip, build_tables): positions [g * half, (g + 1) * half) of an input's 4096-sample slot,
 // half = 2^lg_half = fft_size / 2, hold rows 2 (pair * groups + g), + 1.  The accumulator then holds one
 // spectrum per group (slots k1 = g * (32 / groups) + k1'), which the unpacking step adds up.
+// runs > 1 (gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's pairs; dkf[run][h].
 template <typename TT, bool FULL>
 __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u, const uint16_t *__restrict__ dy,
                                                  float2 *__restrict__ dkf, Consts cs, int B, int H, int N, int groups,
-                                                 int lg_half)
+                                                 int lg_half, int runs)
 {
     extern __shared__ uint32_t smem[];
     uint32_t *const XBb = smem;                                   // [2][XBW]
@@ -49,8 +51,10 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // channels of this workgroup: h = blockIdx.x + j * gridDim.x; its input stream: index
     // s = (j * npairs + pair) * 2 + which, which = 0 for the u rows of the pair, 1 for the dy rows
-    const int npairs = (B + 2 * groups - 1) / (2 * groups);
-    const int nch = (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int all_pairs = (B + 2 * groups - 1) / (2 * groups);
+    const int run = runs > 1 ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
+    const int pair0 = (int)((int64_t)all_pairs * run / runs), npairs = (int)((int64_t)all_pairs * (run + 1) / runs) - pair0;
+    const int nch = runs > 1 ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int S = nch * npairs * 2;
     if (S <= 0) return;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -78,8 +82,8 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
         auto issue_loads = [&](int s) {
             const int sc = s < S ? s : S - 1;                     // past the end: the last input again (unused)
             const int which = sc & 1, item = sc >> 1;
-            const int j = item / npairs, pair = item - j * npairs;
-            const int h = (int)blockIdx.x + j * (int)gridDim.x;
+            const int j = item / npairs, pair = pair0 + item - j * npairs;
+            const int h = h_first + j * (int)gridDim.x;
             const uint16_t *src = which ? dy : u;
 #pragma unroll
             for (int c = 0; c < PCH; ++c) {
@@ -213,12 +217,12 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
                 // last pair of a channel: write the accumulator out ([h][k1][r][lane], the k_f order) and clear it
                 const int j = item / npairs, pair = item - j * npairs;
                 if (which == 1 && pair == npairs - 1) {
-                    const int h = (int)blockIdx.x + j * (int)gridDim.x;
+                    const size_t h = (size_t)run * H + h_first + j * (int)gridDim.x;
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            dkf[(size_t)h * G::KF_PER_H + ((8 * wq + i) * 4 + r) * 64 + l] =
+                            dkf[h * G::KF_PER_H + ((8 * wq + i) * 4 + r) * 64 + l] =
                                 make_float2(accre[i][r], accim[i][r]);
                             accre[i][r] = 0.f;
                             accim[i][r] = 0.f;
@@ -234,7 +238,19 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
 
 bool fused3_dk_supported(const fftconv_plan *p) { return p->path == PATH_FUSED3 && p->M <= G::M; }
 
-// dkf: H * 8192 float2 in the kernel's order.
+// Runs of a channel's pairs: a workgroup for every compute unit, no more than there are pairs, and no more than pay for their sum
+// (5 us for a pair, 0.65 us for adding up a run's spectrum, one after another in row_dk_finish).  Whole gradient, us, bf16 fft 8192,
+// one run -> these: 64 x 4 rows 104 -> 39, 64 x 128 114 -> 73, 16 x 1 36 -> 27.
+int64_t fused3_dk_runs(const fftconv_plan *p, int64_t B)
+{
+    const int64_t groups = G::M / p->M, npairs = (B + 2 * groups - 1) / (2 * groups);
+    int64_t runs = p->f3.num_cu / p->H;
+    if (runs > npairs) runs = npairs;
+    while (runs > 1 && runs * runs > 8 * npairs) --runs;
+    return runs < 1 ? 1 : runs;
+}
+
+// dkf: runs * H * 8192 float2 in the kernel's order.
 int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s)
 {
     if (((uintptr_t)u | (uintptr_t)dy) & 15) {
@@ -252,13 +268,15 @@ int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, v
     }
     const bool full = (B % (2 * groups) == 0) && p->N == G::M / 2 / groups;
     const bool f16 = p->dtype == FFTCONV_F16;
-    void (*kern)(const uint16_t *, const uint16_t *, float2 *, Consts, int, int, int, int, int) =
+    void (*kern)(const uint16_t *, const uint16_t *, float2 *, Consts, int, int, int, int, int, int) =
         f16 ? (full ? k_fused3_dk<F16, true> : k_fused3_dk<F16, false>)
             : (full ? k_fused3_dk<BF16, true> : k_fused3_dk<BF16, false>);
     FC_TRY(raise_dynamic_lds((const void *)kern, (int)DK_LDS_BYTES));
-    const int grid = (int)(p->H < p->f3.num_cu ? p->H : p->f3.num_cu);
+    const int64_t runs = fused3_dk_runs(p, B);
+    const int grid = (int)(p->H < p->f3.num_cu ? p->H * runs : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), DK_LDS_BYTES, s, (const uint16_t *)u, (const uint16_t *)dy,
-                       (float2 *)dkf, consts_at<16, 16>(p->f3.consts), (int)B, (int)p->H, (int)p->N, groups, lg_half);
+                       (float2 *)dkf, consts_at<16, 16>(p->f3.consts), (int)B, (int)p->H, (int)p->N, groups, lg_half,
+                       (int)runs);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

@@ -102,10 +102,11 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     }
 }
 
-// dk[h][n] = Re(inverse transform)[n] / M, n < Nk, of the sum of the groups' spectra (added one after the other).
-template <int M>
+// dk[h][n] = Re(inverse transform)[n] / M, n < Nk, of the sum of the groups' spectra, and of the runs' (dkf[run][h]), added one
+// after the other.  RUNS: more than one (the loop over them takes up to 45 registers, 1 - 2 us of 20 with many channels).
+template <int M, bool RUNS>
 __global__ void __launch_bounds__(rf::threads_of(M), 2)
-    k_row_dk_finish(const float2 *__restrict__ dkf, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk)
+    k_row_dk_finish(const float2 *__restrict__ dkf, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk, int runs)
 {
     using G = Row<M>;
     constexpr int RW = ROWS<M>, NTHR = rf::threads_of(M);
@@ -127,6 +128,17 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
                 v[0].x += v[g].x;
                 v[0].y += v[g].y;
             }
+            for (int i = 1; RUNS && i < runs; ++i) {
+                const float2 *const next = in + (int64_t)i * H * SLOTS;
+                float2 t[SLOTS / M];
+#pragma unroll
+                for (int g = 0; g < SLOTS / M; ++g) t[g] = next[g * M + d];
+#pragma unroll
+                for (int g = 0; g < SLOTS / M; ++g) {
+                    v[0].x += t[g].x;
+                    v[0].y += t[g].y;
+                }
+            }
             image[d] = v[0];
         }
         __syncthreads();
@@ -136,17 +148,20 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     } else {
 #pragma unroll
         for (int p = 0; p < G::P; ++p) x[p] = in[kernel_slot<M>(G::freq(tid, p))];
-#pragma unroll
-        for (int g = 1; g < SLOTS / M; ++g) {
+        auto add = [&](const float2 *spec) {
             float2 v[G::P];
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) v[p] = in[g * M + kernel_slot<M>(G::freq(tid, p))];
+            for (int p = 0; p < G::P; ++p) v[p] = spec[kernel_slot<M>(G::freq(tid, p))];
 #pragma unroll
             for (int p = 0; p < G::P; ++p) {
                 x[p].x += v[p].x;
                 x[p].y += v[p].y;
             }
-        }
+        };
+#pragma unroll
+        for (int g = 1; g < SLOTS / M; ++g) add(in + g * M);
+#pragma unroll 1
+        for (int i = SLOTS / M; RUNS && i < runs * (SLOTS / M); ++i) add(in + (int64_t)(i / (SLOTS / M)) * H * SLOTS + i % (SLOTS / M) * M);
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
@@ -257,7 +272,7 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
 }
 
 // dkf: H * 8192 float2 in the kernels' slot order
-int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk, hipStream_t s)
+int row_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, float *dk, int64_t Nk, hipStream_t s)
 {
     return rf::with_row(p->M, [&](auto g) -> int {
         using G = decltype(g);
@@ -265,9 +280,10 @@ int row_dk_finish(const fftconv_plan *p, const void *dkf, float *dk, int64_t Nk,
             return FFTCONV_EUNSUPPORTED;
         } else {
             constexpr int NTHR = rf::threads_of(G::M), RW = ROWS<G::M>, lds = LDS_BYTES<G::M>;
-            FC_TRY(raise_dynamic_lds((const void *)k_row_dk_finish<G::M>, lds));
-            hipLaunchKernelGGL(k_row_dk_finish<G::M>, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float2 *)dkf,
-                               dk, rf::row_table<G>(p), (int)p->H, Nk);
+            const auto kern = runs > 1 ? k_row_dk_finish<G::M, true> : k_row_dk_finish<G::M, false>;
+            FC_TRY(raise_dynamic_lds((const void *)kern, lds));
+            hipLaunchKernelGGL(kern, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float2 *)dkf,
+                               dk, rf::row_table<G>(p), (int)p->H, Nk, (int)runs);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;
         }

@@ -1,5 +1,5 @@
-"""The filter gradient of transforms beyond 16384 points: the ways its batch rows are cut into runs, its channels into trips and its
-batch into pieces.  Short rows in long transforms, so that the reference is a short linear correlation in fp64."""
+"""The filter gradient of few channels and of transforms beyond 16384 points: the ways batch rows are cut into runs, channels into
+trips and a batch into pieces.  Short rows in long transforms, so that the reference is a short linear correlation in fp64."""
 import pytest
 import torch
 
@@ -28,6 +28,35 @@ def test_runs_trips_and_pieces(dtype, B, H, N, M):
     err = parity_error(dk.numpy(), ref.numpy(), TOL["f32"], "dk")
     print("long gradient %s B=%d H=%d N=%d M=%d err=%.3e" % (dtype, B, H, N, M, err), flush=True)
     assert err <= TOL["f32"]             # fp32 sums whatever the I/O type
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,N,M", [
+    (64, 2, 128, 256), (70, 3, 120, 256),        # two runs of one input each; of an input and a ragged one
+    (19, 1, 1000, 4096),                         # four transforms of 4096 points to an input: five inputs, five runs
+    (13, 100, 4096, 8192), (6, 1, 4000, 8192),   # two runs, of three and four pairs; a run for every pair, ragged rows
+    (5, 1, 8192, 16384), (27, 60, 5000, 16384),  # runs of one pair, the last without a partner; four runs, of three and four pairs
+    (8, 1, 16384, 32768), (7, 90, 2000, 32768),
+])
+def test_runs_of_matrix_core_gradients(dtype, B, H, N, M):
+    g = torch.Generator().manual_seed(B * N)
+    u, dy = (torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(2))
+    plan = fftconv.Plan(N, M, H, dtype, path="fused3")
+    dk = plan.backward_filter(u.cuda(), dy.cuda(), N).cpu().double()
+    U, D = torch.fft.rfft(u.double(), 2 * N), torch.fft.rfft(dy.double(), 2 * N)
+    ref = torch.fft.irfft((U.conj() * D).sum(0), 2 * N)[:, :N]
+    err = parity_error(dk.numpy(), ref.numpy(), TOL[dtype], "dk")
+    print("gradient in runs %s B=%d H=%d N=%d M=%d err=%.3e" % (dtype, B, H, N, M, err), flush=True)
+    assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("H,M,dtype", [(1, 8192, "bf16"), (100, 8192, "f16"), (300, 512, "bf16"), (7, 16384, "bf16"), (3, 32768, "f16")])
+def test_workspace_of_a_larger_batch_of_a_matrix_core_plan(H, M, dtype):
+    plan = fftconv.Plan(M // 2, M, H, dtype)
+    assert plan.path == "fused3"
+    sizes = [int(plan._lib.fftconv_workspace_bytes_backward_filter(plan._h, B)) for B in range(1, 80)]
+    assert sizes[0] > 0
+    assert sizes == sorted(sizes)
 
 
 @pytest.mark.parametrize("H,M", [(1, 32768), (40, 65536), (3, 1 << 21), (300, 1 << 17)])
