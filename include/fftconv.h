@@ -125,7 +125,8 @@ int fftconv_forward(const fftconv_plan *plan, const void *u, const void *k_f, vo
  * fftconv_forward; the call allocates and frees nothing (no hipMalloc, hipFree or allocating library
  * routine), it only launches the plan's kernels on `stream`.
  *   Fails with FFTCONV_EINVAL, before anything is launched, when fftconv_workspace_bytes(plan, B)
- *   exceeds FFTCONV_STATIC_WORKSPACE_BYTES (plans that need no workspace always fit).
+ *   exceeds FFTCONV_STATIC_WORKSPACE_BYTES (plans that need no workspace always fit; fp32 plans, whose rows can go
+ *   in smaller trips, fit up to H * fft_size * 8 bytes, whatever B).
  *   All calls on one GPU share that GPU's array, which keeps the previous call's contents; every kernel
  *   writes what it later reads, so nothing has to be cleared between calls.  Calls that overlap on one
  *   GPU (different streams or threads) race on the array: serialise them. */

@@ -459,7 +459,7 @@ int fftconv_forward_static(const fftconv_plan *p, const void *u, const void *k_f
 {
     int rc = forward_check(p, u, k_f, y, B, H, N, (void *)1, "fftconv_forward_static");
     if (rc || B == 0) return rc;
-    const size_t need = fftconv_workspace_bytes(p, B);
+    const size_t need = p->path == PATH_STAGED ? staged_workspace_bytes(p, B, true) : fftconv_workspace_bytes(p, B);
     if (need > FFTCONV_STATIC_WORKSPACE_BYTES) {
         set_error("fftconv_forward_static: this plan needs %zu bytes of workspace for B=%lld, the static workspace "
                   "holds %zu; use fftconv_forward with a workspace of the caller's",
@@ -471,6 +471,7 @@ int fftconv_forward_static(const fftconv_plan *p, const void *u, const void *k_f
         set_error("fftconv_forward_static: the static workspace of device %d was never initialised", p->device);
         return FFTCONV_EHIP;
     }
+    if (p->path == PATH_STAGED) return staged_forward(p, u, k_f, y, B, ws, (hipStream_t)stream, true);
     return fftconv_forward(p, u, k_f, y, B, H, N, need ? ws : nullptr, stream);
 }
 

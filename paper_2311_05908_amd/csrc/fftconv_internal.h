@@ -135,9 +135,9 @@ namespace fftconv {
 int staged_init(fftconv_plan *p);
 void staged_destroy(fftconv_plan *p);
 size_t staged_kf_bytes(const fftconv_plan *p);
-size_t staged_workspace_bytes(const fftconv_plan *p, int64_t B);
+size_t staged_workspace_bytes(const fftconv_plan *p, int64_t B, bool least = false);
 int staged_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B,
-                   void *workspace, hipStream_t s);
+                   void *workspace, hipStream_t s, bool least = false);
 // fp64 transform of zero-padded filters into p->filt_a for channels [h0, h0+nh):
 // on return filt_a holds position-ordered spectra (position -> frequency via staged_pos_to_freq).
 // adjoint: the spectrum of the circularly time-reversed filter (= the conjugate spectrum)
@@ -158,8 +158,9 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s);
 FacList long_fft_factor_list(int64_t M);
-size_t long_forward_workspace_bytes(const fftconv_plan *p);
-int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, hipStream_t s);
+// least: what the static workspace was sized for; the pass then goes in smaller trips
+size_t long_forward_workspace_bytes(const fftconv_plan *p, int64_t B, bool least);
+int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s);
 size_t long_backward_filter_bytes(const fftconv_plan *p, int64_t B);
 int long_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B,
                          void *workspace, hipStream_t s);

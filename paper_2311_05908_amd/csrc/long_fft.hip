@@ -72,6 +72,14 @@ struct LongTw {
     __device__ __forceinline__ float2 operator()(int64_t e) const { return cmul(hi[e >> 11], lo[e & 2047]); }
 };
 
+// Rows of a launch of the column kernels: row i is row first + i of the tensor, or, counted in pairs of batch rows of H channels,
+// channel j % H of batch row 2 (j / H), j = first + i (its partner lies H rows further, if the tensor has so many)
+struct LongRows {
+    int64_t first, H, rows;                    // H = 0: not in pairs
+    __device__ __forceinline__ int64_t at(int64_t i) const { return H ? (first + i) / H * H + first + i : first + i; }
+    __device__ __forceinline__ bool partner(int64_t i) const { return at(i) + H < rows; }
+};
+
 // A thread's share of a tile of 8192 points: LPT points LT apart.  All loads of a thread are issued before the
 // first value is used (a loop of load -> LDS write waits for every load in turn, and the round trip to HBM was most
 // of these kernels' time); the launches use LT threads.
@@ -129,17 +137,19 @@ __device__ inline void cols_stage_any(float2 *X, const LongTw &w, int A, int C, 
 
 // Forward, columns: rows of real input (re from src_re, im from src_im or zero; `len` valid samples, zeros
 // beyond; reversed: position n holds sample (M - n) mod M) -> tmp (rows, M) after the factors of A.
+// rows: where row i of the launch lies in its tensor (LongRows).
 // half_rows (real input only, src_im == nullptr): only the blocks of the outer frequency digits ko <= A/2 are
 // written; the others hold mirror images (see k_long_blocks_kf) and nobody reads them.
 template <typename In>
 __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src_re, const In *__restrict__ src_im,
                                                      float2 *__restrict__ tmp, LongTw w, FacList flA, int A, int C, int64_t len,
-                                                     bool reversed, bool half_rows)
+                                                     bool reversed, bool half_rows, LongRows rows)
 {
     extern __shared__ float2 XL[];
-    const int64_t M = (int64_t)A * LB, row = blockIdx.y;
+    const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(row) * len;
     const int col0 = blockIdx.x * C;
     const int lgC = __ffs(C) - 1;
+    const bool two = src_im && rows.partner(row);
     // samples beyond `len` are zeros: their loads go to sample 0 instead and are discarded, so that every load of
     // the thread is unconditional and in flight at once (see load_block)
     float vr[LPT], vi[LPT];
@@ -148,9 +158,9 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
         const int i = threadIdx.x + j * LT;
         int64_t n = (int64_t)(i >> lgC) * LB + col0 + (i & (C - 1));
         if (reversed && n != 0) n = M - n;
-        const int64_t at = row * len + (n < len ? n : 0);
+        const int64_t at = first + (n < len ? n : 0);
         vr[j] = ld_real(src_re, at);
-        vi[j] = src_im ? ld_real(src_im, at) : 0.f;
+        vi[j] = two ? ld_real(src_im, at) : 0.f;
     }
 #pragma unroll
     for (int j = 0; j < LPT; ++j) asm volatile("" ::"v"(vr[j]), "v"(vi[j]));      // keeps the loads unconditional
@@ -436,16 +446,18 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_dk(const float2 *__restric
 // rows share a complex transform (re = row b, im = row b + 1; k is real, so the two convolutions come back as re and im).
 //
 // Middle kernel: a block of 8192 positions forward, times its piece of k_f, and back, in place in tmp.
-// natural: tmp holds the rows ko <= A/2 of real sequences in the order of ko (A/2 + 1 blocks per channel, the output
-// of k_filter_outer_real); the k_f of digit ko sits at that digit's position among the A blocks of the channel.
+// natural: tmp holds the rows ko <= A/2 of real sequences in the order of ko (A/2 + 1 blocks per row, the output
+// of k_filter_outer_real); the k_f of digit ko sits at that digit's position among the A blocks of the channel.  Row i of the
+// launch belongs to channel (h0 + i) mod H.
 __global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restrict__ tmp, const float4 *__restrict__ kf,
-                                                               const float2 *__restrict__ tab, FacList flA, int A, bool natural)
+                                                               const float2 *__restrict__ tab, FacList flA, int A, bool natural, int h0,
+                                                               int H)
 {
     using G = RB;
     extern __shared__ float2 XL[];
     const int64_t base = natural ? ((int64_t)blockIdx.y * (A / 2 + 1) + blockIdx.x) * LB
                                  : ((int64_t)blockIdx.y * A + blockIdx.x) * LB;
-    const int64_t kbase = natural ? ((int64_t)blockIdx.y * A + lds_pos(blockIdx.x, flA, A)) * LB : base;
+    const int64_t kbase = ((int64_t)((h0 + (int)blockIdx.y) % H) * A + (natural ? lds_pos(blockIdx.x, flA, A) : (int)blockIdx.x)) * LB;
     const int tid = threadIdx.x;
     float2 x[G::P];
     load_row<G>(x, tmp + base, tid);
@@ -470,12 +482,14 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restric
 // (nullptr: no second row), the first N samples.
 template <typename IO>
 __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict__ tmp, IO *__restrict__ y_re,
-                                                       IO *__restrict__ y_im, LongTw w, FacList flA, int A, int C, int64_t N)
+                                                       IO *__restrict__ y_im, LongTw w, FacList flA, int A, int C, int64_t N,
+                                                       LongRows rows)
 {
     extern __shared__ float2 XL[];
-    const int64_t M = (int64_t)A * LB, row = blockIdx.y;
+    const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(row) * N;
     const int col0 = blockIdx.x * C;
     if (col0 >= N) return;
+    const bool two = y_im && rows.partner(row);
     load_cols(XL, tmp + row * M, C, col0);
     __syncthreads();
     int Sp = 1, R = A;
@@ -491,8 +505,8 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
         const int64_t n = (int64_t)a * LB + col0 + c;
         if (n < N) {
             const float2 v = XL[lds_slot(i)];
-            st_real(y_re, row * N + n, v.x);
-            if (y_im) st_real(y_im, row * N + n, v.y);
+            st_real(y_re, first + n, v.x);
+            if (two) st_real(y_im, first + n, v.y);
         }
     }
 }
@@ -515,12 +529,12 @@ int raise_lds(const void *kern) { return raise_dynamic_lds(kern, (int)L_LDS); }
 
 template <typename In>
 int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, const LongTw &w, int64_t rows, int64_t len,
-                    bool reversed, hipStream_t s, bool half_rows = false)
+                    bool reversed, hipStream_t s, bool half_rows = false, LongRows where = LongRows{0, 0, INT64_MAX})
 {
     const int rc = raise_lds((const void *)k_long_fwd_cols<In>);
     if (rc) return rc;
     hipLaunchKernelGGL(k_long_fwd_cols<In>, dim3((unsigned)g.A, (unsigned)rows), dim3(LT), L_LDS, s, re, im, tmp, w, g.flA,
-                       g.A, g.C, len, reversed, half_rows && im == nullptr);
+                       g.A, g.C, len, reversed, half_rows && im == nullptr, where);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -639,62 +653,97 @@ int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 
     return FFTCONV_OK;
 }
 
-// channels per trip through the workspace of the long forward pass: at most 512 MiB of it
-int64_t conv_chunk(const fftconv_plan *p)
+// ---- the forward pass: rows of the whole batch go through the workspace in trips (one pair of batch rows at a time, three launches each,
+// left the chip idle where channels are few: 30 x 1 x 65536 fft 65536 348 -> 28 us, 7 x 2 x 2^19 gated 219 -> 79, 8 x 16 x 131072 fft 2^18
+// 281 -> 169, 16 x 64 x 16384 fft 32768 262 -> 177).
+// Rows one at a time as real sequences (outer pass on the rows ko <= A/2, the blocks of those rows (forward, k_f, inverse), real
+// inverse outer pass; k_f is the spectrum of real taps, so the product is the spectrum of a real sequence again) where outer
+// lengths have register kernels for real rows (multipass.hip).  That is half the blocks of a complex transform per row, the same as
+// a pair's share, with cheaper outer kernels.  Measured, pairs against real rows, us: faster from A = 32 up (2.8 against 3.3 ms for 2^27
+// samples at fft 2^18), at A = 8 (8 x 64 x 32768 175, 168), and at A = 4, where the rows ko <= A/2 are 3 of 4, as long as
+// there are few (16 x 1 x 16384 25, 19; 16 x 64 177, 186).  A = 16 (8 x 32 x 65536 180, 159) keeps to pairs, as real rows are a tenth less
+// accurate there (3.45e-7, 3.80e-7; A = 8 3.55e-7, 3.51e-7; A = 4 3.29e-7, 3.20e-7).  A row without a partner goes as a real one,
+// or, where the chip has room, with the pairs and zeros for a partner.
+bool conv_real(const fftconv_plan *p, int64_t B)
 {
-    int64_t c = ((int64_t)512 << 20) / (p->M * (int64_t)sizeof(float2));
-    if (c < 1) c = 1;
-    return c < p->H ? c : p->H;
+    const int64_t A = p->M / LB;
+    return multipass_filter_outer_ok(p) && (A >= 32 || A == 8 || (A == 4 && B * p->H <= 512));
+}
+bool lone_in_pairs(const fftconv_plan *p, int64_t B) { return B > 1 && p->M / LB == 16 && (B + 1) / 2 * p->H * 16 <= 1024; }
+int64_t real_row(const fftconv_plan *p) { return (p->M / LB / 2 + 1) * LB; }
+
+// pairs of fp32 values in the workspace of a trip: 512 MiB, or a row where that is more.  us with 64, 128, 256, 512 MiB: 4 x 8 x 2^20 fft
+// 2^21 390, 368, 350, 344; 16 x 256 x 16384 fft 32768 751, 703, 719, 681; 16 x 256 x 32768 1572, 1419, 1443, 1378
+constexpr int64_t CONV_TRIP = (int64_t)1 << 26;
+// the workspace that the static entry point was sized for: a pair of batch rows of as many channels as 512 MiB hold
+int64_t conv_least(const fftconv_plan *p)
+{
+    const int64_t c = ((int64_t)512 << 20) / (p->M * (int64_t)sizeof(float2));
+    return (c < 1 ? 1 : c < p->H ? c : p->H) * p->M;
+}
+// no more for a smaller batch
+int64_t conv_pairs(const fftconv_plan *p, int64_t B)
+{
+    auto pairs = [](int64_t units, int64_t unit) {
+        const int64_t fit = CONV_TRIP / unit < 1 ? 1 : CONV_TRIP / unit;
+        return (units < fit ? units : fit) * unit;
+    };
+    if (conv_real(p, B)) return pairs(B * p->H, real_row(p));
+    const int64_t n = pairs((B + 1) / 2 * p->H, p->M);
+    const int64_t few = p->M / LB == 4 ? pairs(512, real_row(p)) : 0;
+    return n > few ? n : few;
 }
 
+// cap: pairs that the workspace holds (at least a row's)
 template <typename IO>
-int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, int64_t B, void *workspace, hipStream_t s)
+int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, int64_t B, void *workspace, int64_t cap, hipStream_t s)
 {
     const int64_t M = p->M, N = p->N, H = p->H;
     const LongGeo g = long_geo(M);
     const LongTw tw = long_tw(p);
     float2 *tmp = (float2 *)workspace;
-    const int64_t chunk = conv_chunk(p);
-    int rc = raise_dynamic_lds((const void *)k_long_conv_blocks, B_LDS);
-    if (!rc) rc = raise_lds((const void *)k_long_inv_cols_y<IO>);
-    if (rc) return rc;
-    // fp32 rows at outer lengths with register kernels for real rows (multipass.hip) can go one row at a time as
-    // real sequences: outer pass on the rows ko <= A/2, the blocks of those rows (forward, k_f, inverse), real inverse
-    // outer pass (k_f is the spectrum of real taps, so the product is the spectrum of a real sequence again).  That is
-    // half the blocks of a complex transform per row, the same as a pair's share, with cheaper outer kernels: measured
-    // faster from A = 32 up (2.8 against 3.3 ms for 2^27 samples at fft 2^18, 1.9 against 2.2 ms at 2^21), slower
-    // below, where the rows ko <= A/2 are well over half of all (3 of 4 at A = 4) -- except for a row without a
-    // partner, which otherwise pays for a whole pair.
-    const bool real_ok = std::is_same<IO, float>::value && multipass_filter_outer_ok(p);
-    const int NR = g.A / 2 + 1;
-    for (int64_t b = 0; b < B;) {
-        const bool two = b + 1 < B;
-        const bool as_real = real_ok && (g.A >= 32 || !two);
-        for (int64_t h0 = 0; h0 < H; h0 += chunk) {
-            const int64_t nh = H - h0 < chunk ? H - h0 : chunk;
-            const int64_t o0 = (b * H + h0) * N;
-            if (as_real) {
-                rc = multipass_filter_outer(p, outer_rows(u + o0), FFTCONV_F32, N, nh, tmp, s);
-                if (rc) return rc;
-                hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)NR, (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
-                                   (const float4 *)(kf + h0 * M), rf::row_table<RB>(p), g.flA, g.A, true);
-                FC_HIP(hipGetLastError());
-                rc = multipass_dk_outer_inv(p, tmp, (float *)(y + o0), N, nh, 1.0f, s);
-                if (rc) return rc;
-                continue;
-            }
-            rc = launch_fwd_cols<IO>(g, u + o0, two ? u + o0 + H * N : nullptr, tmp, tw, nh, N, false, s);
-            if (rc) return rc;
-            hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)g.A, (unsigned)nh), dim3(RB::T), B_LDS, s, tmp,
-                               (const float4 *)(kf + h0 * M), rf::row_table<RB>(p), g.flA, g.A, false);
+    FC_TRY(raise_dynamic_lds((const void *)k_long_conv_blocks, B_LDS));
+    FC_TRY(raise_lds((const void *)k_long_inv_cols_y<IO>));
+    auto blocks = [&](int per_row, int64_t first, int64_t n, bool natural) -> int {
+        hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)per_row, (unsigned)n), dim3(RB::T), B_LDS, s, tmp, (const float4 *)kf,
+                           rf::row_table<RB>(p), g.flA, g.A, natural, (int)(first % H), (int)H);
+        FC_HIP(hipGetLastError());
+        return FFTCONV_OK;
+    };
+    // trips of n of `units` units from `first` on, of about equal size; 65535: the grid's second dimension
+    auto trips = [&](int64_t units, int64_t unit, auto trip) -> int {
+        int64_t fit = cap / unit < 1 ? 1 : cap / unit;
+        if (fit > 65535) fit = 65535;
+        const int64_t count = (units + fit - 1) / fit;
+        for (int64_t i = 0; i < count; ++i) FC_TRY(trip(units * i / count, units * (i + 1) / count - units * i / count));
+        return FFTCONV_OK;
+    };
+    auto as_real = [&](int64_t row0, int64_t rows) -> int {
+        return trips(rows, real_row(p), [&](int64_t first, int64_t n) -> int {
+            const int64_t o = (row0 + first) * N;
+            FC_TRY(multipass_filter_outer(p, outer_rows(u + o), FFTCONV_F32, N, n, tmp, s));
+            FC_TRY(blocks(g.A / 2 + 1, row0 + first, n, true));
+            return multipass_dk_outer_inv(p, tmp, (float *)(y + o), N, n, 1.0f, s);
+        });
+    };
+    auto as_complex = [&](int64_t b, int64_t units, bool pairs) -> int {
+        return trips(units, M, [&](int64_t first, int64_t n) -> int {
+            const LongRows where{first, pairs ? H : 0, (B - b) * H};
+            const IO *u0 = u + b * H * N;
+            IO *y0 = y + b * H * N;
+            FC_TRY(launch_fwd_cols<IO>(g, u0, pairs ? u0 + H * N : nullptr, tmp, tw, n, N, false, s, false, where));
+            FC_TRY(blocks(g.A, first, n, false));
+            hipLaunchKernelGGL(k_long_inv_cols_y<IO>, dim3((unsigned)g.A, (unsigned)n), dim3(LT), L_LDS, s, (const float2 *)tmp, y0,
+                               pairs ? y0 + H * N : nullptr, tw, g.flA, g.A, g.C, N, where);
             FC_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_long_inv_cols_y<IO>, dim3((unsigned)g.A, (unsigned)nh), dim3(LT), L_LDS, s,
-                               (const float2 *)tmp, y + o0, two ? y + o0 + H * N : nullptr, tw, g.flA, g.A, g.C, N);
-            FC_HIP(hipGetLastError());
-        }
-        b += as_real ? 1 : 2;
-    }
-    return FFTCONV_OK;
+            return FFTCONV_OK;
+        });
+    };
+    if (conv_real(p, B)) return as_real(0, B * H);
+    if (lone_in_pairs(p, B)) return as_complex(0, (B + 1) / 2 * H, true);
+    if (B > 1) FC_TRY(as_complex(0, B / 2 * H, true));
+    if (B % 2 == 0) return FFTCONV_OK;
+    return multipass_filter_outer_ok(p) ? as_real((B - 1) * H, H) : as_complex(B - 1, H, false);
 }
 
 }  // namespace
@@ -755,15 +804,17 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
 // The position order of the spectra of these transforms (k_f of the fp32 plans from fft_size 32768 up is stored in it)
 FacList long_fft_factor_list(int64_t M) { return long_geo(M).fl; }
 
-size_t long_forward_workspace_bytes(const fftconv_plan *p)
+size_t long_forward_workspace_bytes(const fftconv_plan *p, int64_t B, bool least)
 {
-    return p->M <= 2 * LB ? 0 : (size_t)(conv_chunk(p) * p->M) * sizeof(float2);
+    return p->M <= 2 * LB ? 0 : (size_t)(least ? conv_least(p) : conv_pairs(p, B)) * sizeof(float2);
 }
 
-// forward pass of the fp32 plans from fft_size 32768 up; kf: (H, fft_size) fp32 pairs in position order
-int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, hipStream_t s)
+// forward pass of the fp32 plans from fft_size 32768 up; kf: (H, fft_size) fp32 pairs in position order; least: the workspace
+// holds only long_forward_workspace_bytes(p, B, true)
+int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s)
 {
-    return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace, s);
+    return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace,
+                                 least ? conv_least(p) : conv_pairs(p, B), s);
 }
 
 // enough for every smaller batch

@@ -305,14 +305,14 @@ void staged_destroy(fftconv_plan *p)
 
 size_t staged_kf_bytes(const fftconv_plan *p) { return (size_t)(p->H * p->M) * sizeof(float2); }
 
-size_t staged_workspace_bytes(const fftconv_plan *p, int64_t) { return long_forward_workspace_bytes(p); }
+size_t staged_workspace_bytes(const fftconv_plan *p, int64_t B, bool least) { return long_forward_workspace_bytes(p, B, least); }
 
 // fp32 I/O from fft_size 8192 up: one kernel up to 16384 (row_conv.hip), three above (long_fft.hip)
 int staged_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace,
-                   hipStream_t s)
+                   hipStream_t s, bool least)
 {
     if (p->M <= 16384) return row_forward(p, u, kf, y, B, s);
-    return long_forward(p, u, kf, y, B, workspace, s);
+    return long_forward(p, u, kf, y, B, workspace, least, s);
 }
 
 // Largest row the LDS-resident kernels take: 8192 fp64 or 16384 fp32 complex points with their padding.

@@ -1,0 +1,57 @@
+"""fp32 convolutions of transforms beyond 16384 points at the edges of how their rows share launches: as real rows or in pairs, an odd
+batch's last row, several trips through the workspace and those of the static one.  Short rows in long transforms, so that the
+reference is a short linear convolution in fp64."""
+import pytest
+import torch
+
+from paper_2311_05908_amd import fftconv
+from parity_util import TOL, parity_error
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(u, k):
+    N = u.shape[-1]
+    return torch.fft.irfft(torch.fft.rfft(u.double(), 2 * N) * torch.fft.rfft(k.double(), 2 * N), 2 * N)[..., :N]
+
+
+def data(B, H, N):
+    g = torch.Generator().manual_seed(B * H + N)
+    return torch.randn(B, H, N, generator=g), torch.randn(H, N, generator=g) / N ** 0.5
+
+
+@pytest.mark.parametrize("B,H,N,M", [
+    (1, 3, 100, 32768), (7, 73, 60, 32768), (7, 74, 61, 32768),     # real rows up to 512 of them, pairs and a lone row beyond
+    (2, 342, 50, 32768), (171, 3, 50, 32768),                       # pairs; pairs and a lone row, one row beyond the line
+    (5, 3, 1001, 65536), (86, 24, 40, 65536),                       # real rows, in one trip and in two
+    (1, 2, 333, 131072), (7, 16, 50, 131072), (9, 16, 51, 131072),  # pairs, the lone row with them or on its own
+    (16, 70, 30, 131072),                                           # pairs in two trips, the second from within a batch row
+    (3, 2, 777, 1 << 18), (35, 1, 20, 1 << 22),                     # real rows; pairs where there are no kernels for them
+])
+def test_rows_of_a_batch(B, H, N, M):
+    u, k = data(B, H, N)
+    plan = fftconv.Plan(N, M, H, "f32")
+    assert plan.path == "staged"
+    kf = plan.filter_fft(k.cuda())
+    y = plan.forward(u.cuda(), kf, out=torch.full_like(u, float("nan"), device="cuda"))
+    err = parity_error(y.cpu().double().numpy(), reference(u, k).numpy(), TOL["f32"], "y")
+    print("fp32 rows B=%d H=%d N=%d M=%d err=%.3e" % (B, H, N, M, err), flush=True)
+    assert err <= TOL["f32"]
+
+
+@pytest.mark.parametrize("B,H,N,M", [(40, 32, 30, 131072), (300, 1, 20, 131072), (50, 4, 100, 1 << 20)])
+def test_static_workspace_takes_any_batch(B, H, N, M):
+    """H * M * 8 bytes fit into the static workspace: smaller trips than fftconv_forward's, the same results."""
+    u, k = data(B, H, N)
+    plan = fftconv.Plan(N, M, H, "f32")
+    kf = plan.filter_fft(k.cuda())
+    assert plan.workspace_bytes(B) > fftconv.STATIC_WORKSPACE_BYTES >= H * M * 8
+    y = plan.forward_static(u.cuda(), kf, torch.full_like(u, float("nan"), device="cuda"))
+    assert torch.equal(y, plan.forward(u.cuda(), kf))
+
+
+@pytest.mark.parametrize("H,M", [(1, 32768), (40, 32768), (3, 65536), (2, 131072), (5, 1 << 18), (1, 1 << 22)])
+def test_workspace_of_a_larger_batch(H, M):
+    plan = fftconv.Plan(40, M, H, "f32")
+    sizes = [plan.workspace_bytes(B) for B in range(1, 700)]
+    assert sizes[0] > 0 and sizes == sorted(sizes)
