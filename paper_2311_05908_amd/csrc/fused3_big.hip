@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
                                                   const void *__restrict__ kf, const void *__restrict__ consts,
                                                   uint32_t kf_bytes, int B, int H, int N,
                                                   const uint16_t *__restrict__ wg, const uint16_t *__restrict__ vg,
-                                                  uint32_t live_k1, LaunchGate gate)
+                                                  uint32_t live_k1, int nx, LaunchGate gate)
 {
     using CW = typename TT::CW;
     using BG = BigGeo<N2>;
@@ -133,9 +133,9 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
     // Persistent workgroup; a work item t = h * npairs + pair.  Workgroups are dealt to the 8
     // accelerator dies (each with its own L2) round-robin, so die x = blockIdx % 8 takes the
     // channels h = x mod 8 and its workgroups walk through them side by side: at any time the
-    // workgroups of a die share a few channels, whose k_f then stays in that die's L2.
+    // workgroups of a die share a few channels, whose k_f then stays in that die's L2.  nx = 1: channels too few or too
+    // uneven for that (launch_big).
     const int npairs = (B + 1) / 2;
-    const int nx = gridDim.x % 8 == 0 ? 8 : 1;                    // dies the grid is spread over
     const int x = blockIdx.x % nx, nb = gridDim.x / nx, jb = blockIdx.x / nx;
     const int n_local = ((H - x + nx - 1) / nx) * npairs;         // work items of this die
     if (jb >= n_local) return;
@@ -601,42 +601,49 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
     vmem_settled();                                     // nothing of the prologue is still in flight inside the loop
     // Per pair, 5 workgroup barriers:
     //   [B(t)] | [C(t) -> registers] | [y(t), u(t+1) -> staging] | [staging -> registers] | [A(t+1); store y(t)] |
-    for (int v = jb; v < n_local; v += nb) {
+    // The last pair prepares no other one (calls of one pair a workgroup, us: bf16 4 x 100 x 8192 of fft 16384 22 -> 11.5, 2 x 100 x 16384 gated of
+    // fft 32768 44 -> 37); it is code of its own, so that the loop's stays free of branches.
+    auto pair_step = [&](const int v, const bool more) __attribute__((always_inline)) {
         opaque();
-        // Past the end of the range the last pair is prepared once more (in range, never used):
-        // the loop body stays free of branches.
-        const int t = item(v), tn = v + nb < n_local ? item(v + nb) : t;
+        const int t = item(v), tn = more ? item(v + nb) : t;
         phase_B(t / npairs);
         SCHED_FENCE();
         // tables of the next phase and the next pair's input: in flight across the barrier and phase C
         if constexpr (!RESIDENT) load_fixed_outer();
+        if (more) {
 #pragma unroll
-        for (int i = 0; i < PD; ++i) {
-            load_tabA(i);
-            load_twa(i);
+            for (int i = 0; i < PD; ++i) {
+                load_tabA(i);
+                load_twa(i);
+            }
+            issue_pre(tn);
         }
-        issue_pre(tn);
         issue_gate_v(t);
         SCHED_FENCE();
         lds_barrier();
         phase_C();
         lds_barrier();                                  // every wave has read its planes: the buffer is free
         stage_out();
-        stage_in();
+        if (more) stage_in();
         lds_barrier();
         read_y();
-        read_x1();
-        lds_barrier();                                  // staging consumed: phase A may overwrite it
-        phase_A();
-        SCHED_FENCE();
-        if constexpr (!RESIDENT) load_tab3();
-        load_plane0(tn / npairs);
-        SCHED_FENCE();
+        if (more) {
+            read_x1();
+            lds_barrier();                              // staging consumed: phase A may overwrite it
+            phase_A();
+            SCHED_FENCE();
+            if constexpr (!RESIDENT) load_tab3();
+            load_plane0(tn / npairs);
+            SCHED_FENCE();
+        }
         // the stores go last: loads and stores retire through one counter on this target, and
         // nothing issued after them is waited for before the next barrier
         store_y(t);
-        lds_barrier();
-    }
+        if (more) lds_barrier();
+    };
+    int v = jb;
+    for (; v + nb < n_local; v += nb) pair_step(v, true);
+    pair_step(v, false);
 }
 
 // ---- Filter gradient for fft 16384 and 32768 (Section 3.1 "Kernel Fusion and Recomputation"; see fused3_dk.hip
@@ -1111,9 +1118,14 @@ int launch_big(const fftconv_plan *p, const void *u, const void *kf, void *y, in
     const int64_t resident = (int64_t)p->f3.num_cu * ((N2 == 16 && !GATED) ? 2 : 1);
     int grid = (int)(T < resident ? T : resident);
     if (grid >= 8) grid -= grid % 8;
+    // a die's channels one after another, unless that takes more steps of a workgroup than all items in turn: us, f16
+    // 16 x 1 x 8192 of fft 16384 55 -> 9.7 (with what the last pair of a workgroup no longer prepares)
+    const int64_t pairs = (B + 1) / 2, steps = (T + grid - 1) / grid;
+    const int nx = grid % 8 == 0 && ((p->H + 7) / 8 * pairs + grid / 8 - 1) / (grid / 8) <= steps ? 8 : 1;
+    if (nx == 1) grid = (int)(T < resident ? T : resident);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), BG::LDS_BYTES, s, (const uint16_t *)u, (uint16_t *)y,
                        kf, (const void *)p->f3.consts, (uint32_t)kf_bytes, (int)B, (int)p->H, (int)p->N,
-                       (const uint16_t *)wg, (const uint16_t *)vg, live_k1, launch_gate());
+                       (const uint16_t *)wg, (const uint16_t *)vg, live_k1, nx, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
