@@ -274,7 +274,8 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         FC_HIP(hipMemcpyAsync(p->keep_dev, block_keep, (size_t)n_blocks, hipMemcpyHostToDevice, s));
         keep_dev = p->keep_dev;
     }
-    if (p->path == PATH_FUSED3) {
+    const bool fused = p->path == PATH_FUSED3 || p->f3.odd;
+    if (fused) {
         rc = fused3_filter(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, s);
         if (rc) return rc;
     }
@@ -284,7 +285,7 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         rc = row_filter64(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, s);
         if (rc) return rc;
     }
-    const bool long_rows = p->path == PATH_MULTIPASS && long_fft_supported(p);
+    const bool long_rows = p->path == PATH_MULTIPASS && !fused && long_fft_supported(p);
     // fp32 k_f in the position order of the long transforms (staged plans from fft 32768 up) with a real outer pass
     const bool long_rows_f32 = p->path == PATH_STAGED && p->M >= 32768 && long_fft_supported(p) && multipass_filter_outer_ok(p);
     // fp32 in two kernels per chunk; the scratch buffers, one behind the other, are sized for fp64 spectra, so they take four
@@ -309,7 +310,7 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         rc = long_filter_transform_f32(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, s);
         if (rc) return rc;
     }
-    for (int64_t h0 = 0; p->path != PATH_FUSED3 && !rows64 && !long_rows && !long_rows_f32 && h0 < p->H; h0 += p->filt_chunk) {
+    for (int64_t h0 = 0; !fused && !rows64 && !long_rows && !long_rows_f32 && h0 < p->H; h0 += p->filt_chunk) {
         int64_t nh = p->H - h0 < p->filt_chunk ? p->H - h0 : p->filt_chunk;
         double2 *spec = nullptr;
         rc = staged_filter_transform(p, k, Nk, h0, nh, s, &spec, adjoint);

@@ -91,6 +91,9 @@ struct Fused3Tables {
     // fft 16384 plans also carry the 8192-point tables: a short (partial) filter runs as overlapping
     // 8192-point segments, and k_f then holds a second, 8192-point spectrum after the dense one
     void *consts_short = nullptr;
+    // multi-pass plans of fft 16384 and 32768 whose rows the single kernel takes at any length (fused3_odd_rows); k_f and tables
+    // are that kernel's then
+    bool odd = false;
 };
 
 // fp16 plans of the multi-pass path (fft_size = No * 8192): 1 / fft_size itself is already a subnormal
@@ -190,6 +193,9 @@ int fused3_forward_short(const fftconv_plan *p, const void *u, const void *kf, v
                          hipStream_t s);
 // the 8192-point complex-row kernel used as the inner step of the multi-pass path
 int fused3_init_inner(fftconv_plan *p);
+// causal 16-bit shapes of fft 16384 and 32768 that are no multiple of 8 samples long: multi-pass plans by name (path, factors, workspace,
+// limits) that run on the single kernel
+bool fused3_odd_rows(const fftconv_plan *p);
 int fused3_inner_rows(const fftconv_plan *p, void *rows, const void *kf, int64_t rows_per_kf, int64_t kf_rows,
                       hipStream_t s, int ko_n = 0, int ko_lo = 0, int ko_hi = 0, bool quarter_rows = false);
 // the same kernel running the whole convolution of an 8192-point plan, u (B, H, N) -> y with N a multiple of 4
@@ -261,6 +267,9 @@ int staged_backward_filter(const fftconv_plan *p, const void *u, const void *dy,
 
 // fused filter gradient of the 8192-point plans (fused3_dk.hip)
 namespace f3 {
+// rows of any length 8 <= N <= fft_size / 2, anywhere in memory (plans with f3.odd; fused3_big.hip); either gate may be null
+int fused3_big_forward_odd(const fftconv_plan *p, const void *u, const void *wg, const void *vg, const void *kf, void *y, int64_t B,
+                           hipStream_t s);
 bool fused3_dk_supported(const fftconv_plan *p);
 int64_t fused3_dk_runs(const fftconv_plan *p, int64_t B);          // accumulated spectra of a channel, to be added up
 int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, void *dkf, int64_t B, hipStream_t s);

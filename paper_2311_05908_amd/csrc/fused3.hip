@@ -339,7 +339,14 @@ int fused3_init_inner(fftconv_plan *p)
     hipDeviceProp_t prop;
     FC_HIP(hipGetDeviceProperties(&prop, p->device));
     p->f3.num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    return build_tables<16, 16>(p, &p->f3.consts);
+    p->f3.odd = fused3_odd_rows(p);
+    return p->f3.odd ? fused3_big_init(p) : build_tables<16, 16>(p, &p->f3.consts);
+}
+
+// k_f of all channels within the kernel's 32-bit addressing (launch_big)
+bool fused3_odd_rows(const fftconv_plan *p)
+{
+    return (p->M == 16384 || p->M == 32768) && p->N >= 8 && p->N <= p->M / 2 && p->N % 8 != 0 && p->H * p->M * 4 < ((int64_t)1 << 31);
 }
 
 // ko_n > 0: the k_f rows come in groups of ko_n (outer frequency digit ko); only ko < ko_lo and ko >= ko_hi

@@ -103,7 +103,11 @@ template <int N2> __host__ __device__ inline int big_tau(int m) { return N2 == 3
 // nothing may be moved across: pins where the streamed table loads are issued
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// FULL: B even and N == fft_size / 2, every access of a work item is in range.
+// FORM: ROWS_FULL: B even and N == fft_size / 2, every access of a work item is in range.  ROWS_EVEN: N a multiple of 8, rows on 16-byte
+// boundaries, whole chunks are inside or outside.  ROWS_ODD: any N >= 8, rows anywhere: the chunk across the row's end is fetched from
+// the row's last 8 samples and moved down when it is staged, those beyond it likewise (a branch around either would have each load
+// waited for in turn).  Such shapes took the multi-pass route before; us, bf16, 5 x 256 x 10007 of fft 32768 111 -> 59, gated 128 -> 75, 47 x 1 x 13655
+// 36 -> 20, one row of 16 channels 17 -> 19; 16 x 256 x 5121 of fft 16384 130 -> 65, gated 198 -> 87, one row of 16 channels 15 -> 11.  Their bf16 instances compute the elementwise products in fp32 (B16W), to be no less accurate than that route.
 // SP (frequency-sparse filters, Appendix A.4), a set of bits:
 //   1 (HALF3): k_f is zero wherever k3 is in tile 1 of the order big_sigma();
 //   2 (HALF2, N2 = 32): k_f is zero wherever k2 is in tile 1 of the order big_tau();
@@ -112,7 +116,8 @@ template <int N2> __host__ __device__ inline int big_tau(int m) { return N2 == 3
 // GATED (gated form y = v . ((u . w) * k), Section 3.1 / 4.1): wg multiplies u as its chunks go into the
 // staging area, vg multiplies y as its chunks leave it (either may be null); the gates are fetched with the
 // next pair's input, right after phase B.  One workgroup per compute unit then (the extra chunks need registers).
-template <typename TT, bool FULL, int N2, int SP, bool GATED = false>
+enum RowForm { ROWS_EVEN, ROWS_FULL, ROWS_ODD };
+template <typename TT, int FORM, int N2, int SP, bool GATED = false>
 __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big(const uint16_t *__restrict__ u, uint16_t *__restrict__ y,
                                                   const void *__restrict__ kf, const void *__restrict__ consts,
                                                   uint32_t kf_bytes, int B, int H, int N,
@@ -122,6 +127,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
     using CW = typename TT::CW;
     using BG = BigGeo<N2>;
     constexpr int BPK1 = BG::PK1, BPN3 = BG::PN3, R2 = BG::R2, NCH = BG::NCH;
+    constexpr bool FULL = FORM == ROWS_FULL, ODD = FORM == ROWS_ODD;
     constexpr bool HALF3 = (SP & 1) != 0, HALF2 = (SP & 2) != 0, SKIP1 = (SP & 4) != 0;
     static_assert(!HALF2 || N2 == 32, "the middle digit has a second tile only at N2 = 32");
     constexpr int T3 = HALF3 ? 1 : 2;                             // live k3 tiles
@@ -269,6 +275,8 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
             const bool ok = FULL || (b < B && n < N);
             if constexpr (FULL) {
                 pre[j] = *(const uint4 *)(row + n);
+            } else if constexpr (ODD) {
+                pre[j] = load16(row + min(n, N - 8));
             } else {
                 uint4 v = make_uint4(0, 0, 0, 0);
                 if (ok) v = *(const uint4 *)(row + n);
@@ -280,6 +288,8 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
                 const uint16_t *wsrc = wg ? wg : u;
                 if constexpr (FULL) {
                     prew[j] = *(const uint4 *)(wsrc + (row - u) + n);
+                } else if constexpr (ODD) {
+                    prew[j] = load16(wsrc + (row - u) + min(n, N - 8));
                 } else {
                     uint4 g = make_uint4(0, 0, 0, 0);
                     if (ok) g = *(const uint4 *)(wsrc + (row - u) + n);
@@ -288,6 +298,9 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
             }
         }
     };
+    // ROWS_ODD: the samples behind the last whole chunk of row s of the pair are stored by the threads 8 s .. 8 s + 7, one each
+    const int tail_s = tid >> 3 & 1, tail_n = (N & ~7) + (tid & 7);
+    uint32_t vt = 0;
     // output gate of pair t (the pair whose y is stored at the end of this iteration)
     auto issue_gate_v = [&](int t) {
         if constexpr (GATED) {
@@ -300,11 +313,17 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
                 const uint16_t *vsrc = vg ? vg : u;               // see the input gate
                 if constexpr (FULL) {
                     prev[j] = *(const uint4 *)(vsrc + ((size_t)b * H + h) * N + n);
+                } else if constexpr (ODD) {
+                    prev[j] = load16(vsrc + ((size_t)min(b, B - 1) * H + h) * N + min(n, N - 8));
                 } else {
                     uint4 g = make_uint4(0, 0, 0, 0);
                     if (b < B && n < N) g = *(const uint4 *)(vsrc + ((size_t)b * H + h) * N + n);
                     prev[j] = g;
                 }
+            }
+            if constexpr (ODD) {
+                const uint16_t *vsrc = vg ? vg : u;
+                vt = vsrc[((size_t)min(2 * pair + tail_s, B - 1) * H + h) * N + min(tail_n, N - 1)];
             }
         }
     };
@@ -318,13 +337,20 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
     auto piece_ofs = [&](int s, int tile, int r) {
         return ((s * 16 + 4 * q + r) * N2 + 16 * tile + c16) * SB_ROW + 8 * w;
     };
-    auto stage_in = [&]() {                                   // pre -> US
+    // elements of chunk j that lie beyond the row's end, if any
+    auto beyond = [&](int j) { return (tid + NT * (j % (NCH / 2))) * 8 + 8 - N; };
+    auto stage_in = [&](int t) {                              // pre (of pair t) -> US
+        const bool two = 2 * (t % npairs) + 1 < B;
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             uint2 *dst = (uint2 *)(US + chunk_ofs(j));
             uint4 v = pre[j];
             if constexpr (GATED) {
                 if (wg) v = TT::mul8(v, prew[j]);
+            }
+            if constexpr (ODD) {
+                if (beyond(j) > 0) v = shift_down(v, beyond(j));
+                if (j >= NCH / 2 && !two) v = make_uint4(0, 0, 0, 0);
             }
             dst[0] = make_uint2(v.x, v.y);
             dst[1] = make_uint2(v.z, v.w);
@@ -439,6 +465,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
             }
     };
     uint4 yc[NCH];                                        // y of this pair, 16-byte chunks in memory order
+    uint32_t yt = 0;                                      // ROWS_ODD: ... and the sample (tail_s, tail_n)
     auto stage_out = [&]() {                              // yo -> YS
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -454,6 +481,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
             const uint2 a = src[0], b = src[1];
             yc[j] = make_uint4(a.x, a.y, b.x, b.y);
         }
+        if constexpr (ODD) yt = *(const uint16_t *)(YS + (tail_s * 16 * N2 + tail_n / 32) * SB_ROW + tail_n % 32 * 2);
     };
     auto store_y = [&](int t) {
         const int h = t / npairs, pair = t - h * npairs;
@@ -467,7 +495,16 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
             if constexpr (GATED) {
                 if (vg) v = TT::mul8(v, prev[j]);
             }
+            if constexpr (ODD) {
+                if (b < B && n + 8 <= N) store16(row + n, v);
+                continue;
+            }
             if (FULL || (b < B && n < N)) *(uint4 *)(row + n) = v;
+        }
+        if constexpr (ODD) {
+            if (GATED && vg) yt = (uint16_t)TT::mul8(make_uint4(yt, 0, 0, 0), make_uint4(vt, 0, 0, 0)).x;
+            const int b = 2 * pair + tail_s;
+            if (tid < 16 && tail_n < N && b < B) y[((size_t)b * H + h) * N + tail_n] = (uint16_t)yt;
         }
     };
 
@@ -516,7 +553,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
                         dim = TT::mfma(tab3[ks][ct3][1], x3[ct2][ks], dim);
                     }
                     // lane: k2 = big_tau(16 ct2 + c16); reg r: k3 = big_sigma(16 ct3 + 4q + r)
-                    x3i[ct2][ct3] = TT::template ctw4<true>(dre, dim, kfR[i % PD][ct2][ct3]);
+                    x3i[ct2][ct3] = TT::template kfw4<true>(dre, dim, kfR[i % PD][ct2][ct3]);
                 }
             SCHED_FENCE();
             if (next) load_kf(i + PD, h);
@@ -587,7 +624,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
         load_tabA(i);
         load_twa(i);
     }
-    stage_in();
+    stage_in(item(jb));
     lds_barrier();
     read_x1();
     lds_barrier();
@@ -624,7 +661,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
         phase_C();
         lds_barrier();                                  // every wave has read its planes: the buffer is free
         stage_out();
-        if (more) stage_in();
+        if (more) stage_in(tn);
         lds_barrier();
         read_y();
         if (more) {
@@ -1095,12 +1132,12 @@ template <typename Fn> void fill_op(uint16_t *dst, bool f16, int t, int ct, int 
     }
 }
 
-template <typename TT, bool FULL, int N2, int SP, bool GATED = false>
+template <typename TT, int FORM, int N2, int SP, bool GATED = false>
 int launch_big(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s,
                const void *wg = nullptr, const void *vg = nullptr, uint32_t live_k1 = 0xffffffffu)
 {
     using BG = BigGeo<N2>;
-    auto kern = k_fused3_big<TT, FULL, N2, SP, GATED>;
+    auto kern = k_fused3_big<TT, FORM, N2, SP, GATED>;
     FC_TRY(raise_dynamic_lds((const void *)kern, (int)BG::LDS_BYTES));
     const int64_t T = p->H * ((B + 1) / 2);
     const int64_t kf_bytes = p->H * BG::M * 4;
@@ -1170,10 +1207,11 @@ template <int N2> int big_init_t(fftconv_plan *p)
         set_error("fused3 (32 x N2 x 32): operand table size mismatch");
         return FFTCONV_EINVAL;
     }
-    // twiddles as 16-bit constants in the form TT::ctw4 expects
+    // twiddles as 16-bit constants in the form TT::ctw4 expects (B16W: fp16 as well)
     std::vector<uint32_t> tw((size_t)2 * M);
     auto put = [&](size_t idx, Cx v, bool conj) {
-        const uint32_t re = f16 ? h_f16(v.re) : h_bf16(v.re), im = f16 ? h_f16(v.im) : h_bf16(v.im);
+        const bool h = f16 || p->f3.odd;
+        const uint32_t re = h ? h_f16(v.re) : h_bf16(v.re), im = h ? h_f16(v.im) : h_bf16(v.im);
         tw[idx] = f16 ? H16::cconst(re, im, conj) : B16::cconst(re, im, conj);
     };
     size_t e = 0;
@@ -1219,8 +1257,8 @@ template <typename TT, int N2, int SP>
 int big_forward_tt(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, uint32_t live_k1, hipStream_t s)
 {
     const bool full = (B % 2 == 0) && p->N == BigGeo<N2>::M / 2;
-    return full ? launch_big<TT, true, N2, SP>(p, u, kf, y, B, s, nullptr, nullptr, live_k1)
-                : launch_big<TT, false, N2, SP>(p, u, kf, y, B, s, nullptr, nullptr, live_k1);
+    return full ? launch_big<TT, ROWS_FULL, N2, SP>(p, u, kf, y, B, s, nullptr, nullptr, live_k1)
+                : launch_big<TT, ROWS_EVEN, N2, SP>(p, u, kf, y, B, s, nullptr, nullptr, live_k1);
 }
 
 // sp: bit 0 = the k3 tile 1 is empty, bit 1 = the k2 tile 1 is empty (N2 = 32), bit 2 = some k1 planes are empty
@@ -1300,17 +1338,29 @@ int fused3_big_forward_gated(const fftconv_plan *p, const void *u, const void *w
     if (p->M == 32768) {
         const bool full = (B % 2 == 0) && p->N == BigGeo<32>::M / 2;
         if (f16)
-            return full ? launch_big<H16, true, 32, 0, true>(p, u, kf, y, B, s, wg, vg)
-                        : launch_big<H16, false, 32, 0, true>(p, u, kf, y, B, s, wg, vg);
-        return full ? launch_big<B16, true, 32, 0, true>(p, u, kf, y, B, s, wg, vg)
-                    : launch_big<B16, false, 32, 0, true>(p, u, kf, y, B, s, wg, vg);
+            return full ? launch_big<H16, ROWS_FULL, 32, 0, true>(p, u, kf, y, B, s, wg, vg)
+                        : launch_big<H16, ROWS_EVEN, 32, 0, true>(p, u, kf, y, B, s, wg, vg);
+        return full ? launch_big<B16, ROWS_FULL, 32, 0, true>(p, u, kf, y, B, s, wg, vg)
+                    : launch_big<B16, ROWS_EVEN, 32, 0, true>(p, u, kf, y, B, s, wg, vg);
     }
     const bool full = (B % 2 == 0) && p->N == BigGeo<16>::M / 2;
     if (f16)
-        return full ? launch_big<H16, true, 16, 0, true>(p, u, kf, y, B, s, wg, vg)
-                    : launch_big<H16, false, 16, 0, true>(p, u, kf, y, B, s, wg, vg);
-    return full ? launch_big<B16, true, 16, 0, true>(p, u, kf, y, B, s, wg, vg)
-                : launch_big<B16, false, 16, 0, true>(p, u, kf, y, B, s, wg, vg);
+        return full ? launch_big<H16, ROWS_FULL, 16, 0, true>(p, u, kf, y, B, s, wg, vg)
+                    : launch_big<H16, ROWS_EVEN, 16, 0, true>(p, u, kf, y, B, s, wg, vg);
+    return full ? launch_big<B16, ROWS_FULL, 16, 0, true>(p, u, kf, y, B, s, wg, vg)
+                : launch_big<B16, ROWS_EVEN, 16, 0, true>(p, u, kf, y, B, s, wg, vg);
+}
+
+int fused3_big_forward_odd(const fftconv_plan *p, const void *u, const void *wg, const void *vg, const void *kf, void *y, int64_t B,
+                           hipStream_t s)
+{
+    const bool f16 = p->dtype == FFTCONV_F16, gated = wg || vg;
+    if (p->M == 32768) {
+        if (gated) return f16 ? launch_big<H16, ROWS_ODD, 32, 0, true>(p, u, kf, y, B, s, wg, vg) : launch_big<B16W, ROWS_ODD, 32, 0, true>(p, u, kf, y, B, s, wg, vg);
+        return f16 ? launch_big<H16, ROWS_ODD, 32, 0>(p, u, kf, y, B, s) : launch_big<B16W, ROWS_ODD, 32, 0>(p, u, kf, y, B, s);
+    }
+    if (gated) return f16 ? launch_big<H16, ROWS_ODD, 16, 0, true>(p, u, kf, y, B, s, wg, vg) : launch_big<B16W, ROWS_ODD, 16, 0, true>(p, u, kf, y, B, s, wg, vg);
+    return f16 ? launch_big<H16, ROWS_ODD, 16, 0>(p, u, kf, y, B, s) : launch_big<B16W, ROWS_ODD, 16, 0>(p, u, kf, y, B, s);
 }
 
 bool fused3_big_dk_supported(const fftconv_plan *p) { return p->path == PATH_FUSED3 && (p->M == 16384 || p->M == 32768); }

@@ -185,7 +185,45 @@ struct B16 {
     {
         return make_float2(__uint_as_float(c << 16), __uint_as_float(c & 0xffff0000u));
     }
+    // products with k_f, whose constants have the I/O type
+    template <bool CONJ> static __device__ __forceinline__ uint4 kfw4(f32x4 re, f32x4 im, const CW (&c)[4])
+    {
+        return ctw4<CONJ>(re, im, c);
+    }
     static __device__ __forceinline__ uint4 mul8(uint4 a, uint4 b) { return BF16::mul8(a, b); }
+};
+
+// bf16 I/O with the elementwise products in fp32, rounded once, and the twiddles as fp16 pairs (11 bits instead of 8); k_f in bf16
+// as above.  As many vector operations for a twiddle (the multiply-adds take an fp16 operand), two more for k_f.
+struct B16W : B16 {
+    // re[r], im[r] times w(r), a pair of fp32 or fp16 values.  The first product is an addition of zero, which the compiler is kept
+    // from seeing: as a multiply-add it takes the fp16 operand as it is.
+    template <bool CONJ, typename W> static __device__ __forceinline__ uint4 product(f32x4 re, f32x4 im, float zero, W w)
+    {
+        uint32_t o[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const auto v = w(r);
+            const float x = (float)v[0], y = (float)v[1], s = CONJ ? -1.f : 1.f;
+            const float a = __builtin_fmaf(re[r], x, -__builtin_fmaf(im[r], y, zero));
+            const float b = __builtin_fmaf(s * re[r], y, __builtin_fmaf(s * im[r], x, zero));
+            o[r] = pack(a, b);
+        }
+        return make_uint4(o[0], o[1], o[2], o[3]);
+    }
+    template <bool CONJ> static __device__ __forceinline__ uint4 ctw4(f32x4 re, f32x4 im, const CW (&c)[4])
+    {
+        float zero;
+        asm("s_mov_b32 %0, 0" : "=s"(zero));
+        return product<CONJ>(re, im, zero, [&](int r) { return __builtin_bit_cast(f16x2, c[r]); });
+    }
+    template <bool CONJ> static __device__ __forceinline__ uint4 kfw4(f32x4 re, f32x4 im, const CW (&c)[4])
+    {
+        return product<CONJ>(re, im, 0.f, [&](int r) {
+            const float2 v = widen(c[r]);
+            return f32x2{v.x, v.y};
+        });
+    }
 };
 
 // fp16: packed arithmetic.  Constant of a factor: the pair (wr, wi); the operand selectors
@@ -218,6 +256,10 @@ struct H16 {
         return make_float2((float)h[0], (float)h[1]);
     }
     static __device__ __forceinline__ uint4 mul8(uint4 a, uint4 b) { return F16::mul8(a, b); }
+    template <bool CONJ> static __device__ __forceinline__ uint4 kfw4(f32x4 re, f32x4 im, const CW (&c)[4])
+    {
+        return ctw4<CONJ>(re, im, c);
+    }
     template <bool CONJ> static __device__ __forceinline__ uint4 ctw4(f32x4 re, f32x4 im, const CW (&c)[4])
     {
         uint32_t o[4];
@@ -376,6 +418,28 @@ int fused3_big_forward(const fftconv_plan *p, const void *u, const void *kf, voi
                        hipStream_t s, uint32_t live_k2 = 0xffffffffu, uint32_t live_k1 = 0xffffffffu);
 int fused3_big_forward_gated(const fftconv_plan *p, const void *u, const void *wg, const void *vg, const void *kf, void *y,
                              int64_t B, hipStream_t s);
+
+// 16 bytes at any element of a 16-bit row: the hardware takes vector accesses at any address in this ABI's mode
+__device__ __forceinline__ uint4 load16(const uint16_t *p)
+{
+    uint4 v;
+    __builtin_memcpy(&v, p, sizeof(v));
+    return v;
+}
+__device__ __forceinline__ void store16(uint16_t *p, uint4 v) { __builtin_memcpy(p, &v, sizeof(v)); }
+// the 8 elements of v moved down by d >= 1 places, zeros behind them
+__device__ __forceinline__ uint4 shift_down(uint4 v, int d)
+{
+    uint64_t lo = v.x | (uint64_t)v.y << 32, hi = v.z | (uint64_t)v.w << 32;
+    if (d >= 4) {
+        lo = d >= 8 ? 0 : hi >> (16 * (d & 3));
+        hi = 0;
+    } else {
+        lo = lo >> (16 * d) | hi << (64 - 16 * d);
+        hi >>= 16 * d;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
 
 }  // namespace f3
 }  // namespace fftconv

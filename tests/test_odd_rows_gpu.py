@@ -1,0 +1,98 @@
+"""16-bit causal rows of lengths that are no multiple of 8, of transforms that run in a single kernel: rows that begin anywhere in
+memory, the chunk across a row's end, batches with and without a partner for the last row; nothing is read or written beyond."""
+import pytest
+import torch
+
+from paper_2311_05908_amd import fftconv, synth
+from parity_util import TOL, parity_error
+
+pytestmark = pytest.mark.gpu
+
+
+def conv(x, k, N):
+    n = 2 * N
+    return torch.fft.irfft(torch.fft.rfft(x, n) * torch.fft.rfft(k, n), n)[..., :N]
+
+
+def placed(t, shift):
+    """The tensor on the GPU, its first element `shift` elements behind an allocation's start, NaN before and after it."""
+    buf = torch.full((t.numel() + shift + 64,), float("nan"), dtype=t.dtype, device="cuda")
+    buf[shift:shift + t.numel()] = t.flatten().cuda()
+    return buf, buf[shift:shift + t.numel()].view(t.shape)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [16384, 32768])
+@pytest.mark.parametrize("B,H,N,shift", [
+    (1, 1, 9, 0), (2, 3, 15, 1), (3, 2, 4095, 3), (2, 1, 4100, 2), (5, 9, 5003, 0),
+    (1, 2, -1, 5), (4, 1, -7, 0), (3, 300, 1001, 0),               # negative: short of half the transform
+])
+def test_odd_rows(dtype, M, B, H, N, shift):
+    N = M // 2 + N if N < 0 else N
+    g = torch.Generator().manual_seed(N + B)
+    u, w, v = (torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(3))
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.path == "multipass"
+    kf, ka = plan.filter_fft(k.cuda()), plan.filter_fft_adjoint(k.cuda())
+    (_, cu), (_, cw), (_, cv) = (placed(t, shift) for t in (u, w, v))
+    ubuf, ux = placed(u, shift)
+    for name in ("y", "w", "v", "wv", "du"):
+        buf, out = placed(torch.zeros_like(u), shift)
+        if name == "y":
+            plan.forward(cu, kf, out=out)
+        elif name == "du":
+            plan.backward_input(cu, ka, out=out)
+        else:
+            plan.forward_gated(cu, cw if "w" in name else None, cv if "v" in name else None, kf, out=out)
+        ud, kd = u.double(), k.double()
+        if name == "du":
+            ref = conv(ud.flip(-1), kd, N).flip(-1)
+        else:
+            ref = conv(ud * (w.double() if "w" in name else 1.0), kd, N)
+        weight = None
+        if name in ("v", "wv"):
+            ref, weight = ref * v.double(), v.double().abs().numpy()
+        assert torch.isnan(buf[:shift]).all() and torch.isnan(buf[shift + u.numel():]).all()
+        err = parity_error(out.cpu().double().numpy(), ref.numpy(), TOL[dtype], name, weight=weight)
+        print("odd rows %s M=%d B=%d H=%d N=%d %s err=%.3e" % (dtype, M, B, H, N, name, err), flush=True)
+        assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,M,bound", [("bf16", 16384, 4.80e-3), ("bf16", 32768, 4.96e-3), ("f16", 16384, 6.56e-4), ("f16", 32768, 6.79e-4)])
+def test_odd_rows_are_no_less_accurate_than_in_three_passes(dtype, M, bound):
+    """Error (2-norm, fp64 reference, N(0, 1) rows and decaying filters that nearly fill half the transform) of the three-pass route on such rows; 2^20
+    outputs, whose errors' norm scatters by well under 1 %."""
+    g = torch.Generator().manual_seed(M)
+    B, H, N = 4, 64, M // 2 - 1
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype])
+    alpha = (4.0 / N) * 100.0 ** torch.rand(H, 1, generator=g)
+    k = torch.randn(H, N, generator=g) * torch.exp(-alpha * torch.arange(N))
+    plan = fftconv.Plan(N, M, H, dtype)
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda())).cpu().double()
+    ref = conv(u.double(), k.double(), N)
+    err = ((y - ref).norm() / ref.norm()).item()
+    print("odd rows %s M=%d error %.4e bound %.4e" % (dtype, M, err, bound), flush=True)
+    assert err <= 1.01 * bound
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [16384, 32768])
+def test_odd_rows_with_masks(dtype, M):
+    """Block masks and digit patterns of the plan's factorisation on such plans: Re(IDFT(mask K U)) whatever kernel runs them."""
+    B, H, N = 3, 2, M // 2 - 5
+    g = torch.Generator().manual_seed(M)
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype])
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype)
+    U, K = torch.fft.fft(u.double(), M), torch.fft.fft(k.double(), M)
+    keep = [1 if j < 4 or j >= 28 else 0 for j in range(32)]
+    y = plan.forward_freq_sparse(u.cuda(), plan.filter_fft(k.cuda(), block_keep=keep), keep)
+    mask = torch.tensor(keep, dtype=torch.float64).repeat_interleave(M // 32)
+    ref = torch.fft.ifft(mask * U * K).real[..., :N]
+    assert parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "block") <= TOL[dtype]
+    digits = [max(1, d // 2) for d in plan.factors]
+    y = plan.forward_freq_sparse_digits(u.cuda(), plan.filter_fft_sparse_digits(k.cuda(), digits), digits)
+    mask = torch.from_numpy(synth.digit_keep_mask(plan.factors, digits)).double()
+    ref = torch.fft.ifft(mask * U * K).real[..., :N]
+    assert parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "digits") <= TOL[dtype]
