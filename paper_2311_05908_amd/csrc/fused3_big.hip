@@ -29,6 +29,7 @@
 
 #include "fused3_common.h"
 #include "lds_fft.h"
+#include "row_io.h"
 
 namespace fftconv {
 namespace f3 {
@@ -1024,65 +1025,89 @@ __global__ void k_big_dk_last(const float2 *__restrict__ tmp, float *__restrict_
 }
 
 // Filter transform, one workgroup per channel and nothing but the taps and k_f in HBM.  The taps are real, so
-// the row is transformed as M/2 complex points z[n] = k[2n] + i k[2n+1] in LDS (fp32, the stages of lds_fft.h;
-// 16384 complex points are what LDS holds), and the two interleaved half-length spectra are separated on the way
-// out: with Z = FFT(z), E = (Z[f] + conj Z[M/2 - f]) / 2 and O = (Z[f] - conj Z[M/2 - f]) / (2i) are the spectra
-// of the even and odd taps, K[f] = E + W_M^f O for f < M/2, K[M/2] = Re Z[0] - Im Z[0], K[M - f] = conj K[f].
+// the row is transformed as M/2 complex points z[n] = k[2n] + i k[2n+1], fp32, on the row engine (row_fft.h), and the two
+// interleaved half-length spectra are separated on the way out: with Z = FFT(z), E = (Z[f] + conj Z[M/2 - f]) / 2 and
+// O = (Z[f] - conj Z[M/2 - f]) / (2i) are the spectra of the even and odd taps, K[f] = E + W_M^f O and
+// K[f + M/2] = E - W_M^f O, f < M/2.
 // k_f in the kernel's per-lane order: [h][k1][k2 tile][k3 tile][r][lane]; the lane holds
-// k2 = big_tau(16 tile + lane%16) and k3 = big_sigma(16 tile + 4 (lane/16) + r).  Scaled by 1/M.
-// w: W_M^t, t < M.  flh: factors of the half-length transform.  conj_out: the adjoint filter transform.
-constexpr int BIG_FILT_THREADS = 1024;
-template <typename TT, int N2>
-__global__ void __launch_bounds__(BIG_FILT_THREADS) k_filter_big(const float *__restrict__ k, typename TT::CW *__restrict__ kf,
-                                                                const float2 *__restrict__ w, FacList flh, int64_t Nk,
-                                                                bool conj_out, const uint8_t *__restrict__ keep,
-                                                                int64_t n_blocks)
+// k2 = big_tau(16 tile + lane%16) and k3 = big_sigma(16 tile + 4 (lane/16) + r).  Scaled by 1/M.  conj_out: the adjoint filter
+// transform.  k1, k2 and k3 mod 16 are the digits of the engine's frequency, so that Z goes through LDS as the engine left it, and
+// a lane that forms the bins k3 = 4q + r and k3 + 16 has one value for its own slot of tile 0 and one for tile 1 of the lane 32 away.
+// Bound by the instructions of that loop and the transform's latency, with one workgroup (two at N2 = 16) on a compute unit.  us, with
+// every factor a trip through LDS, gathered twiddles and digits taken apart for every bin, before: fft 32768, 1 / 256 / 768 channels
+// 44, 59, 165 -> 17, 22, 57; fft 16384 25, 30, 74 -> 14, 16, 32.
+// HALF: Nk <= M / 2.
+template <int N2> using FilterRow = rf::Row<BigGeo<N2>::M / 2>;
+template <typename TT, int N2, bool HALF>
+__global__ void __launch_bounds__(FilterRow<N2>::T, 2) k_filter_big(const float *__restrict__ k, typename TT::CW *__restrict__ kf,
+                                                                   const float2 *__restrict__ tab, int64_t Nk, bool conj_out,
+                                                                   const uint8_t *__restrict__ keep, int64_t n_blocks)
 {
+    using G = FilterRow<N2>;
+    constexpr int BM = BigGeo<N2>::M, MH = BM / 2, R2 = BigGeo<N2>::R2, MIN = HALF ? G::P / 2 : G::P;
+    static_assert(G::R0 == 32 && G::R1 == N2 && G::R2 == 16 && G::T / G::RL == N2, "the engine's digits are those of the kernel");
     extern __shared__ float2 ZF[];
-    constexpr int BM = BigGeo<N2>::M, MH = BM / 2, R2 = BigGeo<N2>::R2;
     const int64_t h = blockIdx.x;
     const float *row = k + h * Nk;
-    // all taps of the thread are requested before the first is used (a tap beyond Nk reads tap 0 and is discarded:
-    // behind a branch every load would be waited for in turn)
-    constexpr int TPT = MH / BIG_FILT_THREADS;
-    float ta[TPT], tb[TPT];
+    const int tid = threadIdx.x;
+    {
+        // all taps of the thread are requested before the first is used (a pair across the end comes from the last two taps, one
+        // beyond it likewise and is discarded: behind a branch every load would be waited for in turn)
+        float2 x[G::P];
+        const int last = Nk < 2 ? 0 : (int)Nk - 2;
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int n = threadIdx.x + j * BIG_FILT_THREADS;
-        ta[j] = row[2 * n < Nk ? 2 * n : 0];
-        tb[j] = row[2 * n + 1 < Nk ? 2 * n + 1 : 0];
-    }
+        for (int m = 0; m < MIN; ++m) {
+            const int at = min(2 * (tid + G::T * m), last);
+            x[m].x = row[at];
+            x[m].y = row[Nk < 2 ? 0 : at + 1];
+        }
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) asm volatile("" ::"v"(ta[j]), "v"(tb[j]));
+        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(x[m].x), "v"(x[m].y));
 #pragma unroll
-    for (int j = 0; j < TPT; ++j) {
-        const int n = threadIdx.x + j * BIG_FILT_THREADS;
-        ZF[lds_slot(n)] = make_float2(2 * n < Nk ? ta[j] : 0.f, 2 * n + 1 < Nk ? tb[j] : 0.f);
+        for (int m = 0; m < MIN; ++m) {
+            const int n = 2 * (tid + G::T * m);
+            if (n + 1 >= Nk) x[m] = make_float2(n < Nk ? x[m].y : 0.f, 0.f);
+        }
+        rf::Tw1<G> tw1;
+        tw1.load(tab, tid);
+        rf::forward<G, HALF>(x, ZF, tab, tw1, tid, [] {});
+        // (a butterfly of the last pass goes back to the slots that only it has read)
+#pragma unroll
+        for (int i = 0; i < G::NBL; ++i) {
+            float2 *const z = ZF + G::slotl(tid + G::T * i);
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) z[r] = x[i * G::RL + r];
+        }
     }
     __syncthreads();
-    lds_forward(ZF, w, flh, MH, 2);
-    // (straight-line body, four entries per trip: the twiddle gathers of a trip are then in flight together)
+    // a wave takes whole groups (k1, k2 tile, r): lane = 16 q + c, k2 = big_tau(16 tile + c), k3 = 4 q + r and that + 16
+    const int lane = tid & 63, q = lane >> 4, c16 = lane & 15;
+    typename TT::CW *const out = kf + h * BM + lane;
+    constexpr int GROUPS = 32 * R2 * 4, WAVES = G::T / 64;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll 4
-    for (int d = threadIdx.x; d < BM; d += BIG_FILT_THREADS) {
-        const int lane = d % 64, r = (d / 64) % 4, t3 = (d / 256) % 2, t2 = (d / 512) % R2, k1 = d / (512 * R2);
-        const int k2 = big_tau<N2>(16 * t2 + lane % 16), k3 = big_sigma(16 * t3 + 4 * (lane / 16) + r);
-        const int f = k1 + 32 * k2 + 32 * N2 * k3;
-        const int fe = f <= MH ? f : BM - f;              // K[f] = conj K[M - f]
-        const bool nyq = fe == MH;                        // the bin M/2: Z[0].re - Z[0].im
-        const int fa = nyq ? 0 : fe;
-        const float2 tw = w[fa];
-        const float2 za = ZF[lds_slot(lds_pos(fa, flh, MH))];
-        const float2 zc = ZF[lds_slot(lds_pos((MH - fa) % MH, flh, MH))];
+    for (int i = 0; i < GROUPS / WAVES; ++i) {
+        const int g = i * WAVES + w;
+        const int r = g & 3, t2 = (g >> 2) & (R2 - 1), k1 = g / (4 * R2);
+        const int k2 = big_tau<N2>(16 * t2 + c16), k3 = 4 * q + r, f = k1 + 32 * k2 + 32 * N2 * k3;
+        // digits of M/2 - f: complements, plus one from the first digit that is not zero on
+        const bool z1 = k1 == 0, z2 = z1 && k2 == 0;
+        const int m1 = (32 - k1) & 31, m2 = z1 ? (N2 - k2) & (N2 - 1) : N2 - 1 - k2, m3 = z2 ? (16 - k3) & 15 : 15 - k3;
+        const float2 za = ZF[k1 * G::PITCH + k2 * G::PAD + k3], zc = ZF[m1 * G::PITCH + m2 * G::PAD + m3];
+        const float rev = (float)f * (1.f / (float)BM);                        // exact: the sine and cosine take revolutions
+        const float2 tw = make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
         const float2 e = make_float2(0.5f * (za.x + zc.x), 0.5f * (za.y - zc.y));
         const float2 o = make_float2(0.5f * (za.y + zc.y), -0.5f * (za.x - zc.x));      // (za - conj zc) / (2i)
-        float2 v = cmul(o, tw);
-        v.x += e.x;
-        v.y += e.y;
-        if (nyq) v = make_float2(za.x - za.y, 0.f);
-        if ((f > MH) != conj_out) v.y = -v.y;
-        const float sc = lds_mask_weight(keep, n_blocks, f, BM) / (float)BM;
-        const uint32_t pr = TT::pack(v.x * sc, v.y * sc);                       // (re, im) 16-bit pair
-        kf[h * BM + d] = TT::cconst(pr & 0xffffu, pr >> 16, true);              // the kernel forms conj(A3 * k_f)
+        const float2 v = cmul(o, tw);
+        const float s0 = lds_mask_weight(keep, n_blocks, f, BM) / (float)BM, s1 = lds_mask_weight(keep, n_blocks, f + MH, BM) / (float)BM;
+        const float sgn = conj_out ? -1.f : 1.f;
+        const uint32_t lo = TT::pack((e.x + v.x) * s0, sgn * (e.y + v.y) * s0);         // k3: (re, im) 16-bit pairs
+        const uint32_t hi = TT::pack((e.x - v.x) * s1, sgn * (e.y - v.y) * s1);         // k3 + 16
+        const uint32_t own = q < 2 ? lo : hi;
+        const uint32_t far = (uint32_t)__shfl_xor((int)(q < 2 ? hi : lo), 32, 64);
+        typename TT::CW *const dst = out + (k1 * R2 + t2) * 512 + r * 64;
+        dst[0] = TT::cconst(own & 0xffffu, own >> 16, true);                   // the kernel forms conj(A3 * k_f)
+        dst[256] = TT::cconst(far & 0xffffu, far >> 16, true);
     }
 }
 
@@ -1243,12 +1268,11 @@ template <typename TT, int N2>
 int big_filter_tt(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks,
                   void *kf, hipStream_t s)
 {
-    constexpr int64_t MH = BigGeo<N2>::M / 2;
-    const size_t bytes = lds_row_bytes(MH, sizeof(float2));
-    FC_TRY(raise_dynamic_lds((const void *)k_filter_big<TT, N2>, (int)bytes));
-    hipLaunchKernelGGL((k_filter_big<TT, N2>), dim3((unsigned)p->H), dim3(BIG_FILT_THREADS), bytes, s, k,
-                       (typename TT::CW *)kf, (const float2 *)p->st.w32, staged_factors_for(MH), Nk, adjoint, keep_dev,
-                       n_blocks);
+    using G = FilterRow<N2>;
+    const auto kern = Nk <= BigGeo<N2>::M / 2 ? k_filter_big<TT, N2, true> : k_filter_big<TT, N2, false>;
+    FC_TRY(raise_dynamic_lds((const void *)kern, G::LDS_BYTES));
+    hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), G::LDS_BYTES, s, k, (typename TT::CW *)kf, rf::row_table<G>(p), Nk, adjoint,
+                       keep_dev, n_blocks);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

@@ -195,7 +195,7 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
         });
     };
     add_length(M < 8192 ? M : 8192);
-    if (M == 16384) add_length(M);
+    if (M == 16384 || M == 32768) add_length(16384);
     return t;
 }
 

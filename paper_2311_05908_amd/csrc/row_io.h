@@ -170,7 +170,7 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&v)[4])
 }
 
 // The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
-// that.
+// that or 32768.
 template <typename G> inline const float2 *row_table(const fftconv_plan *p)
 {
     const size_t at = G::M == 16384 ? Row<8192, false>::TABLE + Row<8192, true>::TABLE : 0;
