@@ -234,8 +234,8 @@ __host__ __device__ inline int multipass_row_slot(int r, bool quarter)
     return quarter ? ((r & 12) << 9) | ((r >> 8) << 6) | (((r >> 4) & 15) << 2) | (r & 3) : r;
 }
 
-// slot of bin f of a transform of M = 256 .. 8192 points in the k_f of the 8192-point kernels (shorter transforms: of group 0,
-// the groups' copies follow M slots apart)
+// slot of bin f of a transform of M = 256 .. 8192 points in the k_f of the 8192-point kernels (H x M slots; in the accumulated spectra of
+// their filter gradient, where a channel has 8192 slots, of group 0: the others follow M slots apart)
 template <int M> __host__ __device__ inline int kernel_slot(int f)
 {
     constexpr int N1 = M / 256;
@@ -294,7 +294,7 @@ int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, fl
                         hipStream_t s);
 // the fp32 ends of the 8192-point matrix-core plans (row_filter.hip): taps -> k_f, accumulated spectra -> dk
 int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
-               int64_t n_blocks, uint2 *kf, hipStream_t s);
+               int64_t n_blocks, uint32_t *kf, hipStream_t s);
 // fp64 filter transform of the plans that convolve on the row engine with k_f in fp32
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s);

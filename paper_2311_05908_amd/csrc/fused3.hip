@@ -396,7 +396,7 @@ constexpr size_t SHORT_TAG_BYTES = 256;     // the tag word, padded so that what
 
 size_t fused3_short_kf_bytes(const fftconv_plan *p)
 {
-    return p->f3.consts_short ? (size_t)(p->H * SHORT_M) * sizeof(float2) + SHORT_TAG_BYTES : 0;
+    return p->f3.consts_short ? (size_t)(p->H * SHORT_M) * sizeof(uint32_t) + SHORT_TAG_BYTES : 0;
 }
 
 // bytes of the plan's dense spectrum, = offset of the short one
@@ -409,12 +409,12 @@ static size_t dense_kf_bytes(const fftconv_plan *p)
 size_t fused3_kf_bytes(const fftconv_plan *p)
 {
     if (p->M >= 16384) return fused3_big_kf_bytes(p) + fused3_short_kf_bytes(p);
-    return (size_t)(p->H * 8192) * sizeof(float2);             // fft <= 8192: the 8192 slots of the wave-specialised kernel
+    return (size_t)(p->H * p->M) * sizeof(uint32_t);
 }
 
 const long long *fused3_short_tag(const fftconv_plan *p, const void *kf)
 {
-    return (const long long *)((const char *)kf + dense_kf_bytes(p) + (size_t)(p->H * SHORT_M) * sizeof(float2));
+    return (const long long *)((const char *)kf + dense_kf_bytes(p) + (size_t)(p->H * SHORT_M) * sizeof(uint32_t));
 }
 
 __global__ void k_set_tag(long long *tag, long long value) { *tag = value; }
@@ -436,7 +436,7 @@ bool fused3_short_ok(const fftconv_plan *p, int64_t Nk)
 // the 8192-point spectrum of a short filter, behind the dense one (see fused3_forward_short)
 int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, hipStream_t s)
 {
-    uint2 *dst = (uint2 *)((char *)kf + dense_kf_bytes(p));
+    uint32_t *dst = (uint32_t *)((char *)kf + dense_kf_bytes(p));
     return row_filter(p, k, Nk, SHORT_M, false, nullptr, 1, dst, s);
 }
 
@@ -455,7 +455,7 @@ int fused3_forward_short(const fftconv_plan *p, const void *u, const void *kf, v
     const int P = (int)history_of(Nk);
     const int Lo = (int)(SHORT_M / 2) - P;
     const int nseg = p->N <= SHORT_M / 2 ? 1 : 1 + (int)((p->N - SHORT_M / 2 + Lo - 1) / Lo);
-    const float2 *kf_short = (const float2 *)((const char *)kf + dense_kf_bytes(p));
+    const char *kf_short = (const char *)kf + dense_kf_bytes(p);
     return fused3_ws_launch(p, p->f3.consts_short, u, kf_short, y, B, nseg, P, s);
 }
 
@@ -464,9 +464,8 @@ int fused3_filter(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoin
                   int64_t n_blocks, void *kf, hipStream_t s)
 {
     if (p->M > 8192) return fused3_big_filter(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s);
-    // the 8192-point kernel takes k_f as 16-bit constant pairs; shorter transforms fill its 8192 slots with
-    // 8192 / fft_size copies of their spectrum (see build_tables())
-    return row_filter(p, k, Nk, p->M, adjoint, keep_dev, n_blocks, (uint2 *)kf, s);
+    // one 16-bit pair a bin, in the slot order of the 8192-point kernel (kernel_slot)
+    return row_filter(p, k, Nk, p->M, adjoint, keep_dev, n_blocks, (uint32_t *)kf, s);
 }
 
 bool fused3_gates_fused(const fftconv_plan *p) { return p->path == PATH_FUSED3; }

@@ -83,6 +83,11 @@ struct BF16 {
         };
         return make_uint4(m(a.x, b.x), m(a.y, b.y), m(a.z, b.z), m(a.w, b.w));
     }
+    // the constant of a factor from its 4-byte form, the pair (wr, wi)
+    static __device__ __forceinline__ uint2 constant(uint32_t w)
+    {
+        return make_uint2(w ^ 0x80000000u, __builtin_amdgcn_alignbit(w, w, 16));
+    }
     static constexpr int CFMT = 1;
 };
 struct F16 {
@@ -119,6 +124,10 @@ struct F16 {
             return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, x) * __builtin_bit_cast(f16x2, y));
         };
         return make_uint4(m(a.x, b.x), m(a.y, b.y), m(a.z, b.z), m(a.w, b.w));
+    }
+    static __device__ __forceinline__ uint2 constant(uint32_t w)
+    {
+        return make_uint2(__builtin_amdgcn_perm(w, w, 0x01000100u), __builtin_amdgcn_perm(w, w, 0x03020302u) ^ 0x00008000u);
     }
     static constexpr int CFMT = 2;
 };

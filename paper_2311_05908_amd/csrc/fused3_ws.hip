@@ -44,7 +44,7 @@ constexpr int PCH = G::M / 8 / PT;            // 16-byte input chunks per outer-
 // clear means k_f is zero on the whole plane k1; phase B then writes zeros for it instead of computing.
 template <typename TT, bool FULL, int GATE, bool SKIP1 = false>
 __global__ void __launch_bounds__(NT) k_fused3_ws(const uint16_t *__restrict__ u, uint16_t *__restrict__ y,
-                                                 const uint2 *__restrict__ kf, Consts cs, int B, int H, int N, int nseg, int P, int Lo,
+                                                 const uint32_t *__restrict__ kf, Consts cs, int B, int H, int N, int nseg, int P, int Lo,
                                                  const uint16_t *__restrict__ wg, const uint16_t *__restrict__ vg,
                                                  uint32_t live_k1, int groups, int lg_half, LaunchGate gate)
 {
@@ -340,13 +340,19 @@ __global__ void __launch_bounds__(NT) k_fused3_ws(const uint16_t *__restrict__ u
             if (s >= t0 && s < t1) {
                 const int h = it_b.h;
                 item_next(it_b);
-                if (h != h_cur) {                                 // new channel: its k_f slice for this wave's k1 planes
+                if (h != h_cur) {                                 // new channel: its k_f slice for this wave's k1 planes, as constants
                     h_cur = h;
+                    const int M = G::M / groups;                  // slots of a group: every group has the same spectrum
+                    const uint32_t *const src = kf + (size_t)h * M + l;
+                    uint32_t c[8][4];
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            kfr[i][r] = kf[(size_t)h * G::KF_PER_H + ((8 * wq + i) * 4 + r) * 64 + l];
+                        for (int r = 0; r < 4; ++r) c[i][r] = src[(((8 * wq + i) * 4 + r) * 64) & (M - 1)];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) kfr[i][r] = TT::constant(c[i][r]);
                 }
                 uint32_t *XB = XBb + (s & 1) * XBW;
                 // operand of stage 3 for plane k1: columns k2 = c16, slots = (re, im) of n3 = 4q + r;
@@ -421,7 +427,7 @@ int fused3_ws_launch(const fftconv_plan *p, const void *consts, const void *u, c
     const bool full = (B % (2 * groups) == 0) && p->N == G::M / 2 / groups && nseg == 1;
     const bool f16 = p->dtype == FFTCONV_F16;
     const int gate = (wg ? 1 : 0) | (vg ? 2 : 0);
-    using Kern = void (*)(const uint16_t *, uint16_t *, const uint2 *, Consts, int, int, int, int, int, int,
+    using Kern = void (*)(const uint16_t *, uint16_t *, const uint32_t *, Consts, int, int, int, int, int, int,
                           const uint16_t *, const uint16_t *, uint32_t, int, int, LaunchGate);
     static const Kern table[2][2][4] = {
         {{k_fused3_ws<BF16, false, 0>, k_fused3_ws<BF16, false, 1>, k_fused3_ws<BF16, false, 2>, k_fused3_ws<BF16, false, 3>},
@@ -436,7 +442,7 @@ int fused3_ws_launch(const fftconv_plan *p, const void *consts, const void *u, c
     FC_TRY(raise_dynamic_lds((const void *)kern, (int)WS_LDS_BYTES));
     const int grid = (int)(T < p->f3.num_cu ? T : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), WS_LDS_BYTES, s, (const uint16_t *)u, (uint16_t *)y,
-                       (const uint2 *)kf, consts_at<16, 16>(consts), (int)B, (int)p->H, (int)p->N, nseg, P, Lo,
+                       (const uint32_t *)kf, consts_at<16, 16>(consts), (int)B, (int)p->H, (int)p->N, nseg, P, Lo,
                        (const uint16_t *)wg, (const uint16_t *)vg, live_k1, groups, lg_half, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;

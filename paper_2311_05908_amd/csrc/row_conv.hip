@@ -88,13 +88,13 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
 }
 
 // The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
-// with their k_f: 16-bit constant pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
+// with their k_f: 16-bit (re, im) pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
 // wg multiplies u, bit 1: vg multiplies y).  The transforms and the product with k_f are fp32; u . w is rounded to the I/O type,
 // as is the convolution before it meets the output gate: the same values as without a fused gate, whichever kernel a call
 // takes.  For calls of few rows: see row_forward_few().
 template <int M, typename IO, int GATE>
 __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
-    k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint2 *__restrict__ kf, const float2 *__restrict__ tab,
+    k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint32_t *__restrict__ kf, const float2 *__restrict__ tab,
                    const IO *__restrict__ wg, const IO *__restrict__ vg, int B, int H, int N, int npairs, int total)
 {
     using G = Row<M>;
@@ -118,18 +118,14 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
-    uint2 kv[G::P];
-    const uint2 *kr = kf + (int64_t)h * 8192;
+    uint32_t kv[G::P];
+    const uint32_t *kr = kf + (int64_t)h * M;
     rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
 #pragma unroll
         for (int p = 0; p < G::P; ++p) kv[p] = kr[kernel_slot<M>(G::freq(tid, p))];
     });
 #pragma unroll
-    for (int p = 0; p < G::P; ++p) {                              // bf16: (re, -im), (im, re); fp16: (re, re), (-im, im)
-        const float re = rf::unpack<IO>(kv[p].x).x;
-        const float2 c = rf::unpack<IO>(kv[p].y);
-        x[p] = rf::mul(x[p], make_float2(re, std::is_same<IO, __half>::value ? c.y : c.x));
-    }
+    for (int p = 0; p < G::P; ++p) x[p] = rf::mul(x[p], rf::unpack<IO>(kv[p]));
     rf::inverse<G>(x, Z, tab, tw1, tid);
     if constexpr (GATE & 2) {
         float2 g[G::P];
@@ -215,18 +211,17 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 
 // Few rows: which calls of a matrix-core plan up to fft 4096 the row kernel takes.  Both kernels' times are staircases.  The
 // matrix-core kernel runs its work items (8192 / fft pairs of rows of one channel, however few there are) in rounds of one per
-// compute unit: 9 - 10 us for the first, 15, 19, 23 us for 2, 3, 4, each round also fetching the k_f of its channels (64 KB).
-// The row kernel runs workgroups of `rows` pairs: 8, 12, 15, 19 us for 1, 2, 3, 4 of them per compute unit (fft 2048 and
-// 4096; fft 512: 9, 14, 19, 26; fft 1024, a chain in half a wave: 11, 17, 23, 31).  So
-//   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer;
-//   fft 1024: half as many, and not in the first round (9.2 against 9.7 us);
-//   fft 512: half as many, and only if items are not full (full ones: 9.0 against 9.3 us, gated fp16);
-//   fft 256: it reads 2 KB of k_f a channel, the matrix cores 64 KB, so the line rises with H: 40 Ki pairs + 56 a channel.
-//     B x 768 channels, bf16, matrix cores -> rows: B = 64 20 -> 14 us, 128 29 -> 25, 212 46 -> 37, (512 78, 85), (1365
-//     191, 258); 256 channels: B = 256 22 -> 19, (1024 53, 57).
-// Measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates: what the rule
-// takes is at most 4 % slower than on the matrix cores (one fp16 shape at fft 1024) and 0.59 / 0.76 / 0.66 / 0.83 / 0.85
-// of its time in the mean.  (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
+// compute unit: 8 - 9 us for the first, 13, 16, 20 us for 2, 3, 4.
+// The row kernel runs workgroups of `rows` pairs: 7.5, 11, 14, 18 us for 1, 2, 3, 4 of them per compute unit (fft 2048 and
+// 4096; fft 512: 8, 12, 16, 20; fft 1024, a chain in half a wave: 8, 12, 16, 22).  So
+//   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer; beyond six rounds half as many (fp16, 4096: one
+//     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116);
+//   fft 1024: half as many, and in the first round only if items are not full;
+//   fft 512: half as many, and behind the first round only if items are not full;
+//   fft 256: 40 Ki pairs + 24 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, (256 42, 40); 8192
+//     channels: B = 33 98, 51, (64 fp16 106, 116).
+// Measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
+// (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
 // calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
 // At 8192 points the row kernel never was the faster one (16 channels: 8.8 against 12.8).
 // The kernel counts rows and threads (at most M / 16 to a pair of rows) in 32 bits: calls beyond that are not few rows.
@@ -235,13 +230,13 @@ bool row_few(int64_t M, int64_t H, int64_t B)
     const int64_t npairs = (B + 1) / 2;
     if (M > 4096 || npairs > INT32_MAX / (H * (M / 16))) return false;
     const int64_t pairs = H * npairs;
-    if (M == 256) return pairs < 40 * 1024 + 56 * H;
+    if (M == 256) return pairs < 40 * 1024 + 24 * H;
     constexpr int CUS = 256;
     const int64_t full = 8192 / M, items = H * ((npairs + full - 1) / full), rounds = (items + CUS - 1) / CUS;
     const int64_t rows = M == 512 ? 16 : M == 1024 ? 8 : M == 2048 ? 2 : 1, groups = (pairs + rows - 1) / rows;
-    if (M >= 2048) return groups <= CUS * rounds;
-    if (M == 1024) return rounds > 1 && groups <= CUS * ((rounds + 1) / 2);
-    return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
+    if (M >= 2048) return groups <= CUS * rounds && (rounds <= 6 || 2 * groups <= CUS * rounds);
+    if (M == 1024) return (rounds > 1 || pairs < full * items) && groups <= CUS * ((rounds + 1) / 2);
+    return (rounds == 1 || pairs < full * items) && 2 * groups <= CUS * (rounds + 1);
 }
 
 // for calls that row_few() takes
@@ -261,7 +256,7 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
                 const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
                 FC_TRY(raise_dynamic_lds((const void *)kern, lds));
                 hipLaunchKernelGGL(kern, dim3((unsigned)((total + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
-                                   (const uint2 *)kf, rf::row_table<Row<M>>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,
+                                   (const uint32_t *)kf, rf::row_table<Row<M>>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,
                                    (int)p->N, (int)npairs, (int)total);
                 FC_HIP(hipGetLastError());
                 return FFTCONV_OK;

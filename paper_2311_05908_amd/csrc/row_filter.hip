@@ -3,13 +3,16 @@
 // of threads per channel, nothing in memory in between.
 //
 // The frequency digits of the kernels' slots are those of the engine's registers or multiples of them (8192: k1, k2, k3 are
-// its digits 0, 1, 2), so both ends move 8-byte slots in runs of 8 or 16 lanes straight between memory and registers.
-// Plans below 8192 keep G = 8192 / fft_size copies of the spectrum (of the sum, in the gradient: one per group, see
-// build_tables() in fused3.hip): slot k1 of group g is g (32 / G) + k1'.
-// Up to 1024 points a row is part of one wave and most of the work is the copies: there a workgroup takes one channel, and all
-// of it moves the 64 KB, through an image of one group in LDS.
-// Bound by the 64 KB a channel that k_f and the accumulated spectra take.  768 channels of 4096 taps, fft 8192: filter
-// transform 40 -> 20 us (27 with stores of 16 slots in a row), tail of the gradient 46 -> 22 (with every factor a trip through LDS and gathered twiddles before).
+// its digits 0, 1, 2), so both ends move slots in runs of 8 or 16 lanes straight between memory and registers.
+// k_f has one 4-byte pair a bin, from which the convolution kernel makes its constants when it turns to a channel.  us, with 8-byte constants
+// in as many copies as the kernel has groups (64 KB a channel) before: filter transform of 768 channels, fft 256 / 1024 / 2048 / 8192
+// 12.5, 13.4, 21.9, 20 -> 7.5, 8.7, 8.8, 17.0; 8000 channels of fft 256 107 -> 8; convolutions of fft 8192, 64 x 768 x 4096 bf16 335 -> 323, f16
+// 317 -> 295, 2 x 768 x 4096 20.7 -> 18.5.
+// The gradient of plans below 8192 sums a spectrum for each of G = 8192 / fft_size groups (see build_tables() in fused3.hip): slot
+// k1 of group g is g (32 / G) + k1'.  Up to 1024 points a row is part of one wave and most of the work is adding them up: there a
+// workgroup takes one channel, and all of it moves the 64 KB, through an image of one group in LDS.
+// Bound by the bytes.  Tail of the gradient, 768 channels of fft 8192: 46 -> 22 us (with every factor a trip through LDS and gathered
+// twiddles before).
 #include "fftconv_internal.h"
 #include "lds_fft.h"
 #include "row_io.h"
@@ -27,78 +30,56 @@ template <int M> constexpr int ROWS = IMAGE<M> ? 1 : rf::threads_of(M) / Row<M>:
 template <int M> constexpr int LDS_BYTES = ROWS<M> * Row<M>::LDS_BYTES + (IMAGE<M> ? 8 * M : 0);
 
 // HALF: Nk <= M / 2.  conj_out: the conjugate spectrum, that of the circularly time-reversed taps, which are real.  k_f
-// scaled by 1/M and by the frequency mask, as the constants of TT::ctw (bf16 dot-product form, fp16 packed form).
+// scaled by 1/M and by the frequency mask, one (re, im) pair of the I/O type a bin.
 template <int M, bool F16, bool HALF>
 __global__ void __launch_bounds__(rf::threads_of(M), 2)
-    k_row_filter(const float *__restrict__ k, uint2 *__restrict__ kf, const float2 *__restrict__ tab, int H, int64_t Nk, bool conj_out,
+    k_row_filter(const float *__restrict__ k, uint32_t *__restrict__ kf, const float2 *__restrict__ tab, int H, int64_t Nk, bool conj_out,
                  const uint8_t *__restrict__ keep, int64_t n_blocks)
 {
     using G = Row<M>;
-    constexpr int RW = ROWS<M>, MIN = HALF ? G::P / 2 : G::P, NTHR = rf::threads_of(M);
+    constexpr int RW = rf::threads_of(M) / G::T, MIN = HALF ? G::P / 2 : G::P;
     extern __shared__ float2 smem_rows[];
-    const int row = IMAGE<M> ? 0 : threadIdx.x / G::T, tid = IMAGE<M> ? threadIdx.x : threadIdx.x % G::T;
+    const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
     const int h = min((int)blockIdx.x * RW + row, H - 1);         // rows beyond the last one repeat it, unstored
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
-    uint2 *const image = (uint2 *)((char *)smem_rows + G::LDS_BYTES);
-    uint2 *const o = kf + (int64_t)h * SLOTS;
-    if (!IMAGE<M> || tid < G::T) {
-        float tap[MIN];
+    uint32_t *const o = kf + (int64_t)h * M;
+    float tap[MIN];
 #pragma unroll
-        for (int m = 0; m < MIN; ++m) {
-            const int n = tid + G::T * m;
-            tap[m] = k[h * Nk + (n < Nk ? n : 0)];
-        }
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(tap[m]));   // the loads stay unconditional
-        float2 x[G::P];
-#pragma unroll
-        for (int m = 0; m < MIN; ++m) x[m] = make_float2(tid + G::T * m < Nk ? tap[m] : 0.f, 0.f);
-        rf::Tw1<G> tw1;
-        tw1.load(tab, tid);
-        rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
-        if ((int)blockIdx.x * RW + row >= H) return;
-        auto constant = [&](int p) {
-            const float sc = keep ? lds_mask_weight(keep, n_blocks, G::freq(tid, p), M) / M : 1.f / M;
-            const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
-            if constexpr (F16) return make_uint2(f3::F16::pack(re, re), f3::F16::pack(-im, im));
-            else return make_uint2(f3::BF16::pack(re, -im), f3::BF16::pack(im, re));
-        };
-        if constexpr (M == SLOTS) {
-            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
-            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
-            const int k1w = tid / 64 * 4;
-#pragma unroll
-            for (int ir = 0; ir < 8; ++ir) {
-                const int i = ir / 4, r = ir % 4;
-                uint32_t a[4], b[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint2 v = constant(16 * i + k3_at_index(4 * c + r, 16));
-                    a[c] = v.x;
-                    b[c] = v.y;
-                }
-                rf::transpose_groups(a);
-                rf::transpose_groups(b);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = make_uint2(a[j], b[j]);
-            }
-        } else {
-#pragma unroll
-            for (int p = 0; p < G::P; ++p) {
-                const int d = kernel_slot<M>(G::freq(tid, p));
-                const uint2 c = constant(p);
-                if constexpr (IMAGE<M>) {
-                    image[d] = c;
-                } else {
-#pragma unroll
-                    for (int g = 0; g < SLOTS / M; ++g) o[g * M + d] = c;
-                }
-            }
-        }
+    for (int m = 0; m < MIN; ++m) {
+        const int n = tid + G::T * m;
+        tap[m] = k[h * Nk + (n < Nk ? n : 0)];
     }
-    if constexpr (IMAGE<M>) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < SLOTS; i += NTHR) o[i] = image[i % M];
+#pragma unroll
+    for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(tap[m]));   // the loads stay unconditional
+    float2 x[G::P];
+#pragma unroll
+    for (int m = 0; m < MIN; ++m) x[m] = make_float2(tid + G::T * m < Nk ? tap[m] : 0.f, 0.f);
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
+    if ((int)blockIdx.x * RW + row >= H) return;
+    auto constant = [&](int p) {
+        const float sc = keep ? lds_mask_weight(keep, n_blocks, G::freq(tid, p), M) / M : 1.f / M;
+        const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
+        return F16 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
+    };
+    if constexpr (M == SLOTS) {
+        // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
+        // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
+        const int k1w = tid / 64 * 4;
+#pragma unroll
+        for (int ir = 0; ir < 8; ++ir) {
+            const int i = ir / 4, r = ir % 4;
+            uint32_t a[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = constant(16 * i + k3_at_index(4 * c + r, 16));
+            rf::transpose_groups(a);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = a[j];
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) o[kernel_slot<M>(G::freq(tid, p))] = constant(p);
     }
 }
 
@@ -248,17 +229,17 @@ int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_ou
     });
 }
 
-// k_f (H, 8192 slots) of the 8192-point kernels for a transform of Ms = 256 .. 8192 points (min(fft_size, 8192): plans above
+// k_f (H, Ms slots) of the 8192-point kernels for a transform of Ms = 256 .. 8192 points (min(fft_size, 8192): plans above
 // keep the spectrum of a short filter this way)
 int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
-               int64_t n_blocks, uint2 *kf, hipStream_t s)
+               int64_t n_blocks, uint32_t *kf, hipStream_t s)
 {
     return rf::with_row(Ms, [&](auto g) -> int {
         using G = decltype(g);
         if constexpr (G::M > SLOTS) {
             return FFTCONV_EUNSUPPORTED;
         } else {
-            constexpr int M = G::M, NTHR = rf::threads_of(M), RW = ROWS<M>, lds = LDS_BYTES<M>;
+            constexpr int M = G::M, NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
             const bool f16 = p->dtype == FFTCONV_F16, half = 2 * Nk <= M;
             auto kern = f16 ? (half ? k_row_filter<M, true, true> : k_row_filter<M, true, false>)
                             : (half ? k_row_filter<M, false, true> : k_row_filter<M, false, false>);
