@@ -264,6 +264,14 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         return FFTCONV_EINVAL;
     }
     hipStream_t s = (hipStream_t)stream;
+    // a short filter of a plan that can run partial convolutions as short segments: the
+    // short transform's spectrum goes behind the dense one, and the tag behind it says which filter length it
+    // belongs to (0: none -- masked, adjoint or longer filters leave that region as it was).  The last transform's kernel sets it
+    // (as one of its own it took 4 us of a training step's filter transform, twice)
+    const bool with_short = p->f3.consts_short && !block_keep && !adjoint && fused3_short_ok(p, Nk);
+    KfTag tag;
+    if (p->f3.consts_short) tag = KfTag{(long long *)fused3_short_tag(p, k_f), with_short ? (long long)Nk : 0};
+    const KfTag dense_tag = with_short ? KfTag{} : tag;
     const uint8_t *keep_dev = nullptr;
     if (block_keep) {
         if (!(per_bin && n_blocks == p->M) && (!is_pow2(n_blocks) || n_blocks > MAX_BLOCKS || n_blocks > p->M)) {
@@ -276,7 +284,7 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
     }
     const bool fused = p->path == PATH_FUSED3 || p->f3.odd;
     if (fused) {
-        rc = fused3_filter(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, s);
+        rc = fused3_filter(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, dense_tag, s);
         if (rc) return rc;
     }
     // fp32 k_f in the row engine's order, in fp64 arithmetic
@@ -302,7 +310,7 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
     }
     for (int64_t h0 = 0; long_rows && h0 < p->H; h0 += long_chunk) {
         const int64_t nh = p->H - h0 < long_chunk ? p->H - h0 : long_chunk;
-        rc = long_filter_transform(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, s);
+        rc = long_filter_transform(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, dense_tag, s);
         if (rc) return rc;
     }
     for (int64_t h0 = 0; long_rows_f32 && h0 < p->H; h0 += long_chunk) {
@@ -319,18 +327,8 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
                                        : staged_pack_kf(p, spec, h0, nh, keep_dev, n_blocks, k_f, s);
         if (rc) return rc;
     }
-    // a short filter of a plan that can run partial convolutions as short segments: add the
-    // short transform's spectrum behind the dense one, and say in the tag behind it which filter length it
-    // belongs to (0: none -- masked, adjoint or longer filters leave that region as it was)
-    if (p->f3.consts_short) {
-        const bool with_short = !block_keep && !adjoint && fused3_short_ok(p, Nk);
-        if (with_short) {
-            rc = fused3_filter_short(p, k, Nk, k_f, s);
-            if (rc) return rc;
-        }
-        return fused3_set_short_tag(p, k_f, with_short ? Nk : 0, s);
-    }
-    return FFTCONV_OK;
+    if (with_short) return fused3_filter_short(p, k, Nk, k_f, tag, s);
+    return tag.at && !fused && !long_rows ? fused3_set_short_tag(tag, s) : FFTCONV_OK;
 }
 
 int fftconv_filter_fft(const fftconv_plan *p, const float *k, int64_t Nk, void *k_f, void *stream)

@@ -49,6 +49,16 @@ __device__ __forceinline__ bool gate_closed(const LaunchGate &g)
     return g.tag != nullptr && ((*g.tag == g.want) != (g.run_if_equal != 0));
 }
 
+// The tag behind the short spectrum of a k_f (fused3_short_tag), for the kernel of the filter transform that sets it; at == nullptr: none.
+struct KfTag {
+    long long *at = nullptr;
+    long long value = 0;
+};
+__device__ __forceinline__ void set_tag(const KfTag &t)
+{
+    if (t.at && blockIdx.x == 0 && threadIdx.x == 0) *t.at = t.value;
+}
+
 enum Path { PATH_STAGED = 0, PATH_FUSED3 = 1, PATH_MULTIPASS = 2, PATH_SMALL = 3 };
 
 constexpr int MAX_FACTORS = 8;
@@ -157,7 +167,7 @@ bool long_fft_supported(const fftconv_plan *p);
 int long_fft_init(fftconv_plan *p);
 void long_fft_destroy(fftconv_plan *p);
 int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
-                          const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s);
+                          const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, KfTag tag, hipStream_t s);
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s);
 FacList long_fft_factor_list(int64_t M);
@@ -182,13 +192,13 @@ uint32_t fused3_live_k3(const fftconv_plan *p, const uint8_t *block_keep, int64_
 bool fused3_short_ok(const fftconv_plan *p, int64_t Nk);
 int fused3_init_short(fftconv_plan *p);
 size_t fused3_short_kf_bytes(const fftconv_plan *p);
-int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, hipStream_t s);
+int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, KfTag tag, hipStream_t s);
 // the tag behind the short spectrum: the Nk that spectrum was built for, 0 = none
 const long long *fused3_short_tag(const fftconv_plan *p, const void *kf);
-int fused3_set_short_tag(const fftconv_plan *p, void *kf, int64_t Nk, hipStream_t s);
+int fused3_set_short_tag(KfTag tag, hipStream_t s);
 // filter transform in one kernel, taps to k_f; adjoint: the conjugate spectrum
 int fused3_filter(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev,
-                  int64_t n_blocks, void *kf, hipStream_t s);
+                  int64_t n_blocks, void *kf, KfTag tag, hipStream_t s);
 int fused3_forward_short(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, int64_t Nk,
                          hipStream_t s);
 // the 8192-point complex-row kernel used as the inner step of the multi-pass path
@@ -294,7 +304,7 @@ int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, fl
                         hipStream_t s);
 // the fp32 ends of the 8192-point matrix-core plans (row_filter.hip): taps -> k_f, accumulated spectra -> dk
 int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
-               int64_t n_blocks, uint32_t *kf, hipStream_t s);
+               int64_t n_blocks, uint32_t *kf, KfTag tag, hipStream_t s);
 // fp64 filter transform of the plans that convolve on the row engine with k_f in fp32
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s);

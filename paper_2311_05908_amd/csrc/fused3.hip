@@ -417,11 +417,11 @@ const long long *fused3_short_tag(const fftconv_plan *p, const void *kf)
     return (const long long *)((const char *)kf + dense_kf_bytes(p) + (size_t)(p->H * SHORT_M) * sizeof(uint32_t));
 }
 
-__global__ void k_set_tag(long long *tag, long long value) { *tag = value; }
+__global__ void k_set_tag(KfTag tag) { set_tag(tag); }
 
-int fused3_set_short_tag(const fftconv_plan *p, void *kf, int64_t Nk, hipStream_t s)
+int fused3_set_short_tag(KfTag tag, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_set_tag, dim3(1), dim3(1), 0, s, (long long *)fused3_short_tag(p, kf), (long long)Nk);
+    hipLaunchKernelGGL(k_set_tag, dim3(1), dim3(1), 0, s, tag);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -434,10 +434,10 @@ bool fused3_short_ok(const fftconv_plan *p, int64_t Nk)
 }
 
 // the 8192-point spectrum of a short filter, behind the dense one (see fused3_forward_short)
-int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, hipStream_t s)
+int fused3_filter_short(const fftconv_plan *p, const float *k, int64_t Nk, void *kf, KfTag tag, hipStream_t s)
 {
     uint32_t *dst = (uint32_t *)((char *)kf + dense_kf_bytes(p));
-    return row_filter(p, k, Nk, SHORT_M, false, nullptr, 1, dst, s);
+    return row_filter(p, k, Nk, SHORT_M, false, nullptr, 1, dst, tag, s);
 }
 
 // Partial convolution (Section 3.3) of a plan for fft >= 16384: the filter covers Nk <= 2049 taps, so
@@ -461,11 +461,11 @@ int fused3_forward_short(const fftconv_plan *p, const void *u, const void *kf, v
 
 // The filter transform of every plan on this path is one kernel from the taps to k_f.
 int fused3_filter(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev,
-                  int64_t n_blocks, void *kf, hipStream_t s)
+                  int64_t n_blocks, void *kf, KfTag tag, hipStream_t s)
 {
-    if (p->M > 8192) return fused3_big_filter(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s);
+    if (p->M > 8192) return fused3_big_filter(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
     // one 16-bit pair a bin, in the slot order of the 8192-point kernel (kernel_slot)
-    return row_filter(p, k, Nk, p->M, adjoint, keep_dev, n_blocks, (uint32_t *)kf, s);
+    return row_filter(p, k, Nk, p->M, adjoint, keep_dev, n_blocks, (uint32_t *)kf, tag, s);
 }
 
 bool fused3_gates_fused(const fftconv_plan *p) { return p->path == PATH_FUSED3; }

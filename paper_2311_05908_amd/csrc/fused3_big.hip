@@ -1041,8 +1041,9 @@ template <int N2> using FilterRow = rf::Row<BigGeo<N2>::M / 2>;
 template <typename TT, int N2, bool HALF>
 __global__ void __launch_bounds__(FilterRow<N2>::T, 2) k_filter_big(const float *__restrict__ k, typename TT::CW *__restrict__ kf,
                                                                    const float2 *__restrict__ tab, int64_t Nk, bool conj_out,
-                                                                   const uint8_t *__restrict__ keep, int64_t n_blocks)
+                                                                   const uint8_t *__restrict__ keep, int64_t n_blocks, KfTag kf_tag)
 {
+    set_tag(kf_tag);
     using G = FilterRow<N2>;
     constexpr int BM = BigGeo<N2>::M, MH = BM / 2, R2 = BigGeo<N2>::R2, MIN = HALF ? G::P / 2 : G::P;
     static_assert(G::R0 == 32 && G::R1 == N2 && G::R2 == 16 && G::T / G::RL == N2, "the engine's digits are those of the kernel");
@@ -1266,13 +1267,13 @@ template <int N2> int big_init_t(fftconv_plan *p)
 
 template <typename TT, int N2>
 int big_filter_tt(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks,
-                  void *kf, hipStream_t s)
+                  void *kf, KfTag tag, hipStream_t s)
 {
     using G = FilterRow<N2>;
     const auto kern = Nk <= BigGeo<N2>::M / 2 ? k_filter_big<TT, N2, true> : k_filter_big<TT, N2, false>;
     FC_TRY(raise_dynamic_lds((const void *)kern, G::LDS_BYTES));
     hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), G::LDS_BYTES, s, k, (typename TT::CW *)kf, rf::row_table<G>(p), Nk, adjoint,
-                       keep_dev, n_blocks);
+                       keep_dev, n_blocks, tag);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -1319,14 +1320,14 @@ size_t fused3_big_kf_bytes(const fftconv_plan *p)
 }
 
 int fused3_big_filter(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev,
-                      int64_t n_blocks, void *kf, hipStream_t s)
+                      int64_t n_blocks, void *kf, KfTag tag, hipStream_t s)
 {
     const bool f16 = p->dtype == FFTCONV_F16;
     if (p->M == 32768)
-        return f16 ? big_filter_tt<H16, 32>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s)
-                   : big_filter_tt<B16, 32>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s);
-    return f16 ? big_filter_tt<H16, 16>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s)
-               : big_filter_tt<B16, 16>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, s);
+        return f16 ? big_filter_tt<H16, 32>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s)
+                   : big_filter_tt<B16, 32>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
+    return f16 ? big_filter_tt<H16, 16>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s)
+               : big_filter_tt<B16, 16>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
 }
 
 // live_k3, live_k2, live_k1: bit d set when the value d of that digit of the frequency f = k1 + 32 k2 + 32 N2 k3

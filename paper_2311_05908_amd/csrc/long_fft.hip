@@ -229,8 +229,9 @@ template <int KF>
 __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__restrict__ tmp, void *__restrict__ kf,
                                                              const float2 *__restrict__ tab, FacList flA, int A, int64_t h0, int blocks,
                                                              const uint8_t *__restrict__ keep, int64_t n_blocks, bool natural,
-                                                             bool conj_out)
+                                                             bool conj_out, KfTag kf_tag)
 {
+    set_tag(kf_tag);
     using G = std::conditional_t<KF == 2, RX, RB>;
     extern __shared__ float2 XL[];
     const int M = A * LB, NR = A / 2 + 1;
@@ -642,13 +643,13 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
 
 template <int KF>
 int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 *tmp, void *kf, int64_t h0, const uint8_t *keep_dev,
-              int64_t n_blocks, bool natural, bool conj_out, hipStream_t s)
+              int64_t n_blocks, bool natural, bool conj_out, KfTag tag, hipStream_t s)
 {
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF>, B_LDS));
     const float2 *tab = KF == 2 ? rf::row_table<RX>(p) : rf::row_table<RB>(p);
     const int64_t blocks = nh * (g.A / 2 + 1);                // at most 2^16 channels of 257
     hipLaunchKernelGGL(k_long_blocks_kf<KF>, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(RB::T), B_LDS, s, tmp, kf, tab, g.flA,
-                       g.A, h0, (int)blocks, keep_dev, n_blocks, natural, conj_out);
+                       g.A, h0, (int)blocks, keep_dev, n_blocks, natural, conj_out, tag);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -777,7 +778,7 @@ void long_fft_destroy(fftconv_plan *p)
 // The filter transform of channels [h0, h0 + nh) of a multi-pass plan: taps (nh, Nk) -> their rows of k_f; tmp holds
 // nh * (A/2 + 1) * 8192 float2 with multipass_filter_outer_ok(p) (the chunks of the caller count on it), else nh * M.  adjoint: the spectrum of the circularly time-reversed filter (the conjugate spectrum).
 int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
-                          const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
+                          const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, KfTag tag, hipStream_t s)
 {
     const LongGeo g = long_geo(p->M);
     const LongTw tw = long_tw(p);
@@ -787,8 +788,8 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
     int rc = natural ? multipass_filter_outer(p, outer_rows(k), FFTCONV_F32, Nk, nh, tmp, s)
                      : launch_fwd_cols<float>(g, k, nullptr, tmp, tw, nh, Nk, adjoint, s, true);
     if (rc) return rc;
-    return p->dtype == FFTCONV_F16 ? launch_kf<1>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s)
-                                   : launch_kf<0>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, s);
+    return p->dtype == FFTCONV_F16 ? launch_kf<1>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, tag, s)
+                                   : launch_kf<0>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, tag, s);
 }
 
 // The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block transforms of the
@@ -798,7 +799,7 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
 {
     const LongGeo g = long_geo(p->M);
     FC_TRY(multipass_filter_outer(p, outer_rows(k), FFTCONV_F32, Nk, nh, tmp, s));
-    return launch_kf<2>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, true, adjoint, s);
+    return launch_kf<2>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, true, adjoint, KfTag{}, s);
 }
 
 // The position order of the spectra of these transforms (k_f of the fp32 plans from fft_size 32768 up is stored in it)

@@ -34,9 +34,10 @@ template <int M> constexpr int LDS_BYTES = ROWS<M> * Row<M>::LDS_BYTES + (IMAGE<
 template <int M, bool F16, bool HALF>
 __global__ void __launch_bounds__(rf::threads_of(M), 2)
     k_row_filter(const float *__restrict__ k, uint32_t *__restrict__ kf, const float2 *__restrict__ tab, int H, int64_t Nk, bool conj_out,
-                 const uint8_t *__restrict__ keep, int64_t n_blocks)
+                 const uint8_t *__restrict__ keep, int64_t n_blocks, KfTag kf_tag)
 {
     using G = Row<M>;
+    set_tag(kf_tag);
     constexpr int RW = rf::threads_of(M) / G::T, MIN = HALF ? G::P / 2 : G::P;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
@@ -232,7 +233,7 @@ int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_ou
 // k_f (H, Ms slots) of the 8192-point kernels for a transform of Ms = 256 .. 8192 points (min(fft_size, 8192): plans above
 // keep the spectrum of a short filter this way)
 int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bool conj_out, const uint8_t *keep_dev,
-               int64_t n_blocks, uint32_t *kf, hipStream_t s)
+               int64_t n_blocks, uint32_t *kf, KfTag tag, hipStream_t s)
 {
     return rf::with_row(Ms, [&](auto g) -> int {
         using G = decltype(g);
@@ -245,7 +246,7 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
                             : (half ? k_row_filter<M, false, true> : k_row_filter<M, false, false>);
             FC_TRY(raise_dynamic_lds((const void *)kern, lds));
             hipLaunchKernelGGL(kern, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, k, kf, rf::row_table<G>(p), (int)p->H,
-                               Nk, conj_out, keep_dev, n_blocks);
+                               Nk, conj_out, keep_dev, n_blocks, tag);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;
         }
