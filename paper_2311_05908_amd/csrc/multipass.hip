@@ -133,7 +133,7 @@ struct OuterGeo {
 // RB == 1 (No <= 16; all six outer kernels): a thread reads every outer row of its two columns, transforms them in registers
 // and writes every row; no tile, no barrier, 8 or 16 loads of a thread in flight instead of one per trip of a loop.  Bound by
 // the copy of the bytes.  Same operations on the same values as through the tile.  us, before and after: fft 131072, 2 x 256 x 65536
-// bf16: pass A 54 -> 40 (201 MB), pass C 67 -> 52, gradient: rows of u and dy 39 -> 36 each, last pass 56 -> 37; fft 32768,
+// bf16: pass A 54 -> 40 (201 MB), pass C 67 -> 52 (40 with fewer threads, see there), gradient: rows of u and dy 39 -> 36 each, last pass 56 -> 37; fft 32768,
 // 5 x 256 x 10007: A 29 -> 21, C 30 -> 17, lone row 13 -> 9 and 13 -> 8.
 // EXACT (all four outer kernels): N is even and equals the input length the instantiation is for (M/2, or M
 // with FULLN), so every load of u and store of y is in range, 4-byte aligned and unconditional: the compiler
@@ -322,8 +322,13 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
 }
 
 // ---- pass C: S -> conjugate twiddle -> outer inverse DFT -> the two real rows of the pair
+// RB == 1: 16 rows of two columns, their transform and the packed results do not fit into the 128 registers of four waves per SIMD, and
+// blocks of half the threads can be three: bf16 2 x 256 x 65536 (fft 131072) 157 -> 145 us, 8 x 64 x 30001 157 -> 137 (as many
+// threads less at 128 registers: no difference).
+template <int RB> constexpr int INV_TB = RB == 1 ? TB / 2 : TB;
+template <int RB> constexpr int INV_WAVES = RB == 1 ? 3 : 4;
 template <bool F16, int RA, int RB, int CV, bool FULLN, bool GATED, bool MIRROR, bool EXACT>
-__global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int CT,
+__global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int CT,
                                                  int B, int H, int N, int64_t M, int ko_lo, int ko_hi, int mirror_from,
                                                  const uint16_t *__restrict__ vg, LaunchGate gate)
 {
@@ -344,7 +349,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     const int CG = CT / CV;
     const int lgCG = 31 - __builtin_clz(CG);
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += INV_TB<RB>) wno[j] = wm(j, 2.0f / (float)No);
         __syncthreads();
     }
     const float ihm = 2.0f / (float)M;
@@ -356,7 +361,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     // so the value that enters the inverse is conj(S[ko']) conj(conj(W_Mi^{r}) W_M^{r ko}): the mirror row is
     // read and conjugated (a sign flip on the packed word), and from the first mirrored row on the twiddle of the
     // recurrence carries the extra factor conj(W_Mi^{r}).
-    for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
+    for (int e = tid; RB > 1 && e < RA * CG; e += INV_TB<RB>) {
         const int c = (e & (CG - 1)) * CV, ka = e >> lgCG;
         uint32_t in[RB][CV];
 #pragma unroll
@@ -436,7 +441,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv(const uint32_t *__restrict_
     // output gate of the gated form: multiplies the result after its rounding to the I/O dtype; nullptr = none
     const uint16_t *g0 = GATED ? vg + ((size_t)b0 * H + h) * N : nullptr;
     const uint16_t *g1 = GATED ? vg + ((size_t)(b0 + (two ? 1 : 0)) * H + h) * N : nullptr;
-    for (int e = tid; e < RB * CG; e += TB) {
+    for (int e = tid; e < RB * CG; e += INV_TB<RB>) {
         const int c = (e & (CG - 1)) * CV, b2 = e >> lgCG;
         // RB == 1: a thread reads all rows of its columns and no tile lies in between
         uint32_t in[RB == 1 ? RA : 1][CV];
@@ -1113,6 +1118,8 @@ int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, 
     constexpr int CTC = MI / (RA * RB) < 32 ? 32 : MI / (RA * RB);
     constexpr int CV = (RB <= 16 && RA * CTC / 2 >= TB) ? 2 : 1;
     const size_t lds = g.lds();
+    const int ct_inv = RB == 1 ? g.CT / 2 : g.CT;                 // columns of a block of INV_TB threads
+    const dim3 grid_inv(grid.x * (unsigned)(g.CT / ct_inv), grid.y);
     FC_TRY(raise_dynamic_lds((const void *)k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>, 160 * 1024));
@@ -1120,11 +1127,11 @@ int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, 
         hipLaunchKernelGGL((k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint16_t *)src,
                            (uint32_t *)dst, g.CT, B, H, N, M, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
     else if (mirror_from < g.No)
-        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>), grid, dim3(TB), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, g.CT, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>), grid_inv, dim3(INV_TB<RB>), lds, s, (const uint32_t *)src,
+                           (uint16_t *)dst, ct_inv, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
     else
-        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>), grid, dim3(TB), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, g.CT, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>), grid_inv, dim3(INV_TB<RB>), lds, s, (const uint32_t *)src,
+                           (uint16_t *)dst, ct_inv, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
