@@ -27,9 +27,9 @@ constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 // twiddle is a compile-time constant.  A butterfly with a twiddle is eight fused operations, a + w b and
 // a - w b as two chained multiply-adds per part each; SIX: six, the difference as 2 a - (a + w b), which carries the
 // rounding of the sum (4 % more error of a transform); PRODUCT: eight, w b first, then sum and difference in the place of its
-// operands (for kernels that are out of registers).  Those with w = 1 or -+i are four additions.  HALFIN: the
-// inputs x[R/2 ..] are zero (the padding of a causal convolution) and are not read; the first level of butterflies then
-// only copies.
+// operands (for kernels that are out of registers).  Those with w = 1 or -+i are four additions, those with odd powers of W_8,
+// c (+-1 +-i), two additions and four multiply-adds, whichever the form (SIX has no more itself).  HALFIN: the inputs x[R/2 ..] are zero (the padding of a
+// causal convolution) and are not read; the first level of butterflies then only copies.
 enum Butterfly { EIGHT, SIX, PRODUCT };
 template <int R, bool INV, bool HALFIN = false, Butterfly FORM = EIGHT> __device__ __forceinline__ void dft_reg(float2 (&x)[R])
 {
@@ -55,7 +55,14 @@ template <int R, bool INV, bool HALFIN = false, Butterfly FORM = EIGHT> __device
             for (int j = 0; j < len / 2; ++j) {
                 const int q = j * (32 / len);                  // twiddle W_32^q, 0 <= q < 16
                 const float2 a = x[blk + j], b = x[blk + j + len / 2];
-                if (q == 0 || q == 8 || FORM == PRODUCT) {     // 1; -i forward, +i inverse
+                if ((q == 4 || q == 12) && FORM != SIX) {
+                    // W_8^1, W_8^3: (forward) c (b.x + b.y), c (b.y - b.x) with c = cos(pi/4), and the first of them negative at W_8^3
+                    const float s = INV ? b.x - b.y : b.x + b.y, d = INV ? b.x + b.y : b.y - b.x;
+                    const float cs = C32[4];
+                    const float2 t = q == 4 ? make_float2(s, d) : INV ? make_float2(-d, s) : make_float2(d, -s);
+                    x[blk + j] = make_float2(__builtin_fmaf(cs, t.x, a.x), __builtin_fmaf(cs, t.y, a.y));
+                    x[blk + j + len / 2] = make_float2(__builtin_fmaf(-cs, t.x, a.x), __builtin_fmaf(-cs, t.y, a.y));
+                } else if (q == 0 || q == 8 || FORM == PRODUCT) {     // 1; -i forward, +i inverse
                     const float wr = C32[q], wi = INV ? S32[q] : -S32[q];
                     const float2 t = q == 0   ? b
                                      : q == 8 ? (INV ? make_float2(-b.y, b.x) : make_float2(b.y, -b.x))
@@ -125,6 +132,14 @@ template <int R, bool INV> __device__ __forceinline__ void dft_reg(double2 (&x)[
             for (int j = 0; j < len / 2; ++j) {
                 const int q = j * (32 / len);                  // twiddle W_32^q, 0 <= q < 16
                 const double2 a = x[blk + j], b = x[blk + j + len / 2];
+                if (q == 4 || q == 12) {
+                    const double s = INV ? b.x - b.y : b.x + b.y, d = INV ? b.x + b.y : b.y - b.x;
+                    const double cs = C32D[4];
+                    const double2 t = q == 4 ? make_double2(s, d) : INV ? make_double2(-d, s) : make_double2(d, -s);
+                    x[blk + j] = make_double2(__builtin_fma(cs, t.x, a.x), __builtin_fma(cs, t.y, a.y));
+                    x[blk + j + len / 2] = make_double2(__builtin_fma(-cs, t.x, a.x), __builtin_fma(-cs, t.y, a.y));
+                    continue;
+                }
                 double2 t;
                 if (q == 0) {
                     t = b;

@@ -27,6 +27,7 @@
 
 #include "dft_reg.h"
 #include "fftconv_internal.h"
+#include "fused3_common.h"
 
 #include <mutex>
 
@@ -79,13 +80,12 @@ __device__ __forceinline__ float2 cmulcf(float2 a, float2 b)      // a * conj(b)
 {
     return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
-// exp(-2 pi i e / M) for 0 <= e < M <= 2^22, inv_half_m = 2 / M: e / M is exact in fp32 and goes straight to
-// the hardware sine and cosine, which take their argument in revolutions (two quarter-rate instructions
+// exp(-2 pi i rev), 0 <= rev < 1.  The exponents of W_M, M <= 2^22, are exact in fp32 revolutions, products of them included, and go
+// straight to the hardware sine and cosine, which take their argument in revolutions (two quarter-rate instructions
 // instead of the ~25 of the library routine).  Their absolute error over every e / 2^22 measures 1.3e-7, far
 // below the 16-bit roundings of the values these twiddles multiply.
-__device__ __forceinline__ float2 wm(int e, float inv_half_m)
+__device__ __forceinline__ float2 wrev(float rev)
 {
-    const float rev = (float)e * (0.5f * inv_half_m);
     return make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
 }
 
@@ -109,13 +109,39 @@ template <bool F16> __device__ __forceinline__ float2 unpack2(uint32_t w)
     }
 }
 
+// half v (0, 1) of a packed pair
+template <bool F16> __device__ __forceinline__ float half_of(uint32_t w, int v)
+{
+    if constexpr (F16) return __half2float(__builtin_bit_cast(__half, (uint16_t)(v ? w >> 16 : w)));
+    else return __uint_as_float(v ? w & 0xffff0000u : w << 16);
+}
+template <bool F16> __device__ __forceinline__ uint32_t pack2(float lo, float hi)
+{
+    if constexpr (F16) return (uint32_t)cv16<true>(lo) | ((uint32_t)cv16<true>(hi) << 16);
+    else return f3::BF16::pack(lo, hi);
+}
+
+// An access `bytes` beyond an address that is the same for every thread: a 32-bit offset of the load or store, where an index into the
+// array costs two 64-bit operations for each (rows of these passes are fewer than 2^31 bytes).
+template <typename T> __device__ __forceinline__ T ld_at(const void *base, uint32_t bytes) { return *(const T *)((const char *)base + bytes); }
+// Two 16-bit samples n, n + 1 of a row of N >= 2, wherever the row lies (a 4-byte access needs 2-byte alignment here); what lies
+// beyond its end reads as zeros, and nothing beyond it is touched: there the row's last pair is fetched, unconditionally, so that
+// a thread's loads go out back to back, and pair_of() moves its second half down or drops it.  (A row of one sample: that in the second half.)
+struct __attribute__((packed, aligned(2))) Word { uint32_t w; };
+__device__ __forceinline__ uint32_t ld_pair(const uint16_t *row, int n, int N) { return ld_at<Word>(row, 2u * (uint32_t)min(n, N - 2)).w; }
+__device__ __forceinline__ uint32_t pair_of(uint32_t w, int n, int N) { return n >= N ? 0 : n == N - 1 ? w >> 16 : w; }
+template <typename T> __device__ __forceinline__ void st_at(void *base, uint32_t bytes, T v) { *(T *)((char *)base + bytes) = v; }
+
 // elementwise product of two packed pairs of 16-bit values, each product rounded to the I/O dtype (the
 // gates of the gated form, Section 3.1: the rounded product is what the transform consumes / what is stored)
 template <bool F16> __device__ __forceinline__ uint32_t mul_pair16(uint32_t a, uint32_t b)
 {
     const float2 x = unpack2<F16>(a), g = unpack2<F16>(b);
-    return (uint32_t)cv16<F16>(x.x * g.x) | ((uint32_t)cv16<F16>(x.y * g.y) << 16);
+    return pack2<F16>(x.x * g.x, x.y * g.y);
 }
+
+// columns per block of the passes with a tile, No = RA RB > 16: an fp32 tile T[No][.] of 64 KiB (two blocks per compute unit), at least 32
+template <int RA, int RB> constexpr int TILE_COLS = MI / (RA * RB) < 32 ? 32 : MI / (RA * RB);
 
 struct OuterGeo {
     int No, Ra, Rb, CT;          // outer length, its two factors, columns per block
@@ -135,14 +161,20 @@ struct OuterGeo {
 // the copy of the bytes.  Same operations on the same values as through the tile.  us, before and after: fft 131072, 2 x 256 x 65536
 // bf16: pass A 54 -> 40 (201 MB), pass C 67 -> 52 (40 with fewer threads, see there), gradient: rows of u and dy 39 -> 36 each, last pass 56 -> 37; fft 32768,
 // 5 x 256 x 10007: A 29 -> 21, C 30 -> 17, lone row 13 -> 9 and 13 -> 8.
+// RB > 1: bound by the vector ALU, whose instructions a wave issues every four clocks: 924 of a thread took 112 us of 2^21 points, 64 rows.
+// Hence constant tile shapes (LDS and row offsets are immediates or scalars), twiddle angles as exact products in fp32, pairs packed by one
+// conversion, no masks where nothing is masked: 690.  us: bf16 2^21, 1 x 64 rows 390 -> 366; circular 2 x 128 x 2^19 402 -> 358,
+// 2 x 256 x 2^18 420 -> 383, 1 x 256 x 2^17 (fft 2^18) 218 -> 195.
+// N odd, or rows that start off a 4-byte boundary: pairs are fetched and stored as unaligned words (ld_pair()); a load behind a branch for
+// every sample before: gated 2 x 64 x 400001 639 -> 444 us, 3 x 64 x 200001 330 -> 262, 2 x 64 x 100001 104 -> 84.
 // EXACT (all four outer kernels): N is even and equals the input length the instantiation is for (M/2, or M
 // with FULLN), so every load of u and store of y is in range, 4-byte aligned and unconditional: the compiler
 // can then issue a thread's loads back to back instead of one guarded load at a time.
 // RB > 1: butterflies with the product first.  As chained multiply-adds they cost the passes of full-length rows their last
 // registers (28 - 40 bytes of scratch; 2 x 192 x 2^18 circular bf16 333 -> 352 us, 334 so; 2 x 48 x 2^20 334 - 342 -> 362, 342).
 template <bool F16, int RA, int RB, int CV, bool FULLN, bool GATED, bool EXACT>
-__global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict__ u, uint32_t *__restrict__ S, int CT,
-                                                 int B, int H, int N, int64_t M, int ko_lo, int ko_hi,
+__global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict__ u, uint32_t *__restrict__ S, int ct,
+                                                 int B, int H, int N, int ko_lo, int ko_hi,
                                                  const uint16_t *__restrict__ wg, LaunchGate gate)
 {
     extern __shared__ float2 sm[];
@@ -152,6 +184,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that can hold input
     float2 *wno = sm;                              // W_No^j, j < No
     float2 *T = sm + No;                           // [No][CT]
+    const int CT = RB > 1 ? TILE_COLS<RA, RB> : ct;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * CT;
     const int ph = blockIdx.y;                     // pair * H + h
@@ -163,63 +196,64 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
     // input gate of the gated form (same shape as u), multiplied in as the samples arrive; nullptr = none
     const uint16_t *g0 = GATED ? wg + ((size_t)b0 * H + h) * N : nullptr;
     const uint16_t *g1 = GATED ? wg + ((size_t)(b0 + (two ? 1 : 0)) * H + h) * N : nullptr;
-    const bool wide = CV == 2 && (EXACT || N % 2 == 0);       // rows start 4-byte aligned
+    auto load = [&](const uint16_t *row, int n) -> uint32_t {
+        if constexpr (CV == 1) return ld_at<uint16_t>(row, EXACT || n < N ? 2 * n : 0);
+        else if constexpr (EXACT) return ld_at<uint32_t>(row, 2 * n);
+        else return ld_pair(row, n, N);
+    };
+    auto kept = [&](uint32_t w, int n) -> uint32_t {
+        if constexpr (EXACT) return w;
+        else if constexpr (CV == 1) return n < N ? w : 0;
+        else return pair_of(w, n, N);
+    };
     const int CG = CT / CV;                        // column groups, a power of two
     const int lgCG = 31 - __builtin_clz(CG);
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += TB) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
+#pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, b2 = e >> lgCG;
         uint32_t in0[RAIN], in1[RAIN];             // CV 16-bit values of row b / row b+1
         uint32_t gt0[GATED ? RAIN : 1], gt1[GATED ? RAIN : 1];
+        // (a missing row b+1 reads row b)
+        if (EXACT || CV == 1 || N > 1) {
 #pragma unroll
-        for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + c;
-            in0[a] = in1[a] = 0;
-            if constexpr (GATED) gt0[a] = gt1[a] = 0;
-            if (wide) {
-                // a pair beyond N (n and N are even: in or out as a whole) reads sample 0 and is discarded below, a
-                // missing row b+1 reads row b: the loads need no branch and go out back to back
-                const int64_t at = (EXACT || n < N) ? n : 0;
-                in0[a] = *(const uint32_t *)(row0 + at);
-                in1[a] = *(const uint32_t *)(row1 + at);
+            for (int a = 0; a < RAIN; ++a) {
+                const int n = (a * RB + b2) * MI + r0 + c;
+                in0[a] = load(row0, n);
+                in1[a] = load(row1, n);
                 if constexpr (GATED) {
-                    gt0[a] = *(const uint32_t *)(g0 + at);
-                    gt1[a] = *(const uint32_t *)(g1 + at);
+                    gt0[a] = load(g0, n);
+                    gt1[a] = load(g1, n);
                 }
-            } else {
+            }
+        } else {
 #pragma unroll
-                for (int v = 0; v < CV; ++v)
-                    if (EXACT || n + v < N) {
-                        in0[a] |= (uint32_t)row0[n + v] << (16 * v);
-                        if (two) in1[a] |= (uint32_t)row1[n + v] << (16 * v);
-                        if constexpr (GATED) {
-                            gt0[a] |= (uint32_t)g0[n + v] << (16 * v);
-                            if (two) gt1[a] |= (uint32_t)g1[n + v] << (16 * v);
-                        }
-                    }
+            for (int a = 0; a < RAIN; ++a) {
+                in0[a] = (uint32_t)row0[0] << 16;
+                in1[a] = (uint32_t)row1[0] << 16;
+                if constexpr (GATED) {
+                    gt0[a] = (uint32_t)g0[0] << 16;
+                    gt1[a] = (uint32_t)g1[0] << 16;
+                }
             }
         }
-        if (wide) {
 #pragma unroll
-            for (int a = 0; a < RAIN; ++a) {
-                asm volatile("" ::"v"(in0[a]), "v"(in1[a]));             // keeps the loads unconditional
-                if constexpr (GATED) asm volatile("" ::"v"(gt0[a]), "v"(gt1[a]));
-            }
+        for (int a = 0; a < RAIN; ++a) {
+            asm volatile("" ::"v"(in0[a]), "v"(in1[a]));                 // keeps the loads unconditional
+            if constexpr (GATED) asm volatile("" ::"v"(gt0[a]), "v"(gt1[a]));
+        }
 #pragma unroll
-            for (int a = 0; a < RAIN; ++a) {
-                const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + c;
-                const bool in = EXACT || n < N;
-                if (!in) in0[a] = 0;
-                if (!in || !two) in1[a] = 0;
-                if constexpr (GATED) {                                    // (0 times a discarded gate must stay 0)
-                    if (!in) gt0[a] = 0;
-                    if (!in || !two) gt1[a] = 0;
-                }
+        for (int a = 0; a < RAIN; ++a) {
+            const int n = (a * RB + b2) * MI + r0 + c;
+            in0[a] = kept(in0[a], n);
+            in1[a] = two ? kept(in1[a], n) : 0;
+            if constexpr (GATED) {                                        // (0 times a discarded gate must stay 0)
+                gt0[a] = kept(gt0[a], n);
+                gt1[a] = two ? kept(gt1[a], n) : 0;
             }
         }
         if constexpr (GATED) {
@@ -237,22 +271,23 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
 #pragma unroll
                 for (int a = 0; a < RA; ++a) {
                     x[a] = make_float2(0.f, 0.f);
-                    if (a < RAIN) x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
+                    if (a < RAIN) x[a] = make_float2(half_of<F16>(in0[a], v), half_of<F16>(in1[a], v));
                 }
                 dft_reg<RA, false, !FULLN, FORM>(x);
-                const int r = r0 + c + v;
+                const float rf = (float)(r0 + c + v);
 #pragma unroll
                 for (int ka = 0; ka < RA; ++ka) {
-                    const float2 t = cmulf(x[ka], wm((r * ka) & Mmask, ihm));
-                    o[ka][v] = (uint32_t)cv16<F16>(t.x) | ((uint32_t)cv16<F16>(t.y) << 16);
+                    const float2 t = cmulf(x[ka], wrev(rf * ((float)ka * im)));
+                    o[ka][v] = pack2<F16>(t.x, t.y);
                 }
             }
-            uint32_t *dst = &S[(size_t)ph * No * MI + multipass_row_slot(r0 + c, multipass_quarter_rows(No))];
+            const uint32_t at = 4u * (uint32_t)multipass_row_slot(r0 + c, multipass_quarter_rows(No));
 #pragma unroll
             for (int ka = 0; ka < RA; ++ka)
                 if (ko_lo >= ko_hi || ka < ko_lo || ka >= ko_hi) {        // (a zeroed part of the spectrum is never used)
-                    if constexpr (CV == 2) *(uint2 *)(dst + (size_t)ka * MI) = make_uint2(o[ka][0], o[ka][1]);
-                    else dst[(size_t)ka * MI] = o[ka][0];
+                    uint32_t *const dst = S + ((size_t)ph * No + ka) * MI;
+                    if constexpr (CV == 2) st_at(dst, at, make_uint2(o[ka][0], o[ka][1]));
+                    else st_at(dst, at, o[ka][0]);
                 }
             continue;
         }
@@ -264,7 +299,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
             for (int a = 0; a < RA; ++a) {
                 x[a] = make_float2(0.f, 0.f);
                 if (a < RAIN)                                        // (row b, row b+1) = (re, im)
-                    x[a] = unpack2<F16>(((in0[a] >> (16 * v)) & 0xffffu) | ((in1[a] >> (16 * v)) << 16));
+                    x[a] = make_float2(half_of<F16>(in0[a], v), half_of<F16>(in1[a], v));
             }
             dft_reg<RA, false, !FULLN, FORM>(x);
 #pragma unroll
@@ -281,6 +316,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
     }
     if constexpr (RB == 1) return;
     __syncthreads();
+#pragma unroll 1
     for (int e = tid; e < RA * CG; e += TB) {
         const int c = (e & (CG - 1)) * CV, ka = e >> lgCG;
         uint32_t o[RB][CV];
@@ -290,22 +326,21 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
 #pragma unroll
             for (int b2 = 0; b2 < RB; ++b2) x[b2] = T[(ka * RB + b2) * CT + c + v];
             dft_reg<RB, false, false, FORM>(x);
-            const int r = r0 + c + v;
-            float2 w = wm((r * ka) & Mmask, ihm);                 // W_M^{r ka}
-            const float2 step = wm((r * RA) & Mmask, ihm);        // W_M^{r RA}
+            const float rf = (float)(r0 + c + v);
+            float2 w = wrev(rf * ((float)ka * im));                 // W_M^{r ka}
+            const float2 step = wrev(rf * ((float)RA * im));        // W_M^{r RA}
 #pragma unroll
             for (int kb = 0; kb < RB; ++kb) {
                 const float2 t = cmulf(x[kb], w);
-                o[kb][v] = (uint32_t)cv16<F16>(t.x) | ((uint32_t)cv16<F16>(t.y) << 16);
+                o[kb][v] = pack2<F16>(t.x, t.y);
                 w = cmulf(w, step);
             }
         }
+        const uint32_t at = 4u * (uint32_t)(ka * MI + multipass_row_slot(r0 + c, multipass_quarter_rows(No)));
         auto put = [&](int kb) {
-            uint32_t *dst = &S[((size_t)ph * No + ka + RA * kb) * MI + multipass_row_slot(r0 + c, multipass_quarter_rows(No))];
-            if constexpr (CV == 2)
-                *(uint2 *)dst = make_uint2(o[kb][0], o[kb][1]);
-            else
-                *dst = o[kb][0];
+            uint32_t *const dst = S + ((size_t)ph * No + RA * kb) * MI;
+            if constexpr (CV == 2) st_at(dst, at, make_uint2(o[kb][0], o[kb][1]));
+            else st_at(dst, at, o[kb][0]);
         };
         if (ko_lo >= ko_hi) {                             // dense: unconditional stores, back to back
 #pragma unroll
@@ -322,14 +357,14 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd(const uint16_t *__restrict_
 }
 
 // ---- pass C: S -> conjugate twiddle -> outer inverse DFT -> the two real rows of the pair
-// RB == 1: 16 rows of two columns, their transform and the packed results do not fit into the 128 registers of four waves per SIMD, and
-// blocks of half the threads can be three: bf16 2 x 256 x 65536 (fft 131072) 157 -> 145 us, 8 x 64 x 30001 157 -> 137 (as many
-// threads less at 128 registers: no difference).
-template <int RB> constexpr int INV_TB = RB == 1 ? TB / 2 : TB;
-template <int RB> constexpr int INV_WAVES = RB == 1 ? 3 : 4;
+// No = 8 and 16: 16 rows of two columns, their transform and the packed results do not fit into the 128 registers of four waves per SIMD,
+// and blocks of half the threads can be three: bf16 2 x 256 x 65536 (fft 131072) 157 -> 145 us, 8 x 64 x 30001 157 -> 137 (as many
+// threads less at 128 registers: no difference).  Shorter ones fit, and smaller blocks cost them: 8 x 512 x 1321 (fft 8192) 66 -> 71.
+template <int RA, int RB> constexpr int INV_TB = RB == 1 && RA >= 8 ? TB / 2 : TB;
+template <int RA, int RB> constexpr int INV_WAVES = RB == 1 && RA >= 8 ? 3 : 4;
 template <bool F16, int RA, int RB, int CV, bool FULLN, bool GATED, bool MIRROR, bool EXACT>
-__global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int CT,
-                                                 int B, int H, int N, int64_t M, int ko_lo, int ko_hi, int mirror_from,
+__global__ void __launch_bounds__((INV_TB<RA, RB>), (INV_WAVES<RA, RB>)) k_outer_inv(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int ct,
+                                                 int B, int H, int N, int ko_lo, int ko_hi, int mirror_from,
                                                  const uint16_t *__restrict__ vg, LaunchGate gate)
 {
     extern __shared__ float2 sm[];
@@ -339,21 +374,20 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that are kept
     float2 *wno = sm;
     float2 *T = sm + No;                           // [No][CT]
+    const int CT = RB > 1 ? TILE_COLS<RA, RB> : ct;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * CT;
     const int ph = blockIdx.y;
     const int pair = ph / H, h = ph % H;
     const int b0 = 2 * pair;
     const bool two = b0 + 1 < B;
-    const bool wide = CV == 2 && (EXACT || N % 2 == 0);
     const int CG = CT / CV;
     const int lgCG = 31 - __builtin_clz(CG);
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += INV_TB<RB>) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += INV_TB<RA, RB>) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     // step 1: T[ka*RB + b2] = conj(W_No^{ka b2}) * sum_{kb} conj(W_RB^{b2 kb}) conj(W_M^{r ko}) S[ko], ko = ka + RA kb
     // MIRROR (mirror_from == No/2 + 1): rows ko > No/2 were never computed (a lone real row, see multipass_forward): before the
     // twiddle row ko is the complex conjugate of row ko' = No - ko, i.e.
@@ -361,52 +395,63 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
     // so the value that enters the inverse is conj(S[ko']) conj(conj(W_Mi^{r}) W_M^{r ko}): the mirror row is
     // read and conjugated (a sign flip on the packed word), and from the first mirrored row on the twiddle of the
     // recurrence carries the extra factor conj(W_Mi^{r}).
-    for (int e = tid; RB > 1 && e < RA * CG; e += INV_TB<RB>) {
+#pragma unroll 1
+    for (int e = tid; RB > 1 && e < RA * CG; e += INV_TB<RA, RB>) {
         const int c = (e & (CG - 1)) * CV, ka = e >> lgCG;
+        // the row that holds ko: itself, or with MIRROR from ko > No/2 on row No - ko, which the thread decides only at kb == RB/2;
+        // `up` or `down` beyond a row that is the same for every thread
+        const uint32_t slot = 4u * (uint32_t)multipass_row_slot(r0 + c, multipass_quarter_rows(No));
+        const uint32_t up = 4u * (uint32_t)(ka * MI) + slot, down = 4u * (uint32_t)((RA - ka) * MI) + slot;
+        const uint32_t *const src = S + (size_t)ph * No * MI;
+        auto get = [&](uint32_t (&w)[CV], const uint32_t *base, uint32_t at) {
+            if constexpr (CV == 2) {
+                const uint2 t = ld_at<uint2>(base, at);
+                w[0] = t.x;
+                w[1] = t.y;
+            } else {
+                w[0] = ld_at<uint32_t>(base, at);
+            }
+        };
         uint32_t in[RB][CV];
+        if (ko_lo >= ko_hi || ko_lo >= No) {
 #pragma unroll
-        for (int kb = 0; kb < RB; ++kb) {
-            const int ko = ka + RA * kb;
-            // ko = ka + RA kb > No/2 = RA RB/2, written so that only kb == RB/2 depends on the thread
-            const bool mir = MIRROR && (RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0)));
-            // zeroed part of the spectrum: the row counts as zero and was never written.  The load stays
+            for (int kb = 0; kb < RB; ++kb) {
+                if (MIRROR && kb >= RB / 2) get(in[kb], src + (kb > RB / 2 ? RB - 1 - kb : RB / 2 - 1) * RA * MI, down);
+                else get(in[kb], src + kb * RA * MI, up);
+            }
+        } else {
+            // zeroed part of the spectrum (never with MIRROR): the row counts as zero and was never written.  The load stays
             // unconditional (of row 0 instead, its value discarded), so that a thread's loads go out back to
             // back: behind a branch each of them would be waited for before the next is issued.
-            const bool dead = ko >= ko_lo && ko < ko_hi;
-            const uint32_t *src = &S[((size_t)ph * No + (dead ? 0 : (mir ? No - ko : ko))) * MI + multipass_row_slot(r0 + c, multipass_quarter_rows(No))];
-            if constexpr (CV == 2) {
-                const uint2 t = *(const uint2 *)src;
-                in[kb][0] = t.x;
-                in[kb][1] = t.y;
-            } else {
-                in[kb][0] = *src;
-            }
+            auto dead = [&](int kb) { return ka + RA * kb >= ko_lo && ka + RA * kb < ko_hi; };
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb) get(in[kb], src, dead(kb) ? slot : up + 4u * (uint32_t)(kb * RA * MI));
+            // (an empty statement that reads the loaded words: without it the compiler moves each load back under its
+            //  condition)
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb)
+#pragma unroll
+                for (int v = 0; v < CV; ++v) asm volatile("" ::"v"(in[kb][v]));
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb)
+#pragma unroll
+                for (int v = 0; v < CV; ++v)
+                    if (dead(kb)) in[kb][v] = 0;
         }
-        // (an empty statement that reads the loaded words: without it the compiler moves each load back under its
-        //  condition)
+        if constexpr (MIRROR) {                               // conjugate: the imaginary part is the upper half
 #pragma unroll
-        for (int kb = 0; kb < RB; ++kb)
+            for (int kb = RB / 2; kb < RB; ++kb)
+                if (kb > RB / 2 || ka > 0) {
 #pragma unroll
-            for (int v = 0; v < CV; ++v) asm volatile("" ::"v"(in[kb][v]));
-#pragma unroll
-        for (int kb = 0; kb < RB; ++kb) {
-            const int ko = ka + RA * kb;
-            const bool mir = MIRROR && (RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0)));
-            if (ko >= ko_lo && ko < ko_hi) {
-#pragma unroll
-                for (int v = 0; v < CV; ++v) in[kb][v] = 0;
-            }
-            if (mir) {                                        // conjugate: the imaginary part is the upper half
-#pragma unroll
-                for (int v = 0; v < CV; ++v) in[kb][v] ^= 0x80000000u;
-            }
+                    for (int v = 0; v < CV; ++v) in[kb][v] ^= 0x80000000u;
+                }
         }
         float2 o[RB][CV];
 #pragma unroll
         for (int v = 0; v < CV; ++v) {
-            const int r = r0 + c + v;
-            float2 w = wm((r * ka) & Mmask, ihm);
-            const float2 step = wm((r * RA) & Mmask, ihm);
+            const float rf = (float)(r0 + c + v);
+            float2 w = wrev(rf * ((float)ka * im));
+            const float2 step = wrev(rf * ((float)RA * im));
             constexpr float unboost = 1.0f / (float)multipass_kf_boost(F16, No);     // exact: a power of two
             w.x *= unboost;
             w.y *= unboost;
@@ -417,7 +462,7 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
                 const bool first_mirrored = RB == 1 ? ka > RA / 2
                                                     : ((kb == RB / 2 && ka > 0) || (kb == RB / 2 + 1 && ka == 0));
                 if (MIRROR && first_mirrored)
-                    w = cmulcf(w, wm((r * No) & Mmask, ihm));        // times conj(W_Mi^{r}), once
+                    w = cmulcf(w, wrev(rf * (1.0f / (float)MI)));        // times conj(W_Mi^{r}), once
                 x[kb] = cmulcf(unpack2<F16>(in[kb][v]), w);
                 w = cmulf(w, step);
             }
@@ -441,7 +486,8 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
     // output gate of the gated form: multiplies the result after its rounding to the I/O dtype; nullptr = none
     const uint16_t *g0 = GATED ? vg + ((size_t)b0 * H + h) * N : nullptr;
     const uint16_t *g1 = GATED ? vg + ((size_t)(b0 + (two ? 1 : 0)) * H + h) * N : nullptr;
-    for (int e = tid; e < RB * CG; e += INV_TB<RB>) {
+#pragma unroll 1
+    for (int e = tid; e < RB * CG; e += INV_TB<RA, RB>) {
         const int c = (e & (CG - 1)) * CV, b2 = e >> lgCG;
         // RB == 1: a thread reads all rows of its columns and no tile lies in between
         uint32_t in[RB == 1 ? RA : 1][CV];
@@ -473,8 +519,7 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
                 }
         }
         uint32_t o0[RAIN], o1[RAIN];
-#pragma unroll
-        for (int a = 0; a < RAIN; ++a) o0[a] = o1[a] = 0;
+        float2 left[CV == 2 ? RAIN : 1];           // the even column's results, until the odd one's are there
 #pragma unroll
         for (int v = 0; v < CV; ++v) {
             float2 x[RA];
@@ -482,11 +527,11 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
             for (int ka = 0; ka < RA; ++ka) {
                 if constexpr (RB == 1) {
                     constexpr float unboost = 1.0f / (float)multipass_kf_boost(F16, No);     // exact: a power of two
-                    const int r = r0 + c + v;
-                    float2 w = wm((r * ka) & Mmask, ihm);
+                    const float rf = (float)(r0 + c + v);
+                    float2 w = wrev(rf * ((float)ka * im));
                     w.x *= unboost;
                     w.y *= unboost;
-                    if (MIRROR && ka > RA / 2) w = cmulcf(w, wm((r * No) & Mmask, ihm));
+                    if (MIRROR && ka > RA / 2) w = cmulcf(w, wrev(rf * (1.0f / (float)MI)));
                     x[ka] = cmulcf(unpack2<F16>(in[ka][v]), w);
                 } else {
                     x[ka] = T[(ka * RB + b2) * CT + c + v];
@@ -495,34 +540,32 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
             dft_reg<RA, true, false, FORM>(x);
 #pragma unroll
             for (int a = 0; a < RAIN; ++a) {
-                o0[a] |= (uint32_t)cv16<F16>(x[a].x) << (16 * v);
-                o1[a] |= (uint32_t)cv16<F16>(x[a].y) << (16 * v);
+                if (v == CV - 1) {
+                    o0[a] = CV == 2 ? pack2<F16>(left[CV == 2 ? a : 0].x, x[a].x) : (uint32_t)cv16<F16>(x[a].x);
+                    o1[a] = CV == 2 ? pack2<F16>(left[CV == 2 ? a : 0].y, x[a].y) : (uint32_t)cv16<F16>(x[a].y);
+                } else {
+                    left[a] = x[a];
+                }
             }
         }
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + c;
-            if (wide) {
-                if (EXACT || n < N) {
-                    if constexpr (GATED) {
-                        o0[a] = mul_pair16<F16>(o0[a], *(const uint32_t *)(g0 + n));
-                        if (two) o1[a] = mul_pair16<F16>(o1[a], *(const uint32_t *)(g1 + n));
-                    }
-                    *(uint32_t *)(row0 + n) = o0[a];
-                    if (two) *(uint32_t *)(row1 + n) = o1[a];
+            const int n = (a * RB + b2) * MI + r0 + c;
+            const uint32_t at = 2 * n;
+            if (CV == 2 && (EXACT || n + 1 < N)) {
+                if constexpr (GATED) {
+                    o0[a] = mul_pair16<F16>(o0[a], ld_at<Word>(g0, at).w);
+                    if (two) o1[a] = mul_pair16<F16>(o1[a], ld_at<Word>(g1, at).w);
                 }
-            } else {
-#pragma unroll
-                for (int v = 0; v < CV; ++v)
-                    if (EXACT || n + v < N) {
-                        uint32_t a0 = (o0[a] >> (16 * v)) & 0xffffu, a1 = (o1[a] >> (16 * v)) & 0xffffu;
-                        if constexpr (GATED) {
-                            a0 = mul_pair16<F16>(a0, g0[n + v]) & 0xffffu;
-                            if (two) a1 = mul_pair16<F16>(a1, g1[n + v]) & 0xffffu;
-                        }
-                        row0[n + v] = (uint16_t)a0;
-                        if (two) row1[n + v] = (uint16_t)a1;
-                    }
+                st_at(row0, at, Word{o0[a]});
+                if (two) st_at(row1, at, Word{o1[a]});
+            } else if (EXACT || n < N) {                                  // one column, or the last sample of an odd row
+                if constexpr (GATED) {
+                    o0[a] = mul_pair16<F16>(o0[a], ld_at<uint16_t>(g0, at));
+                    if (two) o1[a] = mul_pair16<F16>(o1[a], ld_at<uint16_t>(g1, at));
+                }
+                st_at(row0, at, (uint16_t)o0[a]);
+                if (two) st_at(row1, at, (uint16_t)o1[a]);
             }
         }
     }
@@ -539,8 +582,8 @@ __global__ void __launch_bounds__(INV_TB<RB>, INV_WAVES<RB>) k_outer_inv(const u
 // One block = 2 CG consecutive columns of one channel, T[No][CG] in LDS; a 16-bit pair of adjacent samples
 // is one 32-bit word, so a wave moves whole 128-byte lines of u and y.
 template <bool F16, int RA, int RB, bool FULLN, bool GATED, bool EXACT>
-__global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__restrict__ u, uint32_t *__restrict__ S, int CG,
-                                                      int H, int N, int64_t M, int ko_lo, const uint16_t *__restrict__ wg,
+__global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__restrict__ u, uint32_t *__restrict__ S, int cgs,
+                                                      int H, int N, int ko_lo, const uint16_t *__restrict__ wg,
                                                       LaunchGate gate)
 {
     extern __shared__ float2 sm[];
@@ -549,45 +592,39 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that can hold input
     float2 *wno = sm;                              // W_No^j, j < No
     float2 *T = sm + No;                           // [No][CG]
+    const int CG = RB > 1 ? TILE_COLS<RA, RB> : cgs;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int h = blockIdx.y;
     const uint16_t *row0 = u + (size_t)h * N;
     const uint16_t *g0 = GATED ? wg + (size_t)h * N : nullptr;
-    const bool wide = EXACT || N % 2 == 0;         // rows start 4-byte aligned
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += TB) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     // step 1: length-RA transforms over a, times W_No^{ka b2}
+#pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
         uint32_t wd[RAIN], gt[GATED ? RAIN : 1];
+        if (EXACT || N > 1) {
 #pragma unroll
-        for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
-            wd[a] = 0;
-            if constexpr (GATED) gt[a] = 0;
-            if (wide) {
-                // a pair beyond N (n and N are even: in or out as a whole) reads sample 0 and is discarded below: the
-                // loads need no branch and go out back to back
-                const int64_t at = (EXACT || n < N) ? n : 0;
-                wd[a] = *(const uint32_t *)(row0 + at);
-                if constexpr (GATED) gt[a] = *(const uint32_t *)(g0 + at);
-            } else {
+            for (int a = 0; a < RAIN; ++a) {
+                const int n = (a * RB + b2) * MI + r0 + 2 * cg;
+                wd[a] = EXACT ? ld_at<uint32_t>(row0, 2 * n) : ld_pair(row0, n, N);
+                if constexpr (GATED) gt[a] = EXACT ? ld_at<uint32_t>(g0, 2 * n) : ld_pair(g0, n, N);
+            }
+        } else {
 #pragma unroll
-                for (int v = 0; v < 2; ++v)
-                    if (EXACT || n + v < N) {
-                        wd[a] |= (uint32_t)row0[n + v] << (16 * v);
-                        if constexpr (GATED) gt[a] |= (uint32_t)g0[n + v] << (16 * v);
-                    }
+            for (int a = 0; a < RAIN; ++a) {
+                wd[a] = (uint32_t)row0[0] << 16;
+                if constexpr (GATED) gt[a] = (uint32_t)g0[0] << 16;
             }
         }
-        if (wide && !EXACT) {
+        if constexpr (!EXACT) {
 #pragma unroll
             for (int a = 0; a < RAIN; ++a) {
                 asm volatile("" ::"v"(wd[a]));                           // keeps the loads unconditional
@@ -595,11 +632,9 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
             }
 #pragma unroll
             for (int a = 0; a < RAIN; ++a) {
-                const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
-                if (n >= N) {
-                    wd[a] = 0;
-                    if constexpr (GATED) gt[a] = 0;                      // (0 times a discarded gate must stay 0)
-                }
+                const int n = (a * RB + b2) * MI + r0 + 2 * cg;
+                wd[a] = pair_of(wd[a], n, N);
+                if constexpr (GATED) gt[a] = pair_of(gt[a], n, N);       // (0 times a discarded gate must stay 0)
             }
         }
 #pragma unroll
@@ -613,16 +648,17 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
         dft_reg<RA, false, !FULLN>(x);
         if constexpr (RB == 1) {                   // Z[ko] and its mirror row are both at hand
             const int r = r0 + 2 * cg;
+            const float rf = (float)r;
 #pragma unroll
             for (int ko = 0; ko <= No / 2; ++ko) {
                 const float2 z = x[ko], zm = x[(No - ko) % No];
                 const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
                 const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
-                const float2 ta = cmulf(xa, wm((r * ko) & Mmask, ihm)), tb = cmulf(xb, wm(((r + 1) * ko) & Mmask, ihm));
+                const float2 ta = cmulf(xa, wrev(rf * ((float)ko * im))), tb = cmulf(xb, wrev((rf + 1.f) * ((float)ko * im)));
                 if (ko < ko_lo)
                     *(uint2 *)&S[((size_t)h * No + ko) * MI + multipass_row_slot(r, multipass_quarter_rows(No))] =
-                        make_uint2((uint32_t)cv16<F16>(ta.x) | ((uint32_t)cv16<F16>(ta.y) << 16),
-                                   (uint32_t)cv16<F16>(tb.x) | ((uint32_t)cv16<F16>(tb.y) << 16));
+                        make_uint2(pack2<F16>(ta.x, ta.y),
+                                   pack2<F16>(tb.x, tb.y));
             }
             continue;
         }
@@ -632,6 +668,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
     if constexpr (RB == 1) return;
     __syncthreads();
     // step 2: length-RB transforms over b2, in place: slot ka*RB + kb then holds Z[ko], ko = ka + RA kb
+#pragma unroll 1
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         float2 x[RB];
@@ -642,24 +679,34 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
         for (int kb = 0; kb < RB; ++kb) T[(ka * RB + kb) * CG + cg] = x[kb];
     }
     __syncthreads();
-    // step 3: split the two columns, twiddle (by recurrence over kb), store the rows ko <= No/2
+    // step 3: split the two columns, twiddle (by recurrence over kb), store the rows ko <= No/2 and below ko_lo (from there on
+    // they only meet zeroed bins of a sparse filter)
+    const int end = ko_lo < No / 2 + 1 ? ko_lo : No / 2 + 1;
+#pragma unroll 1
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
-        float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
-        const float2 s0 = wm((r * RA) & Mmask, ihm), s1 = wm(((r + 1) * RA) & Mmask, ihm);
+        const float rf = (float)r;
+        float2 z[RB / 2 + 1], zm[RB / 2 + 1];                      // ko = ka + RA kb <= No/2 needs kb <= RB/2
 #pragma unroll
-        for (int kb = 0; kb < RB && kb <= RB / 2; ++kb) {          // ko = ka + RA kb <= No/2 needs kb <= RB/2
-            const int ko = ka + RA * kb;
-            if (ko <= No / 2 && ko < ko_lo) {         // (rows from ko_lo on only meet zeroed bins of a sparse filter)
-                const int km = (No - ko) % No;
-                const float2 z = T[(ka * RB + kb) * CG + cg], zm = T[((km % RA) * RB + km / RA) * CG + cg];
-                const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));      // (Z + conj Zm) / 2
-                const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));     // (Z - conj Zm) / (2i)
+        for (int kb = 0; kb <= RB / 2; ++kb) {
+            // row (No - ko) % No: kb' = RB - 1 - kb of ka' = RA - ka, or (RB - kb) % RB of ka' = 0
+            const float2 *const m = T + (ka ? ((RA - ka) * RB + RB - 1 - kb) * CG : (RB - kb) % RB * CG);
+            z[kb] = T[(ka * RB + kb) * CG + cg];
+            zm[kb] = m[cg];
+        }
+        float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
+        const float2 s0 = wrev(rf * ((float)RA * im)), s1 = wrev((rf + 1.f) * ((float)RA * im));
+        w0.x *= 0.5f, w0.y *= 0.5f, w1.x *= 0.5f, w1.y *= 0.5f;
+        uint32_t *const dst = S + (size_t)h * No * MI;
+        const uint32_t at = 4u * (uint32_t)(ka * MI + multipass_row_slot(r, multipass_quarter_rows(No)));
+#pragma unroll
+        for (int kb = 0; kb <= RB / 2; ++kb) {
+            if (ka + RA * kb < end) {
+                const float2 xa = make_float2(z[kb].x + zm[kb].x, z[kb].y - zm[kb].y);        // Z + conj Zm (halved by the twiddle)
+                const float2 xb = make_float2(z[kb].y + zm[kb].y, zm[kb].x - z[kb].x);        // (Z - conj Zm) / i
                 const float2 ta = cmulf(xa, w0), tb = cmulf(xb, w1);
-                *(uint2 *)&S[((size_t)h * No + ko) * MI + multipass_row_slot(r, multipass_quarter_rows(No))] =
-                    make_uint2((uint32_t)cv16<F16>(ta.x) | ((uint32_t)cv16<F16>(ta.y) << 16),
-                               (uint32_t)cv16<F16>(tb.x) | ((uint32_t)cv16<F16>(tb.y) << 16));
+                st_at(dst + RA * kb * MI, at, make_uint2(pack2<F16>(ta.x, ta.y), pack2<F16>(tb.x, tb.y)));
             }
             w0 = cmulf(w0, s0);
             w1 = cmulf(w1, s1);
@@ -668,8 +715,8 @@ __global__ void __launch_bounds__(TB, 4) k_outer_fwd_real(const uint16_t *__rest
 }
 
 template <bool F16, int RA, int RB, bool FULLN, bool GATED, bool EXACT>
-__global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int CG,
-                                                      int H, int N, int64_t M, int ko_lo, const uint16_t *__restrict__ vg,
+__global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int cgs,
+                                                      int H, int N, int ko_lo, const uint16_t *__restrict__ vg,
                                                       LaunchGate gate)
 {
     extern __shared__ float2 sm[];
@@ -678,60 +725,64 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that are kept
     float2 *wno = sm;
     float2 *T = sm + No;                           // [No][CG]
+    const int CG = RB > 1 ? TILE_COLS<RA, RB> : cgs;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int h = blockIdx.y;
-    const bool wide = EXACT || N % 2 == 0;
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += TB) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     constexpr float unboost = 1.0f / (float)multipass_kf_boost(F16, No);     // exact: a power of two
     // step 1: untwiddle both columns, complete the rows ko > No/2 from their mirror rows, combine the columns
     // into one complex sequence, length-RB inverse over kb, times conj(W_No^{ka b2})
+#pragma unroll 1
     for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
+        const float rf = (float)r;
+        // Row ko is held by itself or, beyond No/2, by its mirror row kr = No - ko; which of the two depends on the thread only at kb ==
+        // RB/2.  Either lies `up` or `down` beyond a row that is the same for every thread.
+        const uint32_t slot = 4u * (uint32_t)multipass_row_slot(r, multipass_quarter_rows(No));
+        const uint32_t up = 4u * (uint32_t)(ka * MI) + slot, down = 4u * (uint32_t)((RA - ka) * MI) + slot;
+        const uint32_t *const src = S + (size_t)h * No * MI;
+        auto base = [&](int kb) { return src + (kb < RB / 2 ? kb : kb > RB / 2 ? RB - 1 - kb : RB / 2 - 1) * RA * MI; };
         uint2 in[RB];
+        if (ko_lo > No / 2) {
 #pragma unroll
-        for (int kb = 0; kb < RB; ++kb) {
-            const int ko = ka + RA * kb;
-            // ko > No/2, written so that only kb == RB/2 depends on the thread
-            const bool mir = RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0));
-            const int kr = mir ? No - ko : ko;                // the row that holds it, <= No/2
+            for (int kb = 0; kb < RB; ++kb) in[kb] = ld_at<uint2>(base(kb), kb < RB / 2 ? up : down);
+        } else {
             // rows from ko_lo on: zeroed bins of a sparse filter, never written; they count as zero (the load stays
             // unconditional, of row 0 instead, see k_outer_inv)
-            in[kb] = *(const uint2 *)&S[((size_t)h * No + (kr < ko_lo ? kr : 0)) * MI + multipass_row_slot(r, multipass_quarter_rows(No))];
+            auto dead = [&](int kb) { return (kb < RB / 2 ? ka + RA * kb : RA * (RB - kb) - ka) >= ko_lo; };
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb) in[kb] = ld_at<uint2>(dead(kb) ? src : base(kb), dead(kb) ? slot : kb < RB / 2 ? up : down);
+            // (an empty statement that reads the loaded words: without it the compiler moves each load back under its
+            //  condition)
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb) asm volatile("" ::"v"(in[kb].x), "v"(in[kb].y));
+#pragma unroll
+            for (int kb = 0; kb < RB; ++kb)
+                if (dead(kb)) in[kb] = make_uint2(0, 0);
         }
-        // (an empty statement that reads the loaded words: without it the compiler moves each load back under its
-        //  condition)
 #pragma unroll
-        for (int kb = 0; kb < RB; ++kb) asm volatile("" ::"v"(in[kb].x), "v"(in[kb].y));
-#pragma unroll
-        for (int kb = 0; kb < RB; ++kb) {
-            const int ko = ka + RA * kb;
-            const bool mir = RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0));
-            const int kr = mir ? No - ko : ko;
-            if (kr >= ko_lo) in[kb] = make_uint2(0, 0);
-            if (mir) {                                        // conjugate: the imaginary part is the upper half
+        for (int kb = RB / 2; kb < RB; ++kb)
+            if (kb > RB / 2 || ka > 0) {                      // conjugate: the imaginary part is the upper half
                 in[kb].x ^= 0x80000000u;
                 in[kb].y ^= 0x80000000u;
             }
-        }
-        float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
-        const float2 s0 = wm((r * RA) & Mmask, ihm), s1 = wm(((r + 1) * RA) & Mmask, ihm);
+        float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
+        const float2 s0 = wrev(rf * ((float)RA * im)), s1 = wrev((rf + 1.f) * ((float)RA * im));
         w0.x *= unboost, w0.y *= unboost, w1.x *= unboost, w1.y *= unboost;
         float2 x[RB];
 #pragma unroll
         for (int kb = 0; kb < RB; ++kb) {
             // from the first mirrored row on the twiddle carries the extra factor conj(W_Mi^{r}) (see k_outer_inv)
-            const bool first_mirrored = RB == 1 ? ka > RA / 2 : ((kb == RB / 2 && ka > 0) || (kb == RB / 2 + 1 && ka == 0));
-            if (first_mirrored) {
-                w0 = cmulcf(w0, wm((r * No) & Mmask, ihm));
-                w1 = cmulcf(w1, wm(((r + 1) * No) & Mmask, ihm));
+            if ((kb == RB / 2 && ka > 0) || (kb == RB / 2 + 1 && ka == 0)) {
+                w0 = cmulcf(w0, wrev(rf * (1.0f / (float)MI)));
+                w1 = cmulcf(w1, wrev((rf + 1.f) * (1.0f / (float)MI)));
             }
             const float2 ua = cmulcf(unpack2<F16>(in[kb].x), w0), ub = cmulcf(unpack2<F16>(in[kb].y), w1);
             x[kb] = make_float2(ua.x - ub.y, ua.y + ub.x);               // U_c + i U_{c+1}
@@ -746,18 +797,20 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
     // step 2: length-RA inverse over ka; real part -> column c, imaginary part -> column c+1
     uint16_t *row0 = y + (size_t)h * N;
     const uint16_t *g0 = GATED ? vg + (size_t)h * N : nullptr;
+#pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
         if constexpr (RB == 1) {                   // every row <= No/2 is read once and serves its mirror row too
             const int r = r0 + 2 * cg;
+            const float rf = (float)r;
             uint2 in[No / 2 + 1];
 #pragma unroll
             for (int ko = 0; ko <= No / 2; ++ko)
                 in[ko] = *(const uint2 *)&S[((size_t)h * No + (ko < ko_lo ? ko : 0)) * MI + multipass_row_slot(r, multipass_quarter_rows(No))];
 #pragma unroll
             for (int ko = 0; ko <= No / 2; ++ko) asm volatile("" ::"v"(in[ko].x), "v"(in[ko].y));
-            const float2 m0 = wm((r * No) & Mmask, ihm), m1 = wm(((r + 1) * No) & Mmask, ihm);
+            const float2 m0 = wrev(rf * (1.0f / (float)MI)), m1 = wrev((rf + 1.f) * (1.0f / (float)MI));
 #pragma unroll
             for (int ka = 0; ka < RA; ++ka) {
                 const bool mir = ka > RA / 2;
@@ -767,7 +820,7 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
                     v.x ^= 0x80000000u;
                     v.y ^= 0x80000000u;
                 }
-                float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
+                float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
                 w0.x *= unboost, w0.y *= unboost, w1.x *= unboost, w1.y *= unboost;
                 if (mir) {
                     w0 = cmulcf(w0, m0);
@@ -783,21 +836,14 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
         dft_reg<RA, true>(x);
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
-            uint32_t o = (uint32_t)cv16<F16>(x[a].x) | ((uint32_t)cv16<F16>(x[a].y) << 16);
-            if (wide) {
-                if (EXACT || n < N) {
-                    if constexpr (GATED) o = mul_pair16<F16>(o, *(const uint32_t *)(g0 + n));
-                    *(uint32_t *)(row0 + n) = o;
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < 2; ++v)
-                    if (EXACT || n + v < N) {
-                        uint32_t a0 = (o >> (16 * v)) & 0xffffu;
-                        if constexpr (GATED) a0 = mul_pair16<F16>(a0, g0[n + v]) & 0xffffu;
-                        row0[n + v] = (uint16_t)a0;
-                    }
+            const int n = (a * RB + b2) * MI + r0 + 2 * cg;
+            uint32_t o = pack2<F16>(x[a].x, x[a].y);
+            if (EXACT || n + 1 < N) {
+                if constexpr (GATED) o = mul_pair16<F16>(o, ld_at<Word>(g0, 2 * n).w);
+                st_at(row0, 2 * n, Word{o});
+            } else if (n < N) {                                           // the last sample of an odd row
+                if constexpr (GATED) o = mul_pair16<F16>(o, ld_at<uint16_t>(g0, 2 * n));
+                st_at(row0, 2 * n, (uint16_t)o);
             }
         }
     }
@@ -812,14 +858,15 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
 // The filter gradient of these plans (long_fft.hip) transforms its rows of u and dy the same way: IN = 0: fp32
 // rows, 1: fp16, 2: bf16; row i of the launch is row rows.at(i) of its source, Nk elements each.
 template <int IN, int RA, int RB, bool FULLN>
-__global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, float2 *__restrict__ T2, int CG,
-                                                         int64_t Nk, int64_t M, bool wide)
+__global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, float2 *__restrict__ T2, int cgs,
+                                                         int64_t Nk, bool wide)
 {
     extern __shared__ float2 sm[];
     constexpr int No = RA * RB, NR = No / 2 + 1;
     constexpr int RAIN = FULLN ? RA : RA / 2;      // outer rows that can hold taps
     float2 *wno = sm;                              // W_No^j, j < No
     float2 *T = sm + No;                           // [No][CG]
+    const int CG = RB > 1 ? TILE_COLS<RA, RB> : cgs;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
@@ -831,12 +878,12 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
     const float *row0 = (const float *)src + first;                // IN == 0
     const uint16_t *row16 = (const uint16_t *)src + first;         // IN != 0
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += TB) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     // step 1: length-RA transforms over a, times W_No^{ka b2}; (column c, column c+1) = (re, im)
+#pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
@@ -844,41 +891,40 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
         for (int a = 0; a < RA; ++a) x[a] = make_float2(0.f, 0.f);
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
+            const int n = (a * RB + b2) * MI + r0 + 2 * cg;
             if constexpr (IN == 0) {
                 if (wide) {                        // Nk even, rows 8-byte aligned: a pair is inside or outside as a whole
-                    x[a] = *(const float2 *)(row0 + (n < Nk ? n : 0));
+                    x[a] = ld_at<float2>(row0, n < Nk ? 4 * n : 0);
                 } else {
                     x[a].x = row0[n < Nk ? n : 0];
                     x[a].y = row0[n + 1 < Nk ? n + 1 : 0];
                 }
             } else {
                 uint32_t wd;
-                if (wide)                          // Nk even, rows 4-byte aligned: one word holds the pair
-                    wd = *(const uint32_t *)(row16 + (n < Nk ? n : 0));
-                else
-                    wd = (uint32_t)row16[n < Nk ? n : 0] | ((uint32_t)row16[n + 1 < Nk ? n + 1 : 0] << 16);
-                x[a] = unpack2<IN == 1>(wd);
+                if (wide) wd = ld_pair(row16, n, (int)Nk);                // two samples or more
+                else wd = (uint32_t)row16[0] << 16;
+                x[a] = unpack2<IN == 1>(pair_of(wd, n, (int)Nk));
             }
         }
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) asm volatile("" ::"v"(x[a].x), "v"(x[a].y));      // keeps the loads unconditional
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
+            const int n = (a * RB + b2) * MI + r0 + 2 * cg;
             if (n >= Nk) x[a].x = 0.f;
             if (n + 1 >= Nk) x[a].y = 0.f;
         }
         dft_reg<RA, false, !FULLN>(x);
         if constexpr (RB == 1) {                   // Z[ko] and its mirror row are both at hand
             const int r = r0 + 2 * cg;
+            const float rf = (float)r;
 #pragma unroll
             for (int ko = 0; ko <= No / 2; ++ko) {
                 const float2 z = x[ko], zm = x[(No - ko) % No];
                 const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
                 const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
-                const float2 ta = cmulf(xa, wm((r * ko) & Mmask, ihm)), tb = cmulf(xb, wm(((r + 1) * ko) & Mmask, ihm));
-                *(float4 *)&T2[((size_t)h * NR + ko) * MI + r] = make_float4(ta.x, ta.y, tb.x, tb.y);
+                const float2 ta = cmulf(xa, wrev(rf * ((float)ko * im))), tb = cmulf(xb, wrev((rf + 1.f) * ((float)ko * im)));
+                st_at(T2 + ((size_t)h * NR + ko) * MI, 8u * (uint32_t)r, make_float4(ta.x, ta.y, tb.x, tb.y));
             }
             continue;
         }
@@ -888,6 +934,7 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
     if constexpr (RB == 1) return;
     __syncthreads();
     // step 2: length-RB transforms over b2, in place: slot ka*RB + kb then holds Z[ko], ko = ka + RA kb
+#pragma unroll 1
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         float2 x[RB];
@@ -899,21 +946,31 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
     }
     __syncthreads();
     // step 3: split the two columns, twiddle (by recurrence over kb), store the rows ko <= No/2
+#pragma unroll 1
     for (int e = tid; e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
-        float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
-        const float2 s0 = wm((r * RA) & Mmask, ihm), s1 = wm(((r + 1) * RA) & Mmask, ihm);
+        const float rf = (float)r;
+        float2 z[RB / 2 + 1], zm[RB / 2 + 1];                      // ko = ka + RA kb <= No/2 needs kb <= RB/2
 #pragma unroll
-        for (int kb = 0; kb < RB && kb <= RB / 2; ++kb) {          // ko = ka + RA kb <= No/2 needs kb <= RB/2
-            const int ko = ka + RA * kb;
-            if (ko <= No / 2) {
-                const int km = (No - ko) % No;
-                const float2 z = T[(ka * RB + kb) * CG + cg], zm = T[((km % RA) * RB + km / RA) * CG + cg];
-                const float2 xa = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));      // (Z + conj Zm) / 2
-                const float2 xb = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));     // (Z - conj Zm) / (2i)
+        for (int kb = 0; kb <= RB / 2; ++kb) {
+            // row (No - ko) % No, see k_outer_fwd_real
+            const float2 *const m = T + (ka ? ((RA - ka) * RB + RB - 1 - kb) * CG : (RB - kb) % RB * CG);
+            z[kb] = T[(ka * RB + kb) * CG + cg];
+            zm[kb] = m[cg];
+        }
+        float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
+        const float2 s0 = wrev(rf * ((float)RA * im)), s1 = wrev((rf + 1.f) * ((float)RA * im));
+        w0.x *= 0.5f, w0.y *= 0.5f, w1.x *= 0.5f, w1.y *= 0.5f;
+        float2 *const dst = T2 + (size_t)h * NR * MI;
+        const uint32_t at = 8u * (uint32_t)(ka * MI + r);
+#pragma unroll
+        for (int kb = 0; kb <= RB / 2; ++kb) {
+            if (kb < RB / 2 || ka == 0) {
+                const float2 xa = make_float2(z[kb].x + zm[kb].x, z[kb].y - zm[kb].y);        // Z + conj Zm (halved by the twiddle)
+                const float2 xb = make_float2(z[kb].y + zm[kb].y, zm[kb].x - z[kb].x);        // (Z - conj Zm) / i
                 const float2 ta = cmulf(xa, w0), tb = cmulf(xb, w1);
-                *(float4 *)&T2[((size_t)h * NR + ko) * MI + r] = make_float4(ta.x, ta.y, tb.x, tb.y);
+                st_at(dst + RA * kb * MI, at, make_float4(ta.x, ta.y, tb.x, tb.y));
             }
             w0 = cmulf(w0, s0);
             w1 = cmulf(w1, s1);
@@ -927,8 +984,8 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
 // ko > No/2 are the mirror images described at k_outer_inv.  dk[h][n] = scale * (the inverse outer transform),
 // n < Nk.
 template <int RA, int RB, bool FULLN>
-__global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__restrict__ T2, float *__restrict__ dk, int CG,
-                                                         int64_t Nk, int64_t M, float scale)
+__global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__restrict__ T2, float *__restrict__ dk, int cgs,
+                                                         int64_t Nk, float scale)
 {
     extern __shared__ float2 sm[];
     constexpr int No = RA * RB, NR = No / 2 + 1;
@@ -936,45 +993,47 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
     constexpr int KBC = RB < 8 ? RB : 8;           // rows loaded at a time (16 bytes each per thread)
     float2 *wno = sm;
     float2 *T = sm + No;                           // [No][CG]
+    const int CG = RB > 1 ? TILE_COLS<RA, RB> : cgs;
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * 2 * CG;
     const int lgCG = 31 - __builtin_clz(CG);       // CG is a power of two
     const int64_t h = blockIdx.y;
     if constexpr (RB > 1) {
-        for (int j = tid; j < No; j += TB) wno[j] = wm(j, 2.0f / (float)No);
+        for (int j = tid; j < No; j += TB) wno[j] = wrev((float)j * (1.0f / (float)No));
         __syncthreads();
     }
-    const float ihm = 2.0f / (float)M;
-    const int Mmask = (int)M - 1;                  // M is a power of two, at most 2^22, and so is every r * ko
+    constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     // step 1: untwiddle both columns, complete the rows ko > No/2 from their mirror rows, combine the columns
     // into one complex sequence, length-RB inverse over kb, times conj(W_No^{ka b2})
+#pragma unroll 1
     for (int e = tid; RB > 1 && e < RA * CG; e += TB) {
         const int cg = e & (CG - 1), ka = e >> lgCG;
         const int r = r0 + 2 * cg;
-        float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
-        const float2 s0 = wm((r * RA) & Mmask, ihm), s1 = wm(((r + 1) * RA) & Mmask, ihm);
+        const float rf = (float)r;
+        float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
+        const float2 s0 = wrev(rf * ((float)RA * im)), s1 = wrev((rf + 1.f) * ((float)RA * im));
         w0.x *= scale, w0.y *= scale, w1.x *= scale, w1.y *= scale;
+        // (see k_outer_inv_real)
+        const uint32_t up = 8u * (uint32_t)(ka * MI + r), down = 8u * (uint32_t)((RA - ka) * MI + r);
+        const float2 *const src = T2 + (size_t)h * NR * MI;
+        auto base = [&](int kb) { return src + (kb < RB / 2 ? kb : kb > RB / 2 ? RB - 1 - kb : RB / 2 - 1) * RA * MI; };
         float2 x[RB];
 #pragma unroll
         for (int kb0 = 0; kb0 < RB; kb0 += KBC) {
             float4 in[KBC];
 #pragma unroll
             for (int kk = 0; kk < KBC; ++kk) {
-                const int kb = kb0 + kk, ko = ka + RA * kb;
-                // ko > No/2, written so that only kb == RB/2 depends on the thread
-                const bool mir = RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0));
-                const int kr = mir ? No - ko : ko;            // the row that holds it, <= No/2
-                in[kk] = *(const float4 *)&T2[((size_t)h * NR + kr) * MI + r];
+                const int kb = kb0 + kk;
+                in[kk] = ld_at<float4>(base(kb), kb < RB / 2 ? up : down);
             }
 #pragma unroll
             for (int kk = 0; kk < KBC; ++kk) {
                 const int kb = kb0 + kk;
-                const bool mir = RB == 1 ? ka > RA / 2 : (kb > RB / 2 || (kb == RB / 2 && ka > 0));
+                const bool mir = kb > RB / 2 || (kb == RB / 2 && ka > 0);
                 // from the first mirrored row on the twiddle carries the extra factor conj(W_Mi^{r}) (see k_outer_inv)
-                const bool first_mirrored = RB == 1 ? ka > RA / 2 : ((kb == RB / 2 && ka > 0) || (kb == RB / 2 + 1 && ka == 0));
-                if (first_mirrored) {
-                    w0 = cmulcf(w0, wm((r * No) & Mmask, ihm));
-                    w1 = cmulcf(w1, wm(((r + 1) * No) & Mmask, ihm));
+                if ((kb == RB / 2 && ka > 0) || (kb == RB / 2 + 1 && ka == 0)) {
+                    w0 = cmulcf(w0, wrev(rf * (1.0f / (float)MI)));
+                    w1 = cmulcf(w1, wrev((rf + 1.f) * (1.0f / (float)MI)));
                 }
                 const float2 sa = make_float2(in[kk].x, mir ? -in[kk].y : in[kk].y);
                 const float2 sb = make_float2(in[kk].z, mir ? -in[kk].w : in[kk].w);
@@ -992,20 +1051,22 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
     // step 2: length-RA inverse over ka; real part -> column c, imaginary part -> column c+1
     float *row0 = dk + h * Nk;
     const bool wide = Nk % 2 == 0 && ((uintptr_t)dk & 7) == 0;
+#pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
         float2 x[RA];
         if constexpr (RB == 1) {                   // every row is read once and serves its mirror row too
             const int r = r0 + 2 * cg;
+            const float rf = (float)r;
             float4 in[NR];
 #pragma unroll
-            for (int ko = 0; ko < NR; ++ko) in[ko] = *(const float4 *)&T2[((size_t)h * NR + ko) * MI + r];
-            const float2 m0 = wm((r * No) & Mmask, ihm), m1 = wm(((r + 1) * No) & Mmask, ihm);
+            for (int ko = 0; ko < NR; ++ko) in[ko] = ld_at<float4>(T2 + ((size_t)h * NR + ko) * MI, 8u * (uint32_t)r);
+            const float2 m0 = wrev(rf * (1.0f / (float)MI)), m1 = wrev((rf + 1.f) * (1.0f / (float)MI));
 #pragma unroll
             for (int ka = 0; ka < RA; ++ka) {
                 const bool mir = ka > RA / 2;
                 const float4 v = in[mir ? No - ka : ka];
-                float2 w0 = wm((r * ka) & Mmask, ihm), w1 = wm(((r + 1) * ka) & Mmask, ihm);
+                float2 w0 = wrev(rf * ((float)ka * im)), w1 = wrev((rf + 1.f) * ((float)ka * im));
                 w0.x *= scale, w0.y *= scale, w1.x *= scale, w1.y *= scale;
                 if (mir) {
                     w0 = cmulcf(w0, m0);
@@ -1021,9 +1082,9 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
         dft_reg<RA, true>(x);
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
-            const int64_t n = (int64_t)(a * RB + b2) * MI + r0 + 2 * cg;
+            const int n = (a * RB + b2) * MI + r0 + 2 * cg;
             if (wide) {
-                if (n < Nk) *(float2 *)(row0 + n) = x[a];
+                if (n < Nk) st_at(row0, 4 * n, x[a]);
             } else {
                 if (n < Nk) row0[n] = x[a].x;
                 if (n + 1 < Nk) row0[n + 1] = x[a].y;
@@ -1040,10 +1101,10 @@ int launch_dk_outer_inv(const OuterGeo &g, const float2 *T2, float *dk, int64_t 
     const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
     if (Nk > M / 2) {
         FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, true>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, M, scale);
+        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, true>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, scale);
     } else {
         FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, false>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, M, scale);
+        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, false>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, scale);
     }
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
@@ -1054,13 +1115,13 @@ int launch_filter_outer_in(const OuterGeo &g, const OuterRows &rows, float2 *T2,
 {
     const size_t lds = g.lds();
     const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
-    const bool wide = Nk % 2 == 0 && (((uintptr_t)rows.src | (uintptr_t)rows.src2) & (IN == 0 ? 7 : 3)) == 0;
+    const bool wide = IN == 0 ? Nk % 2 == 0 && (((uintptr_t)rows.src | (uintptr_t)rows.src2) & 7) == 0 : Nk > 1;
     if (Nk > M / 2) {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, wide);
     } else {
         FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, M, wide);
+        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, wide);
     }
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
@@ -1110,28 +1171,27 @@ OuterGeo outer_geo(int64_t M, int64_t rows = 0)
 }
 
 template <bool F16, int RA, int RB, bool FULLN, bool GATED, bool EXACT>
-int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, void *dst, int B, int H, int N, int64_t M,
+int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, void *dst, int B, int H, int N,
                    hipStream_t s, int ko_lo, int ko_hi, int mirror_from, const void *gate)
 {
     // two columns per thread while the registers allow and while that still leaves an entry for every thread
     // (at No = 256 a block has 32 columns: 16 x 32 / 2 entries would keep half of its 512 threads idle)
-    constexpr int CTC = MI / (RA * RB) < 32 ? 32 : MI / (RA * RB);
-    constexpr int CV = (RB <= 16 && RA * CTC / 2 >= TB) ? 2 : 1;
+    constexpr int CV = (RB <= 16 && RA * TILE_COLS<RA, RB> / 2 >= TB) ? 2 : 1;
     const size_t lds = g.lds();
-    const int ct_inv = RB == 1 ? g.CT / 2 : g.CT;                 // columns of a block of INV_TB threads
+    const int ct_inv = g.CT / (TB / INV_TB<RA, RB>);              // columns of a block of INV_TB threads
     const dim3 grid_inv(grid.x * (unsigned)(g.CT / ct_inv), grid.y);
     FC_TRY(raise_dynamic_lds((const void *)k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>, 160 * 1024));
     FC_TRY(raise_dynamic_lds((const void *)k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>, 160 * 1024));
     if (!inverse)
         hipLaunchKernelGGL((k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint16_t *)src,
-                           (uint32_t *)dst, g.CT, B, H, N, M, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
+                           (uint32_t *)dst, g.CT, B, H, N, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
     else if (mirror_from < g.No)
-        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>), grid_inv, dim3(INV_TB<RB>), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, ct_inv, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>), grid_inv, dim3(INV_TB<RA, RB>), lds, s, (const uint32_t *)src,
+                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
     else
-        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>), grid_inv, dim3(INV_TB<RB>), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, ct_inv, B, H, N, M, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+        hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>), grid_inv, dim3(INV_TB<RA, RB>), lds, s, (const uint32_t *)src,
+                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -1143,7 +1203,7 @@ int launch_outer(bool inverse, const OuterGeo &g, dim3 grid, const void *src, vo
                  hipStream_t s, int ko_lo, int ko_hi, int mirror_from, const void *gate)
 {
 #define FFTCONV_OUTER(FULLN, GATED, EXACT) \
-    launch_outer_t<F16, RA, RB, FULLN, GATED, EXACT>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate)
+    launch_outer_t<F16, RA, RB, FULLN, GATED, EXACT>(inverse, g, grid, src, dst, B, H, N, s, ko_lo, ko_hi, mirror_from, gate)
     if constexpr (RA >= 2) {
         if ((int64_t)N <= M / 2) {
             if (gate) return FFTCONV_OUTER(false, true, false);
@@ -1188,11 +1248,11 @@ int launch_outer_real(bool inverse, const OuterGeo &g, const void *src, void *ds
         if (!inverse) {                                                                                                     \
             FC_TRY(raise_dynamic_lds((const void *)k_outer_fwd_real<F16, RA, RB, FULLN, GATED, EXACT>, 160 * 1024));               \
             hipLaunchKernelGGL((k_outer_fwd_real<F16, RA, RB, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint16_t *)src, \
-                               (uint32_t *)dst, g.pairs(), H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
+                               (uint32_t *)dst, g.pairs(), H, N, ko_lo, (const uint16_t *)gate, launch_gate());               \
         } else {                                                                                                            \
             FC_TRY(raise_dynamic_lds((const void *)k_outer_inv_real<F16, RA, RB, FULLN, GATED, EXACT>, 160 * 1024));               \
             hipLaunchKernelGGL((k_outer_inv_real<F16, RA, RB, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint32_t *)src, \
-                               (uint16_t *)dst, g.pairs(), H, N, M, ko_lo, (const uint16_t *)gate, launch_gate());               \
+                               (uint16_t *)dst, g.pairs(), H, N, ko_lo, (const uint16_t *)gate, launch_gate());               \
         }                                                                                                                   \
     } while (0)
     // exact: N is even and fills its half (or the whole transform): no range checks (ungated calls only)
