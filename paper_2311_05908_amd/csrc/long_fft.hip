@@ -76,7 +76,8 @@ struct LongTw {
 // channel j % H of batch row 2 (j / H), j = first + i (its partner lies H rows further, if the tensor has so many)
 struct LongRows {
     int64_t first, H, rows;                    // H = 0: not in pairs
-    __device__ __forceinline__ int64_t at(int64_t i) const { return H ? (first + i) / H * H + first + i : first + i; }
+    // (rows of 32 KB and more in memory are fewer than 2^32: a 64-bit division, in every thread, cost 2 % of a pass)
+    __device__ __forceinline__ int64_t at(int64_t i) const { return H ? (int64_t)((uint32_t)(first + i) / (uint32_t)H) * H + first + i : first + i; }
     __device__ __forceinline__ bool partner(int64_t i) const { return at(i) + H < rows; }
 };
 
@@ -146,7 +147,9 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
                                                      bool reversed, bool half_rows, LongRows rows)
 {
     extern __shared__ float2 XL[];
-    const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(row) * len;
+    const int M = A * LB, N = (int)len;
+    const int64_t row = blockIdx.y, first = rows.at(row) * len;
+    const In *const re = src_re + first, *const im = src_im + first;
     const int col0 = blockIdx.x * C;
     const int lgC = __ffs(C) - 1;
     const bool two = src_im && rows.partner(row);
@@ -156,20 +159,19 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
         const int i = threadIdx.x + j * LT;
-        int64_t n = (int64_t)(i >> lgC) * LB + col0 + (i & (C - 1));
+        int n = (i >> lgC) * LB + col0 + (i & (C - 1));
         if (reversed && n != 0) n = M - n;
-        const int64_t at = first + (n < len ? n : 0);
-        vr[j] = ld_real(src_re, at);
-        vi[j] = two ? ld_real(src_im, at) : 0.f;
+        vr[j] = ld_real(re, n < N ? n : 0);
+        vi[j] = two ? ld_real(im, n < N ? n : 0) : 0.f;
     }
 #pragma unroll
     for (int j = 0; j < LPT; ++j) asm volatile("" ::"v"(vr[j]), "v"(vi[j]));      // keeps the loads unconditional
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
         const int i = threadIdx.x + j * LT;
-        int64_t n = (int64_t)(i >> lgC) * LB + col0 + (i & (C - 1));
+        int n = (i >> lgC) * LB + col0 + (i & (C - 1));
         if (reversed && n != 0) n = M - n;
-        XL[lds_slot(i)] = n < len ? make_float2(vr[j], vi[j]) : make_float2(0.f, 0.f);
+        XL[lds_slot(i)] = n < N ? make_float2(vr[j], vi[j]) : make_float2(0.f, 0.f);
     }
     __syncthreads();
     int Sp = A, R = 1;
@@ -185,7 +187,7 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
         const int i = threadIdx.x + j * LT;
         const int ap = i >> lgC;                              // position of the block; its digit: lds_freq()
         if (!half_rows || 2 * lds_freq(ap, flA, A) <= A)
-            tmp[row * M + (int64_t)ap * LB + col0 + (i & (C - 1))] = XL[lds_slot(i)];
+            (tmp + row * M)[ap * LB + col0 + (i & (C - 1))] = XL[lds_slot(i)];
     }
 }
 
@@ -488,6 +490,7 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
 {
     extern __shared__ float2 XL[];
     const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(row) * N;
+    IO *const re = y_re + first, *const im = y_im + first;
     const int col0 = blockIdx.x * C;
     if (col0 >= N) return;
     const bool two = y_im && rows.partner(row);
@@ -503,11 +506,11 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
     }
     for (int i = threadIdx.x; i < LB; i += LT) {
         const int a = i >> (__ffs(C) - 1), c = i & (C - 1);
-        const int64_t n = (int64_t)a * LB + col0 + c;
+        const int n = a * LB + col0 + c;
         if (n < N) {
             const float2 v = XL[lds_slot(i)];
-            st_real(y_re, first + n, v.x);
-            if (two) st_real(y_im, first + n, v.y);
+            st_real(re, n, v.x);
+            if (two) st_real(im, n, v.y);
         }
     }
 }
