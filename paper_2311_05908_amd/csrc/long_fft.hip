@@ -262,60 +262,66 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
         const int km = mirror ? A - ko : ko;
         const int64_t row = (h * A + (KF == 2 ? lds_pos(ko, flA, A) : ko)) * LB;
         const int64_t row_m = (h * A + (KF == 2 ? lds_pos(km, flA, A) : km)) * LB;
-        // weights of the bins of register p in this row and in the mirror row
-        auto weight = [&](int p) { return keep ? lds_mask_weight(keep, n_blocks, ko + A * G::freq(tid, p), M) * scale : scale; };
-        auto weight_m = [&](int p) {
-            return keep ? lds_mask_weight(keep, n_blocks, km + A * (LB - 1 - G::freq(tid, p)), M) * scale : scale;
-        };
-        if constexpr (KF == 2) {
-            // pairs of registers, as they lie in memory; bin 8191 - f' belongs to the thread and the register with all digits
-            // complemented, T - 1 - tid and P - 1 - p
-            float4 *const o = (float4 *)kf + row / 2 + tid, *const om = (float4 *)kf + row_m / 2 + (G::T - 1 - tid);
-#pragma unroll
-            for (int q = 0; q < G::P / 2; ++q) {
-                const float s0 = weight(2 * q), s1 = weight(2 * q + 1);
-                o[q * G::T] = make_float4(x[2 * q].x * s0, sgn * x[2 * q].y * s0, x[2 * q + 1].x * s1, sgn * x[2 * q + 1].y * s1);
-            }
-            if (mirror) {
+        // (one branch on the mask, not one for every bin)
+        auto emit = [&](auto masked) {
+            constexpr bool MASKED = decltype(masked)::value;
+            // weights of the bins of register p in this row and in the mirror row
+            auto weight = [&](int p) { return MASKED ? lds_mask_weight(keep, n_blocks, ko + A * G::freq(tid, p), M) * scale : scale; };
+            auto weight_m = [&](int p) {
+                return MASKED ? lds_mask_weight(keep, n_blocks, km + A * (LB - 1 - G::freq(tid, p)), M) * scale : scale;
+            };
+            if constexpr (KF == 2) {
+                // pairs of registers, as they lie in memory; bin 8191 - f' belongs to the thread and the register with all digits
+                // complemented, T - 1 - tid and P - 1 - p
+                float4 *const o = (float4 *)kf + row / 2 + tid, *const om = (float4 *)kf + row_m / 2 + (G::T - 1 - tid);
 #pragma unroll
                 for (int q = 0; q < G::P / 2; ++q) {
-                    const int a = G::P - 1 - 2 * q, b = a - 1;
-                    const float s0 = weight_m(a), s1 = weight_m(b);
-                    om[q * G::T] = make_float4(x[a].x * s0, -sgn * x[a].y * s0, x[b].x * s1, -sgn * x[b].y * s1);
+                    const float s0 = weight(2 * q), s1 = weight(2 * q + 1);
+                    o[q * G::T] = make_float4(x[2 * q].x * s0, sgn * x[2 * q].y * s0, x[2 * q + 1].x * s1, sgn * x[2 * q + 1].y * s1);
                 }
-            }
-        } else {
-            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
-            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
-            auto pack = [](float re, float im) { return KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im); };
-            const int lane = tid & 63, k1w = tid / 64 * 4;
-            uint32_t *const o = (uint32_t *)kf + row + lane, *const om = (uint32_t *)kf + row_m + (lane & 48) + 15 - (lane & 15);
+                if (mirror) {
 #pragma unroll
-            for (int ir = 0; ir < 8; ++ir) {
-                const int i = ir / 4, r = ir % 4;
-                uint32_t v[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int p = 16 * i + k3_at_index(4 * c + r, 16);
-                    const float sc = weight(p);
-                    v[c] = pack(x[p].x * sc, sgn * x[p].y * sc);
+                    for (int q = 0; q < G::P / 2; ++q) {
+                        const int a = G::P - 1 - 2 * q, b = a - 1;
+                        const float s0 = weight_m(a), s1 = weight_m(b);
+                        om[q * G::T] = make_float4(x[a].x * s0, -sgn * x[a].y * s0, x[b].x * s1, -sgn * x[b].y * s1);
+                    }
                 }
-                rf::transpose_groups(v);
+            } else {
+                // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
+                // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
+                auto pack = [](float re, float im) { return KF == 1 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im); };
+                const int lane = tid & 63, k1w = tid / 64 * 4;
+                uint32_t *const o = (uint32_t *)kf + row + lane, *const om = (uint32_t *)kf + row_m + (lane & 48) + 15 - (lane & 15);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64] = v[j];
-                if (mirror) {                                     // bin 8191 - f': every digit is complemented
+                for (int ir = 0; ir < 8; ++ir) {
+                    const int i = ir / 4, r = ir % 4;
+                    uint32_t v[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const int p = 16 * i + 15 - k3_at_index(4 * c + r, 16);
-                        const float scm = weight_m(p);
-                        v[c] = pack(x[p].x * scm, -sgn * x[p].y * scm);
+                        const int p = 16 * i + k3_at_index(4 * c + r, 16);
+                        const float sc = weight(p);
+                        v[c] = pack(x[p].x * sc, sgn * x[p].y * sc);
                     }
                     rf::transpose_groups(v);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) om[((31 - (k1w + j + 16 * i)) * 4 + r) * 64] = v[j];
+                    for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64] = v[j];
+                    if (mirror) {                                     // bin 8191 - f': every digit is complemented
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const int p = 16 * i + 15 - k3_at_index(4 * c + r, 16);
+                            const float scm = weight_m(p);
+                            v[c] = pack(x[p].x * scm, -sgn * x[p].y * scm);
+                        }
+                        rf::transpose_groups(v);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) om[((31 - (k1w + j + 16 * i)) * 4 + r) * 64] = v[j];
+                    }
                 }
             }
-        }
+        };
+        if (keep) emit(std::true_type());
+        else emit(std::false_type());
     }
 }
 

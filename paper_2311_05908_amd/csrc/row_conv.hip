@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     const uint32_t *kr = kf + (int64_t)h * M;
     rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) kv[p] = kr[kernel_slot<M>(G::freq(tid, p))];
+        for (int p = 0; p < G::P; ++p) kv[p] = kr[rf::slot_of<G>(tid, p)];
     });
 #pragma unroll
     for (int p = 0; p < G::P; ++p) x[p] = rf::mul(x[p], rf::unpack<IO>(kv[p]));

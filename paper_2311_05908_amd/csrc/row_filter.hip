@@ -11,7 +11,7 @@
 // The gradient of plans below 8192 sums a spectrum for each of G = 8192 / fft_size groups (see build_tables() in fused3.hip): slot
 // k1 of group g is g (32 / G) + k1'.  Up to 1024 points a row is part of one wave and most of the work is adding them up: there a
 // workgroup takes one channel, and all of it moves the 64 KB, through an image of one group in LDS.
-// Bound by the bytes.  Tail of the gradient, 768 channels of fft 8192: 46 -> 22 us (with every factor a trip through LDS and gathered
+// Bound by the bytes.  Tail of the gradient, 768 channels of fft 8192: 46 -> 19 us (with every factor a trip through LDS and gathered
 // twiddles before).
 #include "fftconv_internal.h"
 #include "lds_fft.h"
@@ -59,29 +59,35 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     tw1.load(tab, tid);
     rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
     if ((int)blockIdx.x * RW + row >= H) return;
-    auto constant = [&](int p) {
-        const float sc = keep ? lds_mask_weight(keep, n_blocks, G::freq(tid, p), M) / M : 1.f / M;
-        const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
-        return F16 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
-    };
-    if constexpr (M == SLOTS) {
-        // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
-        // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
-        const int k1w = tid / 64 * 4;
+    // (one branch on the mask, not one for every bin)
+    auto emit = [&](auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        auto constant = [&](int p) {
+            const float sc = MASKED ? lds_mask_weight(keep, n_blocks, G::freq(tid, p), M) / M : 1.f / M;
+            const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
+            return F16 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
+        };
+        if constexpr (M == SLOTS) {
+            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
+            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
+            const int k1w = tid / 64 * 4;
 #pragma unroll
-        for (int ir = 0; ir < 8; ++ir) {
-            const int i = ir / 4, r = ir % 4;
-            uint32_t a[4];
+            for (int ir = 0; ir < 8; ++ir) {
+                const int i = ir / 4, r = ir % 4;
+                uint32_t a[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] = constant(16 * i + k3_at_index(4 * c + r, 16));
-            rf::transpose_groups(a);
+                for (int c = 0; c < 4; ++c) a[c] = constant(16 * i + k3_at_index(4 * c + r, 16));
+                rf::transpose_groups(a);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = a[j];
+                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = a[j];
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) o[rf::slot_of<G>(tid, p)] = constant(p);
         }
-    } else {
-#pragma unroll
-        for (int p = 0; p < G::P; ++p) o[kernel_slot<M>(G::freq(tid, p))] = constant(p);
-    }
+    };
+    if (keep) emit(std::true_type());
+    else emit(std::false_type());
 }
 
 // dk[h][n] = Re(inverse transform)[n] / M, n < Nk, of the sum of the groups' spectra, and of the runs' (dkf[run][h]), added one
@@ -126,14 +132,14 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
         __syncthreads();
         if (tid >= G::T) return;
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = image[kernel_slot<M>(G::freq(tid, p))];
+        for (int p = 0; p < G::P; ++p) x[p] = image[rf::slot_of<G>(tid, p)];
     } else {
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = in[kernel_slot<M>(G::freq(tid, p))];
+        for (int p = 0; p < G::P; ++p) x[p] = in[rf::slot_of<G>(tid, p)];
         auto add = [&](const float2 *spec) {
             float2 v[G::P];
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) v[p] = spec[kernel_slot<M>(G::freq(tid, p))];
+            for (int p = 0; p < G::P; ++p) v[p] = spec[rf::slot_of<G>(tid, p)];
 #pragma unroll
             for (int p = 0; p < G::P; ++p) {
                 x[p].x += v[p].x;

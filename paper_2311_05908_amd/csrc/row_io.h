@@ -169,6 +169,15 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&v)[4])
     }
 }
 
+// kernel_slot() of the frequency in register p of thread tid.  Every digit of a slot but that of 2048 points depends on the thread alone or
+// the register alone, so the slots of a thread lie a constant apart: one address and immediates, where digit by digit they were 1700 of the 3000 vector
+// instructions of the gradient's tail at 8192 points (k_row_dk_finish, 768 channels 25.1 -> 19.8 us; the few-row kernel, 1 x 768 x 2048 gated 13.5 -> 10.5).
+template <typename G> __device__ __forceinline__ int slot_of(int tid, int p)
+{
+    if constexpr (G::M == 2048) return kernel_slot<2048>(G::freq(tid, p));
+    else return kernel_slot<G::M>(G::freq(tid, 0)) + (kernel_slot<G::M>(G::freq(0, p)) - kernel_slot<G::M>(G::freq(0, 0)));
+}
+
 // The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
 // that or 32768.
 template <typename G> inline const float2 *row_table(const fftconv_plan *p)
