@@ -216,10 +216,10 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 // 4096; fft 512: 8, 12, 16, 20; fft 1024, a chain in half a wave: 8, 12, 16, 22).  So
 //   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer; beyond six rounds half as many (fp16, 4096: one
 //     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116);
-//   fft 1024: half as many, and in the first round only if items are not full;
-//   fft 512: half as many, and behind the first round only if items are not full;
-//   fft 256: 40 Ki pairs + 24 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, (256 42, 40); 8192
-//     channels: B = 33 98, 51, (64 fp16 106, 116).
+//   fft 1024: half as many, and not in the first round (both 8 - 9 us there);
+//   fft 512: half as many, and only if items are not full;
+//   fft 256: 40 Ki pairs + 56 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, 256 42, 40; 8192
+//     channels: B = 33 98, 51, fp16 64 106, 116.
 // Measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
 // (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
 // calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
@@ -230,13 +230,13 @@ bool row_few(int64_t M, int64_t H, int64_t B)
     const int64_t npairs = (B + 1) / 2;
     if (M > 4096 || npairs > INT32_MAX / (H * (M / 16))) return false;
     const int64_t pairs = H * npairs;
-    if (M == 256) return pairs < 40 * 1024 + 24 * H;
+    if (M == 256) return pairs < 40 * 1024 + 56 * H;
     constexpr int CUS = 256;
     const int64_t full = 8192 / M, items = H * ((npairs + full - 1) / full), rounds = (items + CUS - 1) / CUS;
     const int64_t rows = M == 512 ? 16 : M == 1024 ? 8 : M == 2048 ? 2 : 1, groups = (pairs + rows - 1) / rows;
     if (M >= 2048) return groups <= CUS * rounds && (rounds <= 6 || 2 * groups <= CUS * rounds);
-    if (M == 1024) return (rounds > 1 || pairs < full * items) && groups <= CUS * ((rounds + 1) / 2);
-    return (rounds == 1 || pairs < full * items) && 2 * groups <= CUS * (rounds + 1);
+    if (M == 1024) return rounds > 1 && groups <= CUS * ((rounds + 1) / 2);
+    return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
 }
 
 // for calls that row_few() takes
