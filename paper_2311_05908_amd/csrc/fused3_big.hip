@@ -1199,27 +1199,31 @@ template <int N2> int big_init_t(fftconv_plan *p)
     constexpr int R2 = BG::R2;
     const bool f16 = p->dtype == FFTCONV_F16;
     const int64_t M = BG::M;
+    // the half a million entries of the tables are products of M roots of unity (a sine and a cosine for each were most of the creation of a plan)
+    std::vector<Cx> roots(M);
+    for (int64_t e = 0; e < M; ++e) roots[e] = wp(M, e);
+    auto root = [&](int64_t m, int64_t e) { return roots[(e & (m - 1)) * (M / m)]; };       // m a power of two up to M, e >= 0
     std::vector<uint16_t> ops(BG::U4 * 8);
     size_t o = 0;
     auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 64; return d; };
     for (int ct = 0; ct < 2; ++ct)                        // tab1: K step 0 only (n1 < 16)
         for (int part = 0; part < 2; ++part)
-            fill_op(next(), f16, 0, ct, part, [&](int n1, int k1) { return wp(32, (int64_t)n1 * k1); });
+            fill_op(next(), f16, 0, ct, part, [&](int n1, int k1) { return root(32, (int64_t)n1 * k1); });
     for (int ks = 0; ks < 2; ++ks)                        // tab1i: row tile 0 only (n1 < 16)
         for (int part = 0; part < 2; ++part)
-            fill_op(next(), f16, ks, 0, part, [&](int k1, int n1) { return cj(wp(32, (int64_t)n1 * k1)); });
+            fill_op(next(), f16, ks, 0, part, [&](int k1, int n1) { return cj(root(32, (int64_t)n1 * k1)); });
     for (int ks = 0; ks < 2; ++ks)                        // tab3 (forward; also serves the inverse, see the kernel)
         for (int ct = 0; ct < 2; ++ct)
             for (int part = 0; part < 2; ++part)
                 fill_op(next(), f16, ks, ct, part,
-                        [&](int m3, int j3) { return wp(32, (int64_t)big_sigma(m3) * big_sigma(j3)); });   // slots, both digits
+                        [&](int m3, int j3) { return root(32, (int64_t)big_sigma(m3) * big_sigma(j3)); });   // slots, both digits
     for (int n3 = 0; n3 < 32; ++n3)                       // tab2
         for (int ks = 0; ks < R2; ++ks)
             for (int ct = 0; ct < R2; ++ct)
                 for (int part = 0; part < 2; ++part)
                     fill_op(next(), f16, ks, ct, part, [&](int n2, int m2) {       // row slot m2 holds digit k2
                         const int k2 = big_tau<N2>(m2);
-                        return cm(wp(N2, (int64_t)n2 * k2), wp(32 * N2, (int64_t)k2 * n3));
+                        return cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k2 * n3));
                     });
     for (int k1 = 0; k1 < 32; ++k1)                       // tab2i
         for (int ks = 0; ks < R2; ++ks)
@@ -1227,7 +1231,7 @@ template <int N2> int big_init_t(fftconv_plan *p)
                 for (int part = 0; part < 2; ++part)
                     fill_op(next(), f16, ks, ct, part, [&](int m2, int n2) {       // contraction slot m2 holds digit k2
                         const int k2 = big_tau<N2>(m2);
-                        return cj(cm(wp(N2, (int64_t)n2 * k2), wp(32 * N2, (int64_t)k1 * n2)));
+                        return cj(cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k1 * n2)));
                     });
     if (o != BG::U4) {
         set_error("fused3 (32 x N2 x 32): operand table size mismatch");
@@ -1247,7 +1251,7 @@ template <int N2> int big_init_t(fftconv_plan *p)
                 for (int r = 0; r < 4; ++r)
                     for (int lane = 0; lane < 64; ++lane) {
                         const int k1 = 16 * ct + lane % 16, n2 = 16 * rt + 4 * (lane / 16) + r;
-                        put(e++, wp(M, (int64_t)k1 * (32 * n2 + n3)), false);
+                        put(e++, root(M, (int64_t)k1 * (32 * n2 + n3)), false);
                     }
     for (int k1 = 0; k1 < 32; ++k1)                       // twb: n3 = big_sigma(16 ct3 + c16), k2 = 16 ct2 + 4 q + r
         for (int ct2 = 0; ct2 < R2; ++ct2)
@@ -1255,7 +1259,7 @@ template <int N2> int big_init_t(fftconv_plan *p)
                 for (int r = 0; r < 4; ++r)
                     for (int lane = 0; lane < 64; ++lane) {
                         const int n3 = big_sigma(16 * ct3 + lane % 16), k2 = big_tau<N2>(16 * ct2 + 4 * (lane / 16) + r);
-                        put(e++, wp(M, ((int64_t)k1 + 32 * (int64_t)k2) * n3), true);
+                        put(e++, root(M, ((int64_t)k1 + 32 * (int64_t)k2) * n3), true);
                     }
     const size_t bytes = BG::U4 * 16 + tw.size() * 4;
     FC_HIP(hipMalloc(&p->f3.consts, bytes));
