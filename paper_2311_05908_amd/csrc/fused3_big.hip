@@ -1030,7 +1030,7 @@ __global__ void k_big_dk_last(const float2 *__restrict__ tmp, float *__restrict_
 // O = (Z[f] - conj Z[M/2 - f]) / (2i) are the spectra of the even and odd taps, K[f] = E + W_M^f O and
 // K[f + M/2] = E - W_M^f O, f < M/2.
 // k_f in the kernel's per-lane order: [h][k1][k2 tile][k3 tile][r][lane]; the lane holds
-// k2 = big_tau(16 tile + lane%16) and k3 = big_sigma(16 tile + 4 (lane/16) + r).  Scaled by 1/M.  conj_out: the adjoint filter
+// k2 = big_tau(16 tile + lane%16) and k3 = big_sigma(16 tile + 4 (lane/16) + r).  scale: kf_boost() / M.  conj_out: the adjoint filter
 // transform.  k1, k2 and k3 mod 16 are the digits of the engine's frequency, so that Z goes through LDS as the engine left it, and
 // a lane that forms the bins k3 = 4q + r and k3 + 16 has one value for its own slot of tile 0 and one for tile 1 of the lane 32 away.
 // Bound by the instructions of that loop and the transform's latency, with one workgroup (two at N2 = 16) on a compute unit.  us, with
@@ -1040,7 +1040,7 @@ __global__ void k_big_dk_last(const float2 *__restrict__ tmp, float *__restrict_
 template <int N2> using FilterRow = rf::Row<BigGeo<N2>::M / 2>;
 template <typename TT, int N2, bool HALF>
 __global__ void __launch_bounds__(FilterRow<N2>::T, 2) k_filter_big(const float *__restrict__ k, typename TT::CW *__restrict__ kf,
-                                                                   const float2 *__restrict__ tab, int64_t Nk, bool conj_out,
+                                                                   const float2 *__restrict__ tab, int64_t Nk, bool conj_out, float scale,
                                                                    const uint8_t *__restrict__ keep, int64_t n_blocks, KfTag kf_tag)
 {
     set_tag(kf_tag);
@@ -1100,7 +1100,7 @@ __global__ void __launch_bounds__(FilterRow<N2>::T, 2) k_filter_big(const float 
         const float2 e = make_float2(0.5f * (za.x + zc.x), 0.5f * (za.y - zc.y));
         const float2 o = make_float2(0.5f * (za.y + zc.y), -0.5f * (za.x - zc.x));      // (za - conj zc) / (2i)
         const float2 v = cmul(o, tw);
-        const float s0 = lds_mask_weight(keep, n_blocks, f, BM) / (float)BM, s1 = lds_mask_weight(keep, n_blocks, f + MH, BM) / (float)BM;
+        const float s0 = lds_mask_weight(keep, n_blocks, f, BM) * scale, s1 = lds_mask_weight(keep, n_blocks, f + MH, BM) * scale;
         const float sgn = conj_out ? -1.f : 1.f;
         const uint32_t lo = TT::pack((e.x + v.x) * s0, sgn * (e.y + v.y) * s0);         // k3: (re, im) 16-bit pairs
         const uint32_t hi = TT::pack((e.x - v.x) * s1, sgn * (e.y - v.y) * s1);         // k3 + 16
@@ -1158,6 +1158,12 @@ template <typename Fn> void fill_op(uint16_t *dst, bool f16, int t, int ct, int 
     }
 }
 
+// k_f of fp16 plans of odd rows is kept at this power of two, as that of the three passes is (multipass_kf_boost), and the inverse stage 1
+// matrix, whose entries are nowhere near the end of fp16's range, takes it out again: exact, and no instruction more.  At 1 / M a
+// filter of small norm has subnormal bins (2-norm error of a call, fft 32768, white filters of norm 1 / 0.1 / 0.05:
+// 1.1e-3, 8.0e-3, 1.6e-2 so; 8.2e-4, 2.1e-3, 4.1e-3 with the power, in three passes 8.6e-4, 2.2e-3, 4.1e-3).
+int kf_boost(const fftconv_plan *p) { return p->f3.odd ? multipass_kf_boost(p->dtype == FFTCONV_F16, (int)(p->M / 8192)) : 1; }
+
 template <typename TT, int FORM, int N2, int SP, bool GATED = false>
 int launch_big(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s,
                const void *wg = nullptr, const void *vg = nullptr, uint32_t live_k1 = 0xffffffffu)
@@ -1209,9 +1215,10 @@ template <int N2> int big_init_t(fftconv_plan *p)
     for (int ct = 0; ct < 2; ++ct)                        // tab1: K step 0 only (n1 < 16)
         for (int part = 0; part < 2; ++part)
             fill_op(next(), f16, 0, ct, part, [&](int n1, int k1) { return root(32, (int64_t)n1 * k1); });
+    const double unboost = 1.0 / kf_boost(p);
     for (int ks = 0; ks < 2; ++ks)                        // tab1i: row tile 0 only (n1 < 16)
         for (int part = 0; part < 2; ++part)
-            fill_op(next(), f16, ks, 0, part, [&](int k1, int n1) { return cj(root(32, (int64_t)n1 * k1)); });
+            fill_op(next(), f16, ks, 0, part, [&](int k1, int n1) { return cm(cj(root(32, (int64_t)n1 * k1)), {unboost, 0.0}); });
     for (int ks = 0; ks < 2; ++ks)                        // tab3 (forward; also serves the inverse, see the kernel)
         for (int ct = 0; ct < 2; ++ct)
             for (int part = 0; part < 2; ++part)
@@ -1277,7 +1284,7 @@ int big_filter_tt(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoin
     const auto kern = Nk <= BigGeo<N2>::M / 2 ? k_filter_big<TT, N2, true> : k_filter_big<TT, N2, false>;
     FC_TRY(raise_dynamic_lds((const void *)kern, G::LDS_BYTES));
     hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), G::LDS_BYTES, s, k, (typename TT::CW *)kf, rf::row_table<G>(p), Nk, adjoint,
-                       keep_dev, n_blocks, tag);
+                       (float)kf_boost(p) / (float)p->M, keep_dev, n_blocks, tag);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

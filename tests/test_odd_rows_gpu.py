@@ -76,6 +76,26 @@ def test_odd_rows_are_no_less_accurate_than_in_three_passes(dtype, M, bound):
     assert err <= 1.01 * bound
 
 
+@pytest.mark.parametrize("M,norm,bound", [
+    (16384, 1.0, 8.48e-4), (16384, 0.1, 2.149e-3), (16384, 0.05, 4.052e-3),
+    (32768, 1.0, 8.63e-4), (32768, 0.1, 2.155e-3), (32768, 0.05, 4.071e-3),
+])
+def test_odd_rows_keep_the_bits_of_small_fp16_filters(M, norm, bound):
+    """White filters of small norm, whose spectrum over fft_size is subnormal in fp16: the error (2-norm, fp64 reference) of the three-pass route on
+    such rows, which keeps k_f at a power of two above that; 2^20 outputs, as above."""
+    g = torch.Generator().manual_seed(M)
+    B, H, N = 4, 64, M // 2 - 1
+    u = torch.randn(B, H, N, generator=g).to(torch.float16)
+    k = torch.randn(H, N, generator=g) * (norm / N ** 0.5)
+    plan = fftconv.Plan(N, M, H, "f16")
+    for kf, ref in ((plan.filter_fft(k.cuda()), conv(u.double(), k.double(), N)),
+                    (plan.filter_fft_adjoint(k.cuda()), conv(u.double().flip(-1), k.double(), N).flip(-1))):
+        y = plan.forward(u.cuda(), kf).cpu().double()
+        err = ((y - ref).norm() / ref.norm()).item()
+        print("odd rows f16 M=%d norm %g error %.4e bound %.4e" % (M, norm, err, bound), flush=True)
+        assert err <= 1.01 * bound
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M", [16384, 32768])
 def test_odd_rows_with_masks(dtype, M):
