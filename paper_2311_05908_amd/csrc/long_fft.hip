@@ -24,6 +24,7 @@
 #include "fftconv_internal.h"
 #include "lds_fft.h"
 #include "row_io.h"
+#include "work_index.h"
 
 namespace fftconv {
 
@@ -70,15 +71,6 @@ __device__ __forceinline__ void st_real(__hip_bfloat16 *p, int64_t i, float v) {
 struct LongTw {
     const float2 *lo, *hi;                     // W_M^t, t < 2048; W_M^{2048 t}, t < M / 2048
     __device__ __forceinline__ float2 operator()(int64_t e) const { return cmul(hi[e >> 11], lo[e & 2047]); }
-};
-
-// Rows of a launch of the column kernels: row i is row first + i of the tensor, or, counted in pairs of batch rows of H channels,
-// channel j % H of batch row 2 (j / H), j = first + i (its partner lies H rows further, if the tensor has so many)
-struct LongRows {
-    int64_t first, H, rows;                    // H = 0: not in pairs
-    // (rows of 32 KB and more in memory are fewer than 2^32: a 64-bit division, in every thread, cost 2 % of a pass)
-    __device__ __forceinline__ int64_t at(int64_t i) const { return H ? (int64_t)((uint32_t)(first + i) / (uint32_t)H) * H + first + i : first + i; }
-    __device__ __forceinline__ bool partner(int64_t i) const { return at(i) + H < rows; }
 };
 
 // A thread's share of a tile of 8192 points: LPT points LT apart.  All loads of a thread are issued before the
@@ -148,11 +140,11 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
 {
     extern __shared__ float2 XL[];
     const int M = A * LB, N = (int)len;
-    const int64_t row = blockIdx.y, first = rows.at(row) * len;
+    const int64_t row = blockIdx.y, first = rows.at(blockIdx.y) * len;
     const In *const re = src_re + first, *const im = src_im + first;
     const int col0 = blockIdx.x * C;
     const int lgC = __ffs(C) - 1;
-    const bool two = src_im && rows.partner(row);
+    const bool two = src_im && rows.partner(blockIdx.y);
     // samples beyond `len` are zeros: their loads go to sample 0 instead and are discarded, so that every load of
     // the thread is unconditional and in flight at once (see load_block)
     float vr[LPT], vi[LPT];
@@ -495,11 +487,11 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
                                                        LongRows rows)
 {
     extern __shared__ float2 XL[];
-    const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(row) * N;
+    const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(blockIdx.y) * N;
     IO *const re = y_re + first, *const im = y_im + first;
     const int col0 = blockIdx.x * C;
     if (col0 >= N) return;
-    const bool two = y_im && rows.partner(row);
+    const bool two = y_im && rows.partner(blockIdx.y);
     load_cols(XL, tmp + row * M, C, col0);
     __syncthreads();
     int Sp = 1, R = A;
@@ -539,7 +531,7 @@ int raise_lds(const void *kern) { return raise_dynamic_lds(kern, (int)L_LDS); }
 
 template <typename In>
 int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, const LongTw &w, int64_t rows, int64_t len,
-                    bool reversed, hipStream_t s, bool half_rows = false, LongRows where = LongRows{0, 0, INT64_MAX})
+                    bool reversed, hipStream_t s, bool half_rows = false, LongRows where = long_rows(0))
 {
     const int rc = raise_lds((const void *)k_long_fwd_cols<In>);
     if (rc) return rc;
@@ -741,7 +733,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
     };
     auto as_complex = [&](int64_t b, int64_t units, bool pairs) -> int {
         return trips(units, M, [&](int64_t first, int64_t n) -> int {
-            const LongRows where{first, pairs ? H : 0, (B - b) * H};
+            const LongRows where = pairs ? long_row_pairs(first, H, (B - b) * H) : long_rows(first);
             const IO *u0 = u + b * H * N;
             IO *y0 = y + b * H * N;
             FC_TRY(launch_fwd_cols<IO>(g, u0, pairs ? u0 + H * N : nullptr, tmp, tw, n, N, false, s, false, where));

@@ -1,0 +1,25 @@
+// Which rows of a tensor the workgroups of a launch take: index arithmetic without anything of the GPU's, so that it can be checked
+// on the CPU at sizes that no test runs (tests/test_work_index.py).
+#pragma once
+
+#include <cstdint>
+
+namespace fftconv {
+
+// Rows of a launch of the column kernels (long_fft.hip): row i, i < 65536, is row first + i of the tensor, or, counted in pairs of batch
+// rows of H < 2^31 - 65536 channels, channel j % H of batch row 2 (j / H), j = first + i (its partner lies H rows further, if the tensor has so many).
+// A row may be a single sample, so that a tensor holds more than 2^32 of them; the division, in every thread, is of 32 bits all the
+// same (64 bits cost 2 % of a pass): the host takes the pairs before the launch's first channel out.
+struct LongRows {
+    int64_t base, rows;                        // row 0 of the launch; rows of the tensor
+    uint32_t channel, H;                       // channel of row 0; H = 0: not in pairs
+    __host__ __device__ int64_t at(uint32_t i) const { return base + i + (H ? (int64_t)((channel + i) / H) * H : 0); }
+    __host__ __device__ bool partner(uint32_t i) const { return at(i) + H < rows; }
+};
+inline LongRows long_rows(int64_t first) { return LongRows{first, INT64_MAX, 0, 0}; }
+inline LongRows long_row_pairs(int64_t first, int64_t H, int64_t rows)
+{
+    return LongRows{first / H * H + first, rows, (uint32_t)(first % H), (uint32_t)H};
+}
+
+}  // namespace fftconv
