@@ -30,6 +30,7 @@
 #include "fused3_common.h"
 #include "lds_fft.h"
 #include "row_io.h"
+#include "work_index.h"
 
 namespace fftconv {
 namespace f3 {
@@ -680,7 +681,7 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
         if (more) lds_barrier();
     };
     int v = jb;
-    for (; v + nb < n_local; v += nb) pair_step(v, true);
+    for (; big_item_follows(v, nb, n_local); v += nb) pair_step(v, true);
     pair_step(v, false);
 }
 
@@ -1178,8 +1179,8 @@ int launch_big(const fftconv_plan *p, const void *u, const void *kf, void *y, in
                   (long long)(p->H * BG::M));
         return FFTCONV_EUNSUPPORTED;
     }
-    if (T >= ((int64_t)1 << 31) - 8) {
-        set_error("fftconv_forward: H * ceil(B/2) = %lld work items exceed the fused kernel's limit", (long long)T);
+    if (!big_items_fit(B, p->H)) {
+        set_error("fftconv_forward: H * ceil(B/2) = %lld work items, or B = %lld, exceed the fused kernel's limit", (long long)T, (long long)B);
         return FFTCONV_EUNSUPPORTED;
     }
     // persistent workgroups, as many as are resident at once (two per compute unit for the smaller

@@ -22,4 +22,10 @@ inline LongRows long_row_pairs(int64_t first, int64_t H, int64_t rows)
     return LongRows{first / H * H + first, rows, (uint32_t)(first % H), (uint32_t)H};
 }
 
+// Work items of the streamed-table kernel (fused3_big.hip), pairs of batch rows of a channel: a workgroup takes every step-th of up to
+// 2^31 - 9 of them, counted in 32 bits, so that the last one plus a step may lie beyond; batch rows are counted in 32 bits as well, up to the
+// number of a pair's second one.
+inline bool big_items_fit(int64_t B, int64_t H) { return B < INT32_MAX && H * ((B + 1) / 2) < ((int64_t)1 << 31) - 8; }
+__host__ __device__ inline bool big_item_follows(int v, int step, int items) { return v < items - step; }
+
 }  // namespace fftconv

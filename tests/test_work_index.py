@@ -17,10 +17,19 @@ def program(tmp_path_factory):
 #include <cstdio>
 int main()
 {
-    long long first, H, rows, i;
-    while (std::scanf("%lld %lld %lld %lld", &first, &H, &rows, &i) == 4) {
-        const fftconv::LongRows r = H ? fftconv::long_row_pairs(first, H, rows) : fftconv::long_rows(first);
-        std::printf("%lld %d\\n", (long long)r.at((uint32_t)i), (int)r.partner((uint32_t)i));
+    char what;
+    long long a, b, c, d;
+    while (std::scanf(" %c %lld %lld %lld %lld", &what, &a, &b, &c, &d) == 5) {
+        if (what == 'r') {                                // row d of a launch from row or pair a on; b channels, c rows
+            const fftconv::LongRows r = b ? fftconv::long_row_pairs(a, b, c) : fftconv::long_rows(a);
+            std::printf("%lld %d\\n", (long long)r.at((uint32_t)d), (int)r.partner((uint32_t)d));
+        } else if (what == 'w') {                         // a workgroup's items from a on: every b-th of c; the last one and how many
+            int v = (int)a, n = 1;
+            for (; fftconv::big_item_follows(v, (int)b, (int)c); v += (int)b) ++n;
+            std::printf("%d %d\\n", v, n);
+        } else {                                          // a batch rows of b channels
+            std::printf("%d 0\\n", (int)fftconv::big_items_fit(a, b));
+        }
     }
 }
 """)
@@ -28,6 +37,12 @@ int main()
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover", "-I", CSRC, "-o", str(exe),
                     str(d / "main.cpp")], check=True)
     return str(exe)
+
+
+def answers(program, lines):
+    text = "".join("%s %d %d %d %d\n" % l for l in lines)
+    out = subprocess.run([program], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+    return [tuple(int(x) for x in l.split()) for l in out if l]
 
 
 @pytest.mark.parametrize("H,B", [(1, 7), (3, 2), (16, 9), (768, 64), (1 << 17, 65538), (65535, 1 << 18), ((1 << 24) - 1, 1031), (1, 1 << 34)])
@@ -39,16 +54,26 @@ def test_rows_of_pairs(program, H, B):
             if 0 <= first and 0 <= i < 65535 and first + i < pairs:
                 ask.add((first, i))
     ask = sorted(ask)
-    text = "".join("%d %d %d %d\n" % (f, H, rows, i) for f, i in ask)
-    out = subprocess.run([program], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
     assert len(ask) > 3
-    for (f, i), line in zip(ask, out):
-        j = f + i
-        want = 2 * (j // H) * H + j % H
-        assert line == "%d %d" % (want, want + H < rows), (f, i)
+    want = [2 * ((f + i) // H) * H + (f + i) % H for f, i in ask]
+    assert answers(program, [("r", f, H, rows, i) for f, i in ask]) == [(w, int(w + H < rows)) for w in want]
 
 
 def test_single_rows(program):
     ask = [(0, 0), (5, 65534), ((1 << 33) + 7, 40000)]
-    out = subprocess.run([program], input="".join("%d 0 0 %d\n" % a for a in ask), capture_output=True, text=True, check=True).stdout.split("\n")
-    assert [int(l.split()[0]) for l in out[:3]] == [sum(a) for a in ask]
+    assert [a for a, _ in answers(program, [("r", f, 0, 0, i) for f, i in ask])] == [sum(a) for a in ask]
+
+
+@pytest.mark.parametrize("step", [1, 32, 255, 512])
+@pytest.mark.parametrize("items", [1, 2, 511, 512, 513, 100000, (1 << 31) - 600, (1 << 31) - 512, (1 << 31) - 9])
+def test_items_of_a_workgroup(program, items, step):
+    first = [f for f in (0, 1, 31, items - 1, items - step, items - 2 * step + 1, items - 5 * step) if 0 <= f < items and (items - f) // step < 10 ** 6]
+    got = answers(program, [("w", f, step, items, 0) for f in first])
+    assert got == [(f + (items - 1 - f) // step * step, (items - 1 - f) // step + 1) for f in first]
+
+
+def test_item_limits(program):
+    fits = [(1, 1), ((1 << 31) - 2, 1), ((1 << 31) - 10, 2), (2, (1 << 31) - 9), (5, 30000)]
+    not_ = [((1 << 31) - 1, 1), (1 << 32, 1), ((1 << 32) + 4, 1), ((1 << 31) - 9, 2), (2, (1 << 31) - 8), (1 << 20, 1 << 20)]
+    assert answers(program, [("f", B, H, 0, 0) for B, H in fits]) == [(1, 0)] * len(fits)
+    assert answers(program, [("f", B, H, 0, 0) for B, H in not_]) == [(0, 0)] * len(not_)
