@@ -1385,13 +1385,6 @@ int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int
     }
 }
 
-static int check_rows(int64_t rows)
-{
-    if (rows <= 65535) return FFTCONV_OK;
-    set_error("fftconv_forward: ceil(B/2) * H = %lld exceeds the multi-pass grid limit 65535", (long long)rows);
-    return FFTCONV_EUNSUPPORTED;
-}
-
 // One set of the three passes over rows [0, B) of u.  ko_lo, ko_hi: outer frequency digits ko in [ko_lo, ko_hi)
 // only meet zeroed bins of k_f (frequency-sparse filters); their rows of the workspace are skipped by all three
 // passes.  ko_lo >= ko_hi: none.  wg, vg: input / output gate of the gated form, fused into passes A and C.
@@ -1408,7 +1401,10 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
     const int64_t rows = npairs * p->H;
     const bool packed = lone && outer_real_ok((int)(p->M / MI));
     const OuterGeo g = outer_geo(p->M, packed ? 0 : rows);
-    FC_TRY(check_rows(rows));
+    if (rows > 65535) {
+        set_error("fftconv_forward: ceil(B/2) * H = %lld exceeds the multi-pass grid limit 65535", (long long)rows);
+        return FFTCONV_EUNSUPPORTED;
+    }
     const bool f16 = p->dtype == FFTCONV_F16;
     const dim3 grid((unsigned)(MI / g.CT), (unsigned)rows);
     if (ko_lo >= ko_hi) ko_lo = ko_hi = g.No;            // nothing skipped
@@ -1448,10 +1444,7 @@ int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void
                       hipStream_t s, int ko_lo, int ko_hi, const void *wg, const void *vg)
 {
     uint32_t *S = (uint32_t *)workspace;
-    if (p->f3.odd) {
-        FC_TRY(check_rows((B + 1) / 2 * p->H));
-        return f3::fused3_big_forward_odd(p, u, wg, vg, kf, y, B, s);
-    }
+    if (p->f3.odd) return f3::fused3_big_forward_odd(p, u, wg, vg, kf, y, B, s);
     // fft_size 8192 (outer length 1: a circular or ragged shape the causal kernel does not take): the inner kernel
     // reads u and writes y itself, nothing passes through the workspace.  Gated calls and N not a multiple of 4
     // (rows that start off an 8-byte boundary) keep the three passes.

@@ -96,6 +96,23 @@ def test_odd_rows_keep_the_bits_of_small_fp16_filters(M, norm, bound):
         assert err <= 1.01 * bound
 
 
+@pytest.mark.parametrize("B,H", [(5, 30000), (6, 24000)])
+def test_odd_rows_of_many_channels(B, H):
+    """More pairs of rows than a launch of the three passes takes (90000 and 72000; 65535).  Those took the first shape, an odd batch's lone
+    rows and its pairs being launches of their own.  (101 samples a row: the bound is the worst row's error over that row's norm, and of 150000 rows of 9
+    samples one in some 10^4 has so small a norm that the roundings of its partial sums, 5e-3 of |u| |k| at any norm, are over it: 1.03e-2.)"""
+    M, N = 16384, 101
+    g = torch.Generator().manual_seed(H)
+    u = torch.randn(B, H, N, generator=g).to(torch.bfloat16)
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, "bf16")
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda()), out=torch.full_like(u, float("nan"), device="cuda")).cpu()
+    w = torch.randn(B, H, N, generator=g).to(torch.bfloat16)
+    yg = plan.forward_gated(u.cuda(), w.cuda(), None, plan.filter_fft(k.cuda())).cpu()
+    assert parity_error(y.double().numpy(), conv(u.double(), k.double(), N).numpy(), TOL["bf16"], "y") <= TOL["bf16"]
+    assert parity_error(yg.double().numpy(), conv(u.double() * w.double(), k.double(), N).numpy(), TOL["bf16"], "w") <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M", [16384, 32768])
 def test_odd_rows_with_masks(dtype, M):
