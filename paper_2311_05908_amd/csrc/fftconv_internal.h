@@ -101,8 +101,8 @@ struct Fused3Tables {
     // fft 16384 plans also carry the 8192-point tables: a short (partial) filter runs as overlapping
     // 8192-point segments, and k_f then holds a second, 8192-point spectrum after the dense one
     void *consts_short = nullptr;
-    // multi-pass plans of fft 16384 and 32768 whose rows the single kernel takes at any length (fused3_odd_rows); k_f and tables
-    // are that kernel's then
+    // multi-pass plans of fft 16384 and 32768 whose rows the single kernel takes at any length (fused3_odd_rows): multi-pass by name and
+    // factors (digit patterns are counted in those); k_f, tables, limits and the lack of a workspace are that kernel's
     bool odd = false;
 };
 
@@ -203,8 +203,8 @@ int fused3_forward_short(const fftconv_plan *p, const void *u, const void *kf, v
                          hipStream_t s);
 // the 8192-point complex-row kernel used as the inner step of the multi-pass path
 int fused3_init_inner(fftconv_plan *p);
-// causal 16-bit shapes of fft 16384 and 32768 that are no multiple of 8 samples long: multi-pass plans by name (path, factors, workspace,
-// limits) that run on the single kernel
+// causal 16-bit shapes of fft 16384 and 32768 that are no multiple of 8 samples long: multi-pass plans by name and factors that run on
+// the single kernel
 bool fused3_odd_rows(const fftconv_plan *p);
 int fused3_inner_rows(const fftconv_plan *p, void *rows, const void *kf, int64_t rows_per_kf, int64_t kf_rows,
                       hipStream_t s, int ko_n = 0, int ko_lo = 0, int ko_hi = 0, bool quarter_rows = false);

@@ -1315,6 +1315,7 @@ size_t multipass_kf_bytes(const fftconv_plan *p)
 
 size_t multipass_workspace_bytes(const fftconv_plan *p, int64_t B)
 {
+    if (p->f3.odd) return 0;
     const int64_t npairs = (B + 1) / 2;
     return (size_t)(npairs * p->H * p->M) * sizeof(uint32_t);
 }

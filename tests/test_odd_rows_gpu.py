@@ -133,3 +133,22 @@ def test_odd_rows_with_masks(dtype, M):
     mask = torch.from_numpy(synth.digit_keep_mask(plan.factors, digits)).double()
     ref = torch.fft.ifft(mask * U * K).real[..., :N]
     assert parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "digits") <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [16384, 32768])
+def test_odd_rows_need_no_workspace(dtype, M):
+    """Nothing passes through memory: no workspace, none missed by any entry point, and the static one's size bounds no batch."""
+    B, H, N = 1031, 2, 1001
+    g = torch.Generator().manual_seed(M)
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]).cuda()
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.workspace_bytes(B) == plan.workspace_bytes_gated(B) == 0
+    kf = plan.filter_fft((torch.randn(H, N, generator=g) / N ** 0.5).cuda())
+    y = plan.forward(u, kf)
+    assert torch.equal(plan.forward_static(u, kf, torch.full_like(u, float("nan"))), y)
+    keep, digits = [1] * 32, plan.factors
+    assert torch.equal(plan.forward_freq_sparse(u, kf, keep), y)
+    assert torch.equal(plan.forward_freq_sparse_digits(u, kf, digits), y)
+    assert torch.equal(plan.forward_partial(u, kf, 100), y)
+    assert torch.equal(plan.forward_gated(u, torch.ones_like(u), None, kf), y)
