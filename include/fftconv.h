@@ -84,7 +84,10 @@ int fftconv_plan_create(fftconv_plan **out, int64_t N, int64_t fft_size, int64_t
 /* As fftconv_plan_create, with the kernel family chosen by the caller instead of by the cost model:
  * path is one of the names fftconv_plan_path returns ("fused3", "small", "multipass", "staged"), or NULL /
  * "" for the model's choice.  Fails with FFTCONV_EUNSUPPORTED when that family has no kernel for the
- * shape.  Where several families can run a shape (16-bit causal shapes: "fused3" everywhere it exists,
+ * shape.  (Causal 16-bit rows of fft_size 16384 and 32768 whose length is no multiple of 8 are "multipass"
+ * plans with that family's factors: one that the model chose runs them in a single kernel without a
+ * workspace, one asked for by name in the family's three passes.)
+ * Where several families can run a shape (16-bit causal shapes: "fused3" everywhere it exists,
  * "small" up to fft_size 4096, "multipass" from 8192), fftconv_plan_create evaluates Eq. 2 of Section 3.2
  * (fftconv_cost_model with the FFTCONV_MACHINE_MI355X constants) on each family's own factorisation --
  * matrix-unit rate for the families that multiply on the matrix cores, general arithmetic rate for the

@@ -204,7 +204,7 @@ int fftconv_plan_create_path(fftconv_plan **out, int64_t N, int64_t fft_size, in
     if (rc == FFTCONV_OK) {
         if (p->path == PATH_FUSED3) rc = fused3_init(p);
         else if (p->path == PATH_SMALL) rc = small_init(p);
-        else if (p->path == PATH_MULTIPASS) rc = multipass_init(p);
+        else if (p->path == PATH_MULTIPASS) rc = multipass_init(p, path && path[0]);
     }
     if (rc != FFTCONV_OK) {
         fftconv_plan_destroy(p);

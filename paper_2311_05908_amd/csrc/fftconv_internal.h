@@ -321,7 +321,7 @@ void *static_workspace(int device);        // its device address, nullptr before
 
 // ---- multi-pass path (multipass.hip)
 bool multipass_supported(int64_t N, int64_t M, int dtype);
-int multipass_init(fftconv_plan *p);
+int multipass_init(fftconv_plan *p, bool forced);       // forced: by name, in three passes whatever other kernel takes the shape
 size_t multipass_kf_bytes(const fftconv_plan *p);
 size_t multipass_workspace_bytes(const fftconv_plan *p, int64_t B);
 // outer pass of the filter transform of a multi-pass plan (multipass.hip), where a kernel for the plan's outer length exists

@@ -339,7 +339,6 @@ int fused3_init_inner(fftconv_plan *p)
     hipDeviceProp_t prop;
     FC_HIP(hipGetDeviceProperties(&prop, p->device));
     p->f3.num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    p->f3.odd = fused3_odd_rows(p);
     return p->f3.odd ? fused3_big_init(p) : build_tables<16, 16>(p, &p->f3.consts);
 }
 

@@ -1301,8 +1301,9 @@ bool multipass_supported(int64_t N, int64_t M, int dtype)
     return N >= 1 && N <= M;
 }
 
-int multipass_init(fftconv_plan *p)
+int multipass_init(fftconv_plan *p, bool forced)
 {
+    p->f3.odd = !forced && fused3_odd_rows(p);
     int rc = fused3_init_inner(p);
     if (rc) return rc;
     return fused3_init_short(p);      // short filters run as overlapping 8192-point segments (fused3.hip)
