@@ -210,6 +210,7 @@ int fftconv_plan_create_path(fftconv_plan **out, int64_t N, int64_t fft_size, in
         fftconv_plan_destroy(p);
         return rc;
     }
+    std::vector<double2>().swap(p->roots);
     *out = p;
     return FFTCONV_OK;
 }

@@ -140,6 +140,9 @@ struct fftconv_plan {
     uint8_t *keep_dev = nullptr;      // device copy of a frequency-block mask (sparse filter transform)
     float2 *long_tw = nullptr;        // twiddle tables of the two-kernel long transforms (long_fft.hip)
     const float2 *row_tw = nullptr;   // twiddle tables of the row kernels (row_io.h), behind st.w32
+    // 16-bit plans of fft 16384 and 32768: exp(-2 pi i t / M), t < M, from staged_init() to the end of the plan's creation, for the tables
+    // made of them
+    std::vector<double2> roots;
 };
 
 namespace fftconv {

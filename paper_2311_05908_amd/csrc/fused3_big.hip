@@ -22,8 +22,6 @@
 //    (instruction modifiers), and 32 registers of matrix are saved.
 //  * Schedule per pair, 5 workgroup barriers: [phase B] | [phase C into registers] | [y and the next
 //    u into the staging areas] | [staging into registers] | [phase A of the next pair, store y].
-#include <cmath>
-#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -1131,30 +1129,24 @@ uint16_t h_f16(double x)
     return b;
 }
 struct Cx { double re, im; };
-Cx wp(int64_t M, int64_t e)                   // exp(-2 pi i e / M)
-{
-    const double two_pi = 6.283185307179586476925286766559;
-    e %= M;
-    if (e < 0) e += M;
-    const double a = two_pi * (double)e / (double)M;
-    return {std::cos(a), -std::sin(a)};
-}
 Cx cm(Cx a, Cx b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 Cx cj(Cx a) { return {a.re, -a.im}; }
 
-// One MFMA operand (64 lanes x 8 16-bit slots) of the real form of a complex matrix G: lane
+// The two MFMA operands (64 lanes x 8 16-bit slots each) of the real form of a complex matrix G: lane
 // (c16, q), slot 2r+s multiplies data element e_in = 16 t + 4 q + r, part s (0 = re, 1 = im), and
-// contributes to output element e_out = 16 ct + c16, part `part`.
-template <typename Fn> void fill_op(uint16_t *dst, bool f16, int t, int ct, int part, Fn G)
+// contributes to output element e_out = 16 ct + c16, part re (the first operand) or im (the 512 slots behind it).
+template <typename Fn> void fill_ops(uint16_t *dst, bool f16, int t, int ct, Fn G)
 {
     for (int lane = 0; lane < 64; ++lane) {
         const int c16 = lane % 16, q = lane / 16;
         for (int r = 0; r < 4; ++r) {
             const Cx g = G(16 * t + 4 * q + r, 16 * ct + c16);
-            const double v0 = part == 0 ? g.re : g.im;
-            const double v1 = part == 0 ? -g.im : g.re;
-            dst[lane * 8 + 2 * r + 0] = f16 ? h_f16(v0) : h_bf16(v0);
-            dst[lane * 8 + 2 * r + 1] = f16 ? h_f16(v1) : h_bf16(v1);
+            const uint16_t re = f16 ? h_f16(g.re) : h_bf16(g.re), im = f16 ? h_f16(g.im) : h_bf16(g.im);
+            uint16_t *const o = dst + lane * 8 + 2 * r;
+            o[0] = re;
+            o[1] = im ^ 0x8000u;
+            o[512] = im;
+            o[513] = re;
         }
     }
 }
@@ -1206,41 +1198,40 @@ template <int N2> int big_init_t(fftconv_plan *p)
     constexpr int R2 = BG::R2;
     const bool f16 = p->dtype == FFTCONV_F16;
     const int64_t M = BG::M;
-    // the half a million entries of the tables are products of M roots of unity (a sine and a cosine for each were most of the creation of a plan)
-    std::vector<Cx> roots(M);
-    for (int64_t e = 0; e < M; ++e) roots[e] = wp(M, e);
-    auto root = [&](int64_t m, int64_t e) { return roots[(e & (m - 1)) * (M / m)]; };       // m a power of two up to M, e >= 0
+    // the half a million entries of the tables are products of the plan's M roots of unity, formed once for the two operands that hold them
+    // (ms to create a plan of fft 32768, 256 channels of 10007 bf16 samples: a sine and a cosine for each 6.6; roots of their own, each product formed
+    // twice 2.2; now 1.7, as with the multi-pass tables)
+    const double2 *const roots = p->roots.data();
+    auto root = [&](int64_t m, int64_t e) -> Cx {                     // m a power of two up to M, e >= 0
+        const double2 w = roots[(e & (m - 1)) * (M / m)];
+        return {w.x, w.y};
+    };
     std::vector<uint16_t> ops(BG::U4 * 8);
     size_t o = 0;
-    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 64; return d; };
+    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 128; return d; };
     for (int ct = 0; ct < 2; ++ct)                        // tab1: K step 0 only (n1 < 16)
-        for (int part = 0; part < 2; ++part)
-            fill_op(next(), f16, 0, ct, part, [&](int n1, int k1) { return root(32, (int64_t)n1 * k1); });
+        fill_ops(next(), f16, 0, ct, [&](int n1, int k1) { return root(32, (int64_t)n1 * k1); });
     const double unboost = 1.0 / kf_boost(p);
     for (int ks = 0; ks < 2; ++ks)                        // tab1i: row tile 0 only (n1 < 16)
-        for (int part = 0; part < 2; ++part)
-            fill_op(next(), f16, ks, 0, part, [&](int k1, int n1) { return cm(cj(root(32, (int64_t)n1 * k1)), {unboost, 0.0}); });
+        fill_ops(next(), f16, ks, 0, [&](int k1, int n1) { return cm(cj(root(32, (int64_t)n1 * k1)), {unboost, 0.0}); });
     for (int ks = 0; ks < 2; ++ks)                        // tab3 (forward; also serves the inverse, see the kernel)
         for (int ct = 0; ct < 2; ++ct)
-            for (int part = 0; part < 2; ++part)
-                fill_op(next(), f16, ks, ct, part,
-                        [&](int m3, int j3) { return root(32, (int64_t)big_sigma(m3) * big_sigma(j3)); });   // slots, both digits
+            fill_ops(next(), f16, ks, ct,
+                     [&](int m3, int j3) { return root(32, (int64_t)big_sigma(m3) * big_sigma(j3)); });   // slots, both digits
     for (int n3 = 0; n3 < 32; ++n3)                       // tab2
         for (int ks = 0; ks < R2; ++ks)
             for (int ct = 0; ct < R2; ++ct)
-                for (int part = 0; part < 2; ++part)
-                    fill_op(next(), f16, ks, ct, part, [&](int n2, int m2) {       // row slot m2 holds digit k2
-                        const int k2 = big_tau<N2>(m2);
-                        return cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k2 * n3));
-                    });
+                fill_ops(next(), f16, ks, ct, [&](int n2, int m2) {       // row slot m2 holds digit k2
+                    const int k2 = big_tau<N2>(m2);
+                    return cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k2 * n3));
+                });
     for (int k1 = 0; k1 < 32; ++k1)                       // tab2i
         for (int ks = 0; ks < R2; ++ks)
             for (int ct = 0; ct < R2; ++ct)
-                for (int part = 0; part < 2; ++part)
-                    fill_op(next(), f16, ks, ct, part, [&](int m2, int n2) {       // contraction slot m2 holds digit k2
-                        const int k2 = big_tau<N2>(m2);
-                        return cj(cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k1 * n2)));
-                    });
+                fill_ops(next(), f16, ks, ct, [&](int m2, int n2) {       // contraction slot m2 holds digit k2
+                    const int k2 = big_tau<N2>(m2);
+                    return cj(cm(root(N2, (int64_t)n2 * k2), root(32 * N2, (int64_t)k1 * n2)));
+                });
     if (o != BG::U4) {
         set_error("fused3 (32 x N2 x 32): operand table size mismatch");
         return FFTCONV_EINVAL;

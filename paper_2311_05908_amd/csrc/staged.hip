@@ -280,6 +280,7 @@ int staged_init(fftconv_plan *p)
     p->row_tw = p->st.w32 + M;
     FC_HIP(hipMemcpy(p->st.w64, w64.data(), sizeof(double2) * M, hipMemcpyHostToDevice));
     FC_HIP(hipMemcpy(p->st.w32, w32.data(), sizeof(float2) * w32.size(), hipMemcpyHostToDevice));
+    if ((M == 16384 || M == 32768) && p->dtype != FFTCONV_F32) p->roots.swap(w64);
 
     // filter-transform scratch: two ping-pong buffers of at most 64 MiB, or 8 channels, each
     const int64_t cap = (int64_t)64 << 20;
