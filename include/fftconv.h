@@ -45,8 +45,10 @@
  *  - Arithmetic: 16-bit I/O plans multiply bf16/fp16 operands on the matrix
  *    cores with fp32 accumulation; fp32 I/O plans compute in fp32.  Plans of
  *    the "small" family, and calls of few rows on "fused3" plans up to
- *    fft_size 4096, run their transforms in fp32 whatever the I/O type: the
- *    last bits of a row may depend on how many rows the call has.  All
+ *    fft_size 4096, run their transforms in fp32 whatever the I/O type, and
+ *    16-bit rows of fft_size 32768 whose length is no multiple of 8 take one
+ *    of two kernels by their number: the last bits of a row may depend on how
+ *    many rows the call has.  All
  *    16-bit roundings are round-to-nearest-even.
  */
 #ifndef FFTCONV_H
@@ -86,7 +88,7 @@ int fftconv_plan_create(fftconv_plan **out, int64_t N, int64_t fft_size, int64_t
  * "" for the model's choice.  Fails with FFTCONV_EUNSUPPORTED when that family has no kernel for the
  * shape.  (Causal 16-bit rows of fft_size 16384 and 32768 whose length is no multiple of 8 are "multipass"
  * plans with that family's factors: one that the model chose runs them in a single kernel without a
- * workspace, one asked for by name in the family's three passes.)
+ * workspace -- at 32768 calls of few rows still in three passes --, one asked for by name in three passes.)
  * Where several families can run a shape (16-bit causal shapes: "fused3" everywhere it exists,
  * "small" up to fft_size 4096, "multipass" from 8192), fftconv_plan_create evaluates Eq. 2 of Section 3.2
  * (fftconv_cost_model with the FFTCONV_MACHINE_MI355X constants) on each family's own factorisation --

@@ -102,8 +102,9 @@ struct Fused3Tables {
     // 8192-point segments, and k_f then holds a second, 8192-point spectrum after the dense one
     void *consts_short = nullptr;
     // multi-pass plans of fft 16384 and 32768 whose rows the single kernel takes at any length (fused3_odd_rows): multi-pass by name and
-    // factors (digit patterns are counted in those); k_f, tables, limits and the lack of a workspace are that kernel's
+    // factors (digit patterns are counted in those); k_f, tables and limits are that kernel's, and it has no workspace
     bool odd = false;
+    void *consts_few = nullptr;       // ... and the tables of the three passes' inner kernel, for calls of few rows (fused3_odd_few)
 };
 
 // fp16 plans of the multi-pass path (fft_size = No * 8192): 1 / fft_size itself is already a subnormal
@@ -209,6 +210,9 @@ int fused3_init_inner(fftconv_plan *p);
 // causal 16-bit shapes of fft 16384 and 32768 that are no multiple of 8 samples long: multi-pass plans by name and factors that run on
 // the single kernel
 bool fused3_odd_rows(const fftconv_plan *p);
+// which of their calls take the three passes all the same, on the single kernel's k_f; workspace rows (of a pair) that such calls need at most
+bool fused3_odd_few(const fftconv_plan *p, int64_t B, bool gated);
+int64_t fused3_odd_few_rows(const fftconv_plan *p);
 int fused3_inner_rows(const fftconv_plan *p, void *rows, const void *kf, int64_t rows_per_kf, int64_t kf_rows,
                       hipStream_t s, int ko_n = 0, int ko_lo = 0, int ko_hi = 0, bool quarter_rows = false);
 // the same kernel running the whole convolution of an 8192-point plan, u (B, H, N) -> y with N a multiple of 4

@@ -91,20 +91,22 @@ Cplx wpow(int64_t M, int64_t e)             // exp(-2 pi i e / M)
 Cplx cmulh(Cplx a, Cplx b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 Cplx conjh(Cplx a) { return {a.re, -a.im}; }
 
-// One MFMA operand (64 lanes x 8 16-bit slots) of the real form of a complex matrix G:
+// The two MFMA operands (64 lanes x 8 16-bit slots each) of the real form of a complex matrix G:
 // lane (c16, q), slot 2r+s multiplies data element e_in = 16 t + 4 q + r, part s (0 = re, 1 = im),
-// and contributes to output e_out = 16 ct + c16, part `part`.
+// and contributes to output e_out = 16 ct + c16, part re (the first operand) or im (the 512 slots behind it).
 template <typename Fn>
-void fill_operand(uint16_t *dst, bool f16, int t, int ct, int part, Fn G)
+void fill_operands(uint16_t *dst, bool f16, int t, int ct, Fn G)
 {
     for (int lane = 0; lane < 64; ++lane) {
         int c16 = lane % 16, q = lane / 16;
         for (int r = 0; r < 4; ++r) {
-            Cplx g = G(16 * t + 4 * q + r, 16 * ct + c16);
-            double v0 = part == 0 ? g.re : g.im;     // multiplies the real part of the data
-            double v1 = part == 0 ? -g.im : g.re;    // multiplies the imaginary part
-            dst[lane * 8 + 2 * r + 0] = f16 ? to_f16(v0) : to_bf16(v0);
-            dst[lane * 8 + 2 * r + 1] = f16 ? to_f16(v1) : to_bf16(v1);
+            const Cplx g = G(16 * t + 4 * q + r, 16 * ct + c16);
+            const uint16_t re = f16 ? to_f16(g.re) : to_bf16(g.re), im = f16 ? to_f16(g.im) : to_bf16(g.im);
+            uint16_t *const o = dst + lane * 8 + 2 * r;
+            o[0] = re;                               // times the real part of the data
+            o[1] = im ^ 0x8000u;                     // times the imaginary part
+            o[512] = im;
+            o[513] = re;
         }
     }
 }
@@ -133,6 +135,14 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
     auto sub_n1 = [&](int n1) { return groups == 1 ? n1 : halves ? 0 : n1 % H1; };
     auto own_half = [&](int k1, int n2) { return !halves || ((n2 >= N2 / 2) == ((k1 & 1) != 0)); };
     const Cplx zero_c = {0.0, 0.0};
+    // of the plan's roots of unity where they are at hand (the same values)
+    const int64_t n_roots = (int64_t)p->roots.size();
+    const double2 *const roots = p->roots.data();
+    auto root = [&](int64_t m, int64_t e) -> Cplx {
+        if (m > n_roots) return wpow(m, e);
+        const double2 w = roots[(e & (m - 1)) * (n_roots / m)];
+        return {w.x, w.y};
+    };
     const bool f16 = p->dtype == FFTCONV_F16;
     const size_t n_u4 = (size_t)G::TAB1 + G::TAB2 + 2 * (size_t)G::TAB3 + G::TAB2I + G::TAB1I;
     const size_t n_f2 = (size_t)G::TWA + G::TWB;
@@ -142,52 +152,46 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
     const int cfmt = f16 ? 2 : 1;
     auto hi16 = [&](double v) { return f16 ? to_f16(v) : to_bf16(v); };
     size_t o = 0;
-    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 64; return d; };
+    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 128; return d; };
     // tab1 [K step][ct][part]: W_N1^{n1 k1}; zero-padded real input only meets K step 0 (n1 < 16)
     for (int ks = 0; ks < 2; ++ks)
         for (int ct = 0; ct < 2; ++ct)
-            for (int part = 0; part < 2; ++part)
-                fill_operand(next(), f16, ks, ct, part, [&](int n1, int k1) {
-                    if (groups > 1 && (n1 >= 16 || g_of_n1(n1) != g_of_k1(k1))) return zero_c;
-                    return wpow(N1s, (int64_t)sub_n1(n1) * (k1 % N1s));
-                });
+            fill_operands(next(), f16, ks, ct, [&](int n1, int k1) {
+                if (groups > 1 && (n1 >= 16 || g_of_n1(n1) != g_of_k1(k1))) return zero_c;
+                return root(N1s, (int64_t)sub_n1(n1) * (k1 % N1s));
+            });
     // tab2 [n3][t][ct][part]: W_N2^{n2 k2} W_{N2 N3}^{k2 n3}
     for (int n3 = 0; n3 < N3; ++n3)
         for (int t = 0; t < G::R2; ++t)
             for (int ct = 0; ct < G::R2; ++ct)
-                for (int part = 0; part < 2; ++part)
-                    fill_operand(next(), f16, t, ct, part, [&](int n2, int k2) {
-                        return cmulh(wpow(N2, (int64_t)n2 * k2), wpow((int64_t)N2 * N3, (int64_t)k2 * n3));
-                    });
+                fill_operands(next(), f16, t, ct, [&](int n2, int k2) {
+                    return cmulh(root(N2, (int64_t)n2 * k2), root((int64_t)N2 * N3, (int64_t)k2 * n3));
+                });
     // tab3 [t][ct][part]: W_N3^{n3 k3}, output rows in the k3 order of k3_at_index()
     for (int t = 0; t < G::R3; ++t)
         for (int ct = 0; ct < G::R3; ++ct)
-            for (int part = 0; part < 2; ++part)
-                fill_operand(next(), f16, t, ct, part,
-                             [&](int n3, int idx) { return wpow(N3, (int64_t)n3 * k3_at_index(idx, N3)); });
+            fill_operands(next(), f16, t, ct,
+                          [&](int n3, int idx) { return root(N3, (int64_t)n3 * k3_at_index(idx, N3)); });
     // tab3i: conj(W_N3^{k3 n3}), contraction slots in the same k3 order
     for (int t = 0; t < G::R3; ++t)
         for (int ct = 0; ct < G::R3; ++ct)
-            for (int part = 0; part < 2; ++part)
-                fill_operand(next(), f16, t, ct, part,
-                             [&](int idx, int n3) { return conjh(wpow(N3, (int64_t)n3 * k3_at_index(idx, N3))); });
+            fill_operands(next(), f16, t, ct,
+                          [&](int idx, int n3) { return conjh(root(N3, (int64_t)n3 * k3_at_index(idx, N3))); });
     // tab2i [k1][t][ct][part]: conj(W_N2^{k2 n2} W_{N1 N2}^{k1 n2})
     for (int k1 = 0; k1 < N1; ++k1)
         for (int t = 0; t < G::R2; ++t)
             for (int ct = 0; ct < G::R2; ++ct)
-                for (int part = 0; part < 2; ++part)
-                    fill_operand(next(), f16, t, ct, part, [&](int k2, int n2) {
-                        if (!own_half(k1, n2)) return zero_c;
-                        return conjh(cmulh(wpow(N2, (int64_t)n2 * k2), wpow((int64_t)N1s * N2, (int64_t)(k1 % N1s) * n2)));
-                    });
+                fill_operands(next(), f16, t, ct, [&](int k2, int n2) {
+                    if (!own_half(k1, n2)) return zero_c;
+                    return conjh(cmulh(root(N2, (int64_t)n2 * k2), root((int64_t)N1s * N2, (int64_t)(k1 % N1s) * n2)));
+                });
     // tab1i [K step][row tile][part]: conj(W_N1^{k1 n1}); the causal kernel only forms row tile 0 (n1 < 16)
     for (int t = 0; t < 2; ++t)
         for (int rt = 0; rt < 2; ++rt)
-            for (int part = 0; part < 2; ++part)
-                fill_operand(next(), f16, t, rt, part, [&](int k1, int n1) {
-                    if (groups > 1 && (n1 >= 16 || g_of_n1(n1) != g_of_k1(k1))) return zero_c;
-                    return conjh(wpow(N1s, (int64_t)sub_n1(n1) * (k1 % N1s)));
-                });
+            fill_operands(next(), f16, t, rt, [&](int k1, int n1) {
+                if (groups > 1 && (n1 >= 16 || g_of_n1(n1) != g_of_k1(k1))) return zero_c;
+                return conjh(root(N1s, (int64_t)sub_n1(n1) * (k1 % N1s)));
+            });
     if (o != n_u4) {
         set_error("fused3: operand table size mismatch");
         return FFTCONV_EINVAL;
@@ -200,7 +204,7 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
                 for (int r = 0; r < 4; ++r)
                     for (int lane = 0; lane < 64; ++lane) {
                         int k1 = 16 * ct + lane % 16, n2 = 16 * rt + 4 * (lane / 16) + r;
-                        Cplx v = own_half(k1, n2) ? wpow(Ms, (int64_t)(k1 % N1s) * ((int64_t)N3 * n2 + n3)) : zero_c;
+                        Cplx v = own_half(k1, n2) ? root(Ms, (int64_t)(k1 % N1s) * ((int64_t)N3 * n2 + n3)) : zero_c;
                         tw16[w] = ctw_const(v.re, v.im, cfmt, hi16);
                         tw[w++] = make_float2((float)v.re, (float)v.im);
                     }
@@ -211,7 +215,7 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
                 for (int r = 0; r < 4; ++r)
                     for (int lane = 0; lane < 64; ++lane) {
                         int n3 = 16 * ct3 + lane % 16, k2 = 16 * ct2 + 4 * (lane / 16) + r;
-                        Cplx v = conjh(wpow(Ms, ((int64_t)(k1 % N1s) + (int64_t)N1s * k2) * n3));
+                        Cplx v = conjh(root(Ms, ((int64_t)(k1 % N1s) + (int64_t)N1s * k2) * n3));
                         tw16[w] = ctw_const(v.re, v.im, cfmt, hi16);
                         tw[w++] = make_float2((float)v.re, (float)v.im);
                     }
@@ -339,13 +343,34 @@ int fused3_init_inner(fftconv_plan *p)
     hipDeviceProp_t prop;
     FC_HIP(hipGetDeviceProperties(&prop, p->device));
     p->f3.num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    return p->f3.odd ? fused3_big_init(p) : build_tables<16, 16>(p, &p->f3.consts);
+    if (!p->f3.odd) return build_tables<16, 16>(p, &p->f3.consts);
+    FC_TRY(fused3_big_init(p));
+    return fused3_odd_few_rows(p) > 0 ? build_tables<16, 16>(p, &p->f3.consts_few) : FFTCONV_OK;
 }
 
 // k_f of all channels within the kernel's 32-bit addressing (launch_big)
 bool fused3_odd_rows(const fftconv_plan *p)
 {
     return (p->M == 16384 || p->M == 32768) && p->N >= 8 && p->N <= p->M / 2 && p->N % 8 != 0 && p->H * p->M * 4 < ((int64_t)1 << 31);
+}
+
+// Calls of few odd rows of fft 32768 go in three passes, which spread a pair over the chip; the single kernel takes as long for one pair as for
+// one on every compute unit.  us, three passes (k_f gathered, 0.5 - 1 of it), single kernel, N = 10007 / 16383:
+//   one row     H =  8 bf16 16.3, 18.3 / 16.2, 18.9   f16 16.4, 17.0 / 16.2, 17.6   gated bf16 16.6, 21.6 / 16.9, 22.6   f16 17.3, 20.2 / 16.7, 21.6
+//                   24      17.6, 18.4 / 17.4, 19.0       17.3, 17.0 / 17.2, 17.7              18.2, 21.8 / 18.3, 22.9       18.1, 20.4 / 17.6, 21.9
+//                   40      19.9, 18.5 / 19.9, 19.2       20.1, 17.2 / 19.5, 17.8       48:    20.8, 21.8 / 21.0, 23.0       21.2, 20.7 / 20.5, 22.1
+//   B even, pairs: 16       17.5, 18.5 / 17.6, 18.8       17.6, 17.2 / 17.4, 17.7              18.5, 21.4 / 18.2, 21.4       18.0, 20.2 / 18.8, 21.3
+//                  32       19.5, 18.7 / 20.0, 19.1       19.7, 17.3 / 20.1, 18.1              20.6, 21.4 / 20.9, 21.6       20.6, 20.4 / 20.8, 21.3
+// An odd batch beyond one row would be six launches (28 us and more).  At fft 16384 the single kernel is the faster one from the first pair on.
+constexpr int64_t FEW_LONE = 24, FEW_LONE_GATED = 48, FEW_PAIRS = 16, FEW_PAIRS_GATED = 32;
+bool fused3_odd_few(const fftconv_plan *p, int64_t B, bool gated)
+{
+    if (!p->f3.odd || p->M != 32768) return false;
+    return B == 1 ? p->H <= (gated ? FEW_LONE_GATED : FEW_LONE) : B % 2 == 0 && B / 2 * p->H <= (gated ? FEW_PAIRS_GATED : FEW_PAIRS);
+}
+int64_t fused3_odd_few_rows(const fftconv_plan *p)
+{
+    return p->f3.odd && p->M == 32768 && p->H <= FEW_LONE_GATED ? FEW_LONE_GATED : 0;
 }
 
 // ko_n > 0: the k_f rows come in groups of ko_n (outer frequency digit ko); only ko < ko_lo and ko >= ko_hi
@@ -358,7 +383,7 @@ int fused3_inner_rows(const fftconv_plan *p, void *rows, const void *kf, int64_t
         if (ko_lo >= ko_hi) ko_n = 0;                            // everything live
         else live_rows = kf_rows / ko_n * (ko_lo + ko_n - ko_hi);
     }
-    return fused3_wsc_launch(p, rows, kf, rows_per_kf, live_rows, s, ko_n, ko_lo, ko_hi, quarter_rows);
+    return fused3_wsc_launch(p, rows, kf, rows_per_kf, live_rows, s, ko_n, ko_lo, ko_hi, quarter_rows, p->f3.odd);
 }
 
 int fused3_inner_whole(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
@@ -370,7 +395,8 @@ void fused3_destroy(fftconv_plan *p)
 {
     if (p->f3.consts) (void)hipFree(p->f3.consts);
     if (p->f3.consts_short) (void)hipFree(p->f3.consts_short);
-    p->f3.consts = nullptr;
+    if (p->f3.consts_few) (void)hipFree(p->f3.consts_few);
+    p->f3.consts = p->f3.consts_few = nullptr;
     p->f3.consts_short = nullptr;
 }
 

@@ -58,34 +58,6 @@ template <int N2> struct BigGeo {
     static_assert((size_t)OFF_TWA == U4 * 16 && 32 * PLANEW == M * 4, "table layout");
 };
 
-// Order of the innermost digit (n3 in time, k3 in frequency; 32 values) inside phase B: slot
-// m = 16 tile + 4 q + r of a stage-3 operand or result holds digit sigma(m).  Tile 0 holds the
-// 16 digits nearest zero on the circle ({0..7} and {24..31}), tile 1 the rest.  k3 is the most
-// significant digit of the natural frequency, so a filter whose spectrum is confined to low
-// |f| (Appendix A.4: sparsity in the first dimension of k_f) leaves tile 1 of k3 empty, and the
-// HALF3 kernels skip its matrix products, its k_f and its share of the inverse contraction.
-// The same order on both digits keeps the stage-3 matrix symmetric (see the conjugation trick
-// above); on the n3 side it only changes which LDS rows a lane addresses.
-__host__ __device__ inline int big_sigma(int m)
-{
-    const int t = m / 16, q = (m % 16) / 4, r = m % 4;
-    const int base = t == 0 ? (q < 2 ? 4 * q : 16 + 4 * q) : 8 + 4 * q;
-    return base + r;
-}
-__host__ __device__ inline int big_sigma_inv(int d)
-{
-    if (d < 8) return d;
-    if (d >= 24) return d - 16;
-    return 16 + (d - 8);
-}
-// Order of the middle frequency digit k2: slot m (16 tile + position in the tile) of a stage-2 result, of the
-// exchange buffer, of k_f and of the twiddle tables holds digit big_tau<N2>(m).  With 32 values (fft 32768) it is
-// the order above, so that the low-pass set of the digit -- the values nearest the two ends of its range, see
-// fftconv_filter_fft_sparse_digits -- falls into tile 0 and the HALF2 kernels can leave tile 1 out: its stage-2
-// rows, its columns of stage 3 and of the inverse stage 3, its share of the inverse stage-2 contraction, its k_f
-// and twiddles (Appendix A.4: sparsity in the second dimension of k_f).  With 16 values there is one tile.
-template <int N2> __host__ __device__ inline int big_tau(int m) { return N2 == 32 ? big_sigma(m) : m; }
-
 // The constant block of a plan, one allocation (byte offsets in BigGeo):
 //   tab1   [ct][part][lane] uint4                  W_32^{n1 k1}, n1 < 16
 //   tab1i  [K step][part][lane]                    conj(W_32^{k1 n1}), n1 < 16

@@ -414,7 +414,7 @@ int fused3_ws_launch(const fftconv_plan *p, const void *consts, const void *u, c
 // wave-specialised kernel for complex rows of length 8192, in place (fused3_wsc.hip): the inner step of the
 // multi-pass scheme
 int fused3_wsc_launch(const fftconv_plan *p, void *rows, const void *kf, int64_t rows_per_kf, int64_t live_rows,
-                      hipStream_t s, int ko_n, int ko_lo, int ko_hi, bool quarter_rows);
+                      hipStream_t s, int ko_n, int ko_lo, int ko_hi, bool quarter_rows, bool big_kf);
 // the same kernel running a whole 8192-point convolution (u and y in place of the rows; N a multiple of 4)
 int fused3_wsc_real_launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
 
@@ -427,6 +427,41 @@ int fused3_big_forward(const fftconv_plan *p, const void *u, const void *kf, voi
                        hipStream_t s, uint32_t live_k2 = 0xffffffffu, uint32_t live_k1 = 0xffffffffu);
 int fused3_big_forward_gated(const fftconv_plan *p, const void *u, const void *wg, const void *vg, const void *kf, void *y,
                              int64_t B, hipStream_t s);
+
+// The streamed-table kernels (fused3_big.hip).  Order of the innermost digit (n3 in time, k3 in frequency; 32 values) inside phase B: slot
+// m = 16 tile + 4 q + r of a stage-3 operand or result holds digit sigma(m).  Tile 0 holds the
+// 16 digits nearest zero on the circle ({0..7} and {24..31}), tile 1 the rest.  k3 is the most
+// significant digit of the natural frequency, so a filter whose spectrum is confined to low
+// |f| (Appendix A.4: sparsity in the first dimension of k_f) leaves tile 1 of k3 empty, and the
+// HALF3 kernels skip its matrix products, its k_f and its share of the inverse contraction.
+// The same order on both digits keeps the stage-3 matrix symmetric (see the conjugation trick
+// above); on the n3 side it only changes which LDS rows a lane addresses.
+__host__ __device__ inline int big_sigma(int m)
+{
+    const int t = m / 16, q = (m % 16) / 4, r = m % 4;
+    const int base = t == 0 ? (q < 2 ? 4 * q : 16 + 4 * q) : 8 + 4 * q;
+    return base + r;
+}
+__host__ __device__ inline int big_sigma_inv(int d)
+{
+    if (d < 8) return d;
+    if (d >= 24) return d - 16;
+    return 16 + (d - 8);
+}
+// Order of the middle frequency digit k2: slot m (16 tile + position in the tile) of a stage-2 result, of the
+// exchange buffer, of k_f and of the twiddle tables holds digit big_tau<N2>(m).  With 32 values (fft 32768) it is
+// the order above, so that the low-pass set of the digit -- the values nearest the two ends of its range, see
+// fftconv_filter_fft_sparse_digits -- falls into tile 0 and the HALF2 kernels can leave tile 1 out: its stage-2
+// rows, its columns of stage 3 and of the inverse stage 3, its share of the inverse stage-2 contraction, its k_f
+// and twiddles (Appendix A.4: sparsity in the second dimension of k_f).  With 16 values there is one tile.
+template <int N2> __host__ __device__ inline int big_tau(int m) { return N2 == 32 ? big_sigma(m) : m; }
+
+// Slot of the bin k1 + 32 k2 + 1024 k3 in the k_f of a channel of fft 32768: [k1][k2 tile][k3 tile][r][lane]
+__host__ __device__ inline int big_kf_slot(int k1, int k2, int k3)
+{
+    const int m2 = big_sigma_inv(k2), m3 = big_sigma_inv(k3);
+    return (((k1 * 2 + m2 / 16) * 2 + m3 / 16) * 4 + m3 % 4) * 64 + m3 % 16 / 4 * 16 + m2 % 16;
+}
 
 // 16 bytes at any element of a 16-bit row: the hardware takes vector accesses at any address in this ABI's mode
 __device__ __forceinline__ uint4 load16(const uint16_t *p)

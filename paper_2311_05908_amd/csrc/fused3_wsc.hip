@@ -70,7 +70,11 @@ __device__ __forceinline__ void redefine(uint32_t &c) { asm volatile("" : "+v"(c
 // length 1), an item is a pair of batch rows of u (row 2*pair as the real, row 2*pair+1 as the imaginary part; samples
 // from N on are zero and are not read) and the real / imaginary parts of the result are the first N samples of the two
 // rows of y.  A lane's piece is then 4 consecutive samples (8 bytes) of either row; N is a multiple of 4, Hlive = H.
-template <typename TT, int MODE>
+//
+// BIG_KF (fft 32768, groups of four rows): k_f is that of the single kernel (big_kf_slot), for calls of few rows on its plans.  The bin of row ko
+// and inner digits k1, k2, k3 is ko + 4 (k1 + 32 k2 + 512 k3): of its digits there the first, ko + 4 (k1 mod 8), moves with the plane, the
+// others belong to the lane and the register.  (Four-byte gathers; such a call reads the k_f of 48 channels at most.)
+template <typename TT, int MODE, bool BIG_KF = false>
 __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_t *__restrict__ kf, Consts cs, int npairs,
                                                   int Hlive, int KoN, int ko_lo, int ko_hi, const uint16_t *__restrict__ u,
                                                   uint16_t *__restrict__ y, int B, int N, LaunchGate gate)
@@ -327,14 +331,25 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
         }
         // k_f of item t, plane i of this wave (k1 = 8 wq + i): four constants per lane
         auto kf_ptr = [&](int t) {
-            return kf + (size_t)row_of(t / npairs) * G::KF_PER_H + (size_t)(8 * wq) * 256 + l;
+            const int row = row_of(t / npairs);
+            if constexpr (BIG_KF) return kf + (size_t)(row / 4) * (4 * G::M) + big_kf_slot(row % 4, 0, 0);
+            else return kf + (size_t)row * G::KF_PER_H + (size_t)(8 * wq) * 256 + l;
+        };
+        int big_ofs[BIG_KF ? 4 : 1];
+        if constexpr (BIG_KF) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) big_ofs[r] = big_kf_slot(0, wq + 4 * (c16 & 7), (c16 >> 3) + 2 * k3_at_index(4 * q + r, 16));
+        }
+        auto kf_at = [&](int i, int r) {
+            if constexpr (BIG_KF) return big_kf_slot(4 * i, 0, 0) + big_ofs[r];
+            else return (i * 4 + r) * 64;
         };
         {
             const uint32_t *src = kf_ptr(t0);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) kfr[i][r] = src[(i * 4 + r) * 64];
+                for (int r = 0; r < 4; ++r) kfr[i][r] = src[kf_at(i, r)];
         }
         vmem_settled();
         lds_barrier();                                            // step t0 - 1: nothing to do yet
@@ -369,7 +384,7 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
                     const uint4 x3i = cmul4<TT, TT>(dre, dim, kfr[i]);
                     // this plane's constants of the next item (the same row again while the item's k_f row stays)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) kfr[i][r] = kf_next[(i * 4 + r) * 64];
+                    for (int r = 0; r < 4; ++r) kfr[i][r] = kf_next[kf_at(i, r)];
                     // inverse stage 3: rows k2, contraction over k3
                     dre = TT::mfma(x3i, tab3i[0], zero4);
                     dim = TT::mfma(x3i, tab3i[1], zero4);
@@ -391,9 +406,9 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
 
 }  // namespace
 
-// rows_per_kf rows per k_f row, `live_rows` live k_f rows (see the kernel for ko_n, ko_lo, ko_hi)
+// rows_per_kf rows per k_f row, `live_rows` live k_f rows (see the kernel for ko_n, ko_lo, ko_hi, BIG_KF)
 int fused3_wsc_launch(const fftconv_plan *p, void *rows, const void *kf, int64_t rows_per_kf, int64_t live_rows,
-                      hipStream_t s, int ko_n, int ko_lo, int ko_hi, bool quarter_rows)
+                      hipStream_t s, int ko_n, int ko_lo, int ko_hi, bool quarter_rows, bool big_kf)
 {
     const int64_t T = live_rows * rows_per_kf;
     if (T >= ((int64_t)1 << 31) - 8) {
@@ -402,12 +417,13 @@ int fused3_wsc_launch(const fftconv_plan *p, void *rows, const void *kf, int64_t
     }
     if (T <= 0) return FFTCONV_OK;
     const bool f16 = p->dtype == FFTCONV_F16;
-    auto kern = f16 ? (quarter_rows ? k_fused3_wsc<H16, 1> : k_fused3_wsc<H16, 0>)
-                    : (quarter_rows ? k_fused3_wsc<B16, 1> : k_fused3_wsc<B16, 0>);
+    auto kern = big_kf ? (f16 ? k_fused3_wsc<H16, 1, true> : k_fused3_wsc<B16, 1, true>)
+                : f16  ? (quarter_rows ? k_fused3_wsc<H16, 1> : k_fused3_wsc<H16, 0>)
+                       : (quarter_rows ? k_fused3_wsc<B16, 1> : k_fused3_wsc<B16, 0>);
     FC_TRY(raise_dynamic_lds((const void *)kern, (int)WSC_LDS_BYTES));
     const int grid = (int)(T < p->f3.num_cu ? T : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), WSC_LDS_BYTES, s, (uint32_t *)rows, (const uint32_t *)kf,
-                       consts_at<16, 16>(p->f3.consts), (int)rows_per_kf, (int)live_rows, ko_n, ko_lo, ko_hi,
+                       consts_at<16, 16>(big_kf ? p->f3.consts_few : p->f3.consts), (int)rows_per_kf, (int)live_rows, ko_n, ko_lo, ko_hi,
                        (const uint16_t *)nullptr, (uint16_t *)nullptr, 0, 0, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;

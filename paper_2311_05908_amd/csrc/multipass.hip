@@ -1316,9 +1316,10 @@ size_t multipass_kf_bytes(const fftconv_plan *p)
 
 size_t multipass_workspace_bytes(const fftconv_plan *p, int64_t B)
 {
-    if (p->f3.odd) return 0;
-    const int64_t npairs = (B + 1) / 2;
-    return (size_t)(npairs * p->H * p->M) * sizeof(uint32_t);
+    int64_t rows = (B + 1) / 2 * p->H;
+    // (a larger batch that needs none: enough for a smaller one that does)
+    if (p->f3.odd && rows > fused3_odd_few_rows(p)) rows = fused3_odd_few_rows(p);
+    return (size_t)(rows * p->M) * sizeof(uint32_t);
 }
 
 int multipass_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh, const uint8_t *keep_dev,
@@ -1446,7 +1447,7 @@ int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void
                       hipStream_t s, int ko_lo, int ko_hi, const void *wg, const void *vg)
 {
     uint32_t *S = (uint32_t *)workspace;
-    if (p->f3.odd) return f3::fused3_big_forward_odd(p, u, wg, vg, kf, y, B, s);
+    if (p->f3.odd && !fused3_odd_few(p, B, wg || vg)) return f3::fused3_big_forward_odd(p, u, wg, vg, kf, y, B, s);
     // fft_size 8192 (outer length 1: a circular or ragged shape the causal kernel does not take): the inner kernel
     // reads u and writes y itself, nothing passes through the workspace.  Gated calls and N not a multiple of 4
     // (rows that start off an 8-byte boundary) keep the three passes.
