@@ -1148,18 +1148,13 @@ int launch_big(const fftconv_plan *p, const void *u, const void *kf, void *y, in
         return FFTCONV_EUNSUPPORTED;
     }
     // persistent workgroups, as many as are resident at once (two per compute unit for the smaller
-    // size: 80 KB of LDS and 128 registers each), a multiple of 8 (see the kernel's work split)
+    // size: 80 KB of LDS and 128 registers each).  us, f16 16 x 1 x 8192 of fft 16384 55 -> 9.7 where all pairs go in turn (with what the last pair
+    // of a workgroup no longer prepares); one row of 37 channels of fft 32768, 10007 bf16 samples, 33 as two steps of 32, 19
     const int64_t resident = (int64_t)p->f3.num_cu * ((N2 == 16 && !GATED) ? 2 : 1);
-    int grid = (int)(T < resident ? T : resident);
-    if (grid >= 8) grid -= grid % 8;
-    // a die's channels one after another, unless that takes more steps of a workgroup than all items in turn: us, f16
-    // 16 x 1 x 8192 of fft 16384 55 -> 9.7 (with what the last pair of a workgroup no longer prepares)
-    const int64_t pairs = (B + 1) / 2, steps = (T + grid - 1) / grid;
-    const int nx = grid % 8 == 0 && ((p->H + 7) / 8 * pairs + grid / 8 - 1) / (grid / 8) <= steps ? 8 : 1;
-    if (nx == 1) grid = (int)(T < resident ? T : resident);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), BG::LDS_BYTES, s, (const uint16_t *)u, (uint16_t *)y,
+    const BigSplit split = big_split(p->H, (B + 1) / 2, resident);
+    hipLaunchKernelGGL(kern, dim3((unsigned)split.grid), dim3(NT), BG::LDS_BYTES, s, (const uint16_t *)u, (uint16_t *)y,
                        kf, (const void *)p->f3.consts, (uint32_t)kf_bytes, (int)B, (int)p->H, (int)p->N,
-                       (const uint16_t *)wg, (const uint16_t *)vg, live_k1, nx, launch_gate());
+                       (const uint16_t *)wg, (const uint16_t *)vg, live_k1, split.nx, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }

@@ -26,6 +26,17 @@ inline LongRows long_row_pairs(int64_t first, int64_t H, int64_t rows)
 // 2^31 - 9 of them, counted in 32 bits, so that the last one plus a step may lie beyond; batch rows are counted in 32 bits as well, up to the
 // number of a pair's second one.
 inline bool big_items_fit(int64_t B, int64_t H) { return B < INT32_MAX && H * ((B + 1) / 2) < ((int64_t)1 << 31) - 8; }
+// Workgroups, and the dies (8, or 1: all items in turn) they are dealt to, for H channels of `pairs` items on a chip that holds `resident` of them at
+// once.  A die's channels one after another, unless that takes more steps of a workgroup than all items in turn on as many workgroups
+// as there can be (not only on a multiple of 8 of them: 37 items are one step of 37, but two of 32).
+struct BigSplit { int grid, nx; };
+inline BigSplit big_split(int64_t H, int64_t pairs, int64_t resident)
+{
+    const int64_t items = H * pairs, most = items < resident ? items : resident, steps = (items + most - 1) / most;
+    const int64_t each = most / 8;                                  // workgroups of a die
+    if (each > 0 && ((H + 7) / 8 * pairs + each - 1) / each <= steps) return BigSplit{(int)(8 * each), 8};
+    return BigSplit{(int)most, 1};
+}
 __host__ __device__ inline bool big_item_follows(int v, int step, int items) { return v < items - step; }
 
 }  // namespace fftconv

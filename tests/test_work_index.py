@@ -27,6 +27,9 @@ int main()
             int v = (int)a, n = 1;
             for (; fftconv::big_item_follows(v, (int)b, (int)c); v += (int)b) ++n;
             std::printf("%d %d\\n", v, n);
+        } else if (what == 'g') {                         // a channels of b items on a chip of c workgroups
+            const fftconv::BigSplit g = fftconv::big_split(a, b, c);
+            std::printf("%d %d\\n", g.grid, g.nx);
         } else {                                          // a batch rows of b channels
             std::printf("%d 0\\n", (int)fftconv::big_items_fit(a, b));
         }
@@ -77,3 +80,19 @@ def test_item_limits(program):
     not_ = [((1 << 31) - 1, 1), (1 << 32, 1), ((1 << 32) + 4, 1), ((1 << 31) - 9, 2), (2, (1 << 31) - 8), (1 << 20, 1 << 20)]
     assert answers(program, [("f", B, H, 0, 0) for B, H in fits]) == [(1, 0)] * len(fits)
     assert answers(program, [("f", B, H, 0, 0) for B, H in not_]) == [(0, 0)] * len(not_)
+
+
+def test_split_of_items(program):
+    """As few steps of a workgroup as all the chip's workgroups allow, channels dealt to the dies where that takes no more; H = 37 and 65 took two steps."""
+    shapes = [(H, pairs, resident) for H in (1, 2, 7, 8, 9, 15, 16, 17, 37, 40, 64, 65, 100, 255, 256, 257, 300, 768, 1032)
+              for pairs in (1, 2, 3, 8, 17, 32, 255) for resident in (256, 512, 304, 4)]
+    for (H, pairs, resident), (grid, nx) in zip(shapes, answers(program, [("g", H, p, r, 0) for H, p, r in shapes])):
+        items = H * pairs
+        best = -(-items // min(items, resident))
+        assert 1 <= grid <= min(items, resident) and (nx == 1 or (nx == 8 and grid % 8 == 0))
+        # die x: channels x, x + nx, ...; its workgroups take its items in turn
+        steps = max(-(-len(range(x, H, nx)) * pairs // (grid // nx)) for x in range(nx))
+        assert steps == best, (H, pairs, resident, grid, nx)
+        if nx == 1 and resident >= 8 and items >= 8:
+            each = min(items, resident) // 8
+            assert -(-(-(-H // 8) * pairs) // each) > best
