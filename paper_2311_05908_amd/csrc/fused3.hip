@@ -355,18 +355,16 @@ bool fused3_odd_rows(const fftconv_plan *p)
 }
 
 // Calls of few odd rows of fft 32768 go in three passes, which spread a pair over the chip; the single kernel takes as long for one pair as for
-// one on every compute unit.  us, three passes (k_f gathered, 0.5 - 1 of it), single kernel, N = 10007 / 16383:
-//   one row     H =  8 bf16 16.3, 18.3 / 16.2, 18.9   f16 16.4, 17.0 / 16.2, 17.6   gated bf16 16.6, 21.6 / 16.9, 22.6   f16 17.3, 20.2 / 16.7, 21.6
-//                   24      17.6, 18.4 / 17.4, 19.0       17.3, 17.0 / 17.2, 17.7              18.2, 21.8 / 18.3, 22.9       18.1, 20.4 / 17.6, 21.9
-//                   40      19.9, 18.5 / 19.9, 19.2       20.1, 17.2 / 19.5, 17.8       48:    20.8, 21.8 / 21.0, 23.0       21.2, 20.7 / 20.5, 22.1
-//   B even, pairs: 16       17.5, 18.5 / 17.6, 18.8       17.6, 17.2 / 17.4, 17.7              18.5, 21.4 / 18.2, 21.4       18.0, 20.2 / 18.8, 21.3
-//                  32       19.5, 18.7 / 20.0, 19.1       19.7, 17.3 / 20.1, 18.1              20.6, 21.4 / 20.9, 21.6       20.6, 20.4 / 20.8, 21.3
+// one on every compute unit.  us, three passes, single kernel, N = 10007:
+//   one row,  H =  8: bf16 14.1, 18.3, gated 14.6, 21.6;  24: 15.2, 18.4, 15.6, 21.8;  36: 17.2, 18.5, 17.9, 21.8;  48: 18.8 (*), 18.6, 19.2, 21.8;
+//                  64: 20.8 (*), 18.6, 20.9, 22.1;  fp16 36: 17.0, 17.1, 17.4, 20.6;  64: 20.8 (*), 17.4, 20.9, 20.7        (*: with a k_f of their own)
+//   B even, 16 pairs: bf16 15.1, 18.5, gated 15.8, 21.4;  32: 17.6, 18.8, 18.2, 21.6;  fp16 17.3, 17.4, 17.8, 20.4;  33 bf16 19.6 (*), 18.6, 21.4 (*), 21.6
 // An odd batch beyond one row would be six launches (28 us and more).  At fft 16384 the single kernel is the faster one from the first pair on.
-constexpr int64_t FEW_LONE = 24, FEW_LONE_GATED = 48, FEW_PAIRS = 16, FEW_PAIRS_GATED = 32;
+constexpr int64_t FEW_LONE = 40, FEW_LONE_GATED = 64, FEW_PAIRS = 32;
 bool fused3_odd_few(const fftconv_plan *p, int64_t B, bool gated)
 {
     if (!p->f3.odd || p->M != 32768) return false;
-    return B == 1 ? p->H <= (gated ? FEW_LONE_GATED : FEW_LONE) : B % 2 == 0 && B / 2 * p->H <= (gated ? FEW_PAIRS_GATED : FEW_PAIRS);
+    return B == 1 ? p->H <= (gated ? FEW_LONE_GATED : FEW_LONE) : B % 2 == 0 && B / 2 * p->H <= FEW_PAIRS;
 }
 int64_t fused3_odd_few_rows(const fftconv_plan *p)
 {

@@ -72,8 +72,9 @@ __device__ __forceinline__ void redefine(uint32_t &c) { asm volatile("" : "+v"(c
 // rows of y.  A lane's piece is then 4 consecutive samples (8 bytes) of either row; N is a multiple of 4, Hlive = H.
 //
 // BIG_KF (fft 32768, groups of four rows): k_f is that of the single kernel (big_kf_slot), for calls of few rows on its plans.  The bin of row ko
-// and inner digits k1, k2, k3 is ko + 4 (k1 + 32 k2 + 512 k3): of its digits there the first, ko + 4 (k1 mod 8), moves with the plane, the
-// others belong to the lane and the register.  (Four-byte gathers; such a call reads the k_f of 48 channels at most.)
+// and inner digits k1, k2, k3 is ko + 4 (k1 + 32 k2 + 512 k3), of digits ko + 4 (k1 mod 8), k1 / 8 + 4 (k2 mod 8) and k2 / 8 + 2 k3 there.  An inner
+// wave then takes the planes k1 = wave + 4 i instead of eight in a row: four of them, i and every other one, lie side by side in a channel's
+// k_f, and eight loads of 16 bytes fetch a row's constants whole (one row, four channels: 11.4 us with a load for each bin, 9.1 so; 9.3 with k_f in its own order).
 template <typename TT, int MODE, bool BIG_KF = false>
 __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_t *__restrict__ kf, Consts cs, int npairs,
                                                   int Hlive, int KoN, int ko_lo, int ko_hi, const uint16_t *__restrict__ u,
@@ -314,6 +315,7 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
     } else {
         // =========================== inner role: phase B ===========================
         const int wq = w - 4;
+        auto plane = [&](int i) { return BIG_KF ? 4 * i + wq : 8 * wq + i; };      // k1 of this wave's planes
         uint4 tab3[2], tab3i[2], tab2i[8][2];
         uint32_t twb[8][4], kfr[8][4];                            // fp16 pairs; pairs of the I/O type
 #pragma unroll
@@ -323,33 +325,37 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int c = 8 * wq + i;
+            const int c = plane(i);
 #pragma unroll
             for (int p = 0; p < 2; ++p) tab2i[i][p] = cs.tab2i[(c * 2 + p) * 64 + l];
 #pragma unroll
             for (int r = 0; r < 4; ++r) twb[i][r] = tw_f16(cs.twb[(c * 4 + r) * 64 + l]);
         }
-        // k_f of item t, plane i of this wave (k1 = 8 wq + i): four constants per lane
+        // k_f of item t, plane i of this wave: four constants per lane
         auto kf_ptr = [&](int t) {
+            return kf + (size_t)row_of(t / npairs) * G::KF_PER_H + (size_t)(8 * wq) * 256 + l;
+        };
+        auto load_big = [&](int t) {
             const int row = row_of(t / npairs);
-            if constexpr (BIG_KF) return kf + (size_t)(row / 4) * (4 * G::M) + big_kf_slot(row % 4, 0, 0);
-            else return kf + (size_t)row * G::KF_PER_H + (size_t)(8 * wq) * 256 + l;
-        };
-        int big_ofs[BIG_KF ? 4 : 1];
-        if constexpr (BIG_KF) {
+            const uint32_t *src = kf + (size_t)(row / 4) * (4 * G::M) + big_kf_slot(row % 4 + 4 * wq, 0, 0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) big_ofs[r] = big_kf_slot(0, wq + 4 * (c16 & 7), (c16 >> 3) + 2 * k3_at_index(4 * q + r, 16));
-        }
-        auto kf_at = [&](int i, int r) {
-            if constexpr (BIG_KF) return big_kf_slot(4 * i, 0, 0) + big_ofs[r];
-            else return (i * 4 + r) * 64;
+            for (int r = 0; r < 4; ++r) {
+                const int ofs = big_kf_slot(0, 4 * (c16 & 7), (c16 >> 3) + 2 * k3_at_index(4 * q + r, 16));
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint4 v = *(const uint4 *)(src + ofs + big_kf_slot(16 * i, 0, 0));
+                    kfr[i][r] = v.x, kfr[i + 2][r] = v.y, kfr[i + 4][r] = v.z, kfr[i + 6][r] = v.w;
+                }
+            }
         };
-        {
+        if constexpr (BIG_KF) {
+            load_big(t0);
+        } else {
             const uint32_t *src = kf_ptr(t0);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) kfr[i][r] = src[kf_at(i, r)];
+                for (int r = 0; r < 4; ++r) kfr[i][r] = src[(i * 4 + r) * 64];
         }
         vmem_settled();
         lds_barrier();                                            // step t0 - 1: nothing to do yet
@@ -363,11 +369,11 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
             {
                 uint32_t *XB = XBb + (s & 1) * XBW;
                 const bool more = s + 1 < t1;
-                const uint32_t *kf_next = kf_ptr(more ? s + 1 : s);
+                const uint32_t *kf_next = BIG_KF ? nullptr : kf_ptr(more ? s + 1 : s);
                 // operand of stage 3 for plane k1: columns k2 = c16, slots = (re, im) of n3 = 4q + r;
                 // read two planes ahead of the one being computed
                 auto read_plane = [&](int i) {
-                    const uint32_t *src = XB + (4 * q) * G::PN3 + (8 * wq + i) * G::PK1 + c16;
+                    const uint32_t *src = XB + (4 * q) * G::PN3 + plane(i) * G::PK1 + c16;
                     return make_uint4(src[0], src[G::PN3], src[2 * G::PN3], src[3 * G::PN3]);
                 };
                 uint4 xq[3];
@@ -375,7 +381,7 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
                 for (int i = 0; i < 2; ++i) xq[i] = read_plane(i);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int c = 8 * wq + i;
+                    const int c = plane(i);
                     if (i + 2 < 8) xq[(i + 2) % 3] = read_plane(i + 2);
                     const uint4 x3v = xq[i % 3];
                     // stage 3: matrix rows k3, data columns k2
@@ -383,8 +389,10 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
                     f32x4 dim = TT::mfma(tab3[1], x3v, zero4);
                     const uint4 x3i = cmul4<TT, TT>(dre, dim, kfr[i]);
                     // this plane's constants of the next item (the same row again while the item's k_f row stays)
+                    if constexpr (!BIG_KF) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) kfr[i][r] = kf_next[kf_at(i, r)];
+                        for (int r = 0; r < 4; ++r) kfr[i][r] = kf_next[(i * 4 + r) * 64];
+                    }
                     // inverse stage 3: rows k2, contraction over k3
                     dre = TT::mfma(x3i, tab3i[0], zero4);
                     dim = TT::mfma(x3i, tab3i[1], zero4);
@@ -396,6 +404,9 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
                     uint32_t *dst = XB + c16 * G::PN3 + c * G::PK1 + 4 * q;
                     *(uint4 *)dst = make_uint4(TT::pack(dre[0], dim[0]), TT::pack(dre[1], dim[1]),
                                                TT::pack(dre[2], dim[2]), TT::pack(dre[3], dim[3]));
+                }
+                if constexpr (BIG_KF) {
+                    if (more) load_big(s + 1);
                 }
             }
             lds_barrier();

@@ -153,10 +153,10 @@ def test_odd_rows_need_no_workspace(dtype, M):
     assert torch.equal(plan.forward_freq_sparse_digits(u, kf, digits), y)
     assert torch.equal(plan.forward_partial(u, kf, 100), y)
     assert torch.equal(plan.forward_gated(u, torch.ones_like(u), None, kf), y)
-    for h in (1, 3, 33, 48):
+    for h in (1, 3, 33, 64):
         small = fftconv.Plan(N, M, h, dtype)
         sizes = [small.workspace_bytes(b) for b in range(1, 140)]
-        assert sizes == sorted(sizes) and max(sizes) == (48 * M * 4 if M == 32768 else 0)
+        assert sizes == sorted(sizes) and max(sizes) == (64 * M * 4 if M == 32768 else 0)
         assert sizes == [small.workspace_bytes_gated(b) for b in range(1, 140)]
 
 
@@ -172,7 +172,7 @@ def test_odd_rows_in_three_passes(dtype, M, B, H, N, shift):
     (_, cu), (_, cw), (_, cv) = (placed(t, shift) for t in (u, w, v))
     one, three = fftconv.Plan(N, M, H, dtype), fftconv.Plan(N, M, H, dtype, path="multipass")
     assert three.path == one.path and three.factors == one.factors
-    assert one.workspace_bytes(B) <= 48 * M * 4 and three.workspace_bytes(B) == (B + 1) // 2 * H * M * 4
+    assert one.workspace_bytes(B) <= 64 * M * 4 and three.workspace_bytes(B) == (B + 1) // 2 * H * M * 4
     for gated in (False, True):
         ud = u.double() * (w.double() if gated else 1.0)
         ref = conv(ud, k.double(), N) * (v.double() if gated else 1.0)
@@ -191,9 +191,8 @@ def test_odd_rows_in_three_passes(dtype, M, B, H, N, shift):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("B,H,gated", [
-    (1, 1, False), (1, 24, False), (1, 25, False), (1, 48, True), (1, 49, True),       # the lines of a single row
-    (2, 16, False), (2, 17, False), (32, 1, False), (34, 1, False), (2, 32, True), (2, 33, True), (64, 1, True), (66, 1, True),
-    (8, 4, False), (3, 1, False), (3, 1, True),
+    (1, 1, False), (1, 40, False), (1, 41, False), (1, 64, True), (1, 65, True),       # the lines of a single row
+    (2, 32, False), (2, 33, False), (64, 1, False), (66, 1, True), (2, 32, True), (8, 4, False), (3, 1, False), (3, 1, True),
 ])
 @pytest.mark.parametrize("N,shift", [(9, 1), (10007, 3), (16382, 1)])
 def test_calls_of_few_odd_rows(dtype, B, H, gated, N, shift):
