@@ -25,9 +25,13 @@ using rf::Row;
 
 constexpr int SLOTS = 8192;                                       // of a channel, whatever the transform's length
 
-template <int M> constexpr bool IMAGE = M <= 1024;                // one channel per workgroup, one group's slots in LDS
-template <int M> constexpr int ROWS = IMAGE<M> ? 1 : rf::threads_of(M) / Row<M>::T;      // channels per workgroup
-template <int M> constexpr int LDS_BYTES = ROWS<M> * Row<M>::LDS_BYTES + (IMAGE<M> ? 8 * M : 0);
+// The gradient's tail.  One channel per workgroup, one group's slots in LDS: up to 1024 points, and where the runs of 2048 are added up (their
+// slots lie scattered for a thread: 2.9 us for a run's spectrum, and those of two runs more than the second saved)
+template <int M, bool RUNS> constexpr bool IMAGE = M <= 1024 || (RUNS && M == 2048);
+template <int M, bool RUNS> constexpr int ROWS = IMAGE<M, RUNS> ? 1 : rf::threads_of(M) / Row<M>::T;      // channels per workgroup
+// rows of the engine in a workgroup (2048 points: the second one repeats the first, unstored)
+template <int M> constexpr int CHAINS = M <= 1024 ? 1 : rf::threads_of(M) / Row<M>::T;
+template <int M, bool RUNS> constexpr int LDS_BYTES = CHAINS<M> * Row<M>::LDS_BYTES + (IMAGE<M, RUNS> ? 8 * M : 0);
 
 // HALF: Nk <= M / 2.  conj_out: the conjugate spectrum, that of the circularly time-reversed taps, which are real.  k_f
 // scaled by 1/M and by the frequency mask, one (re, im) pair of the I/O type a bin.
@@ -97,49 +101,61 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     k_row_dk_finish(const float2 *__restrict__ dkf, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk, int runs)
 {
     using G = Row<M>;
-    constexpr int RW = ROWS<M>, NTHR = rf::threads_of(M);
+    constexpr int RW = ROWS<M, RUNS>, NTHR = rf::threads_of(M);
     extern __shared__ float2 smem_rows[];
-    const int row = IMAGE<M> ? 0 : threadIdx.x / G::T, tid = IMAGE<M> ? threadIdx.x : threadIdx.x % G::T;
-    const int h = min((int)blockIdx.x * RW + row, H - 1);
+    const int row = CHAINS<M> == 1 ? 0 : threadIdx.x / G::T, tid = CHAINS<M> == 1 ? threadIdx.x : threadIdx.x % G::T;
+    const int h = IMAGE<M, RUNS> ? (int)blockIdx.x : min((int)blockIdx.x * RW + row, H - 1);
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     float2 x[G::P];
     const float2 *in = dkf + (int64_t)h * SLOTS;
-    if constexpr (IMAGE<M>) {
-        float2 *const image = (float2 *)((char *)smem_rows + G::LDS_BYTES);
+    if constexpr (IMAGE<M, RUNS>) {
+        float2 *const image = (float2 *)((char *)smem_rows + CHAINS<M> * G::LDS_BYTES);
+        constexpr int D = M / NTHR;
+        static_assert(D * NTHR == M, "whole slots to a thread");
+        float2 sum[D];
+        auto add = [&](const float2 *spec, bool first) {           // all of a spectrum in flight at once
+            float2 v[D][SLOTS / M];
 #pragma unroll
-        for (int d = threadIdx.x; d < M; d += NTHR) {
-            float2 v[SLOTS / M];
+            for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int g = 0; g < SLOTS / M; ++g) v[g] = in[g * M + d];
+                for (int g = 0; g < SLOTS / M; ++g) v[d][g] = spec[g * M + d * NTHR + threadIdx.x];
 #pragma unroll
-            for (int g = 1; g < SLOTS / M; ++g) {
-                v[0].x += v[g].x;
-                v[0].y += v[g].y;
-            }
-            for (int i = 1; RUNS && i < runs; ++i) {
-                const float2 *const next = in + (int64_t)i * H * SLOTS;
-                float2 t[SLOTS / M];
-#pragma unroll
-                for (int g = 0; g < SLOTS / M; ++g) t[g] = next[g * M + d];
+            for (int d = 0; d < D; ++d)
 #pragma unroll
                 for (int g = 0; g < SLOTS / M; ++g) {
-                    v[0].x += t[g].x;
-                    v[0].y += t[g].y;
+                    sum[d].x = first && g == 0 ? v[d][g].x : sum[d].x + v[d][g].x;
+                    sum[d].y = first && g == 0 ? v[d][g].y : sum[d].y + v[d][g].y;
                 }
-            }
-            image[d] = v[0];
-        }
+        };
+        add(in, true);
+#pragma unroll 1
+        for (int i = 1; RUNS && i < runs; ++i) add(in + (int64_t)i * H * SLOTS, false);
+#pragma unroll
+        for (int d = 0; d < D; ++d) image[d * NTHR + threadIdx.x] = sum[d];
         __syncthreads();
-        if (tid >= G::T) return;
+        if (CHAINS<M> == 1 && tid >= G::T) return;
 #pragma unroll
         for (int p = 0; p < G::P; ++p) x[p] = image[rf::slot_of<G>(tid, p)];
     } else {
+        // (those of 2048 points, no base and immediates, are formed once: 6.8 us for few channels, 7.8 with each group's anew)
+        int kept[M == 2048 ? G::P : 1];
+        if constexpr (M == 2048) {
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = in[rf::slot_of<G>(tid, p)];
+            for (int p = 0; p < G::P; ++p) {
+                kept[p] = rf::slot_of<G>(tid, p);
+                asm("" : "+v"(kept[p]));
+            }
+        }
+        auto slot = [&](int p) {
+            if constexpr (M == 2048) return kept[p];
+            else return rf::slot_of<G>(tid, p);
+        };
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) x[p] = in[slot(p)];
         auto add = [&](const float2 *spec) {
             float2 v[G::P];
 #pragma unroll
-            for (int p = 0; p < G::P; ++p) v[p] = spec[rf::slot_of<G>(tid, p)];
+            for (int p = 0; p < G::P; ++p) v[p] = spec[slot(p)];
 #pragma unroll
             for (int p = 0; p < G::P; ++p) {
                 x[p].x += v[p].x;
@@ -154,7 +170,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
     rf::inverse<G>(x, Z, tab, tw1, tid);
-    if ((int)blockIdx.x * RW + row >= H) return;
+    if (IMAGE<M, RUNS> ? row > 0 : (int)blockIdx.x * RW + row >= H) return;
     float *const o = dk + (int64_t)h * Nk;
 #pragma unroll
     for (int m = 0; m < G::P; ++m) {
@@ -267,8 +283,9 @@ int row_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, float *d
         if constexpr (G::M > SLOTS) {
             return FFTCONV_EUNSUPPORTED;
         } else {
-            constexpr int NTHR = rf::threads_of(G::M), RW = ROWS<G::M>, lds = LDS_BYTES<G::M>;
+            constexpr int NTHR = rf::threads_of(G::M);
             const auto kern = runs > 1 ? k_row_dk_finish<G::M, true> : k_row_dk_finish<G::M, false>;
+            const int RW = runs > 1 ? ROWS<G::M, true> : ROWS<G::M, false>, lds = runs > 1 ? LDS_BYTES<G::M, true> : LDS_BYTES<G::M, false>;
             FC_TRY(raise_dynamic_lds((const void *)kern, lds));
             hipLaunchKernelGGL(kern, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float2 *)dkf,
                                dk, rf::row_table<G>(p), (int)p->H, Nk, (int)runs);
