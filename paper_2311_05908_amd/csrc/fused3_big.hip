@@ -665,9 +665,10 @@ __global__ void __launch_bounds__(NT, (N2 == 16 && !GATED) ? 4 : 2) k_fused3_big
 // at N2 = 16 and would be 2 x 128 at N2 = 32, where the kernel therefore walks through a channel's pairs twice,
 // each time keeping one k3 tile of the bins (phase A is repeated, stage 3 is not) with the spectrum of u held as
 // 16-bit pairs (32 registers; the accumulator stays fp32).  One workgroup per compute unit.
-// runs > 1 (fewer channels than compute units; gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's
-// pairs, dkf[run][h], and k_big_dk_blocks adds the runs up.
-template <typename TT, bool FULL, int N2>
+// RUNS: runs > 1 (fewer channels than compute units; gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's
+// pairs, dkf[run][h], and k_big_dk_blocks adds the runs up.  (Code of its own: the run's first pair costs the instances of ragged rows at N2 = 16, which have
+// no register left, three more reloads from scratch memory for every input; fp16 3 x 300 x 8192 of fft 16384 49 -> 54 us.)
+template <typename TT, bool FULL, int N2, bool RUNS>
 __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restrict__ u, const uint16_t *__restrict__ dy,
                                                          float2 *__restrict__ dkf, const void *__restrict__ consts, int B,
                                                          int H, int N, int runs)
@@ -682,10 +683,10 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
     extern __shared__ uint32_t XB[];
     const int tid = threadIdx.x, l = tid & 63, q = l >> 4, c16 = l & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int run = runs > 1 ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
-    const int all_pairs = (B + 1) / 2, pair0 = (int)((int64_t)all_pairs * run / runs);
-    const int npairs = (int)((int64_t)all_pairs * (run + 1) / runs) - pair0;
-    const int nch = runs > 1 ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;      // channels h = blockIdx.x + j gridDim.x
+    const int run = RUNS ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
+    const int all_pairs = (B + 1) / 2, pair0 = RUNS ? run_start(all_pairs, run, runs) : 0;
+    const int npairs = RUNS ? run_start(all_pairs, run + 1, runs) - pair0 : all_pairs;
+    const int nch = RUNS ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;      // channels h = blockIdx.x + j gridDim.x
     const int S = nch * NPASS * npairs * 2;                // inputs: ((j * NPASS + pass) * npairs + pair) * 2 + (0 = u, 1 = dy)
     if (S <= 0) return;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -1366,11 +1367,16 @@ static int big_dk_accumulate_t(const fftconv_plan *p, const void *u, const void 
     using BG = BigGeo<N2>;
     const bool full = (B % 2 == 0) && p->N == BG::M / 2;
     const bool f16 = p->dtype == FFTCONV_F16;
-    void (*kern)(const uint16_t *, const uint16_t *, float2 *, const void *, int, int, int, int) =
-        f16 ? (full ? k_fused3_big_dk<H16, true, N2> : k_fused3_big_dk<H16, false, N2>)
-            : (full ? k_fused3_big_dk<B16, true, N2> : k_fused3_big_dk<B16, false, N2>);
-    FC_TRY(raise_dynamic_lds((const void *)kern, (int)BG::LDS_BYTES));
     const int64_t runs = fused3_big_dk_runs(p, B);
+    using Kern = void (*)(const uint16_t *, const uint16_t *, float2 *, const void *, int, int, int, int);
+    static const Kern table[2][2][2] = {
+        {{k_fused3_big_dk<B16, false, N2, false>, k_fused3_big_dk<B16, false, N2, true>},
+         {k_fused3_big_dk<B16, true, N2, false>, k_fused3_big_dk<B16, true, N2, true>}},
+        {{k_fused3_big_dk<H16, false, N2, false>, k_fused3_big_dk<H16, false, N2, true>},
+         {k_fused3_big_dk<H16, true, N2, false>, k_fused3_big_dk<H16, true, N2, true>}},
+    };
+    const Kern kern = table[f16][full][runs > 1];
+    FC_TRY(raise_dynamic_lds((const void *)kern, (int)BG::LDS_BYTES));
     const int grid = (int)(p->H < p->f3.num_cu ? p->H * runs : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), BG::LDS_BYTES, s, (const uint16_t *)u, (const uint16_t *)dy,
                        (float2 *)dkf, (const void *)p->f3.consts, (int)B, (int)p->H, (int)p->N, (int)runs);

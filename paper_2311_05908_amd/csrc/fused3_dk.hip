@@ -37,8 +37,8 @@ constexpr int PCH = G::M / 8 / PT;            // 16-byte input chunks per outer-
 // input (fused3.hip, build_tables): positions [g * half, (g + 1) * half) of an input's 4096-sample slot,
 // half = 2^lg_half = fft_size / 2, hold rows 2 (pair * groups + g), + 1.  The accumulator then holds one
 // spectrum per group (slots k1 = g * (32 / groups) + k1'), which the unpacking step adds up.
-// runs > 1 (gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's pairs; dkf[run][h].
-template <typename TT, bool FULL>
+// RUNS: runs > 1 (gridDim.x = runs * H): workgroup run * H + h sums the run's share of channel h's pairs; dkf[run][h].
+template <typename TT, bool FULL, bool RUNS>
 __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u, const uint16_t *__restrict__ dy,
                                                  float2 *__restrict__ dkf, Consts cs, int B, int H, int N, int groups,
                                                  int lg_half, int runs)
@@ -52,9 +52,10 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
     // channels of this workgroup: h = blockIdx.x + j * gridDim.x; its input stream: index
     // s = (j * npairs + pair) * 2 + which, which = 0 for the u rows of the pair, 1 for the dy rows
     const int all_pairs = (B + 2 * groups - 1) / (2 * groups);
-    const int run = runs > 1 ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
-    const int pair0 = (int)((int64_t)all_pairs * run / runs), npairs = (int)((int64_t)all_pairs * (run + 1) / runs) - pair0;
-    const int nch = runs > 1 ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int run = RUNS ? (int)blockIdx.x / H : 0, h_first = (int)blockIdx.x - run * H;
+    const int pair0 = RUNS ? run_start(all_pairs, run, runs) : 0;
+    const int npairs = RUNS ? run_start(all_pairs, run + 1, runs) - pair0 : all_pairs;
+    const int nch = RUNS ? 1 : (H - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int S = nch * npairs * 2;
     if (S <= 0) return;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -240,13 +241,15 @@ bool fused3_dk_supported(const fftconv_plan *p) { return p->path == PATH_FUSED3 
 
 // Runs of a channel's pairs: a workgroup for every compute unit, no more than there are pairs, and no more than pay for their sum
 // (5 us for a pair, 0.65 us for adding up a run's spectrum, one after another in row_dk_finish).  Whole gradient, us, bf16 fft 8192,
-// one run -> these: 64 x 4 rows 104 -> 39, 64 x 128 114 -> 73, 16 x 1 36 -> 27.
+// one run -> these: 64 x 4 rows 104 -> 39, 64 x 128 114 -> 73, 16 x 1 36 -> 27.  Up to 1024 points runs of two or
+// three pairs of many channels do not pay (fft 1024, 48 x 85 rows 21.3, 22.0, 48 x 60 20.6, 18.3; fft 256, 128 x 100 rows 16.2, 16.5).
 int64_t fused3_dk_runs(const fftconv_plan *p, int64_t B)
 {
     const int64_t groups = G::M / p->M, npairs = (B + 2 * groups - 1) / (2 * groups);
     int64_t runs = p->f3.num_cu / p->H;
     if (runs > npairs) runs = npairs;
     while (runs > 1 && runs * runs > 8 * npairs) --runs;
+    if (p->M <= 1024 && npairs <= 3 && p->H > 64) runs = 1;
     return runs < 1 ? 1 : runs;
 }
 
@@ -268,11 +271,14 @@ int fused3_dk_accumulate(const fftconv_plan *p, const void *u, const void *dy, v
     }
     const bool full = (B % (2 * groups) == 0) && p->N == G::M / 2 / groups;
     const bool f16 = p->dtype == FFTCONV_F16;
-    void (*kern)(const uint16_t *, const uint16_t *, float2 *, Consts, int, int, int, int, int, int) =
-        f16 ? (full ? k_fused3_dk<F16, true> : k_fused3_dk<F16, false>)
-            : (full ? k_fused3_dk<BF16, true> : k_fused3_dk<BF16, false>);
-    FC_TRY(raise_dynamic_lds((const void *)kern, (int)DK_LDS_BYTES));
     const int64_t runs = fused3_dk_runs(p, B);
+    using Kern = void (*)(const uint16_t *, const uint16_t *, float2 *, Consts, int, int, int, int, int, int);
+    static const Kern table[2][2][2] = {
+        {{k_fused3_dk<BF16, false, false>, k_fused3_dk<BF16, false, true>}, {k_fused3_dk<BF16, true, false>, k_fused3_dk<BF16, true, true>}},
+        {{k_fused3_dk<F16, false, false>, k_fused3_dk<F16, false, true>}, {k_fused3_dk<F16, true, false>, k_fused3_dk<F16, true, true>}},
+    };
+    const Kern kern = table[f16][full][runs > 1];
+    FC_TRY(raise_dynamic_lds((const void *)kern, (int)DK_LDS_BYTES));
     const int grid = (int)(p->H < p->f3.num_cu ? p->H * runs : p->f3.num_cu);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), DK_LDS_BYTES, s, (const uint16_t *)u, (const uint16_t *)dy,
                        (float2 *)dkf, consts_at<16, 16>(p->f3.consts), (int)B, (int)p->H, (int)p->N, groups, lg_half,
