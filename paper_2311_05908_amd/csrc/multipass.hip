@@ -364,7 +364,7 @@ template <int RA, int RB> constexpr int INV_TB = RB == 1 && RA >= 8 ? TB / 2 : T
 template <int RA, int RB> constexpr int INV_WAVES = RB == 1 && RA >= 8 ? 3 : 4;
 template <bool F16, int RA, int RB, int CV, bool FULLN, bool GATED, bool MIRROR, bool EXACT>
 __global__ void __launch_bounds__((INV_TB<RA, RB>), (INV_WAVES<RA, RB>)) k_outer_inv(const uint32_t *__restrict__ S, uint16_t *__restrict__ y, int ct,
-                                                 int B, int H, int N, int ko_lo, int ko_hi, int mirror_from,
+                                                 int B, int H, int N, int ko_lo, int ko_hi,
                                                  const uint16_t *__restrict__ vg, LaunchGate gate)
 {
     extern __shared__ float2 sm[];
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__((INV_TB<RA, RB>), (INV_WAVES<RA, RB>)) k_outer
     }
     constexpr float im = 1.0f / (float)((int64_t)No * MI);       // exact, and so are r ko / M (r < 8192, ko < 512)
     // step 1: T[ka*RB + b2] = conj(W_No^{ka b2}) * sum_{kb} conj(W_RB^{b2 kb}) conj(W_M^{r ko}) S[ko], ko = ka + RA kb
-    // MIRROR (mirror_from == No/2 + 1): rows ko > No/2 were never computed (a lone real row, see multipass_forward): before the
+    // MIRROR: rows ko > No/2 were never computed (a lone real row, see multipass_forward): before the
     // twiddle row ko is the complex conjugate of row ko' = No - ko, i.e.
     //   conj(W_M^{r ko}) S[ko] = conj(conj(W_M^{r ko'}) S[ko']),   W_M^{r ko'} = W_Mi^{r} conj(W_M^{r ko}),
     // so the value that enters the inverse is conj(S[ko']) conj(conj(W_Mi^{r}) W_M^{r ko}): the mirror row is
@@ -1172,7 +1172,7 @@ OuterGeo outer_geo(int64_t M, int64_t rows = 0)
 
 template <bool F16, int RA, int RB, bool FULLN, bool GATED, bool EXACT>
 int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, void *dst, int B, int H, int N,
-                   hipStream_t s, int ko_lo, int ko_hi, int mirror_from, const void *gate)
+                   hipStream_t s, int ko_lo, int ko_hi, bool mirror, const void *gate)
 {
     // two columns per thread while the registers allow and while that still leaves an entry for every thread
     // (at No = 256 a block has 32 columns: 16 x 32 / 2 entries would keep half of its 512 threads idle)
@@ -1186,12 +1186,12 @@ int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, 
     if (!inverse)
         hipLaunchKernelGGL((k_outer_fwd<F16, RA, RB, CV, FULLN, GATED, EXACT>), grid, dim3(TB), lds, s, (const uint16_t *)src,
                            (uint32_t *)dst, g.CT, B, H, N, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
-    else if (mirror_from < g.No)
+    else if (mirror)
         hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, true, EXACT>), grid_inv, dim3(INV_TB<RA, RB>), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
     else
         hipLaunchKernelGGL((k_outer_inv<F16, RA, RB, CV, FULLN, GATED, false, EXACT>), grid_inv, dim3(INV_TB<RA, RB>), lds, s, (const uint32_t *)src,
-                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, mirror_from, (const uint16_t *)gate, launch_gate());
+                           (uint16_t *)dst, ct_inv, B, H, N, ko_lo, ko_hi, (const uint16_t *)gate, launch_gate());
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -1200,10 +1200,10 @@ int launch_outer_t(bool inverse, const OuterGeo &g, dim3 grid, const void *src, 
 // half (or, FULLN, the whole transform), so that no load or store needs a range check (ungated calls only)
 template <bool F16, int RA, int RB>
 int launch_outer(bool inverse, const OuterGeo &g, dim3 grid, const void *src, void *dst, int B, int H, int N, int64_t M,
-                 hipStream_t s, int ko_lo, int ko_hi, int mirror_from, const void *gate)
+                 hipStream_t s, int ko_lo, int ko_hi, bool mirror, const void *gate)
 {
 #define FFTCONV_OUTER(FULLN, GATED, EXACT) \
-    launch_outer_t<F16, RA, RB, FULLN, GATED, EXACT>(inverse, g, grid, src, dst, B, H, N, s, ko_lo, ko_hi, mirror_from, gate)
+    launch_outer_t<F16, RA, RB, FULLN, GATED, EXACT>(inverse, g, grid, src, dst, B, H, N, s, ko_lo, ko_hi, mirror, gate)
     if constexpr (RA >= 2) {
         if ((int64_t)N <= M / 2) {
             if (gate) return FFTCONV_OUTER(false, true, false);
@@ -1217,19 +1217,19 @@ int launch_outer(bool inverse, const OuterGeo &g, dim3 grid, const void *src, vo
 
 template <bool F16>
 int dispatch_outer(bool inverse, const OuterGeo &g, dim3 grid, const void *src, void *dst, int B, int H, int N,
-                   int64_t M, hipStream_t s, int ko_lo, int ko_hi, int mirror_from, const void *gate)
+                   int64_t M, hipStream_t s, int ko_lo, int ko_hi, bool mirror, const void *gate)
 {
     switch (g.No) {
-    case 1: return launch_outer<F16, 1, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 2: return launch_outer<F16, 2, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 4: return launch_outer<F16, 4, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 8: return launch_outer<F16, 8, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 16: return launch_outer<F16, 16, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 32: return launch_outer<F16, 16, 2>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 64: return launch_outer<F16, 16, 4>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 128: return launch_outer<F16, 16, 8>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 256: return launch_outer<F16, 16, 16>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
-    case 512: return launch_outer<F16, 16, 32>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror_from, gate);
+    case 1: return launch_outer<F16, 1, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 2: return launch_outer<F16, 2, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 4: return launch_outer<F16, 4, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 8: return launch_outer<F16, 8, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 16: return launch_outer<F16, 16, 1>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 32: return launch_outer<F16, 16, 2>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 64: return launch_outer<F16, 16, 4>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 128: return launch_outer<F16, 16, 8>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 256: return launch_outer<F16, 16, 16>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
+    case 512: return launch_outer<F16, 16, 32>(inverse, g, grid, src, dst, B, H, N, M, s, ko_lo, ko_hi, mirror, gate);
     default:
         set_error("multipass: unsupported outer length %d", g.No);
         return FFTCONV_EUNSUPPORTED;
@@ -1412,14 +1412,16 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
     const dim3 grid((unsigned)(MI / g.CT), (unsigned)rows);
     if (ko_lo >= ko_hi) ko_lo = ko_hi = g.No;            // nothing skipped
     // rows that passes A and B leave out, rows that pass C takes as zero, rows that pass C mirrors
-    int ab_lo = ko_lo, ab_hi = ko_hi, c_lo = ko_lo, c_hi = ko_hi, mirror_from = g.No;
+    int ab_lo = ko_lo, ab_hi = ko_hi, c_lo = ko_lo, c_hi = ko_hi;
+    bool mirror = false;
     if (packed) {
         // a sparse filter keeps ko < ko_lo and ko >= ko_hi = No - (ko_lo - 1), mirror images of each other: of the rows
         // ko <= No/2 those below ko_lo are live
         ab_lo = ko_lo < g.No / 2 + 1 ? ko_lo : g.No / 2 + 1;
         ab_hi = g.No;
     } else if (lone && g.No >= 4 && ko_lo >= ko_hi) {     // outer length 512: paired kernels, pass C mirrors the rows
-        mirror_from = ab_lo = g.No / 2 + 1;
+        mirror = true;
+        ab_lo = g.No / 2 + 1;
         ab_hi = g.No;
     }
     // the lone row's outer passes pack two columns into one complex transform where such kernels exist
@@ -1429,16 +1431,16 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
         rc = f16 ? dispatch_outer_real<true>(false, g, u, S, (int)p->H, (int)p->N, p->M, s, ab_lo, wg)
                  : dispatch_outer_real<false>(false, g, u, S, (int)p->H, (int)p->N, p->M, s, ab_lo, wg);
     else
-        rc = f16 ? dispatch_outer<true>(false, g, grid, u, S, (int)B, (int)p->H, (int)p->N, p->M, s, ab_lo, ab_hi, g.No, wg)
-                 : dispatch_outer<false>(false, g, grid, u, S, (int)B, (int)p->H, (int)p->N, p->M, s, ab_lo, ab_hi, g.No, wg);
+        rc = f16 ? dispatch_outer<true>(false, g, grid, u, S, (int)B, (int)p->H, (int)p->N, p->M, s, ab_lo, ab_hi, false, wg)
+                 : dispatch_outer<false>(false, g, grid, u, S, (int)B, (int)p->H, (int)p->N, p->M, s, ab_lo, ab_hi, false, wg);
     if (rc) return rc;
     rc = fused3_inner_rows(p, S, kf, npairs, p->H * g.No, s, g.No, ab_lo, ab_hi, multipass_quarter_rows(g.No));
     if (rc) return rc;
     if (packed)
         return f16 ? dispatch_outer_real<true>(true, g, S, y, (int)p->H, (int)p->N, p->M, s, ab_lo, vg)
                    : dispatch_outer_real<false>(true, g, S, y, (int)p->H, (int)p->N, p->M, s, ab_lo, vg);
-    return f16 ? dispatch_outer<true>(true, g, grid, S, y, (int)B, (int)p->H, (int)p->N, p->M, s, c_lo, c_hi, mirror_from, vg)
-               : dispatch_outer<false>(true, g, grid, S, y, (int)B, (int)p->H, (int)p->N, p->M, s, c_lo, c_hi, mirror_from, vg);
+    return f16 ? dispatch_outer<true>(true, g, grid, S, y, (int)B, (int)p->H, (int)p->N, p->M, s, c_lo, c_hi, mirror, vg)
+               : dispatch_outer<false>(true, g, grid, S, y, (int)B, (int)p->H, (int)p->N, p->M, s, c_lo, c_hi, mirror, vg);
 }
 
 // Batch rows are transformed two at a time (one complex transform per pair, the filter being real); a row left
