@@ -55,3 +55,36 @@ def test_outer_passes(M, B, H, n, shift):
         err = ((dk - ref).norm() / ref.norm()).item()
         print("outer passes M=%d N=%d dk err=%.3e" % (M, N, err), flush=True)
         assert err <= 2e-6
+
+
+@pytest.mark.parametrize("B", [1, 2, 3])
+@pytest.mark.parametrize("M", [8192 << lg for lg in range(10)])
+def test_rows_of_one_fp16_sample(M, B):
+    """The shortest rows in fp16 at every outer length.  Values within a quarter of 1, so that every row's bound is one number: some roundings
+    of 2^-11 (input gate, k_f, intermediates, output), and, as fp16 k_f and its products are kept at boost / fft_size (boost = min(fft_size / 8192, 64))
+    and are subnormal there from 2^20 points on, two roundings of 2^-25 fft_size / boost over the product's size, in a flat spectrum the same in every bin."""
+    H = 5
+    g = torch.Generator().manual_seed(M + B)
+
+    def near_one(*shape):
+        return (0.8 + 0.45 * torch.rand(*shape, generator=g)) * (1 - 2 * torch.randint(0, 2, shape, generator=g))
+
+    u, w, v = (near_one(B, H, 1).to(torch.float16) for _ in range(3))
+    k = near_one(H, 1)
+    plan = fftconv.Plan(1, M, H, "f16")
+    kf = plan.filter_fft(k.cuda())
+    (_, cu), (_, cw), (_, cv) = (placed(t, 1) for t in (u, w, v))
+    for name in ("y", "wv"):
+        buf, out = placed(torch.zeros_like(u), 1)
+        if name == "y":
+            plan.forward(cu, kf, out=out)
+            inner, ref = u.double() * k.double(), u.double() * k.double()
+        else:
+            plan.forward_gated(cu, cw, cv, kf, out=out)
+            inner = u.double() * w.double() * k.double()
+            ref = inner * v.double()
+        assert torch.isnan(buf[:1]).all() and torch.isnan(buf[1 + u.numel():]).all()
+        err = ((out.cpu().double() - ref).abs() / ref.abs()).max().item()
+        bound = 2.0 ** -9 + 2 * 2.0 ** -25 * M / min(M // 8192, 64) / inner.abs().min().item()
+        print("one sample f16 M=%d B=%d %s err=%.3e bound=%.3e" % (M, B, name, err, bound), flush=True)
+        assert err <= bound
