@@ -403,7 +403,7 @@ constexpr int64_t SHORT_MAX_P = 2048;      // most history a segment may carry (
 
 // Plans for fft >= 16384 (the single-kernel ones and the multi-pass route) also carry the 8192-point tables:
 // a short (partial) filter runs as overlapping 8192-point segments, and k_f then holds a second,
-// 8192-point spectrum (8 bytes per bin) after the dense one.
+// 8192-point spectrum (4 bytes per bin) after the dense one.
 int fused3_init_short(fftconv_plan *p)
 {
     if (p->M < 2 * SHORT_M || p->N > p->M / 2 || p->N % 8 != 0) return FFTCONV_OK;      // no segmented route

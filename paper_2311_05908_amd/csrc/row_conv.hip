@@ -211,19 +211,22 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 
 // Few rows: which calls of a matrix-core plan up to fft 4096 the row kernel takes.  Both kernels' times are staircases.  The
 // matrix-core kernel runs its work items (8192 / fft pairs of rows of one channel, however few there are) in rounds of one per
-// compute unit: 8 - 9 us for the first, 13, 16, 20 us for 2, 3, 4.
-// The row kernel runs workgroups of `rows` pairs: 7.5, 11, 14, 18 us for 1, 2, 3, 4 of them per compute unit (fft 2048 and
-// 4096; fft 512: 8, 12, 16, 20; fft 1024, a chain in half a wave: 8, 12, 16, 22).  So
+// compute unit: 8.9, 12.2, 15.7, 19.2, 24.6 us for 1, 2, 3, 4, 6 of them (bf16; with both gates 9.4, 14.4, 18.9, 22, 28.3).
+// The row kernel runs workgroups of `rows` pairs, us for 1, 2, 3, 4, 6 of them per compute unit (both gates):
+//   fft  512  8.6, 11.1, 13.8, 18.2, 24.7 (9.1, 13.1, 17.4, 23.6, 30.5)      fft 2048  8.3, 10.6, 13.0, 16.8, 23.3 (8.9, 11.8, 15.0, 19.2, 26.1)
+//   fft 1024  8.7, 11.5, 14.5, 19.2, 25.1 (9.5, 13.7, 18.0, 22.8, 30.5)      fft 4096  6.6, 8.2, 10.1, 12.3, 17.2 (7.2, 9.1, 12.0, 15.0, 20.5)
+// So
 //   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer; beyond six rounds half as many (fp16, 4096: one
-//     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116);
+//     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116).  The lines of 4096 are from before the
+//     row kernel became a quarter faster there: it is now the faster one with up to half as many workgroups again as there are rounds;
 //   fft 1024: half as many, and not in the first round (both 8 - 9 us there);
 //   fft 512: half as many, and only if items are not full;
 //   fft 256: 40 Ki pairs + 56 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, 256 42, 40; 8192
 //     channels: B = 33 98, 51, fp16 64 106, 116.
-// Measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
+// Lines measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
 // (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
 // calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
-// At 8192 points the row kernel never was the faster one (16 channels: 8.8 against 12.8).
+// At 8192 points the row kernel was not the faster one before it gained that quarter (16 channels: 8.8 against 12.8); not measured since.
 // The kernel counts rows and threads (at most M / 16 to a pair of rows) in 32 bits: calls beyond that are not few rows.
 bool row_few(int64_t M, int64_t H, int64_t B)
 {
