@@ -894,7 +894,9 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
             const int n = (a * RB + b2) * MI + r0 + 2 * cg;
             if constexpr (IN == 0) {
                 if (wide) {                        // Nk even, rows 8-byte aligned: a pair is inside or outside as a whole
-                    x[a] = ld_at<float2>(row0, n < Nk ? 4 * n : 0);
+                    // (from four rows to a thread's second factor up with 64-bit addresses: 64 channels of fft 2^21 425 -> 385 us the
+                    // filter transform, 2^20 202 -> 184; below, 16 x 100001 of fft 2^18, the offsets are the faster ones: 24.9, 25.4)
+                    x[a] = RB >= 4 ? *(const float2 *)(row0 + (int64_t)(n < Nk ? n : 0)) : ld_at<float2>(row0, n < Nk ? 4 * n : 0);
                 } else {
                     x[a].x = row0[n < Nk ? n : 0];
                     x[a].y = row0[n + 1 < Nk ? n + 1 : 0];
