@@ -665,14 +665,18 @@ int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 
 // inverse outer pass; k_f is the spectrum of real taps, so the product is the spectrum of a real sequence again) where outer
 // lengths have register kernels for real rows (multipass.hip).  That is half the blocks of a complex transform per row, the same as
 // a pair's share, with cheaper outer kernels.  Measured, pairs against real rows, us: faster from A = 32 up (2.8 against 3.3 ms for 2^27
-// samples at fft 2^18), at A = 8 (8 x 64 x 32768 175, 168), and at A = 4, where the rows ko <= A/2 are 3 of 4, as long as
-// there are few (16 x 1 x 16384 25, 19; 16 x 64 177, 186).  A = 16 (8 x 32 x 65536 180, 159) keeps to pairs, as real rows are a tenth less
+// samples at fft 2^18), at A = 8 up to 640 rows (64 rows 37.5, 31.4, 512 179, 177, 640 215, 212; 768 272, 279, 1024 364, 371, 2048 688, 752), and at A = 4,
+// where the rows ko <= A/2 are 3 of 4, where their blocks take no more rounds of the chip, two workgroups to a compute unit (8 rows 23.9, 16.8, 128
+// 34.3, 32.4, 320 71.1, 65.5; one round more 192 46.1, 48.6, 256 54.3, 56.1, 512 93.6, 96.4, 1024 177, 186).  A = 16 (8 x 32 x 65536 180, 159) keeps to pairs, as real rows are a tenth less
 // accurate there (3.45e-7, 3.80e-7; A = 8 3.55e-7, 3.51e-7; A = 4 3.29e-7, 3.20e-7).  A row without a partner goes as a real one,
 // or, where the chip has room, with the pairs and zeros for a partner.
+int64_t conv_real_most(int64_t A) { return A >= 32 ? INT64_MAX : A == 8 ? 640 : A == 4 ? 512 : 0; }
 bool conv_real(const fftconv_plan *p, int64_t B)
 {
-    const int64_t A = p->M / LB;
-    return multipass_filter_outer_ok(p) && (A >= 32 || A == 8 || (A == 4 && B * p->H <= 512));
+    const int64_t A = p->M / LB, H = p->H;
+    if (!multipass_filter_outer_ok(p) || B * H > conv_real_most(A)) return false;
+    auto rounds = [](int64_t blocks) { return (blocks + 511) / 512; };
+    return A != 4 || rounds(3 * B * H) <= rounds(4 * (B / 2 * H)) + rounds(3 * (B % 2 * H));
 }
 bool lone_in_pairs(const fftconv_plan *p, int64_t B) { return B > 1 && p->M / LB == 16 && (B + 1) / 2 * p->H * 16 <= 1024; }
 int64_t real_row(const fftconv_plan *p) { return (p->M / LB / 2 + 1) * LB; }
@@ -694,8 +698,8 @@ int64_t conv_pairs(const fftconv_plan *p, int64_t B)
         return (units < fit ? units : fit) * unit;
     };
     if (conv_real(p, B)) return pairs(B * p->H, real_row(p));
-    const int64_t n = pairs((B + 1) / 2 * p->H, p->M);
-    const int64_t few = p->M / LB == 4 ? pairs(512, real_row(p)) : 0;
+    const int64_t n = pairs((B + 1) / 2 * p->H, p->M), most = multipass_filter_outer_ok(p) ? conv_real_most(p->M / LB) : 0;
+    const int64_t few = most ? pairs(most < B * p->H ? most : B * p->H, real_row(p)) : 0;         // a smaller batch that goes as real rows
     return n > few ? n : few;
 }
 

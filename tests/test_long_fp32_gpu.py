@@ -55,3 +55,18 @@ def test_workspace_of_a_larger_batch(H, M):
     plan = fftconv.Plan(40, M, H, "f32")
     sizes = [plan.workspace_bytes(B) for B in range(1, 700)]
     assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("B,H,M", [
+    (2, 85, 32768), (2, 86, 32768),              # blocks of real rows in one round of the chip; in two, where those of pairs take one
+    (2, 160, 32768), (3, 100, 32768),            # two rounds either way; the lone rows in a round of their own
+    (2, 320, 65536), (2, 321, 65536), (3, 214, 65536),      # real rows up to 640 of them, pairs (and lone rows) beyond
+])
+def test_rows_on_either_side_of_the_lines(B, H, M):
+    N = 30
+    u, k = data(B, H, N)
+    plan = fftconv.Plan(N, M, H, "f32")
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda()), out=torch.full_like(u, float("nan"), device="cuda"))
+    assert parity_error(y.cpu().double().numpy(), reference(u, k).numpy(), TOL["f32"], "y") <= TOL["f32"]
+    sizes = [plan.workspace_bytes(b) for b in range(1, 40)]
+    assert sizes == sorted(sizes)
