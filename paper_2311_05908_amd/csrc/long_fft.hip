@@ -544,11 +544,12 @@ int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, c
 // rows of the block kernels' launches: their LDS and the plan's table
 constexpr int B_LDS = RB::LDS_BYTES;
 
-// Filter gradient of real rows: pairs of transformed rows of u and dy that a trip through the workspace aims at, 256 MiB.  us
-// with trips of 64, 128, 256 MiB, all at once: bf16 2 x 256 x 65536 545, 408, 402, 404; fp32 16 x 64 x 16384 fft 32768 510, 310, 231, 244;
-// bf16 64 rows of 2^20, one batch row 1196, 983, 911, 936; below, launches too short for the chip cost more than the memory-side
-// cache returns.
-constexpr int64_t GRAD_TRIP = (int64_t)1 << 25;
+// Filter gradient of real rows: pairs of transformed rows of u and dy in a trip through the workspace, as many as it holds, up to 2 GiB.  us
+// with trips of 128, 256, 768 MiB, all at once: bf16 64 rows of 2^20, two batch rows 1664, 1434, 1385, 1350, one 908, 807, 800, 783; fp32 64 rows of
+// 2^19, two batch rows 771, 752, 726, 713; bf16 2 x 256 x 65536 367, 376, 367, 369; launches too short for the chip cost more than the
+// memory-side cache returns.  The workspace: three spectra of a batch row, and no less than 256 MiB (fp32 16 x 64 x 16384 fft 32768 with
+// 64, 128, 256 MiB, all at once 510, 325, 246, 246).
+constexpr int64_t GRAD_TRIP = (int64_t)1 << 28, GRAD_LEAST = (int64_t)1 << 25;
 
 // nh channels of `blocks` blocks each; runs of batch rows where channels alone leave compute units idle: as many as fill the
 // chip (two workgroups to a unit), and no more than pay for adding them up (a run's sum takes about a sixteenth of the time of
@@ -579,7 +580,7 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
 int64_t grad_rows(const fftconv_plan *p)
 {
     const int64_t row = (p->M / LB / 2 + 1) * LB, all = 3 * p->H * p->M;
-    return (all > GRAD_TRIP ? all : GRAD_TRIP) / row;
+    return (all > GRAD_LEAST ? all : GRAD_LEAST) / row;
 }
 
 template <typename IO>
@@ -601,16 +602,17 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         // acc (+)= conj(U) DY on them -- and the sum, the spectrum of a real sequence again, goes back through the
         // inverse block transforms and the real inverse outer pass: half the intermediate traffic of the complex
         // pipeline below, and a row without a partner costs no more than half a pair.
-        // The channels go in trips of about GRAD_TRIP pairs of transformed rows of u and dy, with all batch rows where they fit,
+        // The channels go in trips of at most GRAD_TRIP pairs of transformed rows of u and dy, with all batch rows where they fit,
         // else in pieces with the sum so far behind them.
         const int NR = g.A / 2 + 1;
         const int64_t row = NR * (int64_t)LB, fit = grad_rows(p);
+        const int64_t trip = fit < GRAD_TRIP / row ? fit : GRAD_TRIP / row;
         int64_t nh = H;
-        if (2 * B * H > GRAD_TRIP / row) nh = GRAD_TRIP / row / (2 * B);
+        if (2 * B * H > trip) nh = trip / (2 * B);
         if (nh > 16384 / B) nh = 16384 / B;                       // rows of a launch
         if (nh < 1) nh = 1;
-        // (of up to a third fewer channels, the number whose blocks leave least of a round of the chip empty: bf16 2 x 256 x 65536,
-        // three trips of 86, 113 + 113 + 30: 402, 393 us)
+        // (of up to a third fewer channels, the number whose blocks leave least of a round of the chip empty: bf16 2 x 256 x 65536 in
+        // three trips, of 86, 113 + 113 + 30: 402, 393 us)
         auto full = [&](int64_t n) { return (double)(n * NR) / (double)((n * NR + 511) / 512); };
         for (int64_t n = nh - 1, most = nh; nh < H && 3 * n >= 2 * most; --n)
             if (full(n) > full(nh)) nh = n;
