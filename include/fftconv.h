@@ -196,8 +196,9 @@ int fftconv_forward_freq_sparse_digits(const fftconv_plan *plan, const void *u, 
                                        const int64_t *digit_keep, int ndigits, void *y,
                                        int64_t B, int64_t H, int64_t N, void *workspace, void *stream);
 
-/* Bytes of workspace fftconv_forward_gated needs for batch size B: fftconv_workspace_bytes plus,
- * for plans whose kernel does not fuse the gates, room for the gated input (B*H*N elements). */
+/* Bytes of workspace fftconv_forward_gated asks for at batch size B: fftconv_workspace_bytes plus, for
+ * "small" and "staged" plans (fftconv_plan_path), room for a gated input (B*H*N elements), which their
+ * kernels no longer touch. */
 size_t fftconv_workspace_bytes_gated(const fftconv_plan *plan, int64_t B);
 
 /* Gated convolution (Section 3.1 "Domain-Specific Optimizations"; Section 4.1):
@@ -206,10 +207,8 @@ size_t fftconv_workspace_bytes_gated(const fftconv_plan *plan, int64_t B);
  *   side; both NULL is fftconv_forward).  v must not alias y.
  * Arithmetic: the product u . w is rounded to the I/O dtype (nearest even) before the transform
  * (it is what the matrix cores consume); the output gate multiplies the convolution result after
- * it has been rounded to the I/O dtype, and the product is rounded again.  Plans whose path
- * (fftconv_plan_path) is "fused3" or "multipass" apply both gates inside their kernels (u, w, v each read
- * once, y written once, no extra workspace); "small" and "staged" plans run one elementwise kernel per
- * gate around fftconv_forward.
+ * it has been rounded to the I/O dtype, and the product is rounded again.  Every plan applies both gates
+ * inside its kernels (u, w, v each read once, y written once).
  * workspace: at least fftconv_workspace_bytes_gated(plan, B) bytes, may be NULL when that is 0. */
 int fftconv_forward_gated(const fftconv_plan *plan, const void *u, const void *w, const void *v, const void *k_f,
                           void *y, int64_t B, int64_t H, int64_t N, void *workspace, void *stream);

@@ -625,7 +625,8 @@ size_t fftconv_workspace_bytes_gated(const fftconv_plan *p, int64_t B)
 {
     if (!p || B <= 0) return 0;
     const size_t base = fftconv_workspace_bytes(p, B);
-    if (fused3_gates_fused(p) || p->path == PATH_MULTIPASS) return base;       // gates fused into the plan's kernels
+    if (fused3_gates_fused(p) || p->path == PATH_MULTIPASS) return base;
+    // (the kernels of the other plans fuse the gates too; the room that a gated input took is still asked for, as callers know it)
     return align256(base) + (size_t)(B * p->H * p->N) * elem_bytes(p);
 }
 
@@ -649,17 +650,8 @@ int fftconv_forward_gated(const fftconv_plan *p, const void *u, const void *w, c
     if (fused3_gates_fused(p)) return fused3_forward_gated(p, u, w, v, k_f, y, B, s);
     if (p->path == PATH_MULTIPASS)          // the outer passes multiply the gates in as they load u / store y
         return multipass_forward(p, u, k_f, y, B, workspace, s, 0, 0, w, v);
-    const int64_t n = B * p->H * p->N;
-    const void *src = u;
-    if (w) {
-        void *prod = (char *)workspace + align256(fftconv_workspace_bytes(p, B));
-        rc = gate_multiply(p->dtype, u, w, prod, n, s);
-        if (rc) return rc;
-        src = prod;
-    }
-    rc = fftconv_forward(p, src, k_f, y, B, H, N, workspace, stream);
-    if (rc || !v) return rc;
-    return gate_multiply(p->dtype, y, v, y, n, s);
+    if (p->path == PATH_SMALL) return row_forward(p, u, k_f, y, B, s, w, v);
+    return staged_forward(p, u, k_f, y, B, workspace, s, false, w, v);
 }
 
 double fftconv_sparsity_fraction(const int64_t *dims, const int64_t *cuts, int ndim)

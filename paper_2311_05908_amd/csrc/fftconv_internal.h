@@ -154,7 +154,7 @@ void staged_destroy(fftconv_plan *p);
 size_t staged_kf_bytes(const fftconv_plan *p);
 size_t staged_workspace_bytes(const fftconv_plan *p, int64_t B, bool least = false);
 int staged_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B,
-                   void *workspace, hipStream_t s, bool least = false);
+                   void *workspace, hipStream_t s, bool least = false, const void *wg = nullptr, const void *vg = nullptr);
 // fp64 transform of zero-padded filters into p->filt_a for channels [h0, h0+nh):
 // on return filt_a holds position-ordered spectra (position -> frequency via staged_pos_to_freq).
 // adjoint: the spectrum of the circularly time-reversed filter (= the conjugate spectrum)
@@ -177,7 +177,8 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
 FacList long_fft_factor_list(int64_t M);
 // least: what the static workspace was sized for; the pass then goes in smaller trips
 size_t long_forward_workspace_bytes(const fftconv_plan *p, int64_t B, bool least);
-int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s);
+int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s,
+                 const void *wg, const void *vg);
 size_t long_backward_filter_bytes(const fftconv_plan *p, int64_t B);
 int long_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B,
                          void *workspace, hipStream_t s);
@@ -273,8 +274,6 @@ __host__ __device__ inline int fused3_kf_slot_8192(int64_t fi)
 bool fused3_gates_fused(const fftconv_plan *p);
 int fused3_forward_gated(const fftconv_plan *p, const void *u, const void *w, const void *v, const void *kf, void *y,
                          int64_t B, hipStream_t s);
-// out[i] = a[i] * b[i] rounded to the I/O dtype (staged.hip); out may alias a
-int gate_multiply(int dtype, const void *a, const void *b, void *out, int64_t n, hipStream_t s);
 
 // filter gradient dk[h,t] = sum_b sum_i dy[b,h,i] upad[b,h,(i-t) mod M], t < Nk, through the generic
 // one-kernel-per-stage transforms in fp32 (staged.hip); any plan above fft_size 16384
@@ -299,7 +298,8 @@ int fused3_big_dk_finish(const fftconv_plan *p, const void *dkf, int64_t runs, v
 
 // ---- fp32 convolutions of rows that fit on chip (row_conv.hip): twiddle tables, k_f layout, the convolution
 std::vector<float2> row_tables(int64_t M, const double2 *w);
-int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s);
+int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s, const void *wg = nullptr,
+                const void *vg = nullptr);
 // the convolution of a matrix-core plan up to fft_size 4096 on them, and whether a call has few enough rows for it
 bool row_few(int64_t M, int64_t H, int64_t B);
 int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
@@ -340,8 +340,11 @@ struct OuterRows {
     int split, nh, H;
 };
 inline OuterRows outer_rows(const void *src) { return OuterRows{src, nullptr, INT32_MAX, INT32_MAX, 0}; }       // one after another
-int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s);
-int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int64_t Nk, int64_t nh, float scale, hipStream_t s);
+// gate: fp32 rows that multiply those of src (outer_rows()), or null; of the inverse, those of dk
+int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s,
+                           const float *gate = nullptr);
+int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int64_t Nk, int64_t nh, float scale, hipStream_t s,
+                           const float *gate = nullptr);
 int multipass_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, int64_t nh,
                       const uint8_t *keep_dev, int64_t n_blocks, void *kf, hipStream_t s);
 int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace,

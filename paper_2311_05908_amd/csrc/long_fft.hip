@@ -136,7 +136,8 @@ __device__ inline void cols_stage_any(float2 *X, const LongTw &w, int A, int C, 
 template <typename In>
 __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src_re, const In *__restrict__ src_im,
                                                      float2 *__restrict__ tmp, LongTw w, FacList flA, int A, int C, int64_t len,
-                                                     bool reversed, bool half_rows, LongRows rows)
+                                                     bool reversed, bool half_rows, LongRows rows, const In *__restrict__ g_re,
+                                                     const In *__restrict__ g_im)
 {
     extern __shared__ float2 XL[];
     const int M = A * LB, N = (int)len;
@@ -158,6 +159,20 @@ __global__ void __launch_bounds__(LT) k_long_fwd_cols(const In *__restrict__ src
     }
 #pragma unroll
     for (int j = 0; j < LPT; ++j) asm volatile("" ::"v"(vr[j]), "v"(vi[j]));      // keeps the loads unconditional
+    if (g_re) {                                               // the input gate (never with reversed)
+        float gr[LPT], gi[LPT];
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            const int i = threadIdx.x + j * LT, n = (i >> lgC) * LB + col0 + (i & (C - 1));
+            gr[j] = ld_real(g_re + first, n < N ? n : 0);
+            gi[j] = two ? ld_real(g_im + first, n < N ? n : 0) : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            vr[j] *= gr[j];
+            vi[j] *= gi[j];
+        }
+    }
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
         const int i = threadIdx.x + j * LT;
@@ -484,7 +499,7 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restric
 template <typename IO>
 __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict__ tmp, IO *__restrict__ y_re,
                                                        IO *__restrict__ y_im, LongTw w, FacList flA, int A, int C, int64_t N,
-                                                       LongRows rows)
+                                                       LongRows rows, const IO *__restrict__ g_re, const IO *__restrict__ g_im)
 {
     extern __shared__ float2 XL[];
     const int64_t M = (int64_t)A * LB, row = blockIdx.y, first = rows.at(blockIdx.y) * N;
@@ -506,7 +521,11 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
         const int a = i >> (__ffs(C) - 1), c = i & (C - 1);
         const int n = a * LB + col0 + c;
         if (n < N) {
-            const float2 v = XL[lds_slot(i)];
+            float2 v = XL[lds_slot(i)];
+            if (g_re) {                                           // the output gate
+                v.x *= ld_real(g_re + first, n);
+                if (two) v.y *= ld_real(g_im + first, n);
+            }
             st_real(re, n, v.x);
             if (two) st_real(im, n, v.y);
         }
@@ -531,12 +550,13 @@ int raise_lds(const void *kern) { return raise_dynamic_lds(kern, (int)L_LDS); }
 
 template <typename In>
 int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, const LongTw &w, int64_t rows, int64_t len,
-                    bool reversed, hipStream_t s, bool half_rows = false, LongRows where = long_rows(0))
+                    bool reversed, hipStream_t s, bool half_rows = false, LongRows where = long_rows(0), const In *g_re = nullptr,
+                    const In *g_im = nullptr)
 {
     const int rc = raise_lds((const void *)k_long_fwd_cols<In>);
     if (rc) return rc;
     hipLaunchKernelGGL(k_long_fwd_cols<In>, dim3((unsigned)g.A, (unsigned)rows), dim3(LT), L_LDS, s, re, im, tmp, w, g.flA,
-                       g.A, g.C, len, reversed, half_rows && im == nullptr, where);
+                       g.A, g.C, len, reversed, half_rows && im == nullptr, where, g_re, g_im);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -707,7 +727,8 @@ int64_t conv_pairs(const fftconv_plan *p, int64_t B)
 
 // cap: pairs that the workspace holds (at least a row's)
 template <typename IO>
-int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, int64_t B, void *workspace, int64_t cap, hipStream_t s)
+int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, int64_t B, void *workspace, int64_t cap, hipStream_t s,
+                   const IO *wg, const IO *vg)
 {
     const int64_t M = p->M, N = p->N, H = p->H;
     const LongGeo g = long_geo(M);
@@ -732,20 +753,21 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
     auto as_real = [&](int64_t row0, int64_t rows) -> int {
         return trips(rows, real_row(p), [&](int64_t first, int64_t n) -> int {
             const int64_t o = (row0 + first) * N;
-            FC_TRY(multipass_filter_outer(p, outer_rows(u + o), FFTCONV_F32, N, n, tmp, s));
+            FC_TRY(multipass_filter_outer(p, outer_rows(u + o), FFTCONV_F32, N, n, tmp, s, wg ? wg + o : nullptr));
             FC_TRY(blocks(g.A / 2 + 1, row0 + first, n, true));
-            return multipass_dk_outer_inv(p, tmp, (float *)(y + o), N, n, 1.0f, s);
+            return multipass_dk_outer_inv(p, tmp, (float *)(y + o), N, n, 1.0f, s, vg ? vg + o : nullptr);
         });
     };
     auto as_complex = [&](int64_t b, int64_t units, bool pairs) -> int {
         return trips(units, M, [&](int64_t first, int64_t n) -> int {
             const LongRows where = pairs ? long_row_pairs(first, H, (B - b) * H) : long_rows(first);
-            const IO *u0 = u + b * H * N;
+            const IO *u0 = u + b * H * N, *w0 = wg ? wg + b * H * N : nullptr, *v0 = vg ? vg + b * H * N : nullptr;
             IO *y0 = y + b * H * N;
-            FC_TRY(launch_fwd_cols<IO>(g, u0, pairs ? u0 + H * N : nullptr, tmp, tw, n, N, false, s, false, where));
+            FC_TRY(launch_fwd_cols<IO>(g, u0, pairs ? u0 + H * N : nullptr, tmp, tw, n, N, false, s, false, where, w0,
+                                       wg && pairs ? w0 + H * N : nullptr));
             FC_TRY(blocks(g.A, first, n, false));
             hipLaunchKernelGGL(k_long_inv_cols_y<IO>, dim3((unsigned)g.A, (unsigned)n), dim3(LT), L_LDS, s, (const float2 *)tmp, y0,
-                               pairs ? y0 + H * N : nullptr, tw, g.flA, g.A, g.C, N, where);
+                               pairs ? y0 + H * N : nullptr, tw, g.flA, g.A, g.C, N, where, v0, vg && pairs ? v0 + H * N : nullptr);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;
         });
@@ -822,10 +844,11 @@ size_t long_forward_workspace_bytes(const fftconv_plan *p, int64_t B, bool least
 
 // forward pass of the fp32 plans from fft_size 32768 up; kf: (H, fft_size) fp32 pairs in position order; least: the workspace
 // holds only long_forward_workspace_bytes(p, B, true)
-int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s)
+int long_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace, bool least, hipStream_t s,
+                 const void *wg, const void *vg)
 {
     return long_forward_t<float>(p, (const float *)u, (const float2 *)kf, (float *)y, B, workspace,
-                                 least ? conv_least(p) : conv_pairs(p, B), s);
+                                 least ? conv_least(p) : conv_pairs(p, B), s, (const float *)wg, (const float *)vg);
 }
 
 // enough for every smaller batch

@@ -857,9 +857,11 @@ __global__ void __launch_bounds__(TB, 4) k_outer_inv_real(const uint32_t *__rest
 // Taps at and beyond Nk are zeros (their loads read tap 0 and are discarded: no load sits behind a branch).
 // The filter gradient of these plans (long_fft.hip) transforms its rows of u and dy the same way: IN = 0: fp32
 // rows, 1: fp16, 2: bf16; row i of the launch is row rows.at(i) of its source, Nk elements each.
-template <int IN, int RA, int RB, bool FULLN>
+// GATED (fp32 convolutions; IN = 0): the rows are multiplied by those of gate, which lie alike.  As a kernel of its own that took as long as this pass:
+// 7 x 2 x 2^19 circular fp32, both gates, 74 -> 53 us; 4 x 16 x 65536 fft 131072 70 -> 63.
+template <int IN, int RA, int RB, bool FULLN, bool GATED>
 __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, float2 *__restrict__ T2, int cgs,
-                                                         int64_t Nk, bool wide)
+                                                         int64_t Nk, bool wide, const float *__restrict__ gate)
 {
     extern __shared__ float2 sm[];
     constexpr int No = RA * RB, NR = No / 2 + 1;
@@ -908,8 +910,30 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
                 x[a] = unpack2<IN == 1>(pair_of(wd, n, (int)Nk));
             }
         }
+        float2 gt[GATED ? RAIN : 1];
+        if constexpr (GATED) {
+            const float *const row = gate + first;
+#pragma unroll
+            for (int a = 0; a < RAIN; ++a) {
+                const int n = (a * RB + b2) * MI + r0 + 2 * cg;
+                if (wide) {
+                    gt[a] = RB >= 4 ? *(const float2 *)(row + (int64_t)(n < Nk ? n : 0)) : ld_at<float2>(row, n < Nk ? 4 * n : 0);
+                } else {
+                    gt[a].x = row[n < Nk ? n : 0];
+                    gt[a].y = row[n + 1 < Nk ? n + 1 : 0];
+                }
+            }
+        }
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) asm volatile("" ::"v"(x[a].x), "v"(x[a].y));      // keeps the loads unconditional
+        if constexpr (GATED) {
+#pragma unroll
+            for (int a = 0; a < RAIN; ++a) {
+                x[a].x *= gt[a].x;
+                x[a].y *= gt[a].y;
+                asm("" : "+v"(x[a].x), "+v"(x[a].y));             // (rounded: not part of a multiply-add)
+            }
+        }
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
             const int n = (a * RB + b2) * MI + r0 + 2 * cg;
@@ -985,9 +1009,10 @@ __global__ void __launch_bounds__(TB, 4) k_filter_outer_real(OuterRows rows, flo
 // after their inverse 8192-point transforms (unnormalised); the spectrum is that of a real sequence, so the rows
 // ko > No/2 are the mirror images described at k_outer_inv.  dk[h][n] = scale * (the inverse outer transform),
 // n < Nk.
-template <int RA, int RB, bool FULLN>
+// GATED (fp32 convolutions): times the rows of gate, which lie like those of dk.
+template <int RA, int RB, bool FULLN, bool GATED>
 __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__restrict__ T2, float *__restrict__ dk, int cgs,
-                                                         int64_t Nk, float scale)
+                                                         int64_t Nk, float scale, const float *__restrict__ gate)
 {
     extern __shared__ float2 sm[];
     constexpr int No = RA * RB, NR = No / 2 + 1;
@@ -1052,7 +1077,7 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
     if constexpr (RB > 1) __syncthreads();
     // step 2: length-RA inverse over ka; real part -> column c, imaginary part -> column c+1
     float *row0 = dk + h * Nk;
-    const bool wide = Nk % 2 == 0 && ((uintptr_t)dk & 7) == 0;
+    const bool wide = Nk % 2 == 0 && (((uintptr_t)dk | (uintptr_t)(GATED ? gate : nullptr)) & 7) == 0;
 #pragma unroll 1
     for (int e = tid; e < RB * CG; e += TB) {
         const int cg = e & (CG - 1), b2 = e >> lgCG;
@@ -1082,6 +1107,30 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
             for (int ka = 0; ka < RA; ++ka) x[ka] = T[(ka * RB + b2) * CG + cg];
         }
         dft_reg<RA, true>(x);
+        if constexpr (GATED) {                     // (samples beyond Nk read the row's first gate and are not stored)
+            const float *const g = gate + h * Nk;
+            constexpr int CH = RAIN < 8 ? RAIN : 8;                  // at a time
+#pragma unroll
+            for (int a0 = 0; a0 < RAIN; a0 += CH) {
+                float2 gt[CH];
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    const int n = ((a0 + i) * RB + b2) * MI + r0 + 2 * cg;
+                    if (wide) {
+                        gt[i] = ld_at<float2>(g, n < Nk ? 4 * n : 0);
+                    } else {
+                        gt[i].x = g[n < Nk ? n : 0];
+                        gt[i].y = g[n + 1 < Nk ? n + 1 : 0];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    x[a0 + i].x *= gt[i].x;
+                    x[a0 + i].y *= gt[i].y;
+                    asm volatile("" : "+v"(x[a0 + i].x), "+v"(x[a0 + i].y));
+                }
+            }
+        }
 #pragma unroll
         for (int a = 0; a < RAIN; ++a) {
             const int n = (a * RB + b2) * MI + r0 + 2 * cg;
@@ -1097,44 +1146,37 @@ __global__ void __launch_bounds__(TB, 4) k_dk_outer_inv_real(const float2 *__res
 
 template <int RA, int RB>
 int launch_dk_outer_inv(const OuterGeo &g, const float2 *T2, float *dk, int64_t Nk, int64_t M, int64_t nh, float scale,
-                        hipStream_t s)
+                        const float *gate, hipStream_t s)
 {
-    const size_t lds = g.lds();
-    const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
-    if (Nk > M / 2) {
-        FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, true>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, scale);
-    } else {
-        FC_TRY(raise_dynamic_lds((const void *)k_dk_outer_inv_real<RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_dk_outer_inv_real<RA, RB, false>), grid, dim3(TB), lds, s, T2, dk, g.pairs(), Nk, scale);
-    }
+    auto kern = Nk > M / 2 ? (gate ? k_dk_outer_inv_real<RA, RB, true, true> : k_dk_outer_inv_real<RA, RB, true, false>)
+                           : (gate ? k_dk_outer_inv_real<RA, RB, false, true> : k_dk_outer_inv_real<RA, RB, false, false>);
+    FC_TRY(raise_dynamic_lds((const void *)kern, 160 * 1024));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(MI / (2 * g.pairs())), (unsigned)nh), dim3(TB), g.lds(), s, T2, dk, g.pairs(), Nk, scale, gate);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
 
-template <int IN, int RA, int RB>
-int launch_filter_outer_in(const OuterGeo &g, const OuterRows &rows, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
+template <int IN, int RA, int RB, bool GATED>
+int launch_filter_outer_in(const OuterGeo &g, const OuterRows &rows, float2 *T2, int64_t Nk, int64_t M, int64_t nh, const float *gate,
+                           hipStream_t s)
 {
-    const size_t lds = g.lds();
-    const dim3 grid((unsigned)(MI / (2 * g.pairs())), (unsigned)nh);
-    const bool wide = IN == 0 ? Nk % 2 == 0 && (((uintptr_t)rows.src | (uintptr_t)rows.src2) & 7) == 0 : Nk > 1;
-    if (Nk > M / 2) {
-        FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, true>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, true>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, wide);
-    } else {
-        FC_TRY(raise_dynamic_lds((const void *)k_filter_outer_real<IN, RA, RB, false>, 160 * 1024));
-        hipLaunchKernelGGL((k_filter_outer_real<IN, RA, RB, false>), grid, dim3(TB), lds, s, rows, T2, g.pairs(), Nk, wide);
-    }
+    const bool wide = IN == 0 ? Nk % 2 == 0 && (((uintptr_t)rows.src | (uintptr_t)rows.src2 | (uintptr_t)gate) & 7) == 0 : Nk > 1;
+    auto kern = Nk > M / 2 ? k_filter_outer_real<IN, RA, RB, true, GATED> : k_filter_outer_real<IN, RA, RB, false, GATED>;
+    FC_TRY(raise_dynamic_lds((const void *)kern, 160 * 1024));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(MI / (2 * g.pairs())), (unsigned)nh), dim3(TB), g.lds(), s, rows, T2, g.pairs(), Nk, wide, gate);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
-// dtype: FFTCONV_F32 / F16 / BF16 of the rows
+// dtype: FFTCONV_F32 / F16 / BF16 of the rows; gate: fp32 rows only
 template <int RA, int RB>
-int launch_filter_outer(const OuterGeo &g, const OuterRows &rows, int dtype, float2 *T2, int64_t Nk, int64_t M, int64_t nh, hipStream_t s)
+int launch_filter_outer(const OuterGeo &g, const OuterRows &rows, int dtype, float2 *T2, int64_t Nk, int64_t M, int64_t nh,
+                        const float *gate, hipStream_t s)
 {
-    if (dtype == FFTCONV_F32) return launch_filter_outer_in<0, RA, RB>(g, rows, T2, Nk, M, nh, s);
-    if (dtype == FFTCONV_F16) return launch_filter_outer_in<1, RA, RB>(g, rows, T2, Nk, M, nh, s);
-    return launch_filter_outer_in<2, RA, RB>(g, rows, T2, Nk, M, nh, s);
+    if (dtype == FFTCONV_F32)
+        return gate ? launch_filter_outer_in<0, RA, RB, true>(g, rows, T2, Nk, M, nh, gate, s)
+                    : launch_filter_outer_in<0, RA, RB, false>(g, rows, T2, Nk, M, nh, nullptr, s);
+    if (dtype == FFTCONV_F16) return launch_filter_outer_in<1, RA, RB, false>(g, rows, T2, Nk, M, nh, nullptr, s);
+    return launch_filter_outer_in<2, RA, RB, false>(g, rows, T2, Nk, M, nh, nullptr, s);
 }
 
 // k_f for the multi-pass path: [h][ko][inner order of f'] 16-bit (re, im) pairs, f = ko + No*f', scaled 1/M
@@ -1344,7 +1386,8 @@ int multipass_pack_kf(const fftconv_plan *p, const double2 *spec, int64_t h0, in
 // for this outer length (the caller takes the generic column kernel instead).
 bool multipass_filter_outer_ok(const fftconv_plan *p) { return outer_real_ok((int)(p->M / MI)); }
 
-int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s)
+int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dtype, int64_t Nk, int64_t nh, void *T2, hipStream_t s,
+                           const float *gate)
 {
     const OuterGeo g = outer_geo(p->M);
     if (nh > 65535) {
@@ -1353,13 +1396,13 @@ int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dty
     }
     float2 *t = (float2 *)T2;
     switch (g.No) {
-    case 4: return launch_filter_outer<4, 1>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 8: return launch_filter_outer<8, 1>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 16: return launch_filter_outer<16, 1>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 32: return launch_filter_outer<16, 2>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 64: return launch_filter_outer<16, 4>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 128: return launch_filter_outer<16, 8>(g, rows, dtype, t, Nk, p->M, nh, s);
-    case 256: return launch_filter_outer<16, 16>(g, rows, dtype, t, Nk, p->M, nh, s);
+    case 4: return launch_filter_outer<4, 1>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 8: return launch_filter_outer<8, 1>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 16: return launch_filter_outer<16, 1>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 32: return launch_filter_outer<16, 2>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 64: return launch_filter_outer<16, 4>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 128: return launch_filter_outer<16, 8>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
+    case 256: return launch_filter_outer<16, 16>(g, rows, dtype, t, Nk, p->M, nh, gate, s);
     default:
         set_error("multipass: no real outer pass for outer length %d", g.No);
         return FFTCONV_EUNSUPPORTED;
@@ -1368,7 +1411,8 @@ int multipass_filter_outer(const fftconv_plan *p, const OuterRows &rows, int dty
 
 // Last pass of the filter gradient, and of the fp32 forward pass of long plans (see k_dk_outer_inv_real): T2 holds
 // nh * (No/2 + 1) rows; dk (nh, Nk) = scale * the real inverse outer transform.
-int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int64_t Nk, int64_t nh, float scale, hipStream_t s)
+int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int64_t Nk, int64_t nh, float scale, hipStream_t s,
+                           const float *gate)
 {
     const OuterGeo g = outer_geo(p->M);
     if (nh > 65535) {
@@ -1377,13 +1421,13 @@ int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int
     }
     const float2 *t = (const float2 *)T2;
     switch (g.No) {
-    case 4: return launch_dk_outer_inv<4, 1>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 8: return launch_dk_outer_inv<8, 1>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 16: return launch_dk_outer_inv<16, 1>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 32: return launch_dk_outer_inv<16, 2>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 64: return launch_dk_outer_inv<16, 4>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 128: return launch_dk_outer_inv<16, 8>(g, t, dk, Nk, p->M, nh, scale, s);
-    case 256: return launch_dk_outer_inv<16, 16>(g, t, dk, Nk, p->M, nh, scale, s);
+    case 4: return launch_dk_outer_inv<4, 1>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 8: return launch_dk_outer_inv<8, 1>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 16: return launch_dk_outer_inv<16, 1>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 32: return launch_dk_outer_inv<16, 2>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 64: return launch_dk_outer_inv<16, 4>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 128: return launch_dk_outer_inv<16, 8>(g, t, dk, Nk, p->M, nh, scale, gate, s);
+    case 256: return launch_dk_outer_inv<16, 16>(g, t, dk, Nk, p->M, nh, scale, gate, s);
     default:
         set_error("multipass: no real outer pass for outer length %d", g.No);
         return FFTCONV_EUNSUPPORTED;

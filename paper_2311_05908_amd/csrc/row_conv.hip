@@ -29,7 +29,8 @@ using rf::Row;
 
 // waves per SIMD the register budget is held to: what LDS allows (8.5 KB a wave, 17 KB where 32 points of a thread go
 // through it as pairs) and the registers can be had for (spilled: 16 - 28 bytes of k_row_conv_few<2048> with an output gate)
-constexpr int waves_of(int M) { return M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2; }
+// (GATED: one less, for the gates)
+constexpr int waves_of(int M, bool gated = false) { return (M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2) - (gated && M <= 4096 && M != 512 && M != 1024 ? 1 : 0); }
 
 template <int M, typename IO> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096>;
 
@@ -41,10 +42,13 @@ template <int M, typename IO> constexpr bool BY_PAIR = M == 256 && sizeof(IO) ==
 
 // kf: see the head of this file, scaled by 1/M.  HALF: N <= M / 2.  total: pairs of rows, t = h * npairs + pair, or, with nh > 0
 // channels (BY_PAIR), t = pair * nh + h.
-template <int M, typename IO, bool HALF>
-__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
+// GATED: y = v . ((u . w) * k), either gate may be null; roundings as below (k_row_conv_few).  With an elementwise kernel for each gate
+// instead, us: f16 circular 42 x 768 x 512 69 -> 36, bf16 circular 64 x 256 x 256 23 -> 11, 16 x 256 x 2048 41 -> 23, odd rows 16 x 256 x 1001
+// (fft 2048) 28 -> 19; fp32 8 x 128 x 4096 (fft 8192) 35 -> 20, 8 x 64 x 16384 circular 55 -> 31, 16 x 64 x 1024 (fft 2048) 16 -> 8.
+template <int M, typename IO, bool HALF, bool GATED>
+__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M, GATED))
     k_row_conv(const IO *__restrict__ u, IO *__restrict__ y, const float4 *__restrict__ kf, const float2 *__restrict__ tab, int B,
-               int H, int N, int npairs, int total, int per_die, int nh)
+               int H, int N, int npairs, int total, int per_die, int nh, const IO *__restrict__ wg, const IO *__restrict__ vg)
 {
     using G = ConvRow<M, IO>;
     constexpr int RW = rf::threads_of(M) / G::T;                  // rows (pairs) per workgroup
@@ -61,10 +65,19 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     const bool exact = N == (HALF ? G::R0 / 2 : G::R0) * G::T;    // every sample of the registers exists
-    const bool words = rf::word_rows<IO>(u, y, N);
+    const bool words = rf::word_rows<IO>(u, y, N) && (!GATED || rf::word_rows<IO>(wg, vg, N));
 
     float2 x[G::P];
-    rf::load_pair<G, IO, HALF>(x, u + r0, u + r1, N, tid, exact, words, true, two);
+    if constexpr (GATED) {
+        using Raw = rf::RawPair<G, IO, HALF>;
+        Raw ru, rw;
+        ru.fetch(u + r0, u + r1, N, tid, words);
+        if (wg) rw.fetch(wg + r0, wg + r1, N, tid, words);
+#pragma unroll
+        for (int m = 0; m < Raw::MIN; ++m) x[m] = ru.value(m, N, tid, words, two, rw, wg);
+    } else {
+        rf::load_pair<G, IO, HALF>(x, u + r0, u + r1, N, tid, exact, words, true, two);
+    }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
     // k_f of this thread's bins: requested ahead of the last pass as far as the registers go
@@ -82,9 +95,21 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
         x[2 * q] = rf::mul(x[2 * q], make_float2(kv[q].x, kv[q].y));
         x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
     }
-    rf::inverse<G>(x, Z, tab, tw1, tid);
-    // real part -> row b, imaginary part -> row b + 1
-    if (live) rf::store_pair<G, IO, HALF>(x, y + r0, y + r1, N, tid, exact, words, two);
+    if constexpr (GATED) {
+        using Raw = rf::RawPair<G, IO, HALF>;
+        constexpr bool AHEAD = HALF ? M <= 8192 : M <= 4096;      // the output gate asked for ahead of the inverse transform, as registers allow
+        Raw rv;
+        if (AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, tid, words);
+        rf::inverse<G>(x, Z, tab, tw1, tid);
+        if (!AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, tid, words);
+        int j = tid;
+        asm volatile("" : "+v"(j));                               // (the masks of the samples are not kept from the input to here)
+        if (live) rv.store(x, y + r0, y + r1, N, j, words, two, vg);
+    } else {
+        rf::inverse<G>(x, Z, tab, tw1, tid);
+        // real part -> row b, imaginary part -> row b + 1
+        if (live) rf::store_pair<G, IO, HALF>(x, y + r0, y + r1, N, tid, exact, words, two);
+    }
 }
 
 // The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
@@ -108,13 +133,17 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     const bool exact = N == M / 2;
+    using Raw = rf::RawPair<G, IO, true>;
     float2 x[G::P];
-    rf::load_pair<G, IO, true>(x, u + r0, u + r1, N, tid, exact, true, true, two);
+    Raw rv;
     if constexpr (GATE & 1) {
-        float2 g[G::P];
-        rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
+        Raw ru, rw;
+        ru.fetch(u + r0, u + r1, N, tid, true);
+        rw.fetch(wg + r0, wg + r1, N, tid, true);
 #pragma unroll
-        for (int m = 0; m < G::P / 2; ++m) x[m] = rf::rounded<IO>(x[m].x * g[m].x, x[m].y * g[m].y);
+        for (int m = 0; m < Raw::MIN; ++m) x[m] = ru.value(m, N, tid, true, two, rw, true);
+    } else {
+        rf::load_pair<G, IO, true>(x, u + r0, u + r1, N, tid, exact, true, true, two);
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
@@ -126,26 +155,22 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     });
 #pragma unroll
     for (int p = 0; p < G::P; ++p) x[p] = rf::mul(x[p], rf::unpack<IO>(kv[p]));
+    if constexpr (GATE & 2) rv.fetch(vg + r0, vg + r1, N, tid, true);
     rf::inverse<G>(x, Z, tab, tw1, tid);
     if constexpr (GATE & 2) {
-        float2 g[G::P];
-        rf::load_pair<G, IO, true>(g, vg + r0, vg + r1, N, tid, exact, true, true, two);
-#pragma unroll
-        for (int m = 0; m < G::P / 2; ++m) {
-            const float2 c = rf::rounded<IO>(x[m].x, x[m].y);
-            x[m] = make_float2(c.x * g[m].x, c.y * g[m].y);
-        }
+        if (live) rv.store(x, y + r0, y + r1, N, tid, true, two, true);
+        return;
     }
     if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }
 
-template <int M, typename IO, bool HALF>
-int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
+template <int M, typename IO, bool HALF, bool GATED>
+int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
     using G = ConvRow<M, IO>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T;
     constexpr int lds = RW * G::LDS_BYTES;
-    FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF>, lds));
+    FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF, GATED>, lds));
     // A launch holds less than 2^32 threads, and the kernel counts rows in 32 bits: longer calls go out in pieces of MOST
     // pairs, whole channels where the batch allows it.
     constexpr int64_t MOST = ((int64_t)1 << 31) / G::T;
@@ -156,9 +181,10 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
         for (int64_t h0 = 0; h0 < H; h0 += nh) {
             const int64_t hs = H - h0 < nh ? H - h0 : nh, total = hs * np, groups = (total + RW - 1) / RW, per_die = (groups + 7) / 8;
             const int64_t at = (2 * p0 * H + h0) * N;
-            hipLaunchKernelGGL((k_row_conv<M, IO, HALF>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u + at,
+            hipLaunchKernelGGL((k_row_conv<M, IO, HALF, GATED>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u + at,
                                (IO *)y + at, (const float4 *)kf + h0 * (M / 2), rf::row_table<G>(p), (int)nb, (int)H, (int)N, (int)np,
-                               (int)total, (int)per_die, by_pair ? (int)hs : 0);
+                               (int)total, (int)per_die, by_pair ? (int)hs : 0, wg ? (const IO *)wg + at : nullptr,
+                               vg ? (const IO *)vg + at : nullptr);
             FC_HIP(hipGetLastError());
         }
     }
@@ -166,9 +192,12 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 }
 
 template <int M, typename IO>
-int launch_half(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
+int launch_half(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
-    return p->N <= M / 2 ? launch<M, IO, true>(p, u, kf, y, B, s) : launch<M, IO, false>(p, u, kf, y, B, s);
+    if (wg || vg)
+        return p->N <= M / 2 ? launch<M, IO, true, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true>(p, u, kf, y, B, wg, vg, s);
+    return p->N <= M / 2 ? launch<M, IO, true, false>(p, u, kf, y, B, nullptr, nullptr, s)
+                         : launch<M, IO, false, false>(p, u, kf, y, B, nullptr, nullptr, s);
 }
 
 }  // namespace
@@ -195,14 +224,14 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     return t;
 }
 
-int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
+int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s, const void *wg, const void *vg)
 {
     return rf::with_row(p->M, [&](auto g) -> int {
         using G = decltype(g);
-        if (p->dtype == FFTCONV_F32) return launch_half<G::M, float>(p, u, kf, y, B, s);
+        if (p->dtype == FFTCONV_F32) return launch_half<G::M, float>(p, u, kf, y, B, wg, vg, s);
         if constexpr (G::M <= 4096) {                             // longer 16-bit rows run on the matrix cores
-            if (p->dtype == FFTCONV_F16) return launch_half<G::M, __half>(p, u, kf, y, B, s);
-            return launch_half<G::M, __hip_bfloat16>(p, u, kf, y, B, s);
+            if (p->dtype == FFTCONV_F16) return launch_half<G::M, __half>(p, u, kf, y, B, wg, vg, s);
+            return launch_half<G::M, __hip_bfloat16>(p, u, kf, y, B, wg, vg, s);
         }
         set_error("row kernels: no 16-bit instance for rows of %lld points", (long long)p->M);
         return FFTCONV_EUNSUPPORTED;

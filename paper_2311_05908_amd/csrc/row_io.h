@@ -133,6 +133,108 @@ __device__ __forceinline__ void store_pair(const float2 (&x)[G::P], IO *__restri
     }
 }
 
+// a . b of two packed pairs, each product rounded to the I/O type (the fp32 product of 16-bit values is exact)
+template <typename IO> __device__ __forceinline__ uint32_t mul_words(uint32_t a, uint32_t b)
+{
+    if constexpr (std::is_same<IO, __half>::value) {
+        return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f3::f16x2, a) * __builtin_bit_cast(f3::f16x2, b));
+    } else {
+        const float2 x = unpack<IO>(a), y = unpack<IO>(b);
+        return pack<IO>(x.x * y.x, x.y * y.y);
+    }
+}
+template <typename IO> __device__ __forceinline__ float mul_io(float a, float b)
+{
+    if constexpr (sizeof(IO) == 2) return rounded<IO>(a * b, 0.f).x;
+    float v = a * b;
+    asm("" : "+v"(v));                                            // (rounded: not part of a multiply-add)
+    return v;
+}
+
+// The samples of load_pair() in two steps, for kernels that multiply by gates: fetch() only asks for them, so that those of a row and of its
+// gates are in flight together, and value() multiplies and unpacks.  Words are multiplied as they are, before the neighbours of a
+// pair of lanes swap halves.
+template <typename G, typename IO, bool HALF> struct RawPair {
+    static constexpr int MIN = HALF ? G::R0 / 2 : G::R0;
+    uint32_t a[MIN], b[MIN];                                      // words (b unused), or a sample of either row
+
+    __device__ __forceinline__ void fetch(const IO *__restrict__ r0, const IO *__restrict__ r1, int N, int tid, bool words)
+    {
+        if (words) {
+            const int odd = tid & 1;
+            const IO *const wrow = (odd ? r1 : r0) - odd;
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) {
+                const int n = tid + G::T * m;
+                a[m] = *(const uint32_t *)(wrow + (n < N ? n : odd));
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) {
+                const int n = tid + G::T * m, at = n < N ? n : 0;
+                if constexpr (sizeof(IO) == 4) {
+                    a[m] = ((const uint32_t *)r0)[at];
+                    b[m] = ((const uint32_t *)r1)[at];
+                } else {
+                    a[m] = ((const uint16_t *)r0)[at];
+                    b[m] = ((const uint16_t *)r1)[at];
+                }
+            }
+        }
+    }
+    static __device__ __forceinline__ float one(uint32_t w)
+    {
+        if constexpr (sizeof(IO) == 4) return __uint_as_float(w);
+        else return unpack<IO>(w).x;
+    }
+    // sample m of both rows, times the gate's where there is one (on); zero from N on, and the second where it is not there
+    __device__ __forceinline__ float2 value(int m, int N, int tid, bool words, bool has1, const RawPair &g, bool on) const
+    {
+        const bool in = tid + G::T * m < N;
+        if (words) {
+            const uint32_t sel = tid & 1 ? 0x03020706u : 0x05040100u;
+            uint32_t w = on ? mul_words<IO>(a[m], g.a[m]) : a[m];
+            w = in ? w : 0;
+            return unpack<IO>(__builtin_amdgcn_perm(neighbour(w), w, sel) & (has1 ? 0xffffffffu : 0xffffu));
+        }
+        float2 x = make_float2(one(a[m]), one(b[m]));
+        if (on) x = make_float2(mul_io<IO>(x.x, one(g.a[m])), mul_io<IO>(x.y, one(g.b[m])));
+        return make_float2(in ? x.x : 0.f, in && has1 ? x.y : 0.f);
+    }
+    // x[m], rounded to the I/O type, times this gate where there is one (on) -> the rows r0, r1 as in store_pair()
+    __device__ __forceinline__ void store(const float2 (&x)[G::P], IO *__restrict__ r0, IO *__restrict__ r1, int N, int tid, bool words,
+                                          bool two, bool on) const
+    {
+        if (words) {
+            const int odd = tid & 1;
+            IO *const wrow = (odd ? r1 : r0) - odd;
+            const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+            const bool put = two || !odd;
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) {
+                const uint32_t z = pack<IO>(x[m].x, x[m].y);
+                uint32_t o = __builtin_amdgcn_perm(neighbour(z), z, sel);
+                if (on) o = mul_words<IO>(o, a[m]);
+                if (put && tid + G::T * m < N) *(uint32_t *)(wrow + tid + G::T * m) = o;
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < MIN; ++m) {
+                const int n = tid + G::T * m;
+                float2 c = x[m];
+                if (on) {
+                    if constexpr (sizeof(IO) == 2) c = rounded<IO>(c.x, c.y);
+                    c = make_float2(c.x * one(a[m]), c.y * one(b[m]));
+                }
+                if (n < N) {
+                    st(r0, n, c.x);
+                    if (two) st(r1, n, c.y);
+                }
+            }
+        }
+    }
+};
+
 // calls f(Row<M>()) for the row length of the plan
 template <typename F> int with_row(int64_t M, F f)
 {

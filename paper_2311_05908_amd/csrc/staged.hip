@@ -310,10 +310,10 @@ size_t staged_workspace_bytes(const fftconv_plan *p, int64_t B, bool least) { re
 
 // fp32 I/O from fft_size 8192 up: one kernel up to 16384 (row_conv.hip), three above (long_fft.hip)
 int staged_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace,
-                   hipStream_t s, bool least)
+                   hipStream_t s, bool least, const void *wg, const void *vg)
 {
-    if (p->M <= 16384) return row_forward(p, u, kf, y, B, s);
-    return long_forward(p, u, kf, y, B, workspace, least, s);
+    if (p->M <= 16384) return row_forward(p, u, kf, y, B, s, wg, vg);
+    return long_forward(p, u, kf, y, B, workspace, least, s, wg, vg);
 }
 
 // Largest row the LDS-resident kernels take: 8192 fp64 or 16384 fp32 complex points with their padding.
@@ -508,37 +508,6 @@ int staged_backward_filter(const fftconv_plan *p, const void *u, const void *dy,
         return staged_backward_filter_t<__hip_bfloat16>(p, (const __hip_bfloat16 *)u, (const __hip_bfloat16 *)dy, dk, Nk,
                                                         B, workspace, s);
     }
-}
-
-// Elementwise gate of the gated convolution for plans without a fused-gate kernel:
-// out = a * b, the fp32 product rounded to the I/O dtype (exact product for 16-bit inputs).
-template <typename T> __global__ void k_gate_multiply(const T *a, const T *b, T *out, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if constexpr (std::is_same<T, float>::value)
-        out[i] = a[i] * b[i];
-    else if constexpr (std::is_same<T, __half>::value)
-        out[i] = __float2half_rn(__half2float(a[i]) * __half2float(b[i]));
-    else
-        out[i] = __float2bfloat16(__bfloat162float(a[i]) * __bfloat162float(b[i]));
-}
-
-int gate_multiply(int dtype, const void *a, const void *b, void *out, int64_t n, hipStream_t s)
-{
-    const int bs = 256;
-    const unsigned grid = (unsigned)((n + bs - 1) / bs);
-    if (dtype == FFTCONV_F32)
-        hipLaunchKernelGGL(k_gate_multiply<float>, dim3(grid), dim3(bs), 0, s, (const float *)a, (const float *)b,
-                           (float *)out, n);
-    else if (dtype == FFTCONV_F16)
-        hipLaunchKernelGGL(k_gate_multiply<__half>, dim3(grid), dim3(bs), 0, s, (const __half *)a, (const __half *)b,
-                           (__half *)out, n);
-    else
-        hipLaunchKernelGGL(k_gate_multiply<__hip_bfloat16>, dim3(grid), dim3(bs), 0, s, (const __hip_bfloat16 *)a,
-                           (const __hip_bfloat16 *)b, (__hip_bfloat16 *)out, n);
-    FC_HIP(hipGetLastError());
-    return FFTCONV_OK;
 }
 
 }  // namespace fftconv

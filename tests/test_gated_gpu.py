@@ -1,5 +1,5 @@
 """Gated convolution y = v . ((u . w) * k) through the C ABI against the CPU oracle:
-the fused-gate 8192-point kernel and the elementwise-kernel route of the other plans."""
+the fused-gate 8192-point kernel, the row engine and the outer passes."""
 import ctypes
 
 import numpy as np
@@ -83,6 +83,44 @@ def test_gated_other_plans(dtype, B, H, N, M):
               flush=True)
         assert plan.workspace_bytes_gated(B) >= plan.workspace_bytes(B) + B * H * N * (4 if dtype == "f32" else 2)
         assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M,shift", [
+    ("bf16", 5, 3, 256, 256, 0),        # circular rows, words of two samples; odd batch
+    ("bf16", 4, 3, 256, 256, 1),        # ... gates that start off a word
+    ("f16", 3, 5, 255, 256, 0),         # odd rows: sample by sample
+    ("bf16", 3, 2, 510, 512, 0),        # words, the last registers partly filled
+    ("f16", 2, 9, 1024, 1024, 0),
+    ("bf16", 3, 2, 1001, 2048, 0),
+    ("f16", 1, 2, 2047, 2048, 0),       # N > M / 2, a row without a partner
+    ("bf16", 2, 2, 4096, 4096, 0),
+    ("f32", 3, 2, 130, 256, 0),
+    ("f32", 2, 3, 4096, 4096, 0),
+    ("f32", 3, 1, 8192, 8192, 0),
+    ("f32", 3, 1, 5001, 16384, 0),
+    ("f32", 1, 2, 16384, 16384, 0),
+    ("f32", 3, 2, 9001, 32768, 0),      # outer passes of real rows: odd N, then N > M / 2 and pairs of samples
+    ("f32", 2, 1, 20002, 32768, 0),
+    ("f32", 2, 1, 9002, 65536, 1),      # gates that start off a pair
+    ("f32", 5, 1, 9001, 131072, 0),     # pairs of rows, the last one with zeros
+    ("f32", 1, 2, 9002, 524288, 0),     # outer passes with a tile
+])
+def test_gates_on_the_row_engine(dtype, B, H, N, M, shift):
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype, alpha=(1e-3, 1e-2))
+    u, gw, gv, k = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v"), synth.gen_k(w)
+    plan = fftconv.Plan(N, M, H, dtype)
+    kf = plan.filter_fft(torch.from_numpy(k).cuda())
+
+    def placed(t):                      # `shift` elements behind an aligned address
+        room = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")
+        room[shift:].copy_(t.flatten())
+        return room[shift:].view(t.shape)
+
+    for use_w, use_v in ((True, True), (True, False), (False, True)):
+        y = plan.forward_gated(u.cuda(), placed(gw) if use_w else None, placed(gv) if use_v else None, kf).cpu()
+        v = gv.double().numpy() if use_v else None
+        ref = oracle.fftconv_gated(u.double().numpy(), gw.double().numpy() if use_w else None, v, k, M)
+        assert parity_error(y.double().numpy(), ref, TOL[dtype], "gates %d%d" % (use_w, use_v), v) <= TOL[dtype]
 
 
 def test_gated_without_gates_is_forward_and_errors():
