@@ -340,7 +340,7 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
 // Several runs: a run's sum goes, in register order, where its first row of u was (nobody else reads that block), and
 // k_long_blocks_sum adds them up.  Few channels leave the chip idle otherwise, and two launches per batch row and tensor ahead of
 // this one: whole gradient, us, bf16 16 x 1 x 65536 307 -> 63, f16 73 x 1 x 20000 fft 65536 1317 -> 101, 16 x 1 x 2^20 467 -> 192, fp32
-// 8 x 16 x 10000 fft 32768 170 -> 52; 16 x 64 x 16384 464 -> 231; where the chip was full, bf16 2 x 256 x 65536, 414 -> 402.
+// 8 x 16 x 10000 fft 32768 170 -> 52; 16 x 64 x 16384 464 -> 231 (the first four less again, see ADD_RUNS); where the chip was full, bf16 2 x 256 x 65536, 414 -> 402.
 __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(float2 *tu, const float2 *td, int64_t stride, int nb, int per,
                                                                float4 *acc, float2 *out, const float2 *__restrict__ tab, bool first,
                                                                bool last)
@@ -430,6 +430,29 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_sum(const float2 *part
     tw1.load(tab, tid);
     rf::inverse<G>(x, XL, tab, tw1, tid);
     store_row<G>(x, out + base, tid);
+}
+
+// Several runs: the same sums, a pair of bins to a thread, to out (acc, or the first run's place); every compute unit takes part, where the
+// few workgroups of k_long_blocks_sum fetch a run's 64 KB after the other's.  Same additions in the same order.
+__global__ void __launch_bounds__(256) k_long_runs_add(const float4 *part, int64_t apart, int runs, const float4 *acc, float4 *out, bool first)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    float4 x = first ? part[i] : acc[i];
+    constexpr int AT_ONCE = 8;
+    for (int r = first ? 1 : 0; r < runs; r += AT_ONCE) {
+        float4 v[AT_ONCE];
+#pragma unroll
+        for (int j = 0; j < AT_ONCE; ++j) v[j] = part[min(r + j, runs - 1) * apart + i];
+#pragma unroll
+        for (int j = 0; j < AT_ONCE; ++j)
+            if (r + j < runs) {
+                x.x += v[j].x;
+                x.y += v[j].y;
+                x.z += v[j].z;
+                x.w += v[j].w;
+            }
+    }
+    out[i] = x;
 }
 
 // Inverse, columns: the factors of A, then real part times scale of the samples n < Nk -> dk (rows, Nk).
@@ -571,16 +594,21 @@ constexpr int B_LDS = RB::LDS_BYTES;
 // 64, 128, 256 MiB, all at once 510, 325, 246, 246).
 constexpr int64_t GRAD_TRIP = (int64_t)1 << 28, GRAD_LEAST = (int64_t)1 << 25;
 
+// Four runs or more (of 128 spectra at most, then) are added up by k_long_runs_add first, and cost less.  Whole gradient, us, with the
+// other kernel alone: bf16 16 x 1 x 65536 59.7 -> 40.5, 16 x 5 74.0 -> 67.9, 8 x 4 56.0 -> 50.2, 30 x 2 x 131072 105 -> 87, f16 73 x 1 x 20000 fft 65536
+// 97.8 -> 60.9 (64.7 with no more runs than before), fp32 4 x 4 x 16384 30.2 -> 29.1, 8 x 16 x 10000 fft 32768 53.8 -> 51.3.
+constexpr int64_t ADD_RUNS = 4;
+
 // nh channels of `blocks` blocks each; runs of batch rows where channels alone leave compute units idle: as many as fill the
 // chip (two workgroups to a unit), and no more than pay for adding them up (a run's sum takes about a sixteenth of the time of
-// a batch row's two transforms, one after another)
+// a batch row's two transforms, one after another; a quarter of that from ADD_RUNS up)
 int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const float2 *td, int64_t stride, int64_t nb, float2 *acc,
                 float2 *out, bool first, bool last, hipStream_t s)
 {
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_corr, B_LDS));
     int64_t runs = 512 / (blocks * nh);
     if (runs > nb) runs = nb;
-    while (runs > 1 && runs * runs > 16 * nb) --runs;
+    while (runs > 1 && runs * runs > (runs >= ADD_RUNS ? 64 : 16) * nb) --runs;
     if (runs < 1) runs = 1;
     const int64_t per = (nb + runs - 1) / runs;
     runs = (nb + per - 1) / per;
@@ -589,6 +617,15 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
                        (int)nb, (int)per, (float4 *)acc, out, tab, first, last);
     FC_HIP(hipGetLastError());
     if (runs == 1) return FFTCONV_OK;
+    if (runs >= ADD_RUNS) {
+        const int64_t pairs = blocks * nh * (LB / 2);             // a multiple of 256
+        hipLaunchKernelGGL(k_long_runs_add, dim3((unsigned)(pairs / 256)), dim3(256), 0, s, (const float4 *)tu, per * stride / 2, (int)runs,
+                           (const float4 *)acc, last ? (float4 *)tu : (float4 *)acc, first);
+        FC_HIP(hipGetLastError());
+        if (!last) return FFTCONV_OK;
+        first = true;
+        runs = 1;
+    }
     FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_sum, B_LDS));
     hipLaunchKernelGGL(k_long_blocks_sum, dim3((unsigned)blocks, (unsigned)nh), dim3(RB::T), B_LDS, s, tu, per * stride, (int)runs,
                        (float4 *)acc, out, tab, first, last);

@@ -30,6 +30,15 @@ def test_runs_trips_and_pieces(dtype, B, H, N, M):
     assert err <= TOL["f32"]             # fp32 sums whatever the I/O type
 
 
+@pytest.mark.parametrize("dtype,B,H,N,M", [
+    ("f16", 73, 1, 200, 65536),          # 37 runs of two, the last one of one: added up eight at a time, the last time four
+    ("bf16", 4, 2, 120, 131072),         # four runs, the fewest that are added up by a kernel of their own
+    ("f32", 9, 42, 60, 32768),           # four runs of 126 spectra
+])
+def test_many_runs(dtype, B, H, N, M):
+    test_runs_trips_and_pieces(dtype, B, H, N, M)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("B,H,N,M", [
     (64, 2, 128, 256), (70, 3, 120, 256),        # two runs of one input each; of an input and a ragged one
