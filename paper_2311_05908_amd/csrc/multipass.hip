@@ -1489,8 +1489,15 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
                : dispatch_outer<false>(true, g, grid, S, y, (int)B, (int)p->H, (int)p->N, p->M, s, c_lo, c_hi, mirror, vg);
 }
 
+// Whether the last row of an odd batch goes with the pairs and zeros for a partner.  On its own it has half the work, and three launches:
+// 15 us where the chip has room for it beside the pairs.  us, on its own, with the pairs (outer length x H; B = 3): 16 11 x 1 x 65536 fp16 35.0, 19.3; 256
+// 3 x 16 x 65536 43.9, 34.4; 512 54.5, 45.7; 1024 75.5, 69.8, outer length 8 71.2, 66.7, 256 91.8, 85.8, 512 113, 103; 33 x 64 x 65536 561, 554; 1536
+// 112, 113; 2048 152, 170.  Outer lengths 1 and 2 have no passes for a row on its own: 9 x 400 x 8190 circular 90, 73.  Its error is that of the
+// other rows, a fifth to a quarter below that of a real row.
+static bool lone_in_pairs(const fftconv_plan *p) { return p->M <= 2 * MI || p->H * (p->M / MI) <= 1024; }
+
 // Batch rows are transformed two at a time (one complex transform per pair, the filter being real); a row left
-// over (odd B, B = 1) goes through a set of passes of its own as a real sequence (see above).
+// over (odd B, B = 1) goes with them, or through a set of passes of its own as a real sequence (see above).
 int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, void *workspace,
                       hipStream_t s, int ko_lo, int ko_hi, const void *wg, const void *vg)
 {
@@ -1500,12 +1507,12 @@ int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void
     // reads u and writes y itself, nothing passes through the workspace.  Gated calls and N not a multiple of 4
     // (rows that start off an 8-byte boundary) keep the three passes.
     if (p->M == MI && p->N % 4 == 0 && !wg && !vg) return fused3_inner_whole(p, u, kf, y, B, s);
-    const int64_t Be = B - B % 2;                        // rows in pairs
+    const int64_t Be = B > 1 && lone_in_pairs(p) ? B : B - B % 2;      // rows in pairs
     if (Be > 0) {
         const int rc = multipass_passes(p, u, kf, y, Be, S, s, ko_lo, ko_hi, wg, vg, false);
         if (rc) return rc;
     }
-    if (B % 2 == 0) return FFTCONV_OK;
+    if (Be == B) return FFTCONV_OK;
     const size_t ofs = (size_t)Be * (size_t)p->H * (size_t)p->N;             // elements before the last row
     auto at = [&](const void *base) { return base ? (const void *)((const uint16_t *)base + ofs) : nullptr; };
     return multipass_passes(p, at(u), kf, (uint16_t *)y + ofs, 1, S + (size_t)(Be / 2) * p->H * p->M, s, ko_lo, ko_hi,

@@ -88,3 +88,22 @@ def test_rows_of_one_fp16_sample(M, B):
         bound = 2.0 ** -9 + 2 * 2.0 ** -25 * M / min(M // 8192, 64) / inner.abs().min().item()
         print("one sample f16 M=%d B=%d %s err=%.3e bound=%.3e" % (M, B, name, err, bound), flush=True)
         assert err <= bound
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,N,M", [
+    (3, 128, 500, 65536),       # the last row of an odd batch with the pairs, at the line
+    (3, 129, 500, 65536),       # ... and beyond, as a real row
+    (5, 2, 4001, 1 << 22),      # outer length 512, the line again
+    (3, 3, 4001, 1 << 22),
+    (3, 700, 8190, 8192),       # outer length 1 has no passes of real rows
+])
+def test_the_last_row_of_an_odd_batch(dtype, B, H, N, M):
+    g = torch.Generator().manual_seed(B * H)
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype])
+    k = torch.randn(H, 300, generator=g) * 0.1
+    plan = fftconv.Plan(N, M, H, dtype, path="multipass")
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda())).cpu().double()
+    L = M if N + 299 > M else 2 * N             # the circular length, or one that no output reaches around
+    ref = torch.fft.irfft(torch.fft.rfft(u.double(), L) * torch.fft.rfft(k.double(), L), L)[..., :N]
+    assert parity_error(y.numpy(), ref.numpy(), TOL[dtype], "odd batch") <= TOL[dtype]
