@@ -32,7 +32,7 @@ using rf::Row;
 // (GATED: one less, for the gates)
 constexpr int waves_of(int M, bool gated = false) { return (M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2) - (gated && M <= 4096 && M != 512 && M != 1024 ? 1 : 0); }
 
-template <int M, typename IO> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096>;
+template <int M, typename IO, bool WIDE = false> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096, false, WIDE>;
 
 // 16-bit rows of 256 points, which lie 512 bytes or less from those of the next channel: beyond the 256 MB memory-side cache the
 // order of the rows in memory counts for more than that of k_f (2 KB a channel), and neighbours are the channels of a pair,
@@ -45,12 +45,12 @@ template <int M, typename IO> constexpr bool BY_PAIR = M == 256 && sizeof(IO) ==
 // GATED: y = v . ((u . w) * k), either gate may be null; roundings as below (k_row_conv_few).  With an elementwise kernel for each gate
 // instead, us: f16 circular 42 x 768 x 512 69 -> 36, bf16 circular 64 x 256 x 256 23 -> 11, 16 x 256 x 2048 41 -> 23, odd rows 16 x 256 x 1001
 // (fft 2048) 28 -> 19; fp32 8 x 128 x 4096 (fft 8192) 35 -> 20, 8 x 64 x 16384 circular 55 -> 31, 16 x 64 x 1024 (fft 2048) 16 -> 8.
-template <int M, typename IO, bool HALF, bool GATED>
-__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M, GATED))
+template <int M, typename IO, bool HALF, bool GATED, bool WIDE>
+__global__ void __launch_bounds__(rf::threads_of(M), WIDE ? (GATED ? 3 : 4) : waves_of(M, GATED))
     k_row_conv(const IO *__restrict__ u, IO *__restrict__ y, const float4 *__restrict__ kf, const float2 *__restrict__ tab, int B,
                int H, int N, int npairs, int total, int per_die, int nh, const IO *__restrict__ wg, const IO *__restrict__ vg)
 {
-    using G = ConvRow<M, IO>;
+    using G = ConvRow<M, IO, WIDE>;
     constexpr int RW = rf::threads_of(M) / G::T;                  // rows (pairs) per workgroup
     extern __shared__ float2 smem_rows[];
     const bool by_pair = BY_PAIR<M, IO> && nh > 0;
@@ -81,19 +81,31 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M, GATED))
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
     // k_f of this thread's bins: requested ahead of the last pass as far as the registers go
-    constexpr int EARLY = M == 16384 ? G::P / 4 : G::P / 2;
-    float4 kv[G::P / 2];
-    const float4 *kr = kf + (int64_t)h * (M / 2) + tid;
-    rf::forward<G, HALF>(x, Z, tab, tw1, tid, [&] {
+    if constexpr (WIDE) {                                         // (it lies in the order of the other rows' registers)
+        using G0 = ConvRow<M, IO>;
+        float2 kv[G::P];
+        const float2 *const kr = (const float2 *)kf + (int64_t)h * M + G0::index(G::freq(tid, 0));
+        rf::forward<G, HALF>(x, Z, tab, tw1, tid, [&] {
 #pragma unroll
-        for (int q = 0; q < EARLY; ++q) kv[q] = kr[q * G::T];
-    });
+            for (int p = 0; p < G::P; ++p) kv[p] = kr[G0::index(G::freq(0, p))];
+        });
 #pragma unroll
-    for (int q = EARLY; q < G::P / 2; ++q) kv[q] = kr[q * G::T];
+        for (int p = 0; p < G::P; ++p) x[p] = rf::mul(x[p], kv[p]);
+    } else {
+        constexpr int EARLY = M == 16384 ? G::P / 4 : G::P / 2;
+        float4 kv[G::P / 2];
+        const float4 *kr = kf + (int64_t)h * (M / 2) + tid;
+        rf::forward<G, HALF>(x, Z, tab, tw1, tid, [&] {
 #pragma unroll
-    for (int q = 0; q < G::P / 2; ++q) {
-        x[2 * q] = rf::mul(x[2 * q], make_float2(kv[q].x, kv[q].y));
-        x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
+            for (int q = 0; q < EARLY; ++q) kv[q] = kr[q * G::T];
+        });
+#pragma unroll
+        for (int q = EARLY; q < G::P / 2; ++q) kv[q] = kr[q * G::T];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) {
+            x[2 * q] = rf::mul(x[2 * q], make_float2(kv[q].x, kv[q].y));
+            x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
+        }
     }
     if constexpr (GATED) {
         using Raw = rf::RawPair<G, IO, HALF>;
@@ -117,12 +129,12 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M, GATED))
 // wg multiplies u, bit 1: vg multiplies y).  The transforms and the product with k_f are fp32; u . w is rounded to the I/O type,
 // as is the convolution before it meets the output gate: the same values as without a fused gate, whichever kernel a call
 // takes.  For calls of few rows: see row_forward_few().
-template <int M, typename IO, int GATE>
-__global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
+template <int M, typename IO, int GATE, bool WIDE>
+__global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint32_t *__restrict__ kf, const float2 *__restrict__ tab,
                    const IO *__restrict__ wg, const IO *__restrict__ vg, int B, int H, int N, int npairs, int total)
 {
-    using G = Row<M>;
+    using G = Row<M, false, false, WIDE>;
     constexpr int RW = rf::threads_of(M) / G::T;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
@@ -164,13 +176,13 @@ __global__ void __launch_bounds__(rf::threads_of(M), waves_of(M))
     if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }
 
-template <int M, typename IO, bool HALF, bool GATED>
+template <int M, typename IO, bool HALF, bool GATED, bool WIDE>
 int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
-    using G = ConvRow<M, IO>;
+    using G = ConvRow<M, IO, WIDE>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T;
     constexpr int lds = RW * G::LDS_BYTES;
-    FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF, GATED>, lds));
+    FC_TRY(raise_dynamic_lds((const void *)k_row_conv<M, IO, HALF, GATED, WIDE>, lds));
     // A launch holds less than 2^32 threads, and the kernel counts rows in 32 bits: longer calls go out in pieces of MOST
     // pairs, whole channels where the batch allows it.
     constexpr int64_t MOST = ((int64_t)1 << 31) / G::T;
@@ -181,7 +193,7 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
         for (int64_t h0 = 0; h0 < H; h0 += nh) {
             const int64_t hs = H - h0 < nh ? H - h0 : nh, total = hs * np, groups = (total + RW - 1) / RW, per_die = (groups + 7) / 8;
             const int64_t at = (2 * p0 * H + h0) * N;
-            hipLaunchKernelGGL((k_row_conv<M, IO, HALF, GATED>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u + at,
+            hipLaunchKernelGGL((k_row_conv<M, IO, HALF, GATED, WIDE>), dim3((unsigned)(8 * per_die)), dim3(NTHR), lds, s, (const IO *)u + at,
                                (IO *)y + at, (const float4 *)kf + h0 * (M / 2), rf::row_table<G>(p), (int)nb, (int)H, (int)N, (int)np,
                                (int)total, (int)per_die, by_pair ? (int)hs : 0, wg ? (const IO *)wg + at : nullptr,
                                vg ? (const IO *)vg + at : nullptr);
@@ -191,13 +203,26 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
     return FFTCONV_OK;
 }
 
+// Pairs of rows up to which they are WIDE.  us, others, wide: fp32 causal fft 512, 512 pairs 7.9, 5.3, 2048 8.3, 6.1, 3072 8.6, 8.1, 4096 8.8, 10.1; 1024, 512 8.6,
+// 6.1, 2048 9.5, 8.3, 4096 16.4, 15.6, 6144 20.2, 22.1; fp16 circular 512, 3072 9.2, 7.8, 4096 9.4, 9.5; 1024, 4096 15.2, 15.0, 6144 20.3, 20.4.  Both gates: 512,
+// fp32 6144 17.2, 16.4, 8192 20.3, 21.4, bf16 circular 20.9, 19.5 and 22.9, 23.3; 1024 always, fp32 8192 35.6, 33.0, 24576 43.8, 41.1, bf16 circular 8192
+// 42.5, 36.3, fp16 32768 160, 159.  Calls of few rows (k_row_conv_few): 512 bf16 3072 7.9, 7.1, 4096 8.0, 8.2; 1024, 1024 8.0, 6.9, 1536 8.1, 8.9.
+template <int M> constexpr int64_t wide_most(bool gated) { return M == 512 ? (gated ? 6144 : 3072) : gated ? INT64_MAX : 4096; }
+template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
+
 template <int M, typename IO>
-int launch_half(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
+int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
-    if (wg || vg)
-        return p->N <= M / 2 ? launch<M, IO, true, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true>(p, u, kf, y, B, wg, vg, s);
-    return p->N <= M / 2 ? launch<M, IO, true, false>(p, u, kf, y, B, nullptr, nullptr, s)
-                         : launch<M, IO, false, false>(p, u, kf, y, B, nullptr, nullptr, s);
+    const bool half = p->N <= M / 2, gated = wg || vg;
+    if constexpr (rf::has_wide(M)) {
+        if (p->H * ((B + 1) / 2) <= wide_most<M>(gated)) {
+            if (gated) return half ? launch<M, IO, true, true, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true, true>(p, u, kf, y, B, wg, vg, s);
+            return half ? launch<M, IO, true, false, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, true>(p, u, kf, y, B, wg, vg, s);
+        }
+    }
+    if constexpr (M != 1024)
+        if (gated) return half ? launch<M, IO, true, true, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true, false>(p, u, kf, y, B, wg, vg, s);
+    return half ? launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, false>(p, u, kf, y, B, wg, vg, s);
 }
 
 }  // namespace
@@ -221,6 +246,8 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     };
     add_length(M < 8192 ? M : 8192);
     if (M == 16384 || M == 32768) add_length(16384);
+    if (M == 512) add(Row<512, false, false, true>()), add(Row<512, true, false, true>());
+    if (M == 1024) add(Row<1024, false, false, true>()), add(Row<1024, true, false, true>());
     return t;
 }
 
@@ -228,10 +255,10 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 {
     return rf::with_row(p->M, [&](auto g) -> int {
         using G = decltype(g);
-        if (p->dtype == FFTCONV_F32) return launch_half<G::M, float>(p, u, kf, y, B, wg, vg, s);
+        if (p->dtype == FFTCONV_F32) return launch_row<G::M, float>(p, u, kf, y, B, wg, vg, s);
         if constexpr (G::M <= 4096) {                             // longer 16-bit rows run on the matrix cores
-            if (p->dtype == FFTCONV_F16) return launch_half<G::M, __half>(p, u, kf, y, B, wg, vg, s);
-            return launch_half<G::M, __hip_bfloat16>(p, u, kf, y, B, wg, vg, s);
+            if (p->dtype == FFTCONV_F16) return launch_row<G::M, __half>(p, u, kf, y, B, wg, vg, s);
+            return launch_row<G::M, __hip_bfloat16>(p, u, kf, y, B, wg, vg, s);
         }
         set_error("row kernels: no 16-bit instance for rows of %lld points", (long long)p->M);
         return FFTCONV_EUNSUPPORTED;
@@ -248,8 +275,10 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 //   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer; beyond six rounds half as many (fp16, 4096: one
 //     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116).  The lines of 4096 are from before the
 //     row kernel became a quarter faster there: it is now the faster one with up to half as many workgroups again as there are rounds;
-//   fft 1024: half as many, and not in the first round (both 8 - 9 us there);
-//   fft 512: half as many, and only if items are not full;
+//   fft 1024: up to 4096 pairs, beyond half as many workgroups;
+//   fft 512: up to 8192 pairs, beyond half as many, and only if items are not full.  With WIDE rows and full items (bf16, fp16, both gates), us, matrix cores, rows:
+//     512 32 x 16 8.4, 5.0 (8.9, 6.3), 32 x 256 9.0, 8.0 (9.3, 8.8), 32 x 512 12.1, 10.8 (13.4, 12.2), 32 x 1024 18.4, 18.0 (21.6, 23.1);
+//     1024 16 x 16 8.4, 6.6 (8.9, 7.1), 16 x 256 9.2, 8.4 (9.5, 9.1), 16 x 512 12.0, 11.0 (13.4, 12.7), 16 x 1024 18.5, 18.8 (21.6, 22.8);
 //   fft 256: 40 Ki pairs + 56 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, 256 42, 40; 8192
 //     channels: B = 33 98, 51, fp16 64 106, 116.
 // Lines measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
@@ -267,8 +296,8 @@ bool row_few(int64_t M, int64_t H, int64_t B)
     const int64_t full = 8192 / M, items = H * ((npairs + full - 1) / full), rounds = (items + CUS - 1) / CUS;
     const int64_t rows = M == 512 ? 16 : M == 1024 ? 8 : M == 2048 ? 2 : 1, groups = (pairs + rows - 1) / rows;
     if (M >= 2048) return groups <= CUS * rounds && (rounds <= 6 || 2 * groups <= CUS * rounds);
-    if (M == 1024) return rounds > 1 && groups <= CUS * ((rounds + 1) / 2);
-    return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
+    if (M == 1024) return pairs <= 4096 || (rounds > 1 && groups <= CUS * ((rounds + 1) / 2));
+    return pairs <= 8192 || (pairs < full * items && 2 * groups <= CUS * (rounds + 1));
 }
 
 // for calls that row_few() takes
@@ -280,18 +309,25 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
         if constexpr (M > 4096) {
             return FFTCONV_EUNSUPPORTED;
         } else {
-            auto go = [&](auto io) -> int {
+            auto form = [&](auto io, auto w) -> int {
                 using IO = decltype(io);
-                constexpr int NTHR = rf::threads_of(M), RW = NTHR / Row<M>::T, lds = RW * Row<M>::LDS_BYTES;
-                auto kern = wg ? (vg ? k_row_conv_few<M, IO, 3> : k_row_conv_few<M, IO, 1>)
-                               : (vg ? k_row_conv_few<M, IO, 2> : k_row_conv_few<M, IO, 0>);
+                constexpr bool WIDE = decltype(w)::value;
+                using G = Row<M, false, false, WIDE>;
+                constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
+                auto kern = wg ? (vg ? k_row_conv_few<M, IO, 3, WIDE> : k_row_conv_few<M, IO, 1, WIDE>)
+                               : (vg ? k_row_conv_few<M, IO, 2, WIDE> : k_row_conv_few<M, IO, 0, WIDE>);
                 const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
                 FC_TRY(raise_dynamic_lds((const void *)kern, lds));
                 hipLaunchKernelGGL(kern, dim3((unsigned)((total + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
-                                   (const uint32_t *)kf, rf::row_table<Row<M>>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,
+                                   (const uint32_t *)kf, rf::row_table<G>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,
                                    (int)p->N, (int)npairs, (int)total);
                 FC_HIP(hipGetLastError());
                 return FFTCONV_OK;
+            };
+            auto go = [&](auto io) -> int {
+                if constexpr (rf::has_wide(M))
+                    if (p->H * ((B + 1) / 2) <= FEW_WIDE<M>) return form(io, std::true_type());
+                return form(io, std::false_type());
             };
             return p->dtype == FFTCONV_F16 ? go(__half()) : go(__hip_bfloat16());
         }

@@ -37,7 +37,7 @@
 namespace fftconv {
 namespace rf {
 
-template <int M> struct Radix;
+template <int M, bool WIDE = false> struct Radix;
 template <> struct Radix<256> { static constexpr int R0 = 16, R1 = 16, R2 = 1; };
 template <> struct Radix<512> { static constexpr int R0 = 32, R1 = 16, R2 = 1; };
 template <> struct Radix<1024> { static constexpr int R0 = 32, R1 = 32, R2 = 1; };
@@ -45,15 +45,19 @@ template <> struct Radix<2048> { static constexpr int R0 = 16, R1 = 16, R2 = 8; 
 template <> struct Radix<4096> { static constexpr int R0 = 16, R1 = 16, R2 = 16; };
 template <> struct Radix<8192> { static constexpr int R0 = 32, R1 = 16, R2 = 16; };
 template <> struct Radix<16384> { static constexpr int R0 = 32, R1 = 32, R2 = 16; };
+// WIDE rows: a wave each, 8 or 16 points a thread and a trip through LDS more, for calls of few rows: the instructions of a thread one after the
+// other are the time there (16 pairs of rows: fp32 fft 512 7.4 -> 5.0 us, 1024 8.0 -> 5.4; 16 . 8 . 8 instead, 5.7).
+template <> struct Radix<512, true> { static constexpr int R0 = 8, R1 = 8, R2 = 8; };
+template <> struct Radix<1024, true> { static constexpr int R0 = 16, R1 = 4, R2 = 16; };
 
 // number of twiddles of a radix-R pass that come from the table, all or 1, 2, 3, 4, 8, 12, .., and their powers
 constexpr int tw_count(int R, bool exact) { return exact ? R - 1 : R / 4 + 2; }
 constexpr int tw_power(int i, bool exact) { return exact || i < 3 ? i + 1 : 4 * (i - 2); }
 
-template <int M_, bool EXACT_ = false, bool FINE_ = false> struct Row {
+template <int M_, bool EXACT_ = false, bool FINE_ = false, bool WIDE_ = false> struct Row {
     static constexpr int M = M_;
-    static constexpr bool EXACT = EXACT_, FINE = FINE_;
-    static constexpr int R0 = Radix<M>::R0, R1 = Radix<M>::R1, R2 = Radix<M>::R2;
+    static constexpr bool EXACT = EXACT_, FINE = FINE_, WIDE = WIDE_;
+    static constexpr int R0 = Radix<M, WIDE>::R0, R1 = Radix<M, WIDE>::R1, R2 = Radix<M, WIDE>::R2;
     static constexpr int P = R0;                           // points per thread
     static constexpr int T = M / R0;                       // threads per row
     static constexpr bool THREE = R2 > 1;

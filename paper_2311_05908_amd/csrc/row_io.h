@@ -276,16 +276,20 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&v)[4])
 // instructions of the gradient's tail at 8192 points (k_row_dk_finish, 768 channels 25.1 -> 19.8 us; the few-row kernel, 1 x 768 x 2048 gated 13.5 -> 10.5).
 template <typename G> __device__ __forceinline__ int slot_of(int tid, int p)
 {
-    if constexpr (G::M == 2048) return kernel_slot<2048>(G::freq(tid, p));
+    if constexpr (G::M == 2048 || (G::M == 512 && G::WIDE)) return kernel_slot<G::M>(G::freq(tid, p));
     else return kernel_slot<G::M>(G::freq(tid, 0)) + (kernel_slot<G::M>(G::freq(0, p)) - kernel_slot<G::M>(G::freq(0, 0)));
 }
 
+// lengths with WIDE rows
+constexpr bool has_wide(int M) { return M == 512 || M == 1024; }
+
 // The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
-// that or 32768.
+// that or 32768, and of wide rows where M has them.
 template <typename G> inline const float2 *row_table(const fftconv_plan *p)
 {
-    const size_t at = G::M == 16384 ? Row<8192, false>::TABLE + Row<8192, true>::TABLE : 0;
-    return p->row_tw + at + (G::EXACT ? Row<G::M, false>::TABLE : 0);
+    size_t at = G::M == 16384 ? Row<8192, false>::TABLE + Row<8192, true>::TABLE : 0;
+    if (G::WIDE) at = Row<G::M, false>::TABLE + Row<G::M, true>::TABLE;
+    return p->row_tw + at + (G::EXACT ? Row<G::M, false, false, G::WIDE>::TABLE : 0);
 }
 
 }  // namespace rf

@@ -253,3 +253,26 @@ def test_few_rows_round_at_the_gates(M, dtype):
         differ = (y != ref).float().mean().item()
         print("gates %s M=%d w=%d v=%d differ=%.4f" % (dtype, M, wg is not None, vg is not None, differ), flush=True)
         assert differ <= 0.02
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M,gates", [
+    ("f32", 2, 3072, 65, 512, 0), ("f32", 3, 1537, 65, 512, 0),          # wide rows up to the line, the others from there on
+    ("bf16", 2, 3072, 300, 512, 0), ("f16", 2, 3073, 511, 512, 0),
+    ("f16", 2, 6144, 64, 512, 3), ("bf16", 1, 6145, 300, 512, 2),
+    ("f32", 2, 4096, 65, 1024, 0), ("bf16", 2, 4097, 514, 1024, 0), ("f32", 1, 4500, 300, 1024, 1),
+    ("bf16", 2, 3072, 64, 512, 0), ("f16", 2, 3073, 64, 512, 3),         # the same of calls of few rows on a matrix-core plan
+    ("bf16", 1, 1024, 512, 1024, 3), ("f16", 2, 1025, 256, 1024, 0),
+    ("f16", 2, 8192, 32, 512, 0), ("bf16", 32, 256, 512, 1024, 0), ("bf16", 16, 513, 64, 1024, 0),      # those of 4096 and 8192 pairs
+])
+def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
+    g = torch.Generator().manual_seed(H + N)
+    u, w, v = (torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(3))
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype)
+    y = plan.forward_gated(u.cuda(), w.cuda() if gates & 1 else None, v.cuda() if gates & 2 else None, plan.filter_fft(k.cuda())).cpu().double()
+    x = u.double() * w.double() if gates & 1 else u.double()
+    ref = torch.fft.irfft(torch.fft.rfft(x, M) * torch.fft.rfft(k.double(), M), M)[..., :N]
+    if gates & 2:
+        ref = ref * v.double()
+    weight = v.double().numpy() if gates & 2 else None
+    assert parity_error(y.numpy(), ref.numpy(), TOL[dtype], "line", weight) <= TOL[dtype]
