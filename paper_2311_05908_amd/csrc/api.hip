@@ -522,6 +522,8 @@ int fftconv_backward_filter(const fftconv_plan *p, const void *u, const void *dy
     }
     hipStream_t s = (hipStream_t)stream;
     if (B > 0 && f3::fused3_dk_supported(p)) {
+        // (rows that the matrix-core kernel refuses stay refused)
+        if (row_backward_filter_few(p, B) && (((uintptr_t)u | (uintptr_t)dy) & 15) == 0) return row_backward_filter(p, u, dy, dk, Nk, B, workspace, s);
         rc = f3::fused3_dk_accumulate(p, u, dy, workspace, B, s);       // 8192 accumulator slots per channel
         if (!rc) rc = row_dk_finish(p, workspace, f3::fused3_dk_runs(p, B), dk, Nk, s);
         return rc;

@@ -84,19 +84,20 @@ template <int R, bool INV, bool HALFIN = false, Butterfly FORM = EIGHT> __device
     }
 }
 
-// The transform of 32 points as 4 x 8, the twiddles W_32^{j k} between the two products of their own: x[j + 8 a] over a, times
-// W_32^{j k}, then over j; frequency k + 4 m.  As many operations as the radix-2 form above with eight a butterfly, and half
-// as many roundings on a path (1.2 levels of products instead of 2.1).
-template <bool INV, bool HALFIN> __device__ __forceinline__ void dft32_4x8(float2 (&x)[32])
+// The transform of 32 points as 4 x 8, or of 16 as 4 x 4, the twiddles W_R^{j k} between the two products of their own: x[j + R/4 a] over a,
+// times W_R^{j k}, then over j; frequency k + 4 m.  As many operations as the radix-2 form above with eight a butterfly, and half
+// as many roundings on a path (32 points: 1.2 levels of products instead of 2.1).
+template <int R, bool INV, bool HALFIN> __device__ __forceinline__ void dft_4xn(float2 (&x)[R])
 {
-    float2 t[4][8];
+    constexpr int Q = R / 4;
+    float2 t[4][Q];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float2 v[4] = {x[j], x[j + 8], x[j + 16], x[j + 24]};
+    for (int j = 0; j < Q; ++j) {
+        float2 v[4] = {x[j], x[j + Q], x[j + 2 * Q], x[j + 3 * Q]};
         dft_reg<4, INV, HALFIN>(v);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int q = j * k;                               // 0 .. 21
+            const int q = j * k * (32 / R);                    // 0 .. 21
             const float wr = C32[q], wi = INV ? S32[q] : -S32[q];
             if (q == 0) t[k][j] = v[k];
             else if (q == 8) t[k][j] = INV ? make_float2(-v[k].y, v[k].x) : make_float2(v[k].y, -v[k].x);
@@ -105,9 +106,9 @@ template <bool INV, bool HALFIN> __device__ __forceinline__ void dft32_4x8(float
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        dft_reg<8, INV>(t[k]);
+        dft_reg<Q, INV>(t[k]);
 #pragma unroll
-        for (int m = 0; m < 8; ++m) x[k + 4 * m] = t[k][m];
+        for (int m = 0; m < Q; ++m) x[k + 4 * m] = t[k][m];
     }
 }
 

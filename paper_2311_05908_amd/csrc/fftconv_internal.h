@@ -306,6 +306,7 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
                     hipStream_t s);
 // the filter gradient on the same rows (row_grad.hip): plans up to fft_size 16384 without a matrix-core gradient kernel
 bool row_backward_filter_ok(const fftconv_plan *p);
+bool row_backward_filter_few(const fftconv_plan *p, int64_t B);       // calls of matrix-core plans, in the workspace of their own gradient
 size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B);
 int row_backward_filter(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace,
                         hipStream_t s);

@@ -18,7 +18,7 @@
 //  * radices 32 and 16 (fewest twiddle products and exchanges that 64 data registers allow);
 //  * twiddles come from tables in thread order, [factor][thread] (gathers from a table of W_M^t, one cache line per lane,
 //    bounded the kernels that this file replaces).
-// FINE: radix-32 butterflies as 4 x 8 (dft32_4x8()), see row_grad.hip.
+// FINE: radix-32 butterflies as 4 x 8, radix-16 ones as 4 x 4 (dft_4xn()), see row_grad.hip.
 // Two kinds of row.  EXACT: all R - 1 twiddles of a butterfly come from the table, each correct to its own rounding, and the
 // in-register butterflies take eight operations.  Otherwise the table holds those for 1, 2, 3 and the multiples of 4, the
 // others are products of them, and butterflies take six: a tenth more error of a transform, and at fft 1024 68 us
@@ -196,7 +196,7 @@ template <typename G, bool FWD> __device__ __forceinline__ void exchange(float2 
 // a butterfly of the row's passes
 template <typename G, int R, bool INV, bool HALFIN = false> __device__ __forceinline__ void butterfly(float2 (&x)[R])
 {
-    if constexpr (G::FINE && R == 32) dft32_4x8<INV, HALFIN>(x);
+    if constexpr (G::FINE && R >= 16) dft_4xn<R, INV, HALFIN>(x);
     else dft_reg<R, INV, HALFIN, G::EXACT ? EIGHT : SIX>(x);
 }
 

@@ -15,7 +15,7 @@
 // 192 registers), by the latency of the exchanges between passes.  It replaces one
 // kernel for every factor of either transform, batch row by batch row, with the row in memory between them.  A training step
 // (filter transforms, forward pass, both gradients), us: fp32 8 x 128 x 3000 fft 8192 750 -> 124; bf16 circular
-// 16 x 256 x 1024 699 -> 86, 8 x 256 x 8192 1005 -> 229; bf16 8 x 256 x 777 fft 2048 490 -> 78.
+// 16 x 256 x 1024 699 -> 86, 8 x 256 x 8192 1005 -> 229; bf16 8 x 256 x 777 fft 2048 490 -> 78.  Few rows since (fp32 8 x 2 x 1024, fft 1024): 51 -> 38.
 #include "fftconv_internal.h"
 #include "row_io.h"
 
@@ -25,13 +25,13 @@ namespace {
 
 // Rows of the gradient.  Of 1024 points: radix-32 butterflies as 4 x 8 (FINE), as both passes are of radix 32 there and dk came out
 // at 2.05e-7 of error (fp32, 4 x 64 rows of 512 samples), where a kernel for every factor had 1.97e-7; now 1.78e-7.
-// Same time: 64 x 768 rows of 512, 125 -> 117 us, of 1024, 158 - 161 -> 171, 16 x 256 37 -> 37.  Dividing 16 x 16 x 4 instead, 1.80e-7, costs
+// (WIDE, with the radix-16 ones as 4 x 4: 1.73e-7.)  Same time: 64 x 768 rows of 512, 125 -> 117 us, of 1024, 158 - 161 -> 171, 16 x 256 37 -> 37.  Dividing 16 x 16 x 4 instead, 1.80e-7, costs
 // a trip through LDS: 154, 177, 30.
-template <int M> using GradRow = rf::Row<M, true, M == 1024>;
+template <int M, bool WIDE = false> using GradRow = rf::Row<M, true, M == 1024, WIDE>;
 
 // waves per SIMD that the registers allow: 192 data registers with 32 points a thread (12 - 60 bytes spilled where N > M / 2, and at
 // 1024 points), half of that with 16
-template <int M> constexpr int GRAD_WAVES = GradRow<M>::P == 32 ? 2 : 3;
+template <int M, bool WIDE = false> constexpr int GRAD_WAVES = GradRow<M, WIDE>::P == 32 ? 2 : 3;
 
 template <typename G>
 __device__ __forceinline__ void store_dk(const float2 (&x)[G::P], float *__restrict__ dk, int64_t Nk, float scale, int tid)
@@ -44,12 +44,12 @@ __device__ __forceinline__ void store_dk(const float2 (&x)[G::P], float *__restr
 }
 
 // HALF: N <= M / 2.  Row t = h * S + s of threads: batch rows [s * per, (s + 1) * per) of channel h.
-template <int M, typename IO, bool HALF>
-__global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
+template <int M, typename IO, bool HALF, bool WIDE>
+__global__ void __launch_bounds__(rf::threads_of(M), (GRAD_WAVES<M, WIDE>))
     k_row_corr(const IO *__restrict__ u, const IO *__restrict__ dy, float4 *__restrict__ part, float *__restrict__ dk,
                const float2 *__restrict__ tab, int B, int H, int N, int64_t Nk, int S, int per)
 {
-    using G = GradRow<M>;
+    using G = GradRow<M, WIDE>;
     constexpr int RW = rf::threads_of(M) / G::T;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T, rows = H * S;
@@ -112,11 +112,11 @@ __global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
 }
 
 // dk[h] from the S sums of channel h
-template <int M>
-__global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
+template <int M, bool WIDE>
+__global__ void __launch_bounds__(rf::threads_of(M), (GRAD_WAVES<M, WIDE>))
     k_row_dk(const float4 *__restrict__ part, float *__restrict__ dk, const float2 *__restrict__ tab, int H, int64_t Nk, int S)
 {
-    using G = GradRow<M>;
+    using G = GradRow<M, WIDE>;
     constexpr int RW = rf::threads_of(M) / G::T;
     extern __shared__ float2 smem_rows[];
     const int row = threadIdx.x / G::T, tid = threadIdx.x % G::T;
@@ -150,6 +150,36 @@ __global__ void __launch_bounds__(rf::threads_of(M), GRAD_WAVES<M>)
     if (live) store_dk<G>(x, dk + (int64_t)h * Nk, Nk, 1.f / M, tid);
 }
 
+// The sums of a channel's runs, two bins to a thread, to the first run's place: what k_row_dk does with a workgroup to a channel, a trip to memory
+// for each run.  The same additions in the same order.
+__global__ void __launch_bounds__(256) k_row_runs_add(float4 *part, int64_t apart, int S)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= apart) return;
+    float4 x = part[i];
+    constexpr int AT_ONCE = 8;
+    for (int s = 1; s < S; s += AT_ONCE) {
+        float4 v[AT_ONCE];
+#pragma unroll
+        for (int j = 0; j < AT_ONCE; ++j) v[j] = part[min(s + j, S - 1) * apart + i];
+#pragma unroll
+        for (int j = 0; j < AT_ONCE; ++j)
+            if (s + j < S) {
+                x.x += v[j].x;
+                x.y += v[j].y;
+                x.z += v[j].z;
+                x.w += v[j].w;
+            }
+    }
+    part[i] = x;
+}
+
+// From how many runs on that kernel adds them up, and the most pairs of bins that it does so with.  A run costs k_row_dk 0.2 us at 256 points, 0.3 at 512, 0.35 to 4096,
+// 0.75 at 8192, 1.5 at 16384; this kernel 3.5 us and little more (fp32, us: fft 512 16 x 1 rows 10.6, 14.2, 45 x 1 18.2, 14.1; 1024 16 x 1 14.2, 14.2, 45 x 1
+// 24.5, 16.1; 4096 45 x 1 30.9, 18.7; 8192 8 x 16 28.4, 26.6, 4 x 100 33.1, 35.9; 256 40 x 100 25.1, 17.2), unless it waits for memory: 1024, 16 x 256 27.9, 29.5.
+template <int M> constexpr int64_t ADD_RUNS = M == 256 ? 21 : M == 512 ? 17 : M <= 4096 ? 13 : M == 8192 ? 7 : 4;
+constexpr int64_t ADD_MOST = (int64_t)1 << 20;
+
 // Runs per channel: as many as give every SIMD of 256 compute units two waves (16 points a thread: four), no more than
 // the batch has rows, of equal length.
 // most: the runs that no smaller batch exceeds (4 rows in runs of 1 are more than 5 in runs of 2): what the workspace holds.
@@ -168,10 +198,10 @@ Splits grad_splits(int64_t M, int64_t H, int64_t B)
     return Splits{(B + per - 1) / per, per, want};
 }
 
-template <int M, typename IO, bool HALF>
+template <int M, typename IO, bool HALF, bool WIDE>
 int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
 {
-    using G = GradRow<M>;
+    using G = GradRow<M, WIDE>;
     constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
     const Splits sp = grad_splits(M, p->H, B);
     // rows of threads, and the threads of a launch (cut short without an error beyond 2^32), are 32-bit numbers
@@ -179,35 +209,69 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
         set_error("fftconv_backward_filter: too many sequences for the row kernel");
         return FFTCONV_EUNSUPPORTED;
     }
-    FC_TRY(raise_dynamic_lds((const void *)k_row_corr<M, IO, HALF>, lds));
+    FC_TRY(raise_dynamic_lds((const void *)k_row_corr<M, IO, HALF, WIDE>, lds));
     // so are batch rows: a longer batch goes out in pieces of whole runs, two or more in each
     const int64_t pieces = (sp.S * sp.per + (1 << 30) - 1) >> 30;
     for (int64_t i = 0; i < pieces; ++i) {
         const int64_t s0 = sp.S * i / pieces, ns = sp.S * (i + 1) / pieces - s0, b0 = s0 * sp.per, at = b0 * p->H * p->N;
         const int64_t nb = B - b0 < ns * sp.per ? B - b0 : ns * sp.per;
-        hipLaunchKernelGGL((k_row_corr<M, IO, HALF>), dim3((unsigned)((p->H * ns + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u + at,
+        hipLaunchKernelGGL((k_row_corr<M, IO, HALF, WIDE>), dim3((unsigned)((p->H * ns + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u + at,
                            (const IO *)dy + at, (float4 *)workspace + s0 * p->H * (M / 2), dk, rf::row_table<G>(p), (int)nb, (int)p->H,
                            (int)p->N, Nk, (int)ns, (int)sp.per);
         FC_HIP(hipGetLastError());
     }
     if (sp.S == 1) return FFTCONV_OK;
-    FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M>, lds));
-    hipLaunchKernelGGL(k_row_dk<M>, dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float4 *)workspace, dk,
-                       rf::row_table<G>(p), (int)p->H, Nk, (int)sp.S);
+    int64_t left = sp.S;
+    const int64_t apart = p->H * (M / 2);
+    if (sp.S >= ADD_RUNS<M> && sp.S * apart <= ADD_MOST) {
+        hipLaunchKernelGGL(k_row_runs_add, dim3((unsigned)((apart + 255) / 256)), dim3(256), 0, s, (float4 *)workspace, apart, (int)sp.S);
+        FC_HIP(hipGetLastError());
+        left = 1;
+    }
+    FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M, WIDE>, lds));
+    hipLaunchKernelGGL((k_row_dk<M, WIDE>), dim3((unsigned)((p->H + RW - 1) / RW)), dim3(NTHR), lds, s, (const float4 *)workspace, dk,
+                       rf::row_table<G>(p), (int)p->H, Nk, (int)left);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
 
+// WIDE rows (row_fft.h): always at 512 points, at 1024 for a few thousand rows.  us, others, wide (and with fewer runs' sums, see above): fp32 fft 512 1 x 16 10.5, 8.0, 16 x 16 22.9,
+// 11.7, 16 x 1024 32.0, 28.1, 64 x 768 68.8, 62.8, 2 x 4096 27.2, 26.7; fft 1024 1 x 16 11.0, 7.8, 16 x 16 25.4, 14.4, 32 x 256 39.3, 33.7, 16 x 1024 47.4, 49.5, 64 x 768 109, 123, 2 x 4096 22.8, 25.2.
+bool grad_wide(int64_t M, int64_t H, int64_t B) { return M == 512 || (H <= 1024 && H * B <= 8192); }
+
 template <int M, typename IO>
 int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
 {
-    return p->N <= M / 2 ? launch<M, IO, true>(p, u, dy, dk, Nk, B, workspace, s)
-                         : launch<M, IO, false>(p, u, dy, dk, Nk, B, workspace, s);
+    const bool half = p->N <= M / 2;
+    if constexpr (rf::has_wide(M))
+        if (grad_wide(M, p->H, B))
+            return half ? launch<M, IO, true, true>(p, u, dy, dk, Nk, B, workspace, s) : launch<M, IO, false, true>(p, u, dy, dk, Nk, B, workspace, s);
+    if constexpr (M != 512)
+        return half ? launch<M, IO, true, false>(p, u, dy, dk, Nk, B, workspace, s) : launch<M, IO, false, false>(p, u, dy, dk, Nk, B, workspace, s);
+    return FFTCONV_EUNSUPPORTED;                                  // (not reached)
 }
 
 }  // namespace
 
 bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSED3 && p->M <= 16384; }
+
+// Which gradients of matrix-core plans run on these rows: those of one batch row, where the other kernel sums a single product, and leaves it to a second one
+// to transform it back, and of few at short lengths.  us, matrix cores, rows (bf16): 1 x 16 fft 256 11.5, 8.1, 512 13.4, 8.3, 1024 13.5, 8.4, 2048 15.0, 9.3,
+// 4096 12.3, 9.4, 8192 14.1, 16.8; 1 x 768 25.8, 8.4, 29.5, 8.5, 28.6, 8.4, 35.5, 11.2, 28.0, 15.4; 2 x 64 11.8, 10.9, 13.6, 11.3, 13.8, 11.2, 16.1, 12.5, 12.5, 13.5;
+// 8 x 16 11.5, 10.9, 13.3, 11.2, 13.6, 12.5, 14.9, 14.9; 8 x 64 12.0, 11.2, 13.9, 11.4, 14.1, 13.8; 8 x 256 13.8, 12.0, 15.9, 12.7, 16.1, 20.1; 16 x 16 11.4, 13.3,
+// 13.4, 11.6, 13.5, 13.9; 16 x 768 fft 512 31.1, 26.9.  The spectra of their runs, a batch row each at most, fit into the workspace for that kernel's 8192 slots a channel.
+bool row_backward_filter_few(const fftconv_plan *p, int64_t B)
+{
+    if (B * p->H > 1 << 20) return false;                         // (far within the limits of a launch)
+    switch (p->M) {
+    case 256: return B <= 8;
+    case 512: return B <= 16;
+    case 1024: return B == 1 || (B <= 8 && B * p->H <= 512);
+    case 2048: return B <= 4 && (B == 1 || B * p->H <= 512);
+    case 4096: return B == 1;
+    default: return false;
+    }
+}
 
 // the sums of the runs; never 0 (the entry point refuses a missing workspace), and enough for every smaller batch
 size_t row_backward_filter_bytes(const fftconv_plan *p, int64_t B)

@@ -276,3 +276,25 @@ def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
         ref = ref * v.double()
     weight = v.double().numpy() if gates & 2 else None
     assert parity_error(y.numpy(), ref.numpy(), TOL[dtype], "line", weight) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M", [
+    ("bf16", 1, 3, 128, 256), ("f16", 8, 5, 120, 256), ("bf16", 9, 5, 128, 256),        # few rows of matrix-core plans, and more than those
+    ("f16", 16, 3, 256, 512), ("bf16", 17, 3, 256, 512),
+    ("bf16", 8, 64, 512, 1024), ("f16", 7, 74, 504, 1024), ("bf16", 1, 700, 512, 1024),
+    ("f16", 4, 128, 1024, 2048), ("bf16", 3, 171, 1024, 2048), ("bf16", 1, 3, 2048, 4096), ("f16", 2, 3, 2048, 4096),
+    ("f32", 16, 2, 200, 512), ("f32", 17, 2, 512, 512), ("bf16", 47, 1, 301, 512),      # sums of runs by a kernel of their own, or not
+    ("f32", 12, 3, 1024, 1024), ("f32", 29, 3, 400, 1024), ("f32", 14, 2, 3000, 4096), ("bf16", 7, 1, 8192, 8192), ("f32", 5, 2, 9001, 16384),
+    ("f32", 8, 1024, 30, 1024), ("f32", 8, 1025, 30, 1024),                             # wide rows of 1024 points and the others
+])
+def test_gradients_of_few_rows(dtype, B, H, N, M):
+    beyond = {256: 8, 512: 16, 1024: 512 // H, 2048: 512 // H, 4096: 1}[M] < B if M <= 4096 else False
+    if dtype == "f32" or 2 * N > M or not beyond:
+        check_row_gradient(dtype, B, H, N, M, N, None)            # fp32 transforms
+    else:                                                         # operands of 16 bits
+        g = torch.Generator().manual_seed(B * H)
+        u, dy = (torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(2))
+        dk = fftconv.Plan(N, M, H, dtype).backward_filter(u.cuda(), dy.cuda(), N).cpu().double()
+        U, D = torch.fft.rfft(u.double(), M), torch.fft.rfft(dy.double(), M)
+        ref = torch.fft.irfft((U.conj() * D).sum(0), M)[:, :N]
+        assert parity_error(dk.numpy(), ref.numpy(), TOL[dtype], "dk") <= TOL[dtype]
