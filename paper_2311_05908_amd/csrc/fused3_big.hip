@@ -947,7 +947,8 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
 // (16, 16, 16, M / 4096) last to first; all but the first act inside contiguous blocks of M / 16 positions, and
 // block d0 (the low four bits of k1) is made of the bins of k1 = d0 and d0 + 16: two contiguous runs of dk_f.
 // Kernel 1, one workgroup per (channel, block): the two runs -> LDS at their positions, the length-M/16
-// inverse there (twiddle table of W_M with stride 16), natural order out to a scratch row.  Kernel 2: the
+// inverse there (twiddle table of W_M with stride 16), natural order out to a scratch row; the loads of a run go out together (one by one before: bf16
+// gradients of fft 32768, 16 x 1 rows 59 -> 45 us, 64 x 8 114 -> 63, fft 16384, 16 x 1 30 -> 24, 40 x 2 42 -> 27).  Kernel 2: the
 // remaining factor across the 16 blocks, real part, 1/M, the first Nk samples.
 constexpr int DK_BLK_THREADS = 256;
 template <int N2>
@@ -958,19 +959,33 @@ __global__ void __launch_bounds__(DK_BLK_THREADS) k_big_dk_blocks(const float2 *
     __shared__ float2 XS[BLK + BLK / 16];
     const int d0 = blockIdx.x;
     const int64_t h = blockIdx.y;
+    constexpr int PER = BLK / DK_BLK_THREADS;
+    const float2 *const in = dkf + h * BM;
+    auto at = [&](int n) {                                                     // slot (k1, j) of dk_f[h]
+        const int i = threadIdx.x + n * DK_BLK_THREADS;
+        return (d0 + 16 * (i / RUN)) * RUN + i % RUN;
+    };
+    float2 v[PER];
 #pragma unroll
-    for (int i = threadIdx.x; i < BLK; i += DK_BLK_THREADS) {
-        const int k1 = d0 + 16 * (i / RUN), j = i % RUN;                       // slot (k1, j) of dk_f[h]
+    for (int n = 0; n < PER; ++n) v[n] = in[at(n)];
+#pragma unroll 2
+    for (int i2 = 1; i2 < runs; ++i2) {
+        const float2 *const run = in + (int64_t)i2 * gridDim.y * BM;
+        float2 t[PER];
+#pragma unroll
+        for (int n = 0; n < PER; ++n) t[n] = run[at(n)];
+#pragma unroll
+        for (int n = 0; n < PER; ++n) {
+            v[n].x += t[n].x;
+            v[n].y += t[n].y;
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < PER; ++n) {
+        const int i = threadIdx.x + n * DK_BLK_THREADS, k1 = d0 + 16 * (i / RUN), j = i % RUN;
         const int lane = j % 64, r = (j / 64) % 4, t3 = (j / 256) % 2, t2 = (j / 512) % R2;
         const int k2 = big_tau<N2>(16 * t2 + lane % 16), k3 = big_sigma(16 * t3 + 4 * (lane / 16) + r);
-        const int f = k1 + 32 * k2 + 32 * N2 * k3;
-        float2 v = dkf[h * BM + k1 * RUN + j];
-        for (int i2 = 1; i2 < runs; ++i2) {
-            const float2 t = dkf[((int64_t)i2 * gridDim.y + h) * BM + k1 * RUN + j];
-            v.x += t.x;
-            v.y += t.y;
-        }
-        XS[lds_slot(lds_pos(f, fl, BM) - d0 * BLK)] = v;
+        XS[lds_slot(lds_pos(k1 + 32 * k2 + 32 * N2 * k3, fl, BM) - d0 * BLK)] = v[n];
     }
     __syncthreads();
     lds_inverse(XS, w, fl_tail, BLK, 16);
