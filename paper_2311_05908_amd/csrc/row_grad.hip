@@ -224,8 +224,7 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
     int64_t left = sp.S;
     const int64_t apart = p->H * (M / 2);
     if (sp.S >= ADD_RUNS<M> && sp.S * apart <= ADD_MOST) {
-        hipLaunchKernelGGL(k_row_runs_add, dim3((unsigned)((apart + 255) / 256)), dim3(256), 0, s, (float4 *)workspace, apart, (int)sp.S);
-        FC_HIP(hipGetLastError());
+        FC_TRY(row_runs_add(workspace, apart, sp.S, s));
         left = 1;
     }
     FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M, WIDE>, lds));
@@ -252,6 +251,14 @@ int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk,
 }
 
 }  // namespace
+
+// S spectra, `apart` pairs of bins from one to the next, added up in order in the first one's place
+int row_runs_add(void *part, int64_t apart, int64_t S, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_row_runs_add, dim3((unsigned)((apart + 255) / 256)), dim3(256), 0, s, (float4 *)part, apart, (int)S);
+    FC_HIP(hipGetLastError());
+    return FFTCONV_OK;
+}
 
 bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSED3 && p->M <= 16384; }
 

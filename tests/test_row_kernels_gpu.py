@@ -279,6 +279,7 @@ def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
 
 
 @pytest.mark.parametrize("dtype,B,H,N,M", [
+    ("bf16", 16, 1, 4096, 8192), ("f16", 14, 1, 4000, 8192), ("bf16", 64, 2, 1000, 2048), ("f16", 400, 3, 200, 512),      # sums of eight runs, of seven; of groups' slots
     ("bf16", 1, 3, 128, 256), ("f16", 8, 5, 120, 256), ("bf16", 9, 5, 128, 256),        # few rows of matrix-core plans, and more than those
     ("f16", 16, 3, 256, 512), ("bf16", 17, 3, 256, 512),
     ("bf16", 8, 64, 512, 1024), ("f16", 7, 74, 504, 1024), ("bf16", 1, 700, 512, 1024),
@@ -288,8 +289,8 @@ def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
     ("f32", 8, 1024, 30, 1024), ("f32", 8, 1025, 30, 1024),                             # wide rows of 1024 points and the others
 ])
 def test_gradients_of_few_rows(dtype, B, H, N, M):
-    beyond = {256: 8, 512: 16, 1024: 512 // H, 2048: 512 // H, 4096: 1}[M] < B if M <= 4096 else False
-    if dtype == "f32" or 2 * N > M or not beyond:
+    few = {256: B <= 8, 512: B <= 16, 1024: B <= 8 and B * H <= max(512, H), 2048: B <= 4 and B * H <= max(512, H), 4096: B == 1}
+    if dtype == "f32" or 2 * N > M or few.get(M, M > 8192):
         check_row_gradient(dtype, B, H, N, M, N, None)            # fp32 transforms
     else:                                                         # operands of 16 bits
         g = torch.Generator().manual_seed(B * H)
