@@ -73,7 +73,14 @@ uint16_t to_bf16(double x)
 }
 uint16_t to_f16(double x)
 {
-    _Float16 hv = (_Float16)(float)x;
+    const float f = (float)x;
+    uint32_t a;
+    std::memcpy(&a, &f, 4);
+    const uint32_t sign = (a >> 16) & 0x8000u;
+    a &= 0x7fffffffu;
+    // normal numbers by hand, to nearest even (the compiler's conversion is a call of 8 ns, 0.4 ms of a plan's creation)
+    if (a >= 0x38800000u && a < 0x477fe000u) return (uint16_t)(sign | ((a + 0xfffu + ((a >> 13) & 1u)) >> 13) - (112u << 10));
+    _Float16 hv = (_Float16)f;
     uint16_t b;
     std::memcpy(&b, &hv, 2);
     return b;
@@ -91,9 +98,9 @@ Cplx wpow(int64_t M, int64_t e)             // exp(-2 pi i e / M)
 Cplx cmulh(Cplx a, Cplx b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 Cplx conjh(Cplx a) { return {a.re, -a.im}; }
 
-// The two MFMA operands (64 lanes x 8 16-bit slots each) of the real form of a complex matrix G:
+// The MFMA operand (64 lanes x 8 16-bit slots) of the real part of a product with a complex matrix G, in real form:
 // lane (c16, q), slot 2r+s multiplies data element e_in = 16 t + 4 q + r, part s (0 = re, 1 = im),
-// and contributes to output e_out = 16 ct + c16, part re (the first operand) or im (the 512 slots behind it).
+// and contributes to output e_out = 16 ct + c16.
 template <typename Fn>
 void fill_operands(uint16_t *dst, bool f16, int t, int ct, Fn G)
 {
@@ -105,8 +112,6 @@ void fill_operands(uint16_t *dst, bool f16, int t, int ct, Fn G)
             uint16_t *const o = dst + lane * 8 + 2 * r;
             o[0] = re;                               // times the real part of the data
             o[1] = im ^ 0x8000u;                     // times the imaginary part
-            o[512] = im;
-            o[513] = re;
         }
     }
 }
@@ -145,29 +150,31 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
     };
     const bool f16 = p->dtype == FFTCONV_F16;
     const size_t n_u4 = (size_t)G::TAB1 + G::TAB2 + 2 * (size_t)G::TAB3 + G::TAB2I + G::TAB1I;
-    const size_t n_f2 = (size_t)G::TWA + G::TWB;
+    const size_t n_tw = (size_t)G::TWA + G::TWB;
     std::vector<uint16_t> ops(n_u4 * 8);
-    std::vector<float2> tw(n_f2);
-    std::vector<uint2> tw16(n_f2);
-    const int cfmt = f16 ? 2 : 1;
-    auto hi16 = [&](double v) { return f16 ? to_f16(v) : to_bf16(v); };
+    std::vector<uint32_t> tw(2 * n_tw);                           // pairs of the I/O type, then fp16 pairs
+    auto twiddle = [&](size_t at, Cplx v) {
+        const uint32_t h = to_f16(v.re) | (uint32_t)to_f16(v.im) << 16;
+        tw[at] = f16 ? h : to_bf16(v.re) | (uint32_t)to_bf16(v.im) << 16;
+        tw[n_tw + at] = h;
+    };
     size_t o = 0;
-    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 128; return d; };
-    // tab1 [K step][ct][part]: W_N1^{n1 k1}; zero-padded real input only meets K step 0 (n1 < 16)
+    auto next = [&]() { uint16_t *d = ops.data() + o * 8; o += 64; return d; };
+    // tab1 [K step][ct]: W_N1^{n1 k1}; zero-padded real input only meets K step 0 (n1 < 16)
     for (int ks = 0; ks < 2; ++ks)
         for (int ct = 0; ct < 2; ++ct)
             fill_operands(next(), f16, ks, ct, [&](int n1, int k1) {
                 if (groups > 1 && (n1 >= 16 || g_of_n1(n1) != g_of_k1(k1))) return zero_c;
                 return root(N1s, (int64_t)sub_n1(n1) * (k1 % N1s));
             });
-    // tab2 [n3][t][ct][part]: W_N2^{n2 k2} W_{N2 N3}^{k2 n3}
+    // tab2 [n3][t][ct]: W_N2^{n2 k2} W_{N2 N3}^{k2 n3}
     for (int n3 = 0; n3 < N3; ++n3)
         for (int t = 0; t < G::R2; ++t)
             for (int ct = 0; ct < G::R2; ++ct)
                 fill_operands(next(), f16, t, ct, [&](int n2, int k2) {
                     return cmulh(root(N2, (int64_t)n2 * k2), root((int64_t)N2 * N3, (int64_t)k2 * n3));
                 });
-    // tab3 [t][ct][part]: W_N3^{n3 k3}, output rows in the k3 order of k3_at_index()
+    // tab3 [t][ct]: W_N3^{n3 k3}, output rows in the k3 order of k3_at_index()
     for (int t = 0; t < G::R3; ++t)
         for (int ct = 0; ct < G::R3; ++ct)
             fill_operands(next(), f16, t, ct,
@@ -177,7 +184,7 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
         for (int ct = 0; ct < G::R3; ++ct)
             fill_operands(next(), f16, t, ct,
                           [&](int idx, int n3) { return conjh(root(N3, (int64_t)n3 * k3_at_index(idx, N3))); });
-    // tab2i [k1][t][ct][part]: conj(W_N2^{k2 n2} W_{N1 N2}^{k1 n2})
+    // tab2i [k1][t][ct]: conj(W_N2^{k2 n2} W_{N1 N2}^{k1 n2})
     for (int k1 = 0; k1 < N1; ++k1)
         for (int t = 0; t < G::R2; ++t)
             for (int ct = 0; ct < G::R2; ++ct)
@@ -185,7 +192,7 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
                     if (!own_half(k1, n2)) return zero_c;
                     return conjh(cmulh(root(N2, (int64_t)n2 * k2), root((int64_t)N1s * N2, (int64_t)(k1 % N1s) * n2)));
                 });
-    // tab1i [K step][row tile][part]: conj(W_N1^{k1 n1}); the causal kernel only forms row tile 0 (n1 < 16)
+    // tab1i [K step][row tile]: conj(W_N1^{k1 n1}); the causal kernel only forms row tile 0 (n1 < 16)
     for (int t = 0; t < 2; ++t)
         for (int rt = 0; rt < 2; ++rt)
             fill_operands(next(), f16, t, rt, [&](int k1, int n1) {
@@ -205,8 +212,7 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
                     for (int lane = 0; lane < 64; ++lane) {
                         int k1 = 16 * ct + lane % 16, n2 = 16 * rt + 4 * (lane / 16) + r;
                         Cplx v = own_half(k1, n2) ? root(Ms, (int64_t)(k1 % N1s) * ((int64_t)N3 * n2 + n3)) : zero_c;
-                        tw16[w] = ctw_const(v.re, v.im, cfmt, hi16);
-                        tw[w++] = make_float2((float)v.re, (float)v.im);
+                        twiddle(w++, v);
                     }
     // twb [k1][ct2][ct3][r][lane]: conj(W_M^{(k1 + N1 k2) n3}), n3 = 16 ct3 + c16, k2 = 16 ct2 + 4 q + r
     for (int k1 = 0; k1 < N1; ++k1)
@@ -216,15 +222,13 @@ int build_tables(fftconv_plan *p, void **dest, int groups = 1)
                     for (int lane = 0; lane < 64; ++lane) {
                         int n3 = 16 * ct3 + lane % 16, k2 = 16 * ct2 + 4 * (lane / 16) + r;
                         Cplx v = conjh(root(Ms, ((int64_t)(k1 % N1s) + (int64_t)N1s * k2) * n3));
-                        tw16[w] = ctw_const(v.re, v.im, cfmt, hi16);
-                        tw[w++] = make_float2((float)v.re, (float)v.im);
+                        twiddle(w++, v);
                     }
-    const size_t bytes = n_u4 * 16 + 2 * n_f2 * 8;
+    const size_t bytes = n_u4 * 16 + 2 * n_tw * 4;
     FC_HIP(hipMalloc(dest, bytes));
     p->f3.consts_bytes += bytes;
     FC_HIP(hipMemcpy(*dest, ops.data(), n_u4 * 16, hipMemcpyHostToDevice));
-    FC_HIP(hipMemcpy((char *)*dest + n_u4 * 16, tw.data(), n_f2 * 8, hipMemcpyHostToDevice));
-    FC_HIP(hipMemcpy((char *)*dest + n_u4 * 16 + n_f2 * 8, tw16.data(), n_f2 * 8, hipMemcpyHostToDevice));
+    FC_HIP(hipMemcpy((char *)*dest + n_u4 * 16, tw.data(), 2 * n_tw * 4, hipMemcpyHostToDevice));
     return FFTCONV_OK;
 }
 

@@ -88,7 +88,6 @@ struct BF16 {
     {
         return make_uint2(w ^ 0x80000000u, __builtin_amdgcn_alignbit(w, w, 16));
     }
-    static constexpr int CFMT = 1;
 };
 struct F16 {
     static __device__ __forceinline__ f32x4 mfma(uint4 a, uint4 b, f32x4 c)
@@ -129,7 +128,6 @@ struct F16 {
     {
         return make_uint2(__builtin_amdgcn_perm(w, w, 0x01000100u), __builtin_amdgcn_perm(w, w, 0x03020302u) ^ 0x00008000u);
     }
-    static constexpr int CFMT = 2;
 };
 
 // ---- complex products with 4-byte constants: the traits of the kernels that stream their tables
@@ -341,36 +339,26 @@ template <int N2, int N3> struct Geo {
     static constexpr int SU = (N1 / 2) * PQ1;
     static constexpr int UB_ELEMS = 2 * SU;
     // table sizes (entries)
-    static constexpr int TAB1 = 2 * 2 * 2 * 64;             // [K step][ct][part][lane] uint4
-    static constexpr int TAB2 = N3 * R2 * R2 * 2 * 64;      // [n3][t][ct][part][lane]
-    static constexpr int TAB3 = R3 * R3 * 2 * 64;           // [t][ct][part][lane]
-    static constexpr int TAB2I = N1 * R2 * R2 * 2 * 64;     // [k1][t][ct][part][lane]
-    static constexpr int TAB1I = 2 * 2 * 2 * 64;            // [K step][row tile][part][lane]
-    static constexpr int TWA = N3 * R2 * 2 * 4 * 64;        // [n3][rt][ct][r][lane] float2
-    static constexpr int TWB = N1 * R2 * R3 * 4 * 64;       // [k1][ct2][ct3][r][lane] float2
+    static constexpr int TAB1 = 2 * 2 * 64;                 // [K step][ct][lane] uint4: the operands of the real parts
+    static constexpr int TAB2 = N3 * R2 * R2 * 64;          // [n3][t][ct][lane]
+    static constexpr int TAB3 = R3 * R3 * 64;               // [t][ct][lane]
+    static constexpr int TAB2I = N1 * R2 * R2 * 64;         // [k1][t][ct][lane]
+    static constexpr int TAB1I = 2 * 2 * 64;                // [K step][row tile][lane]
+    static constexpr int TWA = N3 * R2 * 2 * 4 * 64;        // [n3][rt][ct][r][lane] uint32_t
+    static constexpr int TWB = N1 * R2 * R3 * 4 * 64;       // [k1][ct2][ct3][r][lane] uint32_t
     static constexpr int KF_PER_H = N1 * R2 * R3 * 4 * 64;  // == M
 };
 
+// The tables of the 8192-point kernels.  Of a matrix they hold the operand of the real part only: that of the imaginary part is the same numbers in
+// another arrangement (imag_operand()); of a twiddle the 4-byte pair, from which BF16 / F16 make their constants (constant()).  A
+// workgroup reads its tables through a compute unit's 64 bytes a clock, and with one row for each of them that was most of a call: with both operands and
+// 8-byte twiddles read from memory, us: 2 x 1 x 4096 fft 8192 8.0 -> 6.6, 2 x 1 x 8192 circular 8.3 -> 7.3, 2 x 1 x 65536 17.2 -> 16.0, 2 x 32 x 65536 35.1 -> 32.5; 2 x 256
+// x 65536 138 -> 135, 64 x 768 x 4096 262, 262.
 struct Consts {
     const uint4 *tab1, *tab2, *tab3, *tab3i, *tab2i, *tab1i;
-    const float2 *twa, *twb;
-    const uint2 *twa16, *twb16;       // the same twiddles as 16-bit constant pairs for TT::ctw
+    const uint32_t *twa, *twb;        // pairs of the I/O type
+    const uint32_t *twah, *twbh;      // fp16 pairs
 };
-
-// 16-bit constant pair of a complex factor (wr, wi) in the form TT::ctw expects
-// (fmt 1: bf16 dot-product form, fmt 2: fp16 packed-math form).  hi16(x) converts one value.
-template <typename F> __host__ __device__ inline uint2 ctw_const(double wr, double wi, int fmt, F hi16)
-{
-    uint2 c;
-    if (fmt == 1) {
-        c.x = (uint32_t)hi16(wr) | ((uint32_t)hi16(-wi) << 16);
-        c.y = (uint32_t)hi16(wi) | ((uint32_t)hi16(wr) << 16);
-    } else {
-        c.x = (uint32_t)hi16(wr) | ((uint32_t)hi16(wr) << 16);
-        c.y = (uint32_t)hi16(-wi) | ((uint32_t)hi16(wi) << 16);
-    }
-    return c;
-}
 
 __device__ __forceinline__ void cmul_ip(float &re, float &im, float2 w)
 {
@@ -393,10 +381,10 @@ inline Consts consts_at(const void *base)
     c.tab3i = c.tab3 + G::TAB3;
     c.tab2i = c.tab3i + G::TAB3;
     c.tab1i = c.tab2i + G::TAB2I;
-    c.twa = (const float2 *)(c.tab1i + G::TAB1I);
+    c.twa = (const uint32_t *)(c.tab1i + G::TAB1I);
     c.twb = c.twa + G::TWA;
-    c.twa16 = (const uint2 *)(c.twb + G::TWB);
-    c.twb16 = c.twa16 + G::TWA;
+    c.twah = c.twb + G::TWB;
+    c.twbh = c.twah + G::TWA;
     return c;
 }
 

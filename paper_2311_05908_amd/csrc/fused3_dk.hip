@@ -66,18 +66,26 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
         uint4 tab1[2][2], tab2[4][2];
         uint2 twa[4][2][4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) tab1[a][p] = cs.tab1[((0 * 2 + a) * 2 + p) * 64 + l];   // K step 0 only (n1 < 16)
+        for (int a = 0; a < 2; ++a) tab1[a][0] = cs.tab1[(0 * 2 + a) * 64 + l];   // K step 0 only (n1 < 16)
+        uint32_t tw[4][2][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = 4 * w + i;
-#pragma unroll
-            for (int p = 0; p < 2; ++p) tab2[i][p] = cs.tab2[(c * 2 + p) * 64 + l];
+            tab2[i][0] = cs.tab2[c * 64 + l];
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) twa[i][ct][r] = cs.twa16[((c * 2 + ct) * 4 + r) * 64 + l];
+                for (int r = 0; r < 4; ++r) tw[i][ct][r] = cs.twa[((c * 2 + ct) * 4 + r) * 64 + l];
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) tab1[a][1] = B16::imag_operand(tab1[a][0]);   // (bits: the same for either type)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            tab2[i][1] = B16::imag_operand(tab2[i][0]);
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) twa[i][ct][r] = TT::constant(tw[i][ct][r]);
         }
         uint4 pre[PCH];
         auto issue_loads = [&](int s) {
@@ -173,9 +181,8 @@ __global__ void __launch_bounds__(NT) k_fused3_dk(const uint16_t *__restrict__ u
     } else {
         // =========================== inner role: stage 3, product, accumulation ===========================
         const int wq = w - 4;
-        uint4 tab3[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) tab3[p] = cs.tab3[p * 64 + l];
+        uint4 tab3[2] = {cs.tab3[l], make_uint4(0, 0, 0, 0)};
+        tab3[1] = B16::imag_operand(tab3[0]);
         f32x4 z1re[8], z1im[8], accre[8], accim[8];               // per k1 plane of this wave
 #pragma unroll
         for (int i = 0; i < 8; ++i) {

@@ -107,21 +107,32 @@ __global__ void __launch_bounds__(NT) k_fused3_ws(const uint16_t *__restrict__ u
         uint4 tab1[2][2], tab1i[2][2], tab2[4][2];
         uint2 twa[4][2][4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                tab1[a][p] = cs.tab1[((0 * 2 + a) * 2 + p) * 64 + l];       // K step 0 only (n1 < 16)
-                tab1i[a][p] = cs.tab1i[((a * 2 + 0) * 2 + p) * 64 + l];     // row tile 0 only (n1 < 16)
-            }
+        for (int a = 0; a < 2; ++a) {
+            tab1[a][0] = cs.tab1[(0 * 2 + a) * 64 + l];           // K step 0 only (n1 < 16)
+            tab1i[a][0] = cs.tab1i[(a * 2 + 0) * 64 + l];         // row tile 0 only (n1 < 16)
+        }
+        uint32_t tw[4][2][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = 4 * w + i;
-#pragma unroll
-            for (int p = 0; p < 2; ++p) tab2[i][p] = cs.tab2[(c * 2 + p) * 64 + l];
+            tab2[i][0] = cs.tab2[c * 64 + l];
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) twa[i][ct][r] = cs.twa16[((c * 2 + ct) * 4 + r) * 64 + l];
+                for (int r = 0; r < 4; ++r) tw[i][ct][r] = cs.twa[((c * 2 + ct) * 4 + r) * 64 + l];
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            tab1[a][1] = B16::imag_operand(tab1[a][0]);           // (bits: the same for either type)
+            tab1i[a][1] = B16::imag_operand(tab1i[a][0]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            tab2[i][1] = B16::imag_operand(tab2[i][0]);
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) twa[i][ct][r] = TT::constant(tw[i][ct][r]);
         }
         // input prefetch: the loads of item s+2 are issued at the start of step s and staged at its end
         uint4 pre[PCH];
@@ -320,18 +331,23 @@ __global__ void __launch_bounds__(NT) k_fused3_ws(const uint16_t *__restrict__ u
         const int wq = w - 4;
         uint4 tab3[2], tab3i[2], tab2i[8][2];
         uint2 twb[8][4], kfr[8][4];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            tab3[p] = cs.tab3[p * 64 + l];
-            tab3i[p] = cs.tab3i[p * 64 + l];
-        }
+        tab3[0] = cs.tab3[l];
+        tab3i[0] = cs.tab3i[l];
+        uint32_t tw[8][4];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int c = 8 * wq + i;
+            tab2i[i][0] = cs.tab2i[c * 64 + l];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) tab2i[i][p] = cs.tab2i[(c * 2 + p) * 64 + l];
+            for (int r = 0; r < 4; ++r) tw[i][r] = cs.twb[(c * 4 + r) * 64 + l];
+        }
+        tab3[1] = B16::imag_operand(tab3[0]);
+        tab3i[1] = B16::imag_operand(tab3i[0]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) twb[i][r] = cs.twb16[(c * 4 + r) * 64 + l];
+        for (int i = 0; i < 8; ++i) {
+            tab2i[i][1] = B16::imag_operand(tab2i[i][0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) twb[i][r] = TT::constant(tw[i][r]);
         }
         lds_barrier();                                          // pairs with the outer role's prologue barrier
         int h_cur = -1;

@@ -38,7 +38,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));        // a 16-byte 
 // the I/O type; CT is the type of the 4-byte constant.  The 16-bit forms TT::ctw4 round the operand before the
 // product as well, and their twiddles carry 8 bits in bf16 plans; over the three products of an inner row,
 // inside transforms of up to 2^22 points, that takes the bf16 error past the tolerance.  So here the twiddles
-// are fp16 pairs for both I/O types (11 bits, converted from the fp32 tables when the kernel starts), k_f
+// are fp16 pairs for both I/O types (11 bits), k_f
 // comes in the I/O type as stored, and the products of a bf16 plan run in fp32 (7 vector operations per point
 // instead of 4.5; the kernel waits for memory more than for the vector ALUs).  An fp16 plan keeps the packed
 // fp16 form (3 operations per point), whose roundings are 8 times smaller than the tolerance allows.
@@ -54,7 +54,6 @@ template <typename TT, typename CT> __device__ __forceinline__ uint4 cmul4(f32x4
     }
     return make_uint4(o[0], o[1], o[2], o[3]);
 }
-__device__ __forceinline__ uint32_t tw_f16(float2 w) { return F16::pack(w.x, w.y); }
 // Re-defines a register-resident constant in place (no instruction).  The bf16 products widen their fp16
 // twiddles to fp32 at every use; seen as loop invariant, the widened values would be computed once before the
 // loop and kept: twice the registers of the table, which the role does not have (they ended up in scratch
@@ -109,20 +108,18 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    tab1[a][b][p] = cs.tab1[((a * 2 + b) * 2 + p) * 64 + l];       // [K step][k1 tile][part]
-                    tab1i[a][b][p] = cs.tab1i[((a * 2 + b) * 2 + p) * 64 + l];     // [K step][n1 tile][part]
-                }
+            for (int b = 0; b < 2; ++b) {
+                tab1[a][b][0] = cs.tab1[(a * 2 + b) * 64 + l];                     // [K step][k1 tile]
+                tab1i[a][b][0] = cs.tab1i[(a * 2 + b) * 64 + l];                   // [K step][n1 tile]
+            }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = 4 * w + i;
-            tab2[i] = cs.tab2[(c * 2 + 0) * 64 + l];
+            tab2[i] = cs.tab2[c * 64 + l];
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) twa[i][ct][r] = tw_f16(cs.twa[((c * 2 + ct) * 4 + r) * 64 + l]);
+                for (int r = 0; r < 4; ++r) twa[i][ct][r] = cs.twah[((c * 2 + ct) * 4 + r) * 64 + l];
         }
         // this lane's piece (tile k, register r) of a row: n1 = 16k + 4q + r, n2 = c16, n3 = 4w .. 4w+3
         // (words: multipass_row_slot() of (n1 = 4q, n2 = c16, n3 = 4w), and the distance between consecutive n1)
@@ -174,6 +171,13 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
         };
 
         issue_loads(t0);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                tab1[a][b][1] = B16::imag_operand(tab1[a][b][0]);                  // (bits: the same for either type)
+                tab1i[a][b][1] = B16::imag_operand(tab1i[a][b][0]);
+            }
         vmem_settled();
         // One step s: phase C of item s-1 (doC), phase A of item s+1 (doA), the loads of item s+2 (doL: only with
         // doA).  The steps in the middle of a workgroup's range have all three and are a loop of their own with
@@ -318,18 +322,14 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
         auto plane = [&](int i) { return BIG_KF ? 4 * i + wq : 8 * wq + i; };      // k1 of this wave's planes
         uint4 tab3[2], tab3i[2], tab2i[8][2];
         uint32_t twb[8][4], kfr[8][4];                            // fp16 pairs; pairs of the I/O type
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            tab3[p] = cs.tab3[p * 64 + l];
-            tab3i[p] = cs.tab3i[p * 64 + l];
-        }
+        tab3[0] = cs.tab3[l];
+        tab3i[0] = cs.tab3i[l];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int c = plane(i);
+            tab2i[i][0] = cs.tab2i[c * 64 + l];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) tab2i[i][p] = cs.tab2i[(c * 2 + p) * 64 + l];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) twb[i][r] = tw_f16(cs.twb[(c * 4 + r) * 64 + l]);
+            for (int r = 0; r < 4; ++r) twb[i][r] = cs.twbh[(c * 4 + r) * 64 + l];
         }
         // k_f of item t, plane i of this wave: four constants per lane
         auto kf_ptr = [&](int t) {
@@ -357,6 +357,10 @@ __global__ void __launch_bounds__(NT) k_fused3_wsc(uint32_t *rows, const uint32_
 #pragma unroll
                 for (int r = 0; r < 4; ++r) kfr[i][r] = src[(i * 4 + r) * 64];
         }
+        tab3[1] = B16::imag_operand(tab3[0]);
+        tab3i[1] = B16::imag_operand(tab3i[0]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) tab2i[i][1] = B16::imag_operand(tab2i[i][0]);
         vmem_settled();
         lds_barrier();                                            // step t0 - 1: nothing to do yet
         for (int s = t0; s < t1; ++s) {
