@@ -267,25 +267,20 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 
 // Few rows: which calls of a matrix-core plan up to fft 4096 the row kernel takes.  Both kernels' times are staircases.  The
 // matrix-core kernel runs its work items (8192 / fft pairs of rows of one channel, however few there are) in rounds of one per
-// compute unit: 8.9, 12.2, 15.7, 19.2, 24.6 us for 1, 2, 3, 4, 6 of them (bf16; with both gates 9.4, 14.4, 18.9, 22, 28.3).
-// The row kernel runs workgroups of `rows` pairs, us for 1, 2, 3, 4, 6 of them per compute unit (both gates):
-//   fft  512  8.6, 11.1, 13.8, 18.2, 24.7 (9.1, 13.1, 17.4, 23.6, 30.5)      fft 2048  8.3, 10.6, 13.0, 16.8, 23.3 (8.9, 11.8, 15.0, 19.2, 26.1)
-//   fft 1024  8.7, 11.5, 14.5, 19.2, 25.1 (9.5, 13.7, 18.0, 22.8, 30.5)      fft 4096  6.6, 8.2, 10.1, 12.3, 17.2 (7.2, 9.1, 12.0, 15.0, 20.5)
-// So
-//   fft 2048, 4096: as many workgroups per compute unit as there are rounds, or fewer; beyond six rounds half as many (fp16, 4096: one
-//     row of 2048 and 8192 channels 28.9, 30.6 and 96, 113; 2048: one row of 8192 88, 61, three 92, 116).  The lines of 4096 are from before the
-//     row kernel became a quarter faster there: it is now the faster one with up to half as many workgroups again as there are rounds;
-//   fft 1024: up to 4096 pairs, beyond half as many workgroups;
-//   fft 512: up to 8192 pairs, beyond half as many, and only if items are not full.  With WIDE rows and full items (bf16, fp16, both gates), us, matrix cores, rows:
-//     512 32 x 16 8.4, 5.0 (8.9, 6.3), 32 x 256 9.0, 8.0 (9.3, 8.8), 32 x 512 12.1, 10.8 (13.4, 12.2), 32 x 1024 18.4, 18.0 (21.6, 23.1);
-//     1024 16 x 16 8.4, 6.6 (8.9, 7.1), 16 x 256 9.2, 8.4 (9.5, 9.1), 16 x 512 12.0, 11.0 (13.4, 12.7), 16 x 1024 18.5, 18.8 (21.6, 22.8);
+// compute unit: 7.0 - 7.9, 10.7, 14.1, 17.2 us for 1, 2, 3, 4 of them (bf16; fp16 with both gates 7.3 - 8.2, 11.5, 16.1, 19).  The row kernel runs workgroups of
+// `rows` pairs.  us, rows, matrix cores (bf16, or fp16 with both gates where two pairs are given):
+//   fft 4096: as many workgroups as one a compute unit for each round: 1 x 64 6.1, 7.3, 1 x 768 9.3, 13.0, 1 x 2048 20.5, 26.6, 1 x 8192 77, 87; half as many again
+//     would still do (4 x 384 9.7, 10.6; 11.3, 11.9), twice as many not (4 x 256 7.8, 7.7; 9.3, 8.2; 3 x 1024 21.4, 17.5);
+//   fft 2048: as many, beyond six rounds half as many: 1 x 512 7.6, 10.2, 3 x 1024 15.9, 16.2, 3 x 2048 28.9, 26.8, 1 x 8192 51, 85 (in the first round
+//     either: 3 x 64 7.6, 7.5, 8 x 128 7.8, 7.2);
+//   fft 1024: half as many, and not in the first round (16 x 16 6.7, 7.0, 16 x 256 8.3, 7.8): 1 x 768 6.7, 12.6, 1 x 8192 17.9, 84.6;
+//   fft 512: half as many, and only if items are not full: 1 x 64 5.2, 7.2, 1 x 2048 5.5, 24.8; 32 x 256 8.0, 7.9 (8.6, 8.2), though 32 x 16 5.5, 6.9;
 //   fft 256: 40 Ki pairs + 56 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, 256 42, 40; 8192
 //     channels: B = 33 98, 51, fp16 64 106, 116.
-// Lines measured over 1900 shapes, B = 1 .. 2048 (fft 256: .. 2^20), H = 1 .. 8192, bf16 and fp16, with and without gates.
 // (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
 // calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
-// At 8192 points the row kernel was not the faster one before it gained that quarter (16 channels: 8.8 against 12.8); not measured since.
-// The kernel counts rows and threads (at most M / 16 to a pair of rows) in 32 bits: calls beyond that are not few rows.
+// At 8192 points the row kernel is not the faster one (16 channels: 8.8 and more against 7.5).
+// The kernel counts rows and threads (at most 64, or M / 16, to a pair of rows) in 32 bits: calls beyond that are not few rows.
 bool row_few(int64_t M, int64_t H, int64_t B)
 {
     const int64_t npairs = (B + 1) / 2;
@@ -295,9 +290,9 @@ bool row_few(int64_t M, int64_t H, int64_t B)
     constexpr int CUS = 256;
     const int64_t full = 8192 / M, items = H * ((npairs + full - 1) / full), rounds = (items + CUS - 1) / CUS;
     const int64_t rows = M == 512 ? 16 : M == 1024 ? 8 : M == 2048 ? 2 : 1, groups = (pairs + rows - 1) / rows;
-    if (M >= 2048) return groups <= CUS * rounds && (rounds <= 6 || 2 * groups <= CUS * rounds);
-    if (M == 1024) return pairs <= 4096 || (rounds > 1 && groups <= CUS * ((rounds + 1) / 2));
-    return pairs <= 8192 || (pairs < full * items && 2 * groups <= CUS * (rounds + 1));
+    if (M >= 2048) return groups <= CUS * rounds && (M == 4096 || rounds <= 6 || 2 * groups <= CUS * rounds);
+    if (M == 1024) return rounds > 1 && groups <= CUS * ((rounds + 1) / 2);
+    return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
 }
 
 // for calls that row_few() takes

@@ -262,7 +262,6 @@ def test_few_rows_round_at_the_gates(M, dtype):
     ("f32", 2, 4096, 65, 1024, 0), ("bf16", 2, 4097, 514, 1024, 0), ("f32", 1, 4500, 300, 1024, 1),
     ("bf16", 2, 3072, 64, 512, 0), ("f16", 2, 3073, 64, 512, 3),         # the same of calls of few rows on a matrix-core plan
     ("bf16", 1, 1024, 512, 1024, 3), ("f16", 2, 1025, 256, 1024, 0),
-    ("f16", 2, 8192, 32, 512, 0), ("bf16", 32, 256, 512, 1024, 0), ("bf16", 16, 513, 64, 1024, 0),      # those of 4096 and 8192 pairs
 ])
 def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
     g = torch.Generator().manual_seed(H + N)
