@@ -233,6 +233,10 @@ __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
 
 }  // namespace
 
+// Factors of its half-length rows: sixteens first, but 512 points as 8 . 8 . 8, as many passes as 16 . 16 . 2 and shorter ones (fft 1024, 128 / 257 / 768 channels
+// 7.1, 12.1, 13.0 -> 6.0, 10.7, 11.8 us; eights cost the other lengths a pass or more work: fft 8192, 128 channels 13.1, 14.5).
+static FacList filter64_factors(int64_t L) { return L == 512 ? FacList{3, {8, 8, 8}} : staged_factors_for(L); }
+
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s)
 {
@@ -243,7 +247,7 @@ int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_ou
             constexpr bool FEW = decltype(few)::value;
             FC_TRY(raise_dynamic_lds((const void *)k_row_filter64<M, FEW>, (int)lds));
             hipLaunchKernelGGL((k_row_filter64<M, FEW>), dim3((unsigned)p->H), dim3(FILTER64_THREADS<M, FEW>), lds, s, k, (float2 *)kf,
-                               p->st.w64, staged_factors_for(M / 2), Nk, conj_out, keep_dev, n_blocks);
+                               p->st.w64, filter64_factors(M / 2), Nk, conj_out, keep_dev, n_blocks);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;
         };
