@@ -179,6 +179,29 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
     }
 }
 
+// Factors of the fp64 filter transform's half-length rows: sixteens first, but 512 points as 8 . 8 . 8, as many passes as 16 . 16 . 2 and
+// shorter ones (fft 1024, 257 / 3000 channels 12.0, 20.0 -> 10.6, 17.6 us; eights cost the other lengths a pass or more work: fft 8192,
+// 128 channels 13.1, 14.5).
+constexpr int filter64_factor(int L, int rest) { return L == 512 ? 8 : rest >= 16 ? 16 : rest; }
+static FacList filter64_factors(int L)
+{
+    FacList fl{};
+    for (int rest = L; rest > 1; rest /= fl.fac[fl.nf - 1]) fl.fac[fl.nf++] = filter64_factor(L, rest);
+    return fl;
+}
+// lds_pos() for those factors.  The kernel asks for two of them a bin on its way out, and a loop over a list that it holds in memory took a
+// quarter to a half of its time: fft 1024, 257 channels 10.6 -> 6.7 us, 3000 17.6 -> 12.4; 8192, 128 / 3000 13.1, 109 -> 11.5, 89; 16384, 2 / 3000
+// 23.9, 313 -> 19.6, 268.
+template <int L, int REST = L> __device__ __forceinline__ int filter64_pos(int f)
+{
+    if constexpr (REST == 1) {
+        return 0;
+    } else {
+        constexpr int F = filter64_factor(L, REST);
+        return (f & (F - 1)) * (REST / F) + filter64_pos<L, REST / F>(f / F);
+    }
+}
+
 // ---- the filter transform of the plans that convolve on the row engine with k_f in fp32 (fft_size 256 .. 16384), in fp64:
 // k_f[h] in the order of the engine's registers, [register pair][thread][2], scaled by 1/M and by the frequency mask.
 // The taps are real, so a row is half as long: z[n] = k[2n] + i k[2n+1] is transformed in LDS (lds_fft.h, M/2 points: 139 KB at
@@ -188,7 +211,8 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
 // that fit beside one another do.  us, 4 / 256 / 3000 channels, one kernel for every row and one that permuted its spectrum (fft 16384: a
 // kernel for every factor) -> half-length rows with few threads -> now: fft 1024 8.3, 14, 70 -> 12.3, 12.6, 21 -> 7.0, 7.6, 21;
 // 4096 10.6, 46, 416 -> 13.2, 14.8, 60 -> 8.4, 10.2, 60; 8192 15, 53, 554 -> 15, 18, 112 -> 12, 15, 112; 16384 (4, 256, 1500) 26, 158, 966 ->
-// 32, 37, 206 -> 25, 29, 150.
+// 32, 37, 206 -> 25, 29, 150.  With positions known at compile time, 2 / 256 / 3000 channels: 6.5, 6.6, 12; 7.0, 8.5, 44;
+// 10, 12, 89; 19.6, 24, 268.
 template <int M, bool FEW> constexpr int FILTER64_THREADS = FEW ? (M >= 4096 ? 1024 : M / 4) : M >= 8192 ? 512 : M <= 1024 ? 64 : M / 16;
 template <int M, bool FEW>
 __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
@@ -221,7 +245,7 @@ __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
 #pragma unroll 4
     for (int d = threadIdx.x; d < M; d += NTHR) {
         const int f = G::freq(d / 2 % G::T, d / (2 * G::T) * 2 + d % 2), fh = f & (MH - 1);
-        const double2 z = XD[lds_slot(lds_pos(fh, fl, MH))], m = XD[lds_slot(lds_pos((MH - fh) & (MH - 1), fl, MH))];
+        const double2 z = XD[lds_slot(filter64_pos<MH>(fh))], m = XD[lds_slot(filter64_pos<MH>((MH - fh) & (MH - 1)))];
         const double2 e = make_double2(0.5 * (z.x + m.x), 0.5 * (z.y - m.y));          // (Z + conj Zm) / 2
         const double2 q = make_double2(0.5 * (z.y + m.y), -0.5 * (z.x - m.x));         // (Z - conj Zm) / (2i)
         const double2 v = cmul(q, w[f]);
@@ -232,10 +256,6 @@ __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
 }
 
 }  // namespace
-
-// Factors of its half-length rows: sixteens first, but 512 points as 8 . 8 . 8, as many passes as 16 . 16 . 2 and shorter ones (fft 1024, 128 / 257 / 768 channels
-// 7.1, 12.1, 13.0 -> 6.0, 10.7, 11.8 us; eights cost the other lengths a pass or more work: fft 8192, 128 channels 13.1, 14.5).
-static FacList filter64_factors(int64_t L) { return L == 512 ? FacList{3, {8, 8, 8}} : staged_factors_for(L); }
 
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s)
