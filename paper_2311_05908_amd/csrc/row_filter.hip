@@ -214,7 +214,9 @@ template <int L, int REST = L> __device__ __forceinline__ int filter64_pos(int f
 // 32, 37, 206 -> 25, 29, 150.  With positions known at compile time, 2 / 256 / 3000 channels: 6.5, 6.6, 12; 7.0, 8.5, 44;
 // 10, 12, 89; 19.6, 24, 268.
 template <int M, bool FEW> constexpr int FILTER64_THREADS = FEW ? (M >= 4096 ? 1024 : M / 4) : M >= 8192 ? 512 : M <= 1024 ? 64 : M / 16;
-template <int M, bool FEW>
+// SPLIT: gridDim.y workgroups a channel, each of which transforms the whole row and puts out its share of the bins, for channels that leave
+// compute units idle: the way out is most of the time (fft 16384, 2 channels: 19.6 us, 11.5 without fifteen sixteenths of it).
+template <int M, bool FEW, bool SPLIT>
 __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
     k_row_filter64(const float *__restrict__ k, float2 *__restrict__ kf, const double2 *__restrict__ w, FacList fl, int64_t Nk,
                    bool conj_out, const uint8_t *__restrict__ keep, int64_t n_blocks)
@@ -242,8 +244,9 @@ __global__ void __launch_bounds__((FILTER64_THREADS<M, FEW>))
     __syncthreads();
     lds_forward(XD, w, fl, MH, 2);
     float2 *const o = kf + (int64_t)blockIdx.x * M;
+    const int first = SPLIT ? blockIdx.y * NTHR + threadIdx.x : threadIdx.x, step = SPLIT ? gridDim.y * NTHR : NTHR;
 #pragma unroll 4
-    for (int d = threadIdx.x; d < M; d += NTHR) {
+    for (int d = first; d < M; d += step) {
         const int f = G::freq(d / 2 % G::T, d / (2 * G::T) * 2 + d % 2), fh = f & (MH - 1);
         const double2 z = XD[lds_slot(filter64_pos<MH>(fh))], m = XD[lds_slot(filter64_pos<MH>((MH - fh) & (MH - 1)))];
         const double2 e = make_double2(0.5 * (z.x + m.x), 0.5 * (z.y - m.y));          // (Z + conj Zm) / 2
@@ -265,8 +268,15 @@ int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_ou
         constexpr size_t lds = (size_t)(M / 2 + M / 32) * sizeof(double2);
         auto go = [&](auto few) -> int {
             constexpr bool FEW = decltype(few)::value;
-            FC_TRY(raise_dynamic_lds((const void *)k_row_filter64<M, FEW>, (int)lds));
-            hipLaunchKernelGGL((k_row_filter64<M, FEW>), dim3((unsigned)p->H), dim3(FILTER64_THREADS<M, FEW>), lds, s, k, (float2 *)kf,
+            // Workgroups a channel: as many as the chip has compute units for, and a bin a thread at least.  us, one -> this rule, 2 / 16 / 64 / 128
+            // channels: fft 4096 7.0, 7.3, 7.6, 8.0 -> 6.4, 6.7, 6.7, 7.5; 8192 10.1, 10.5, 10.9, 11.5 -> 7.1, 7.4, 8.5, 9.7; 16384 19.6,
+            // 20.3, 21.1, 21.9 -> 11.5, 12.2, 14.4, 17.2.  Shorter rows are as fast without (fft 2048 6.5, 6.5).
+            constexpr bool SPLIT = FEW && M >= 4096;
+            int parts = 1;
+            while (SPLIT && 2 * parts * p->H <= 256 && 2 * parts * FILTER64_THREADS<M, FEW> <= M) parts *= 2;
+            const auto kernel = parts > 1 ? k_row_filter64<M, FEW, SPLIT> : k_row_filter64<M, FEW, false>;
+            FC_TRY(raise_dynamic_lds((const void *)kernel, (int)lds));
+            hipLaunchKernelGGL(kernel, dim3((unsigned)p->H, (unsigned)parts), dim3(FILTER64_THREADS<M, FEW>), lds, s, k, (float2 *)kf,
                                p->st.w64, filter64_factors(M / 2), Nk, conj_out, keep_dev, n_blocks);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;

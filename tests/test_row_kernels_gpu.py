@@ -159,6 +159,17 @@ def test_fp64_filter_transform_of_few_and_many_channels(M):
         assert torch.equal(many[1:], few)
 
 
+@pytest.mark.parametrize("H", [1, 3, 16, 17, 64, 100, 128, 129])
+@pytest.mark.parametrize("M", [2048, 4096, 8192, 16384])
+def test_fp64_filter_transform_in_shares(M, H):
+    """Up to 128 channels several workgroups put out the bins of one; every channel's k_f is the same (to the bit) as without."""
+    path = "small" if M <= 4096 else "staged"
+    k = torch.randn(256, M - 3, generator=torch.Generator().manual_seed(H)).cuda()
+    whole = fftconv.Plan(M - 3, M, 256, "f32", path=path).filter_fft(k).view(256, -1)
+    few = fftconv.Plan(M - 3, M, H, "f32", path=path).filter_fft(k[:H].contiguous()).view(H, -1)
+    assert torch.equal(whole[:H], few)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M", [256, 512, 1024, 2048, 4096, 8192])
 def test_row_filter_edges(M, dtype):
