@@ -944,16 +944,17 @@ __global__ void __launch_bounds__(NT, 2) k_fused3_big_dk(const uint16_t *__restr
 
 // dk_f of the kernel above ([h][k1][k2 tile][k3 tile][r][lane], lane = (k3 slot / 4 % 4) * 16 + k2 % 16, k3 in the
 // order big_sigma()) -> dk, in two kernels.  The inverse transform runs the factors of the generic path
-// (16, 16, 16, M / 4096) last to first; all but the first act inside contiguous blocks of M / 16 positions, and
+// (16, 16, 16, M / 4096: sixteens_pos) last to first; all but the first act inside contiguous blocks of M / 16 positions, and
 // block d0 (the low four bits of k1) is made of the bins of k1 = d0 and d0 + 16: two contiguous runs of dk_f.
 // Kernel 1, one workgroup per (channel, block): the two runs -> LDS at their positions, the length-M/16
 // inverse there (twiddle table of W_M with stride 16), natural order out to a scratch row; the loads of a run go out together (one by one before: bf16
-// gradients of fft 32768, 16 x 1 rows 59 -> 45 us, 64 x 8 114 -> 63, fft 16384, 16 x 1 30 -> 24, 40 x 2 42 -> 27).  Kernel 2: the
+// gradients of fft 32768, 16 x 1 rows 59 -> 45 us, 64 x 8 114 -> 63, fft 16384, 16 x 1 30 -> 24, 40 x 2 42 -> 27) and positions
+// are known at compile time (2 x 256 rows of fft 32768 104 -> 98, 16 x 64 of 16384 41.9 -> 39.8).  Kernel 2: the
 // remaining factor across the 16 blocks, real part, 1/M, the first Nk samples.
 constexpr int DK_BLK_THREADS = 256;
 template <int N2>
 __global__ void __launch_bounds__(DK_BLK_THREADS) k_big_dk_blocks(const float2 *__restrict__ dkf, float2 *__restrict__ tmp,
-                                                                 const float2 *__restrict__ w, FacList fl, FacList fl_tail, int runs)
+                                                                 const float2 *__restrict__ w, FacList fl_tail, int runs)
 {
     constexpr int BM = BigGeo<N2>::M, BLK = BM / 16, RUN = BLK / 2, R2 = BigGeo<N2>::R2;
     __shared__ float2 XS[BLK + BLK / 16];
@@ -985,7 +986,7 @@ __global__ void __launch_bounds__(DK_BLK_THREADS) k_big_dk_blocks(const float2 *
         const int i = threadIdx.x + n * DK_BLK_THREADS, k1 = d0 + 16 * (i / RUN), j = i % RUN;
         const int lane = j % 64, r = (j / 64) % 4, t3 = (j / 256) % 2, t2 = (j / 512) % R2;
         const int k2 = big_tau<N2>(16 * t2 + lane % 16), k3 = big_sigma(16 * t3 + 4 * (lane / 16) + r);
-        XS[lds_slot(lds_pos(k1 + 32 * k2 + 32 * N2 * k3, fl, BM) - d0 * BLK)] = v[n];
+        XS[lds_slot(sixteens_pos<BM>(k1 + 32 * k2 + 32 * N2 * k3) - d0 * BLK)] = v[n];
     }
     __syncthreads();
     lds_inverse(XS, w, fl_tail, BLK, 16);
@@ -1440,7 +1441,7 @@ static int big_dk_finish_t(const fftconv_plan *p, const void *dkf, int64_t runs,
     tail.nf = fl.nf - 1;
     for (int i = 0; i < MAX_FACTORS; ++i) tail.fac[i] = i + 1 < fl.nf ? fl.fac[i + 1] : 0;
     hipLaunchKernelGGL(k_big_dk_blocks<N2>, dim3(16, (unsigned)p->H), dim3(DK_BLK_THREADS), 0, s, (const float2 *)dkf,
-                       (float2 *)tmp, (const float2 *)p->st.w32, fl, tail, (int)runs);
+                       (float2 *)tmp, (const float2 *)p->st.w32, tail, (int)runs);
     FC_HIP(hipGetLastError());
     const int bs = 256;
     hipLaunchKernelGGL(k_big_dk_last<N2>, dim3((unsigned)((p->H * BLK + bs - 1) / bs)), dim3(bs), 0, s, (const float2 *)tmp,

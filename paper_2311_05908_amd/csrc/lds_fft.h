@@ -136,6 +136,16 @@ __device__ inline int lds_pos(int f, const FacList &fl, int M)
     }
     return pos;
 }
+// lds_pos() for staged_factors_for(L), with L and so the factors known at compile time
+template <int L> __device__ __forceinline__ int sixteens_pos(int f)
+{
+    if constexpr (L == 1) {
+        return 0;
+    } else {
+        constexpr int F = L >= 16 ? 16 : L;
+        return (f & (F - 1)) * (L / F) + sixteens_pos<L / F>(f / F);
+    }
+}
 // the inverse of lds_pos(): the frequency held at a position
 __device__ inline int lds_freq(int pos, const FacList &fl, int M)
 {
