@@ -1434,6 +1434,8 @@ int multipass_dk_outer_inv(const fftconv_plan *p, const void *T2, float *dk, int
     }
 }
 
+constexpr int64_t MOST_ROWS = 65535;          // second dimension of a launch's grid
+
 // One set of the three passes over rows [0, B) of u.  ko_lo, ko_hi: outer frequency digits ko in [ko_lo, ko_hi)
 // only meet zeroed bins of k_f (frequency-sparse filters); their rows of the workspace are skipped by all three
 // passes.  ko_lo >= ko_hi: none.  wg, vg: input / output gate of the gated form, fused into passes A and C.
@@ -1450,8 +1452,8 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
     const int64_t rows = npairs * p->H;
     const bool packed = lone && outer_real_ok((int)(p->M / MI));
     const OuterGeo g = outer_geo(p->M, packed ? 0 : rows);
-    if (rows > 65535) {
-        set_error("fftconv_forward: ceil(B/2) * H = %lld exceeds the multi-pass grid limit 65535", (long long)rows);
+    if (rows > MOST_ROWS) {
+        set_error("fftconv_forward: ceil(B/2) * H = %lld exceeds the multi-pass grid limit %lld", (long long)rows, (long long)MOST_ROWS);
         return FFTCONV_EUNSUPPORTED;
     }
     const bool f16 = p->dtype == FFTCONV_F16;
@@ -1493,8 +1495,11 @@ static int multipass_passes(const fftconv_plan *p, const void *u, const void *kf
 // 15 us where the chip has room for it beside the pairs.  us, on its own, with the pairs (outer length x H; B = 3): 16 11 x 1 x 65536 fp16 35.0, 19.3; 256
 // 3 x 16 x 65536 43.9, 34.4; 512 54.5, 45.7; 1024 75.5, 69.8, outer length 8 71.2, 66.7, 256 91.8, 85.8, 512 113, 103; 33 x 64 x 65536 561, 554; 1536
 // 112, 113; 2048 152, 170.  Outer lengths 1 and 2 have no passes for a row on its own: 9 x 400 x 8190 circular 90, 73.  Its error is that of the
-// other rows, a fifth to a quarter below that of a real row.
-static bool lone_in_pairs(const fftconv_plan *p) { return p->M <= 2 * MI || p->H * (p->M / MI) <= 1024; }
+// other rows, a fifth to a quarter below that of a real row.  Only where a launch holds them all: pairs and lone rows may be MOST_ROWS each.
+static bool lone_in_pairs(const fftconv_plan *p, int64_t B)
+{
+    return (B + 1) / 2 * p->H <= MOST_ROWS && (p->M <= 2 * MI || p->H * (p->M / MI) <= 1024);
+}
 
 // Batch rows are transformed two at a time (one complex transform per pair, the filter being real); a row left
 // over (odd B, B = 1) goes with them, or through a set of passes of its own as a real sequence (see above).
@@ -1507,7 +1512,7 @@ int multipass_forward(const fftconv_plan *p, const void *u, const void *kf, void
     // reads u and writes y itself, nothing passes through the workspace.  Gated calls and N not a multiple of 4
     // (rows that start off an 8-byte boundary) keep the three passes.
     if (p->M == MI && p->N % 4 == 0 && !wg && !vg) return fused3_inner_whole(p, u, kf, y, B, s);
-    const int64_t Be = B > 1 && lone_in_pairs(p) ? B : B - B % 2;      // rows in pairs
+    const int64_t Be = B > 1 && lone_in_pairs(p, B) ? B : B - B % 2;      // rows in pairs
     if (Be > 0) {
         const int rc = multipass_passes(p, u, kf, y, Be, S, s, ko_lo, ko_hi, wg, vg, false);
         if (rc) return rc;

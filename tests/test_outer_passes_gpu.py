@@ -107,3 +107,31 @@ def test_the_last_row_of_an_odd_batch(dtype, B, H, N, M):
     L = M if N + 299 > M else 2 * N             # the circular length, or one that no output reaches around
     ref = torch.fft.irfft(torch.fft.rfft(u.double(), L) * torch.fft.rfft(k.double(), L), L)[..., :N]
     assert parity_error(y.numpy(), ref.numpy(), TOL[dtype], "odd batch") <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M,gated", [
+    ("bf16", 3, 33000, 101, 8192, False), ("f16", 3, 40000, 104, 8192, True),
+    ("bf16", 3, 40000, 101, 16384, False), ("f16", 5, 30000, 104, 16384, True),
+    ("bf16", 511, 256, 101, 32768, False), ("f16", 511, 256, 101, 32768, True),
+    ("bf16", 4095, 32, 101, 65536, False),
+])
+def test_odd_batches_of_many_rows(dtype, B, H, N, M, gated):
+    """The pairs and the lone rows fit into a launch's 65535 rows each, all pairs of the odd batch (65536 to 90000) do not."""
+    assert B // 2 * H <= 65535 < (B + 1) // 2 * H
+    g = torch.Generator().manual_seed(H)
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype])
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype, path="multipass")
+    kf, out = plan.filter_fft(k.cuda()), torch.full_like(u, float("nan"), device="cuda")
+    x = u.double()
+    if gated:
+        w = torch.randn(B, H, N, generator=g).to(u.dtype)
+        y, x = plan.forward_gated(u.cuda(), w.cuda(), None, kf, out=out), x * w.double()
+    else:
+        y = plan.forward(u.cuda(), kf, out=out)
+    ref = conv(x, k.double(), 256, N).numpy()               # (no output reaches around 256 samples, either)
+    assert parity_error(y.cpu().double().numpy(), ref, TOL[dtype], "y") <= TOL[dtype]
+    if not gated:                                           # the gradient of u: the same passes on the conjugate spectrum
+        du = plan.backward_input(u.cuda(), plan.filter_fft_adjoint(k.cuda()), out=out.fill_(float("nan")))
+        ref = conv(x.flip(-1), k.double(), 256, N).flip(-1).numpy()
+        assert parity_error(du.cpu().double().numpy(), ref, TOL[dtype], "du") <= TOL[dtype]
