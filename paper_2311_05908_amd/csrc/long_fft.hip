@@ -519,7 +519,10 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restric
 
 // Longer rows, last kernel: the outer factors back, real part -> row of y_re, imaginary part -> row of y_im
 // (nullptr: no second row), the first N samples.
-template <typename IO>
+// GATED: times the rows of g_re and g_im.  A thread asks for all its gates at once, and ahead of the transforms: a workgroup has its compute
+// unit to itself (70 KB, 131 registers), so nothing else covers a load that is waited for.  us, output gate, sample by sample behind them -> so (with a
+// kernel of its own): 2 x 256 x 131072 circular 641 -> 435 (552), 2 x 1024 x 16384 fft 32768 494 -> 408 (446).
+template <typename IO, bool GATED>
 __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict__ tmp, IO *__restrict__ y_re,
                                                        IO *__restrict__ y_im, LongTw w, FacList flA, int A, int C, int64_t N,
                                                        LongRows rows, const IO *__restrict__ g_re, const IO *__restrict__ g_im)
@@ -530,6 +533,16 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
     const int col0 = blockIdx.x * C;
     if (col0 >= N) return;
     const bool two = y_im && rows.partner(blockIdx.y);
+    const int lgC = __ffs(C) - 1;
+    float gr[GATED ? LPT : 1], gi[GATED ? LPT : 1];
+    if constexpr (GATED) {
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            const int i = threadIdx.x + j * LT, n = (i >> lgC) * LB + col0 + (i & (C - 1));
+            gr[j] = ld_real(g_re + first, n < N ? n : 0);
+            gi[j] = two ? ld_real(g_im + first, n < N ? n : 0) : 0.f;
+        }
+    }
     load_cols(XL, tmp + row * M, C, col0);
     __syncthreads();
     int Sp = 1, R = A;
@@ -540,17 +553,24 @@ __global__ void __launch_bounds__(LT) k_long_inv_cols_y(const float2 *__restrict
         __syncthreads();
         Sp *= Nj;
     }
-    for (int i = threadIdx.x; i < LB; i += LT) {
-        const int a = i >> (__ffs(C) - 1), c = i & (C - 1);
-        const int n = a * LB + col0 + c;
-        if (n < N) {
-            float2 v = XL[lds_slot(i)];
-            if (g_re) {                                           // the output gate
-                v.x *= ld_real(g_re + first, n);
-                if (two) v.y *= ld_real(g_im + first, n);
+    if constexpr (GATED) {
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            const int i = threadIdx.x + j * LT, n = (i >> lgC) * LB + col0 + (i & (C - 1));
+            if (n < N) {
+                const float2 v = XL[lds_slot(i)];
+                st_real(re, n, v.x * gr[j]);
+                if (two) st_real(im, n, v.y * gi[j]);
             }
-            st_real(re, n, v.x);
-            if (two) st_real(im, n, v.y);
+        }
+    } else {
+        for (int i = threadIdx.x; i < LB; i += LT) {
+            const int n = (i >> lgC) * LB + col0 + (i & (C - 1));
+            if (n < N) {
+                const float2 v = XL[lds_slot(i)];
+                st_real(re, n, v.x);
+                if (two) st_real(im, n, v.y);
+            }
         }
     }
 }
@@ -772,7 +792,8 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
     const LongTw tw = long_tw(p);
     float2 *tmp = (float2 *)workspace;
     FC_TRY(raise_dynamic_lds((const void *)k_long_conv_blocks, B_LDS));
-    FC_TRY(raise_lds((const void *)k_long_inv_cols_y<IO>));
+    const auto inv_cols = vg ? k_long_inv_cols_y<IO, true> : k_long_inv_cols_y<IO, false>;
+    FC_TRY(raise_lds((const void *)inv_cols));
     auto blocks = [&](int per_row, int64_t first, int64_t n, bool natural) -> int {
         hipLaunchKernelGGL(k_long_conv_blocks, dim3((unsigned)per_row, (unsigned)n), dim3(RB::T), B_LDS, s, tmp, (const float4 *)kf,
                            rf::row_table<RB>(p), g.flA, g.A, natural, (int)(first % H), (int)H);
@@ -803,7 +824,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
             FC_TRY(launch_fwd_cols<IO>(g, u0, pairs ? u0 + H * N : nullptr, tmp, tw, n, N, false, s, false, where, w0,
                                        wg && pairs ? w0 + H * N : nullptr));
             FC_TRY(blocks(g.A, first, n, false));
-            hipLaunchKernelGGL(k_long_inv_cols_y<IO>, dim3((unsigned)g.A, (unsigned)n), dim3(LT), L_LDS, s, (const float2 *)tmp, y0,
+            hipLaunchKernelGGL(inv_cols, dim3((unsigned)g.A, (unsigned)n), dim3(LT), L_LDS, s, (const float2 *)tmp, y0,
                                pairs ? y0 + H * N : nullptr, tw, g.flA, g.A, g.C, N, where, v0, vg && pairs ? v0 + H * N : nullptr);
             FC_HIP(hipGetLastError());
             return FFTCONV_OK;

@@ -123,6 +123,40 @@ def test_gates_on_the_row_engine(dtype, B, H, N, M, shift):
         assert parity_error(y.double().numpy(), ref, TOL[dtype], "gates %d%d" % (use_w, use_v), v) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("B,H,N,M", [
+    (2, 1024, 16384, 32768), (2, 512, 65534, 65536), (2, 256, 131072, 131072),        # outer passes of pairs of fp32 rows
+])
+def test_an_output_gate_costs_no_more_than_a_kernel_of_its_own(B, H, N, M):
+    """A gate inside the last kernel reads v; one of its own reads y and writes it again, a third of such a call (0.78 of the time with
+    it at 2 x 256 x 131072, 1.15 when the kernel waited for its gates one after another)."""
+    u, v = (torch.randn(B, H, N, device="cuda") for _ in range(2))
+    plan = fftconv.Plan(N, M, H, "f32")
+    kf = plan.filter_fft(torch.randn(H, N, device="cuda") / N ** 0.5)
+    y, z = torch.empty_like(u), torch.empty_like(u)
+
+    def apart():
+        torch.mul(plan.forward(u, kf, out=y), v, out=z)
+
+    def fused():
+        plan.forward_gated(u, None, v, kf, out=y)
+
+    def time(call):
+        best = float("inf")
+        for _ in range(10):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            call()
+            t[1].record()
+            t[1].synchronize()
+            best = min(best, t[0].elapsed_time(t[1]))
+        return best
+
+    two, one = time(apart), time(fused)
+    print("output gate %d x %d x %d: %.3f ms, of its own %.3f ms" % (B, H, N, one, two), flush=True)
+    assert torch.equal(y, z)                # the same roundings, too
+    assert one <= two
+
+
 def test_gated_without_gates_is_forward_and_errors():
     w = synth.scaled(W["cfg2"], B=2, H=2)
     u = synth.gen_u(w).cuda()
