@@ -28,8 +28,7 @@ namespace {
 using rf::Row;
 
 // waves per SIMD the register budget is held to: what LDS allows (8.5 KB a wave, 17 KB where 32 points of a thread go
-// through it as pairs) and the registers can be had for (spilled: 16 - 28 bytes of k_row_conv_few<2048> with an output gate)
-// (GATED: one less, for the gates)
+// through it as pairs) and the registers can be had for (GATED: one less, for the gates); nothing is spilled
 constexpr int waves_of(int M, bool gated = false) { return (M == 256 ? 5 : M == 2048 || M == 4096 ? 4 : 2) - (gated && M <= 4096 && M != 512 && M != 1024 ? 1 : 0); }
 
 template <int M, typename IO, bool WIDE = false> using ConvRow = Row<M, std::is_same<IO, float>::value && M <= 4096, false, WIDE>;
@@ -109,13 +108,16 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? (GATED ? 3 : 4) : wa
     }
     if constexpr (GATED) {
         using Raw = rf::RawPair<G, IO, HALF>;
-        constexpr bool AHEAD = HALF ? M <= 8192 : M <= 4096;      // the output gate asked for ahead of the inverse transform, as registers allow
+        // the output gate asked for ahead of the inverse transform, as registers allow (kept from there, nineteen of fp32 512 were spilled:
+        // 3 x 16384 x 512, output gate, 132 -> 81 us)
+        constexpr bool AHEAD = HALF ? M <= 8192 : M <= 4096 && !(M == 512 && sizeof(IO) == 4) && !(M == 256 && std::is_same<IO, __hip_bfloat16>::value);
         Raw rv;
-        if (AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, tid, words);
-        rf::inverse<G>(x, Z, tab, tw1, tid);
-        if (!AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, tid, words);
         int j = tid;
-        asm volatile("" : "+v"(j));                               // (the masks of the samples are not kept from the input to here)
+        if (!HALF) asm volatile("" : "+v"(j));                    // (neither addresses nor masks of the samples are kept from the input to here)
+        if (AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, j, words);
+        rf::inverse<G>(x, Z, tab, tw1, tid);
+        asm volatile("" : "+v"(j));
+        if (!AHEAD && vg) rv.fetch(vg + r0, vg + r1, N, j, words);
         if (live) rv.store(x, y + r0, y + r1, N, j, words, two, vg);
     } else {
         rf::inverse<G>(x, Z, tab, tw1, tid);
@@ -205,8 +207,8 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 
 // Pairs of rows up to which they are WIDE.  us, others, wide: fp32 causal fft 512, 512 pairs 7.9, 5.3, 2048 8.3, 6.1, 3072 8.6, 8.1, 4096 8.8, 10.1; 1024, 512 8.6,
 // 6.1, 2048 9.5, 8.3, 4096 16.4, 15.6, 6144 20.2, 22.1; fp16 circular 512, 3072 9.2, 7.8, 4096 9.4, 9.5; 1024, 4096 15.2, 15.0, 6144 20.3, 20.4.  Both gates: 512,
-// fp32 6144 17.2, 16.4, 8192 20.3, 21.4, bf16 circular 20.9, 19.5 and 22.9, 23.3; 1024 always, fp32 8192 35.6, 33.0, 24576 43.8, 41.1, bf16 circular 8192
-// 42.5, 36.3, fp16 32768 160, 159.  Calls of few rows (k_row_conv_few): 512 bf16 3072 7.9, 7.1, 4096 8.0, 8.2; 1024, 1024 8.0, 6.9, 1536 8.1, 8.9.
+// fp32 6144 18.3, 17.4, 8192 21.1, 22.2, bf16 circular 19.3, 18.0 and 21.4, 22.6; 1024 always, fp32 8192 36.8, 34.1, 32768 160, 156, bf16 circular 8192
+// 40.5, 37.2, fp16 32768 171, 171.  Calls of few rows (k_row_conv_few): 512 bf16 3072 7.9, 7.1, 4096 8.0, 8.2; 1024, 1024 8.0, 6.9, 1536 8.1, 8.9.
 template <int M> constexpr int64_t wide_most(bool gated) { return M == 512 ? (gated ? 6144 : 3072) : gated ? INT64_MAX : 4096; }
 template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
 

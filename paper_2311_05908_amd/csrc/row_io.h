@@ -157,6 +157,8 @@ template <typename IO> __device__ __forceinline__ float mul_io(float a, float b)
 template <typename G, typename IO, bool HALF> struct RawPair {
     static constexpr int MIN = HALF ? G::R0 / 2 : G::R0;
     uint32_t a[MIN], b[MIN];                                      // words (b unused), or a sample of either row
+    // (16-bit samples: a behind b.  The compiler makes one store of the last ones of both branches below, and where those are of a and of b
+    // the arrays stay in memory for it)
 
     __device__ __forceinline__ void fetch(const IO *__restrict__ r0, const IO *__restrict__ r1, int N, int tid, bool words)
     {
@@ -176,8 +178,8 @@ template <typename G, typename IO, bool HALF> struct RawPair {
                     a[m] = ((const uint32_t *)r0)[at];
                     b[m] = ((const uint32_t *)r1)[at];
                 } else {
-                    a[m] = ((const uint16_t *)r0)[at];
                     b[m] = ((const uint16_t *)r1)[at];
+                    a[m] = ((const uint16_t *)r0)[at];
                 }
             }
         }
