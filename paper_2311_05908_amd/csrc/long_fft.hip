@@ -432,29 +432,6 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_sum(const float2 *part
     store_row<G>(x, out + base, tid);
 }
 
-// Several runs: the same sums, a pair of bins to a thread, to out (acc, or the first run's place); every compute unit takes part, where the
-// few workgroups of k_long_blocks_sum fetch a run's 64 KB after the other's.  Same additions in the same order.
-__global__ void __launch_bounds__(256) k_long_runs_add(const float4 *part, int64_t apart, int runs, const float4 *acc, float4 *out, bool first)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    float4 x = first ? part[i] : acc[i];
-    constexpr int AT_ONCE = 8;
-    for (int r = first ? 1 : 0; r < runs; r += AT_ONCE) {
-        float4 v[AT_ONCE];
-#pragma unroll
-        for (int j = 0; j < AT_ONCE; ++j) v[j] = part[min(r + j, runs - 1) * apart + i];
-#pragma unroll
-        for (int j = 0; j < AT_ONCE; ++j)
-            if (r + j < runs) {
-                x.x += v[j].x;
-                x.y += v[j].y;
-                x.z += v[j].z;
-                x.w += v[j].w;
-            }
-    }
-    out[i] = x;
-}
-
 // Inverse, columns: the factors of A, then real part times scale of the samples n < Nk -> dk (rows, Nk).
 __global__ void __launch_bounds__(LT) k_long_inv_cols_dk(const float2 *__restrict__ tmp, float *__restrict__ dk, LongTw w,
                                                         FacList flA, int A, int C, int64_t Nk, float scale)
@@ -614,7 +591,7 @@ constexpr int B_LDS = RB::LDS_BYTES;
 // 64, 128, 256 MiB, all at once 510, 325, 246, 246).
 constexpr int64_t GRAD_TRIP = (int64_t)1 << 28, GRAD_LEAST = (int64_t)1 << 25;
 
-// Four runs or more (of 128 spectra at most, then) are added up by k_long_runs_add first, and cost less.  Whole gradient, us, with the
+// Four runs or more (of 128 spectra at most, then) are added up by k_runs_add (row_grad.hip) first, and cost less.  Whole gradient, us, with the
 // other kernel alone: bf16 16 x 1 x 65536 59.7 -> 40.5, 16 x 5 74.0 -> 67.9, 8 x 4 56.0 -> 50.2, 30 x 2 x 131072 105 -> 87, f16 73 x 1 x 20000 fft 65536
 // 97.8 -> 60.9 (64.7 with no more runs than before), fp32 4 x 4 x 16384 30.2 -> 29.1, 8 x 16 x 10000 fft 32768 53.8 -> 51.3.
 constexpr int64_t ADD_RUNS = 4;
@@ -638,10 +615,7 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
     FC_HIP(hipGetLastError());
     if (runs == 1) return FFTCONV_OK;
     if (runs >= ADD_RUNS) {
-        const int64_t pairs = blocks * nh * (LB / 2);             // a multiple of 256
-        hipLaunchKernelGGL(k_long_runs_add, dim3((unsigned)(pairs / 256)), dim3(256), 0, s, (const float4 *)tu, per * stride / 2, (int)runs,
-                           (const float4 *)acc, last ? (float4 *)tu : (float4 *)acc, first);
-        FC_HIP(hipGetLastError());
+        FC_TRY(runs_add(tu, per * stride / 2, runs, first ? nullptr : acc, last ? tu : acc, blocks * nh * (LB / 2), s));
         if (!last) return FFTCONV_OK;
         first = true;
         runs = 1;

@@ -150,28 +150,38 @@ __global__ void __launch_bounds__(rf::threads_of(M), (GRAD_WAVES<M, WIDE>))
     if (live) store_dk<G>(x, dk + (int64_t)h * Nk, Nk, 1.f / M, tid);
 }
 
-// The sums of a channel's runs, two bins to a thread, to the first run's place: what k_row_dk does with a workgroup to a channel, a trip to memory
-// for each run.  The same additions in the same order.
-__global__ void __launch_bounds__(256) k_row_runs_add(float4 *part, int64_t apart, int S)
+// The sums of gradients' runs, two bins to a thread, n threads in all: part[r * apart + i] over r < runs, and acc[i] where there is one, to
+// out[i] (in place, too).  Every compute unit takes part, where the kernels that transform them back have a workgroup to a channel or block and
+// wait for a run after the other.  Eight runs are fetched at a time and added up in pairs: one after the other, more runs meant more error (dk of
+// bf16 64 x 1 x 32768 in 64 runs 3.99e-7, in pairs 3.79e-7; in 32 runs, in order, 3.87e-7).
+__global__ void __launch_bounds__(256) k_runs_add(const float4 *part, int64_t apart, int runs, const float4 *acc, float4 *out, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= apart) return;
-    float4 x = part[i];
+    if (i >= n) return;
+    float4 x = acc ? acc[i] : part[i];
     constexpr int AT_ONCE = 8;
-    for (int s = 1; s < S; s += AT_ONCE) {
+    for (int r = acc ? 0 : 1; r < runs; r += AT_ONCE) {
         float4 v[AT_ONCE];
 #pragma unroll
-        for (int j = 0; j < AT_ONCE; ++j) v[j] = part[min(s + j, S - 1) * apart + i];
+        for (int j = 0; j < AT_ONCE; ++j) v[j] = part[min(r + j, runs - 1) * apart + i];
 #pragma unroll
         for (int j = 0; j < AT_ONCE; ++j)
-            if (s + j < S) {
-                x.x += v[j].x;
-                x.y += v[j].y;
-                x.z += v[j].z;
-                x.w += v[j].w;
+            if (r + j >= runs) v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int half = AT_ONCE / 2; half > 0; half /= 2)
+#pragma unroll
+            for (int j = 0; j < half; ++j) {
+                v[j].x += v[j + half].x;
+                v[j].y += v[j + half].y;
+                v[j].z += v[j + half].z;
+                v[j].w += v[j + half].w;
             }
+        x.x += v[0].x;
+        x.y += v[0].y;
+        x.z += v[0].z;
+        x.w += v[0].w;
     }
-    part[i] = x;
+    out[i] = x;
 }
 
 // From how many runs on that kernel adds them up, and the most pairs of bins that it does so with.  A run costs k_row_dk 0.2 us at 256 points, 0.3 at 512, 0.35 to 4096,
@@ -224,7 +234,7 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
     int64_t left = sp.S;
     const int64_t apart = p->H * (M / 2);
     if (sp.S >= ADD_RUNS<M> && sp.S * apart <= ADD_MOST) {
-        FC_TRY(row_runs_add(workspace, apart, sp.S, s));
+        FC_TRY(runs_add(workspace, apart, sp.S, nullptr, workspace, apart, s));
         left = 1;
     }
     FC_TRY(raise_dynamic_lds((const void *)k_row_dk<M, WIDE>, lds));
@@ -252,10 +262,10 @@ int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk,
 
 }  // namespace
 
-// S spectra, `apart` pairs of bins from one to the next, added up in order in the first one's place
-int row_runs_add(void *part, int64_t apart, int64_t S, hipStream_t s)
+int runs_add(const void *part, int64_t apart, int64_t runs, const void *acc, void *out, int64_t pairs, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_row_runs_add, dim3((unsigned)((apart + 255) / 256)), dim3(256), 0, s, (float4 *)part, apart, (int)S);
+    hipLaunchKernelGGL(k_runs_add, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s, (const float4 *)part, apart, (int)runs,
+                       (const float4 *)acc, (float4 *)out, pairs);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
