@@ -273,8 +273,9 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&v)[4])
     }
 }
 
-// kernel_slot() of the frequency in register p of thread tid.  Every digit of a slot but that of 2048 points depends on the thread alone or
-// the register alone, so the slots of a thread lie a constant apart: one address and immediates, where digit by digit they were 1700 of the 3000 vector
+// kernel_slot() of the frequency in register p of thread tid.  Every digit of a slot depends on the thread alone or the register alone, but at
+// 2048 points and in wide rows of 512 (bit 5 of a frequency is a thread's there, the other bits of its digit k3 a register's), whose slots are worked
+// out in full.  Otherwise the slots of a thread lie a constant apart: one address and immediates, where digit by digit they were 1700 of the 3000 vector
 // instructions of the gradient's tail at 8192 points (k_row_dk_finish, 768 channels 25.1 -> 19.8 us; the few-row kernel, 1 x 768 x 2048 gated 13.5 -> 10.5).
 template <typename G> __device__ __forceinline__ int slot_of(int tid, int p)
 {

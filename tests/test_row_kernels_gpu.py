@@ -266,6 +266,46 @@ def test_few_rows_round_at_the_gates(M, dtype):
         assert differ <= 0.02
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("H,N,M,shift", [
+    (3, 256, 256, 0), (3, 256, 256, 1), (5, 191, 256, 0),         # words of two samples; gates that begin off a word, odd rows: sample by sample
+    (3, 512, 512, 0), (3, 512, 512, 1), (5, 383, 512, 0), (6200, 512, 512, 0), (6200, 383, 512, 0),       # wide rows, and beyond their line
+    (3, 1024, 1024, 0), (5, 767, 1024, 0), (3, 1024, 1024, 1), (3, 2048, 2048, 0), (5, 1535, 2048, 0), (3, 4096, 4096, 0), (5, 3071, 4096, 0),
+])
+def test_rows_of_small_plans_round_at_the_gates(dtype, H, N, M, shift):
+    """As above, of the kernel of plans whose k_f is fp32, with the same filter, whose convolution is p[n] + 91/128 p[n - M/4] around the
+    transform.  Then an infinity in the output gate and a NaN in the input gate: the one reaches its own element, the other its pair of rows."""
+    B = 3 if H < 10 else 2
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
+    u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.path == "small"
+    taps = torch.zeros(H, N, device="cuda")
+    taps[:, 0], taps[:, M // 4] = 1.0, 91 / 128
+    kf = plan.filter_fft(taps)
+
+    def placed(t):
+        room = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")
+        room[shift:].copy_(t.flatten())
+        return room[shift:].view(t.shape)
+
+    for wg, vg in ((g, None), (None, v), (g, v)):
+        y = plan.forward_gated(u.cuda(), None if wg is None else placed(wg), None if vg is None else placed(vg), kf).cpu()
+        p = u if wg is None else u * wg
+        around = torch.zeros(B, H, M, dtype=torch.float64)
+        around[..., :N] = p.double()
+        c = p.double() + 91 / 128 * around.roll(M // 4, -1)[..., :N]
+        ref = c.to(u.dtype) if vg is None else c.to(u.dtype) * vg
+        differ = (y != ref).float().mean().item()
+        print("gates %s N=%d M=%d w=%d v=%d differ=%.4f" % (dtype, N, M, wg is not None, vg is not None, differ), flush=True)
+        assert differ <= 0.02
+    v[0, 0, N // 2 | 1], g[1, 2, 7] = float("inf"), float("nan")
+    bad = ~torch.isfinite(plan.forward_gated(u.cuda(), placed(g), placed(v), kf).cpu().float())
+    assert bad[0, 0, N // 2 | 1] and bool(bad[1, 2].all())
+    bad[0, 0, N // 2 | 1] = bad[0:2, 2] = False
+    assert not bool(bad.any())
+
+
 @pytest.mark.parametrize("dtype,B,H,N,M,gates", [
     ("f32", 2, 3072, 65, 512, 0), ("f32", 3, 1537, 65, 512, 0),          # wide rows up to the line, the others from there on
     ("bf16", 2, 3072, 300, 512, 0), ("f16", 2, 3073, 511, 512, 0),
