@@ -316,9 +316,9 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
 // fp64 filter transform of the plans that convolve on the row engine with k_f in fp32
 int row_filter64(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks,
                  void *kf, hipStream_t s);
-// `pairs` pairs of bins of `runs` spectra, `apart` of them from one to the next, and of acc unless null, added up to out (acc or the first
-// spectrum's place, too)
-int runs_add(const void *part, int64_t apart, int64_t runs, const void *acc, void *out, int64_t pairs, hipStream_t s);
+// `pairs` pairs of bins of `runs` runs, `apart` of them from one to the next, and of acc unless null, added up to out (acc or the first
+// run's place, too); rows: see the kernel
+int runs_add(const void *part, int64_t apart, int64_t runs, const void *acc, void *out, int64_t pairs, hipStream_t s, int rows = 0);
 int row_dk_finish(const fftconv_plan *p, void *dkf, int64_t runs, float *dk, int64_t Nk, hipStream_t s);
 // short transforms on them, fft_size 256 .. 4096, any dtype; radices reported in f3.N1..N3
 bool small_supported(int64_t N, int64_t M, int dtype);
