@@ -147,10 +147,14 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     const bool exact = N == M / 2;
+    // The gates as words, in flight with what they multiply; at 256 points, 8 samples a thread, as fp32 one after the other: the masks of the words, which
+    // rows that fill their registers do without, are more there (output gate, 16 x 768 x 128, 6.36 us, words 6.64; fp16 input gate, 2 x 256 x 128, 4.70, 4.95;
+    // bf16 input gates are the faster ones as words, 4.85, 4.68 at 1 x 2048 x 128).
+    constexpr bool WORDS = M > 256, WORDS_IN = WORDS || std::is_same<IO, __hip_bfloat16>::value;
     using Raw = rf::RawPair<G, IO, true>;
-    float2 x[G::P];
+    float2 x[G::P], g[G::P];
     Raw rv;
-    if constexpr (GATE & 1) {
+    if constexpr ((GATE & 1) && WORDS_IN) {
         Raw ru, rw;
         ru.fetch(u + r0, u + r1, N, tid, true);
         rw.fetch(wg + r0, wg + r1, N, tid, true);
@@ -158,6 +162,11 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
         for (int m = 0; m < Raw::MIN; ++m) x[m] = ru.value(m, N, tid, true, two, rw, true);
     } else {
         rf::load_pair<G, IO, true>(x, u + r0, u + r1, N, tid, exact, true, true, two);
+    }
+    if constexpr ((GATE & 1) && !WORDS_IN) {
+        rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
+#pragma unroll
+        for (int m = 0; m < G::P / 2; ++m) x[m] = rf::rounded<IO>(x[m].x * g[m].x, x[m].y * g[m].y);
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
@@ -169,11 +178,19 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     });
 #pragma unroll
     for (int p = 0; p < G::P; ++p) x[p] = rf::mul(x[p], rf::unpack<IO>(kv[p]));
-    if constexpr (GATE & 2) rv.fetch(vg + r0, vg + r1, N, tid, true);
+    if constexpr ((GATE & 2) && WORDS) rv.fetch(vg + r0, vg + r1, N, tid, true);
     rf::inverse<G>(x, Z, tab, tw1, tid);
-    if constexpr (GATE & 2) {
+    if constexpr ((GATE & 2) && WORDS) {
         if (live) rv.store(x, y + r0, y + r1, N, tid, true, two, true);
         return;
+    }
+    if constexpr ((GATE & 2) && !WORDS) {
+        rf::load_pair<G, IO, true>(g, vg + r0, vg + r1, N, tid, exact, true, true, two);
+#pragma unroll
+        for (int m = 0; m < G::P / 2; ++m) {
+            const float2 c = rf::rounded<IO>(x[m].x, x[m].y);
+            x[m] = make_float2(c.x * g[m].x, c.y * g[m].y);
+        }
     }
     if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }
