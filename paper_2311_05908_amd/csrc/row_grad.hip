@@ -279,13 +279,14 @@ bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSE
 // to transform it back, and of few at short lengths.  us, matrix cores, rows (bf16): 1 x 16 fft 256 11.5, 8.1, 512 13.4, 8.3, 1024 13.5, 8.4, 2048 15.0, 9.3,
 // 4096 12.3, 9.4, 8192 14.1, 16.8; 1 x 768 25.8, 8.4, 29.5, 8.5, 28.6, 8.4, 35.5, 11.2, 28.0, 15.4; 2 x 64 11.8, 10.9, 13.6, 11.3, 13.8, 11.2, 16.1, 12.5, 12.5, 13.5;
 // 8 x 16 11.5, 10.9, 13.3, 11.2, 13.6, 12.5, 14.9, 14.9; 8 x 64 12.0, 11.2, 13.9, 11.4, 14.1, 13.8; 8 x 256 13.8, 12.0, 15.9, 12.7, 16.1, 20.1; 16 x 16 11.4, 13.3,
-// 13.4, 11.6, 13.5, 13.9; 16 x 768 fft 512 31.1, 26.9.  The spectra of their runs, a batch row each at most, fit into the workspace for that kernel's 8192 slots a channel.
+// 13.4, 11.6, 13.5, 13.9; fft 512 from 12 batch rows on, where the other kernel has a round of channels to itself and these a chip full of runs, 12 x 256 17.4, 17.8, 16 x 96 14.7,
+// 15.0, 16 x 256 17.7, 22.0, 16 x 512 25.2, 26.7, but 16 x 64 14.4, 13.5, 16 x 768 31.1, 26.9.  The spectra of their runs, a batch row each at most, fit into the workspace for that kernel's 8192 slots a channel.
 bool row_backward_filter_few(const fftconv_plan *p, int64_t B)
 {
     if (B * p->H > 1 << 20) return false;                         // (far within the limits of a launch)
     switch (p->M) {
     case 256: return B <= 8;
-    case 512: return B <= 16;
+    case 512: return B <= 11 || (B <= 16 && (p->H <= 64 || p->H > 512));
     case 1024: return B == 1 || (B <= 8 && B * p->H <= 512);
     case 2048: return B <= 4 && (B == 1 || B * p->H <= 512);
     case 4096: return B == 1;
