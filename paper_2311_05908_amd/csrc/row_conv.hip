@@ -223,10 +223,11 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 }
 
 // Pairs of rows up to which they are WIDE.  us, others, wide: fp32 causal fft 512, 512 pairs 7.9, 5.3, 2048 8.3, 6.1, 3072 8.6, 8.1, 4096 8.8, 10.1; 1024, 512 8.6,
-// 6.1, 2048 9.5, 8.3, 4096 16.4, 15.6, 6144 20.2, 22.1; fp16 circular 512, 3072 9.2, 7.8, 4096 9.4, 9.5; 1024, 4096 15.2, 15.0, 6144 20.3, 20.4.  Both gates: 512,
+// 6.1, 2048 9.5, 8.3, 3072 13.4, 13.1, 3584 13.0, 14.6; fp16 circular 512, 3072 9.2, 7.8, 4096 9.4, 9.5; bf16 circular 1024, 3072 13.7, 13.3, 3584 13.5, 14.6 (256 channels;
+// 3584 of a pair each 17.5, 16.7 in circular fp32, 13.5, 14.0 in bf16).  Both gates: 512,
 // fp32 6144 18.3, 17.4, 8192 21.1, 22.2, bf16 circular 19.3, 18.0 and 21.4, 22.6; 1024 always, fp32 8192 36.8, 34.1, 32768 160, 156, bf16 circular 8192
 // 40.5, 37.2, fp16 32768 171, 171.  Calls of few rows (k_row_conv_few): 512 bf16 3072 7.9, 7.1, 4096 8.0, 8.2; 1024, 1024 8.0, 6.9, 1536 8.1, 8.9.
-template <int M> constexpr int64_t wide_most(bool gated) { return M == 512 ? (gated ? 6144 : 3072) : gated ? INT64_MAX : 4096; }
+template <int M> constexpr int64_t wide_most(bool gated) { return !gated ? 3072 : M == 512 ? 6144 : INT64_MAX; }
 template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
 
 template <int M, typename IO>

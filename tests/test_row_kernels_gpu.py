@@ -311,6 +311,7 @@ def test_rows_of_small_plans_round_at_the_gates(dtype, H, N, M, shift):
     ("bf16", 2, 3072, 300, 512, 0), ("f16", 2, 3073, 511, 512, 0),
     ("f16", 2, 6144, 64, 512, 3), ("bf16", 1, 6145, 300, 512, 2),
     ("f32", 2, 4096, 65, 1024, 0), ("bf16", 2, 4097, 514, 1024, 0), ("f32", 1, 4500, 300, 1024, 1),
+    ("f32", 2, 3072, 65, 1024, 0), ("f32", 24, 257, 65, 1024, 0), ("bf16", 2, 3073, 514, 1024, 0), ("f16", 48, 128, 511, 1024, 0),
     ("bf16", 2, 3072, 64, 512, 0), ("f16", 2, 3073, 64, 512, 3),         # the same of calls of few rows on a matrix-core plan
     ("bf16", 1, 1024, 512, 1024, 3), ("f16", 2, 1025, 256, 1024, 0),
 ])
