@@ -247,20 +247,30 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
     return FFTCONV_OK;
 }
 
-// WIDE rows (row_fft.h): always at 512 points, at 1024 for a few thousand rows.  us, others, wide (and with fewer runs' sums, see above): fp32 fft 512 1 x 16 10.5, 8.0, 16 x 16 22.9,
-// 11.7, 16 x 1024 32.0, 28.1, 64 x 768 68.8, 62.8, 2 x 4096 27.2, 26.7; fft 1024 1 x 16 11.0, 7.8, 16 x 16 25.4, 14.4, 32 x 256 39.3, 33.7, 16 x 1024 47.4, 49.5, 64 x 768 109, 123, 2 x 4096 22.8, 25.2.
-bool grad_wide(int64_t M, int64_t H, int64_t B) { return M == 512 || (H <= 1024 && H * B <= 8192); }
+// WIDE rows (row_fft.h).  us, others, wide (and with fewer runs' sums, see above): fp32 fft 512 1 x 16 10.5, 8.0, 16 x 16 22.9, 11.7, 16 x 1024 32.0, 28.1, 64 x 768 68.8, 62.8,
+// 2 x 4096 27.2, 26.7; fft 1024 1 x 16 11.0, 7.8, 16 x 16 25.4, 14.4, 32 x 256 39.3, 33.7, 16 x 1024 47.4, 49.5, 64 x 768 109, 123, 2 x 4096 22.8, 25.2.
+// At 512 points for fewer than 65536 fp32 rows or 32768 16-bit ones, or few channels, and for more of fp32 rows beyond M / 2 and of 16-bit ones up to it: from 8192 rows on
+// 0.64 to 1.02 of the others' time (1 x 8192, whole rounds of the others, 1.05); fp32 32 x 4096 x 512 207, 195, 16-bit 64 x 2048 x 256 95, 95, but fp32 64 x 2048 x 256 144, 161,
+// bf16 6 x 8192 x 512 58, 61, 64 x 1024 x 512 82, 84, 32 x 4096 x 512 167, 185; few channels 1024 x 64 x 512 0.80, 4096 x 16 x 512 344, 247.
+template <int M, typename IO, bool HALF> bool grad_wide(int64_t H, int64_t B)
+{
+    if (M == 1024) return H <= 1024 && H * B <= 8192;
+    return HALF == (sizeof(IO) == 2) || H * B < (sizeof(IO) == 4 ? 1 << 16 : 1 << 15) || H <= 128;
+}
+
+template <int M, typename IO, bool HALF>
+int launch_rows(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
+{
+    if constexpr (rf::has_wide(M))
+        if (grad_wide<M, IO, HALF>(p->H, B)) return launch<M, IO, HALF, true>(p, u, dy, dk, Nk, B, workspace, s);
+    return launch<M, IO, HALF, false>(p, u, dy, dk, Nk, B, workspace, s);
+}
 
 template <int M, typename IO>
 int launch_half(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
 {
-    const bool half = p->N <= M / 2;
-    if constexpr (rf::has_wide(M))
-        if (grad_wide(M, p->H, B))
-            return half ? launch<M, IO, true, true>(p, u, dy, dk, Nk, B, workspace, s) : launch<M, IO, false, true>(p, u, dy, dk, Nk, B, workspace, s);
-    if constexpr (M != 512)
-        return half ? launch<M, IO, true, false>(p, u, dy, dk, Nk, B, workspace, s) : launch<M, IO, false, false>(p, u, dy, dk, Nk, B, workspace, s);
-    return FFTCONV_EUNSUPPORTED;                                  // (not reached)
+    return p->N <= M / 2 ? launch_rows<M, IO, true>(p, u, dy, dk, Nk, B, workspace, s)
+                         : launch_rows<M, IO, false>(p, u, dy, dk, Nk, B, workspace, s);
 }
 
 }  // namespace
