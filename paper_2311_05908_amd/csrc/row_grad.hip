@@ -189,7 +189,8 @@ __global__ void __launch_bounds__(256) k_runs_add(const float4 *part, int64_t ap
 
 // From how many runs on that kernel adds them up, and the most pairs of bins that it does so with.  A run costs k_row_dk 0.2 us at 256 points, 0.3 at 512, 0.35 to 4096,
 // 0.75 at 8192, 1.5 at 16384; this kernel 3.5 us and little more (fp32, us: fft 512 16 x 1 rows 10.6, 14.2, 45 x 1 18.2, 14.1; 1024 16 x 1 14.2, 14.2, 45 x 1
-// 24.5, 16.1; 4096 45 x 1 30.9, 18.7; 8192 8 x 16 28.4, 26.6, 4 x 100 33.1, 35.9; 256 40 x 100 25.1, 17.2), unless it waits for memory: 1024, 16 x 256 27.9, 29.5.
+// 24.5, 16.1; 4096 45 x 1 30.9, 18.7; 8192 8 x 16 28.4, 26.6, 4 x 100 33.1, 35.9; 256 40 x 100 25.1, 17.2), unless it waits for memory: 1024, 16 x 256 27.9, 29.5;
+// four runs, which save least, from half of that on: 16384, 4 x 16 39.0 both, 4 x 32 40.3, 43.0.
 template <int M> constexpr int64_t ADD_RUNS = M == 256 ? 21 : M == 512 ? 17 : M <= 4096 ? 13 : M == 8192 ? 7 : 4;
 constexpr int64_t ADD_MOST = (int64_t)1 << 20;
 
@@ -236,7 +237,7 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
     if (sp.S == 1) return FFTCONV_OK;
     int64_t left = sp.S;
     const int64_t apart = p->H * (M / 2);
-    if (sp.S >= ADD_RUNS<M> && sp.S * apart <= ADD_MOST) {
+    if (sp.S >= ADD_RUNS<M> && sp.S * apart <= (sp.S == 4 ? ADD_MOST / 2 : ADD_MOST)) {
         FC_TRY(runs_add(workspace, apart, sp.S, nullptr, workspace, apart, s));
         left = 1;
     }

@@ -338,6 +338,7 @@ def test_rows_on_either_side_of_a_line(dtype, B, H, N, M, gates):
     ("f16", 4, 128, 1024, 2048), ("bf16", 3, 171, 1024, 2048), ("bf16", 1, 3, 2048, 4096), ("f16", 2, 3, 2048, 4096),
     ("f32", 16, 2, 200, 512), ("f32", 17, 2, 512, 512), ("bf16", 47, 1, 301, 512),      # sums of runs by a kernel of their own, or not
     ("f32", 12, 3, 1024, 1024), ("f32", 29, 3, 400, 1024), ("f32", 14, 2, 3000, 4096), ("bf16", 7, 1, 8192, 8192), ("f32", 5, 2, 9001, 16384),
+    ("bf16", 4, 16, 9, 16384), ("f32", 4, 17, 9, 16384),
     ("f32", 8, 1024, 30, 1024), ("f32", 8, 1025, 30, 1024),                             # wide rows of 1024 points and the others
     ("f32", 63, 1040, 20, 512), ("f32", 64, 1024, 20, 512), ("bf16", 63, 520, 257, 512), ("bf16", 64, 512, 257, 512),                                     # of 512
     ("f16", 256, 128, 260, 512), ("bf16", 256, 129, 21, 512),
