@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? (GATED ? 3 : 4) : wa
 // wg multiplies u, bit 1: vg multiplies y).  The transforms and the product with k_f are fp32; u . w is rounded to the I/O type,
 // as is the convolution before it meets the output gate: the same values as without a fused gate, whichever kernel a call
 // takes.  For calls of few rows: see row_forward_few().
-template <int M, typename IO, int GATE, bool WIDE>
+template <int M, typename IO, int GATE, bool WIDE, bool WORDS>
 __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     k_row_conv_few(const IO *__restrict__ u, IO *__restrict__ y, const uint32_t *__restrict__ kf, const float2 *__restrict__ tab,
                    const IO *__restrict__ wg, const IO *__restrict__ vg, int B, int H, int N, int npairs, int total)
@@ -147,10 +147,9 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
     float2 *const Z = (float2 *)((char *)smem_rows + row * G::LDS_BYTES);
     const bool exact = N == M / 2;
-    // The gates as words, in flight with what they multiply; at 256 points, 8 samples a thread, as fp32 one after the other: the masks of the words, which
-    // rows that fill their registers do without, are more there (output gate, 16 x 768 x 128, 6.36 us, words 6.64; fp16 input gate, 2 x 256 x 128, 4.70, 4.95;
-    // bf16 input gates are the faster ones as words, 4.85, 4.68 at 1 x 2048 x 128).
-    constexpr bool WORDS = M > 256, WORDS_IN = WORDS || std::is_same<IO, __hip_bfloat16>::value;
+    // WORDS: the gates as words, in flight with what they multiply.  Otherwise as fp32, one after the other (but bf16 input gates, which are the faster ones
+    // as words).
+    constexpr bool WORDS_IN = WORDS || std::is_same<IO, __hip_bfloat16>::value;
     using Raw = rf::RawPair<G, IO, true>;
     float2 x[G::P], g[G::P];
     Raw rv;
@@ -162,11 +161,11 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
         for (int m = 0; m < Raw::MIN; ++m) x[m] = ru.value(m, N, tid, true, two, rw, true);
     } else {
         rf::load_pair<G, IO, true>(x, u + r0, u + r1, N, tid, exact, true, true, two);
-    }
-    if constexpr ((GATE & 1) && !WORDS_IN) {
-        rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
+        if constexpr (GATE & 1) {
+            rf::load_pair<G, IO, true>(g, wg + r0, wg + r1, N, tid, exact, true, true, two);
 #pragma unroll
-        for (int m = 0; m < G::P / 2; ++m) x[m] = rf::rounded<IO>(x[m].x * g[m].x, x[m].y * g[m].y);
+            for (int m = 0; m < G::P / 2; ++m) x[m] = rf::rounded<IO>(x[m].x * g[m].x, x[m].y * g[m].y);
+        }
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
@@ -329,9 +328,17 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
                 constexpr bool WIDE = decltype(w)::value;
                 using G = Row<M, false, false, WIDE>;
                 constexpr int NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
-                auto kern = wg ? (vg ? k_row_conv_few<M, IO, 3, WIDE> : k_row_conv_few<M, IO, 1, WIDE>)
-                               : (vg ? k_row_conv_few<M, IO, 2, WIDE> : k_row_conv_few<M, IO, 0, WIDE>);
                 const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
+                auto kern = wg ? (vg ? k_row_conv_few<M, IO, 3, WIDE, true> : k_row_conv_few<M, IO, 1, WIDE, true>)
+                               : (vg ? k_row_conv_few<M, IO, 2, WIDE, true> : k_row_conv_few<M, IO, 0, WIDE, true>);
+                // At 256 points, 8 samples a thread, the masks of the words, which rows that fill their registers do without otherwise, are most of what the
+                // loads in flight save.  us, words, not: input gate fp16 2 x 256 x 128 4.77, 4.55, 16 x 768 x 128 6.09, 6.78, 2 x 256 x 64 4.73, 4.88, 16 x 768 x 64 5.80,
+                // 6.72; output gate 2 x 256 x 128 4.74, 4.59, 16 x 768 x 128 6.66, 6.35, 2 x 256 x 64 4.62, 4.86, fp16 24 x 768 x 120 8.70, 8.29, bf16 16 x 768 x 64 6.05, 6.32; both 16 x 768 x 128
+                // 6.62, 6.48, 16 x 768 x 64 6.19, 6.83.
+                if constexpr (M == 256)
+                    if (wg && vg ? p->N == M / 2 : wg ? p->N == M / 2 && total <= 4096 : vg && (p->N == M / 2 || (std::is_same<IO, __half>::value && total > 4096)))
+                        kern = wg ? (vg ? k_row_conv_few<M, IO, 3, WIDE, false> : k_row_conv_few<M, IO, 1, WIDE, false>)
+                                  : k_row_conv_few<M, IO, 2, WIDE, false>;
                 FC_TRY(raise_dynamic_lds((const void *)kern, lds));
                 hipLaunchKernelGGL(kern, dim3((unsigned)((total + RW - 1) / RW)), dim3(NTHR), lds, s, (const IO *)u, (IO *)y,
                                    (const uint32_t *)kf, rf::row_table<G>(p), (const IO *)wg, (const IO *)vg, (int)B, (int)p->H,

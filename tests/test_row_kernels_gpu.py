@@ -267,6 +267,29 @@ def test_few_rows_round_at_the_gates(M, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("H,N", [(3, 120), (4096, 128), (4097, 128), (4096, 120), (4097, 120)])
+def test_few_rows_of_256_round_at_the_gates(H, N, dtype):
+    """As above, on either side of the lines between gates as words and as fp32."""
+    B, M = 2, 256
+    w = synth.scaled(W["cfg1"], B=B, H=H, N=N, fft_size=M, dtype=dtype)
+    u, g, v = synth.gen_u(w), synth.gen_gate(w, "w"), synth.gen_gate(w, "v")
+    plan = fftconv.Plan(N, M, H, dtype)
+    assert plan.path == "fused3" and row_few(M, H, B)
+    taps = torch.zeros(H, N, device="cuda")
+    taps[:, 0], taps[:, M // 4] = 1.0, 91 / 128
+    kf = plan.filter_fft(taps)
+    for wg, vg in ((g, None), (None, v), (g, v)):
+        y = plan.forward_gated(u.cuda(), None if wg is None else wg.cuda(), None if vg is None else vg.cuda(), kf).cpu()
+        p = u if wg is None else u * wg
+        c = p.double()
+        c[..., M // 4:] += 91 / 128 * p[..., : N - M // 4].double()
+        ref = c.to(u.dtype) if vg is None else c.to(u.dtype) * vg
+        differ = (y != ref).float().mean().item()
+        print("gates %s H=%d N=%d w=%d v=%d differ=%.4f" % (dtype, H, N, wg is not None, vg is not None, differ), flush=True)
+        assert differ <= 0.02
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("H,N,M,shift", [
     (3, 256, 256, 0), (3, 256, 256, 1), (5, 191, 256, 0),         # words of two samples; gates that begin off a word, odd rows: sample by sample
     (3, 512, 512, 0), (3, 512, 512, 1), (5, 383, 512, 0), (6200, 512, 512, 0), (6200, 383, 512, 0),       # wide rows, and beyond their line
