@@ -592,11 +592,11 @@ constexpr int B_LDS = RB::LDS_BYTES;
 constexpr int64_t GRAD_TRIP = (int64_t)1 << 28, GRAD_LEAST = (int64_t)1 << 25;
 
 // Four runs or more are added up by k_runs_add (row_grad.hip) first, on every compute unit, and cost less, up to 64 spectra; beyond those the next
-// kernel has that many workgroups of its own to fetch them.  (Where a trip's sums are not transformed back, that kernel is left out, at any number.)  Whole
-// gradient, us, with the other kernel alone: bf16 16 x 1 x 65536 59.7 -> 40.5, 30 x 2 x 131072 105 -> 87, f16 73 x 1 x 20000 fft 65536 97.8 -> 60.9 (64.7 with no
-// more runs than before), fp32 fft 32768, 3 spectra a channel, 4 x 1 x 16384 28.9 -> 26.2, 4 x 16 38.2 -> 37.7, 4 x 20 43.0, 43.4, 8 x 20 61.0 -> 56.5, 4 x 24 43.6, 45.3,
-// 4 x 30 49.1, 52.0, 8 x 42 85, 89; two trips, 32 x 30 244 -> 221.
-constexpr int64_t ADD_RUNS = 4, ADD_MOST = 64;
+// kernel has that many workgroups of its own to fetch them, and six runs are needed.  (Where a trip's sums are not transformed back, that kernel is left
+// out, at any number.)  Whole gradient, us, with the other kernel alone: bf16 16 x 1 x 65536 59.7 -> 40.5, 30 x 2 x 131072 105 -> 87, f16 73 x 1 x 20000 fft 65536
+// 97.8 -> 60.9 (64.7 with no more runs than before), fp32 fft 32768, 3 spectra a channel, 4 x 1 x 16384 28.9 -> 26.2, 4 x 16 38.2 -> 37.7, 4 x 20 43.0, 43.4, 8 x 20 61.0 -> 56.5,
+// 4 x 24 43.6, 45.3, 4 x 30 49.1, 52.0, 8 x 42 85, 89, but six and seven runs 7 x 24 58.1 -> 54.5, 14 x 24 88.7 -> 85.3, 14 x 26 91.7, 91.4; two trips, 32 x 30 244 -> 221.
+constexpr int64_t ADD_RUNS = 4, ADD_MOST = 64, ADD_MANY = 6;
 
 // nh channels of `blocks` blocks each; runs of batch rows where channels alone leave compute units idle: as many as fill the
 // chip (two workgroups to a unit), and no more than pay for adding them up (a run's sum takes about a sixteenth of the time of
@@ -616,7 +616,7 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
                        (int)nb, (int)per, (float4 *)acc, out, tab, first, last);
     FC_HIP(hipGetLastError());
     if (runs == 1) return FFTCONV_OK;
-    if (runs >= ADD_RUNS && (!last || blocks * nh <= ADD_MOST)) {
+    if (runs >= ADD_RUNS && (!last || blocks * nh <= ADD_MOST || runs >= ADD_MANY)) {
         FC_TRY(runs_add(tu, per * stride / 2, runs, first ? nullptr : acc, last ? tu : acc, blocks * nh * (LB / 2), s, LB / 512));
         if (!last) return FFTCONV_OK;
         first = true;

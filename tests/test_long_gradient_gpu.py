@@ -34,6 +34,7 @@ def test_runs_trips_and_pieces(dtype, B, H, N, M):
     ("f16", 73, 1, 200, 65536),          # 37 runs of two, the last one of one: added up eight at a time, the last time four
     ("bf16", 4, 2, 120, 131072),         # four runs, the fewest that are added up by a kernel of their own
     ("f32", 9, 42, 60, 32768),           # four runs of 126 spectra
+    ("f32", 6, 23, 60, 32768), ("f32", 14, 24, 60, 32768),      # six and seven runs of more than 64 spectra
     ("f32", 4, 16, 60, 32768), ("bf16", 11, 8, 60, 65536),               # a multiple of 8 spectra: each added up on its die
     ("f32", 4, 21, 60, 32768), ("f32", 4, 22, 60, 32768),                # on either side of 64 spectra
 ])
