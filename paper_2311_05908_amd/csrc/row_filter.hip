@@ -310,15 +310,17 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
 }
 
 // Runs from which they are added up by a kernel of its own (k_runs_add in row_grad.hip): a run costs the kernel above 1 us and more, that one 3.5 us in
-// all.  us, bf16: fft 8192 16 x 1 rows (8 runs) 23.0, 17.2, 64 x 4 (16) 35.6, 22.3, 16 x 16 (8) 22.6, 21.2, 16 x 40 (6) 24.3, 27.5; 4096 32 x 1 (8) 22.3, 15.3, 64 x 30 (8)
-// 30.8, 25.2, 16 x 16 (4) 16.1, 17.2; 2048 64 x 1 (8) 22.5, 17.5; 1024 200 x 1 (10) 25.3, 19.4.
+// all.  us, bf16: fft 8192 16 x 1 rows (8 runs) 23.0, 17.2, 64 x 4 (16) 35.6, 22.3, 16 x 20 (8) 24.3, 21.4, 16 x 40 (6) 24.3, 27.5; 4096 32 x 1 (8) 22.3, 15.3, 64 x 30 (8)
+// 30.8, 25.2; 2048 64 x 1 (8) 22.5, 17.5; 1024 200 x 1 (10) 25.3, 19.4.  Where channels are a multiple of 8, the workgroups of all runs of one, and the kernel
+// above's, are on one die, whose L2 holds the sums: each is added up there.  Eight runs, the kernel above alone, with sums from any die, from their own: fft 8192 16 x 16
+// 22.2, 20.2, 16.4, 16 x 32 24.9, 24.6, 19.7; 2048 64 x 32 24.4, 25.4, 20.6; 512 256 x 32 22.6, 24.0, 18.9; 256 512 x 32 20.9, 22.1, 17.1.
 constexpr int64_t ADD_RUNS = 8;
 
 // dkf: H * 8192 float2 in the kernels' slot order
 int row_dk_finish(const fftconv_plan *p, void *dkf, int64_t runs, float *dk, int64_t Nk, hipStream_t s)
 {
     if (runs >= ADD_RUNS) {
-        FC_TRY(runs_add(dkf, p->H * (SLOTS / 2), runs, nullptr, dkf, p->H * (SLOTS / 2), s));
+        FC_TRY(runs_add(dkf, p->H * (SLOTS / 2), runs, nullptr, dkf, p->H * (SLOTS / 2), s, SLOTS / 512));
         runs = 1;
     }
     return rf::with_row(p->M, [&](auto g) -> int {

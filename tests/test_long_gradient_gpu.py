@@ -65,6 +65,7 @@ def test_many_runs_are_no_less_precise_than_one(B, M):
     (64, 2, 128, 256), (70, 3, 120, 256),        # two runs of one input each; of an input and a ragged one
     (19, 1, 1000, 4096),                         # four transforms of 4096 points to an input: five inputs, five runs
     (13, 100, 4096, 8192), (6, 1, 4000, 8192),   # two runs, of three and four pairs; a run for every pair, ragged rows
+    (16, 8, 4000, 8192), (256, 24, 200, 512),    # eight runs of a multiple of 8 channels: each channel added up on its die
     (5, 1, 8192, 16384), (27, 60, 5000, 16384),  # runs of one pair, the last without a partner; four runs, of three and four pairs
     (8, 1, 16384, 32768), (7, 90, 2000, 32768),
 ])
