@@ -195,7 +195,9 @@ template <int M> constexpr int64_t ADD_RUNS = M == 256 ? 21 : M == 512 ? 17 : M 
 constexpr int64_t ADD_MOST = (int64_t)1 << 20;
 
 // Runs per channel: as many as give every SIMD of 256 compute units two waves (16 points a thread: four), no more than
-// the batch has rows, of equal length.
+// the batch has rows, of equal length.  At 512 points, where adding up the runs of a few batch rows took longer than their transforms, up to 16 rows and 512
+// channels: a wave to a SIMD, two beyond 256 channels, where few rows of threads would wait for one another's ends.  us, all runs, so: bf16 16 x 128 14.9, 11.8, 12 x 256
+// 16.9, 12.5, 16 x 256 20.9, 14.3, 16 x 512 25.4, 19.1; fp32 16 x 256 20.7, 14.6; errors 1 to 3 % less.  (16 x 384 with a wave to a SIMD 20.4, with two 17.2.)
 // most: the runs that no smaller batch exceeds (4 rows in runs of 1 are more than 5 in runs of 2): what the workspace holds.
 struct Splits { int64_t S, per, most; };
 Splits grad_splits(int64_t M, int64_t H, int64_t B)
@@ -206,6 +208,7 @@ Splits grad_splits(int64_t M, int64_t H, int64_t B)
         want = 256 * 4 * GRAD_WAVES<G::M> * 64 / G::T / H;
         return FFTCONV_OK;
     });
+    if (const int64_t waves = H <= 256 ? 1024 : 2048; M == 512 && H <= 512 && B <= 16 && want * H > waves) want = waves / H;
     if (want > B) want = B;
     if (want < 1) want = 1;
     const int64_t per = (B + want - 1) / want;
@@ -290,14 +293,13 @@ bool row_backward_filter_ok(const fftconv_plan *p) { return p->path != PATH_FUSE
 // to transform it back, and of few at short lengths.  us, matrix cores, rows (bf16): 1 x 16 fft 256 11.5, 8.1, 512 13.4, 8.3, 1024 13.5, 8.4, 2048 15.0, 9.3,
 // 4096 12.3, 9.4, 8192 14.1, 16.8; 1 x 768 25.8, 8.4, 29.5, 8.5, 28.6, 8.4, 35.5, 11.2, 28.0, 15.4; 2 x 64 11.8, 10.9, 13.6, 11.3, 13.8, 11.2, 16.1, 12.5, 12.5, 13.5;
 // 8 x 16 11.5, 10.9, 13.3, 11.2, 13.6, 12.5, 14.9, 14.9; 8 x 64 12.0, 11.2, 13.9, 11.4, 14.1, 13.8; 8 x 256 13.8, 12.0, 15.9, 12.7, 16.1, 20.1; 16 x 16 11.4, 13.3,
-// 13.4, 11.6, 13.5, 13.9; fft 512 from 12 batch rows on, where the other kernel has a round of channels to itself and these a chip full of runs, 12 x 256 17.4, 17.8, 16 x 96 14.7,
-// 15.0, 16 x 256 17.7, 22.0, 16 x 512 25.2, 26.7, but 16 x 64 14.4, 13.5, 16 x 768 31.1, 26.9.  The spectra of their runs, a batch row each at most, fit into the workspace for that kernel's 8192 slots a channel.
+// 13.4, 11.6, 13.5, 13.9; fft 512 16 x 96 13.7, 11.2, 16 x 256 16.2, 14.3, 16 x 512 23.6, 19.1, 16 x 768 31.1, 26.9.  The spectra of their runs, a batch row each at most, fit into the workspace for that kernel's 8192 slots a channel.
 bool row_backward_filter_few(const fftconv_plan *p, int64_t B)
 {
     if (B * p->H > 1 << 20) return false;                         // (far within the limits of a launch)
     switch (p->M) {
     case 256: return B <= 8;
-    case 512: return B <= 11 || (B <= 16 && (p->H <= 64 || p->H > 512));
+    case 512: return B <= 16;
     case 1024: return B == 1 || (B <= 8 && B * p->H <= 512);
     case 2048: return B <= 4 && (B == 1 || B * p->H <= 512);
     case 4096: return B == 1;
