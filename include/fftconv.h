@@ -47,8 +47,11 @@
  *    the "small" family, and calls of few rows on "fused3" plans up to
  *    fft_size 4096, run their transforms in fp32 whatever the I/O type, and
  *    16-bit rows of fft_size 32768 whose length is no multiple of 8 take one
- *    of two kernels by their number: the last bits of a row may depend on how
- *    many rows the call has.  All
+ *    of two kernels by their number; on "multipass" plans the last row of an
+ *    odd batch is transformed with zeros for a partner or as a real row, and
+ *    filter gradients of "fused3" plans run on the matrix cores or in fp32,
+ *    by the number of rows and channels: the last bits of a result may
+ *    depend on how many of them the call has.  All
  *    16-bit roundings are round-to-nearest-even.
  */
 #ifndef FFTCONV_H

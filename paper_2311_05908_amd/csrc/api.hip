@@ -628,7 +628,8 @@ size_t fftconv_workspace_bytes_gated(const fftconv_plan *p, int64_t B)
     if (!p || B <= 0) return 0;
     const size_t base = fftconv_workspace_bytes(p, B);
     if (fused3_gates_fused(p) || p->path == PATH_MULTIPASS) return base;
-    // (the kernels of the other plans fuse the gates too; the room that a gated input took is still asked for, as callers know it)
+    // (the kernels of the other plans fuse the gates too and leave these bytes alone; what is asked for, and refused without it, stays as it
+    // was when a gated input went through them)
     return align256(base) + (size_t)(B * p->H * p->N) * elem_bytes(p);
 }
 

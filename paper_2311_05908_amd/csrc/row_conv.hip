@@ -288,16 +288,19 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
 // matrix-core kernel runs its work items (8192 / fft pairs of rows of one channel, however few there are) in rounds of one per
 // compute unit: 7.0 - 7.9, 10.7, 14.1, 17.2 us for 1, 2, 3, 4 of them (bf16; fp16 with both gates 7.3 - 8.2, 11.5, 16.1, 19).  The row kernel runs workgroups of
 // `rows` pairs.  us, rows, matrix cores (bf16, or fp16 with both gates where two pairs are given):
-//   fft 4096: as many workgroups as one a compute unit for each round: 1 x 64 6.1, 7.3, 1 x 768 9.3, 13.0, 1 x 2048 20.5, 26.6, 1 x 8192 77, 87; half as many again
-//     would still do (4 x 384 9.7, 10.6; 11.3, 11.9), twice as many not (4 x 256 7.8, 7.7; 9.3, 8.2; 3 x 1024 21.4, 17.5);
+//   fft 4096: as many workgroups as one a compute unit for each round: 1 x 64 6.1, 7.3, 1 x 768 9.3, 13.0, 1 x 2048 20.5, 26.6, 1 x 8192 77, 87; twice as many
+//     would be slower (4 x 256 7.8, 7.7; 9.3, 8.2; 3 x 1024 21.4, 17.5);
 //   fft 2048: as many, beyond six rounds half as many: 1 x 512 7.6, 10.2, 3 x 1024 15.9, 16.2, 3 x 2048 28.9, 26.8, 1 x 8192 51, 85 (in the first round
 //     either: 3 x 64 7.6, 7.5, 8 x 128 7.8, 7.2);
-//   fft 1024: half as many, and not in the first round (16 x 16 6.7, 7.0, 16 x 256 8.3, 7.8): 1 x 768 6.7, 12.6, 1 x 8192 17.9, 84.6;
-//   fft 512: half as many, and only if items are not full: 1 x 64 5.2, 7.2, 1 x 2048 5.5, 24.8; 32 x 256 8.0, 7.9 (8.6, 8.2), though 32 x 16 5.5, 6.9;
+//   fft 1024: half as many, and not in the first round (16 x 256 8.3, 7.8): 1 x 768 6.7, 12.6, 1 x 8192 17.9, 84.6;
+//   fft 512: half as many, and only if items are not full: 1 x 64 5.2, 7.2, 1 x 2048 5.5, 24.8; 32 x 256 8.0, 7.9 (8.6, 8.2);
 //   fft 256: 40 Ki pairs + 56 a channel.  B x 768 channels, bf16, matrix cores, rows: B = 64 16.9, 13.0 us, 128 27, 23, 256 42, 40; 8192
 //     channels: B = 33 98, 51, fp16 64 106, 116.
 // (A line that rose without bound at fft 256 sent all calls here: 191 -> 258 us at B = 1365, and gated
 // calls in the first round at fft 2048 took up to 13.0 against 10.0 us.)
+// At 512, 1024 and 4096 these are the lines of a slower row kernel.  Today's would also be the faster one for full items of few rows at 512 (32 x 16 5.5, 6.9),
+// in the first round of few at 1024 (16 x 16 6.7, 7.0) and for half as many workgroups again at 4096 (4 x 384 9.7, 10.6; 11.3, 11.9).  Those calls keep the
+// kernel and the last bits that they have had; tests/test_planner.py holds shapes of either side.
 // At 8192 points the row kernel is not the faster one (16 channels: 8.8 and more against 7.5).
 // The kernel counts rows and threads (at most 64, or M / 16, to a pair of rows) in 32 bits: calls beyond that are not few rows.
 bool row_few(int64_t M, int64_t H, int64_t B)
