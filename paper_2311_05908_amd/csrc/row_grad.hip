@@ -253,20 +253,24 @@ int launch(const fftconv_plan *p, const void *u, const void *dy, float *dk, int6
 
 // WIDE rows (row_fft.h).  us, others, wide (and with fewer runs' sums, see above): fp32 fft 512 1 x 16 10.5, 8.0, 16 x 16 22.9, 11.7, 16 x 1024 32.0, 28.1, 64 x 768 68.8, 62.8,
 // 2 x 4096 27.2, 26.7; fft 1024 1 x 16 11.0, 7.8, 16 x 16 25.4, 14.4, 32 x 256 39.3, 33.7, 16 x 1024 47.4, 49.5, 64 x 768 109, 123, 2 x 4096 22.8, 25.2.
-// At 512 points for fewer than 65536 fp32 rows or 32768 16-bit ones, or few channels, and for more of fp32 rows beyond M / 2 and of 16-bit ones up to it: from 8192 rows on
-// 0.64 to 1.02 of the others' time (1 x 8192, whole rounds of the others, 1.05); fp32 32 x 4096 x 512 207, 195, 16-bit 64 x 2048 x 256 95, 95, but fp32 64 x 2048 x 256 144, 161,
-// bf16 6 x 8192 x 512 58, 61, 64 x 1024 x 512 82, 84, 32 x 4096 x 512 167, 185; few channels 1024 x 64 x 512 0.80, 4096 x 16 x 512 344, 247.
-template <int M, typename IO, bool HALF> bool grad_wide(int64_t H, int64_t B)
+// At 512 points the others only for many rows, fp32 ones up to M / 2 and 16-bit ones beyond, whose channels fill seven eighths of the rounds of 8192 that
+// run at a time (two waves a SIMD): fp32 32 x 4096 x 256 142, 156, 13 x 8192 101.7, 105.7, 16 x 4096 74.7, 73.2, 98 x 2048 x 200 208, 237, but 32 x 5000 251, 192, 8 x 10000 112, 83, 8 x
+// 12288 120, 98; bf16 32 x 4096 x 512 164, 178, 12 x 8192 102, 111, 12 x 4096 65.3, 66.1, but 16 x 7000 138, 134, 8 x 5000 69.8, 54.9, 258 x 256 99.7, 95.1; fp16 17 x 8192 x 401 149, 153, 8 x 8192
+// 77.8, 76.1, 8 x 5000 74.2, 50.9.  Fewer channels, more of their rows: fp32 391 x 256 x 256 122, 115, 516 x 256 160, 167, fp16 516 x 256 x 401 173, 164, 1024 x 64 x 512 0.80, 4096 x 16 x 512 344, 247.
+template <int M, typename IO, bool HALF> bool grad_wide(int64_t H, int64_t B, int64_t N)
 {
     if (M == 1024) return H <= 1024 && H * B <= 8192;
-    return HALF == (sizeof(IO) == 2) || H * B < (sizeof(IO) == 4 ? 1 << 16 : 1 << 15) || H <= 128;
+    constexpr bool WORD = sizeof(IO) == 2;
+    if (HALF == WORD || H <= 128 || H * B < (!WORD ? (H >= 1024 ? 3 << 15 : 1 << 17) : H < 512 ? 3 << 16 : N == M ? 3 << 14 : 1 << 17)) return true;
+    const int64_t rows = H * grad_splits(M, H, B).S, at_once = (rows + 8191) / 8192 * 8192;
+    return 8 * rows < 7 * at_once;
 }
 
 template <int M, typename IO, bool HALF>
 int launch_rows(const fftconv_plan *p, const void *u, const void *dy, float *dk, int64_t Nk, int64_t B, void *workspace, hipStream_t s)
 {
     if constexpr (rf::has_wide(M))
-        if (grad_wide<M, IO, HALF>(p->H, B)) return launch<M, IO, HALF, true>(p, u, dy, dk, Nk, B, workspace, s);
+        if (grad_wide<M, IO, HALF>(p->H, B, p->N)) return launch<M, IO, HALF, true>(p, u, dy, dk, Nk, B, workspace, s);
     return launch<M, IO, HALF, false>(p, u, dy, dk, Nk, B, workspace, s);
 }
 

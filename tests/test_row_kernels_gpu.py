@@ -379,6 +379,20 @@ def test_gradients_of_few_rows(dtype, B, H, N, M):
         assert parity_error(dk.numpy(), ref.numpy(), TOL[dtype], "dk") <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,B,H,N", [
+    ("f32", 24, 4096, 20), ("f32", 23, 4096, 20), ("f32", 20, 5000, 20), ("f32", 128, 1023, 20),         # narrow rows; too few; no whole rounds; few channels
+    ("bf16", 12, 4096, 512), ("f16", 12, 5000, 512), ("f16", 32, 4096, 257), ("bf16", 27, 4900, 257),
+])
+def test_gradients_of_many_rows_of_512(dtype, B, H, N):
+    """Rows in a wave each and narrower ones, on either side of the lines between them."""
+    g = torch.Generator(device="cuda").manual_seed(B + N)
+    u, dy = (torch.randn(B, H, N, generator=g, device="cuda").to(synth.TORCH_DTYPE[dtype]) for _ in range(2))
+    dk = fftconv.Plan(N, 512, H, dtype).backward_filter(u, dy, N)
+    ref = sum(torch.fft.rfft(a.double(), 512).conj() * torch.fft.rfft(b.double(), 512) for a, b in zip(u, dy))
+    ref = torch.fft.irfft(ref, 512)[:, :N]
+    assert parity_error(dk.cpu().double().numpy(), ref.cpu().numpy(), TOL["f32"], "dk") <= TOL["f32"]
+
+
 @pytest.mark.parametrize("H", [200, 256])
 def test_a_gradient_of_fewer_rows_is_no_slower(H):
     """bf16, fft 512: 16 batch rows beside 17, which are too many for the row kernel (16 x 256 took 21.9 us there in runs of a row each, 17 x 256
