@@ -305,16 +305,20 @@ static int filter_fft_impl(const fftconv_plan *p, const float *k, int64_t Nk, co
         const int64_t No = p->M / 8192;
         long_chunk = long_chunk * No / (No / 2 + 1);
     }
-    if (long_rows || long_rows_f32) {                         // as few passes as fit, of about equal size
+    const bool on_load = (long_rows || long_rows_f32) && long_filter_on_load(p, Nk);
+    if (on_load) {
+        rc = long_filter_taps(p, k, Nk, adjoint, keep_dev, n_blocks, k_f, dense_tag, s);
+        if (rc) return rc;
+    } else if (long_rows || long_rows_f32) {                  // as few passes as fit, of about equal size
         const int64_t n = (p->H + long_chunk - 1) / long_chunk;
         long_chunk = (p->H + n - 1) / n;
     }
-    for (int64_t h0 = 0; long_rows && h0 < p->H; h0 += long_chunk) {
+    for (int64_t h0 = 0; long_rows && !on_load && h0 < p->H; h0 += long_chunk) {
         const int64_t nh = p->H - h0 < long_chunk ? p->H - h0 : long_chunk;
         rc = long_filter_transform(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, dense_tag, s);
         if (rc) return rc;
     }
-    for (int64_t h0 = 0; long_rows_f32 && h0 < p->H; h0 += long_chunk) {
+    for (int64_t h0 = 0; long_rows_f32 && !on_load && h0 < p->H; h0 += long_chunk) {
         const int64_t nh = p->H - h0 < long_chunk ? p->H - h0 : long_chunk;
         rc = long_filter_transform_f32(p, k + h0 * Nk, Nk, h0, nh, adjoint, keep_dev, n_blocks, (float2 *)p->filt_a, k_f, s);
         if (rc) return rc;

@@ -174,6 +174,10 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, KfTag tag, hipStream_t s);
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s);
+// the same of all channels from the taps alone, without scratch
+bool long_filter_on_load(const fftconv_plan *p, int64_t Nk);
+int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks, void *kf,
+                     KfTag tag, hipStream_t s);
 FacList long_fft_factor_list(int64_t M);
 // least: what the static workspace was sized for; the pass then goes in smaller trips
 size_t long_forward_workspace_bytes(const fftconv_plan *p, int64_t B, bool least);

@@ -23,6 +23,7 @@
 
 #include "fftconv_internal.h"
 #include "lds_fft.h"
+#include "outer_row.h"
 #include "row_io.h"
 #include "work_index.h"
 
@@ -32,6 +33,7 @@ namespace {
 
 constexpr int LB = 8192;                       // block length: what one workgroup holds in LDS
 constexpr int LT = 512;                        // threads per workgroup
+constexpr int OUTER_MOST = 16;                 // outer length up to which rows are formed on load
 constexpr size_t L_LDS = (size_t)(LB + LB / 16) * sizeof(float2);
 
 struct LongGeo {
@@ -234,11 +236,13 @@ template <typename G> __device__ __forceinline__ void store_row(const float2 (&x
 // now; 2^21 46.6, 50.8, 42.5; 768 channels of fft 32768 151, 134, 110; bf16, 768 channels of fft 65536 230, 163, 157.
 // Workgroups are persistent, two to a compute unit, and fetch the next block ahead of the present one's transform: loads,
 // transforms and stores of workgroups that all start together otherwise take turns on the whole chip.
-template <int KF>
-__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__restrict__ tmp, void *__restrict__ kf,
+// TAPS: src holds the taps themselves, and the rows ko are formed of them on the way in (outer_row.h).  Up to A = 16 nearly all transforms go so: 256 channels of fft
+// 131072 bf16 95 -> 61 us, 768 of 65536 151 -> 95, 768 of 32768 fp32 109 -> 51 (the times above are of rows from memory).
+template <int KF, bool TAPS>
+__global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const void *__restrict__ src, void *__restrict__ kf,
                                                              const float2 *__restrict__ tab, FacList flA, int A, int64_t h0, int blocks,
                                                              const uint8_t *__restrict__ keep, int64_t n_blocks, bool natural,
-                                                             bool conj_out, KfTag kf_tag)
+                                                             bool conj_out, KfTag kf_tag, const float2 *__restrict__ outer, int Nk)
 {
     set_tag(kf_tag);
     using G = std::conditional_t<KF == 2, RX, RB>;
@@ -247,22 +251,40 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const float2 *__res
     const float scale = (KF == 1 ? (float)multipass_kf_boost(true, A) : 1.f) / (float)M, sgn = conj_out ? -1.f : 1.f;
     auto source = [&](int blk) {                              // block blk = channel * (A / 2 + 1) + ko
         const int h = blk / NR, ko = blk % NR;
-        return tmp + (natural ? (int64_t)blk : (int64_t)h * A + lds_pos(ko, flA, A)) * LB;
+        return (const float2 *)src + (natural ? (int64_t)blk : (int64_t)h * A + lds_pos(ko, flA, A)) * LB;
     };
-    float2 next[G::P];
-    load_row<G>(next, source(blockIdx.x), threadIdx.x);
+    using Taps = OuterRow<float, 32>;
+    auto taps = [&](int blk) { return Taps{(const float *)src + (int64_t)(blk / NR) * Nk, Nk}; };
+    // TAPS: a die takes an eighth of the blocks, so that the rows ko of a channel are formed from one L2
+    const int each = TAPS ? (blocks + 7) / 8 : blocks, at0 = TAPS ? blockIdx.x % 8 * each : 0;
+    const int end = at0 + each < blocks ? at0 + each : blocks, step = TAPS ? gridDim.x / 8 : gridDim.x;
+    const int begin = TAPS ? at0 + blockIdx.x / 8 : blockIdx.x;
+    if (begin >= end) return;
+    float2 next[TAPS ? 1 : G::P];
+    Taps::Units word;
+    if constexpr (TAPS) taps(begin).fetch(word, threadIdx.x);
+    else load_row<G>(next, source(begin), threadIdx.x);
 #pragma unroll 1
-    for (int blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+    for (int blk = begin; blk < end; blk += step) {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));                         // nothing of a step's addresses and twiddles is kept for the next
         float2 x[G::P];
-#pragma unroll
-        for (int p = 0; p < G::P; ++p) x[p] = next[p];
-        if (blk + (int)gridDim.x < blocks) load_row<G>(next, source(blk + (int)gridDim.x), tid);
         rf::Tw1<G> tw1;
-        tw1.load(tab, tid);
-        rf::row_barrier<G::T>();                              // the slots are free
-        rf::forward<G, false>(x, XL, tab, tw1, tid, [] {});
+        if constexpr (TAPS) {
+            const int ko = blk % NR;
+            const float2 factor = outer[outer_tab_sums(A) + ko * OUTER_T + tid];
+            taps(blk).sum(x, word, outer + ko * A * OUTER_M, taps(blk + step < end ? blk + step : blk), tid);
+            tw1.load(tab, tid);
+            rf::row_barrier<G::T>();                          // the slots are free
+            rf::forward<G, false>(x, XL, tab, tw1, tid, [] {}, factor);
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) x[p] = next[p];
+            if (blk + step < end) load_row<G>(next, source(blk + step), tid);
+            tw1.load(tab, tid);
+            rf::row_barrier<G::T>();                          // the slots are free
+            rf::forward<G, false>(x, XL, tab, tw1, tid, [] {});
+        }
         const int ko = blk % NR;
         const int64_t h = h0 + blk / NR;
         const bool mirror = ko > 0 && 2 * ko < A;
@@ -396,6 +418,71 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(float2 *tu, const
     store_row<G>(sum, out + base, tid);
 }
 
+// The same from the rows of u and dy themselves (outer_row.h): block (ko, channel) of all batch rows of a run; part: the sums of the
+// runs, `apart` pairs from one to the next, or out of one run, transformed back.
+// ONE: one batch row to a run; no sum is held beside its transforms, and twice the samples are in flight.
+template <typename IO, bool ONE>
+__global__ void __launch_bounds__(RB::T, 2) k_long_rows_corr(const IO *__restrict__ u, const IO *__restrict__ dy, int N, int H, int A, int nb,
+                                                             int per, float2 *__restrict__ part, int64_t apart,
+                                                             const float2 *__restrict__ tab, const float2 *__restrict__ outer)
+{
+    using G = RB;
+    extern __shared__ float2 XL[];
+    // a die takes an eighth of a run's blocks, so that the rows ko of a channel are formed from one L2
+    const int NR = A / 2 + 1, blocks = H * NR, each = (blocks + 7) / 8, blk = blockIdx.x % 8 * each + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= each || blk >= blocks) return;
+    const int h = blk / NR, ko = blk % NR;
+    const int tid = threadIdx.x, b0 = blockIdx.y * per, b1 = min(b0 + per, nb);
+    const bool runs = gridDim.y > 1;
+    const float2 *const sums = outer + ko * A * OUTER_M, *const factors = outer + outer_tab_sums(A) + ko * OUTER_T;
+    using Samples = OuterRow<IO, ONE ? 32 : 16>;
+    auto row = [&](const IO *t, int b) { return Samples{t + ((int64_t)b * H + h) * N, N}; };
+    float2 sum[G::P];
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) sum[p] = make_float2(0.f, 0.f);
+    auto add = [&](int b) {
+        float2 x[G::P], z[G::P];
+        typename Samples::Units word;
+        auto transform = [&](float2 (&v)[G::P], int j) {
+            rf::Tw1<G> tw1;
+            tw1.load(tab, j);
+            const float2 factor = factors[j];
+            rf::row_barrier<G::T>();                          // the slots are free
+            rf::forward<G, false>(v, XL, tab, tw1, j, [] {}, factor);
+        };
+        int j = tid;
+        asm volatile("" : "+v"(j));                           // nothing of a step's addresses and twiddles is kept for the next
+        row(u, b).fetch(word, j);
+        row(u, b).sum(z, word, sums, row(dy, b), j);
+        transform(z, j);
+        asm volatile("" : "+v"(j));
+        row(dy, b).sum(x, word, sums, Samples{dy, 0}, j);
+        transform(x, j);
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) {                      // sum += conj(Z_u) Z_dy
+            sum[p].x = __builtin_fmaf(z[p].y, x[p].y, __builtin_fmaf(z[p].x, x[p].x, sum[p].x));
+            sum[p].y = __builtin_fmaf(-z[p].y, x[p].x, __builtin_fmaf(z[p].x, x[p].y, sum[p].y));
+        }
+    };
+    if constexpr (ONE) {
+        add(b0);
+    } else {
+#pragma unroll 1
+        for (int b = b0; b < b1; ++b) add(b);
+    }
+    float2 *const out = part + (int64_t)blk * LB;
+    if (runs) {
+        float4 *const o = (float4 *)(out + blockIdx.y * apart) + tid;
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) o[q * G::T] = make_float4(sum[2 * q].x, sum[2 * q].y, sum[2 * q + 1].x, sum[2 * q + 1].y);
+        return;
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    rf::inverse<G>(sum, XL, tab, tw1, tid);
+    store_row<G>(sum, out, tid);
+}
+
 // The sums of the runs above, `apart` pairs from one to the next, added up in order; acc, first, last, out as there.
 __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_sum(const float2 *part, int64_t apart, int runs, float4 *acc, float2 *out,
                                                               const float2 *__restrict__ tab, bool first, bool last)
@@ -409,6 +496,8 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_sum(const float2 *part
         float4 v[G::P / 2];
 #pragma unroll
         for (int q = 0; q < G::P / 2; ++q) v[q] = in[q * G::T];
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) asm volatile("" ::"v"(v[q].x));           // all loads of a run together
 #pragma unroll
         for (int q = 0; q < G::P / 2; ++q) {
             x[2 * q].x = set ? v[q].x : x[2 * q].x + v[q].x;
@@ -492,6 +581,48 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_conv_blocks(float2 *__restric
     }
     rf::inverse<G>(x, XL, tab, tw1, tid);
     store_row<G>(x, tmp + base, tid);
+}
+
+// The same from rows of u (outer_row.h), fp32: row i of the `rows` of u belongs to channel (h0 + i) mod H, and its blocks ko <= A/2 go to
+// tmp.  Whole batch rows (nb of them, else nb = 1): a channel's rows one after another, so that its k_f is fetched once.
+template <bool GATED>
+__global__ void __launch_bounds__(RB::T, 2) k_long_conv_rows(const float *__restrict__ u, const float *__restrict__ gate, int N,
+                                                             float2 *__restrict__ tmp,
+                                                             const float4 *__restrict__ kf, const float2 *__restrict__ tab,
+                                                             const float2 *__restrict__ outer, FacList flA, int A, int rows, int nb, int h0,
+                                                             int H)
+{
+    using G = RB;
+    extern __shared__ float2 XL[];
+    const int NR = A / 2 + 1, blocks = rows * NR, each = (blocks + 7) / 8, blk = blockIdx.x % 8 * each + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= each || blk >= blocks) return;
+    const int ko = blk % NR, i = blk / NR, row = i % nb * (rows / nb) + i / nb;
+    const int64_t kbase = ((int64_t)((h0 + row) % H) * A + lds_pos(ko, flA, A)) * LB;
+    const int tid = threadIdx.x;
+    float2 x[G::P];
+    using Samples = OuterRow<float, GATED ? 16 : 32, GATED>;
+    {
+        const Samples from{u + (int64_t)row * N, N, gate + (GATED ? (int64_t)row * N : 0)};
+        typename Samples::Units word;
+        from.fetch(word, tid);
+        from.sum(x, word, outer + ko * A * OUTER_M, Samples{u, 0, gate}, tid);
+    }
+    const float2 factor = outer[outer_tab_sums(A) + ko * OUTER_T + tid];
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    float4 kv[G::P / 2];
+    const float4 *const kr = kf + kbase / 2 + tid;
+    rf::forward<G, false>(x, XL, tab, tw1, tid, [&] {
+#pragma unroll
+        for (int q = 0; q < G::P / 2; ++q) kv[q] = kr[q * G::T];
+    }, factor);
+#pragma unroll
+    for (int q = 0; q < G::P / 2; ++q) {
+        x[2 * q] = rf::mul(x[2 * q], make_float2(kv[q].x, kv[q].y));
+        x[2 * q + 1] = rf::mul(x[2 * q + 1], make_float2(kv[q].z, kv[q].w));
+    }
+    rf::inverse<G>(x, XL, tab, tw1, tid);
+    store_row<G>(x, tmp + ((int64_t)row * NR + ko) * LB, tid);
 }
 
 // Longer rows, last kernel: the outer factors back, real part -> row of y_re, imaginary part -> row of y_im
@@ -581,6 +712,10 @@ int launch_fwd_cols(const LongGeo &g, const In *re, const In *im, float2 *tmp, c
     return FFTCONV_OK;
 }
 
+// outer lengths whose rows the block kernels form themselves
+bool outer_on_load(int64_t A) { return A >= 4 && A <= OUTER_MOST; }
+const float2 *outer_table(const fftconv_plan *p) { return p->long_tw + 2048 + p->M / 2048; }
+
 // rows of the block kernels' launches: their LDS and the plan's table
 constexpr int B_LDS = RB::LDS_BYTES;
 
@@ -629,6 +764,46 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
     return FFTCONV_OK;
 }
 
+// Gradients whose kernel forms its rows itself (outer_row.h): where the chip has enough of them, or a row has few blocks to add up, one after
+// another.  Whole gradient, us, from an outer pass -> so: bf16 2 x 256 x 65536 364 -> 280, 1 x 256 204 -> 169, 2 x 256 x 32768 194 -> 121, f32 2 x 256 x 65536
+// 404 -> 302, 20 x 100 x 16384 431 -> 252, 1 x 1 x 16384 20.1 -> 19.2, bf16 16 x 1 x 65536 39.4 -> 37.7; one row of 65536 samples 23.7 -> 26.2, one of
+// 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  dk of fft 131072 4.33e-7 -> 3.67e-7.
+bool grad_on_load(const fftconv_plan *p, int64_t B)
+{
+    const int64_t A = p->M / LB, n = (p->N + LB - 1) / LB;
+    return outer_on_load(A) && B < INT32_MAX && (n <= 2 || (n <= 8 && B * p->H * (A / 2 + 1) >= 128));
+}
+
+// The same from u and dy (k_long_rows_corr): the inverse transforms' rows of all channels -> out, which holds `fit` rows of A/2 + 1 blocks
+template <typename IO>
+int launch_rows_corr(const fftconv_plan *p, const IO *u, const IO *dy, int64_t nb, float2 *out, int64_t fit, hipStream_t s)
+{
+    const int64_t A = p->M / LB, blocks = p->H * (A / 2 + 1);
+    int64_t runs = 512 / blocks;
+    if (runs > nb) runs = nb;
+    if (runs > fit / p->H) runs = fit / p->H;
+    while (runs > 1 && runs * runs > (runs >= ADD_RUNS ? 64 : 16) * nb) --runs;
+    if (runs < 1) runs = 1;
+    const int64_t per = (nb + runs - 1) / runs, apart = blocks * LB;
+    runs = (nb + per - 1) / per;
+    const float2 *tab = rf::row_table<RB>(p);
+    const auto kern = per == 1 ? k_long_rows_corr<IO, true> : k_long_rows_corr<IO, false>;
+    FC_TRY(raise_dynamic_lds((const void *)kern, B_LDS));
+    hipLaunchKernelGGL(kern, dim3((unsigned)((blocks + 7) / 8 * 8), (unsigned)runs), dim3(RB::T), B_LDS, s, u, dy, (int)p->N,
+                       (int)p->H, (int)A, (int)nb, (int)per, out, apart, tab, outer_table(p));
+    FC_HIP(hipGetLastError());
+    if (runs == 1) return FFTCONV_OK;
+    if (runs >= ADD_RUNS && (blocks <= ADD_MOST || runs >= ADD_MANY)) {
+        FC_TRY(runs_add(out, apart / 2, runs, nullptr, out, blocks * (LB / 2), s, LB / 512));
+        runs = 1;
+    }
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_sum, B_LDS));
+    hipLaunchKernelGGL(k_long_blocks_sum, dim3((unsigned)(A / 2 + 1), (unsigned)p->H), dim3(RB::T), B_LDS, s, out, apart, (int)runs,
+                       (float4 *)nullptr, out, tab, true, true);
+    FC_HIP(hipGetLastError());
+    return FFTCONV_OK;
+}
+
 // Rows of a batch row's channel (A/2 + 1 blocks of 8192 pairs) that the workspace of the real pipeline below holds at most
 int64_t grad_rows(const fftconv_plan *p)
 {
@@ -648,6 +823,10 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         hipLaunchKernelGGL(k_zero_dk, dim3((unsigned)((H * Nk + bs - 1) / bs)), dim3(bs), 0, s, dk, H * Nk);
         FC_HIP(hipGetLastError());
         return FFTCONV_OK;
+    }
+    if (grad_on_load(p, B)) {
+        FC_TRY(launch_rows_corr(p, u, dy, B, (float2 *)workspace, grad_rows(p), s));
+        return multipass_dk_outer_inv(p, workspace, dk, Nk, H, 1.0f / (float)M, s);
     }
     if (multipass_filter_outer_ok(p)) {
         // Outer lengths with a register kernel for real rows (multipass.hip): every row of u and dy is transformed
@@ -704,11 +883,26 @@ template <int KF>
 int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 *tmp, void *kf, int64_t h0, const uint8_t *keep_dev,
               int64_t n_blocks, bool natural, bool conj_out, KfTag tag, hipStream_t s)
 {
-    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF>, B_LDS));
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF, false>, B_LDS));
     const float2 *tab = KF == 2 ? rf::row_table<RX>(p) : rf::row_table<RB>(p);
     const int64_t blocks = nh * (g.A / 2 + 1);                // at most 2^16 channels of 257
-    hipLaunchKernelGGL(k_long_blocks_kf<KF>, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(RB::T), B_LDS, s, tmp, kf, tab, g.flA,
-                       g.A, h0, (int)blocks, keep_dev, n_blocks, natural, conj_out, tag);
+    hipLaunchKernelGGL((k_long_blocks_kf<KF, false>), dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(RB::T), B_LDS, s, tmp, kf, tab,
+                       g.flA, g.A, h0, (int)blocks, keep_dev, n_blocks, natural, conj_out, tag, nullptr, 0);
+    FC_HIP(hipGetLastError());
+    return FFTCONV_OK;
+}
+
+// from the taps themselves (outer_row.h)
+template <int KF>
+int launch_kf_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_out, const uint8_t *keep_dev, int64_t n_blocks, void *kf,
+                   KfTag tag, hipStream_t s)
+{
+    const LongGeo g = long_geo(p->M);
+    FC_TRY(raise_dynamic_lds((const void *)k_long_blocks_kf<KF, true>, B_LDS));
+    const float2 *tab = KF == 2 ? rf::row_table<RX>(p) : rf::row_table<RB>(p);
+    const int64_t blocks = p->H * (g.A / 2 + 1), grid = blocks < 512 ? (blocks + 7) / 8 * 8 : 512;
+    hipLaunchKernelGGL((k_long_blocks_kf<KF, true>), dim3((unsigned)grid), dim3(RB::T), B_LDS, s, k, kf, tab, g.flA, g.A, (int64_t)0,
+                       (int)blocks, keep_dev, n_blocks, true, conj_out, tag, outer_table(p), (int)Nk);
     FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
@@ -716,22 +910,26 @@ int launch_kf(const fftconv_plan *p, const LongGeo &g, int64_t nh, const float2 
 // ---- the forward pass: rows of the whole batch go through the workspace in trips (one pair of batch rows at a time, three launches each,
 // left the chip idle where channels are few: 30 x 1 x 65536 fft 65536 348 -> 28 us, 7 x 2 x 2^19 gated 219 -> 79, 8 x 16 x 131072 fft 2^18
 // 281 -> 169, 16 x 64 x 16384 fft 32768 262 -> 177).
-// Rows one at a time as real sequences (outer pass on the rows ko <= A/2, the blocks of those rows (forward, k_f, inverse), real
+// Rows go one at a time as real sequences (the rows ko <= A/2 of the outer transform, their blocks (forward, k_f, inverse), real
 // inverse outer pass; k_f is the spectrum of real taps, so the product is the spectrum of a real sequence again) where outer
-// lengths have register kernels for real rows (multipass.hip).  That is half the blocks of a complex transform per row, the same as
-// a pair's share, with cheaper outer kernels.  Measured, pairs against real rows, us: faster from A = 32 up (2.8 against 3.3 ms for 2^27
-// samples at fft 2^18), at A = 8 up to 640 rows (64 rows 37.5, 31.4, 512 179, 177, 640 215, 212; 768 272, 279, 1024 364, 371, 2048 688, 752), and at A = 4,
-// where the rows ko <= A/2 are 3 of 4, where their blocks take no more rounds of the chip, two workgroups to a compute unit (8 rows 23.9, 16.8, 128
-// 34.3, 32.4, 320 71.1, 65.5; one round more 192 46.1, 48.6, 256 54.3, 56.1, 512 93.6, 96.4, 1024 177, 186).  A = 16 (8 x 32 x 65536 180, 159) keeps to pairs, as real rows are a tenth less
-// accurate there (3.45e-7, 3.80e-7; A = 8 3.55e-7, 3.51e-7; A = 4 3.29e-7, 3.20e-7).  A row without a partner goes as a real one,
-// or, where the chip has room, with the pairs and zeros for a partner.
-int64_t conv_real_most(int64_t A) { return A >= 32 ? INT64_MAX : A == 8 ? 640 : A == 4 ? 512 : 0; }
-bool conv_real(const fftconv_plan *p, int64_t B)
+// lengths have register kernels for real rows (multipass.hip), else in pairs of batch rows.  Real rows are half the blocks of a complex transform
+// per row (3 for 2 at A = 4), with cheaper outer kernels (2.8 against 3.3 ms for 2^27 samples at fft 2^18); up to A = 16 the blocks' kernel forms its rows ko
+// itself (outer_row.h), for the trip that this saves.  Pairs -> real rows so formed, us, fp32: A = 4, 8 x 256 x 16384 363 -> 299, 4 x 64 51.5 -> 40.4; A = 8,
+// 4 x 256 x 32768 364 -> 274, 2 x 16 26.3 -> 21.0 (real rows from an outer pass before); A = 16, 4 x 256 x 65536 693 -> 542, 2 x 256 x 131072 394 -> 353; errors
+// 3.29e-7 -> 2.79e-7, 3.54e-7 -> 2.98e-7, 3.45e-7 -> 3.15e-7.
+// Rows of more than 8 blocks (4 with an input gate, which doubles the loads) are not formed so by a few workgroups, which add the blocks up one
+// after another (1 x 1 x 131072 19.9 -> 22.2 us; whole rows of few channels, whose filter takes an outer pass too, would also be 3 % less accurate than in pairs; gated 1 x 1 x 65536 19.5 -> 21.3, 4 x 64 200 -> 179), and not those of more than 8 with a gate
+// (2 x 256 x 131072 442 -> 455).  They take an outer pass, at A = 16 in pairs: real rows from an outer pass are a tenth less accurate there (3.45e-7,
+// 3.80e-7); a row without a partner goes as a real one, or, where the chip has room, with the pairs and zeros for a partner.
+bool conv_on_load(const fftconv_plan *p, int64_t B, bool gated)
 {
-    const int64_t A = p->M / LB, H = p->H;
-    if (!multipass_filter_outer_ok(p) || B * H > conv_real_most(A)) return false;
-    auto rounds = [](int64_t blocks) { return (blocks + 511) / 512; };
-    return A != 4 || rounds(3 * B * H) <= rounds(4 * (B / 2 * H)) + rounds(3 * (B % 2 * H));
+    const int64_t A = p->M / LB, n = (p->N + LB - 1) / LB;
+    if (!outer_on_load(A) || (gated && n > 8)) return false;
+    return n <= (gated ? 4 : 8) || (n <= 8 ? B : 1) * p->H * (A / 2 + 1) >= 128;
+}
+bool conv_real(const fftconv_plan *p, int64_t B, bool gated)
+{
+    return multipass_filter_outer_ok(p) && (p->M / LB != 16 || conv_on_load(p, B, gated));
 }
 bool lone_in_pairs(const fftconv_plan *p, int64_t B) { return B > 1 && p->M / LB == 16 && (B + 1) / 2 * p->H * 16 <= 1024; }
 int64_t real_row(const fftconv_plan *p) { return (p->M / LB / 2 + 1) * LB; }
@@ -752,10 +950,9 @@ int64_t conv_pairs(const fftconv_plan *p, int64_t B)
         const int64_t fit = CONV_TRIP / unit < 1 ? 1 : CONV_TRIP / unit;
         return (units < fit ? units : fit) * unit;
     };
-    if (conv_real(p, B)) return pairs(B * p->H, real_row(p));
-    const int64_t n = pairs((B + 1) / 2 * p->H, p->M), most = multipass_filter_outer_ok(p) ? conv_real_most(p->M / LB) : 0;
-    const int64_t few = most ? pairs(most < B * p->H ? most : B * p->H, real_row(p)) : 0;         // a smaller batch that goes as real rows
-    return n > few ? n : few;
+    const int64_t rows = multipass_filter_outer_ok(p) ? pairs(B * p->H, real_row(p)) : 0;
+    const int64_t two = conv_real(p, 1, true) && conv_real(p, 1, false) ? 0 : pairs((B + 1) / 2 * p->H, p->M);       // (at any batch, with gates or without)
+    return rows > two ? rows : two;
 }
 
 // cap: pairs that the workspace holds (at least a row's)
@@ -787,8 +984,17 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
     auto as_real = [&](int64_t row0, int64_t rows) -> int {
         return trips(rows, real_row(p), [&](int64_t first, int64_t n) -> int {
             const int64_t o = (row0 + first) * N;
-            FC_TRY(multipass_filter_outer(p, outer_rows(u + o), FFTCONV_F32, N, n, tmp, s, wg ? wg + o : nullptr));
-            FC_TRY(blocks(g.A / 2 + 1, row0 + first, n, true));
+            if (conv_on_load(p, B, wg != nullptr)) {
+                const auto kern = wg ? k_long_conv_rows<true> : k_long_conv_rows<false>;
+                FC_TRY(raise_dynamic_lds((const void *)kern, B_LDS));
+                hipLaunchKernelGGL(kern, dim3((unsigned)(n * (g.A / 2 + 1) + 7) / 8 * 8), dim3(RB::T), B_LDS, s, (const float *)(u + o),
+                                   (const float *)(wg ? wg + o : nullptr), (int)N, tmp, (const float4 *)kf, rf::row_table<RB>(p),
+                                   outer_table(p), g.flA, g.A, (int)n, n % H ? 1 : (int)(n / H), (int)((row0 + first) % H), (int)H);
+                FC_HIP(hipGetLastError());
+            } else {
+                FC_TRY(multipass_filter_outer(p, outer_rows(u + o), FFTCONV_F32, N, n, tmp, s, wg ? wg + o : nullptr));
+                FC_TRY(blocks(g.A / 2 + 1, row0 + first, n, true));
+            }
             return multipass_dk_outer_inv(p, tmp, (float *)(y + o), N, n, 1.0f, s, vg ? vg + o : nullptr);
         });
     };
@@ -806,7 +1012,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
             return FFTCONV_OK;
         });
     };
-    if (conv_real(p, B)) return as_real(0, B * H);
+    if (conv_real(p, B, wg != nullptr)) return as_real(0, B * H);
     if (lone_in_pairs(p, B)) return as_complex(0, (B + 1) / 2 * H, true);
     if (B > 1) FC_TRY(as_complex(0, B / 2 * H, true));
     if (B % 2 == 0) return FFTCONV_OK;
@@ -822,7 +1028,8 @@ bool long_fft_supported(const fftconv_plan *p) { return p->M >= 2 * LB && p->M <
 int long_fft_init(fftconv_plan *p)
 {
     const int64_t M = p->M, nhi = M / 2048;
-    std::vector<float2> t((size_t)(2048 + nhi));
+    const int A = (int)(M / LB);
+    std::vector<float2> t((size_t)(2048 + nhi + (outer_on_load(A) ? outer_tab_size(A) : 0)));
     const double two_pi = 6.283185307179586476925286766559;
     auto wpow = [&](double num, double den) {
         const double a = two_pi * num / den;
@@ -830,6 +1037,15 @@ int long_fft_init(fftconv_plan *p)
     };
     for (int64_t i = 0; i < 2048; ++i) t[(size_t)i] = wpow((double)i, (double)M);
     for (int64_t i = 0; i < nhi; ++i) t[(size_t)(2048 + i)] = wpow((double)i, (double)nhi);
+    if (outer_on_load(A)) {
+        float2 *to = t.data() + 2048 + nhi;
+        std::vector<float2> w((size_t)(OUTER_M * A));
+        for (int i = 0; i < OUTER_M * A; ++i) w[(size_t)i] = wpow(i, OUTER_M * A);
+        for (int ko = 0; ko <= A / 2; ++ko)
+            for (int i = 0; i < OUTER_M * A; ++i) *to++ = w[(size_t)(ko * i % (OUTER_M * A))];
+        for (int ko = 0; ko <= A / 2; ++ko)
+            for (int j = 0; j < OUTER_T; ++j) *to++ = wpow((double)(ko * j), (double)M);
+    }
     FC_HIP(hipMalloc((void **)&p->long_tw, t.size() * sizeof(float2)));
     FC_HIP(hipMemcpy(p->long_tw, t.data(), t.size() * sizeof(float2), hipMemcpyHostToDevice));
     return FFTCONV_OK;
@@ -860,6 +1076,24 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
 
 // The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block transforms of the
 // rows ko <= A/2, as above.  tmp holds nh * (A/2 + 1) * 8192 float2.  Needs multipass_filter_outer_ok(p).
+int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks, void *kf,
+                     KfTag tag, hipStream_t s)
+{
+    switch (p->dtype) {
+    case FFTCONV_F32: return launch_kf_taps<2>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, KfTag{}, s);
+    case FFTCONV_F16: return launch_kf_taps<1>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
+    default: return launch_kf_taps<0>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
+    }
+}
+// Filters that take it: where few workgroups would add many blocks up, one after another, an outer pass is faster (us, from an outer pass -> so: one channel of 65536
+// taps, fp32 12.2 -> 12.9, bf16 11.8 -> 11.7; of 131072, fft 131072, 12.6 -> 15.2; 10 of 65536 14.6 -> 12.5, 40 of 131072 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61;
+// 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51)
+bool long_filter_on_load(const fftconv_plan *p, int64_t Nk)
+{
+    const int64_t A = p->M / LB, n = (Nk + LB - 1) / LB;
+    return outer_on_load(A) && (n <= 4 || p->H * (A / 2 + 1) >= (n <= 8 ? 40 : 128));
+}
+
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                               const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
 {

@@ -31,6 +31,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dft_reg.h"
 #include "fused3_common.h"
 
@@ -114,7 +116,18 @@ template <int R, bool CONJ> __device__ __forceinline__ void twiddle(float2 (&x)[
         x[k] = CONJ ? mul_conj(x[k], w) : mul(x[k], w);
     }
 }
-// the same, W^k = tab[(k - 1) * stride], at most 16 of them in registers at a time
+// x[k] *= w W^k, k < R: the factor rides on the products of the table's entries
+template <int R> __device__ __forceinline__ void twiddle_times(float2 (&x)[R], const float2 (&t)[tw_count(R, false)], float2 w)
+{
+#pragma unroll
+    for (int a = 0; a < R / 4; ++a) {
+        const float2 wa = a == 0 ? w : mul(t[a + 2], w);
+        x[4 * a] = mul(x[4 * a], wa);
+#pragma unroll
+        for (int b = 1; b < 4; ++b) x[4 * a + b] = mul(x[4 * a + b], mul(wa, t[b - 1]));
+    }
+}
+// x[k] *= W^k, W^k = tab[(k - 1) * stride], at most 16 of them in registers at a time
 template <int R, bool CONJ> __device__ __forceinline__ void twiddle_exact(float2 (&x)[R], const float2 *tab, int stride)
 {
 #pragma unroll
@@ -174,7 +187,19 @@ template <typename G> struct Tw0 {
         if constexpr (G::EXACT) twiddle_exact<G::R0, CONJ>(x, p, G::T);
         else twiddle<G::R0, CONJ>(x, t);
     }
+    // times w, too
+    __device__ __forceinline__ void apply_times(float2 (&x)[G::R0], float2 w) const
+    {
+        if constexpr (G::EXACT) {
+            twiddle_exact<G::R0, false>(x, p, G::T);
+#pragma unroll
+            for (int k = 0; k < G::R0; ++k) x[k] = mul(x[k], w);
+        } else {
+            twiddle_times<G::R0>(x, t, w);
+        }
+    }
 };
+struct NoFactor {};                                           // of forward()
 
 // The exchange of a two-pass row inside one wave: x[k] of column tid <-> x[i * RL + r] of the butterflies of the last pass
 // (FWD: first to last pass), one part at a time.
@@ -203,15 +228,17 @@ template <typename G, int R, bool INV, bool HALFIN = false> __device__ __forcein
 // Forward transform of the row whose samples j + T m the thread j = tid holds in x[m]; Z: the row's Row<M>::SLOTS
 // slots of LDS, free (the caller's barrier lies before).  HALF: x[m] = 0 for m >= R0 / 2.  On return x[p] holds
 // frequency freq(tid, p).  before_last() runs ahead of the last pass (loads that whoever uses the result needs).
-template <typename G, bool HALF, typename F>
+// factor: every sample of the thread is multiplied by it (a float2; rows of three passes).
+template <typename G, bool HALF, typename F, typename W = NoFactor>
 __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const float2 *__restrict__ tab, const Tw1<G> &tw1, int tid,
-                                        F before_last)
+                                        F before_last, W factor = W())
 {
     {
         Tw0<G> t;
         t.load(tab, tid);
         butterfly<G, G::R0, false, HALF>(x);
-        t.template apply<false>(x);
+        if constexpr (std::is_same<W, NoFactor>::value) t.template apply<false>(x);
+        else t.apply_times(x, factor);
     }
     if constexpr (G::SPLIT) {
         before_last();

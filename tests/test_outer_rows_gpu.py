@@ -1,0 +1,41 @@
+"""Transforms beyond 16384 points whose kernels form the rows of the outer factor from the samples themselves (outer_row.h): blocks of 8192
+samples that end early, odd numbers of them, a single one, rows that fill the transform, and calls on either side of the lines to the
+kernels that read them from memory.  Filter transform, convolution, both gates, both gradients against the same in fp64."""
+import pytest
+import torch
+
+from paper_2311_05908_amd import fftconv, synth
+from parity_util import TOL, parity_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("B,H,N,Nk,M", [
+    (3, 11, 8191, 8191, 32768), (2, 9, 8192, 1, 32768), (2, 30, 8193, 8193, 32768),      # one block, two
+    (2, 22, 32767, 32767, 32768), (1, 43, 16385, 100, 32768), (1, 42, 16385, 16384, 32768),    # 129 and 126 blocks: either side of the line
+    (2, 13, 24577, 24577, 65536), (1, 26, 65536, 40000, 65536), (1, 3, 32768, 32768, 65536),   # of half a transform and of a whole one
+    (5, 3, 65535, 65535, 131072), (1, 3, 65536, 65536, 131072),                          # 135 blocks, 27
+    (1, 3, 131071, 131071, 131072), (2, 8, 81919, 8193, 131072),                         # sixteen blocks to a row, ten
+    (17, 1, 100, 100, 131072),                                                           # runs of one batch row; eighths of less than a row's blocks
+])
+def test_rows_formed_on_load(dtype, B, H, N, Nk, M):
+    g = torch.Generator().manual_seed(N + Nk)
+    u, w, v, dy = (torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(4))
+    k = torch.randn(H, Nk, generator=g) / Nk ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype, path="staged" if dtype == "f32" else "multipass")
+    F = lambda x: torch.fft.rfft(x.double(), M)
+    back = lambda X, n: torch.fft.irfft(X, M)[..., :n]
+
+    def check(got, ref, tol, what, weight=None):
+        err = parity_error(got.cpu().double().numpy(), ref.numpy(), tol, what, weight=weight)
+        print("rows formed on load %s %s B=%d H=%d N=%d Nk=%d M=%d err=%.3e" % (what, dtype, B, H, N, Nk, M, err), flush=True)
+        assert err <= tol
+
+    nan = lambda x: torch.full_like(x, float("nan"), device="cuda")
+    kf = plan.filter_fft(k.cuda())
+    check(plan.forward(u.cuda(), kf, out=nan(u)), back(F(u) * F(k), N), TOL[dtype], "y")
+    check(plan.forward_gated(u.cuda(), w.cuda(), v.cuda(), kf, out=nan(u)), v.double() * back(F(u.double() * w.double()) * F(k), N),
+          TOL[dtype], "gated", v.double().numpy())           # (an element's rounding is relative to its gate)
+    check(plan.backward_input(dy.cuda(), plan.filter_fft_adjoint(k.cuda()), out=nan(dy)), back(F(dy) * F(k).conj(), N), TOL[dtype], "du")
+    check(plan.backward_filter(u.cuda(), dy.cuda(), Nk, out=nan(k)), back((F(u).conj() * F(dy)).sum(0), Nk), TOL["f32"], "dk")
