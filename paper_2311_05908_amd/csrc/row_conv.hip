@@ -267,6 +267,7 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     if (M == 16384 || M == 32768) add_length(16384);
     if (M == 512) add(Row<512, false, false, true>()), add(Row<512, true, false, true>());
     if (M == 1024) add(Row<1024, false, false, true>()), add(Row<1024, true, false, true>());
+    if (M > 4096) add(Row<4096>());
     return t;
 }
 

@@ -6,7 +6,7 @@
 // its digits 0, 1, 2), so both ends move slots in runs of 8 or 16 lanes straight between memory and registers.
 // k_f has one 4-byte pair a bin, from which the convolution kernel makes its constants when it turns to a channel.  us, with 8-byte constants
 // in as many copies as the kernel has groups (64 KB a channel) before: filter transform of 768 channels, fft 256 / 1024 / 2048 / 8192
-// 12.5, 13.4, 21.9, 20 -> 7.5, 8.7, 8.8, 17.0; 8000 channels of fft 256 107 -> 8; convolutions of fft 8192, 64 x 768 x 4096 bf16 335 -> 323, f16
+// 12.5, 13.4, 21.9, 20 -> 7.5, 8.7, 8.8, 17.0 (the last one less again, see k_row_filter_8192); 8000 channels of fft 256 107 -> 8; convolutions of fft 8192, 64 x 768 x 4096 bf16 335 -> 323, f16
 // 317 -> 295, 2 x 768 x 4096 20.7 -> 18.5.
 // The gradient of plans below 8192 sums a spectrum for each of G = 8192 / fft_size groups (see build_tables() in fused3.hip): slot
 // k1 of group g is g (32 / G) + k1'.  Up to 1024 points a row is part of one wave and most of the work is adding them up: there a
@@ -71,23 +71,103 @@ __global__ void __launch_bounds__(rf::threads_of(M), 2)
             const float re = x[p].x * sc, im = (conj_out ? -x[p].y : x[p].y) * sc;
             return F16 ? f3::F16::pack(re, im) : f3::BF16::pack(re, im);
         };
-        if constexpr (M == SLOTS) {
-            // slots (k1 * 4 + r) * 64 + 16 (idx / 4) + k2, idx = k3_index(k3), r = idx % 4: lane group q holds k1 = 4 wave + q (+ 16 i),
-            // k2 = its lane, and all k3 = p % 16 in registers; transposed, a store is a whole run of 64 slots
-            const int k1w = tid / 64 * 4;
 #pragma unroll
-            for (int ir = 0; ir < 8; ++ir) {
-                const int i = ir / 4, r = ir % 4;
-                uint32_t a[4];
+        for (int p = 0; p < G::P; ++p) o[rf::slot_of<G>(tid, p)] = constant(p);
+    };
+    if (keep) emit(std::true_type());
+    else emit(std::false_type());
+}
+
+// cos, sin of 2 pi 4 i / 8192
+__device__ constexpr float COS4[8] = {1.f, 0.99999529380957617151f, 0.99998117528260110909f, 0.99995764455196389786f, 0.99992470183914450299f,
+                                      0.99988234745421256111f, 0.99983058179582344007f, 0.99976940535121526662f};
+__device__ constexpr float SIN4[8] = {0.f, 0.00306795676296597627f, 0.00613588464915447527f, 0.00920375478205981934f, 0.01227153828571992608f,
+                                      0.01533920628498810015f, 0.01840672990580482092f, 0.02147408027546950739f};
+
+// The same at 8192 points, where a row is most of a compute unit's registers: the taps are real, so it is transformed as 4096 points z[n] = k[2n] +
+// i k[2n+1], Z goes back to the slots that the last pass read it from, and a lane forms the bins K[f], K[f + 4096] = E +- W_8192^f O of its f < 4096 from
+// 2 E = Z[f] + conj Z[4096 - f] and 2 O = (Z[f] - conj Z[4096 - f]) / i.
+// Half the transform for one more trip through LDS, and four workgroups to a compute unit instead of two; bound by its instructions, and by latency up to a
+// workgroup or two to a unit.  us, rows of 8192 points -> so: 1 / 256 / 300 / 512 / 768 / 3000 channels 6.7, 7.2, 8.3, 9.3, 14.0, 42 -> 6.6, 6.5, 7.7, 8.7,
+// 10.7, 28.5 (with a sine and a cosine for every k1 12.0 and 32.6).
+// Of f = k1 + 32 k2 + 512 k3 the slot is (4 k1 + r) * 64 + 16 q + k2, where k3 = k3_at_index(4 q + r, 16) is 2 r + q / 2 for q = 0, 2 and 15 - (2 r + q / 2) for
+// q = 1, 3: the bins f, f + 4096 of k3 = 2 r + s, s < 2, belong to q = 2 s of run 4 k1 + r and q = 3 - 2 s of run 4 k1 + 3 - r.  A wave takes two
+// such runs, half its lanes the lower bins of either, and writes them whole in two stores.
+template <bool F16, bool HALF>
+__global__ void __launch_bounds__(256, 4)
+    k_row_filter_8192(const float *__restrict__ k, uint32_t *__restrict__ kf, const float2 *__restrict__ tab, int64_t Nk, bool conj_out,
+                      const uint8_t *__restrict__ keep, int64_t n_blocks, KfTag kf_tag)
+{
+    using G = Row<4096>;
+    set_tag(kf_tag);
+    constexpr int M = SLOTS, MIN = HALF ? G::P / 2 : G::P;
+    static_assert(G::R0 == 16 && G::R1 == 16 && G::R2 == 16 && G::T == 256, "digits of a frequency, below");
+    extern __shared__ float2 Z[];
+    const int tid = threadIdx.x;
+    const float *const row = k + blockIdx.x * Nk;
+    {
+        // (taps beyond Nk read tap 0 and are discarded)
+        float2 x[G::P];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[c] = constant(16 * i + k3_at_index(4 * c + r, 16));
-                rf::transpose_groups(a);
+        for (int m = 0; m < MIN; ++m) {
+            const int n = 2 * (tid + G::T * m);
+            x[m].x = row[n < Nk ? n : 0];
+            x[m].y = row[n + 1 < Nk ? n + 1 : 0];
+        }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[((k1w + j + 16 * i) * 4 + r) * 64 + (tid & 63)] = a[j];
+        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(x[m].x), "v"(x[m].y));
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const int n = 2 * (tid + G::T * m);
+            x[m] = make_float2(n < Nk ? x[m].x : 0.f, n + 1 < Nk ? x[m].y : 0.f);
+        }
+        rf::Tw1<G> tw1;
+        tw1.load(tab, tid);
+        rf::forward<G, HALF>(x, Z, tab, tw1, tid, [] {});
+#pragma unroll
+        for (int i = 0; i < G::NBL; ++i) {
+            float2 *const z = Z + G::slotl(tid + G::T * i);
+#pragma unroll
+            for (int r = 0; r < G::RL; ++r) z[r] = x[i * G::RL + r];
+        }
+    }
+    __syncthreads();
+    const int lane = tid & 63, up = lane >> 5, s = lane >> 4 & 1, k2 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t *const o = kf + blockIdx.x * (int64_t)M + k2;
+    const float sgn = conj_out ? -1.f : 1.f;
+    auto emit = [&](auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+#pragma unroll
+        for (int pair = 0; pair < 2; ++pair) {                    // runs r = pair (lanes 0 .. 31) and 3 - pair
+            const int r = up ? 3 - pair : pair, k3 = 2 * r + s, fl = 32 * k2 + 512 * k3;
+            const float rev = (float)(fl + wave) * (1.f / (float)M);          // exact: the sine and cosine take revolutions
+            const float2 wl = make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
+            // digits of f to base 16: d0 = k1 % 16, d1 = k1 / 16 + 2 (k2 % 8), d2 = k2 / 8 + 2 k3
+            const int d1 = 2 * (k2 & 7), d2 = (k2 >> 3) + 2 * k3;
+            const float2 *const za = Z + d1 * G::PAD + d2 + wave * G::PITCH, *const zm = Z + (15 - d1) * G::PAD + 15 - d2 - wave * G::PITCH;
+            const int lo = wave * 256 + r * 64 + 32 * s, hi = wave * 256 + (3 - r) * 64 + 48 - 32 * s;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int top = i / 4, f = wave + 4 * i + fl;
+                // the digits of 4096 - f: complements, plus one from the first that is not zero on
+                const float2 a = za[4 * (i & 3) * G::PITCH + top * G::PAD];
+                const float2 *m = zm + (16 - 4 * (i & 3)) * G::PITCH - top * G::PAD;
+                if ((i & 3) == 0) {
+                    const int e1 = d1 + top;
+                    const float2 *const m0 = Z + ((16 - e1) & 15) * G::PAD + (e1 ? 15 - d2 : (16 - d2) & 15);
+                    m = wave ? m : m0;
+                }
+                const float2 b = *m;
+                const float2 w = i ? rf::mul(wl, make_float2(COS4[i], -SIN4[i])) : wl;
+                const float2 e = make_float2(a.x + b.x, a.y - b.y);
+                const float2 v = rf::mul(make_float2(a.y + b.y, b.x - a.x), w);
+                const float s0 = MASKED ? lds_mask_weight(keep, n_blocks, f, M) * (0.5f / M) : 0.5f / M;
+                const float s1 = MASKED ? lds_mask_weight(keep, n_blocks, f + M / 2, M) * (0.5f / M) : 0.5f / M;
+                auto put = [&](int at, float re, float im) { o[1024 * i + at] = F16 ? f3::F16::pack(re, sgn * im) : f3::BF16::pack(re, sgn * im); };
+                put(lo, (e.x + v.x) * s0, (e.y + v.y) * s0);
+                put(hi, (e.x - v.x) * s1, (e.y - v.y) * s1);
             }
-        } else {
-#pragma unroll
-            for (int p = 0; p < G::P; ++p) o[rf::slot_of<G>(tid, p)] = constant(p);
         }
     };
     if (keep) emit(std::true_type());
@@ -295,6 +375,16 @@ int row_filter(const fftconv_plan *p, const float *k, int64_t Nk, int64_t Ms, bo
         using G = decltype(g);
         if constexpr (G::M > SLOTS) {
             return FFTCONV_EUNSUPPORTED;
+        } else if constexpr (G::M == SLOTS) {
+            using R = Row<4096>;
+            const bool f16 = p->dtype == FFTCONV_F16, half = 2 * Nk <= SLOTS;
+            const auto kern = f16 ? (half ? k_row_filter_8192<true, true> : k_row_filter_8192<true, false>)
+                                  : (half ? k_row_filter_8192<false, true> : k_row_filter_8192<false, false>);
+            FC_TRY(raise_dynamic_lds((const void *)kern, R::LDS_BYTES));
+            hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(R::T), R::LDS_BYTES, s, k, kf, rf::row_table<R>(p), Nk, conj_out, keep_dev,
+                               n_blocks, tag);
+            FC_HIP(hipGetLastError());
+            return FFTCONV_OK;
         } else {
             constexpr int M = G::M, NTHR = rf::threads_of(M), RW = NTHR / G::T, lds = RW * G::LDS_BYTES;
             const bool f16 = p->dtype == FFTCONV_F16, half = 2 * Nk <= M;

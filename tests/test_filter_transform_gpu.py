@@ -26,3 +26,19 @@ def test_filter_lengths(M, dtype):
             err = parity_error(y.numpy(), torch.fft.irfft(U * ref, M)[..., :N].numpy(), TOL[dtype], "Nk=%d" % Nk)
             print("filter %s M=%d Nk=%d err=%.3e" % (dtype, M, Nk, err), flush=True)
             assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_filter_lengths_of_8192(dtype):
+    """The same at fft 8192, with and without a mask of blocks (a bin and its mirror image masked differently count half)."""
+    M, N, H = 8192, 4096, 5
+    test_filter_lengths(M, dtype)
+    g = torch.Generator().manual_seed(7)
+    u, k = torch.randn(2, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]), torch.randn(H, N, generator=g) / N ** 0.5
+    keep = torch.randint(0, 2, (64,), generator=g)
+    mask = keep.repeat_interleave(M // 64).double()
+    weight = (mask + mask[-torch.arange(M) % M]) / 2
+    plan = fftconv.Plan(N, M, H, dtype)
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda(), block_keep=keep.tolist())).cpu().double()
+    ref = torch.fft.ifft(torch.fft.fft(u.double(), M) * torch.fft.fft(k.double(), M) * weight, dim=-1).real[..., :N]
+    assert parity_error(y.numpy(), ref.numpy(), TOL[dtype], "masked") <= TOL[dtype]
