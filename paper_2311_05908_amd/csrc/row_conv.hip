@@ -194,6 +194,102 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
     if (live) rf::store_pair<G, IO, true>(x, y + r0, y + r1, N, tid, exact, true, two);
 }
 
+// The same for calls of one batch row, whose rows have no partners: M / 2 points z[n] = a[2n] + i a[2n+1], a word of samples each (no halves to swap), instead
+// of M with zeros for imaginary parts.  With Z = FFT(z), E and O the spectra of the even and odd samples, W = W_M^f, and K0, K1 the bins f and f + M/2 of
+// k_f, the result's transform is
+//   Z'[f] = Z S + D (W O + i conj(W) E),  S, D = (K0 +- K1) / 2,  2 E = Z[f] + conj Z[M/2 - f],  2 O = (Z[f] - conj Z[M/2 - f]) / i,
+// so that a thread needs the mirror images of its bins only: one trip through LDS more, of half the points, and half the waves.
+// Bound by the latency of a row up to three of them to a compute unit, by its instructions beyond.  us, rows with zeros -> so: both gates, bf16 1 x 768 x 2048 (fft 4096)
+// 10.4 -> 8.3 (the kernel alone 11.1 -> 8.8 traced), 1 x 8192 80 -> 57, 1 x 8192 x 1024 (fft 2048) 56 -> 43.5; without 1 x 768 x 2048 9.4 -> 7.8, 1 x 4096 x 1024
+// 28.8 -> 22.1, 1 x 64 7.3 -> 6.0.  k_f asked for with the samples, ahead of the transform: 9.5 instead of 8.8.
+template <int M> using LoneRow = Row<M / 2, false, false, M / 2 == 1024>;
+template <int M, typename IO, int GATE>
+__global__ void __launch_bounds__(LoneRow<M>::T, 2)
+    k_row_conv_lone(const IO *__restrict__ u, IO *__restrict__ y, const uint32_t *__restrict__ kf, const float2 *__restrict__ tab,
+                    const IO *__restrict__ wg, const IO *__restrict__ vg, int N)
+{
+    using G = LoneRow<M>;
+    static_assert(G::THREE && G::T / G::RL == G::R1, "slots of the mirror images, below");
+    constexpr int MIN = G::P / 2;
+    extern __shared__ float2 Z[];
+    const int tid = threadIdx.x, words = N / 2;
+    const int64_t first = blockIdx.x * (int64_t)words;
+    const uint32_t *const kr = kf + (int64_t)blockIdx.x * M + kernel_slot<M>(G::freq(tid, 0));
+    auto fetch = [&](uint32_t (&w)[MIN], const IO *t) {
+        const uint32_t *const r = (const uint32_t *)t + first;
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            const int n = tid + G::T * m;
+            w[m] = r[n < words ? n : 0];
+        }
+    };
+    float2 x[G::P];
+    {
+        uint32_t a[MIN], g[MIN];
+        fetch(a, u);
+        if constexpr (GATE & 1) fetch(g, wg);
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) asm volatile("" ::"v"(a[m]));       // the loads stay unconditional
+#pragma unroll
+        for (int m = 0; m < MIN; ++m) {
+            uint32_t w = a[m];
+            if constexpr (GATE & 1) w = rf::mul_words<IO>(w, g[m]);
+            x[m] = rf::unpack<IO>(tid + G::T * m < words ? w : 0);
+        }
+    }
+    rf::Tw1<G> tw1;
+    tw1.load(tab, tid);
+    uint32_t k0[G::P], k1[G::P];
+    rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
+#pragma unroll
+        for (int p = 0; p < G::P; ++p) {                          // the digits of a slot depend on the thread alone or the register alone
+            k0[p] = kr[kernel_slot<M>(G::freq(0, p)) - kernel_slot<M>(0)];
+            k1[p] = kr[kernel_slot<M>(G::freq(0, p) + M / 2) - kernel_slot<M>(0)];
+        }
+    });
+#pragma unroll
+    for (int i = 0; i < G::NBL; ++i) {
+        float2 *const z = Z + G::slotl(tid + G::T * i);
+#pragma unroll
+        for (int r = 0; r < G::RL; ++r) z[r] = x[i * G::RL + r];
+    }
+    rf::row_barrier<G::T>();
+    const float rev = (float)G::freq(tid, 0) * (1.f / (float)M);          // exact: the sine and cosine take revolutions
+    const float2 w0 = make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
+    uint32_t v[MIN];
+    if constexpr (GATE & 2) fetch(v, vg);
+    float2 mirror[G::P];
+#pragma unroll
+    for (int i = 0; i < G::NBL; ++i) {
+        // digits of M/2 - f: complements, plus one from the first that is not zero on
+        const int bi = tid + G::T * i, d0 = bi / G::R1, d1 = bi % G::R1;
+        const float2 *const z = Z + (d0 ? (G::R0 - d0) * G::PITCH + (G::R1 - 1 - d1) * G::PAD + G::RL - 1 : d1 ? (G::R1 - d1) * G::PAD + G::RL - 1 : G::RL);
+#pragma unroll
+        for (int r = 0; r < G::RL; ++r) mirror[i * G::RL + r] = *(r == 0 && bi == 0 ? Z : z - r);
+    }
+#pragma unroll
+    for (int p = 0; p < G::P; ++p) {
+        constexpr float TWO_PI = 6.283185307179586f;
+        const float2 z = x[p], m = mirror[p];
+        const float2 w = p ? rf::mul(w0, make_float2(__builtin_cosf(TWO_PI / M * G::freq(0, p)), -__builtin_sinf(TWO_PI / M * G::freq(0, p)))) : w0;
+        const float2 e = make_float2(z.x + m.x, z.y - m.y), o = make_float2(z.y + m.y, m.x - z.x);             // 2 E, 2 O
+        const float2 a = rf::unpack<IO>(k0[p]), b = rf::unpack<IO>(k1[p]);
+        const float2 s = make_float2(a.x + b.x, a.y + b.y), d = make_float2(0.5f * (a.x - b.x), 0.5f * (a.y - b.y));     // (k_f is scaled by 1 / M)
+        const float2 c = rf::mul_conj(e, w), t = rf::mul(o, w);
+        const float2 q = rf::mul(make_float2(t.x - c.y, t.y + c.x), d), h = rf::mul(z, s);
+        x[p] = make_float2(h.x + q.x, h.y + q.y);
+    }
+    rf::row_barrier<G::T>();                                      // the mirror images have been read
+    rf::inverse<G>(x, Z, tab, tw1, tid);
+    uint32_t *const out = (uint32_t *)y + first;
+#pragma unroll
+    for (int m = 0; m < MIN; ++m) {
+        uint32_t w = rf::pack<IO>(x[m].x, x[m].y);
+        if constexpr (GATE & 2) w = rf::mul_words<IO>(w, v[m]);
+        if (tid + G::T * m < words) out[tid + G::T * m] = w;
+    }
+}
+
 template <int M, typename IO, bool HALF, bool GATED, bool WIDE>
 int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
@@ -267,6 +363,8 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     if (M == 16384 || M == 32768) add_length(16384);
     if (M == 512) add(Row<512, false, false, true>()), add(Row<512, true, false, true>());
     if (M == 1024) add(Row<1024, false, false, true>()), add(Row<1024, true, false, true>());
+    if (M == 2048) add(Row<1024, false, false, true>());
+    if (M == 4096) add(Row<2048>());
     if (M > 4096) add(Row<4096>());
     return t;
 }
@@ -327,6 +425,21 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
         if constexpr (M > 4096) {
             return FFTCONV_EUNSUPPORTED;
         } else {
+            auto lone = [&](auto io) -> int {                     // N is even, and rows lie at whole words
+                if constexpr (M >= 2048) {
+                    using IO = decltype(io);
+                    using G = LoneRow<M>;
+                    const auto kern = wg ? (vg ? k_row_conv_lone<M, IO, 3> : k_row_conv_lone<M, IO, 1>)
+                                         : (vg ? k_row_conv_lone<M, IO, 2> : k_row_conv_lone<M, IO, 0>);
+                    FC_TRY(raise_dynamic_lds((const void *)kern, G::LDS_BYTES));
+                    hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), G::LDS_BYTES, s, (const IO *)u, (IO *)y, (const uint32_t *)kf,
+                                       rf::row_table<G>(p), (const IO *)wg, (const IO *)vg, (int)p->N);
+                    FC_HIP(hipGetLastError());
+                }
+                return FFTCONV_OK;
+            };
+            // (one row to a compute unit takes as long either way at 4096 points, whose other kernel has twice the threads for it)
+            if (B == 1 && (M == 2048 || (M == 4096 && p->H > 256))) return p->dtype == FFTCONV_F16 ? lone(__half()) : lone(__hip_bfloat16());
             auto form = [&](auto io, auto w) -> int {
                 using IO = decltype(io);
                 constexpr bool WIDE = decltype(w)::value;

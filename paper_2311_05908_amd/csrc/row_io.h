@@ -287,15 +287,20 @@ template <typename G> __device__ __forceinline__ int slot_of(int tid, int p)
 constexpr bool has_wide(int M) { return M == 512 || M == 1024; }
 
 // The tables of a plan, behind its table of W_M^t: rows of min(M, 8192) points, fast and exact, then those of 16384 where M is
-// that or 32768, and of wide rows where M has them; beyond 4096 points, last, those of fast rows of 4096 (filter transforms of half the length).
+// that or 32768, and of wide rows where M has them; beyond 1024 points, last, those of fast rows of half
+// the length, or of 4096 points (rows of 1024 wide).
 template <typename G> inline const float2 *row_table(const fftconv_plan *p)
 {
     size_t at = G::M == 16384 ? Row<8192, false>::TABLE + Row<8192, true>::TABLE : 0;
-    if (G::M == 4096 && !G::EXACT && p->M > 4096) {
-        at = Row<8192, false>::TABLE + Row<8192, true>::TABLE;
-        if (p->M == 16384 || p->M == 32768) at += Row<16384, false>::TABLE + Row<16384, true>::TABLE;
+    if constexpr (G::WIDE) at = Row<G::M, false>::TABLE + Row<G::M, true>::TABLE;
+    if constexpr (!G::EXACT && (G::M == 4096 || G::M == 2048 || G::WIDE)) {
+        if (G::M < p->M) {
+            if (G::M == 1024) at = Row<2048, false>::TABLE + Row<2048, true>::TABLE;
+            if (G::M == 2048) at = Row<4096, false>::TABLE + Row<4096, true>::TABLE;
+            if (G::M == 4096) at = Row<8192, false>::TABLE + Row<8192, true>::TABLE;
+            if (p->M == 16384 || p->M == 32768) at += Row<16384, false>::TABLE + Row<16384, true>::TABLE;
+        }
     }
-    if (G::WIDE) at = Row<G::M, false>::TABLE + Row<G::M, true>::TABLE;
     return p->row_tw + at + (G::EXACT ? Row<G::M, false, false, G::WIDE>::TABLE : 0);
 }
 

@@ -412,3 +412,24 @@ def test_a_gradient_of_fewer_rows_is_no_slower(H):
             best[B] = min(best[B], t[0].elapsed_time(t[1]) * 20)
     print("dk of 16, 17 x %d x 256: %.1f, %.1f us" % (H, best[16], best[17]), flush=True)
     assert best[16] <= 1.05 * best[17]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("H,N,M", [
+    (1, 8, 2048), (3, 1024, 2048), (70, 1000, 2048), (2, 520, 2048),      # rows of one wave
+    (256, 2048, 4096), (257, 2048, 4096), (300, 8, 4096), (259, 1032, 4096),      # one row to a compute unit, and more
+])
+def test_calls_of_one_batch_row(dtype, H, N, M):
+    """Rows without partners as half as many points, with either gate, both and none, against the same in fp64."""
+    g = torch.Generator().manual_seed(H * N)
+    u, w, v = (torch.randn(1, H, N, generator=g).to(synth.TORCH_DTYPE[dtype]) for _ in range(3))
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype)
+    kf = plan.filter_fft(k.cuda())
+    for a, b in ((None, None), (w, None), (None, v), (w, v)):
+        z = u.double() if a is None else u.double() * a.double()
+        ref = torch.fft.irfft(torch.fft.rfft(z, M) * torch.fft.rfft(k.double(), M), M)[..., :N] * (1 if b is None else b.double())
+        y = plan.forward_gated(u.cuda(), None if a is None else a.cuda(), None if b is None else b.cuda(), kf,
+                               out=torch.full_like(u, float("nan"), device="cuda"))
+        err = parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "y", None if b is None else b.double().numpy())
+        assert err <= TOL[dtype], (err, a is None, b is None)
