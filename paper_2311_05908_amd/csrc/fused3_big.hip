@@ -1024,6 +1024,8 @@ __global__ void k_big_dk_last(const float2 *__restrict__ tmp, float *__restrict_
 // Bound by the instructions of that loop and the transform's latency, with one workgroup (two at N2 = 16) on a compute unit.  us, with
 // every factor a trip through LDS, gathered twiddles and digits taken apart for every bin, before: fft 32768, 1 / 256 / 768 channels
 // 44, 59, 165 -> 17, 22, 57; fft 16384 25, 30, 74 -> 14, 16, 32.
+// With a wave's tile and r fixed, so that only k1 varies in its loop, with constants for its twiddles: 1 / 256 / 768 channels, fft 16384 10.8, 13.0, 26.5 -> 8.9,
+// 10.9, 22.9; fft 32768 14.2, 18.6, 50.4 -> 12.9, 17.6, 47.8 (of another clock than the figures above).
 // HALF: Nk <= M / 2.
 template <int N2> using FilterRow = rf::Row<BigGeo<N2>::M / 2>;
 template <typename TT, int N2, bool HALF>
@@ -1069,35 +1071,46 @@ __global__ void __launch_bounds__(FilterRow<N2>::T, 2) k_filter_big(const float 
         }
     }
     __syncthreads();
-    // a wave takes whole groups (k1, k2 tile, r): lane = 16 q + c, k2 = big_tau(16 tile + c), k3 = 4 q + r and that + 16
+    // a wave takes one k2 tile and r, and all k1: lane = 16 q + c, k2 = big_tau(16 tile + c), k3 = 4 q + r and that + 16
     const int lane = tid & 63, q = lane >> 4, c16 = lane & 15;
-    typename TT::CW *const out = kf + h * BM + lane;
-    constexpr int GROUPS = 32 * R2 * 4, WAVES = G::T / 64;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-#pragma unroll 4
-    for (int i = 0; i < GROUPS / WAVES; ++i) {
-        const int g = i * WAVES + w;
-        const int r = g & 3, t2 = (g >> 2) & (R2 - 1), k1 = g / (4 * R2);
-        const int k2 = big_tau<N2>(16 * t2 + c16), k3 = 4 * q + r, f = k1 + 32 * k2 + 32 * N2 * k3;
-        // digits of M/2 - f: complements, plus one from the first digit that is not zero on
-        const bool z1 = k1 == 0, z2 = z1 && k2 == 0;
-        const int m1 = (32 - k1) & 31, m2 = z1 ? (N2 - k2) & (N2 - 1) : N2 - 1 - k2, m3 = z2 ? (16 - k3) & 15 : 15 - k3;
-        const float2 za = ZF[k1 * G::PITCH + k2 * G::PAD + k3], zc = ZF[m1 * G::PITCH + m2 * G::PAD + m3];
-        const float rev = (float)f * (1.f / (float)BM);                        // exact: the sine and cosine take revolutions
-        const float2 tw = make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
-        const float2 e = make_float2(0.5f * (za.x + zc.x), 0.5f * (za.y - zc.y));
-        const float2 o = make_float2(0.5f * (za.y + zc.y), -0.5f * (za.x - zc.x));      // (za - conj zc) / (2i)
-        const float2 v = cmul(o, tw);
-        const float s0 = lds_mask_weight(keep, n_blocks, f, BM) * scale, s1 = lds_mask_weight(keep, n_blocks, f + MH, BM) * scale;
-        const float sgn = conj_out ? -1.f : 1.f;
-        const uint32_t lo = TT::pack((e.x + v.x) * s0, sgn * (e.y + v.y) * s0);         // k3: (re, im) 16-bit pairs
-        const uint32_t hi = TT::pack((e.x - v.x) * s1, sgn * (e.y - v.y) * s1);         // k3 + 16
-        const uint32_t own = q < 2 ? lo : hi;
-        const uint32_t far = (uint32_t)__shfl_xor((int)(q < 2 ? hi : lo), 32, 64);
-        typename TT::CW *const dst = out + (k1 * R2 + t2) * 512 + r * 64;
-        dst[0] = TT::cconst(own & 0xffffu, own >> 16, true);                   // the kernel forms conj(A3 * k_f)
-        dst[256] = TT::cconst(far & 0xffffu, far >> 16, true);
-    }
+    static_assert(G::T / 64 == 4 * R2, "a tile and an r to a wave");
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), r = w & 3, t2 = w >> 2;
+    const int k2 = big_tau<N2>(16 * t2 + c16), k3 = 4 * q + r, fl = 32 * k2 + 32 * N2 * k3;
+    // digits of M/2 - f: complements, plus one from the first digit that is not zero on (k1 = 0: m0)
+    const float2 *const za = ZF + k2 * G::PAD + k3, *const zm = ZF + (N2 - 1 - k2) * G::PAD + 15 - k3;
+    const float2 *const m0 = ZF + ((N2 - k2) & (N2 - 1)) * G::PAD + (k2 == 0 ? (16 - k3) & 15 : 15 - k3);
+    // the upper half of the lanes holds k3 of tile 1 where the lower one holds those of tile 0, and the other way round, once they have swapped
+    typename TT::CW *const dst = kf + h * BM + t2 * 512 + r * 64 + lane;
+    const int at0 = lane < 32 ? 0 : 256, at1 = 256 - at0;
+    const float sgn = conj_out ? -1.f : 1.f;
+    auto emit = [&](auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+#pragma unroll 1
+        for (int k8 = 0; k8 < 32; k8 += 8) {
+            const float rev = (float)(fl + k8) * (1.f / (float)BM);                // exact: the sine and cosine take revolutions
+            const float2 wl = make_float2(__builtin_amdgcn_cosf(rev), -__builtin_amdgcn_sinf(rev));
+            const float2 *const a8 = za + k8 * G::PITCH, *const m8 = zm - k8 * G::PITCH;
+            typename TT::CW *const d8 = dst + k8 * R2 * 512;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                constexpr double STEP = 6.283185307179586476925286766559 / BM;
+                const float2 a = a8[i * G::PITCH], b = *(i == 0 && k8 == 0 ? m0 : m8 + (32 - i) * G::PITCH);
+                const float2 tw = i ? rf::mul(wl, make_float2((float)__builtin_cos(STEP * i), (float)-__builtin_sin(STEP * i))) : wl;
+                const float2 e = make_float2(a.x + b.x, a.y - b.y);                 // 2 E, and 2 O = (Z - conj Zm) / i
+                const float2 v = rf::mul(make_float2(a.y + b.y, b.x - a.x), tw);
+                const int f = k8 + i + fl;
+                const float s0 = MASKED ? lds_mask_weight(keep, n_blocks, f, BM) * (0.5f * scale) : 0.5f * scale;
+                const float s1 = MASKED ? lds_mask_weight(keep, n_blocks, f + MH, BM) * (0.5f * scale) : 0.5f * scale;
+                const uint32_t lo = TT::pack((e.x + v.x) * s0, sgn * (e.y + v.y) * s0);         // k3: (re, im) 16-bit pairs
+                const uint32_t hi = TT::pack((e.x - v.x) * s1, sgn * (e.y - v.y) * s1);         // k3 + 16
+                const auto t = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+                d8[i * R2 * 512 + at0] = TT::cconst(t[0] & 0xffffu, t[0] >> 16, true);          // the kernel forms conj(A3 * k_f)
+                d8[i * R2 * 512 + at1] = TT::cconst(t[1] & 0xffffu, t[1] >> 16, true);
+            }
+        }
+    };
+    if (keep) emit(std::true_type());
+    else emit(std::false_type());
 }
 
 // ---------------------------------------------------------------- host side
