@@ -126,6 +126,36 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? (GATED ? 3 : 4) : wa
     }
 }
 
+// The same without gates, one pair of rows to a workgroup of rows of four passes (row_fft.h), for calls of few pairs.
+template <int M, typename IO, bool HALF>
+__global__ void __launch_bounds__(rf::Quad<M>::T)
+    k_row_conv_quad(const IO *__restrict__ u, IO *__restrict__ y, const float2 *__restrict__ kf, const float2 *__restrict__ tab, int B,
+                    int H, int N, int npairs, int total, int per_die)
+{
+    using Q = rf::Quad<M>;
+    using G0 = ConvRow<M, IO>;
+    extern __shared__ float2 smem_rows[];
+    const int tid = threadIdx.x, t = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
+    if (t >= total) return;
+    const int h = t / npairs, pair = t - h * npairs;
+    const bool two = 2 * pair + 1 < B;
+    const int64_t r0 = ((int64_t)(2 * pair) * H + h) * N, r1 = two ? r0 + (int64_t)H * N : r0;
+    const bool exact = N == (HALF ? M / 2 : M), words = rf::word_rows<IO>(u, y, N);
+    rf::QuadTw<Q> tw;
+    tw.load(tab, tid);
+    float2 x[Q::P], kv[Q::P];
+    rf::load_pair<Q, IO, HALF>(x, u + r0, u + r1, N, tid, exact, words, true, two);
+    const float2 *const kr = kf + (int64_t)h * M + G0::index(Q::freq(tid, 0));          // (in the order of the other rows' registers)
+#pragma unroll
+    for (int p = 0; p < Q::P; ++p) kv[p] = kr[G0::index(Q::freq(0, p))];
+    const rf::QuadSlots<Q> z(smem_rows, tid);
+    rf::quad_forward<Q, HALF>(x, z, tw);
+#pragma unroll
+    for (int p = 0; p < Q::P; ++p) x[p] = rf::mul(x[p], kv[p]);
+    rf::quad_inverse<Q>(x, z, tw);
+    rf::store_pair<Q, IO, HALF>(x, y + r0, y + r1, N, tid, exact, words, two);
+}
+
 // The same convolution for the plans of the matrix-core kernels (16-bit I/O, N <= fft/2 a multiple of 8, 16-byte aligned rows),
 // with their k_f: 16-bit (re, im) pairs in the slot order of those kernels (kernel_slot), and with their gates (GATE bit 0:
 // wg multiplies u, bit 1: vg multiplies y).  The transforms and the product with k_f are fp32; u . w is rounded to the I/O type,
@@ -325,6 +355,12 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 template <int M> constexpr int64_t wide_most(bool gated) { return !gated ? 3072 : M == 512 ? 6144 : INT64_MAX; }
 template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
 
+// Pairs of rows up to which they take four passes, without gates.  fp32 rows of 2048 points do at any number of pairs (that a launch holds), the others while
+// they have a compute unit each, or two of them one.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
+// 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0; fft 4096 fp32
+// 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7.
+template <int M, typename IO> constexpr int64_t QUAD_MOST = M == 4096 ? 256 : sizeof(IO) == 4 ? INT32_MAX / 512 : 512;
+
 template <int M, typename IO>
 int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
 {
@@ -333,6 +369,19 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
         if (p->H * ((B + 1) / 2) <= wide_most<M>(gated)) {
             if (gated) return half ? launch<M, IO, true, true, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true, true>(p, u, kf, y, B, wg, vg, s);
             return half ? launch<M, IO, true, false, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, true>(p, u, kf, y, B, wg, vg, s);
+        }
+    }
+    if constexpr (rf::has_quad(M)) {
+        const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
+        if (!gated && total <= QUAD_MOST<M, IO>) {
+            using Q = rf::Quad<M>;
+            const auto kern = half ? k_row_conv_quad<M, IO, true> : k_row_conv_quad<M, IO, false>;
+            FC_TRY(raise_dynamic_lds((const void *)kern, Q::LDS_BYTES));
+            const int64_t per_die = (total + 7) / 8;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_die)), dim3(Q::T), Q::LDS_BYTES, s, (const IO *)u, (IO *)y, (const float2 *)kf,
+                               rf::quad_table<M>(p), (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
+            FC_HIP(hipGetLastError());
+            return FFTCONV_OK;
         }
     }
     if constexpr (M != 1024)
@@ -366,6 +415,13 @@ std::vector<float2> row_tables(int64_t M, const double2 *w)
     if (M == 2048) add(Row<1024, false, false, true>());
     if (M == 4096) add(Row<2048>());
     if (M > 4096) add(Row<4096>());
+    auto add_quad = [&](auto q) {
+        using Q = decltype(q);
+        t.resize(t.size() + Q::TABLE);
+        rf::fill_quad_table<Q>(t.data() + t.size() - Q::TABLE, [&](int num, int den) { return w[num * (M / den)]; });
+    };
+    if (M == 2048) add_quad(rf::Quad<2048>());
+    if (M == 4096) add_quad(rf::Quad<4096>());
     return t;
 }
 

@@ -338,6 +338,125 @@ __device__ __forceinline__ void inverse(float2 (&x)[G::P], float2 *Z, const floa
     butterfly<G, G::R0, true>(x);
 }
 
+// Rows of 2048 and 4096 points for calls of few: 8 points a thread, four passes (8 . 8 . 8 . 4 and 8 . 8 . 8 . 8), exact twiddles.  As with wide rows above, the
+// instructions of a thread one after the other are the time there, and half as many of them are worth a trip through LDS more each way.  Position p < M
+// lies in slot p + p / 8.  Only the first exchange is between waves: the blocks of 8 S1 positions that pass 1 works in, and those of 8 S2 of
+// pass 2, belong to as many threads one after another, S1 <= 64 of them.  Frequency f = k0 + 8 k1 + 64 k2 + 512 k3.
+template <int M_> struct Quad {
+    static constexpr int M = M_, P = 8, R0 = 8, T = M / 8, S1 = T / 8, S2 = S1 / 8, R3 = S2, NB3 = P / R3;
+    static_assert(S1 <= 64 && (R3 == 4 || R3 == 8), "2048 or 4096 points");
+    static constexpr int TABLE = 7 * (T + S1 + S2), SLOTS = M + M / 8, LDS_BYTES = 8 * SLOTS;
+    static __host__ __device__ __forceinline__ int freq(int tid, int p)
+    {
+        const int b = tid * NB3 + p / R3;
+        return b / 64 + 8 * (b / 8 % 8) + 64 * (b % 8) + 512 * (p % R3);
+    }
+};
+// x[k] *= tab[(k - 1) * stride], 0 < k < 8 (CONJ: its conjugate)
+template <bool CONJ> __device__ __forceinline__ void twiddle8(float2 (&x)[8], const float2 (&t)[7])
+{
+#pragma unroll
+    for (int k = 1; k < 8; ++k) x[k] = CONJ ? mul_conj(x[k], t[k - 1]) : mul(x[k], t[k - 1]);
+}
+// The twiddles of a thread's three passes, asked for together
+template <typename Q> struct QuadTw {
+    float2 t0[7], t1[7], t2[7];
+    __device__ __forceinline__ void load(const float2 *__restrict__ tab, int tid)
+    {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) t0[k] = tab[k * Q::T + tid];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) t1[k] = tab[7 * Q::T + k * Q::S1 + tid % Q::S1];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) t2[k] = tab[7 * (Q::T + Q::S1) + k * Q::S2 + tid % Q::S2];
+    }
+};
+template <typename Q> struct QuadSlots {                          // first slots of a thread in passes 0 .. 3
+    float2 *z0, *z1, *z2, *z3;
+    __device__ __forceinline__ QuadSlots(float2 *Z, int tid)
+        : z0(Z + tid + tid / 8), z1(Z + 9 * Q::S1 * (tid / Q::S1) + tid % Q::S1 + tid % Q::S1 / 8),
+          z2(Z + 9 * Q::S2 * (tid / Q::S2) + tid % Q::S2), z3(Z + 9 * tid) {}
+    static constexpr int at(int stride, int m) { return stride * m + stride * m / 8; }
+};
+// forward() and inverse() of such rows
+template <typename Q, bool HALF> __device__ __forceinline__ void quad_forward(float2 (&x)[8], const QuadSlots<Q> &z, const QuadTw<Q> &tw)
+{
+    using S = QuadSlots<Q>;
+    dft_reg<8, false, HALF>(x);
+    twiddle8<false>(x, tw.t0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) z.z0[S::at(Q::T, k)] = x[k];
+    row_barrier<Q::T>();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = z.z1[S::at(Q::S1, m)];
+    dft_reg<8, false>(x);
+    twiddle8<false>(x, tw.t1);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) z.z1[S::at(Q::S1, k)] = x[k];
+    row_barrier<64>();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = z.z2[S::at(Q::S2, m)];
+    dft_reg<8, false>(x);
+    twiddle8<false>(x, tw.t2);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) z.z2[S::at(Q::S2, k)] = x[k];
+    row_barrier<64>();
+#pragma unroll
+    for (int i = 0; i < Q::NB3; ++i) {
+        float2 v[Q::R3];
+#pragma unroll
+        for (int r = 0; r < Q::R3; ++r) v[r] = z.z3[i * Q::R3 + r];
+        dft_reg<Q::R3, false>(v);
+#pragma unroll
+        for (int r = 0; r < Q::R3; ++r) x[i * Q::R3 + r] = v[r];
+    }
+}
+template <typename Q> __device__ __forceinline__ void quad_inverse(float2 (&x)[8], const QuadSlots<Q> &z, const QuadTw<Q> &tw)
+{
+    using S = QuadSlots<Q>;
+#pragma unroll
+    for (int i = 0; i < Q::NB3; ++i) {
+        float2 v[Q::R3];
+#pragma unroll
+        for (int r = 0; r < Q::R3; ++r) v[r] = x[i * Q::R3 + r];
+        dft_reg<Q::R3, true>(v);
+#pragma unroll
+        for (int r = 0; r < Q::R3; ++r) z.z3[i * Q::R3 + r] = v[r];
+    }
+    row_barrier<64>();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = z.z2[S::at(Q::S2, k)];
+    twiddle8<true>(x, tw.t2);
+    dft_reg<8, true>(x);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) z.z2[S::at(Q::S2, m)] = x[m];
+    row_barrier<64>();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = z.z1[S::at(Q::S1, k)];
+    twiddle8<true>(x, tw.t1);
+    dft_reg<8, true>(x);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) z.z1[S::at(Q::S1, m)] = x[m];
+    row_barrier<Q::T>();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = z.z0[S::at(Q::T, k)];
+    twiddle8<true>(x, tw.t0);
+    dft_reg<8, true>(x);
+}
+template <typename Q, typename W> inline void fill_quad_table(float2 *tab, W w)
+{
+    auto put = [&](int k, int j, int den) {
+        const double2 v = w(k * j % den, den);
+        *tab++ = make_float2((float)v.x, (float)v.y);
+    };
+    for (int k = 1; k < 8; ++k)
+        for (int j = 0; j < Q::T; ++j) put(k, j, Q::M);
+    for (int k = 1; k < 8; ++k)
+        for (int j = 0; j < Q::S1; ++j) put(k, j, Q::T);
+    for (int k = 1; k < 8; ++k)
+        for (int j = 0; j < Q::S2; ++j) put(k, j, Q::S1);
+}
+
 // Host side: the twiddle table of Row<M>, rounded once; w(num, den) = exp(-2 pi i num / den) in fp64, num < den.
 template <typename G, typename W> inline void fill_table(float2 *tab, W w)
 {

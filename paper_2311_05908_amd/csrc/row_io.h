@@ -283,6 +283,14 @@ template <typename G> __device__ __forceinline__ int slot_of(int tid, int p)
     else return kernel_slot<G::M>(G::freq(tid, 0)) + (kernel_slot<G::M>(G::freq(0, p)) - kernel_slot<G::M>(G::freq(0, 0)));
 }
 
+// lengths with rows of four passes, and their table, behind all others
+constexpr bool has_quad(int M) { return M == 2048 || M == 4096; }
+template <int M> inline const float2 *quad_table(const fftconv_plan *p)
+{
+    constexpr int HALF = M == 2048 ? Row<1024, false, false, true>::TABLE : Row<2048>::TABLE;
+    return p->row_tw + Row<M, false>::TABLE + Row<M, true>::TABLE + HALF;
+}
+
 // lengths with WIDE rows
 constexpr bool has_wide(int M) { return M == 512 || M == 1024; }
 

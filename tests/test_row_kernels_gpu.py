@@ -433,3 +433,20 @@ def test_calls_of_one_batch_row(dtype, H, N, M):
                                out=torch.full_like(u, float("nan"), device="cuda"))
         err = parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "y", None if b is None else b.double().numpy())
         assert err <= TOL[dtype], (err, a is None, b is None)
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M", [
+    ("f32", 1, 1, 1, 2048), ("f32", 3, 5, 1023, 2048), ("f32", 2, 9, 1024, 2048), ("f32", 2, 7, 1025, 2048), ("f32", 4, 700, 2048, 2048),
+    ("bf16", 3, 5, 2047, 2048), ("f16", 2, 512, 1100, 2048), ("f16", 2, 513, 1100, 2048),          # pairs on either side of the line
+    ("f32", 3, 5, 2047, 4096), ("f32", 2, 256, 2048, 4096), ("f32", 2, 257, 2048, 4096), ("bf16", 2, 3, 4095, 4096), ("f16", 5, 20, 4096, 4096),
+])
+def test_rows_of_four_passes(dtype, B, H, N, M):
+    g = torch.Generator().manual_seed(B * H + N)
+    u = torch.randn(B, H, N, generator=g).to(synth.TORCH_DTYPE[dtype])
+    k = torch.randn(H, N, generator=g) / N ** 0.5
+    plan = fftconv.Plan(N, M, H, dtype, path="small")
+    y = plan.forward(u.cuda(), plan.filter_fft(k.cuda()), out=torch.full_like(u, float("nan"), device="cuda"))
+    ref = torch.fft.irfft(torch.fft.rfft(u.double(), M) * torch.fft.rfft(k.double(), M), M)[..., :N]
+    err = parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "y")
+    print("four passes %s B=%d H=%d N=%d M=%d err=%.3e" % (dtype, B, H, N, M, err), flush=True)
+    assert err <= TOL[dtype]
