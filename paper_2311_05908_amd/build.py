@@ -14,6 +14,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -63,8 +64,28 @@ def _compile(hipcc, src, obj, extra, verbose):
     return obj
 
 
+def fastcall_path() -> str:
+    return os.path.join(HERE, "_fastcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+
+
+def build_fastcall(force: bool = False, verbose: bool = False):
+    """The binding's own extension (csrc/fastcall.c); None where this Python has no headers: the binding then calls through ctypes."""
+    src, out, include = os.path.join(CSRC, "fastcall.c"), fastcall_path(), sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return None
+    if force or not os.path.exists(out) or os.path.getmtime(out) < os.path.getmtime(src):
+        tmp = out + ".tmp%d" % os.getpid()
+        cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", include, "-o", tmp, src]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+        os.replace(tmp, out)
+    return out
+
+
 def build(force: bool = False, verbose: bool = False, sync_check: bool = False) -> str:
     lib = LIB_SYNC_CHECK if sync_check else LIB
+    build_fastcall(force, verbose)
     if not force and up_to_date(lib):
         return lib
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -7,11 +7,17 @@ is no fallback: if the library cannot be loaded, importing callers fail.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
 
 from . import build as _build
+
+try:
+    from . import _fastcall
+except ImportError:                    # not built: ctypes takes its place
+    _fastcall = None
 
 FFTCONV_F32, FFTCONV_F16, FFTCONV_BF16 = 0, 1, 2
 _DTYPE_CODE = {torch.float32: FFTCONV_F32, torch.float16: FFTCONV_F16, torch.bfloat16: FFTCONV_BF16}
@@ -135,6 +141,7 @@ def _check(rc: int, lib=None):
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)      # (callers hold tensors: torch is initialised)
 
 
 def _stream_ptr():
@@ -142,7 +149,16 @@ def _stream_ptr():
     on a call of 9)."""
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_current_device())
+
+
+def _entry(lib, name: str):
+    """An entry point that takes integers, addresses and None, and returns a code: through the binding's extension where it is built
+    (build.build_fastcall), else through ctypes."""
+    f = getattr(lib, name)
+    if _fastcall is None:
+        return f
+    return functools.partial(_fastcall.call, ctypes.cast(f, ctypes.c_void_p).value)
 
 
 def sparsity_fraction(dims, cuts) -> float:
@@ -214,6 +230,10 @@ class Plan:
                                                     path.encode() if path else None))
         self._ws = None
         self._ws_bytes = (None, 0)
+        self._handle = self._h.value
+        self._c_filter, self._c_adjoint = _entry(self._lib, "fftconv_filter_fft"), _entry(self._lib, "fftconv_filter_fft_adjoint")
+        self._c_forward, self._c_gated = _entry(self._lib, "fftconv_forward"), _entry(self._lib, "fftconv_forward_gated")
+        self._c_input, self._c_weight = _entry(self._lib, "fftconv_backward_input"), _entry(self._lib, "fftconv_backward_filter")
 
     def _ok(self, rc: int):
         _check(rc, self._lib)
@@ -222,6 +242,7 @@ class Plan:
         if getattr(self, "_h", None) is not None and self._h:
             self._lib.fftconv_plan_destroy(self._h)
             self._h = ctypes.c_void_p()
+            self._handle = None
 
     def __del__(self):
         try:
@@ -269,7 +290,7 @@ class Plan:
         self._check_k(k)
         kf = torch.empty(self.kf_bytes(), dtype=torch.uint8, device=k.device)
         if block_keep is None:
-            self._ok(self._lib.fftconv_filter_fft(self._h, k.data_ptr(), k.shape[1], kf.data_ptr(), _stream_ptr()))
+            self._ok(self._c_filter(self._handle, k.data_ptr(), k.shape[1], kf.data_ptr(), _stream_ptr()))
         else:
             bk = bytes(bytearray(int(x) for x in block_keep))
             self._ok(self._lib.fftconv_filter_fft_sparse(self._h, k.data_ptr(), k.shape[1], bk, len(bk), kf.data_ptr(),
@@ -286,9 +307,12 @@ class Plan:
         """fftconv_forward."""
         self._check_u(u)
         y = torch.empty_like(u) if out is None else out
-        ws = self._workspace(u.shape[0], u.device)
-        self._ok(self._lib.fftconv_forward(self._h, u.data_ptr(), kf.data_ptr(), y.data_ptr(), u.shape[0], self.H,
-                                         self.N, None if ws is None else ws.data_ptr(), _stream_ptr()))
+        B = u.shape[0]
+        ws = self._workspace(B, u.device)
+        rc = self._c_forward(self._handle, u.data_ptr(), kf.data_ptr(), y.data_ptr(), B, self.H, self.N,
+                             None if ws is None else ws.data_ptr(), _stream_ptr())
+        if rc:
+            self._ok(rc)
         return y
 
     def forward_static(self, u: torch.Tensor, kf: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
@@ -308,17 +332,17 @@ class Plan:
                     raise ValueError("gates must have the shape of u")
         y = torch.empty_like(u) if out is None else out
         ws = self._workspace(u.shape[0], u.device, gated=True)
-        self._ok(self._lib.fftconv_forward_gated(self._h, u.data_ptr(), None if w is None else w.data_ptr(),
-                                               None if v is None else v.data_ptr(), kf.data_ptr(), y.data_ptr(),
-                                               u.shape[0], self.H, self.N, None if ws is None else ws.data_ptr(),
-                                               _stream_ptr()))
+        rc = self._c_gated(self._handle, u.data_ptr(), None if w is None else w.data_ptr(), None if v is None else v.data_ptr(),
+                           kf.data_ptr(), y.data_ptr(), u.shape[0], self.H, self.N, None if ws is None else ws.data_ptr(), _stream_ptr())
+        if rc:
+            self._ok(rc)
         return y
 
     def filter_fft_adjoint(self, k: torch.Tensor) -> torch.Tensor:
         """fftconv_filter_fft_adjoint: the k_f buffer fftconv_backward_input takes."""
         self._check_k(k)
         kf = torch.empty(self.kf_bytes(), dtype=torch.uint8, device=k.device)
-        self._ok(self._lib.fftconv_filter_fft_adjoint(self._h, k.data_ptr(), k.shape[1], kf.data_ptr(), _stream_ptr()))
+        self._ok(self._c_adjoint(self._handle, k.data_ptr(), k.shape[1], kf.data_ptr(), _stream_ptr()))
         return kf
 
     def backward_input(self, dy, kf_adjoint, out=None):
@@ -326,9 +350,8 @@ class Plan:
         self._check_u(dy)
         du = torch.empty_like(dy) if out is None else out
         ws = self._workspace(dy.shape[0], dy.device)
-        self._ok(self._lib.fftconv_backward_input(self._h, dy.data_ptr(), kf_adjoint.data_ptr(), du.data_ptr(),
-                                                dy.shape[0], self.H, self.N, None if ws is None else ws.data_ptr(),
-                                                _stream_ptr()))
+        self._ok(self._c_input(self._handle, dy.data_ptr(), kf_adjoint.data_ptr(), du.data_ptr(), dy.shape[0], self.H, self.N,
+                               None if ws is None else ws.data_ptr(), _stream_ptr()))
         return du
 
     def backward_filter(self, u, dy, Nk: int, out=None):
@@ -341,8 +364,8 @@ class Plan:
         need = int(self._lib.fftconv_workspace_bytes_backward_filter(self._h, u.shape[0]))
         if getattr(self, "_ws_bk", None) is None or self._ws_bk.numel() < need or self._ws_bk.device != u.device:
             self._ws_bk = torch.empty(max(need, 1), dtype=torch.uint8, device=u.device)
-        self._ok(self._lib.fftconv_backward_filter(self._h, u.data_ptr(), dy.data_ptr(), dk.data_ptr(), int(Nk),
-                                                 u.shape[0], self.H, self.N, self._ws_bk.data_ptr(), _stream_ptr()))
+        self._ok(self._c_weight(self._handle, u.data_ptr(), dy.data_ptr(), dk.data_ptr(), int(Nk), u.shape[0], self.H, self.N,
+                                self._ws_bk.data_ptr(), _stream_ptr()))
         return dk
 
     def forward_partial(self, u, kf, Nk: int, out=None):

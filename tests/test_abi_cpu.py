@@ -100,3 +100,26 @@ def test_workload_table_matches_the_stated_configs():
     assert (W["cfg3"].B, W["cfg3"].H, W["cfg3"].N, W["cfg3"].fft_size, W["cfg3"].dtype) == (16, 768, 16384, 32768, "f16")
     assert (W["cfg4"].B, W["cfg4"].H, W["cfg4"].N, W["cfg4"].fft_size, W["cfg4"].dtype) == (1, 64, 1 << 20, 1 << 21, "bf16")
     assert (W["cfg5a"].B, W["cfg5a"].H, W["cfg5a"].N, W["cfg5a"].fft_size, W["cfg5a"].Nk) == (32, 768, 8192, 16384, 1024)
+
+
+def test_fastcall_passes_what_it_is_given():
+    """The binding's extension: counts of arguments, None for a null pointer, addresses beyond 32 bits, negative numbers, errors."""
+    from paper_2311_05908_amd import build
+
+    if build.build_fastcall() is None:
+        pytest.skip("no Python headers")
+    from paper_2311_05908_amd import _fastcall
+
+    for n in (5, 9, 10, 11):
+        seen = []
+        f = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_int64] * n)(lambda *a: seen.append(a) or 7 - n)
+        address = ctypes.cast(f, ctypes.c_void_p).value
+        given = [0x7f1234567890, None, -1, 0, 3, 1 << 40, -(1 << 40), 8, 9, 10, 11][:n]
+        assert _fastcall.call(address, *given) == 7 - n
+        assert seen == [tuple(x or 0 for x in given)]
+        for bad in ([0] * 4, [0] * 8, [0] * 12, given[:-1] + [1 << 64], given[:-1] + ["x"], given[:-1] + [1.5]):
+            with pytest.raises((TypeError, OverflowError)):
+                _fastcall.call(address, *bad)
+    assert len(seen) == 1
+    with pytest.raises(ValueError):
+        _fastcall.call(0, *given)
