@@ -228,15 +228,16 @@ template <typename G, int R, bool INV, bool HALFIN = false> __device__ __forcein
 // Forward transform of the row whose samples j + T m the thread j = tid holds in x[m]; Z: the row's Row<M>::SLOTS
 // slots of LDS, free (the caller's barrier lies before).  HALF: x[m] = 0 for m >= R0 / 2.  On return x[p] holds
 // frequency freq(tid, p).  before_last() runs ahead of the last pass (loads that whoever uses the result needs).
-// factor: every sample of the thread is multiplied by it (a float2; rows of three passes).
-template <typename G, bool HALF, typename F, typename W = NoFactor>
+// factor: every sample of the thread is multiplied by it (a float2; rows of three passes).  REAL: the samples are real, the imaginary parts of x are not read.
+template <typename G, bool HALF, bool REAL = false, typename F, typename W = NoFactor>
 __device__ __forceinline__ void forward(float2 (&x)[G::P], float2 *Z, const float2 *__restrict__ tab, const Tw1<G> &tw1, int tid,
                                         F before_last, W factor = W())
 {
     {
         Tw0<G> t;
         t.load(tab, tid);
-        butterfly<G, G::R0, false, HALF>(x);
+        if constexpr (REAL && !(G::FINE && G::R0 >= 16)) dft_real<G::R0, HALF>(x);
+        else butterfly<G, G::R0, false, HALF>(x);
         if constexpr (std::is_same<W, NoFactor>::value) t.template apply<false>(x);
         else t.apply_times(x, factor);
     }
