@@ -230,8 +230,9 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
 //   Z'[f] = Z S + D (W O + i conj(W) E),  S, D = (K0 +- K1) / 2,  2 E = Z[f] + conj Z[M/2 - f],  2 O = (Z[f] - conj Z[M/2 - f]) / i,
 // so that a thread needs the mirror images of its bins only: one trip through LDS more, of half the points, and half the waves.
 // Bound by the latency of a row up to three of them to a compute unit, by its instructions beyond.  us, rows with zeros -> so: both gates, bf16 1 x 768 x 2048 (fft 4096)
-// 10.4 -> 8.3 (the kernel alone 11.1 -> 8.8 traced), 1 x 8192 80 -> 57, 1 x 8192 x 1024 (fft 2048) 56 -> 43.5; without 1 x 768 x 2048 9.4 -> 7.8, 1 x 4096 x 1024
-// 28.8 -> 22.1, 1 x 64 7.3 -> 6.0.  k_f asked for with the samples, ahead of the transform: 9.5 instead of 8.8.
+// 10.4 -> 8.3 (the kernel alone 11.1 -> 8.8 traced), 1 x 8192 80 -> 57, 1 x 8192 x 1024 (fft 2048) 56 -> 33; without 1 x 768 x 2048 9.4 -> 7.8, 1 x 4096 x 1024
+// 28.8 -> 17.9, 1 x 64 7.3 -> 5.8.  k_f asked for with the samples, ahead of the transform: 9.5 instead of 8.8.
+template <int M> constexpr bool LONE_STAGED = M == 2048;
 template <int M> using LoneRow = Row<M / 2, false, false, M / 2 == 1024>;
 template <int M, typename IO, int GATE>
 __global__ void __launch_bounds__(LoneRow<M>::T, 2)
@@ -244,7 +245,6 @@ __global__ void __launch_bounds__(LoneRow<M>::T, 2)
     extern __shared__ float2 Z[];
     const int tid = threadIdx.x, words = N / 2;
     const int64_t first = blockIdx.x * (int64_t)words;
-    const uint32_t *const kr = kf + (int64_t)blockIdx.x * M + kernel_slot<M>(G::freq(tid, 0));
     auto fetch = [&](uint32_t (&w)[MIN], const IO *t) {
         const uint32_t *const r = (const uint32_t *)t + first;
 #pragma unroll
@@ -269,12 +269,34 @@ __global__ void __launch_bounds__(LoneRow<M>::T, 2)
     }
     rf::Tw1<G> tw1;
     tw1.load(tab, tid);
-    uint32_t k0[G::P], k1[G::P];
-    rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
+    // k_f: the digits of a slot depend on the thread alone or the register alone.  Rows of 4096 points ask for their bins ahead of the last pass; those of
+    // 2048, of one wave, whose lanes lie scattered in it, take it whole into LDS, asked for with the samples (1 x 8192 x 1024 both gates 43.5 -> 33.1 us; 4096 points so:
+    // 57 -> 71), with 16 words of padding behind 256.
+    constexpr bool STAGED = LONE_STAGED<M>;
+    typedef uint32_t Four __attribute__((ext_vector_type(4)));
+    constexpr int KQ = STAGED ? M / (4 * G::T) : 1;
+    auto padded = [](int slot) { return STAGED ? slot + slot / 256 * 16 : slot; };
+    auto lower = [&](int p) { return padded(kernel_slot<M>(G::freq(0, p)) - kernel_slot<M>(0)); };
+    auto upper = [&](int p) { return padded(kernel_slot<M>(G::freq(0, p) + M / 2) - kernel_slot<M>(0)); };
+    uint32_t *const KL = (uint32_t *)(Z + G::SLOTS);
+    const int slot = padded(kernel_slot<M>(G::freq(tid, 0)));
+    Four kq[KQ];
+    uint32_t k0[STAGED ? 1 : G::P], k1[STAGED ? 1 : G::P];
+    if constexpr (STAGED) {
 #pragma unroll
-        for (int p = 0; p < G::P; ++p) {                          // the digits of a slot depend on the thread alone or the register alone
-            k0[p] = kr[kernel_slot<M>(G::freq(0, p)) - kernel_slot<M>(0)];
-            k1[p] = kr[kernel_slot<M>(G::freq(0, p) + M / 2) - kernel_slot<M>(0)];
+        for (int i = 0; i < KQ; ++i) kq[i] = ((const Four *)kf)[(int64_t)blockIdx.x * (M / 4) + tid + G::T * i];
+    }
+    rf::forward<G, true>(x, Z, tab, tw1, tid, [&] {
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int i = 0; i < KQ; ++i) *(Four *)(KL + padded(4 * (tid + G::T * i))) = kq[i];
+        } else {
+            const uint32_t *const kr = kf + (int64_t)blockIdx.x * M + slot;
+#pragma unroll
+            for (int p = 0; p < G::P; ++p) {
+                k0[p] = kr[lower(p)];
+                k1[p] = kr[upper(p)];
+            }
         }
     });
 #pragma unroll
@@ -303,7 +325,10 @@ __global__ void __launch_bounds__(LoneRow<M>::T, 2)
         const float2 z = x[p], m = mirror[p];
         const float2 w = p ? rf::mul(w0, make_float2(__builtin_cosf(TWO_PI / M * G::freq(0, p)), -__builtin_sinf(TWO_PI / M * G::freq(0, p)))) : w0;
         const float2 e = make_float2(z.x + m.x, z.y - m.y), o = make_float2(z.y + m.y, m.x - z.x);             // 2 E, 2 O
-        const float2 a = rf::unpack<IO>(k0[p]), b = rf::unpack<IO>(k1[p]);
+        uint32_t ka, kb;
+        if constexpr (STAGED) ka = KL[slot + lower(p)], kb = KL[slot + upper(p)];
+        else ka = k0[p], kb = k1[p];
+        const float2 a = rf::unpack<IO>(ka), b = rf::unpack<IO>(kb);
         const float2 s = make_float2(a.x + b.x, a.y + b.y), d = make_float2(0.5f * (a.x - b.x), 0.5f * (a.y - b.y));     // (k_f is scaled by 1 / M)
         const float2 c = rf::mul_conj(e, w), t = rf::mul(o, w);
         const float2 q = rf::mul(make_float2(t.x - c.y, t.y + c.x), d), h = rf::mul(z, s);
@@ -487,8 +512,9 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
                     using G = LoneRow<M>;
                     const auto kern = wg ? (vg ? k_row_conv_lone<M, IO, 3> : k_row_conv_lone<M, IO, 1>)
                                          : (vg ? k_row_conv_lone<M, IO, 2> : k_row_conv_lone<M, IO, 0>);
-                    FC_TRY(raise_dynamic_lds((const void *)kern, G::LDS_BYTES));
-                    hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), G::LDS_BYTES, s, (const IO *)u, (IO *)y, (const uint32_t *)kf,
+                    constexpr int lds = G::LDS_BYTES + (LONE_STAGED<M> ? 4 * (M + M / 16) : 0);
+                    FC_TRY(raise_dynamic_lds((const void *)kern, lds));
+                    hipLaunchKernelGGL(kern, dim3((unsigned)p->H), dim3(G::T), lds, s, (const IO *)u, (IO *)y, (const uint32_t *)kf,
                                        rf::row_table<G>(p), (const IO *)wg, (const IO *)vg, (int)p->N);
                     FC_HIP(hipGetLastError());
                 }
