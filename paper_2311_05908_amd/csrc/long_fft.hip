@@ -423,17 +423,18 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_corr(float2 *tu, const
 // ONE: one batch row to a run; no sum is held beside its transforms, and twice the samples are in flight.
 template <typename IO, bool ONE>
 __global__ void __launch_bounds__(RB::T, 2) k_long_rows_corr(const IO *__restrict__ u, const IO *__restrict__ dy, int N, int H, int A, int nb,
-                                                             int per, float2 *__restrict__ part, int64_t apart,
+                                                             int per, int nruns, float2 *__restrict__ part, int64_t apart,
                                                              const float2 *__restrict__ tab, const float2 *__restrict__ outer)
 {
     using G = RB;
     extern __shared__ float2 XL[];
-    // a die takes an eighth of a run's blocks, so that the rows ko of a channel are formed from one L2
-    const int NR = A / 2 + 1, blocks = H * NR, each = (blocks + 7) / 8, blk = blockIdx.x % 8 * each + blockIdx.x / 8;
-    if (blockIdx.x / 8 >= each || blk >= blocks) return;
-    const int h = blk / NR, ko = blk % NR;
-    const int tid = threadIdx.x, b0 = blockIdx.y * per, b1 = min(b0 + per, nb);
-    const bool runs = gridDim.y > 1;
+    // a die takes an eighth of the blocks of all runs, so that the rows ko of a channel are formed from one L2, and no die is left without
+    // work where a run has few of them (an eighth of each run's: three dies idle at 5 blocks: f32 300 x 1 x 65536 205.8 -> 84.5 us, 128 x 2 155 -> 80, bf16 128 x 1 x 65536 fft 131072 127 -> 80)
+    const int NR = A / 2 + 1, blocks = H * NR, total = blocks * nruns, each = (total + 7) / 8, unit = blockIdx.x % 8 * each + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= each || unit >= total) return;
+    const int run = unit / blocks, blk = unit % blocks, h = blk / NR, ko = blk % NR;
+    const int tid = threadIdx.x, b0 = run * per, b1 = min(b0 + per, nb);
+    const bool runs = nruns > 1;
     const float2 *const sums = outer + ko * A * OUTER_M, *const factors = outer + outer_tab_sums(A) + ko * OUTER_T;
     using Samples = OuterRow<IO, ONE ? 32 : 16>;
     auto row = [&](const IO *t, int b) { return Samples{t + ((int64_t)b * H + h) * N, N}; };
@@ -472,7 +473,7 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_rows_corr(const IO *__restric
     }
     float2 *const out = part + (int64_t)blk * LB;
     if (runs) {
-        float4 *const o = (float4 *)(out + blockIdx.y * apart) + tid;
+        float4 *const o = (float4 *)(out + run * apart) + tid;
 #pragma unroll
         for (int q = 0; q < G::P / 2; ++q) o[q * G::T] = make_float4(sum[2 * q].x, sum[2 * q].y, sum[2 * q + 1].x, sum[2 * q + 1].y);
         return;
@@ -789,8 +790,8 @@ int launch_rows_corr(const fftconv_plan *p, const IO *u, const IO *dy, int64_t n
     const float2 *tab = rf::row_table<RB>(p);
     const auto kern = per == 1 ? k_long_rows_corr<IO, true> : k_long_rows_corr<IO, false>;
     FC_TRY(raise_dynamic_lds((const void *)kern, B_LDS));
-    hipLaunchKernelGGL(kern, dim3((unsigned)((blocks + 7) / 8 * 8), (unsigned)runs), dim3(RB::T), B_LDS, s, u, dy, (int)p->N,
-                       (int)p->H, (int)A, (int)nb, (int)per, out, apart, tab, outer_table(p));
+    hipLaunchKernelGGL(kern, dim3((unsigned)((blocks * runs + 7) / 8 * 8)), dim3(RB::T), B_LDS, s, u, dy, (int)p->N, (int)p->H, (int)A,
+                       (int)nb, (int)per, (int)runs, out, apart, tab, outer_table(p));
     FC_HIP(hipGetLastError());
     if (runs == 1) return FFTCONV_OK;
     if (runs >= ADD_RUNS && (blocks <= ADD_MOST || runs >= ADD_MANY)) {
