@@ -1086,13 +1086,24 @@ int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adj
     default: return launch_kf_taps<0>(p, k, Nk, adjoint, keep_dev, n_blocks, kf, tag, s);
     }
 }
-// Filters that take it: where few workgroups would add many blocks up, one after another, an outer pass is faster (us, from an outer pass -> so: one channel of 65536
-// taps, fp32 12.2 -> 12.9, bf16 11.8 -> 11.7; of 131072, fft 131072, 12.6 -> 15.2; 10 of 65536 14.6 -> 12.5, 40 of 131072 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61;
-// 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51)
+// Filters of n blocks of taps that take it.  Where few workgroups would add many blocks up, one after another, an outer pass is faster, us from an outer pass -> so:
+// one channel of 65536 taps, fp32 12.2 -> 12.9, bf16 11.8 -> 11.7, 8 of fft 65536 fp32 12.9 -> 13.3, bf16 13.9 -> 13.8; of 131072, fft 131072, 12.6 -> 15.2; 10 of
+// 65536 14.6 -> 12.5, 15 of 131072 17.1 -> 16.4, 20 19.8 -> 16.9, 40 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61; 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51.
+// The workgroups take the same number of blocks each, 512 a round, and beyond 10 blocks of taps a second or third round of few costs more than the pass: 131072 taps,
+// bf16, 56 channels 26.6 -> 24.0, 57 29.0 -> 36.7, 85 36.5 -> 39.1, 97 41.9 -> 39.6, 128 51.0 -> 55.7, 160 65.3 -> 59.5, fp32 57 33.8 -> 42.9, 128 69 -> 63; 98304
+// taps 57 28.4 -> 33.7, 72 33.2 -> 32.1; 81920 57 30.0 -> 29.3.
+bool filter_on_load(int64_t A, int64_t n, int64_t H, bool f32)
+{
+    const int64_t blocks = H * (A / 2 + 1), rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
+    if (!outer_on_load(A)) return false;
+    if (n <= 4) return true;
+    if (n <= 8) return blocks >= 40 && (!f32 || n <= 6 || H * A >= 88);
+    if (blocks < 128) return false;
+    return n <= 10 || rounds == 1 || rounds > 3 || last >= (turns - 5) * (rounds == 2 ? 120 : f32 ? 35 : 110);
+}
 bool long_filter_on_load(const fftconv_plan *p, int64_t Nk)
 {
-    const int64_t A = p->M / LB, n = (Nk + LB - 1) / LB;
-    return outer_on_load(A) && (n <= 4 || p->H * (A / 2 + 1) >= (n <= 8 ? 40 : 128));
+    return filter_on_load(p->M / LB, (Nk + LB - 1) / LB, p->H, p->dtype == FFTCONV_F32);
 }
 
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (2, 13, 24577, 24577, 65536), (1, 26, 65536, 40000, 65536), (1, 3, 32768, 32768, 65536),   # of half a transform and of a whole one
     (5, 3, 65535, 65535, 131072), (1, 3, 65536, 65536, 131072),                          # 135 blocks, 27
     (1, 3, 131071, 131071, 131072), (2, 8, 81919, 8193, 131072),                         # sixteen blocks to a row, ten
+    (1, 57, 100, 131072, 131072), (1, 97, 100, 131072, 131072),                          # filters in a second round of few workgroups, and of many
     (17, 1, 100, 100, 131072),                                                           # runs of one batch row; eighths of less than a row's blocks
     (150, 1, 9000, 9000, 32768),                                                         # runs of two, whose blocks lie across the dies' eighths
 ])
