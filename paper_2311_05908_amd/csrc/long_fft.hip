@@ -919,14 +919,35 @@ int launch_kf_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_
 // 4 x 256 x 32768 364 -> 274, 2 x 16 26.3 -> 21.0 (real rows from an outer pass before); A = 16, 4 x 256 x 65536 693 -> 542, 2 x 256 x 131072 394 -> 353; errors
 // 3.29e-7 -> 2.79e-7, 3.54e-7 -> 2.98e-7, 3.45e-7 -> 3.15e-7.
 // Rows of more than 8 blocks (4 with an input gate, which doubles the loads) are not formed so by a few workgroups, which add the blocks up one
-// after another (1 x 1 x 131072 19.9 -> 22.2 us; whole rows of few channels, whose filter takes an outer pass too, would also be 3 % less accurate than in pairs; gated 1 x 1 x 65536 19.5 -> 21.3, 4 x 64 200 -> 179), and not those of more than 8 with a gate
+// after another (1 x 1 x 131072 19.9 -> 22.2 us; gated 1 x 1 x 65536 19.5 -> 21.3, 4 x 64 200 -> 179), nor are those of 7 and 8 by fewer still (fft 65536, 1, 2, 4, 6 rows of
+// 65536 16.9 -> 17.9, 17.2 -> 18.2, 17.7 -> 18.1, 18.4 -> 18.3; gated, four blocks of fft 32768, 1 and 12 rows 16.1 -> 16.4, 19.4 -> 18.9), and not those of more than 8 with a gate
 // (2 x 256 x 131072 442 -> 455).  They take an outer pass, at A = 16 in pairs: real rows from an outer pass are a tenth less accurate there (3.45e-7,
 // 3.80e-7); a row without a partner goes as a real one, or, where the chip has room, with the pairs and zeros for a partner.
+// Rounds of 512 workgroups, as with the filters (filter_on_load()): a second one of few does not pay from 13 blocks on, 1 x 57 x 131072 51 -> 57, 1 x 90 1.03 times as
+// fast, 2 x 29 53 -> 55, 2 x 32 59 -> 58, 4 x 15 55.5 -> 57; odd batches, whose last row has no partner, gain all the same (3 x 20 1.29 times), and so do more
+// rounds but for one batch row of more than 14 blocks (1 x 114 1.08 times, 1 x 190 145 -> 149, 1 x 200 159 -> 152, 1 x 228 176 -> 178, 1 x 256 196 -> 190), which goes so
+// in the first round, too, from 24 channels on (20 31.5 -> 32.5).
+}  // namespace
+bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated)
+{
+    if (!outer_on_load(A) || (gated && n > 8)) return false;
+    const int64_t blocks = B * H * (A / 2 + 1);
+    if (n <= 3 || (n <= 6 && !gated)) return true;
+    if (n == 4) return A != 4 || blocks >= 36;
+    if (!gated && n <= 8) return blocks >= (A == 8 ? 30 : 18);
+    if ((gated ? B : 1) * H * (A / 2 + 1) < 128) return false;
+    const int64_t rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
+    if (gated) return A != 16 || n < 8 || B > 1 || rounds != 2 || last >= 64;
+    if (turns < 7) return true;
+    if (rounds == 1) return B > 1 || turns < 8 || blocks >= 216;
+    if (rounds > 2) return B > 1 || turns < 8 || rounds == 3 || rounds > 5 || last >= 200;
+    return B == 1 ? last >= 149 * (turns - 6) : B % 2 == 1 || last >= 64;
+}
+namespace {
+
 bool conv_on_load(const fftconv_plan *p, int64_t B, bool gated)
 {
-    const int64_t A = p->M / LB, n = (p->N + LB - 1) / LB;
-    if (!outer_on_load(A) || (gated && n > 8)) return false;
-    return n <= (gated ? 4 : 8) || (n <= 8 ? B : 1) * p->H * (A / 2 + 1) >= 128;
+    return fftconv::conv_on_load(p->M / LB, (p->N + LB - 1) / LB, B, p->H, gated);
 }
 bool conv_real(const fftconv_plan *p, int64_t B, bool gated)
 {
@@ -952,7 +973,8 @@ int64_t conv_pairs(const fftconv_plan *p, int64_t B)
         return (units < fit ? units : fit) * unit;
     };
     const int64_t rows = multipass_filter_outer_ok(p) ? pairs(B * p->H, real_row(p)) : 0;
-    const int64_t two = conv_real(p, 1, true) && conv_real(p, 1, false) ? 0 : pairs((B + 1) / 2 * p->H, p->M);       // (at any batch, with gates or without)
+    // (whether any batch goes in pairs, with gates or without)
+    const int64_t two = conv_real(p, 2, true) && conv_real(p, 2, false) ? 0 : pairs((B + 1) / 2 * p->H, p->M);
     return rows > two ? rows : two;
 }
 

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (5, 3, 65535, 65535, 131072), (1, 3, 65536, 65536, 131072),                          # 135 blocks, 27
     (1, 3, 131071, 131071, 131072), (2, 8, 81919, 8193, 131072),                         # sixteen blocks to a row, ten
     (1, 57, 100, 131072, 131072), (1, 97, 100, 131072, 131072),                          # filters in a second round of few workgroups, and of many
+    (2, 29, 106501, 100, 131072), (1, 20, 122882, 100, 131072), (3, 1, 57345, 100, 65536),     # rows in a second round of few; too few rows
     (17, 1, 100, 100, 131072),                                                           # runs of one batch row; eighths of less than a row's blocks
     (150, 1, 9000, 9000, 32768),                                                         # runs of two, whose blocks lie across the dies' eighths
 ])

@@ -31,3 +31,35 @@ def test_filters_formed_on_load(A, blocks, dtype, on_load, from_memory):
     """Channels whose filter transform forms its rows itself, and those where an outer pass is faster: a second round of few workgroups too."""
     f = rule("_ZN7fftconv14filter_on_loadElllb", i64, i64, i64, flag)
     assert [H for H in on_load + from_memory if f(A, blocks, H, dtype == "f32")] == list(on_load)
+
+
+@pytest.mark.parametrize("A,blocks,gated,on_load,from_memory", [
+    (8, 8, False, ((1, 6), (6, 1), (1, 256)), ((1, 1), (3, 1), (1, 5))),             # (B, H); a row 16.9 -> 17.9 us
+    (8, 6, False, ((1, 1), (2, 256)), ()),
+    (16, 8, False, ((1, 2), (2, 1), (4, 256)), ((1, 1),)),
+    (4, 4, True, ((1, 12), (12, 1)), ((1, 1), (4, 2))),
+    (4, 4, False, ((1, 1), (2, 300)), ()),
+    (16, 4, True, ((1, 1), (2, 300)), ()),
+    (8, 8, True, ((1, 26), (26, 1)), ((1, 25),)),
+    (16, 8, True, ((1, 56), (1, 64), (2, 29), (3, 19)), ((1, 14), (1, 57))),
+    (16, 16, True, (), ((1, 256), (4, 256))),
+    (16, 16, False, ((1, 24), (2, 15), (2, 28), (2, 32), (3, 20), (4, 16), (1, 90), (1, 114), (1, 200), (1, 256), (2, 57), (3, 57)),
+     ((4, 14), (1, 20), (1, 57), (1, 64), (1, 171), (1, 190), (1, 228), (2, 29), (4, 15))),
+    (16, 14, False, ((1, 15), (1, 74), (1, 114), (3, 20)), ((1, 57), (1, 64), (2, 29))),
+    (16, 12, False, ((1, 57), (2, 29), (4, 15)), ((8, 14),)),
+])
+def test_fp32_rows_formed_on_load(A, blocks, gated, on_load, from_memory):
+    """Batch rows and channels of fp32 convolutions whose kernel forms its rows itself, and those that take an outer pass."""
+    f = rule("_ZN7fftconv12conv_on_loadEllllb", i64, i64, i64, i64, flag)
+    assert [s for s in on_load + from_memory if f(A, blocks, *s, gated)] == list(on_load)
+
+
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("blocks", range(1, 17))
+def test_fp32_rows_beside_a_workspace_without_pairs(blocks, gated):
+    """The workspace of outer length 16 has no room for pairs of rows where two batch rows form theirs on load with and without a gate: larger
+    batches then do, too."""
+    f = rule("_ZN7fftconv12conv_on_loadEllllb", i64, i64, i64, i64, flag)
+    for H in list(range(1, 70)) + [114, 256, 1000]:
+        if f(16, blocks, 2, H, True) and f(16, blocks, 2, H, False):
+            assert all(f(16, blocks, B, H, gated) for B in range(2, 200)), H
