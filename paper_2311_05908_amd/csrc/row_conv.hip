@@ -497,6 +497,11 @@ bool row_few(int64_t M, int64_t H, int64_t B)
     return pairs < full * items && 2 * groups <= CUS * (rounds + 1);
 }
 
+// Calls of one batch row whose rows go as half as many points.  At 4096 points, one row to a compute unit takes as long either way, the other kernel having twice
+// the threads for it, and fp16 rows, whose samples take conversions, up to two longer: 1 x 257 / 400 / 512 / 513 / 768 x 2048, us, rows with zeros -> so,
+// fp16 6.9, 7.6, 7.8, 8.7, 9.6 -> 7.6, 8.2, 8.3, 8.3, 8.5, bf16 7.0, 7.5, 7.6, 8.5, 9.3 -> 7.0, 7.4, 7.5, 7.6, 7.9.
+bool row_lone(int64_t M, int64_t H, bool f16) { return M == 2048 || (M == 4096 && H > (f16 ? 512 : 256)); }
+
 // for calls that row_few() takes
 int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
                     hipStream_t s)
@@ -520,8 +525,7 @@ int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *
                 }
                 return FFTCONV_OK;
             };
-            // (one row to a compute unit takes as long either way at 4096 points, whose other kernel has twice the threads for it)
-            if (B == 1 && (M == 2048 || (M == 4096 && p->H > 256))) return p->dtype == FFTCONV_F16 ? lone(__half()) : lone(__hip_bfloat16());
+            if (B == 1 && row_lone(M, p->H, p->dtype == FFTCONV_F16)) return p->dtype == FFTCONV_F16 ? lone(__half()) : lone(__hip_bfloat16());
             auto form = [&](auto io, auto w) -> int {
                 using IO = decltype(io);
                 constexpr bool WIDE = decltype(w)::value;

@@ -63,3 +63,12 @@ def test_fp32_rows_beside_a_workspace_without_pairs(blocks, gated):
     for H in list(range(1, 70)) + [114, 256, 1000]:
         if f(16, blocks, 2, H, True) and f(16, blocks, 2, H, False):
             assert all(f(16, blocks, B, H, gated) for B in range(2, 200)), H
+
+
+def test_rows_of_a_single_batch_row():
+    """Rows as half as many points, or with zeros for imaginary parts (fp16 1 x 400 x 2048 7.6 us so, 8.2 in half the points)."""
+    f = rule("_ZN7fftconv8row_loneEllb", i64, i64, flag)
+    for f16, first in ((False, 257), (True, 513)):
+        assert all(f(2048, H, f16) for H in (1, 256, 8192))
+        assert [H for H in (1, 256, 257, 400, 512, 513, 768, 8192) if f(4096, H, f16)] == [H for H in (257, 400, 512, 513, 768, 8192) if H >= first]
+        assert not any(f(M, H, f16) for M in (256, 512, 1024) for H in (1, 8192))

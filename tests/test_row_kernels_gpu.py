@@ -417,7 +417,7 @@ def test_a_gradient_of_fewer_rows_is_no_slower(H):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("H,N,M", [
     (1, 8, 2048), (3, 1024, 2048), (70, 1000, 2048), (2, 520, 2048),      # rows of one wave
-    (256, 2048, 4096), (257, 2048, 4096), (300, 8, 4096), (259, 1032, 4096),      # one row to a compute unit, and more
+    (256, 2048, 4096), (257, 2048, 4096), (300, 8, 4096), (259, 1032, 4096), (512, 64, 4096), (513, 72, 4096),      # one row to a compute unit, two, and more
 ])
 def test_calls_of_one_batch_row(dtype, H, N, M):
     """Rows without partners as half as many points, with either gate, both and none, against the same in fp64."""
