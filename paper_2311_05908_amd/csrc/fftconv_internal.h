@@ -306,6 +306,8 @@ int row_forward(const fftconv_plan *p, const void *u, const void *kf, void *y, i
                 const void *vg = nullptr);
 // the convolution of a matrix-core plan up to fft_size 4096 on them, and whether a call has few enough rows for it
 bool row_few(int64_t M, int64_t H, int64_t B);
+bool row_lone(int64_t M, int64_t H, bool f16);
+bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B);
 int row_forward_few(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg,
                     hipStream_t s);
 // the filter gradient on the same rows (row_grad.hip): plans up to fft_size 16384 without a matrix-core gradient kernel

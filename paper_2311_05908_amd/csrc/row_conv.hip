@@ -380,11 +380,27 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 template <int M> constexpr int64_t wide_most(bool gated) { return !gated ? 3072 : M == 512 ? 6144 : INT64_MAX; }
 template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
 
-// Pairs of rows up to which they take four passes, without gates.  fp32 rows of 2048 points do at any number of pairs (that a launch holds), the others while
-// they have a compute unit each, or two of them one.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
-// 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0; fft 4096 fp32
-// 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7.
-template <int M, typename IO> constexpr int64_t QUAD_MOST = M == 4096 ? 256 : sizeof(IO) == 4 ? INT32_MAX / 512 : 512;
+// The same of four passes, in pieces alike
+template <int M, typename IO>
+int launch_quad(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
+{
+    using Q = rf::Quad<M>;
+    const bool half = p->N <= M / 2;
+    const auto kern = half ? k_row_conv_quad<M, IO, true> : k_row_conv_quad<M, IO, false>;
+    FC_TRY(raise_dynamic_lds((const void *)kern, Q::LDS_BYTES));
+    constexpr int64_t MOST = ((int64_t)1 << 31) / Q::T;
+    const int64_t H = p->H, N = p->N, npairs = (B + 1) / 2;
+    for (int64_t p0 = 0; p0 < npairs; p0 += MOST) {
+        const int64_t np = npairs - p0 < MOST ? npairs - p0 : MOST, nb = B - 2 * p0 < 2 * np ? B - 2 * p0 : 2 * np, nh = MOST / np;
+        for (int64_t h0 = 0; h0 < H; h0 += nh) {
+            const int64_t hs = H - h0 < nh ? H - h0 : nh, total = hs * np, per_die = (total + 7) / 8, at = (2 * p0 * H + h0) * N;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_die)), dim3(Q::T), Q::LDS_BYTES, s, (const IO *)u + at, (IO *)y + at,
+                               (const float2 *)kf + h0 * M, rf::quad_table<M>(p), (int)nb, (int)H, (int)N, (int)np, (int)total, (int)per_die);
+            FC_HIP(hipGetLastError());
+        }
+    }
+    return FFTCONV_OK;
+}
 
 template <int M, typename IO>
 int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, const void *wg, const void *vg, hipStream_t s)
@@ -396,25 +412,35 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
             return half ? launch<M, IO, true, false, true>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, true>(p, u, kf, y, B, wg, vg, s);
         }
     }
-    if constexpr (rf::has_quad(M)) {
-        const int64_t npairs = (B + 1) / 2, total = p->H * npairs;
-        if (!gated && total <= QUAD_MOST<M, IO>) {
-            using Q = rf::Quad<M>;
-            const auto kern = half ? k_row_conv_quad<M, IO, true> : k_row_conv_quad<M, IO, false>;
-            FC_TRY(raise_dynamic_lds((const void *)kern, Q::LDS_BYTES));
-            const int64_t per_die = (total + 7) / 8;
-            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_die)), dim3(Q::T), Q::LDS_BYTES, s, (const IO *)u, (IO *)y, (const float2 *)kf,
-                               rf::quad_table<M>(p), (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
-            FC_HIP(hipGetLastError());
-            return FFTCONV_OK;
-        }
-    }
+    if constexpr (rf::has_quad(M))
+        if (!gated && row_quad(M, std::is_same<IO, float>::value, p->N, p->H, B)) return launch_quad<M, IO>(p, u, kf, y, B, s);
     if constexpr (M != 1024)
         if (gated) return half ? launch<M, IO, true, true, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true, false>(p, u, kf, y, B, wg, vg, s);
-    return half ? launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, false>(p, u, kf, y, B, wg, vg, s);
+    if constexpr (M == 2048 && std::is_same<IO, float>::value) return launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s);
+    else return half ? launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, false>(p, u, kf, y, B, wg, vg, s);
 }
 
 }  // namespace
+
+// Calls without gates whose rows take four passes: while the pairs have a compute unit each, or two of them one, and fp32 rows of 2048 points at nearly any
+// number.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
+// 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0; fft 4096 fp32
+// 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7.
+// fp32 rows of 2048 points that are half zeros: three passes are as fast or faster with 769 to 1024 pairs, and short rows with 1281 to 2048, where the memory's
+// time does not count: 1024 pairs of 100 samples 7.6, 7.9, of 1024 8.9, 8.9, 2048 of 100 11.8, 12.4, of 512 13.2, 13.4, of 1024 17.1, 15.2;
+// between those lines a few calls of 1536 to 2048 pairs are up to 3 % slower so (2 x 1536 x 400 10.3, 10.7; 2 x 2048 x 400 14.9, 13.4).
+// fp32 rows of 4096 beyond 256 pairs: full rows of 700 to 1700 pairs are up to a tenth faster so, as are those of half as many samples in two batch rows, but short
+// rows, and many batch rows, up to a tenth slower (2 x 768 x 2048 13.7, 13.2, 4 x 384 x 2048 12.0, 12.8, 2 x 1024 x 100 12.3, 13.7): three passes.
+bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B)
+{
+    const int64_t npairs = (B + 1) / 2;
+    if (npairs > INT32_MAX / H) return M == 2048 && f32;
+    const int64_t pairs = H * npairs;
+    if (M == 4096) return pairs <= 256;
+    if (!f32) return pairs <= 512;
+    if (N > M / 2) return true;
+    return pairs <= 768 || (pairs > 1024 && (pairs <= 1280 || pairs > 2048 || N > M / 8));
+}
 
 // The twiddle tables of the row kernels for a plan of M points (see row_table()), from w[t] = W_M^t
 std::vector<float2> row_tables(int64_t M, const double2 *w)

@@ -437,6 +437,7 @@ def test_calls_of_one_batch_row(dtype, H, N, M):
 
 @pytest.mark.parametrize("dtype,B,H,N,M", [
     ("f32", 1, 1, 1, 2048), ("f32", 3, 5, 1023, 2048), ("f32", 2, 9, 1024, 2048), ("f32", 2, 7, 1025, 2048), ("f32", 4, 700, 2048, 2048),
+    ("f32", 2, 768, 100, 2048), ("f32", 2, 769, 100, 2048), ("f32", 3, 512, 1024, 2048), ("f32", 2, 1025, 64, 2048), ("f32", 2, 1281, 30, 2048), ("f32", 2, 2049, 30, 2048),
     ("bf16", 3, 5, 2047, 2048), ("f16", 2, 512, 1100, 2048), ("f16", 2, 513, 1100, 2048),          # pairs on either side of the line
     ("f32", 3, 5, 2047, 4096), ("f32", 2, 256, 2048, 4096), ("f32", 2, 257, 2048, 4096), ("bf16", 2, 3, 4095, 4096), ("f16", 5, 20, 4096, 4096),
 ])
@@ -450,3 +451,12 @@ def test_rows_of_four_passes(dtype, B, H, N, M):
     err = parity_error(y.cpu().double().numpy(), ref.numpy(), TOL[dtype], "y")
     print("four passes %s B=%d H=%d N=%d M=%d err=%.3e" % (dtype, B, H, N, M, err), flush=True)
     assert err <= TOL[dtype]
+
+
+def test_rows_of_four_passes_in_pieces():
+    """More pairs of rows than a launch holds: 2^23 and two of one sample each, the last row without a partner."""
+    u = torch.randn((2 << 23) + 3, 1, 1, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    k = torch.randn(1, 1, device="cuda")
+    plan = fftconv.Plan(1, 2048, 1, "f32", path="small")
+    y = plan.forward(u, plan.filter_fft(k), out=torch.full_like(u, float("nan")))
+    assert (y - u * k).abs().max().item() <= TOL["f32"] * u.abs().max().item() * k.abs().item()
