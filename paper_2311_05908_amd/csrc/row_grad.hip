@@ -12,7 +12,9 @@
 //    order, which also transforms back.  With S = 1 the first kernel does that itself and no sum leaves the registers.
 //  * The sums go through memory in register order, [run][h][register pair][thread][2], as 16-byte accesses.
 //  * Of the first pass' butterflies, on real samples, the half that is not a mirror image (dft_real(); the same bits).  us: fp32 8 x 256 x 4096 67.8 -> 63.4,
-//    8 x 128 x 3000 43.9 -> 41.4, 4 x 128 x 8192 54.0 -> 52.4; bf16 8 x 4096 x 512 circular 48.5 -> 47.1; not at 256 points (64 x 768 x 128 31.3, 31.7).
+//    8 x 128 x 3000 43.9 -> 41.4, 4 x 128 x 8192 54.0 -> 52.4; bf16 8 x 4096 x 512 circular 48.5 -> 47.1; not at 256 points (64 x 768 x 128 31.3, 31.7) and not
+//    at 4096, where it gains 1 to 3 % with many rows in fp32 but a launch of one to two rows to a compute unit loses (bf16 1 x 300 x 4095 11.4 -> 13.0, x 2047
+//    10.6 -> 11.5, fp32 10.5 -> 10.7).
 // Bound by the vector ALU and, at two waves per SIMD (the accumulator, a spectrum of u and the transform under way take
 // 192 registers), by the latency of the exchanges between passes.  It replaces one
 // kernel for every factor of either transform, batch row by batch row, with the row in memory between them.  A training step
@@ -88,7 +90,7 @@ __global__ void __launch_bounds__(rf::threads_of(M), (GRAD_WAVES<M, WIDE>))
         rf::Tw1<G> tw1;
         tw1.load(tab, j);
         rf::row_barrier<G::T>();                                  // the slots are free
-        rf::forward<G, HALF, M != 256>(x, Z, tab, tw1, j, [] {});
+        rf::forward<G, HALF, M != 256 && M != 4096>(x, Z, tab, tw1, j, [] {});
         if (i & 1) {
 #pragma unroll
             for (int p = 0; p < G::P; ++p) {                      // acc += conj(Z_u) Z_dy
