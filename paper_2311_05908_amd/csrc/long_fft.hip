@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const void *__restr
     const int each = TAPS ? (blocks + 7) / 8 : blocks, at0 = TAPS ? blockIdx.x % 8 * each : 0;
     const int end = at0 + each < blocks ? at0 + each : blocks, step = TAPS ? gridDim.x / 8 : gridDim.x;
     const int begin = TAPS ? at0 + blockIdx.x / 8 : blockIdx.x;
-    if (begin >= end) return;
+    if (TAPS && begin >= end) return;                         // (the others have no more workgroups than blocks)
     float2 next[TAPS ? 1 : G::P];
     Taps::Units word;
     if constexpr (TAPS) taps(begin).fetch(word, threadIdx.x);
