@@ -12,6 +12,7 @@ from __future__ import annotations
 import concurrent.futures
 import glob
 import os
+import shlex
 import subprocess
 import sys
 import sysconfig
@@ -75,7 +76,7 @@ def build_fastcall(force: bool = False, verbose: bool = False):
         return None
     if force or not os.path.exists(out) or os.path.getmtime(out) < os.path.getmtime(src):
         tmp = out + ".tmp%d" % os.getpid()
-        cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", include, "-o", tmp, src]
+        cmd = shlex.split(os.environ.get("CC", "gcc")) + ["-O2", "-Wall", "-shared", "-fPIC", "-I", include, "-o", tmp, src]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
@@ -83,9 +84,18 @@ def build_fastcall(force: bool = False, verbose: bool = False):
     return out
 
 
+def try_build_fastcall(force: bool = False, verbose: bool = False):
+    """build_fastcall(), but a failure (no C compiler, a read-only folder) only says so: the library and the binding work without."""
+    try:
+        return build_fastcall(force, verbose)
+    except (OSError, ValueError, subprocess.CalledProcessError) as e:
+        print("%s is not built, calls go through ctypes: %s" % (os.path.basename(fastcall_path()), e), file=sys.stderr, flush=True)
+        return None
+
+
 def build(force: bool = False, verbose: bool = False, sync_check: bool = False) -> str:
     lib = LIB_SYNC_CHECK if sync_check else LIB
-    build_fastcall(force, verbose)
+    try_build_fastcall(force, verbose)
     if not force and up_to_date(lib):
         return lib
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -8,16 +8,12 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib
 import os
 
 import torch
 
 from . import build as _build
-
-try:
-    from . import _fastcall
-except ImportError:                    # not built: ctypes takes its place
-    _fastcall = None
 
 FFTCONV_F32, FFTCONV_F16, FFTCONV_BF16 = 0, 1, 2
 _DTYPE_CODE = {torch.float32: FFTCONV_F32, torch.float16: FFTCONV_F16, torch.bfloat16: FFTCONV_BF16}
@@ -152,13 +148,23 @@ def _stream_ptr():
     return _raw_stream(_current_device())
 
 
+@functools.lru_cache(maxsize=None)
+def _fastcall():
+    """call() of the binding's extension, which is built first if there is none; None where it cannot be."""
+    if not os.path.exists(_build.fastcall_path()):
+        _build.try_build_fastcall()
+        importlib.invalidate_caches()
+    try:
+        return importlib.import_module("._fastcall", __package__).call
+    except ImportError:
+        return None
+
+
 def _entry(lib, name: str):
-    """An entry point that takes integers, addresses and None, and returns a code: through the binding's extension where it is built
-    (build.build_fastcall), else through ctypes."""
-    f = getattr(lib, name)
-    if _fastcall is None:
-        return f
-    return functools.partial(_fastcall.call, ctypes.cast(f, ctypes.c_void_p).value)
+    """An entry point that takes integers, addresses and None, and returns a code: through the binding's extension where it can be built,
+    else through ctypes."""
+    f, call = getattr(lib, name), _fastcall()
+    return f if call is None else functools.partial(call, ctypes.cast(f, ctypes.c_void_p).value)
 
 
 def sparsity_fraction(dims, cuts) -> float:

@@ -3,6 +3,7 @@ validates arguments before touching a device, and its host-only helpers are righ
 import ctypes
 import os
 import re
+import sysconfig
 
 import numpy as np
 import pytest
@@ -123,3 +124,32 @@ def test_fastcall_passes_what_it_is_given():
     assert len(seen) == 1
     with pytest.raises(ValueError):
         _fastcall.call(0, *given)
+
+
+@pytest.mark.parametrize("cc", ["no-such-compiler", "false", "'unbalanced"])
+def test_the_library_builds_without_a_c_compiler(cc, monkeypatch, tmp_path, capsys):
+    """The extension is optional: a compiler that is missing or fails is reported, and the library is built (here: found up to date) all the same."""
+    from paper_2311_05908_amd import build
+
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        pytest.skip("no Python headers")
+    monkeypatch.setenv("CC", cc)
+    monkeypatch.setattr(build, "fastcall_path", lambda: str(tmp_path / "_fastcall.so"))
+    monkeypatch.setattr(build, "up_to_date", lambda lib=None: True)
+    assert build.build() == build.LIB
+    assert "_fastcall" in capsys.readouterr().err and not os.listdir(tmp_path)
+
+
+def test_the_extension_is_built_where_it_is_absent(monkeypatch, tmp_path):
+    """By the first plan of a process, also beside a library that is there already, with a compiler command of several words."""
+    from paper_2311_05908_amd import build, fftconv
+
+    if build.build_fastcall() is None:
+        pytest.skip("no Python headers")
+    out = tmp_path / "_fastcall.so"
+    monkeypatch.setenv("CC", "env LC_ALL=C gcc")
+    monkeypatch.setattr(build, "fastcall_path", lambda: str(out))
+    assert callable(fftconv._fastcall.__wrapped__()) and out.exists()
+    monkeypatch.setattr(fftconv, "_fastcall", lambda: None)
+    lib = fftconv.load()
+    assert fftconv._entry(lib, "fftconv_forward") is lib.fftconv_forward
