@@ -160,6 +160,7 @@ def _fastcall():
         return None
 
 
+@functools.lru_cache(maxsize=None)      # (of six entry points a plan: 5 of the 90 us that a plan of short rows takes)
 def _entry(lib, name: str):
     """An entry point that takes integers, addresses and None, and returns a code: through the binding's extension where it can be built,
     else through ctypes."""

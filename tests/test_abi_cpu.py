@@ -152,4 +152,11 @@ def test_the_extension_is_built_where_it_is_absent(monkeypatch, tmp_path):
     assert callable(fftconv._fastcall.__wrapped__()) and out.exists()
     monkeypatch.setattr(fftconv, "_fastcall", lambda: None)
     lib = fftconv.load()
-    assert fftconv._entry(lib, "fftconv_forward") is lib.fftconv_forward
+    assert fftconv._entry.__wrapped__(lib, "fftconv_forward") is lib.fftconv_forward
+
+
+def test_plans_share_the_entry_points_of_a_library():
+    """Made once for a library, not once for a plan."""
+    lib = fftconv.load()
+    assert fftconv._entry(lib, "fftconv_forward") is fftconv._entry(lib, "fftconv_forward")
+    assert fftconv._entry(lib, "fftconv_forward") is not fftconv._entry(lib, "fftconv_forward_gated")
