@@ -99,10 +99,12 @@ def test_gated_other_plans(dtype, B, H, N, M):
     ("f32", 3, 1, 8192, 8192, 0),
     ("f32", 3, 1, 5001, 16384, 0),
     ("f32", 1, 2, 16384, 16384, 0),
-    ("f32", 3, 2, 9001, 32768, 0),      # outer passes of real rows: odd N, then N > M / 2 and pairs of samples
+    ("f32", 3, 2, 9001, 32768, 0),      # rows of the outer factor formed on load: odd N, then N > M / 2
     ("f32", 2, 1, 20002, 32768, 0),
-    ("f32", 2, 1, 9002, 65536, 1),      # gates that start off a pair
-    ("f32", 5, 1, 9001, 131072, 0),     # pairs of rows, the last one with zeros
+    ("f32", 2, 1, 9002, 65536, 1),      # ... gates that start off a pair of samples
+    ("f32", 2, 1, 40002, 65536, 1),     # outer passes of real rows, of whose gates the same holds
+    ("f32", 3, 1, 65538, 131072, 1),    # pairs of rows, the last one with zeros
+    ("f32", 5, 1, 9001, 131072, 0),     # rows of the outer factor formed on load
     ("f32", 1, 2, 9002, 524288, 0),     # outer passes with a tile
 ])
 def test_gates_on_the_row_engine(dtype, B, H, N, M, shift):
