@@ -37,3 +37,11 @@ def test_convolutions_of_the_row_kernels_use_no_scratch():
     rows = {n: k for n, k in kernels().items() if "k_row_conv" in n}
     assert len(rows) > 100
     assert {n: k[".private_segment_fixed_size"] for n, k in rows.items() if k[".private_segment_fixed_size"]} == {}
+
+
+def test_kernels_that_form_rows_on_load_use_no_scratch():
+    """Nor those of the same transforms from rows in memory: all are held to two workgroups of a compute unit by their registers."""
+    names = "k_long_conv_rows", "k_long_rows_corr", "k_long_blocks_kf", "k_long_blocks_corr", "k_long_conv_blocks"
+    long_rows = {n: k for n, k in kernels().items() if any(x in n for x in names)}
+    assert all(any(x in n for n in long_rows) for x in names)
+    assert {n: k[".private_segment_fixed_size"] for n, k in long_rows.items() if k[".private_segment_fixed_size"]} == {}

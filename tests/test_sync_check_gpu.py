@@ -63,3 +63,25 @@ def test_checking_build_gated_partial_and_fp16():
     both_builds(synth.scaled(W["cfg2"], B=8, H=64), gated=True)
     both_builds(synth.scaled(W["cfg2"], B=8, H=64, dtype="f16"))
     both_builds(synth.scaled(W["cfg5a"], B=4, H=32), partial=True)
+
+
+@pytest.mark.parametrize("dtype,B,H,N,M", [
+    ("f32", 2, 40, 1024, 2048), ("f32", 3, 30, 4095, 4096),     # rows of four passes
+    ("bf16", 1, 300, 2048, 4096),                               # one batch row in half the points
+    ("f32", 2, 20, 50000, 65536), ("f32", 7, 3, 30000, 65536),  # rows formed on load; gradients in runs of one batch row and of several
+    ("bf16", 12, 20, 9000, 65536), ("f32", 8, 64, 4096, 8192),
+])
+def test_row_kernels_agree_bit_for_bit(dtype, B, H, N, M):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    u, w, dy = (torch.randn(B, H, N, generator=g, device="cuda").to(synth.TORCH_DTYPE[dtype]) for _ in range(3))
+    k = torch.randn(H, N, generator=g, device="cuda") / N ** 0.5
+    out = []
+    for lib in (fftconv.load(), fftconv.load(hip_build.LIB_SYNC_CHECK)):
+        plan = fftconv.Plan(N, M, H, dtype, lib=lib)
+        kf = plan.filter_fft(k)
+        out.append((plan.forward(u, kf), plan.forward_gated(u, w, None, kf), plan.backward_input(dy, plan.filter_fft_adjoint(k)),
+                    plan.backward_filter(u, dy, N)))
+        torch.cuda.synchronize()
+        plan.close()
+    for what, a, b in zip(("y", "gated", "du", "dk"), *out):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b), what
