@@ -416,16 +416,19 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
         if (!gated && row_quad(M, std::is_same<IO, float>::value, p->N, p->H, B)) return launch_quad<M, IO>(p, u, kf, y, B, s);
     if constexpr (M != 1024)
         if (gated) return half ? launch<M, IO, true, true, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, true, false>(p, u, kf, y, B, wg, vg, s);
-    if constexpr (M == 2048 && std::is_same<IO, float>::value) return launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s);
-    else return half ? launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, false>(p, u, kf, y, B, wg, vg, s);
+    return half ? launch<M, IO, true, false, false>(p, u, kf, y, B, wg, vg, s) : launch<M, IO, false, false, false>(p, u, kf, y, B, wg, vg, s);
 }
 
 }  // namespace
 
-// Calls without gates whose rows take four passes: while the pairs have a compute unit each, or two of them one, and fp32 rows of 2048 points at nearly any
-// number.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
-// 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0; fft 4096 fp32
+// Calls without gates whose rows take four passes: while the pairs have a compute unit each, or, where rows are full, two of them one, and fp32 rows of 2048
+// points at nearly any number.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
+// 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0, 500 samples 257 to 512 pairs
+// 6.15, 6.3; fft 4096 fp32
 // 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7.
+// fp32 rows of 2048 points that are more than half full, once u and y exceed the memory-side cache: three passes are faster (8 x 1024 x 2048 128 MB 1.20 times as
+// fast in four, 16 x 768 192 MB 1.15, 16 x 1024 256 MB 0.98, 64 x 768 384 MB 0.96, 64 x 768 x 1500 562 MB 0.92); half-empty rows are no slower in four there
+// (64 x 1500 x 1024 750 MB 1.01, 256 x 2048 x 256 1 GB 1.03).
 // fp32 rows of 2048 points that are half zeros: three passes are as fast or faster with 769 to 1024 pairs, and short rows with 1281 to 2048, where the memory's
 // time does not count: 1024 pairs of 100 samples 7.6, 7.9, of 1024 8.9, 8.9, 2048 of 100 11.8, 12.4, of 512 13.2, 13.4, of 1024 17.1, 15.2;
 // between those lines a few calls of 1536 to 2048 pairs are up to 3 % slower so (2 x 1536 x 400 10.3, 10.7; 2 x 2048 x 400 14.9, 13.4).
@@ -434,11 +437,12 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
 bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B)
 {
     const int64_t npairs = (B + 1) / 2;
-    if (npairs > INT32_MAX / H) return M == 2048 && f32;
+    const bool half = N <= M / 2;
+    if (npairs > INT32_MAX / H) return M == 2048 && f32 && half;
     const int64_t pairs = H * npairs;
     if (M == 4096) return pairs <= 256;
-    if (!f32) return pairs <= 512;
-    if (N > M / 2) return true;
+    if (!f32) return pairs <= (half ? 256 : 512);
+    if (!half) return B * H * N <= (int64_t)28 << 20;             // 224 MB of u and y
     return pairs <= 768 || (pairs > 1024 && (pairs <= 1280 || pairs > 2048 || N > M / 8));
 }
 

@@ -437,7 +437,7 @@ def test_calls_of_one_batch_row(dtype, H, N, M):
 
 @pytest.mark.parametrize("dtype,B,H,N,M", [
     ("f32", 1, 1, 1, 2048), ("f32", 3, 5, 1023, 2048), ("f32", 2, 9, 1024, 2048), ("f32", 2, 7, 1025, 2048), ("f32", 4, 700, 2048, 2048),
-    ("f32", 2, 768, 100, 2048), ("f32", 2, 769, 100, 2048), ("f32", 3, 512, 1024, 2048), ("f32", 2, 1025, 64, 2048), ("f32", 2, 1281, 30, 2048), ("f32", 2, 2049, 30, 2048),
+    ("bf16", 2, 256, 777, 2048), ("f16", 2, 257, 777, 2048), ("f32", 2, 768, 100, 2048), ("f32", 2, 769, 100, 2048), ("f32", 3, 512, 1024, 2048), ("f32", 2, 1025, 64, 2048), ("f32", 2, 1281, 30, 2048), ("f32", 2, 2049, 30, 2048),
     ("bf16", 3, 5, 2047, 2048), ("f16", 2, 512, 1100, 2048), ("f16", 2, 513, 1100, 2048),          # pairs on either side of the line
     ("f32", 3, 5, 2047, 4096), ("f32", 2, 256, 2048, 4096), ("f32", 2, 257, 2048, 4096), ("bf16", 2, 3, 4095, 4096), ("f16", 5, 20, 4096, 4096),
 ])
@@ -481,3 +481,14 @@ def test_a_gradient_of_a_few_rows_more_than_compute_units():
             best[H] = min(best[H], t[0].elapsed_time(t[1]) * 10)
     print("dk of 1 x 256, 300 x 4095: %.1f, %.1f us" % (best[256], best[300]), flush=True)
     assert best[300] <= 1.15 * best[256]
+
+
+def test_fp32_rows_beyond_the_memory_side_cache():
+    """224 MB of full rows of 2048 points, the line to rows of three passes, on either side."""
+    k = torch.randn(100, 2048, device="cuda") / 2048 ** 0.5
+    for B, N in ((280, 1047), (281, 1047), (2, 2048)):
+        u = torch.randn(B, 100, N, device="cuda")
+        plan = fftconv.Plan(N, 2048, 100, "f32")
+        y = plan.forward(u, plan.filter_fft(k[:, :N].contiguous()), out=torch.full_like(u, float("nan")))
+        ref = torch.fft.irfft(torch.fft.rfft(u.double(), 2048) * torch.fft.rfft(k[:, :N].double(), 2048), 2048)[..., :N]
+        assert ((y - ref).norm(dim=-1) / ref.norm(dim=-1)).max().item() <= TOL["f32"]
