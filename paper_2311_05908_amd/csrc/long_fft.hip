@@ -428,11 +428,12 @@ __global__ void __launch_bounds__(RB::T, 2) k_long_rows_corr(const IO *__restric
 {
     using G = RB;
     extern __shared__ float2 XL[];
-    // a die takes an eighth of the blocks of all runs, so that the rows ko of a channel are formed from one L2, and no die is left without
-    // work where a run has few of them (an eighth of each run's: three dies idle at 5 blocks: f32 300 x 1 x 65536 205.8 -> 84.5 us, 128 x 2 155 -> 80, bf16 128 x 1 x 65536 fft 131072 127 -> 80)
-    const int NR = A / 2 + 1, blocks = H * NR, total = blocks * nruns, each = (total + 7) / 8, unit = blockIdx.x % 8 * each + blockIdx.x / 8;
+    // A die takes an eighth of the blocks, those of a channel's runs one after another, so that the rows ko of a run are formed from one L2, and no die is left
+    // without work where channels are few.  (An eighth of each run's blocks: three dies idle at 5 blocks, f32 300 x 1 x 65536 205.8 -> 84.9 us, 128 x 2 155 -> 80,
+    // bf16 128 x 1 x 65536 fft 131072 127 -> 79; one run's blocks after another's: f32 8 x 8 x 32768 fft 65536 38.0 -> 35.8, 3 x 57 x 32768 49.2 -> 47.7.)
+    const int NR = A / 2 + 1, total = H * NR * nruns, each = (total + 7) / 8, unit = blockIdx.x % 8 * each + blockIdx.x / 8;
     if (blockIdx.x / 8 >= each || unit >= total) return;
-    const int run = unit / blocks, blk = unit % blocks, h = blk / NR, ko = blk % NR;
+    const int h = unit / (NR * nruns), of_h = unit % (NR * nruns), run = of_h / NR, ko = of_h % NR, blk = h * NR + ko;
     const int tid = threadIdx.x, b0 = run * per, b1 = min(b0 + per, nb);
     const bool runs = nruns > 1;
     const float2 *const sums = outer + ko * A * OUTER_M, *const factors = outer + outer_tab_sums(A) + ko * OUTER_T;
@@ -768,7 +769,8 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
 // Gradients whose kernel forms its rows itself (outer_row.h): where the chip has enough of them, or a row has few blocks to add up, one after
 // another.  Whole gradient, us, from an outer pass -> so: bf16 2 x 256 x 65536 364 -> 280, 1 x 256 204 -> 169, 2 x 256 x 32768 194 -> 121, f32 2 x 256 x 65536
 // 404 -> 302, 20 x 100 x 16384 431 -> 252, 1 x 1 x 16384 20.1 -> 19.2, bf16 16 x 1 x 65536 39.4 -> 37.7; one row of 65536 samples 23.7 -> 26.2, one of
-// 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  dk of fft 131072 4.33e-7 -> 3.67e-7.
+// 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  A few calls of 7 and 8 blocks just beyond the line lose as well (1 x 40 x 65536 f32 33.6 -> 36.0, bf16
+// 1 x 48 34.4 -> 36.4, 3 x 20 fft 131072 59.1 -> 60.4; 1 x 57 1.06 times as fast).  dk of fft 131072 4.33e-7 -> 3.67e-7.
 bool grad_on_load(const fftconv_plan *p, int64_t B)
 {
     const int64_t A = p->M / LB, n = (p->N + LB - 1) / LB;
