@@ -927,8 +927,8 @@ int launch_kf_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_
 // 3.80e-7); a row without a partner goes as a real one, or, where the chip has room, with the pairs and zeros for a partner.
 // Rounds of 512 workgroups, as with the filters (filter_on_load()): a second one of few does not pay from 13 blocks on, 1 x 57 x 131072 51 -> 57, 1 x 90 1.03 times as
 // fast, 2 x 29 53 -> 55, 2 x 32 59 -> 58, 4 x 15 55.5 -> 57; odd batches, whose last row has no partner, gain all the same (3 x 20 1.29 times), and so do more
-// rounds but for one batch row of more than 14 blocks (1 x 114 1.08 times, 1 x 190 145 -> 149, 1 x 200 159 -> 152, 1 x 228 176 -> 178, 1 x 256 196 -> 190), which goes so
-// in the first round, too, from 24 channels on (20 31.5 -> 32.5).
+// rounds but for one batch row of more than 14 blocks (1 x 114 1.08 times, 1 x 190 145 -> 149, 1 x 200 159 -> 152, 1 x 228 176 -> 178, 1 x 256 196 -> 190), and in the
+// first round 17 to 23 channels of it (16 30.3 -> 28.0, 20 31.5 -> 32.5, 24 1.02 times).
 }  // namespace
 bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated)
 {
@@ -941,7 +941,7 @@ bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated)
     const int64_t rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
     if (gated) return A != 16 || n < 8 || B > 1 || rounds != 2 || last >= 64;
     if (turns < 7) return true;
-    if (rounds == 1) return B > 1 || turns < 8 || blocks >= 216;
+    if (rounds == 1) return B > 1 || turns < 8 || blocks <= 144 || blocks >= 216;
     if (rounds > 2) return B > 1 || turns < 8 || rounds == 3 || rounds > 5 || last >= 200;
     return B == 1 ? last >= 149 * (turns - 6) : B % 2 == 1 || last >= 64;
 }
@@ -1114,8 +1114,8 @@ int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adj
 // one channel of 65536 taps, fp32 12.2 -> 12.9, bf16 11.8 -> 11.7, 8 of fft 65536 fp32 12.9 -> 13.3, bf16 13.9 -> 13.8; of 131072, fft 131072, 12.6 -> 15.2; 10 of
 // 65536 14.6 -> 12.5, 15 of 131072 17.1 -> 16.4, 20 19.8 -> 16.9, 40 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61; 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51.
 // The workgroups take the same number of blocks each, 512 a round, and beyond 10 blocks of taps a second or third round of few costs more than the pass: 131072 taps,
-// bf16, 56 channels 26.6 -> 24.0, 57 29.0 -> 36.7, 85 36.5 -> 39.1, 97 41.9 -> 39.6, 128 51.0 -> 55.7, 160 65.3 -> 59.5, fp32 57 33.8 -> 42.9, 128 69 -> 63; 98304
-// taps 57 28.4 -> 33.7, 72 33.2 -> 32.1; 81920 57 30.0 -> 29.3.
+// bf16, 56 channels 26.6 -> 24.0, 57 29.0 -> 36.7, 85 36.5 -> 39.1, 97 41.9 -> 39.6, 128 51.0 -> 55.7, 160 65.3 -> 59.5, fp32 57 33.8 -> 42.9, 117 58 -> 62, 125 66 -> 62; 98304
+// taps 57 28.4 -> 33.7, 72 33.2 -> 32.1, fp32 114 55.2 -> 53.7; 81920 57 30.0 -> 29.3.
 bool filter_on_load(int64_t A, int64_t n, int64_t H, bool f32)
 {
     const int64_t blocks = H * (A / 2 + 1), rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
@@ -1123,7 +1123,7 @@ bool filter_on_load(int64_t A, int64_t n, int64_t H, bool f32)
     if (n <= 4) return true;
     if (n <= 8) return blocks >= 40 && (!f32 || n <= 6 || H * A >= 88);
     if (blocks < 128) return false;
-    return n <= 10 || rounds == 1 || rounds > 3 || last >= (turns - 5) * (rounds == 2 ? 120 : f32 ? 35 : 110);
+    return n <= 10 || rounds == 1 || rounds > 3 || last >= (rounds == 2 ? 120 * (turns - 5) : f32 ? 70 * (turns - 7) : 110 * (turns - 5));
 }
 bool long_filter_on_load(const fftconv_plan *p, int64_t Nk)
 {

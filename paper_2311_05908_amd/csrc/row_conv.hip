@@ -429,9 +429,9 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
 // fp32 rows of 2048 points that are more than half full, once u and y exceed the memory-side cache: three passes are faster (8 x 1024 x 2048 128 MB 1.20 times as
 // fast in four, 16 x 768 192 MB 1.15, 16 x 1024 256 MB 0.98, 64 x 768 384 MB 0.96, 64 x 768 x 1500 562 MB 0.92); half-empty rows are no slower in four there
 // (64 x 1500 x 1024 750 MB 1.01, 256 x 2048 x 256 1 GB 1.03).
-// fp32 rows of 2048 points that are half zeros: three passes are as fast or faster with 769 to 1024 pairs, and short rows with 1281 to 2048, where the memory's
-// time does not count: 1024 pairs of 100 samples 7.6, 7.9, of 1024 8.9, 8.9, 2048 of 100 11.8, 12.4, of 512 13.2, 13.4, of 1024 17.1, 15.2;
-// between those lines a few calls of 1536 to 2048 pairs are up to 3 % slower so (2 x 1536 x 400 10.3, 10.7; 2 x 2048 x 400 14.9, 13.4).
+// fp32 rows of 2048 points that are half zeros: three passes are as fast or faster with 769 to 1024 pairs, and short rows with 1793 to 2048, where the memory's
+// time does not count: 1024 pairs of 100 samples 7.6, 7.9, of 1024 8.9, 8.9, 1536 of 100 10.1, 10.1, 1600 11.6, 11.2, 2048 11.8, 12.4, of 512 13.2, 13.4, of 1024
+// 17.1, 15.2; between those lines a few calls of 1536 to 2048 pairs are up to 3 % slower so (2 x 1536 x 400 10.3, 10.7; 2 x 2048 x 400 14.9, 13.4).
 // fp32 rows of 4096 beyond 256 pairs: full rows of 700 to 1700 pairs are up to a tenth faster so, as are those of half as many samples in two batch rows, but short
 // rows, and many batch rows, up to a tenth slower (2 x 768 x 2048 13.7, 13.2, 4 x 384 x 2048 12.0, 12.8, 2 x 1024 x 100 12.3, 13.7): three passes.
 bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B)
@@ -443,7 +443,7 @@ bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B)
     if (M == 4096) return pairs <= 256;
     if (!f32) return pairs <= (half ? 256 : 512);
     if (!half) return B * H * N <= (int64_t)28 << 20;             // 224 MB of u and y
-    return pairs <= 768 || (pairs > 1024 && (pairs <= 1280 || pairs > 2048 || N > M / 8));
+    return pairs <= 768 || (pairs > 1024 && (pairs <= 1792 || pairs > 2048 || N > M / 8));
 }
 
 // The twiddle tables of the row kernels for a plan of M points (see row_table()), from w[t] = W_M^t
