@@ -236,8 +236,9 @@ template <typename G> __device__ __forceinline__ void store_row(const float2 (&x
 // now; 2^21 46.6, 50.8, 42.5; 768 channels of fft 32768 151, 134, 110; bf16, 768 channels of fft 65536 230, 163, 157.
 // Workgroups are persistent, two to a compute unit, and fetch the next block ahead of the present one's transform: loads,
 // transforms and stores of workgroups that all start together otherwise take turns on the whole chip.
-// TAPS: src holds the taps themselves, and the rows ko are formed of them on the way in (outer_row.h).  Up to A = 16 nearly all transforms go so: 256 channels of fft
-// 131072 bf16 95 -> 61 us, 768 of 65536 151 -> 95, 768 of 32768 fp32 109 -> 51 (the times above are of rows from memory).
+// TAPS: src holds the taps themselves, and the rows ko are formed of them on the way in (outer_row.h).  Up to A = 16 most transforms go so: 256 channels of fft
+// 131072 bf16 95 -> 61 us (of 65536 taps that stay in the caches; 76 each in a training step), 768 of 65536 151 -> 95, 768 of 32768 fp32 109 -> 51 (the times
+// above are of rows from memory).
 template <int KF, bool TAPS>
 __global__ void __launch_bounds__(RB::T, 2) k_long_blocks_kf(const void *__restrict__ src, void *__restrict__ kf,
                                                              const float2 *__restrict__ tab, FacList flA, int A, int64_t h0, int blocks,
@@ -1099,8 +1100,7 @@ int long_filter_transform(const fftconv_plan *p, const float *k, int64_t Nk, int
                                    : launch_kf<0>(p, g, nh, tmp, kf, h0, keep_dev, n_blocks, natural, natural && adjoint, tag, s);
 }
 
-// The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block transforms of the
-// rows ko <= A/2, as above.  tmp holds nh * (A/2 + 1) * 8192 float2.  Needs multipass_filter_outer_ok(p).
+// The filter transform of all channels of a plan with A = M / 8192 = 4, 8 or 16, whatever its I/O type: one kernel from the taps to k_f (filter_on_load())
 int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks, void *kf,
                      KfTag tag, hipStream_t s)
 {
@@ -1130,6 +1130,8 @@ bool long_filter_on_load(const fftconv_plan *p, int64_t Nk)
     return filter_on_load(p->M / LB, (Nk + LB - 1) / LB, p->H, p->dtype == FFTCONV_F32);
 }
 
+// The filter transform of channels [h0, h0 + nh) of a plan that keeps k_f as fp32 pairs (fp32 I/O, fft_size 32768 .. 2^21): the real outer pass and the block
+// transforms of the rows ko <= A/2.  tmp holds nh * (A/2 + 1) * 8192 float2.  Needs multipass_filter_outer_ok(p).
 int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk, int64_t h0, int64_t nh, bool adjoint,
                               const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s)
 {

@@ -7,7 +7,7 @@
 // same in all registers of a thread and rides on the twiddles of its first pass (rf::twiddle_times()).  That is two multiply-adds for a
 // real sample and row ko, where a transform for all rows at once takes a few for a point, but the samples of a row reach the A/2 + 1 workgroups of
 // its rows ko from one L2 (they are on one die), and the rows, of fp32 pairs, are neither written nor read: a filter transform of 256 channels of fft 131072
-// moves 0.2 GB instead of 0.5 (95 -> 61 us), a gradient of 2 x 256 x 65536 bf16 samples 0.5 instead of 1.7 (364 -> 280 us; vector instructions at four
+// moves 0.2 GB instead of 0.5 (95 -> 61 us, 76 in a training step), a gradient of 2 x 256 x 65536 bf16 samples 0.5 instead of 1.7 (364 -> 280 us; vector instructions at four
 // cycles each are 220 of them now).  Fewer roundings, too: the gradient's error 4.33e-7 -> 3.67e-7.  At A = 32 the sums cost what the trip does (filter 128
 // channels of fft 2^18 bf16 105 -> 88 us, but 64 fp32 60 -> 62, gradient 205 -> 229), at 64 twice that.
 #pragma once

@@ -229,8 +229,8 @@ __global__ void __launch_bounds__(rf::threads_of(M), WIDE ? 4 : waves_of(M))
 // k_f, the result's transform is
 //   Z'[f] = Z S + D (W O + i conj(W) E),  S, D = (K0 +- K1) / 2,  2 E = Z[f] + conj Z[M/2 - f],  2 O = (Z[f] - conj Z[M/2 - f]) / i,
 // so that a thread needs the mirror images of its bins only: one trip through LDS more, of half the points, and half the waves.
-// Bound by the latency of a row up to three of them to a compute unit, by its instructions beyond.  us, rows with zeros -> so: both gates, bf16 1 x 768 x 2048 (fft 4096)
-// 10.4 -> 8.3 (the kernel alone 11.1 -> 8.8 traced), 1 x 8192 80 -> 57, 1 x 8192 x 1024 (fft 2048) 56 -> 33; without 1 x 768 x 2048 9.4 -> 7.8, 1 x 4096 x 1024
+// Bound by the latency of a row up to three of them to a compute unit, by its instructions beyond.  us, rows with zeros -> so, on inputs that stay in the caches: both
+// gates, bf16 1 x 768 x 2048 (fft 4096) 10.4 -> 8.3 (10.4 -> 9.5 on new inputs each call; the kernel alone 11.1 -> 8.8 traced), 1 x 8192 80 -> 57, 1 x 8192 x 1024 (fft 2048) 56 -> 33; without 1 x 768 x 2048 9.4 -> 7.8, 1 x 4096 x 1024
 // 28.8 -> 17.9, 1 x 64 7.3 -> 5.8.  k_f asked for with the samples, ahead of the transform: 9.5 instead of 8.8.
 template <int M> constexpr bool LONE_STAGED = M == 2048;
 template <int M> using LoneRow = Row<M / 2, false, false, M / 2 == 1024>;
