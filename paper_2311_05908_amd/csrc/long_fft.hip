@@ -772,11 +772,14 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
 // 404 -> 302, 20 x 100 x 16384 431 -> 252, 1 x 1 x 16384 20.1 -> 19.2, bf16 16 x 1 x 65536 39.4 -> 37.7; one row of 65536 samples 23.7 -> 26.2, one of
 // 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  A few calls of 7 and 8 blocks just beyond the line lose as well (1 x 40 x 65536 f32 33.6 -> 36.0, bf16
 // 1 x 48 34.4 -> 36.4, 3 x 20 fft 131072 59.1 -> 60.4; 1 x 57 1.06 times as fast).  dk of fft 131072 4.33e-7 -> 3.67e-7.
-bool grad_on_load(const fftconv_plan *p, int64_t B)
+// (Batch rows are counted in 32 bits, in up to 512 runs that end less than a row each beyond the last one.)
+}  // namespace
+bool grad_on_load(int64_t A, int64_t n, int64_t B, int64_t H)
 {
-    const int64_t A = p->M / LB, n = (p->N + LB - 1) / LB;
-    return outer_on_load(A) && B < INT32_MAX && (n <= 2 || (n <= 8 && B * p->H * (A / 2 + 1) >= 128));
+    return outer_on_load(A) && B < INT32_MAX - 512 && (n <= 2 || (n <= 8 && B * H * (A / 2 + 1) >= 128));
 }
+namespace {
+
 
 // The same from u and dy (k_long_rows_corr): the inverse transforms' rows of all channels -> out, which holds `fit` rows of A/2 + 1 blocks
 template <typename IO>
@@ -828,7 +831,7 @@ int long_backward_filter_t(const fftconv_plan *p, const IO *u, const IO *dy, flo
         FC_HIP(hipGetLastError());
         return FFTCONV_OK;
     }
-    if (grad_on_load(p, B)) {
+    if (grad_on_load(M / LB, (N + LB - 1) / LB, B, H)) {
         FC_TRY(launch_rows_corr(p, u, dy, B, (float2 *)workspace, grad_rows(p), s));
         return multipass_dk_outer_inv(p, workspace, dk, Nk, H, 1.0f / (float)M, s);
     }

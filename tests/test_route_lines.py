@@ -86,3 +86,11 @@ def test_rows_of_four_passes():
     for M, f32, N, most in ((2048, False, 2048, 512), (2048, False, 1025, 512), (2048, False, 1024, 256), (2048, False, 100, 256),
                             (4096, True, 100, 256), (4096, True, 4096, 256), (4096, False, 100, 256), (4096, False, 4096, 256)):
         assert f(M, f32, N, most, 2) and not f(M, f32, N, most + 1, 2) and not f(M, f32, N, 1, 1 << 33)
+
+
+def test_gradients_formed_on_load():
+    """Calls whose kernel forms its rows itself; with as many batch rows as 32 bits count, the last run's end would not fit."""
+    f = rule("_ZN7fftconv12grad_on_loadEllll", i64, i64, i64, i64)
+    on_load = [(8, 8, 26, 1), (8, 8, 1, 26), (16, 8, 15, 1), (16, 2, 1, 1), (4, 1, 1, 1), (4, 4, 43, 1), (16, 1, (1 << 31) - 514, 1)]
+    from_memory = [(8, 8, 25, 1), (16, 8, 14, 1), (4, 4, 42, 1), (16, 9, 300, 300), (32, 1, 8, 8), (2, 1, 8, 8), (16, 1, (1 << 31) - 513, 1), (16, 1, 1 << 33, 1)]
+    assert [c for c in on_load + from_memory if f(*c)] == on_load
