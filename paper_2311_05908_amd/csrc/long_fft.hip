@@ -770,13 +770,14 @@ int launch_corr(const fftconv_plan *p, int blocks, int64_t nh, float2 *tu, const
 // Gradients whose kernel forms its rows itself (outer_row.h): where the chip has enough of them, or a row has few blocks to add up, one after
 // another.  Whole gradient, us, from an outer pass -> so: bf16 2 x 256 x 65536 364 -> 280, 1 x 256 204 -> 169, 2 x 256 x 32768 194 -> 121, f32 2 x 256 x 65536
 // 404 -> 302, 20 x 100 x 16384 431 -> 252, 1 x 1 x 16384 20.1 -> 19.2, bf16 16 x 1 x 65536 39.4 -> 37.7; one row of 65536 samples 23.7 -> 26.2, one of
-// 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  A few calls of 7 and 8 blocks just beyond the line lose as well (1 x 40 x 65536 f32 33.6 -> 36.0, bf16
+// 32768 21.3 -> 21.5, 2 x 8 x 32768 30.0 -> 31.0; with other kernels between, 7 and 8 blocks: bf16 1 x 26 x 65536 28.7 -> 30.1, 4 x 8 34.8 -> 36.0, fft 131072 16 x 1
+// 35.1 -> 36.4, from 176 spectra on none slower; sixteen blocks, 2 x 256 x 131072 400 -> 405, f32 5 x 3 40.4 -> 46.6.  A few calls of 7 and 8 blocks just beyond the line lose as well (1 x 40 x 65536 f32 33.6 -> 36.0, bf16
 // 1 x 48 34.4 -> 36.4, 3 x 20 fft 131072 59.1 -> 60.4; 1 x 57 1.06 times as fast).  dk of fft 131072 4.33e-7 -> 3.67e-7.
 // (Batch rows are counted in 32 bits, in up to 512 runs that end less than a row each beyond the last one.)
 }  // namespace
 bool grad_on_load(int64_t A, int64_t n, int64_t B, int64_t H)
 {
-    return outer_on_load(A) && B < INT32_MAX - 512 && (n <= 2 || (n <= 8 && B * H * (A / 2 + 1) >= 128));
+    return outer_on_load(A) && B < INT32_MAX - 512 && (n <= 2 || (n <= 8 && B * H * (A / 2 + 1) >= (n <= 6 ? 128 : 176)));
 }
 namespace {
 
@@ -926,7 +927,7 @@ int launch_kf_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_
 // 3.29e-7 -> 2.79e-7, 3.54e-7 -> 2.98e-7, 3.45e-7 -> 3.15e-7.
 // Rows of more than 8 blocks (4 with an input gate, which doubles the loads) are not formed so by a few workgroups, which add the blocks up one
 // after another (1 x 1 x 131072 19.9 -> 22.2 us; gated 1 x 1 x 65536 19.5 -> 21.3, 4 x 64 200 -> 179), nor are those of 7 and 8 by fewer still (fft 65536, 1, 2, 4, 6 rows of
-// 65536 16.9 -> 17.9, 17.2 -> 18.2, 17.7 -> 18.1, 18.4 -> 18.3; gated, four blocks of fft 32768, 1 and 12 rows 16.1 -> 16.4, 19.4 -> 18.9), and not those of more than 8 with a gate
+// 65536 16.9 -> 17.9, 17.2 -> 18.2, 17.7 -> 18.1, 18.4 -> 18.3, of 6 and 12 with other kernels between 19.6 -> 20.7 and 20.4 -> 21.1; gated, four blocks of fft 32768, 1 and 12 rows 16.1 -> 16.4, 19.4 -> 18.9), and not those of more than 8 with a gate
 // (2 x 256 x 131072 442 -> 455).  They take an outer pass, at A = 16 in pairs: real rows from an outer pass are a tenth less accurate there (3.45e-7,
 // 3.80e-7); a row without a partner goes as a real one, or, where the chip has room, with the pairs and zeros for a partner.
 // Rounds of 512 workgroups, as with the filters (filter_on_load()): a second one of few does not pay from 13 blocks on, 1 x 57 x 131072 51 -> 57, 1 x 90 1.03 times as
@@ -940,8 +941,8 @@ bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated)
     const int64_t blocks = B * H * (A / 2 + 1);
     if (n <= 3 || (n <= 6 && !gated)) return true;
     if (n == 4) return A != 4 || blocks >= 36;
-    if (!gated && n <= 8) return blocks >= (A == 8 ? 30 : 18);
-    if ((gated ? B : 1) * H * (A / 2 + 1) < 128) return false;
+    if (!gated && n <= 8) return blocks >= (A == 8 ? 60 : 18);
+    if ((gated ? B : 1) * H * (A / 2 + 1) < (gated && n > 6 ? 176 : 128)) return false;
     const int64_t rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
     if (gated) return A != 16 || n < 8 || B > 1 || rounds != 2 || last >= 64;
     if (turns < 7) return true;
@@ -1115,7 +1116,12 @@ int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adj
 }
 // Filters of n blocks of taps that take it.  Where few workgroups would add many blocks up, one after another, an outer pass is faster, us from an outer pass -> so:
 // one channel of 65536 taps, fp32 12.2 -> 12.9, bf16 11.8 -> 11.7, 8 of fft 65536 fp32 12.9 -> 13.3, bf16 13.9 -> 13.8; of 131072, fft 131072, 12.6 -> 15.2; 10 of
-// 65536 14.6 -> 12.5, 15 of 131072 17.1 -> 16.4, 20 19.8 -> 16.9, 40 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61; 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51.
+// 65536 14.6 -> 12.5, 20 of 131072 19.8 -> 16.9, 40 fp32 26.7 -> 24.9, 256 of 65536 bf16 95 -> 61; 768 of 32768 151 -> 95, 768 of 16384 fp32 109 -> 51.
+// Those are calls one after another; in a training step other kernels have put the sums' constants out of the L2s, and each block waits for its own: 131072 taps,
+// with 96 MB copied between calls, bf16 15 / 24 / 32 / 40 channels 0.84, 0.92, 1.00, 1.04 times as fast as an outer pass (98304 taps 0.95, 1.04, 1.11; fft 65536 8 / 16 /
+// 24 of 65536 0.95, 0.96, 1.04), a training step of 1 x 16 x 131072 104.6 -> 108.9.  The lines of 16-bit plans are those of such steps; fp32 plans keep the
+// earlier one beyond 8 blocks (15 of 131072 0.87), as their convolutions go on load from there on, and with a spectrum from an outer pass an odd batch of those
+// would be 3 % less accurate than in pairs (3.90e-7, 3.79e-7).
 // The workgroups take the same number of blocks each, 512 a round, and beyond 10 blocks of taps a second or third round of few costs more than the pass: 131072 taps,
 // bf16, 56 channels 26.6 -> 24.0, 57 29.0 -> 36.7, 85 36.5 -> 39.1, 97 41.9 -> 39.6, 128 51.0 -> 55.7, 160 65.3 -> 59.5, fp32 57 33.8 -> 42.9, 117 58 -> 62, 125 66 -> 62; 98304
 // taps 57 28.4 -> 33.7, 72 33.2 -> 32.1, fp32 114 55.2 -> 53.7; 81920 57 30.0 -> 29.3.
@@ -1124,8 +1130,9 @@ bool filter_on_load(int64_t A, int64_t n, int64_t H, bool f32)
     const int64_t blocks = H * (A / 2 + 1), rounds = (blocks + 511) / 512, last = blocks - 512 * (rounds - 1), turns = (n + 1) / 2;
     if (!outer_on_load(A)) return false;
     if (n <= 4) return true;
-    if (n <= 8) return blocks >= 40 && (!f32 || n <= 6 || H * A >= 88);
-    if (blocks < 128) return false;
+    if (n <= 6) return blocks >= 40;
+    if (n <= 8) return blocks >= (!f32 ? 108 : A == 8 ? 100 : 54);
+    if (blocks < (f32 ? 128 : 128 + 60 * (turns - 5))) return false;
     return n <= 10 || rounds == 1 || rounds > 3 || last >= (rounds == 2 ? 120 * (turns - 5) : f32 ? 70 * (turns - 7) : 110 * (turns - 5));
 }
 bool long_filter_on_load(const fftconv_plan *p, int64_t Nk)

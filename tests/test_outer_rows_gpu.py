@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     (3, 11, 8191, 8191, 32768), (2, 9, 8192, 1, 32768), (2, 30, 8193, 8193, 32768),      # one block, two
     (2, 22, 32767, 32767, 32768), (1, 43, 16385, 100, 32768), (1, 42, 16385, 16384, 32768),    # 129 and 126 blocks: either side of the line
     (2, 13, 24577, 24577, 65536), (1, 26, 65536, 40000, 65536), (1, 3, 32768, 32768, 65536),   # of half a transform and of a whole one
-    (5, 3, 65535, 65535, 131072), (1, 3, 65536, 65536, 131072),                          # 135 blocks, 27
+    (5, 3, 65535, 65535, 131072), (5, 4, 65535, 65535, 131072), (1, 3, 65536, 65536, 131072),      # 135 blocks, 180, 27
     (1, 3, 131071, 131071, 131072), (2, 8, 81919, 8193, 131072),                         # sixteen blocks to a row, ten
     (1, 57, 100, 131072, 131072), (1, 97, 100, 131072, 131072),                          # filters in a second round of few workgroups, and of many
     (2, 29, 106501, 100, 131072), (1, 20, 122882, 100, 131072), (3, 1, 57345, 100, 65536),     # rows in a second round of few; too few rows

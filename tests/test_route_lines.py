@@ -15,14 +15,16 @@ def rule(name, *types):
 
 
 @pytest.mark.parametrize("A,blocks,dtype,on_load,from_memory", [
-    (16, 16, "16 bits", (15, 20, 40, 56, 97, 113, 160, 171, 256), (1, 14, 57, 64, 72, 85, 114, 128, 142)),
+    (16, 16, "16 bits", (35, 40, 56, 97, 113, 160, 171, 256), (1, 15, 24, 32, 57, 64, 72, 85, 114, 128, 142)),
     (16, 16, "f32", (15, 20, 56, 97, 113, 122, 128, 160, 171, 256), (1, 14, 57, 64, 72, 85, 92, 117)),
-    (16, 12, "16 bits", (15, 56, 72, 113, 128, 256), (14, 57, 62)),
+    (16, 12, "16 bits", (21, 56, 72, 113, 128, 256), (14, 20, 57, 62)),
     (16, 12, "f32", (15, 56, 72, 114, 256), (14, 57, 62)),
     (16, 14, "f32", (15, 56, 97, 114, 256), (14, 57, 72)),
     (16, 10, "16 bits", (15, 57, 114, 256), (14,)),
-    (8, 8, "16 bits", (8, 16, 256), (1, 7)),
-    (8, 8, "f32", (11, 16, 256), (1, 7, 8, 9)),              # (8 channels 12.9 -> 13.3 us)
+    (8, 8, "16 bits", (22, 256), (1, 8, 16)),
+    (16, 8, "16 bits", (12, 57, 256), (1, 11)),
+    (8, 6, "16 bits", (8, 256), (1, 7)),
+    (8, 8, "f32", (20, 256), (1, 8, 16)),              # (8 channels 12.9 -> 13.3 us)
     (16, 8, "f32", (6, 57, 256), (1, 4)),
     (8, 6, "f32", (8, 57, 256), (1, 7)),
     (4, 4, "f32", (1, 768), ()),
@@ -35,13 +37,14 @@ def test_filters_formed_on_load(A, blocks, dtype, on_load, from_memory):
 
 
 @pytest.mark.parametrize("A,blocks,gated,on_load,from_memory", [
-    (8, 8, False, ((1, 6), (6, 1), (1, 256)), ((1, 1), (3, 1), (1, 5))),             # (B, H); a row 16.9 -> 17.9 us
+    (8, 8, False, ((1, 12), (12, 1), (1, 256)), ((1, 1), (3, 1), (1, 11))),             # (B, H); a row 16.9 -> 17.9 us
     (8, 6, False, ((1, 1), (2, 256)), ()),
     (16, 8, False, ((1, 2), (2, 1), (4, 256)), ((1, 1),)),
     (4, 4, True, ((1, 12), (12, 1)), ((1, 1), (4, 2))),
     (4, 4, False, ((1, 1), (2, 300)), ()),
     (16, 4, True, ((1, 1), (2, 300)), ()),
-    (8, 8, True, ((1, 26), (26, 1)), ((1, 25),)),
+    (8, 8, True, ((1, 36), (36, 1)), ((1, 35),)),
+    (8, 6, True, ((1, 26), (26, 1)), ((1, 25),)),
     (16, 8, True, ((1, 56), (1, 64), (2, 29), (3, 19)), ((1, 14), (1, 57))),
     (16, 16, True, (), ((1, 256), (4, 256))),
     (16, 16, False, ((1, 16), (1, 24), (2, 15), (2, 28), (2, 32), (3, 20), (4, 16), (1, 90), (1, 114), (1, 200), (1, 256), (2, 57), (3, 57)),
@@ -91,6 +94,6 @@ def test_rows_of_four_passes():
 def test_gradients_formed_on_load():
     """Calls whose kernel forms its rows itself; with as many batch rows as 32 bits count, the last run's end would not fit."""
     f = rule("_ZN7fftconv12grad_on_loadEllll", i64, i64, i64, i64)
-    on_load = [(8, 8, 26, 1), (8, 8, 1, 26), (16, 8, 15, 1), (16, 2, 1, 1), (4, 1, 1, 1), (4, 4, 43, 1), (16, 1, (1 << 31) - 514, 1)]
-    from_memory = [(8, 8, 25, 1), (16, 8, 14, 1), (4, 4, 42, 1), (16, 9, 300, 300), (32, 1, 8, 8), (2, 1, 8, 8), (16, 1, (1 << 31) - 513, 1), (16, 1, 1 << 33, 1)]
+    on_load = [(8, 6, 26, 1), (8, 8, 36, 1), (8, 8, 1, 36), (16, 8, 20, 1), (16, 2, 1, 1), (4, 1, 1, 1), (4, 4, 43, 1), (16, 1, (1 << 31) - 514, 1)]
+    from_memory = [(8, 6, 25, 1), (8, 8, 35, 1), (16, 8, 19, 1), (4, 4, 42, 1), (16, 9, 300, 300), (32, 1, 8, 8), (2, 1, 8, 8), (16, 1, (1 << 31) - 513, 1), (16, 1, 1 << 33, 1)]
     assert [c for c in on_load + from_memory if f(*c)] == on_load
