@@ -176,6 +176,10 @@ int long_filter_transform_f32(const fftconv_plan *p, const float *k, int64_t Nk,
                           const uint8_t *keep_dev, int64_t n_blocks, float2 *tmp, void *kf, hipStream_t s);
 // the same of all channels from the taps alone, without scratch
 bool long_filter_on_load(const fftconv_plan *p, int64_t Nk);
+// lines to the kernels that form the rows of the outer factor on load, for rows or taps of n blocks of 8192 at outer length A
+bool filter_on_load(int64_t A, int64_t n, int64_t H, bool f32);
+bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated);
+bool grad_on_load(int64_t A, int64_t n, int64_t B, int64_t H);
 int long_filter_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool adjoint, const uint8_t *keep_dev, int64_t n_blocks, void *kf,
                      KfTag tag, hipStream_t s);
 FacList long_fft_factor_list(int64_t M);

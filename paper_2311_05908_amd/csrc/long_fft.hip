@@ -934,10 +934,14 @@ int launch_kf_taps(const fftconv_plan *p, const float *k, int64_t Nk, bool conj_
 // fast, 2 x 29 53 -> 55, 2 x 32 59 -> 58, 4 x 15 55.5 -> 57; odd batches, whose last row has no partner, gain all the same (3 x 20 1.29 times), and so do more
 // rounds but for one batch row of more than 14 blocks (1 x 114 1.08 times, 1 x 190 145 -> 149, 1 x 200 159 -> 152, 1 x 228 176 -> 178, 1 x 256 196 -> 190), and in the
 // first round 17 to 23 channels of it (16 30.3 -> 28.0, 20 31.5 -> 32.5, 24 1.02 times).
+// An odd batch whose last row can go with the pairs does, where the filter takes an outer pass: on load it would be less accurate (3 x 3 x 65536 at fft 131072
+// 3.35e-7 -> 3.40e-7, though 3 x 2 19.7 us instead of 27.2; with the filter on load, too, it is more accurate: 3 x 6 3.35e-7 -> 3.14e-7, 36.9 -> 24.8 us).
+bool lone_in_pairs(int64_t A, int64_t B, int64_t H) { return B > 1 && A == 16 && (B + 1) / 2 * H * 16 <= 1024; }
 }  // namespace
 bool conv_on_load(int64_t A, int64_t n, int64_t B, int64_t H, bool gated)
 {
     if (!outer_on_load(A) || (gated && n > 8)) return false;
+    if (A == 16 && B > 1 && B % 2 == 1 && lone_in_pairs(A, B, H) && !filter_on_load(A, n, H, true)) return false;
     const int64_t blocks = B * H * (A / 2 + 1);
     if (n <= 3 || (n <= 6 && !gated)) return true;
     if (n == 4) return A != 4 || blocks >= 36;
@@ -960,7 +964,6 @@ bool conv_real(const fftconv_plan *p, int64_t B, bool gated)
 {
     return multipass_filter_outer_ok(p) && (p->M / LB != 16 || conv_on_load(p, B, gated));
 }
-bool lone_in_pairs(const fftconv_plan *p, int64_t B) { return B > 1 && p->M / LB == 16 && (B + 1) / 2 * p->H * 16 <= 1024; }
 int64_t real_row(const fftconv_plan *p) { return (p->M / LB / 2 + 1) * LB; }
 
 // pairs of fp32 values in the workspace of a trip: 512 MiB, or a row where that is more.  us with 64, 128, 256, 512 MiB: 4 x 8 x 2^20 fft
@@ -1043,7 +1046,7 @@ int long_forward_t(const fftconv_plan *p, const IO *u, const float2 *kf, IO *y, 
         });
     };
     if (conv_real(p, B, wg != nullptr)) return as_real(0, B * H);
-    if (lone_in_pairs(p, B)) return as_complex(0, (B + 1) / 2 * H, true);
+    if (lone_in_pairs(M / LB, B, H)) return as_complex(0, (B + 1) / 2 * H, true);
     if (B > 1) FC_TRY(as_complex(0, B / 2 * H, true));
     if (B % 2 == 0) return FFTCONV_OK;
     return multipass_filter_outer_ok(p) ? as_real((B - 1) * H, H) : as_complex(B - 1, H, false);

@@ -39,7 +39,10 @@ def test_filters_formed_on_load(A, blocks, dtype, on_load, from_memory):
 @pytest.mark.parametrize("A,blocks,gated,on_load,from_memory", [
     (8, 8, False, ((1, 12), (12, 1), (1, 256)), ((1, 1), (3, 1), (1, 11))),             # (B, H); a row 16.9 -> 17.9 us
     (8, 6, False, ((1, 1), (2, 256)), ()),
-    (16, 8, False, ((1, 2), (2, 1), (4, 256)), ((1, 1),)),
+    (16, 8, False, ((1, 2), (2, 1), (4, 256), (4, 3), (3, 6), (27, 5)), ((1, 1), (3, 1), (3, 5), (5, 3), (23, 5))),      # (odd batches: 3.35e-7 of error, on load 3.40e-7)
+    (16, 6, False, ((3, 5), (2, 4)), ((3, 4),)),
+    (16, 6, True, ((5, 5), (8, 2)), ((5, 3), (9, 2))),
+    (16, 4, False, ((3, 1), (5, 5)), ()),
     (4, 4, True, ((1, 12), (12, 1)), ((1, 1), (4, 2))),
     (4, 4, False, ((1, 1), (2, 300)), ()),
     (16, 4, True, ((1, 1), (2, 300)), ()),
