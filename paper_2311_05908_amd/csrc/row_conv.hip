@@ -380,25 +380,17 @@ int launch(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_
 template <int M> constexpr int64_t wide_most(bool gated) { return !gated ? 3072 : M == 512 ? 6144 : INT64_MAX; }
 template <int M> constexpr int64_t FEW_WIDE = M == 512 ? 3072 : 1024;
 
-// The same of four passes, in pieces alike
+// The same of four passes; row_quad() holds what one launch does
 template <int M, typename IO>
 int launch_quad(const fftconv_plan *p, const void *u, const void *kf, void *y, int64_t B, hipStream_t s)
 {
     using Q = rf::Quad<M>;
-    const bool half = p->N <= M / 2;
-    const auto kern = half ? k_row_conv_quad<M, IO, true> : k_row_conv_quad<M, IO, false>;
+    const auto kern = p->N <= M / 2 ? k_row_conv_quad<M, IO, true> : k_row_conv_quad<M, IO, false>;
     FC_TRY(raise_dynamic_lds((const void *)kern, Q::LDS_BYTES));
-    constexpr int64_t MOST = ((int64_t)1 << 31) / Q::T;
-    const int64_t H = p->H, N = p->N, npairs = (B + 1) / 2;
-    for (int64_t p0 = 0; p0 < npairs; p0 += MOST) {
-        const int64_t np = npairs - p0 < MOST ? npairs - p0 : MOST, nb = B - 2 * p0 < 2 * np ? B - 2 * p0 : 2 * np, nh = MOST / np;
-        for (int64_t h0 = 0; h0 < H; h0 += nh) {
-            const int64_t hs = H - h0 < nh ? H - h0 : nh, total = hs * np, per_die = (total + 7) / 8, at = (2 * p0 * H + h0) * N;
-            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_die)), dim3(Q::T), Q::LDS_BYTES, s, (const IO *)u + at, (IO *)y + at,
-                               (const float2 *)kf + h0 * M, rf::quad_table<M>(p), (int)nb, (int)H, (int)N, (int)np, (int)total, (int)per_die);
-            FC_HIP(hipGetLastError());
-        }
-    }
+    const int64_t npairs = (B + 1) / 2, total = p->H * npairs, per_die = (total + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_die)), dim3(Q::T), Q::LDS_BYTES, s, (const IO *)u, (IO *)y, (const float2 *)kf,
+                       rf::quad_table<M>(p), (int)B, (int)p->H, (int)p->N, (int)npairs, (int)total, (int)per_die);
+    FC_HIP(hipGetLastError());
     return FFTCONV_OK;
 }
 
@@ -421,11 +413,13 @@ int launch_row(const fftconv_plan *p, const void *u, const void *kf, void *y, in
 
 }  // namespace
 
-// Calls without gates whose rows take four passes: while the pairs have a compute unit each, or, where rows are full, two of them one, and fp32 rows of 2048
+// Calls without gates whose rows take four passes (a launch holds 2^23 pairs): while the pairs have a compute unit each, or, where rows are full, two of them one, and fp32 rows of 2048
 // points at nearly any number.  us, three passes, four: fp32 causal fft 2048, 4 pairs 6.6, 4.5 (the kernels alone, traced), 256 6.7, 6.1, 768 8.6, 7.7,
 // 2048 17.1, 15.2, 16384 107, 103, circular 1024 12.8, 10.6; bf16 circular 256 6.9, 6.5, 512 7.2, 6.9, 768 8.7, 8.7, 1024 9.0, 10.0, 500 samples 257 to 512 pairs
 // 6.15, 6.3; fft 4096 fp32
-// 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7.
+// 4 6.6, 5.9 and 256 7.6, 6.9 (traced), 300 8.5, 8.9, 384 8.8, 9.2, bf16 circular 256 7.4, 7.2, 300 9.2, 9.9.  Errors of fp32: fft 2048 1.42e-7 -> 1.34e-7, 4096 1.58e-7 -> 1.38e-7;
+// rows so short that the first pass of three, of 16 points, has a sample or two to add up are more accurate there (fft 2048, 8 samples 5.6e-8, 6.6e-8 in four, 128 7.95e-8, 8.28e-8,
+// 150 8.47e-8, 8.37e-8, 200 9.5e-8, 8.7e-8; 4096, 16 6.2e-8, 6.8e-8, 20 6.8e-8, 6.8e-8, 64 8.9e-8, 7.2e-8).
 // fp32 rows of 2048 points that are more than half full, once u and y exceed the memory-side cache: three passes are faster (8 x 1024 x 2048 128 MB 1.20 times as
 // fast in four, 16 x 768 192 MB 1.15, 16 x 1024 256 MB 0.98, 64 x 768 384 MB 0.96, 64 x 768 x 1500 562 MB 0.92); half-empty rows are no slower in four there
 // (64 x 1500 x 1024 750 MB 1.01, 256 x 2048 x 256 1 GB 1.03).
@@ -438,7 +432,7 @@ bool row_quad(int64_t M, bool f32, int64_t N, int64_t H, int64_t B)
 {
     const int64_t npairs = (B + 1) / 2;
     const bool half = N <= M / 2;
-    if (npairs > INT32_MAX / H) return M == 2048 && f32 && half;
+    if (npairs > (1 << 23) / H || (f32 && N < (M == 2048 ? 150 : 20))) return false;
     const int64_t pairs = H * npairs;
     if (M == 4096) return pairs <= 256;
     if (!f32) return pairs <= (half ? 256 : 512);

@@ -82,16 +82,18 @@ def test_rows_of_a_single_batch_row():
 
 
 def test_rows_of_four_passes():
-    """(N, H, B) of calls without gates in rows of four passes, and of those in three (fp32 2 x 1024 x 100 at fft 2048 7.6 us so, 7.9 in four)."""
+    """(N, H, B) of calls without gates in rows of four passes, and of those in three (fp32 2 x 1024 x 200 at fft 2048 7.7 us so, 8.0 in four)."""
     f = rule("_ZN7fftconv8row_quadElblll", i64, flag, i64, i64, i64)
-    four = [(1024, 4, 2), (100, 768, 2), (1024, 1025, 1), (100, 640, 4), (100, 800, 4), (300, 1024, 4), (100, 2049, 2), (1024, 8192, 2), (1025, 900, 2), (2048, 768, 16),
-            (1, 1, 1 << 32), (1024, 1500, 64), (2048, 1, 1)]
-    three = [(100, 769, 1), (1024, 1024, 2), (100, 512, 4), (256, 1793, 2), (100, 1024, 4), (256, 2048, 1),
-             (2048, 1024, 16), (2047, 2048, 8), (1500, 768, 64), (1025, 1500, 32), (2048, 3, 1 << 31)]      # (64 x 768 x 1500 188 us, 204 in four)
+    four = [(1024, 4, 2), (200, 768, 2), (1024, 1025, 1), (200, 640, 4), (200, 800, 4), (300, 1024, 4), (200, 2049, 2), (1024, 8192, 2), (1025, 900, 2), (2048, 768, 16),
+            (1024, 1500, 64), (2048, 1, 1), (150, 1, 1), (150, 1, 1 << 24)]
+    three = [(200, 769, 1), (1024, 1024, 2), (200, 512, 4), (256, 1793, 2), (200, 1024, 4), (256, 2048, 1),
+             (2048, 1024, 16), (2047, 2048, 8), (1500, 768, 64), (1025, 1500, 32), (2048, 3, 1 << 31),      # (64 x 768 x 1500 188 us, 204 in four)
+             (149, 1, 1), (8, 4, 2), (150, 1, (1 << 24) + 1), (1024, 3, 1 << 32)]                             # (8 samples: 5.6e-8 of error, 6.6e-8 in four)
     assert [c for c in four + three if f(2048, True, *c)] == four
     for M, f32, N, most in ((2048, False, 2048, 512), (2048, False, 1025, 512), (2048, False, 1024, 256), (2048, False, 100, 256),
-                            (4096, True, 100, 256), (4096, True, 4096, 256), (4096, False, 100, 256), (4096, False, 4096, 256)):
+                            (4096, True, 20, 256), (4096, True, 4096, 256), (4096, False, 1, 256), (4096, False, 4096, 256)):
         assert f(M, f32, N, most, 2) and not f(M, f32, N, most + 1, 2) and not f(M, f32, N, 1, 1 << 33)
+    assert not f(4096, True, 19, 1, 1)
 
 
 def test_gradients_formed_on_load():

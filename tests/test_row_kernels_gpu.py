@@ -437,7 +437,8 @@ def test_calls_of_one_batch_row(dtype, H, N, M):
 
 @pytest.mark.parametrize("dtype,B,H,N,M", [
     ("f32", 1, 1, 1, 2048), ("f32", 3, 5, 1023, 2048), ("f32", 2, 9, 1024, 2048), ("f32", 2, 7, 1025, 2048), ("f32", 4, 700, 2048, 2048),
-    ("bf16", 2, 256, 777, 2048), ("f16", 2, 257, 777, 2048), ("f32", 2, 768, 100, 2048), ("f32", 2, 769, 100, 2048), ("f32", 3, 512, 1024, 2048), ("f32", 2, 1025, 64, 2048), ("f32", 2, 1793, 30, 2048), ("f32", 2, 2049, 30, 2048),
+    ("bf16", 2, 256, 777, 2048), ("f16", 2, 257, 777, 2048), ("f32", 2, 768, 150, 2048), ("f32", 2, 768, 149, 2048), ("f32", 2, 769, 200, 2048), ("f32", 3, 512, 1024, 2048), ("f32", 2, 1025, 164, 2048), ("f32", 2, 1793, 160, 2048), ("f32", 2, 2049, 160, 2048),
+    ("f32", 3, 5, 19, 4096), ("f32", 3, 5, 20, 4096),
     ("bf16", 3, 5, 2047, 2048), ("f16", 2, 512, 1100, 2048), ("f16", 2, 513, 1100, 2048),          # pairs on either side of the line
     ("f32", 3, 5, 2047, 4096), ("f32", 2, 256, 2048, 4096), ("f32", 2, 257, 2048, 4096), ("bf16", 2, 3, 4095, 4096), ("f16", 5, 20, 4096, 4096),
 ])
@@ -453,34 +454,32 @@ def test_rows_of_four_passes(dtype, B, H, N, M):
     assert err <= TOL[dtype]
 
 
-def test_rows_of_four_passes_in_pieces():
-    """More pairs of rows than a launch holds: 2^23 and two of one sample each, the last row without a partner."""
-    u = torch.randn((2 << 23) + 3, 1, 1, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+def test_fp32_rows_in_pieces():
+    """More pairs of rows than a launch holds: 2^24 and two of one sample each, the last row without a partner."""
+    u = torch.randn((2 << 24) + 3, 1, 1, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
     k = torch.randn(1, 1, device="cuda")
     plan = fftconv.Plan(1, 2048, 1, "f32", path="small")
     y = plan.forward(u, plan.filter_fft(k), out=torch.full_like(u, float("nan")))
     assert (y - u * k).abs().max().item() <= TOL["f32"] * u.abs().max().item() * k.abs().item()
 
 
-def test_a_gradient_of_a_few_rows_more_than_compute_units():
-    """bf16, fft 4096, odd rows of one batch row: 300 channels, a second workgroup on some compute units, beside 256 (12.9 us and 10.6 when the first pass
-    left out mirror images, 11.4 and 10.6 without)."""
-    N = 4095
-    best = {256: float("inf"), 300: float("inf")}
-    data = {H: [torch.randn(1, H, N, device="cuda").bfloat16() for _ in range(2)] + [torch.empty(H, N, device="cuda")] for H in best}
-    plans = {H: fftconv.Plan(N, 4096, H, "bf16") for H in best}
-    for _ in range(10):
-        for H, (u, dy, dk) in data.items():
-            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            plans[H].backward_filter(u, dy, N, out=dk)
-            t[0].record()
-            for _ in range(100):
-                plans[H].backward_filter(u, dy, N, out=dk)
-            t[1].record()
-            t[1].synchronize()
-            best[H] = min(best[H], t[0].elapsed_time(t[1]) * 10)
-    print("dk of 1 x 256, 300 x 4095: %.1f, %.1f us" % (best[256], best[300]), flush=True)
-    assert best[300] <= 1.15 * best[256]
+@pytest.mark.parametrize("M,N", [(2048, 8), (2048, 100), (2048, 140), (2048, 150), (4096, 16), (4096, 24)])
+def test_short_fp32_rows_are_as_accurate_as_three_passes_make_them(M, N):
+    """Errors of rows of few samples, whose first pass of 16 points adds up next to nothing (5.6e-8, 7.6e-8, 8.2e-8, 8.5e-8, 6.2e-8, 7.5e-8); four passes
+    came out at 6.6e-8 with 8 samples, 7.9e-8 with 100 and 6.8e-8 with 16.  Two percent beside them for other seeds."""
+    e = []
+    for seed in range(6):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        k = torch.randn(160, N, generator=g, device="cuda")
+        k = k * torch.exp(-(4.0 / N) * 100 ** torch.rand(160, 1, generator=g, device="cuda") * torch.arange(N, device="cuda"))
+        u = torch.randn(2, 160, N, generator=g, device="cuda")
+        plan = fftconv.Plan(N, M, 160, "f32")
+        ref = torch.fft.irfft(torch.fft.rfft(u.double(), M) * torch.fft.rfft(k.double(), M), M)[..., :N]
+        e.append(((plan.forward(u, plan.filter_fft(k)).double() - ref).norm() / ref.norm()).item())
+    error = sum(e) / len(e)
+    print("fp32 rows of %d samples, fft %d: %.3e" % (N, M, error), flush=True)
+    assert error <= 1.02 * {(2048, 8): 5.60e-8, (2048, 100): 7.66e-8, (2048, 140): 8.20e-8, (2048, 150): 8.47e-8, (4096, 16): 6.20e-8, (4096, 24): 7.48e-8}[M, N]
+
 
 
 def test_fp32_rows_beyond_the_memory_side_cache():
